@@ -1,5 +1,5 @@
 // Bi-level KV decoding, the integer / bandwidth-bound steps: per-chunk mean keys, relevance
-// scores + top-k selection (LDS bitonic sort), and the dense/sparse gather into the mixed KV.
+// scores + top-k selection (by rank), and the dense/sparse gather into the mixed KV.
 #include <math.h>
 
 #include <algorithm>
@@ -126,170 +126,148 @@ __global__ __launch_bounds__(256) void chunk_summarize_kernel(const T* __restric
 }
 
 // ------------------------------------------------------------------------------------------
-// One block per query b: mean query per kv head, scores of all chunks, bitonic sort of
-// (score, chunk id) in LDS, top-k ids + dense mask.
+// Relevance score of one chunk, formed by 16 neighbouring lanes: lane p takes the 16-byte pieces
+// p, p + 16, ... of the flattened (kv head, d) range (256 contiguous bytes per step), in that
+// order, and the sixteen partial dot products are added in a fixed tree.  A chunk's score thus
+// depends on nothing but its mean keys, whichever kernel computes it: equal chunks tie exactly.
+// Latency bound (2 KiB per chunk): the pieces of eight steps of both operands are requested
+// before the first multiply-add.  Every lane of the group returns the score.
 // ------------------------------------------------------------------------------------------
-__device__ __forceinline__ bool ranks_before(float sa, int ia, float sb, int ib) {
-    return sa > sb || (sa == sb && ia < ib);     // score descending, ties to the lower chunk id
-}
-
-// Bitonic sort of (score, chunk id) in LDS, best first (s_val / s_idx hold n_sort entries, a power
-// of two, padding = (-inf, INT_MAX)), then the ids of the k best and the membership mask of query b.
-// Called by all 256 threads of the block after a barrier.
-__device__ __forceinline__ void sort_select(float* s_val, int* s_idx, int n_sort, int n_chunks, int k, int b,
-                                            int32_t* __restrict__ topk_idx, uint8_t* __restrict__ dense_mask) {
-    const int tid = threadIdx.x;
-    if (n_sort <= 1024) {
-        // Up to 1024 chunks: every thread ranks its chunks (tid, tid + 256, ...) by counting the
-        // chunks that come before them in the order (score descending, id ascending) -- a total
-        // order, so the ranks are a permutation -- instead of the barrier-per-step sort below
-        // (n^2 / 256 comparisons per thread: 4 us at 640 chunks, where the 55 barrier steps of
-        // the sort took 25).
-        for (int c = tid; c < n_chunks; c += 256) {
-            const float sc = s_val[c];
-            int rank = 0;
-            for (int o = 0; o < n_chunks; ++o) rank += ranks_before(s_val[o], o, sc, c) ? 1 : 0;
-            if (rank < k) topk_idx[(size_t)b * k + rank] = c;
-            dense_mask[(size_t)b * n_chunks + c] = (uint8_t)(rank < k ? 1 : 0);
-        }
-        return;
-    }
-    // bitonic sort, best first
-    for (int size = 2; size <= n_sort; size <<= 1) {
-        for (int stride = size >> 1; stride > 0; stride >>= 1) {
-            for (int i = tid; i < n_sort / 2; i += 256) {
-                const int lo = 2 * i - (i & (stride - 1));
-                const int hi = lo + stride;
-                const bool up = ((lo & size) == 0);
-                const float va = s_val[lo], vb = s_val[hi];
-                const int ia = s_idx[lo], ib = s_idx[hi];
-                const bool a_first = ranks_before(va, ia, vb, ib);
-                if (a_first != up) { s_val[lo] = vb; s_val[hi] = va; s_idx[lo] = ib; s_idx[hi] = ia; }
-            }
-            __syncthreads();
-        }
-    }
-    // membership flags in LDS (the sorted scores are no longer needed), then one coalesced
-    // write of the mask
-    int* flag = (int*)s_val;
-    for (int c = tid; c < n_sort; c += 256) flag[c] = 0;
-    __syncthreads();
-    for (int i = tid; i < k; i += 256) {
-        const int c = s_idx[i];
-        topk_idx[(size_t)b * k + i] = c;
-        if (c < n_chunks) flag[c] = 1;       // (a NaN score could surface a padding slot)
-    }
-    __syncthreads();
-    for (int c = tid; c < n_chunks; c += 256) dense_mask[(size_t)b * n_chunks + c] = (uint8_t)flag[c];
-}
-
-// The scores alone, 32 chunks per block (grid: chunk groups x queries): the same lanes, slices and
-// add tree as score_topk_kernel, so a chunk's score does not depend on which of the two computed it.
-template <int D>
-__global__ __launch_bounds__(256) void chunk_score_kernel(const float* __restrict__ qbar_g,
-                                                          const float* __restrict__ kbar, int n_kv_heads,
-                                                          int n_chunks, float scale, float* __restrict__ scores) {
-    extern __shared__ unsigned char smem[];
-    float* qbar = (float*)smem;                               // [Hkv][D]
-    const int b = blockIdx.y, tid = threadIdx.x;
-    for (int e = tid; e < n_kv_heads * D; e += 256) qbar[e] = qbar_g[(size_t)b * n_kv_heads * D + e];
-    __syncthreads();
-    const int part = tid & 7, c = blockIdx.x * 32 + (tid >> 3);
-    const int slice = n_kv_heads * D / 8;
-    float a0 = 0.f;
-    if (c < n_chunks) {
-#pragma unroll 8
-        for (int x = 0; x < slice; x += 4) {
-            const int e = part * slice + x, g = e / D, dd = e % D;
-            const float4 kv = *(const float4*)(kbar + ((size_t)g * n_chunks + c) * D + dd);
-            const float* qg = qbar + e;
-            a0 = fmaf(qg[0], kv.x, a0);
-            a0 = fmaf(qg[1], kv.y, a0);
-            a0 = fmaf(qg[2], kv.z, a0);
-            a0 = fmaf(qg[3], kv.w, a0);
-        }
-    }
-    a0 += __shfl_xor(a0, 1);
-    a0 += __shfl_xor(a0, 2);
-    a0 += __shfl_xor(a0, 4);
-    if (part == 0 && c < n_chunks) scores[(size_t)b * n_chunks + c] = a0 * (scale / (float)n_kv_heads);
-}
+constexpr int kScoreLanes = 16;
 
 template <int D>
-__global__ __launch_bounds__(256) void score_topk_kernel(
-    const float* __restrict__ qbar_g, const float* __restrict__ kbar, int n_kv_heads, int n_chunks, int k,
-    int n_sort, float scale, int32_t* __restrict__ topk_idx, uint8_t* __restrict__ dense_mask,
-    float* __restrict__ scores) {
-    extern __shared__ unsigned char smem[];
-    float* qbar = (float*)smem;                               // [Hkv][D]
-    float* s_val = qbar + n_kv_heads * D;                     // [n_sort]
-    int* s_idx = (int*)(s_val + n_sort);                      // [n_sort]
-    const int b = blockIdx.x, tid = threadIdx.x;
-    for (int e = tid; e < n_kv_heads * D; e += 256) qbar[e] = qbar_g[(size_t)b * n_kv_heads * D + e];
+__device__ __forceinline__ float chunk_score(const float* __restrict__ qbar_b, const float* __restrict__ kbar,
+                                             int c, int n_kv_heads, int n_chunks, int p) {
+    constexpr int PPH = D / 4;                                // 16-byte pieces per KV head
+    constexpr int U = 8;
+    const int n_pieces = n_kv_heads * PPH;
+    const float4* q4 = (const float4*)qbar_b;
+    const float4* k4 = (const float4*)kbar + (size_t)c * PPH;
+    const size_t head_skip = (size_t)(n_chunks - 1) * PPH;    // from piece index to its place in kbar[g][c]
+    float a = 0.f;
+    for (int base = p; base < n_pieces; base += U * kScoreLanes) {
+        float4 kv[U], qv[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int e = min(base + u * kScoreLanes, n_pieces - 1);     // (clamped pieces are not added)
+            kv[u] = k4[e + (e / PPH) * head_skip];
+            qv[u] = q4[e];
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const bool in = base + u * kScoreLanes < n_pieces;
+            const float t = fmaf(qv[u].w, kv[u].w, fmaf(qv[u].z, kv[u].z, fmaf(qv[u].y, kv[u].y, fmaf(qv[u].x, kv[u].x, a))));
+            a = in ? t : a;
+        }
+    }
+#pragma unroll
+    for (int o = 1; o < kScoreLanes; o <<= 1) a += __shfl_xor(a, o);
+    return a;
+}
+
+// ------------------------------------------------------------------------------------------
+// Selection by rank: chunk c's place in the order (score descending, ties to the lower chunk id)
+// is the number of chunks before it.  Score and id are packed into one 64-bit key -- the score's
+// bits mapped so that unsigned order is float order (-0 counts as 0), the id complemented -- so
+// the order is total and one comparison decides; the ranks are a permutation whatever the scores
+// hold.  C^2 comparisons, but spread over many waves with no barrier between them: a wave ranks 64
+// chunks (one per lane) against its slice of the keys, read from LDS two at a time by broadcast.
+// One block counting for all chunks took 50 us at 640 chunks and 8.3 at 256; 64 chunks per block
+// with the keys cut over eight waves: 4.8 and 4.6, most of it the launch.
+// ------------------------------------------------------------------------------------------
+__device__ __forceinline__ unsigned long long rank_key(float s, int c) {
+    uint32_t u = __float_as_uint(s + 0.f);
+    u = (u & 0x80000000u) ? ~u : (u | 0x80000000u);
+    return ((unsigned long long)u << 32) | (uint32_t)~c;
+}
+
+// Keys of the slice [lo, hi) (both even) of `keys` (LDS) that come before `mine`.
+__device__ __forceinline__ int count_before(const unsigned long long* keys, int lo, int hi, unsigned long long mine) {
+    int n = 0;
+#pragma unroll 4
+    for (int o = lo; o < hi; o += 2) {
+        const ulonglong2 k2 = *(const ulonglong2*)(keys + o);
+        n += (k2.x > mine ? 1 : 0) + (k2.y > mine ? 1 : 0);
+    }
+    return n;
+}
+
+// Called by a whole block of WAVES waves: ranks the chunks [64 * group0, 64 * (group0 + GROUPS)) of
+// the n_chunks whose keys lie in LDS (padded to an even count with 0, which precedes nothing) and
+// writes their places in topk_idx / dense_mask of query b.  The WAVES / GROUPS waves of a group of
+// 64 chunks share the keys; `part` holds WAVES * 64 ints.
+template <int WAVES, int GROUPS>
+__device__ __forceinline__ void rank_select(const unsigned long long* keys, int* part, int n_chunks, int group0, int k,
+                                            int b, int32_t* __restrict__ topk_idx, uint8_t* __restrict__ dense_mask) {
+    constexpr int SL = WAVES / GROUPS;                        // slices of the keys
+    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    const int grp = wave % GROUPS, sl = wave / GROUPS;
+    const int c = (group0 + grp) * 64 + lane;
+    const int n2 = (n_chunks + 1) & ~1;
+    const int len = ((n2 / 2 + SL - 1) / SL) * 2;
+    const unsigned long long mine = keys[min(c, n_chunks - 1)];
+    part[(sl * GROUPS + grp) * 64 + lane] = count_before(keys, min(sl * len, n2), min((sl + 1) * len, n2), mine);
     __syncthreads();
-    // Scores: 8 consecutive lanes share a chunk; lane `part` takes the part-th eighth of the
-    // flattened (kv head, d) index range, and the eight partial dot products are added in a fixed
-    // tree.  Every thread works on two chunks at a time so that their loads overlap.
-    {
-        const int part = tid & 7, cl = tid >> 3;              // 32 chunk slots per pass and half
-        const int slice = n_kv_heads * D / 8;                 // elements per part (a multiple of 4)
-        for (int base = 0; base < n_sort; base += 64) {
-            float pg[2] = {0.f, 0.f};
+    if (sl == 0 && c < n_chunks) {
+        int rank = 0;
 #pragma unroll
-            for (int u = 0; u < 2; ++u) {
-                const int c = base + u * 32 + cl;
-                if (c < n_chunks) {
-                    float a0 = 0.f;
-#pragma unroll 8
-                    for (int x = 0; x < slice; x += 4) {
-                        const int e = part * slice + x, g = e / D, dd = e % D;
-                        const float4 kv = *(const float4*)(kbar + ((size_t)g * n_chunks + c) * D + dd);
-                        const float* qg = qbar + e;
-                        a0 = fmaf(qg[0], kv.x, a0);
-                        a0 = fmaf(qg[1], kv.y, a0);
-                        a0 = fmaf(qg[2], kv.z, a0);
-                        a0 = fmaf(qg[3], kv.w, a0);
-                    }
-                    pg[u] = a0;
-                }
-            }
+        for (int i = 0; i < SL; ++i) rank += part[(i * GROUPS + grp) * 64 + lane];
+        if (rank < k) topk_idx[(size_t)b * k + rank] = c;
+        dense_mask[(size_t)b * n_chunks + c] = (uint8_t)(rank < k ? 1 : 0);
+    }
+}
+
+// The scores alone, 16 chunks per block (grid: chunk groups x queries).
+template <int D>
+__global__ __launch_bounds__(256) void chunk_score_kernel(const float* __restrict__ qbar, const float* __restrict__ kbar,
+                                                          int n_kv_heads, int n_chunks, float scale,
+                                                          float* __restrict__ scores) {
+    const int b = blockIdx.y, p = threadIdx.x % kScoreLanes;
+    const int c = blockIdx.x * (256 / kScoreLanes) + threadIdx.x / kScoreLanes;
+    const float a = chunk_score<D>(qbar + (size_t)b * n_kv_heads * D, kbar, min(c, n_chunks - 1), n_kv_heads, n_chunks, p);
+    if (p == 0 && c < n_chunks) scores[(size_t)b * n_chunks + c] = a * (scale / (float)n_kv_heads);
+}
+
+// Scores and selection of up to kFusedChunks chunks in one block per query: a launch less, at the
+// price of one compute unit reading all mean keys of a query (2 KiB per chunk at four KV heads):
+// 4.1 us at 64 chunks (9.6 with 256 threads and one load at a time), against 4.7 for each of the
+// two launches of the separate form.
+constexpr int kFusedChunks = 128;
+
+template <int D>
+__global__ __launch_bounds__(1024) void score_topk_kernel(
+    const float* __restrict__ qbar, const float* __restrict__ kbar, int n_kv_heads, int n_chunks, int k, float scale,
+    int32_t* __restrict__ topk_idx, uint8_t* __restrict__ dense_mask, float* __restrict__ scores) {
+    __shared__ __attribute__((aligned(16))) unsigned long long keys[kFusedChunks];
+    __shared__ int part[1024];
+    const int b = blockIdx.x, tid = threadIdx.x, p = tid % kScoreLanes;
 #pragma unroll
-            for (int u = 0; u < 2; ++u) {
-                float a0 = pg[u];
-                a0 += __shfl_xor(a0, 1);
-                a0 += __shfl_xor(a0, 2);
-                a0 += __shfl_xor(a0, 4);
-                const int c = base + u * 32 + cl;
-                if (part == 0 && c < n_sort) {
-                    float a = -INFINITY;
-                    if (c < n_chunks) {
-                        a = a0 * (scale / (float)n_kv_heads);
-                        if (scores) scores[(size_t)b * n_chunks + c] = a;
-                    }
-                    s_val[c] = a;
-                    s_idx[c] = c < n_chunks ? c : 0x7fffffff;
-                }
-            }
+    for (int base = 0; base < kFusedChunks; base += 1024 / kScoreLanes) {
+        const int c = base + tid / kScoreLanes;
+        if (base >= n_chunks) break;                          // (uniform)
+        const float a = chunk_score<D>(qbar + (size_t)b * n_kv_heads * D, kbar, min(c, n_chunks - 1), n_kv_heads,
+                                       n_chunks, p) * (scale / (float)n_kv_heads);
+        if (p == 0) {
+            if (c < n_chunks && scores) scores[(size_t)b * n_chunks + c] = a;
+            keys[c] = c < n_chunks ? rank_key(a, c) : 0ull;
         }
     }
     __syncthreads();
-    sort_select(s_val, s_idx, n_sort, n_chunks, k, b, topk_idx, dense_mask);
+    rank_select<16, kFusedChunks / 64>(keys, part, n_chunks, 0, k, b, topk_idx, dense_mask);
 }
 
-// Selection alone, from scores some other kernel has written: one block per query.
-__global__ __launch_bounds__(256) void topk_from_scores_kernel(const float* __restrict__ scores, int n_chunks,
-                                                               int k, int n_sort, int32_t* __restrict__ topk_idx,
+// Selection alone, from scores some other kernel has written: 64 chunks per block (grid: chunk
+// groups x queries), every block holding the keys of all chunks (at most 32 KiB).
+__global__ __launch_bounds__(512) void topk_from_scores_kernel(const float* __restrict__ scores, int n_chunks,
+                                                               int k, int32_t* __restrict__ topk_idx,
                                                                uint8_t* __restrict__ dense_mask) {
-    extern __shared__ unsigned char smem[];
-    float* s_val = (float*)smem;                              // [n_sort]
-    int* s_idx = (int*)(s_val + n_sort);                      // [n_sort]
-    const int b = blockIdx.x;
-    for (int c = threadIdx.x; c < n_sort; c += 256) {
-        s_val[c] = c < n_chunks ? scores[(size_t)b * n_chunks + c] : -INFINITY;
-        s_idx[c] = c < n_chunks ? c : 0x7fffffff;
-    }
+    extern __shared__ __attribute__((aligned(16))) unsigned long long keys_dyn[];   // [n_chunks, padded to even]
+    __shared__ int part[512];
+    const int b = blockIdx.y;
+    for (int c = threadIdx.x; c < ((n_chunks + 1) & ~1); c += 512)
+        keys_dyn[c] = c < n_chunks ? rank_key(scores[(size_t)b * n_chunks + c], c) : 0ull;
     __syncthreads();
-    sort_select(s_val, s_idx, n_sort, n_chunks, k, b, topk_idx, dense_mask);
+    rank_select<8, 1>(keys_dyn, part, n_chunks, blockIdx.x, k, b, topk_idx, dense_mask);
 }
 
 // ------------------------------------------------------------------------------------------
@@ -471,42 +449,36 @@ vxl_status launch_summaries(const vxl_layout* L, const vxl_attn_desc* d, const v
 vxl_status launch_score_topk(const vxl_layout* L, const vxl_attn_desc* d, float scale, int batch, int k,
                              const float* qbar, const float* kbar, int32_t* topk_idx, uint8_t* dense_mask,
                              float* scores, float* scores_ws, hipStream_t s) {
-    int n_sort = 2;
-    while (n_sort < L->n_chunks) n_sort <<= 1;
-    // Beyond 128 chunks one block per query is a serial chain (90 us at 640 chunks): the scores are
-    // then formed by 32 chunks per block and the selection reads them back.
-    if (L->n_chunks > 128) {
+    // One block per query reads all its mean keys through one compute unit, so beyond kFusedChunks
+    // chunks the scores are formed by 16 chunks per block and the selection reads them back.
+    if (L->n_chunks > kFusedChunks) {
         float* sc = scores ? scores : scores_ws;
-        const size_t smem_q = (size_t)d->n_kv_heads * d->head_dim * 4;
-        const dim3 grid((L->n_chunks + 31) / 32, batch);
+        const dim3 grid((L->n_chunks + 256 / kScoreLanes - 1) / (256 / kScoreLanes), batch);
         if (d->head_dim == 64)
-            hipLaunchKernelGGL((chunk_score_kernel<64>), grid, dim3(256), smem_q, s, qbar, kbar, d->n_kv_heads,
+            hipLaunchKernelGGL((chunk_score_kernel<64>), grid, dim3(256), 0, s, qbar, kbar, d->n_kv_heads,
                                L->n_chunks, scale, sc);
         else
-            hipLaunchKernelGGL((chunk_score_kernel<128>), grid, dim3(256), smem_q, s, qbar, kbar, d->n_kv_heads,
+            hipLaunchKernelGGL((chunk_score_kernel<128>), grid, dim3(256), 0, s, qbar, kbar, d->n_kv_heads,
                                L->n_chunks, scale, sc);
         VXL_HIP_TRY(hipGetLastError());
         return launch_topk_from_scores(L, sc, batch, k, topk_idx, dense_mask, s);
     }
-    const size_t smem = (size_t)d->n_kv_heads * d->head_dim * 4 + (size_t)n_sort * 8;
-    if (smem > 64 * 1024) return VXL_ERR_UNSUPPORTED;
-    const dim3 grid(batch), block(256);
+    const dim3 grid(batch), block(1024);
     if (d->head_dim == 64)
-        hipLaunchKernelGGL((score_topk_kernel<64>), grid, block, smem, s, qbar, kbar, d->n_kv_heads, L->n_chunks, k,
-                           n_sort, scale, topk_idx, dense_mask, scores);
+        hipLaunchKernelGGL((score_topk_kernel<64>), grid, block, 0, s, qbar, kbar, d->n_kv_heads, L->n_chunks, k,
+                           scale, topk_idx, dense_mask, scores);
     else
-        hipLaunchKernelGGL((score_topk_kernel<128>), grid, block, smem, s, qbar, kbar, d->n_kv_heads, L->n_chunks, k,
-                           n_sort, scale, topk_idx, dense_mask, scores);
+        hipLaunchKernelGGL((score_topk_kernel<128>), grid, block, 0, s, qbar, kbar, d->n_kv_heads, L->n_chunks, k,
+                           scale, topk_idx, dense_mask, scores);
     VXL_HIP_TRY(hipGetLastError());
     return VXL_OK;
 }
 
 vxl_status launch_topk_from_scores(const vxl_layout* L, const float* scores, int batch, int k,
                                    int32_t* topk_idx, uint8_t* dense_mask, hipStream_t s) {
-    int n_sort = 2;
-    while (n_sort < L->n_chunks) n_sort <<= 1;
-    hipLaunchKernelGGL(topk_from_scores_kernel, dim3(batch), dim3(256), (size_t)n_sort * 8, s, scores,
-                       L->n_chunks, k, n_sort, topk_idx, dense_mask);
+    const size_t smem = (size_t)((L->n_chunks + 1) & ~1) * sizeof(unsigned long long);
+    hipLaunchKernelGGL(topk_from_scores_kernel, dim3((L->n_chunks + 63) / 64, batch), dim3(512), smem, s, scores,
+                       L->n_chunks, k, topk_idx, dense_mask);
     VXL_HIP_TRY(hipGetLastError());
     return VXL_OK;
 }

@@ -1,0 +1,34 @@
+"""Scores and selection at the chunk counts where the kernels change form or a block, wave or key pair is only
+partly filled: one launch up to 128 chunks, 16 chunks per score block and 64 per selection block beyond."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from paper_2506_19225_amd import workloads as wl
+
+from gpu_util import full_sort_selection, gpu_score_topk
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("n_chunks", [1, 2, 63, 64, 65, 127, 128, 129, 143, 640, 1025, 4095, 4096])
+def test_selection_is_a_full_sort_of_the_scores(n_chunks):
+    """Every third chunk repeats one of a few contents, so that many scores tie exactly; the scores agree with the
+    oracle to the rounding of 3 x 128 fp32 products (2e-5 of the largest), the selection is the full sort of them."""
+    rng = np.random.default_rng(n_chunks)
+    hkv, d, ln = (3, 128, 2) if n_chunks % 2 else (1, 64, 3)
+    w = wl.tiny_workload("f32", 2 * hkv, hkv, d, T=3, B=2, k=1, seed=n_chunks)
+    lay = wl.layout_from_lists(5, [ln] * n_chunks, [np.zeros(0, np.int32)] * n_chunks)
+    _, k, _ = wl.make_qkv(w, lay, with_q=False)
+    blocks = k[:, 5:].reshape(hkv, n_chunks, ln, d)                        # (a view: k changes)
+    for c in range(0, n_chunks, 3):
+        blocks[:, c] = blocks[:, (c // 3) % min(4, n_chunks)]
+    qd = wl.make_decode_queries(w)
+    want = oracle.chunk_scores(qd, k, lay.chunk_bounds)
+    for top_k in sorted({0, 1, n_chunks // 2, n_chunks}):
+        print(n_chunks, top_k, flush=True)
+        idx, mask, scores = gpu_score_topk(w, lay, qd, k, top_k)
+        assert np.abs(scores - want).max() <= 2e-5 * np.abs(want).max()
+        own_idx, own_mask = full_sort_selection(scores, top_k)
+        assert np.array_equal(idx, own_idx) and np.array_equal(mask, own_mask)
