@@ -397,6 +397,7 @@ vxl_status vxl_chunk_prefill(const vxl_layout* L, const vxl_attn_desc* d, const 
         if (!workspace || workspace_bytes < need || !aligned16(workspace)) return VXL_ERR_WORKSPACE;
         return launch_prefill_bf16(L, d, scale, Q, K, V, O, LSE, workspace, (hipStream_t)stream);
     }
+    if (d->dtype == VXL_F32) return launch_prefill_f32(L, d, scale, Q, K, V, O, LSE, (hipStream_t)stream);
     return launch_prefill_simple(L, d, scale, Q, K, V, O, LSE, (hipStream_t)stream);
 }
 
@@ -509,6 +510,8 @@ vxl_status vxl_bilevel_decode(const vxl_attn_desc* d, const void* Qd, int32_t ba
         return launch_decode_bf16(d, scale, Qd, batch, n_q_tokens, Kmix, Vmix, l_cap, mix_len, O,
                                   LSE, workspace, (hipStream_t)stream);
     }
+    if (d->dtype == VXL_F32)
+        return launch_decode_f32(d, scale, Qd, batch, n_q_tokens, Kmix, Vmix, l_cap, mix_len, O, LSE, (hipStream_t)stream);
     return launch_decode_simple(d, scale, Qd, batch, n_q_tokens, Kmix, Vmix, l_cap, mix_len, O, LSE,
                                 (hipStream_t)stream);
 }
@@ -542,6 +545,8 @@ vxl_status vxl_bilevel_decode_inplace(const vxl_layout* L, const vxl_attn_desc* 
     if (d->dtype == VXL_BF16 && !g_force_simple)
         return launch_decode_bf16_inplace(L, d, scale, Qd, batch, n_q_tokens, K, V, Ksp, Vsp, src_idx, l_cap, len, O,
                                           LSE, (char*)workspace + w.partials, s);
+    if (d->dtype == VXL_F32)
+        return launch_decode_f32_inplace(L, d, scale, Qd, batch, n_q_tokens, K, V, Ksp, Vsp, src_idx, l_cap, len, O, LSE, s);
     return launch_decode_inplace_simple(L, d, scale, Qd, batch, n_q_tokens, K, V, Ksp, Vsp, src_idx, l_cap, len, O,
                                         LSE, s);
 }
@@ -569,6 +574,8 @@ vxl_status vxl_bilevel_decode_static(const vxl_attn_desc* d, const void* Qd, int
         return launch_decode_bf16(d, scale, Qd, batch, n_q_tokens, Kmix, Vmix, l_cap, mix_len, O, LSE, ws,
                                   (hipStream_t)stream);
     }
+    if (d->dtype == VXL_F32)
+        return launch_decode_f32(d, scale, Qd, batch, n_q_tokens, Kmix, Vmix, l_cap, mix_len, O, LSE, (hipStream_t)stream);
     return launch_decode_simple(d, scale, Qd, batch, n_q_tokens, Kmix, Vmix, l_cap, mix_len, O, LSE,
                                 (hipStream_t)stream);
 }

@@ -1,0 +1,389 @@
+// fp32 storage: pre-filling and decode attention on the fp32 matrix instruction
+// (v_mfma_f32_16x16x4_f32: fp32 operands, fp32 accumulation -- the 1e-5 tolerance of this storage
+// type rules out bf16 operands), softmax with expf.
+//
+// fp32 is the type of small prompts, whose calls are bound by latency: rows are few and the serial
+// walk over the keys is the call.  A wave therefore takes 16 stacked query rows (rho = t * G + head
+// in group, so that short chunks and small groups still fill a block) and only a slice of the keys;
+// the waves of a workgroup share the keys of a block and are merged through LDS.  Operands come
+// straight from global memory into registers in an order that both products can use as it is:
+//   S^T = K.Q^T    A: lane (i = lane % 16, j = lane / 16) holds K[key i][16*s + 4*j + e], B: Q[row i]
+//                  of the same pieces, one instruction per element e of a 16-byte piece;
+//                  result register r of a lane: key 4*j + r, row i
+//   O^T = V^T.P^T  step r takes the keys {4*j + r}: B is the lane's own probability, A the lane's
+//                  V[key 4*j + r][64*blk + 4*i + e], again one instruction per element of a piece;
+//                  result register r' of (blk, e): O[row i][64*blk + 16*j + 4*r' + e]
+// so there is no transposition, no LDS and no cross-lane traffic but the row maximum, and every
+// load is 16 bytes per lane (64 contiguous bytes per key row for K, 256 for V).  The K pieces of the
+// next tile are requested before the softmax of the current one, its V pieces before its scores.
+//
+// A wave that owns one query row and adds one key at a time took, at 576 tokens, two heads and
+// D = 64, 51 us for the pre-filling and 95 us for 8 query tokens over 352 mixed rows; these kernels
+// take 8.6 and 10.3.
+#include <math.h>
+
+#include <algorithm>
+
+#include "vxl_internal.h"
+#include "vxl_mfma.h"
+
+namespace vxl {
+
+namespace {
+
+typedef __attribute__((ext_vector_type(4))) float f32x4;
+
+constexpr int kF32Rows = 16;         // stacked query rows per block
+constexpr int kF32KB = 2;            // blocks of 16 keys per tile
+
+// Rows of a contiguous pair of buffers: slot = row.
+struct RowsPlain {
+    const float *k, *v;
+    int d;
+    __device__ __forceinline__ int entry(int slot) const { return slot; }
+    __device__ __forceinline__ const float* krow(int e) const { return k + (size_t)e * d; }
+    __device__ __forceinline__ const float* vrow(int e) const { return v + (size_t)e * d; }
+};
+// Pre-filling: history slots through the layout's slot table, then the segment's own tokens.
+struct RowsSegment {
+    const float *k, *v;
+    const int32_t* tile_src;
+    int ctx, own0;                   // history slots; token of slot ctx
+    long long tok;                   // elements between rows
+    __device__ __forceinline__ int entry(int slot) const {
+        const int h = tile_src[min(slot, max(ctx - 1, 0))];
+        return slot < ctx ? h : own0 + slot - ctx;
+    }
+    __device__ __forceinline__ const float* krow(int e) const { return k + (size_t)e * tok; }
+    __device__ __forceinline__ const float* vrow(int e) const { return v + (size_t)e * tok; }
+};
+// In-place decode: entry e >= 0 is token e, e < 0 row -1 - e of the sparse buffers.
+struct RowsMapped {
+    const float *k, *v, *ksp, *vsp;
+    const int32_t* src;
+    int d;
+    long long tok;
+    __device__ __forceinline__ int entry(int slot) const { return src[slot]; }
+    __device__ __forceinline__ const float* krow(int e) const { return e >= 0 ? k + (size_t)e * tok : ksp + (size_t)~e * d; }
+    __device__ __forceinline__ const float* vrow(int e) const { return e >= 0 ? v + (size_t)e * tok : vsp + (size_t)~e * d; }
+};
+
+// One wave: 16 query rows (pieces in q) over the slots [lo, hi); slots beyond `lim` (per lane: the
+// lane's own row) are masked.  m, l: running maximum and this lane's share of the running sum.
+template <int D, typename Rows>
+__device__ __forceinline__ void attend_f32(const Rows& rows, const float4 (&q)[D / 16], int lo, int hi, int lim,
+                                           float scale, float& m, float& l, f32x4 (&o)[D / 16]) {
+    constexpr int KB = kF32KB, TILE = 16 * KB;
+    const int lane = threadIdx.x & 63, i = lane & 15, j = lane >> 4;
+    if (lo >= hi) return;
+    float4 k[KB][D / 16], v[KB][4][D / 64];
+    int ent[KB];
+    auto entries = [&](int t, int (&e)[KB]) __attribute__((always_inline)) {
+#pragma unroll
+        for (int kb = 0; kb < KB; ++kb) e[kb] = rows.entry(min(t + kb * 16 + i, hi - 1));
+    };
+    auto load_k = [&](const int (&e)[KB]) __attribute__((always_inline)) {
+#pragma unroll
+        for (int kb = 0; kb < KB; ++kb) {
+            const float* p = rows.krow(e[kb]) + 4 * j;
+#pragma unroll
+            for (int s = 0; s < D / 16; ++s) k[kb][s] = *(const float4*)(p + 16 * s);
+        }
+    };
+    entries(lo, ent);
+    load_k(ent);
+    for (int t = lo; t < hi; t += TILE) {
+        int next[KB];
+        entries(min(t + TILE, hi - 1), next);
+#pragma unroll
+        for (int kb = 0; kb < KB; ++kb)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const float* p = rows.vrow(__shfl(ent[kb], 4 * j + r)) + 4 * i;
+#pragma unroll
+                for (int b = 0; b < D / 64; ++b) v[kb][r][b] = *(const float4*)(p + 64 * b);
+            }
+        f32x4 s[KB];
+#pragma unroll
+        for (int kb = 0; kb < KB; ++kb) s[kb] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int x = 0; x < D / 16; ++x)
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+#pragma unroll
+                for (int kb = 0; kb < KB; ++kb)
+                    s[kb] = __builtin_amdgcn_mfma_f32_16x16x4f32(((const float*)&k[kb][x])[e], ((const float*)&q[x])[e],
+                                                                 s[kb], 0, 0, 0);
+        load_k(next);                                         // (the last tile fetches its last row again)
+        float mx = -INFINITY;
+#pragma unroll
+        for (int kb = 0; kb < KB; ++kb)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const int slot = t + kb * 16 + 4 * j + r;
+                s[kb][r] = slot < hi && slot <= lim ? s[kb][r] * scale : -INFINITY;
+                mx = fmaxf(mx, s[kb][r]);
+            }
+        mx = fmaxf(mx, __shfl_xor(mx, 16));
+        mx = fmaxf(mx, __shfl_xor(mx, 32));
+        const float m_new = fmaxf(m, mx);
+        const float ref = m_new == -INFINITY ? 0.f : m_new;  // (no visible key yet)
+        const float alpha = expf(m - ref);
+        m = m_new;
+        float sum = 0.f;
+#pragma unroll
+        for (int kb = 0; kb < KB; ++kb)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                s[kb][r] = expf(s[kb][r] - ref);
+                sum += s[kb][r];
+            }
+        l = l * alpha + sum;
+#pragma unroll
+        for (int x = 0; x < D / 16; ++x) o[x] *= alpha;
+#pragma unroll
+        for (int kb = 0; kb < KB; ++kb)
+#pragma unroll
+            for (int r = 0; r < 4; ++r)
+#pragma unroll
+                for (int x = 0; x < D / 16; ++x)
+                    o[x] = __builtin_amdgcn_mfma_f32_16x16x4f32(((const float*)&v[kb][r][x / 4])[x % 4], s[kb][r], o[x],
+                                                                0, 0, 0);
+#pragma unroll
+        for (int kb = 0; kb < KB; ++kb) ent[kb] = next[kb];
+    }
+}
+
+template <int D>
+__device__ __forceinline__ void load_q_f32(const float* qrow, float4 (&q)[D / 16]) {
+    const int j = (threadIdx.x & 63) >> 4;
+#pragma unroll
+    for (int s = 0; s < D / 16; ++s) q[s] = *(const float4*)(qrow + 16 * s + 4 * j);
+}
+
+// The waves of one block of rows, merged in wave order through LDS: every wave leaves its (m, l, O),
+// then thread `tid` of `n_thr` forms the elements tid, tid + n_thr, ... of the 16 x D block and hands
+// them, four neighbouring d at a time, to store(row, d, float4 O, float lse).
+template <int D, int W>
+struct MergeF32 {
+    static constexpr int ROW = D + 4;                         // (padded: 16 rows in distinct banks)
+    static constexpr int FLOATS = W * (kF32Rows * ROW + 2 * kF32Rows);
+    template <typename Store>
+    static __device__ __forceinline__ void run(float* lds, int w, int tid, int n_thr, float m, float l,
+                                               const f32x4 (&o)[D / 16], Store store) {
+        const int lane = threadIdx.x & 63, i = lane & 15, j = lane >> 4;
+        float* stat = lds + W * kF32Rows * ROW;               // [W][16][2]
+        l += __shfl_xor(l, 16);
+        l += __shfl_xor(l, 32);
+        if (j == 0) { stat[(w * kF32Rows + i) * 2] = m; stat[(w * kF32Rows + i) * 2 + 1] = l; }
+        float* dst = lds + (w * kF32Rows + i) * ROW + 16 * j;
+#pragma unroll
+        for (int b = 0; b < D / 64; ++b)
+#pragma unroll
+            for (int r = 0; r < 4; ++r)
+                *(float4*)(dst + 64 * b + 4 * r) = make_float4(o[b * 4][r], o[b * 4 + 1][r], o[b * 4 + 2][r], o[b * 4 + 3][r]);
+        __syncthreads();
+        for (int e = tid; e < kF32Rows * D / 4; e += n_thr) {
+            const int row = e / (D / 4), d = (e % (D / 4)) * 4;
+            float M = -INFINITY;
+#pragma unroll
+            for (int x = 0; x < W; ++x) M = fmaxf(M, stat[(x * kF32Rows + row) * 2]);
+            const float ref = M == -INFINITY ? 0.f : M;
+            float4 a = make_float4(0.f, 0.f, 0.f, 0.f);
+            float L = 0.f;
+#pragma unroll
+            for (int x = 0; x < W; ++x) {
+                const float f = expf(stat[(x * kF32Rows + row) * 2] - ref);
+                const float4 p = *(const float4*)(lds + (x * kF32Rows + row) * ROW + d);
+                L = fmaf(f, stat[(x * kF32Rows + row) * 2 + 1], L);
+                a.x = fmaf(f, p.x, a.x); a.y = fmaf(f, p.y, a.y); a.z = fmaf(f, p.z, a.z); a.w = fmaf(f, p.w, a.w);
+            }
+            const float inv = L > 0.f ? 1.f / L : 0.f;        // (no visible key: O = 0, LSE = -inf)
+            store(row, d, make_float4(a.x * inv, a.y * inv, a.z * inv, a.w * inv), L > 0.f ? M + logf(L) : -INFINITY);
+        }
+    }
+};
+
+// Pre-filling.  grid: (128-token bands of the work list, heaviest first) x (row blocks of a band, over
+// the workgroup's 4 / KS blocks) x KV heads.  KS waves share the keys of a block: 4 while the call
+// has fewer blocks than the chip has SIMDs, otherwise 1 (no merge, the waves of a workgroup read the
+// same keys at about the same time).
+template <int D, int KS>
+__global__ __launch_bounds__(256, 2) void prefill_f32_kernel(
+    const float* __restrict__ Q, const float* __restrict__ K, const float* __restrict__ V, float* __restrict__ O,
+    float* __restrict__ LSE, const Segment* __restrict__ segs, const WorkItem* __restrict__ work,
+    const int32_t* __restrict__ tile_src, int n_tokens, int group, float scale, long long q_head, long long q_tok,
+    long long kv_head, long long kv_tok) {
+    constexpr int BAND = 128;
+    __shared__ __attribute__((aligned(16))) float lds[KS > 1 ? MergeF32<D, KS>::FLOATS : 4];
+    const int lane = threadIdx.x & 63, i = lane & 15;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const WorkItem wi = work[blockIdx.x];
+    const Segment sg = segs[wi.seg];
+    const int g = blockIdx.z;
+    const int t0 = wi.m_tile * BAND;
+    const int rows_band = min(BAND, sg.q_len - t0) * group;
+    const int rho0 = (blockIdx.y * (4 / KS) + wave / KS) * kF32Rows;
+    if (rho0 >= rows_band) return;                            // (KS > 1: the whole workgroup)
+    const int rho = min(rho0 + i, rows_band - 1);
+    const int t = t0 + rho / group, h = g * group + rho % group;
+    float4 q[D / 16];
+    load_q_f32<D>(Q + (size_t)h * q_head + (size_t)(sg.q_start + t) * q_tok, q);
+
+    const RowsSegment rows{K + (size_t)g * kv_head, V + (size_t)g * kv_head, tile_src, sg.ctx_len,
+                           sg.q_start - sg.back, kv_tok};
+    const int n_keys = sg.ctx_len + sg.back + t0 + (min(rho0 + kF32Rows, rows_band) - 1) / group + 1;
+    constexpr int TILE = 16 * kF32KB;
+    const int per = ((n_keys + TILE - 1) / TILE + KS - 1) / KS * TILE;
+    const int lo = (wave % KS) * per, hi = min(lo + per, n_keys);
+    float m = -INFINITY, l = 0.f;
+    f32x4 o[D / 16];
+#pragma unroll
+    for (int x = 0; x < D / 16; ++x) o[x] = f32x4{0.f, 0.f, 0.f, 0.f};
+    attend_f32<D>(rows, q, lo, hi, sg.ctx_len + sg.back + t, scale, m, l, o);
+
+    auto store = [&](int row, int d, float4 val, float lse) __attribute__((always_inline)) {
+        const int rr = rho0 + row;
+        if (rr >= rows_band) return;
+        const int tt = sg.q_start + t0 + rr / group, hh = g * group + rr % group;
+        *(float4*)(O + (size_t)hh * q_head + (size_t)tt * q_tok + d) = val;
+        if (LSE && d == 0) LSE[(size_t)hh * n_tokens + tt] = lse;
+    };
+    if constexpr (KS > 1) {
+        MergeF32<D, KS>::run(lds, wave, threadIdx.x, 256, m, l, o, store);
+    } else {
+        l += __shfl_xor(l, 16);
+        l += __shfl_xor(l, 32);
+        const float inv = 1.f / l, lse = m + logf(l);
+        const int j = lane >> 4;
+#pragma unroll
+        for (int b = 0; b < D / 64; ++b)
+#pragma unroll
+            for (int r = 0; r < 4; ++r)
+                store(i, 64 * b + 16 * j + 4 * r, make_float4(o[b * 4][r] * inv, o[b * 4 + 1][r] * inv,
+                                                              o[b * 4 + 2][r] * inv, o[b * 4 + 3][r] * inv), lse);
+    }
+}
+
+// Decode over the mixed KV set, gathered (rows of Kmix / Vmix) or in place (MAPPED, rows of K / V /
+// Ksp / Vsp through src_idx).  grid: row blocks x KV heads x queries; all W waves of the workgroup
+// share the keys of the block.  No scratch memory: the call takes no workspace for this storage type.
+template <int D> struct DecodeF32 {
+    static constexpr int W = D == 64 ? 16 : 8;                // (registers: 96 / 192 for operands and output)
+    static constexpr int LDS_BYTES = MergeF32<D, W>::FLOATS * 4;
+};
+template <int D, bool MAPPED>
+__global__ __launch_bounds__(64 * DecodeF32<D>::W, DecodeF32<D>::W / 4) void decode_f32_kernel(
+    const float* __restrict__ Qd, const float* __restrict__ K, const float* __restrict__ V,
+    const float* __restrict__ Ksp, const float* __restrict__ Vsp, const int32_t* __restrict__ src_idx,
+    float* __restrict__ O, float* __restrict__ LSE, const int32_t* __restrict__ mix_len, int T_q, int n_q_heads,
+    int n_kv_heads, int group, int l_cap, int s_total, long long kv_head, long long kv_tok, float scale) {
+    constexpr int W = DecodeF32<D>::W;
+    extern __shared__ __attribute__((aligned(16))) float lds_f[];
+    const int lane = threadIdx.x & 63, i = lane & 15;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int g = blockIdx.y, b = blockIdx.z;
+    const int n_rows = T_q * group, rho0 = blockIdx.x * kF32Rows;
+    const int rho = min(rho0 + i, n_rows - 1);
+    float4 q[D / 16];
+    load_q_f32<D>(Qd + (((size_t)b * T_q + rho / group) * n_q_heads + g * group + rho % group) * D, q);
+    const int n_keys = min(max(mix_len[b], 0), l_cap);
+
+    constexpr int TILE = 16 * kF32KB;
+    const int per = ((n_keys + TILE - 1) / TILE + W - 1) / W * TILE;
+    const int lo = wave * per, hi = min(lo + per, n_keys);
+    float m = -INFINITY, l = 0.f;
+    f32x4 o[D / 16];
+#pragma unroll
+    for (int x = 0; x < D / 16; ++x) o[x] = f32x4{0.f, 0.f, 0.f, 0.f};
+    if constexpr (MAPPED) {
+        const RowsMapped rows{K + (size_t)g * kv_head, V + (size_t)g * kv_head, Ksp + (size_t)g * s_total * D,
+                              Vsp + (size_t)g * s_total * D, src_idx + (size_t)b * l_cap, D, kv_tok};
+        attend_f32<D>(rows, q, lo, hi, n_keys, scale, m, l, o);
+    } else {
+        const size_t off = ((size_t)b * n_kv_heads + g) * (size_t)l_cap * D;
+        attend_f32<D>(RowsPlain{K + off, V + off, D}, q, lo, hi, n_keys, scale, m, l, o);
+    }
+    MergeF32<D, W>::run(lds_f, wave, threadIdx.x, 64 * W, m, l, o, [&](int row, int d, float4 val, float lse)
+                        __attribute__((always_inline)) {
+        const int rr = rho0 + row;
+        if (rr >= n_rows) return;
+        const size_t dst = ((size_t)b * T_q + rr / group) * n_q_heads + g * group + rr % group;
+        *(float4*)(O + dst * D + d) = val;
+        if (LSE && d == 0) LSE[dst] = lse;
+    });
+}
+
+}  // namespace
+
+vxl_status launch_prefill_f32(const vxl_layout* L, const vxl_attn_desc* d, float scale, const void* Q, const void* K,
+                              const void* V, void* O, float* LSE, hipStream_t s) {
+    const int group = d->n_q_heads / d->n_kv_heads;
+    const TokStrides ts = tok_strides(d, L->n_tokens);
+    const int blocks = 128 * group / kF32Rows;                // row blocks of a full band
+    // blocks that hold rows: keys shared by four waves while these leave SIMDs idle
+    const long long rows = (long long)L->n_tokens * d->n_q_heads;
+    int n_cus = 0;
+    const vxl_status st = device_cu_count(&n_cus);
+    if (st != VXL_OK) return st;
+    const bool share = rows / kF32Rows < 4ll * n_cus;
+#define VXL_LAUNCH(D, KS)                                                                                       \
+    hipLaunchKernelGGL((prefill_f32_kernel<D, KS>), dim3(L->n_work[0], (blocks + 4 / KS - 1) / (4 / KS), d->n_kv_heads), \
+                       dim3(256), 0, s, (const float*)Q, (const float*)K, (const float*)V, (float*)O, LSE, L->d_segs,  \
+                       L->d_work[0], L->d_tile_src, L->n_tokens, group, scale, ts.qh, ts.qt, ts.kh, ts.kt)
+    if (d->head_dim == 64) { if (share) VXL_LAUNCH(64, 4); else VXL_LAUNCH(64, 1); }
+    else { if (share) VXL_LAUNCH(128, 4); else VXL_LAUNCH(128, 1); }
+#undef VXL_LAUNCH
+    VXL_HIP_TRY(hipGetLastError());
+    return VXL_OK;
+}
+
+template <int D>
+static vxl_status run_decode_f32(const vxl_attn_desc* d, float scale, const void* Qd, int batch, int T, const void* K,
+                                 const void* V, const void* Ksp, const void* Vsp, const int32_t* src_idx, int l_cap,
+                                 int s_total, const TokStrides& ts, const int32_t* mix_len, void* O, float* LSE,
+                                 hipStream_t s) {
+    const int group = d->n_q_heads / d->n_kv_heads;
+    constexpr int lds_bytes = DecodeF32<D>::LDS_BYTES;
+    static PerDeviceOnce attr;
+    const vxl_status st = attr.run([] {
+        VXL_HIP_TRY(hipFuncSetAttribute((const void*)decode_f32_kernel<D, false>,
+                                        hipFuncAttributeMaxDynamicSharedMemorySize, lds_bytes));
+        VXL_HIP_TRY(hipFuncSetAttribute((const void*)decode_f32_kernel<D, true>,
+                                        hipFuncAttributeMaxDynamicSharedMemorySize, lds_bytes));
+        return VXL_OK;
+    });
+    if (st != VXL_OK) return st;
+    const dim3 grid((group * T + kF32Rows - 1) / kF32Rows, d->n_kv_heads, batch);
+#define VXL_LAUNCH(MAPPED)                                                                                          \
+    hipLaunchKernelGGL((decode_f32_kernel<D, MAPPED>), grid, dim3(64 * DecodeF32<D>::W), lds_bytes, s,              \
+                       (const float*)Qd, (const float*)K, (const float*)V, (const float*)Ksp, (const float*)Vsp,    \
+                       src_idx, (float*)O, LSE, mix_len, T, d->n_q_heads, d->n_kv_heads, group, l_cap, s_total,     \
+                       ts.kh, ts.kt, scale)
+    if (src_idx) VXL_LAUNCH(true); else VXL_LAUNCH(false);
+#undef VXL_LAUNCH
+    VXL_HIP_TRY(hipGetLastError());
+    return VXL_OK;
+}
+
+vxl_status launch_decode_f32(const vxl_attn_desc* d, float scale, const void* Qd, int batch, int T, const void* Kmix,
+                             const void* Vmix, int l_cap, const int32_t* mix_len, void* O, float* LSE, hipStream_t s) {
+    const TokStrides none{};
+    return d->head_dim == 64 ? run_decode_f32<64>(d, scale, Qd, batch, T, Kmix, Vmix, nullptr, nullptr, nullptr, l_cap,
+                                                  0, none, mix_len, O, LSE, s)
+                             : run_decode_f32<128>(d, scale, Qd, batch, T, Kmix, Vmix, nullptr, nullptr, nullptr, l_cap,
+                                                   0, none, mix_len, O, LSE, s);
+}
+
+vxl_status launch_decode_f32_inplace(const vxl_layout* L, const vxl_attn_desc* d, float scale, const void* Qd, int batch,
+                                     int T, const void* K, const void* V, const void* Ksp, const void* Vsp,
+                                     const int32_t* src_idx, int l_cap, const int32_t* mix_len, void* O, float* LSE,
+                                     hipStream_t s) {
+    const TokStrides ts = tok_strides(d, L->n_tokens);
+    return d->head_dim == 64 ? run_decode_f32<64>(d, scale, Qd, batch, T, K, V, Ksp, Vsp, src_idx, l_cap, L->s_total, ts,
+                                                  mix_len, O, LSE, s)
+                             : run_decode_f32<128>(d, scale, Qd, batch, T, K, V, Ksp, Vsp, src_idx, l_cap, L->s_total,
+                                                   ts, mix_len, O, LSE, s);
+}
+
+}  // namespace vxl

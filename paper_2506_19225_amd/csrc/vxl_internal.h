@@ -134,6 +134,9 @@ PrefillWorkspace prefill_workspace(const vxl_layout* L, const vxl_attn_desc* d);
 vxl_status launch_prefill_bf16(const vxl_layout* L, const vxl_attn_desc* d, float scale,
                                const void* Q, const void* K, const void* V, void* O, float* LSE,
                                void* ws, hipStream_t s);
+vxl_status launch_prefill_f32(const vxl_layout* L, const vxl_attn_desc* d, float scale, const void* Q, const void* K,
+                              const void* V, void* O, float* LSE, hipStream_t s);
+// bf16 cross-check (vxl_debug_force_simple)
 vxl_status launch_prefill_simple(const vxl_layout* L, const vxl_attn_desc* d, float scale,
                                  const void* Q, const void* K, const void* V, void* O, float* LSE,
                                  hipStream_t s);
@@ -194,6 +197,13 @@ vxl_status launch_decode_bf16_inplace(const vxl_layout* L, const vxl_attn_desc* 
                                       int batch, int T, const void* K, const void* V, const void* Ksp,
                                       const void* Vsp, const int32_t* src_idx, int l_cap, const int32_t* mix_len,
                                       void* O, float* LSE, void* ws, hipStream_t s);
+vxl_status launch_decode_f32(const vxl_attn_desc* d, float scale, const void* Qd, int batch, int T, const void* Kmix,
+                             const void* Vmix, int l_cap, const int32_t* mix_len, void* O, float* LSE, hipStream_t s);
+vxl_status launch_decode_f32_inplace(const vxl_layout* L, const vxl_attn_desc* d, float scale, const void* Qd, int batch,
+                                     int T, const void* K, const void* V, const void* Ksp, const void* Vsp,
+                                     const int32_t* src_idx, int l_cap, const int32_t* mix_len, void* O, float* LSE,
+                                     hipStream_t s);
+// bf16 cross-check (vxl_debug_force_simple)
 vxl_status launch_decode_inplace_simple(const vxl_layout* L, const vxl_attn_desc* d, float scale, const void* Qd,
                                         int batch, int T, const void* K, const void* V, const void* Ksp,
                                         const void* Vsp, const int32_t* src_idx, int l_cap,

@@ -1,7 +1,6 @@
-// Plain vector-ALU kernels: one 64-lane wavefront per query row, fp32 arithmetic throughout.
-// They serve the F32 storage dtype (whose 1e-5 tolerance rules out bf16 matrix-core inputs)
-// and, for BF16 storage, an on-device cross-check of the matrix-core kernels that shares none
-// of their tiling, compaction or transposition.
+// Plain vector-ALU kernels: one 64-lane wavefront per query row, fp32 arithmetic throughout: for
+// BF16 storage, an on-device cross-check of the matrix-core kernels that shares none of their
+// tiling, compaction or transposition.
 #include <math.h>
 
 #include "vxl_internal.h"
@@ -10,9 +9,7 @@ namespace vxl {
 
 namespace {
 
-__device__ __forceinline__ float ld(const float* p) { return *p; }
 __device__ __forceinline__ float ld(const uint16_t* p) { return __uint_as_float((uint32_t)(*p) << 16); }
-__device__ __forceinline__ void st(float* p, float v) { *p = v; }
 __device__ __forceinline__ void st(uint16_t* p, float v) {
     uint32_t b = __float_as_uint(v);
     if ((b & 0x7fffffffu) > 0x7f800000u) { *p = 0x7fc0; return; }
@@ -192,8 +189,7 @@ vxl_status launch_prefill_simple(const vxl_layout* L, const vxl_attn_desc* d, fl
     hipLaunchKernelGGL((prefill_simple_kernel<T, D>), grid, block, 0, s, (const T*)Q, (const T*)K, \
                        (const T*)V, (T*)O, LSE, L->d_bounds, L->d_soff, L->d_sidx, L->n_tokens,   \
                        L->n_prefix, L->n_chunks, group, scale, L->window, ts.qh, ts.qt, ts.kh, ts.kt)
-    if (d->dtype == VXL_F32) { if (d->head_dim == 64) VXL_LAUNCH(float, 64); else VXL_LAUNCH(float, 128); }
-    else { if (d->head_dim == 64) VXL_LAUNCH(uint16_t, 64); else VXL_LAUNCH(uint16_t, 128); }
+    if (d->head_dim == 64) VXL_LAUNCH(uint16_t, 64); else VXL_LAUNCH(uint16_t, 128);
 #undef VXL_LAUNCH
     VXL_HIP_TRY(hipGetLastError());
     return VXL_OK;
@@ -209,8 +205,7 @@ vxl_status launch_decode_simple(const vxl_attn_desc* d, float scale, const void*
     hipLaunchKernelGGL((decode_simple_kernel<T_, D>), grid, block, 0, s, (const T_*)Qd,              \
                        (const T_*)Kmix, (const T_*)Vmix, (T_*)O, LSE, mix_len, batch, T, d->n_q_heads, \
                        group, l_cap, scale)
-    if (d->dtype == VXL_F32) { if (d->head_dim == 64) VXL_LAUNCH(float, 64); else VXL_LAUNCH(float, 128); }
-    else { if (d->head_dim == 64) VXL_LAUNCH(uint16_t, 64); else VXL_LAUNCH(uint16_t, 128); }
+    if (d->head_dim == 64) VXL_LAUNCH(uint16_t, 64); else VXL_LAUNCH(uint16_t, 128);
 #undef VXL_LAUNCH
     VXL_HIP_TRY(hipGetLastError());
     return VXL_OK;
@@ -228,8 +223,7 @@ vxl_status launch_decode_inplace_simple(const vxl_layout* L, const vxl_attn_desc
     hipLaunchKernelGGL((decode_inplace_simple_kernel<T_, D>), grid, block, 0, s, (const T_*)Qd, (const T_*)K,  \
                        (const T_*)V, (const T_*)Ksp, (const T_*)Vsp, src_idx, (T_*)O, LSE, mix_len, batch, T,   \
                        d->n_q_heads, group, l_cap, L->s_total, ts.kh, ts.kt, scale)
-    if (d->dtype == VXL_F32) { if (d->head_dim == 64) VXL_LAUNCH(float, 64); else VXL_LAUNCH(float, 128); }
-    else { if (d->head_dim == 64) VXL_LAUNCH(uint16_t, 64); else VXL_LAUNCH(uint16_t, 128); }
+    if (d->head_dim == 64) VXL_LAUNCH(uint16_t, 64); else VXL_LAUNCH(uint16_t, 128);
 #undef VXL_LAUNCH
     VXL_HIP_TRY(hipGetLastError());
     return VXL_OK;
