@@ -123,9 +123,14 @@ def _ptr(t: Optional[torch.Tensor]) -> Optional[int]:
     return t.data_ptr()
 
 
+# The handle of the current stream without the Stream object that torch.cuda.current_stream() builds for it:
+# 0.1 us instead of 2.8 us per call, a fifth of what a generated token's decode call took on the host.
+_raw_stream, _current_device = torch._C._cuda_getCurrentRawStream, torch._C._cuda_getDevice
+
+
 def _stream(stream) -> Optional[int]:
     if stream is None:
-        stream = torch.cuda.current_stream()
+        return _raw_stream(_current_device()) or None
     return stream.cuda_stream or None
 
 
