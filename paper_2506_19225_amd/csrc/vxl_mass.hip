@@ -6,11 +6,11 @@
 // One pass over the dense keys.  The token range is cut into items (the prefix and every chunk,
 // each in pieces of at most kMassPiece keys; table built with the layout).  A workgroup owns one
 // (item, KV head, row tile, query b) and produces for each of its stacked query rows
-// rho = t*G + hg the pair (m, l): m = the largest scaled logit of the item in base-2 units,
-// l = sum over the item's keys of 2^(logit2 - m).  Two small kernels then combine the items of a
-// row (M = max m, L = sum l*2^(m-M)) and add up, per chunk, l*2^(m-M)/L over the rows; both use
-// fixed summation orders, so equal inputs give equal scores.  The selection is the same LDS
-// bitonic sort as in the mean-logit mode.
+// rho = t*G + hg the pair (m, l): m = a reference logit of the item in base-2 units (no logit of the
+// item lies more than 2^30 above it in the exp2 domain), l = sum over the item's keys of
+// 2^(logit2 - m).  Two small kernels then combine the items of a row (M = max m,
+// L = sum l*2^(m-M)) and add up, per chunk, l*2^(m-M)/L over the rows; both use fixed summation
+// orders, so equal inputs give equal scores.  The selection is the same as in the mean-logit mode.
 #include <math.h>
 
 #include <algorithm>
@@ -54,8 +54,18 @@ struct KTileRegs {
 };
 
 constexpr int kMassRowTile = 128;                     // stacked query rows per workgroup (4 waves x 32)
+constexpr int kXcds = 8;
+constexpr float kMassGrow = 1073741824.f;             // 2^30: a lane's sum over a tile from which the reference is raised
 
 // bf16, matrix cores: S^T = K.Q^T per 64-key tile, running (m, l) per query column.
+// Bound by the exponentials of a tile (a multiply-add, an exponential and an addition per logit,
+// as many issue slots as the matrix instructions take), once the keys come from L2: the row tiles
+// of one (item, KV head) are neighbours in the launch order of one XCD (workgroups go to the eight
+// XCDs in turn), so that HBM delivers a key once and not once per row tile.  The maximum of a tile
+// is formed only when the tile's sum says that the reference no longer fits (`kMassGrow`).
+// 448 rows x 4 heads over 131,328 keys: 87 us with the row tiles a whole pass apart and a maximum per
+// tile, 81 so.  The whole score and selection: 115 -> 92 us; 896 rows over 164,096 keys 305 -> 210.
+// A register-only loop of the same instructions at four waves per SIMD takes 43 us on this many tiles.
 template <int D>
 __global__ __launch_bounds__(256, 2) void mass_partial_kernel(
     const uint16_t* __restrict__ Qd, const uint16_t* __restrict__ K, const MassItem* __restrict__ items,
@@ -64,10 +74,13 @@ __global__ __launch_bounds__(256, 2) void mass_partial_kernel(
     __shared__ __attribute__((aligned(16))) uint16_t Ks[2][kKeyTile * D];
     const int tid = threadIdx.x, lane = tid & 63, l32 = lane & 31, hi = lane >> 5;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int item = blockIdx.x;
-    const int g = blockIdx.y % n_kv_heads, rt = blockIdx.y / n_kv_heads;
-    const int b = blockIdx.z;
-    const int n_rows = group * T_q;
+    // workgroup id -> (unit = (item, KV head), row tile): id = (unit / 8 * n_rt + rt) * 8 + unit % 8
+    const int n_rows = group * T_q, n_rt = (n_rows + kMassRowTile - 1) / kMassRowTile;
+    const int xcd = blockIdx.x % kXcds, seq = blockIdx.x / kXcds;
+    const int rt = seq % n_rt, unit = seq / n_rt * kXcds + xcd;
+    if (unit >= n_items * n_kv_heads) return;
+    const int item = unit / n_kv_heads, g = unit % n_kv_heads;
+    const int b = blockIdx.y;
     const int k_lo = items[item].key_lo, k_hi = items[item].key_hi;
     const int wrow0 = rt * kMassRowTile + wave * 32;
     const bool wave_active = wrow0 < n_rows;          // waves without rows only help with the copies
@@ -110,23 +123,31 @@ __global__ __launch_bounds__(256, 2) void mass_partial_kernel(
                     for (int r = 0; r < 16; ++r)
                         s[0][kb][r] = acc_key(kb, r, hi) <= lim ? s[0][kb][r] : -INFINITY;
             }
-            float mx = s[0][0][0];
+            auto exp_sum = [&](float mc) __attribute__((always_inline)) {
+                float sum[4] = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-            for (int kb = 0; kb < 2; ++kb)
+                for (int kb = 0; kb < 2; ++kb)
 #pragma unroll
-                for (int r = 0; r < 16; ++r) mx = fmaxf(mx, s[0][kb][r]);
-            mx = fmaxf(mx, __shfl_xor(mx, 32));       // every tile holds at least one valid key
-            const float m_new = fmaxf(m_run, mx);
-            const float alpha = __builtin_amdgcn_exp2f((m_run - m_new) * c2);   // 0 on the first tile
-            const float mc = m_new * c2;
-            float sum[4] = {0.f, 0.f, 0.f, 0.f};
+                    for (int r = 0; r < 16; ++r)
+                        sum[r & 3] += __builtin_amdgcn_exp2f(fmaf(s[0][kb][r], c2, -mc));
+                return (sum[0] + sum[1]) + (sum[2] + sum[3]);
+            };
+            // (the first tile, a sum that is too large or not a number: the whole wave takes the maximum,
+            // so the two lanes of a row keep the same reference)
+            float sum = ti == 0 ? INFINITY : exp_sum(m_run * c2);
+            if (__builtin_amdgcn_ballot_w64(!(sum <= kMassGrow)) != 0) {
+                float mx = s[0][0][0];
 #pragma unroll
-            for (int kb = 0; kb < 2; ++kb)
+                for (int kb = 0; kb < 2; ++kb)
 #pragma unroll
-                for (int r = 0; r < 16; ++r)
-                    sum[r & 3] += __builtin_amdgcn_exp2f(fmaf(s[0][kb][r], c2, -mc));
-            l_run = fmaf(l_run, alpha, (sum[0] + sum[1]) + (sum[2] + sum[3]));
-            m_run = m_new;
+                    for (int r = 0; r < 16; ++r) mx = fmaxf(mx, s[0][kb][r]);
+                mx = fmaxf(mx, __shfl_xor(mx, 32));   // every tile holds at least one valid key
+                const float m_new = fmaxf(m_run, mx);
+                l_run *= __builtin_amdgcn_exp2f((m_run - m_new) * c2);              // 0 on the first tile
+                m_run = m_new;
+                sum = exp_sum(m_run * c2);
+            }
+            l_run += sum;
         }
         tr.stage(Ks[buf ^ 1], ld_r, ld_part);
         __syncthreads();
@@ -199,24 +220,41 @@ __global__ __launch_bounds__(256) void mass_partial_simple_kernel(
 }
 
 // Per stacked row (b, g, rho): M = max over the items of m, 1/L with L = sum l * 2^(m - M).  A block
-// handles 32 consecutive rows of one (b, g) with 8 item groups: thread (ig, r) folds the items
-// ig, ig + 8, ... of row r into a running (M, L) in that order (loads coalesced over the rows),
-// and the eight partial pairs of a row are folded in group order -- a fixed summation order.
-__global__ __launch_bounds__(256) void mass_rowstat_kernel(const float* __restrict__ part_m,
-                                                           const float* __restrict__ part_l,
-                                                           float* __restrict__ row_m, float* __restrict__ row_il,
-                                                           int n_items, int n_rows) {
-    __shared__ float sm[8][32], sl[8][32];
+// handles 32 consecutive rows of one (b, g): thread (ig, r) folds the items ig, ig + GROUPS, ... of
+// row r into a running (M, L), eight items at a time whose loads are all requested first (coalesced
+// over the rows), and the GROUPS partial pairs of a row are folded in group order -- a fixed
+// summation order.  Bound by latency: few rows, hundreds of items each.  32 groups beyond 64 items
+// (448 rows x 4 heads, 257 items: 14.3 us with eight groups taking their items one by one, 6.7 so);
+// up to 64 items eight groups hold them all in one batch.
+template <int GROUPS>
+__global__ __launch_bounds__(32 * GROUPS) void mass_rowstat_kernel(const float* __restrict__ part_m,
+                                                                   const float* __restrict__ part_l,
+                                                                   float* __restrict__ row_m,
+                                                                   float* __restrict__ row_il, int n_items,
+                                                                   int n_rows) {
+    constexpr int U = 8;
+    __shared__ float sm[GROUPS][32], sl[GROUPS][32];
     const int r = threadIdx.x & 31, ig = threadIdx.x >> 5;
     const int rho = blockIdx.x * 32 + r;
     const size_t bg = blockIdx.y;
     float M = -INFINITY, L = 0.f;
     if (rho < n_rows) {
         const size_t base = bg * n_items * n_rows + rho;
-        for (int it = ig; it < n_items; it += 8) {
-            const float m = part_m[base + (size_t)it * n_rows], l = part_l[base + (size_t)it * n_rows];
-            const float Mn = fmaxf(M, m);
-            L = L * exp2f(M - Mn) + l * exp2f(m - Mn);         // (M = -inf: L = 0 and 2^-inf = 0)
+        for (int it = ig; it < n_items; it += U * GROUPS) {
+            float m[U], l[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const size_t idx = base + (size_t)min(it + u * GROUPS, n_items - 1) * n_rows;
+                m[u] = part_m[idx];
+                l[u] = part_l[idx];
+            }
+            float Mn = M;
+#pragma unroll
+            for (int u = 0; u < U; ++u) Mn = fmaxf(Mn, m[u]);  // (a clamped item is one of the row's: the maximum stands)
+            L *= exp2f(M - Mn);                                // (M = -inf: L = 0 and 2^-inf = 0)
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+                if (it + u * GROUPS < n_items) L += l[u] * exp2f(m[u] - Mn);
             M = Mn;
         }
     }
@@ -224,8 +262,7 @@ __global__ __launch_bounds__(256) void mass_rowstat_kernel(const float* __restri
     sl[ig][r] = L;
     __syncthreads();
     if (ig == 0 && rho < n_rows) {
-#pragma unroll
-        for (int k = 1; k < 8; ++k) {
+        for (int k = 1; k < GROUPS; ++k) {
             const float m = sm[k][r], l = sl[k][r];
             if (m == -INFINITY) continue;                      // a group without items
             const float Mn = fmaxf(M, m);
@@ -239,20 +276,24 @@ __global__ __launch_bounds__(256) void mass_rowstat_kernel(const float* __restri
 
 // One block per (chunk c, query b): score = (1 / (T * Hq)) * sum over the stacked rows of all KV
 // heads of [sum over the items of c of l * 2^(m - M_row)] / L_row.  A thread adds its rows
-// r = tid, tid + 256, ... in that order; the 256 partial sums are added in a fixed tree.
-__global__ __launch_bounds__(256) void mass_chunk_kernel(const float* __restrict__ part_m,
+// r = tid, tid + blockDim.x, ... in that order; the partial sums are added in a fixed tree.
+// Latency bound (a chain of loads per row): 512 threads where a chunk has more than 256 rows
+// (1,792 rows, 256 chunks: 6.6 us with 256 threads, 4.8 with 512).
+constexpr int kChunkThreads = 512;
+
+__global__ __launch_bounds__(kChunkThreads) void mass_chunk_kernel(const float* __restrict__ part_m,
                                                          const float* __restrict__ part_l,
                                                          const float* __restrict__ row_m,
                                                          const float* __restrict__ row_il,
                                                          const int32_t* __restrict__ item_off,
                                                          float* __restrict__ scores, int n_items, int n_rows,
                                                          int n_kv_heads, int n_chunks, float inv_count) {
-    __shared__ float wsum[4];
+    __shared__ float wsum[kChunkThreads / 64];
     const int c = blockIdx.x, b = blockIdx.y, tid = threadIdx.x;
     const int i0 = item_off[c], i1 = item_off[c + 1];
     const int total = n_kv_heads * n_rows;
     float acc = 0.f;
-    for (int r = tid; r < total; r += 256) {
+    for (int r = tid; r < total; r += (int)blockDim.x) {
         const int g = r / n_rows, rho = r % n_rows;
         const size_t bg = (size_t)b * n_kv_heads + g;
         const float M = row_m[bg * n_rows + rho];
@@ -266,7 +307,11 @@ __global__ __launch_bounds__(256) void mass_chunk_kernel(const float* __restrict
     acc = wave_sum(acc);
     if ((tid & 63) == 0) wsum[tid >> 6] = acc;
     __syncthreads();
-    if (tid == 0) scores[(size_t)b * n_chunks + c] = ((wsum[0] + wsum[1]) + (wsum[2] + wsum[3])) * inv_count;
+    if (tid == 0) {
+        float total_sum = (wsum[0] + wsum[1]) + (wsum[2] + wsum[3]);
+        if (blockDim.x > 256) total_sum += (wsum[4] + wsum[5]) + (wsum[6] + wsum[7]);
+        scores[(size_t)b * n_chunks + c] = total_sum * inv_count;
+    }
 }
 
 }  // namespace
@@ -299,7 +344,7 @@ vxl_status launch_score_mass(const vxl_layout* L, const vxl_attn_desc* d, float 
     const TokStrides ts = tok_strides(d, L->n_tokens);
     if (d->dtype == VXL_BF16 && !force_simple) {
         const int n_rt = (n_rows + kMassRowTile - 1) / kMassRowTile;
-        const dim3 grid(n_items, n_rt * d->n_kv_heads, batch);
+        const dim3 grid((n_items * d->n_kv_heads + kXcds - 1) / kXcds * kXcds * n_rt, batch);
 #define VXL_LAUNCH(D)                                                                                   \
     hipLaunchKernelGGL((mass_partial_kernel<D>), grid, dim3(256), 0, s, (const uint16_t*)Qd,            \
                        (const uint16_t*)K, L->d_mass_items, part_m, part_l, T, d->n_q_heads,            \
@@ -317,10 +362,16 @@ vxl_status launch_score_mass(const vxl_layout* L, const vxl_attn_desc* d, float 
 #undef VXL_LAUNCH
     }
     VXL_HIP_TRY(hipGetLastError());
-    hipLaunchKernelGGL(mass_rowstat_kernel, dim3((n_rows + 31) / 32, batch * d->n_kv_heads), dim3(256), 0, s,
-                       part_m, part_l, row_m, row_il, n_items, n_rows);
+    const dim3 stat_grid((n_rows + 31) / 32, batch * d->n_kv_heads);
+    if (n_items > 64)
+        hipLaunchKernelGGL((mass_rowstat_kernel<32>), stat_grid, dim3(32 * 32), 0, s, part_m, part_l, row_m, row_il,
+                           n_items, n_rows);
+    else
+        hipLaunchKernelGGL((mass_rowstat_kernel<8>), stat_grid, dim3(32 * 8), 0, s, part_m, part_l, row_m, row_il,
+                           n_items, n_rows);
     VXL_HIP_TRY(hipGetLastError());
-    hipLaunchKernelGGL(mass_chunk_kernel, dim3(L->n_chunks, batch), dim3(256), 0, s, part_m, part_l, row_m,
+    hipLaunchKernelGGL(mass_chunk_kernel, dim3(L->n_chunks, batch),
+                       dim3(d->n_kv_heads * n_rows > 256 ? kChunkThreads : 256), 0, s, part_m, part_l, row_m,
                        row_il, L->d_mass_off, scores, n_items, n_rows, d->n_kv_heads, L->n_chunks,
                        1.f / ((float)T * (float)d->n_q_heads));
     VXL_HIP_TRY(hipGetLastError());

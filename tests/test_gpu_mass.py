@@ -109,3 +109,17 @@ def test_mass_full_size(name):
     _, k, _ = wl.make_qkv(w, lay, with_q=False)
     qd = wl.make_decode_queries(w)
     check_mass(w, lay, qd, k, w.k)
+
+
+@pytest.mark.parametrize("d,t,lens", [(64, 1, [64, 65, 1, 200]), (128, 19, [63, 640, 129]), (128, 64, [1025, 300])])
+def test_mass_reference_raised_inside_an_item(d, t, lens):
+    """Logits that climb by far more than 2^30 (exp2 domain) from the first tile of an item to its last, fall again in
+    the next chunk and differ in sign between the rows of a wave; row counts around the 128-row tile."""
+    w = wl.tiny_workload("bf16", 14, 2, d, T=t, B=2, k=2, seed=75)
+    lay = wl.layout_from_lists(5, lens, [np.zeros(0, np.int32)] * len(lens))
+    _, k, _ = wl.make_qkv(w, lay, with_q=False)
+    qd = wl.make_decode_queries(w)
+    ramp = np.concatenate([np.linspace(-1, 1, 5)] + [np.linspace(-1, 1, n) * (1 - 2 * (i % 2)) for i, n in enumerate(lens)])
+    k = wl.round_to_bf16(k * 0.1 + ramp[None, :, None].astype(np.float32) * np.sign(k[:, :1, :]))
+    qd = wl.round_to_bf16((np.sign(qd) * np.float32(0.2) + np.sign(k[0, 0])) * 3)
+    check_mass(w, lay, qd, k, 2, scale=1.0)
