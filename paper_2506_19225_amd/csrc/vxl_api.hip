@@ -70,58 +70,70 @@ DecodePlan decode_plan(const vxl_attn_desc* d, int batch, int T, int l_cap, bool
     if (d->dtype != VXL_BF16) { p.n_split = 1; p.split_len = l_cap; p.total = 0; return p; }
     const int rows = (d->n_q_heads / d->n_kv_heads) * T;
     const int tiles = (l_cap + kKeyTile - 1) / kKeyTile;
-    // 129-256 stacked rows fit one 256-row workgroup of the ring kernel or two 128-row workgroups
-    // of the 4-wave kernel.  The ring kernel streams better, but only when its launch covers the
-    // chip; at short mixed sets the split cap below leaves it a fraction of the compute units
-    // (measured at 224 rows: 64 and 120 workgroups, 4-wave kernel 9 % and 5 % faster; 176 and
-    // 256 workgroups, ring kernel 5 % and 8 % faster).
-    bool ring = rows > 128;
-    if (ring && rows <= 256) {
-        const long blocks = (long)batch * d->n_kv_heads;
-        const long splits = std::max<long>(1, std::min<long>(std::min<long>((256 + blocks - 1) / blocks, (long)l_cap / rows), tiles));
-        const int per = (int)((tiles + splits - 1) / splits);
-        ring = blocks * ((tiles + per - 1) / per) >= 150;
+    if (rows > kRowBlock) {
+        // 129-256 stacked rows fit one 256-row workgroup of the ring kernel or two 128-row workgroups
+        // of the 4-wave kernel.  The ring kernel streams better, but only when its launch covers the
+        // chip; at short mixed sets the split cap below leaves it a fraction of the compute units
+        // (measured at 224 rows: 64 and 120 workgroups, 4-wave kernel 9 % and 5 % faster; 176 and
+        // 256 workgroups, ring kernel 5 % and 8 % faster).
+        bool ring = rows > 128;
+        if (ring && rows <= 256) {
+            const long blocks = (long)batch * d->n_kv_heads;
+            const long splits = std::max<long>(1, std::min<long>(std::min<long>((256 + blocks - 1) / blocks, (long)l_cap / rows), tiles));
+            const int per = (int)((tiles + splits - 1) / splits);
+            ring = blocks * ((tiles + per - 1) / per) >= 150;
+        }
+        p.use_ring = ring ? 1 : 0;
+        const int row_tile = ring ? 256 : 128;
+        const int n_rtile = (rows + row_tile - 1) / row_tile;
+        // Split the keys until every compute unit has its workgroups (one of the 8-wave ring kernel,
+        // two of the 4-wave kernel), but keep the partial results (fp32 rows per split) below roughly
+        // the KV bytes they summarise (measured at 224 rows over 4,096 keys: 16 splits 20.0 us per
+        // call, 32 splits 21.3, 22 splits 21.2, 8 splits 24.0).
+        const long base_blocks = (long)batch * d->n_kv_heads * n_rtile;
+        const long target = ring ? 256 : 512;
+        long want = (target + base_blocks - 1) / base_blocks;
+        const long cap = std::max<long>(1, (long)l_cap / rows);
+        want = std::max<long>(1, std::min<long>(std::min<long>(want, cap), tiles));
+        const int tiles_per = (int)((tiles + want - 1) / want);
+        p.n_split = (tiles + tiles_per - 1) / tiles_per;
+        p.split_len = tiles_per * kKeyTile;
     }
-    p.use_ring = ring ? 1 : 0;
-    const int row_tile = ring ? 256 : 128;
-    const int n_rtile = (rows + row_tile - 1) / row_tile;
-    if (rows <= kRowBlock) {
-        // Step mode: every wave of a workgroup owns whole 32-key tiles; one workgroup per compute
-        // unit (its tile pairs fill the LDS), tiles spread evenly over at most ~256 workgroups.
+    // Step mode: every wave of a workgroup owns whole 32-key tiles of a 32-row block; one workgroup per
+    // compute unit (its tile pairs fill the LDS), tiles spread evenly over at most ~256 workgroups.
+    {
         constexpr int kTile = 32;
         const int tiles32 = (l_cap + kTile - 1) / kTile;
+        const int n_rtile = (rows + kRowBlock - 1) / kRowBlock;
         const long units = (long)batch * d->n_kv_heads;
-        const long max_split = std::max<long>(1, 256 / units);
+        // (the row blocks of a unit go to one XCD: whole units on its 32 compute units)
+        const long max_split = std::max<long>(1, (n_rtile == 1 ? 256 : 8 * (32 / n_rtile)) / units);
         // four double-buffered waves (measured equal or faster than eight single-buffered ones at every size)
-        const int kWaves = gathered && g_decode_step_waves == 8 ? 8 : 4;
-        p.step_waves = kWaves;
+        const int kWaves = gathered && rows <= kRowBlock && g_decode_step_waves == 8 ? 8 : 4;
         long n_split = std::min<long>((tiles32 + kWaves - 1) / kWaves, max_split);
         // (in-place form: a wave's row map lives in LDS, 32 tiles at most -- more splits instead)
         if (!gathered) n_split = std::max<long>(n_split, (tiles32 + kWaves * 32 - 1) / (kWaves * 32));
+        if (rows > kRowBlock) n_split = std::min<long>(n_split, p.n_split);      // no more partial rows than the other kernels
         const int tpw = (int)((tiles32 + kWaves * n_split - 1) / (kWaves * n_split));
         n_split = (tiles32 + kWaves * tpw - 1) / (kWaves * tpw);
-        p.n_split = (int)n_split;
-        p.split_len = kWaves * tpw * kTile;
-        size_t off = 0;
-        p.part_o = off;
-        off += align_up((size_t)batch * d->n_kv_heads * p.n_split * rows * d->head_dim * sizeof(float), 256);
-        p.part_ml = off;
-        off += align_up((size_t)batch * d->n_kv_heads * p.n_split * rows * sizeof(float), 256);
-        p.total = off;
-        return p;
+        // More than one row block: this form reads the mixed set once per block, but from the L2 of one
+        // XCD, and starts as fast as the one-row-block call; the 128-row kernel moves its tiles through
+        // registers and barriers.  One round of workgroups or none (us per call, before -> with row blocks, G = 7,
+        // four KV heads; keys): 224 rows, 4,096 keys 23.4 -> 18.0; 56 rows, 7,936 keys 23.8 -> 16.0 and
+        // 45,312 keys 49.8 -> 25.3; 112 rows, 45,312 keys 60.2 -> 33.0; in place, 224 rows, 4,096 keys (with
+        // pooling and map) 51.8 -> 43.4.  Against the ring kernel it wins while that one's launch is small
+        // (448 rows: 72 workgroups 25.9 -> 22.7, but 136 workgroups 27.4 -> 28.7; 140 rows at 248 workgroups
+        // 18.5 -> 19.4).  Up to 64 rows at one tile per wave the 128-row kernel stays (56 rows, 1,031 keys:
+        // 12.7 against 13.4).
+        const bool fits = units * n_split * n_rtile <= 256 && (gathered || tpw <= 32);
+        const bool few = p.use_ring ? (long)batch * d->n_kv_heads * ((rows + 255) / 256) * p.n_split < 100 : rows > 64 || tpw > 1;
+        if (rows <= kRowBlock || (fits && few)) {
+            p.use_ring = 0;
+            p.step_waves = kWaves;
+            p.n_split = (int)n_split;
+            p.split_len = kWaves * tpw * kTile;
+        }
     }
-    // Split the keys until every compute unit has its workgroups (one of the 8-wave ring kernel,
-    // two of the 4-wave kernel), but keep the partial results (fp32 rows per split) below roughly
-    // the KV bytes they summarise (measured at 224 rows over 4,096 keys: 16 splits 20.0 us per
-    // call, 32 splits 21.3, 22 splits 21.2, 8 splits 24.0).
-    const long base_blocks = (long)batch * d->n_kv_heads * n_rtile;
-    const long target = ring ? 256 : 512;
-    long want = (target + base_blocks - 1) / base_blocks;
-    const long cap = std::max<long>(1, (long)l_cap / rows);
-    want = std::max<long>(1, std::min<long>(std::min<long>(want, cap), tiles));
-    const int tiles_per = (int)((tiles + want - 1) / want);
-    p.n_split = (tiles + tiles_per - 1) / tiles_per;
-    p.split_len = tiles_per * kKeyTile;
     size_t off = 0;
     p.part_o = off;
     off += align_up((size_t)batch * d->n_kv_heads * p.n_split * rows * d->head_dim * sizeof(float), 256);

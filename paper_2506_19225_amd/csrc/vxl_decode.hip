@@ -368,8 +368,9 @@ __global__ __launch_bounds__(512, 2) void decode_ring_kernel(
 }
 
 // ------------------------------------------------------------------------------------------
-// Step-mode kernel for at most 32 stacked query rows (e.g. T = 1..4 at G = 7): the work is pure
-// streaming, so every WAVE owns its own 32-key tiles (tile = NW*(split*tpw + i) + wave) and its
+// Kernel of the calls that are latency or streaming rather than matrix work: at most 32 stacked query
+// rows (the generated token, T = 1..4 at G = 7), or a few row tiles of 32 over a short mixed set
+// (decode_plan draws the line).  Every WAVE owns its own 32-key tiles (tile = NW*(split*tpw + i) + wave) and its
 // own LDS tile pairs, filled by direct global->LDS loads; there is no workgroup barrier in the
 // loop.  The waves' running (reference, sum, O) are merged through LDS in wave order and the
 // workgroup writes one normalised partial + base-2 LSE per row.
@@ -378,13 +379,15 @@ __global__ __launch_bounds__(512, 2) void decode_ring_kernel(
 // tile (the default: 3-8 % faster on long streams, 5 % at a single tile per wave, where it spreads
 // over twice as many compute units) -- and NW = 8 waves with one tile pair each (cross-check).
 constexpr int kStepTile = 32;       // keys per wave tile
+constexpr int kXcds = 8;
 constexpr int kMaxStepTpw = 32;     // in-place form: tiles per wave whose row map fits the wave's LDS area
 
-template <int D, int NW, int NBUF, bool IND = false>
+template <int D, int NW, int NBUF, bool IND = false, bool ROWS = false>
 __global__ __launch_bounds__(64 * NW, 2) void decode_wave_kernel(
     const uint16_t* __restrict__ Qd, const uint16_t* __restrict__ Kmix, const uint16_t* __restrict__ Vmix,
     const int32_t* __restrict__ mix_len, float* __restrict__ part_o, float* __restrict__ part_lse, int T_q,
-    int n_q_heads, int n_kv_heads, int group, int l_cap, int tiles_per_wave, float scale, RowMap rm) {
+    int n_q_heads, int n_kv_heads, int group, int l_cap, int tiles_per_wave, int n_split, int n_units, int n_rtile, float scale,
+    RowMap rm) {
     static_assert(!IND || NBUF == 2, "the in-place form exists for the double-buffered kernel only");
     constexpr int TK = kStepTile;
     constexpr int TILE_ELEMS = TK * D;                         // one unpadded tile
@@ -394,11 +397,23 @@ __global__ __launch_bounds__(64 * NW, 2) void decode_wave_kernel(
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     uint16_t* Kw = lds + wave * NBUF * 2 * TILE_ELEMS;         // this wave's K tile, then its V tile (NBUF times)
     uint16_t* Vw = Kw + TILE_ELEMS;
-    const int split = blockIdx.x, n_split = gridDim.x, g = blockIdx.y, b = blockIdx.z;
-    const int n_rows = group * T_q;                            // <= 32
+    // One row tile: grid (split, KV head, query).  Several (ROWS): a one-dimensional grid in which the row tiles of
+    // a unit = (query, KV head, split) are neighbours on one XCD (workgroups go to the eight XCDs in turn),
+    // whose L2 then serves all but the first of them: id = (unit / 8 * n_rtile + row tile) * 8 + unit % 8.
+    int split = blockIdx.x, g = blockIdx.y, b = blockIdx.z, row0 = 0;
+    if (!ROWS) n_split = gridDim.x;
+    if constexpr (ROWS) {
+        const int seq = blockIdx.x / kXcds, unit = seq / n_rtile * kXcds + blockIdx.x % kXcds;
+        row0 = seq % n_rtile * 32;
+        if (unit >= n_units) return;
+        split = unit % n_split;
+        g = unit / n_split % n_kv_heads;
+        b = unit / n_split / n_kv_heads;
+    }
+    const int all_rows = group * T_q, n_rows = ROWS ? min(32, all_rows - row0) : all_rows;   // rows of the call, of this workgroup
     const int len = min(max(mix_len[b], 0), l_cap);
     const int n_tiles = (len + TK - 1) / TK;
-    const size_t part_base = (((size_t)b * n_kv_heads + g) * n_split + split) * (size_t)n_rows;
+    const size_t part_base = (((size_t)b * n_kv_heads + g) * n_split + split) * (size_t)all_rows + row0;
 
     const float c2 = scale * kLog2e;
     // (IND: Kmix / Vmix are the dense K / V of the layer, read through the row map)
@@ -513,7 +528,7 @@ __global__ __launch_bounds__(64 * NW, 2) void decode_wave_kernel(
 
     bf16x8 qreg[1][D / 16];
     {
-        const int rho = min(l32, n_rows - 1);
+        const int rho = row0 + min(l32, n_rows - 1);
         const int t = rho / group, hg = rho % group;
         const uint4* src = (const uint4*)(Qd + (((size_t)b * T_q + t) * n_q_heads + g * group + hg) * D);
 #pragma unroll
@@ -804,6 +819,9 @@ static vxl_status run_decode_wave(const vxl_attn_desc* d, float scale, const voi
     float* part_lse = (float*)((char*)ws + p.part_ml);
     const int group = d->n_q_heads / d->n_kv_heads;
     const int n_rows = group * T;
+    const int n_rtile = (n_rows + kRowBlock - 1) / kRowBlock;
+    const int units = p.n_split * d->n_kv_heads * batch;
+    const dim3 grid = n_rtile > 1 ? dim3((units + kXcds - 1) / kXcds * kXcds * n_rtile) : dim3(p.n_split, d->n_kv_heads, batch);
     constexpr int lds_bytes = 8 * 2 * kStepTile * D * 2;      // 8 tile pairs in either form
     static PerDeviceOnce attr;
     const vxl_status ast = attr.run([] {
@@ -813,26 +831,26 @@ static vxl_status run_decode_wave(const vxl_attn_desc* d, float scale, const voi
                                         hipFuncAttributeMaxDynamicSharedMemorySize, lds_bytes));
         VXL_HIP_TRY(hipFuncSetAttribute((const void*)decode_wave_kernel<D, 4, 2, true>,
                                         hipFuncAttributeMaxDynamicSharedMemorySize, lds_bytes));
+        VXL_HIP_TRY(hipFuncSetAttribute((const void*)decode_wave_kernel<D, 4, 2, false, true>,
+                                        hipFuncAttributeMaxDynamicSharedMemorySize, lds_bytes));
+        VXL_HIP_TRY(hipFuncSetAttribute((const void*)decode_wave_kernel<D, 4, 2, true, true>,
+                                        hipFuncAttributeMaxDynamicSharedMemorySize, lds_bytes));
         return VXL_OK;
     });
     if (ast != VXL_OK) return ast;
-    if (rm) {
-        // (the plan of the in-place form always has 4 waves; the row map of a wave's tiles must fit its LDS area)
-        if (p.split_len / (4 * kStepTile) > kMaxStepTpw) return VXL_ERR_UNSUPPORTED;
-        hipLaunchKernelGGL((decode_wave_kernel<D, 4, 2, true>), dim3(p.n_split, d->n_kv_heads, batch), dim3(256),
-                           lds_bytes, s, (const uint16_t*)Qd, (const uint16_t*)Kmix, (const uint16_t*)Vmix,
-                           mix_len, part_o, part_lse, T, d->n_q_heads, d->n_kv_heads, group, l_cap,
-                           p.split_len / (4 * kStepTile), scale, *rm);
-    } else if (p.step_waves == 8)
-        hipLaunchKernelGGL((decode_wave_kernel<D, 8, 1>), dim3(p.n_split, d->n_kv_heads, batch), dim3(512),
-                           lds_bytes, s, (const uint16_t*)Qd, (const uint16_t*)Kmix, (const uint16_t*)Vmix,
-                           mix_len, part_o, part_lse, T, d->n_q_heads, d->n_kv_heads, group, l_cap,
-                           p.split_len / (8 * kStepTile), scale, RowMap{});
-    else
-        hipLaunchKernelGGL((decode_wave_kernel<D, 4, 2>), dim3(p.n_split, d->n_kv_heads, batch), dim3(256),
-                           lds_bytes, s, (const uint16_t*)Qd, (const uint16_t*)Kmix, (const uint16_t*)Vmix,
-                           mix_len, part_o, part_lse, T, d->n_q_heads, d->n_kv_heads, group, l_cap,
-                           p.split_len / (4 * kStepTile), scale, RowMap{});
+    const int tpw = p.split_len / ((p.step_waves == 8 ? 8 : 4) * kStepTile);
+    // (the plan of the in-place form always has 4 waves; the row map of a wave's tiles must fit its LDS area)
+    if (rm && tpw > kMaxStepTpw) return VXL_ERR_UNSUPPORTED;
+#define VXL_LAUNCH(NW, ...)                                                                              \
+    hipLaunchKernelGGL((decode_wave_kernel<D, NW, __VA_ARGS__>), grid, dim3(64 * NW), lds_bytes, s,       \
+                       (const uint16_t*)Qd, (const uint16_t*)Kmix, (const uint16_t*)Vmix, mix_len, part_o, \
+                       part_lse, T, d->n_q_heads, d->n_kv_heads, group, l_cap, tpw, p.n_split, units, n_rtile, \
+                       scale, rm ? *rm : RowMap{})
+    if (rm) { if (n_rtile > 1) VXL_LAUNCH(4, 2, true, true); else VXL_LAUNCH(4, 2, true); }
+    else if (p.step_waves == 8) VXL_LAUNCH(8, 1);
+    else if (n_rtile > 1) VXL_LAUNCH(4, 2, false, true);
+    else VXL_LAUNCH(4, 2);
+#undef VXL_LAUNCH
     VXL_HIP_TRY(hipGetLastError());
     const size_t merge_lds = (size_t)(((p.n_split + 3) & ~3) + 256 / (D / 4) * D) * sizeof(float);
     hipLaunchKernelGGL((decode_merge_kernel<D>), dim3(n_rows, d->n_kv_heads, batch), dim3(256), merge_lds, s,
@@ -866,12 +884,12 @@ vxl_status decode_static_scratch(void** ptr) {
 vxl_status launch_decode_bf16(const vxl_attn_desc* d, float scale, const void* Qd, int batch, int T,
                               const void* Kmix, const void* Vmix, int l_cap, const int32_t* mix_len, void* O,
                               float* LSE, void* ws, hipStream_t s) {
-    const int n_rows = (d->n_q_heads / d->n_kv_heads) * T;
-    if (n_rows <= kRowBlock)
+    const DecodePlan p = decode_plan(d, batch, T, l_cap);
+    if (p.step_waves != 0)
         return d->head_dim == 128
                    ? run_decode_wave<128>(d, scale, Qd, batch, T, Kmix, Vmix, l_cap, mix_len, O, LSE, ws, s)
                    : run_decode_wave<64>(d, scale, Qd, batch, T, Kmix, Vmix, l_cap, mix_len, O, LSE, ws, s);
-    const bool big = decode_plan(d, batch, T, l_cap).use_ring != 0;
+    const bool big = p.use_ring != 0;
     if (d->head_dim == 128)
         return big ? run_decode_ring<128>(d, scale, Qd, batch, T, Kmix, Vmix, l_cap, mix_len, O, LSE, ws, s)
                    : run_decode<128, 1>(d, scale, Qd, batch, T, Kmix, Vmix, l_cap, mix_len, O, LSE, ws, s);
@@ -886,12 +904,12 @@ vxl_status launch_decode_bf16_inplace(const vxl_layout* L, const vxl_attn_desc* 
                                       void* O, float* LSE, void* ws, hipStream_t s) {
     const TokStrides ts = tok_strides(d, L->n_tokens);
     const RowMap rm{src_idx, (const uint16_t*)Ksp, (const uint16_t*)Vsp, ts.kh, ts.kt, L->s_total};
-    const int n_rows = (d->n_q_heads / d->n_kv_heads) * T;
-    if (n_rows <= kRowBlock)
+    const DecodePlan p = decode_plan(d, batch, T, l_cap, false);
+    if (p.step_waves != 0)
         return d->head_dim == 128
                    ? run_decode_wave<128>(d, scale, Qd, batch, T, K, V, l_cap, mix_len, O, LSE, ws, s, &rm)
                    : run_decode_wave<64>(d, scale, Qd, batch, T, K, V, l_cap, mix_len, O, LSE, ws, s, &rm);
-    const bool big = decode_plan(d, batch, T, l_cap, false).use_ring != 0;
+    const bool big = p.use_ring != 0;
     if (d->head_dim == 128)
         return big ? run_decode_ring<128>(d, scale, Qd, batch, T, K, V, l_cap, mix_len, O, LSE, ws, s, &rm)
                    : run_decode<128, 1>(d, scale, Qd, batch, T, K, V, l_cap, mix_len, O, LSE, ws, s, &rm);

@@ -1,0 +1,61 @@
+"""Decode calls whose stacked query rows fill several 32-row blocks over a short mixed set: the row blocks of a key
+split as separate workgroups, gathered and in place, against the oracle at the edges of the row blocks, the key tiles and
+the launch's grouping by eights."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from paper_2506_19225_amd import vxl, workloads as wl
+
+from gpu_util import assert_close, desc_of, gpu_decode, make_layout
+from test_gpu_inplace import check_case
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("hq,hkv,t,d,lens", [
+    (11, 1, 6, 128, [700, 33, 0]),                 # 66 rows: two rows in the last block
+    (14, 2, 5, 64, [1, 129]),                      # 35 rows, fewer tiles than waves
+    (14, 2, 5, 128, [2500, 2113, 0, 31, 64, 2049, 7, 1000]),      # 35 rows, two tiles per wave
+    (8, 1, 12, 64, [4097]),                        # 96 rows: whole blocks
+    (28, 4, 32, 128, [4352]),                      # 224 rows over the mixed set of a 16k-token prompt
+    (28, 4, 36, 128, [1029, 515]),                 # 252 rows, units that do not divide by eight
+    (28, 4, 64, 128, [1031]),                      # 448 rows
+    (7, 1, 128, 64, [300]),                        # 896 rows: 28 blocks on one XCD
+])
+def test_row_blocks_match_the_oracle(hq, hkv, t, d, lens):
+    rng = np.random.default_rng(81 + t)
+    l_cap, bsz = max(lens), len(lens)
+    w = wl.tiny_workload("bf16", hq, hkv, d, T=t, B=bsz, k=1, seed=81)
+    kmix = wl.round_to_bf16(rng.standard_normal((bsz, hkv, l_cap, d)).astype(np.float32))
+    vmix = wl.round_to_bf16(rng.standard_normal((bsz, hkv, l_cap, d)).astype(np.float32))
+    qd = wl.round_to_bf16(rng.standard_normal((bsz, t, hq, d)).astype(np.float32) * np.float32(0.5))
+    dk, dv = vxl.to_device(kmix, "bf16"), vxl.to_device(vmix, "bf16")
+    for b, n in enumerate(lens):                   # what lies past a length is never used
+        dk[b, :, n:] = float("nan")
+        dv[b, :, n:] = float("nan")
+    dl = torch.tensor(lens, dtype=torch.int32, device="cuda")
+    got, lse = gpu_decode(w, qd, dk, dv, dl, want_lse=True)
+    again, _ = gpu_decode(w, qd, dk, dv, dl, want_lse=True)
+    assert np.array_equal(got, again)
+    live = np.array(lens) > 0                      # (the oracle takes no empty set)
+    want, wlse = oracle.decode_lse(qd[live], kmix[live], vmix[live], np.array(lens, np.int32)[live])
+    assert_close(got[live], want, "bf16", head_axis=2, what=f"{hq * t // hkv} rows, d={d}")
+    assert np.abs(lse[live] - wlse).max() < 2e-2
+    assert not got[~live].any() and np.isneginf(lse[~live]).all()
+    # no more partial results than one row per `rows` keys (what callers of the fixed scratch rely on)
+    rows = hq // hkv * t
+    bound = bsz * hkv * max(1, l_cap // rows) * rows * (d + 1) * 4 + 512
+    assert vxl.workspace_bytes(vxl.OP_DECODE, None, desc_of(w), bsz, t, l_cap) <= bound
+
+
+@pytest.mark.parametrize("mode", ["kept_in_place", "pooled"])
+@pytest.mark.parametrize("t,bsz,d", [(6, 3, 128), (11, 1, 64), (23, 2, 128)])
+def test_row_blocks_in_place(mode, t, bsz, d):
+    rng = np.random.default_rng(83 + t)
+    w = wl.tiny_workload("bf16", 14, 2, d, T=t, B=bsz, k=3, seed=83, value_scale=0.5)
+    lay = wl.random_layout(rng, 9, 12, 1, 300)
+    _, k, v = wl.make_qkv(w, lay, with_q=False)
+    masks = (rng.random((bsz, 12)) < 0.4).astype(np.uint8)
+    check_case(w, lay, k, v, wl.make_decode_queries(w), masks, mode)
