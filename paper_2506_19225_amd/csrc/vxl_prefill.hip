@@ -7,9 +7,9 @@
 // Main kernel (prefill_dma_kernel): a persistent workgroup takes bands of query rows of one
 // segment (the prefix or a chunk) and walks 64-key tiles  history[0, ctx_len)  then  own
 // segment[0, diagonal]  with an online softmax; the arithmetic is in vxl_mfma.h.  256 rows and 8
-// waves per workgroup, tiles streamed into an LDS ring by direct global-to-LDS loads.  A second
-// instance of the same template (128 rows, 4 waves, two workgroups per compute unit) is kept as
-// an on-device cross-check.
+// waves per workgroup (128 rows and 4 waves for small prompts), tiles streamed into an LDS ring by
+// direct global-to-LDS loads.  A third instance of the same template (128 rows, 4 waves, a 2-stage
+// ring, two workgroups per compute unit) is kept as an on-device cross-check.
 #include <math.h>
 
 #include <algorithm>
@@ -320,10 +320,11 @@ vxl_status enable_big_lds(F kernel, int bytes) {
 
 static std::atomic<int> g_prefill_variant{0};
 static std::atomic<hipEvent_t> g_ev_start{nullptr}, g_ev_stop{nullptr};
-// Cross-check only (declared in vxl_debug.h): 0 = the default instance (8 waves, 256-row bands, one
-// workgroup per compute unit); 1 = the same kernel as two independent 4-wave workgroups per compute
-// unit (128-row bands, a 2-stage ring each, one meeting per tile).
-extern "C" void vxl_debug_prefill_variant(int v) { g_prefill_variant = v == 1 ? 1 : 0; }
+// Cross-check only (declared in vxl_debug.h): 0 = choose (8 waves, 256-row bands, one workgroup per
+// compute unit; for small prompts 4 waves, 128-row bands); 1 = the same kernel as two independent
+// 4-wave workgroups per compute unit (128-row bands, a 2-stage ring each, one meeting per tile); 2 = the
+// 8-wave instance whatever the size.
+extern "C" void vxl_debug_prefill_variant(int v) { g_prefill_variant = v == 1 || v == 2 ? v : 0; }
 // Measurement hook (declared in vxl_debug.h): when both events are set, every vxl_chunk_prefill
 // records them on its stream immediately before and after the main attention kernel (the pre-pass
 // is outside the bracket).
@@ -371,7 +372,7 @@ static vxl_status run_prefill_dma(const vxl_layout* L, const vxl_attn_desc* d, f
     const int group = d->n_q_heads / d->n_kv_heads;
     const int xpg = 8 % d->n_kv_heads == 0 ? 8 / d->n_kv_heads : 0;
     constexpr int wl_i = NW == 8 ? 1 : 0;                     // the work list cut in bands of 32 * NW rows
-    constexpr int per_cu = 8 / NW;                            // workgroups per compute unit
+    constexpr int per_cu = std::min(8 / NW, 163840 / C::LDS_BYTES);   // workgroups per compute unit
     const long long n_pairs = (long long)L->n_work[wl_i] * d->n_q_heads;
     // no more workgroups than pairs (rounded up to whole rounds over the 8 XCDs when queues are per XCD group)
     const unsigned n_blocks = (unsigned)std::min<long long>((long long)per_cu * (n_cus / 8 * 8),
@@ -405,11 +406,40 @@ vxl_status device_cu_count(int* n_cus) {
     return VXL_OK;
 }
 
+// Parts with cells of all bands of `blocks` 32-row blocks (see the cut in prefill_dma_kernel).
+static long long part_count(const vxl_layout* L, const vxl_attn_desc* d, int blocks) {
+    const int group = d->n_q_heads / d->n_kv_heads;
+    long long n = 0;
+    for (const Segment& sg : L->segs) {
+        const int b = (sg.q_len + 31) / 32;
+        n += (long long)(b / blocks) * group + ((long long)(b % blocks) * group + blocks - 1) / blocks;
+    }
+    return n * d->n_kv_heads;
+}
+
 vxl_status launch_prefill_bf16(const vxl_layout* L, const vxl_attn_desc* d, float scale, const void* Q,
                                const void* K, const void* V, void* O, float* LSE, void* ws, hipStream_t s) {
     if (g_prefill_variant == 1)
         return d->head_dim == 128 ? run_prefill_dma<128, 2, 4>(L, d, scale, Q, K, V, O, LSE, ws, s)
                                   : run_prefill_dma<64, 2, 4>(L, d, scale, Q, K, V, O, LSE, ws, s);
+    // Small prompts: bands of 128 rows, so that twice as many compute units have work, and one wave per
+    // SIMD, which walks its tiles at twice the speed of two; the ring keeps its four stages.  Better
+    // while every part has a compute unit of its own (D = 128, before -> after: 14 heads over 900 ragged
+    // tokens 20.6 -> 16.6 us, 28 heads over 664 tokens 19.7 -> 15.7, 8 heads over 2,112 tokens 25.0 ->
+    // 19.1; but 328 parts 23.0 -> 26.7, 264 parts 34.6 -> 38.9), and as long as parts gain on bands at all
+    // (chunks of two cells make as many parts either way).  At D = 64 two such workgroups fit a compute
+    // unit and share it as well as one of eight waves does once that form needs a second round (896 parts
+    // 51.5 -> 47.7 us, 512 parts 52.9 -> 48.5; 1,792 and 2,048 parts 1 % and 3 % slower), but not where it
+    // gets by with one (452 parts, 226 of eight waves: 25.7 -> 28.7).
+    if (g_prefill_variant == 0) {
+        int n_cus = 0;
+        const vxl_status st = device_cu_count(&n_cus);
+        if (st != VXL_OK) return st;
+        const long long parts4 = part_count(L, d, 4), parts8 = part_count(L, d, 8);
+        if ((parts4 <= n_cus && parts4 > parts8) || (d->head_dim == 64 && parts8 > n_cus && parts4 <= 4ll * n_cus && parts4 > parts8))
+            return d->head_dim == 128 ? run_prefill_dma<128, 4, 4>(L, d, scale, Q, K, V, O, LSE, ws, s)
+                                      : run_prefill_dma<64, 4, 4>(L, d, scale, Q, K, V, O, LSE, ws, s);
+    }
     return d->head_dim == 128 ? run_prefill_dma<128, 4>(L, d, scale, Q, K, V, O, LSE, ws, s)
                               : run_prefill_dma<64, 4>(L, d, scale, Q, K, V, O, LSE, ws, s);
 }

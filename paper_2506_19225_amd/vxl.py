@@ -375,8 +375,9 @@ def debug_decode_step_waves(waves: int) -> None:
 
 
 def debug_prefill_variant(variant: int) -> None:
-    """Cross-check only: 0 = the default instance (8 waves, one workgroup per compute unit);
-    1 = the same kernel as two independent 4-wave workgroups per compute unit."""
+    """Cross-check only: 0 = the library chooses (8 waves, one workgroup per compute unit; 4 waves for
+    small prompts); 1 = the same kernel as two independent 4-wave workgroups per compute unit; 2 = the
+    8-wave instance whatever the size."""
     lib().vxl_debug_prefill_variant(int(variant))
 
 

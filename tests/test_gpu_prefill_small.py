@@ -1,0 +1,70 @@
+"""Small prompts, which take the 4-wave pre-filling instance: both instances against the oracle on layouts on either
+side of the line between them (256 parts at D = 128) and on ragged ones, with a look-back window and token-major
+storage."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2506_19225_amd import vxl, workloads as wl
+
+from gpu_util import assert_close, desc_of, gpu_prefill, make_layout
+from test_gpu_parity import oracle_prefill
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("variant", [0, 2])
+@pytest.mark.parametrize("hq,hkv,d,prefix,lens,window", [
+    (8, 1, 128, 0, [256] * 16, 0),                 # 256 parts: the last size of the 4-wave instance
+    (8, 1, 128, 1, [256] * 16, 0),                 # 258 parts
+    (14, 2, 128, 64, [130, 319, 201, 256], 100),   # ragged bands: one row, one block, a full band
+    (7, 1, 128, 33, [1, 31, 129, 128, 127], 40),
+    (28, 4, 128, 64, [160, 161], 0),
+    (4, 4, 64, 17, [200] * 5 + [64], 64),          # one head per KV head
+    (14, 2, 64, 0, [97, 400], 0),
+    (14, 2, 64, 30, [256] * 19, 0),                # two 4-wave workgroups per compute unit
+])
+def test_small_prompts_match_the_oracle(variant, hq, hkv, d, prefix, lens, window):
+    rng = np.random.default_rng(91 + sum(lens))
+    starts = prefix + np.concatenate([[0], np.cumsum(lens)[:-1]])
+    kept = [np.sort(s + rng.choice(n, max(1, n // 8), replace=False)).astype(np.int32) for s, n in zip(starts, lens)]
+    lay = wl.layout_from_lists(prefix, lens, kept)
+    w = wl.tiny_workload("bf16", hq, hkv, d, T=1, B=1, k=1, seed=91, value_scale=1.0)
+    q, k, v = wl.make_qkv(w, lay)
+    vxl.debug_prefill_variant(variant)
+    try:
+        got, lse = gpu_prefill(w, lay, q, k, v, want_lse=True, gl=make_layout(lay, window=window))
+    finally:
+        vxl.debug_prefill_variant(0)
+    want, wlse = oracle_prefill(q, k, v, lay, return_lse=True, window=window)
+    assert_close(got, want, "bf16", what=f"{lens[:4]} variant {variant}")
+    assert np.abs(lse - wlse).max() < 2e-2
+
+
+@pytest.mark.parametrize("d", [64, 128])
+def test_small_prompt_token_major_equals_head_major(d):
+    """The strided instance of the 4-wave form gives the dense one's bits; a replayed graph gives them again."""
+    lay = wl.layout_from_lists(20, [150, 70, 300], [wl.strided_kept(20, 150, 10), wl.strided_kept(170, 70, 3),
+                                                    wl.strided_kept(240, 300, 30)])
+    w = wl.tiny_workload("bf16", 14, 2, d, T=1, B=1, k=1, seed=92)
+    q, k, v = (vxl.to_device(x, "bf16") for x in wl.make_qkv(w, lay))
+    gl = make_layout(lay)
+    outs = []
+    for token_major in (False, True):
+        desc = vxl.make_desc(14, 2, d, "bf16", token_major=token_major)
+        ten = [x.transpose(0, 1).contiguous() if token_major else x for x in (q, k, v)]
+        o = torch.empty_like(ten[0])
+        ws = torch.randint(0, 256, (vxl.workspace_bytes(vxl.OP_PREFILL, gl, desc),), dtype=torch.uint8, device="cuda")
+        vxl.chunk_prefill(gl, desc, *ten, o, None, ws)
+        torch.cuda.synchronize()
+        graph = torch.cuda.CUDAGraph()
+        first = o.clone()
+        with torch.cuda.graph(graph):
+            vxl.chunk_prefill(gl, desc, *ten, o, None, ws)
+        for _ in range(3):
+            o.fill_(float("nan"))
+            graph.replay()
+            torch.cuda.synchronize()
+            assert torch.equal(o, first)
+        outs.append(first.transpose(0, 1).contiguous() if token_major else first)
+    assert torch.equal(*outs)
