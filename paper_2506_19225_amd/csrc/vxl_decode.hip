@@ -392,7 +392,7 @@ __global__ __launch_bounds__(64 * NW, 2) void decode_wave_kernel(
     constexpr int TK = kStepTile;
     constexpr int TILE_ELEMS = TK * D;                         // one unpadded tile
     extern __shared__ __attribute__((aligned(16))) uint16_t lds[];
-    __shared__ float stats[NW][32][2];                         // per wave and row: reference logit, sum
+    __shared__ float2 stats[NW][32];                           // per wave and row: reference logit, sum
     const int tid = threadIdx.x, lane = tid & 63, l32 = lane & 31, hi = lane >> 5;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     uint16_t* Kw = lds + wave * NBUF * 2 * TILE_ELEMS;         // this wave's K tile, then its V tile (NBUF times)
@@ -599,8 +599,14 @@ __global__ __launch_bounds__(64 * NW, 2) void decode_wave_kernel(
     }
 
     // ---- merge the waves (their tile buffers are free now): area [32 rows][D] floats per wave ----
+    // A chain of LDS round trips at the end of every call, so it moves 16 bytes per lane and step: piece c4
+    // of a row lies at c4 ^ row (mod the D / 4 pieces), which spreads the rows that a wave writes side by
+    // side over all banks (unswizzled they all start at the same one).
+    // Against one float per lane and step: one layer of a generated token over 18,176 keys (with the merge
+    // of the splits) 14.5 -> 13.7 us, a question of 224 rows on a 16k prompt, selection to decode, 33.5 -> 32.0.
     static_assert(32 * D * 4 <= 2 * TILE_ELEMS * 2, "merge area must fit a wave's tile pair");
-    float* red = (float*)Kw;
+    constexpr int PPR4 = D / 4;                                // 16-byte pieces per row
+    float4* red = (float4*)Kw;
     const float l_tot = l_run + __shfl_xor(l_run, 32);
     if (l32 < n_rows) {
 #pragma unroll
@@ -610,29 +616,40 @@ __global__ __launch_bounds__(64 * NW, 2) void decode_wave_kernel(
                 float4 v;
                 v.x = o[0][db][rq * 4 + 0]; v.y = o[0][db][rq * 4 + 1];
                 v.z = o[0][db][rq * 4 + 2]; v.w = o[0][db][rq * 4 + 3];
-                *(float4*)(red + l32 * D + db * 32 + rq * 8 + hi * 4) = v;
+                red[l32 * PPR4 + ((db * 8 + rq * 2 + hi) ^ (l32 & (PPR4 - 1)))] = v;
             }
-        if (hi == 0) { stats[wave][l32][0] = m_run; stats[wave][l32][1] = l_tot; }
+        if (hi == 0) stats[wave][l32] = make_float2(m_run, l_tot);
     }
     __syncthreads();
-    constexpr int WSTRIDE = NBUF * 2 * TILE_ELEMS / 2;         // floats between the waves' areas
-    const float* red0 = (const float*)lds;
-    for (int e = tid; e < n_rows * D; e += 64 * NW) {
-        const int row = e / D, dd = e % D;
+    constexpr int WSTRIDE = NBUF * 2 * TILE_ELEMS / 8;         // 16-byte pieces between the waves' areas
+    const float4* red0 = (const float4*)lds;
+    for (int e = tid; e < n_rows * PPR4; e += 64 * NW) {
+        const int row = e / PPR4, c4 = e % PPR4, at = row * PPR4 + (c4 ^ (row & (PPR4 - 1)));
+        float2 st[NW];
+        float4 v[NW];
         float M = -INFINITY;
 #pragma unroll
-        for (int w = 0; w < NW; ++w) M = fmaxf(M, stats[w][row][0]);
-        float acc = 0.f, L = 0.f;
+        for (int w = 0; w < NW; ++w) {
+            st[w] = stats[w][row];
+            v[w] = red0[w * WSTRIDE + at];
+            M = fmaxf(M, st[w].x);
+        }
+        float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
+        float L = 0.f;
 #pragma unroll
         for (int w = 0; w < NW; ++w) {
-            const float mw = stats[w][row][0];
-            const float f = mw == -INFINITY ? 0.f : __builtin_amdgcn_exp2f((mw - M) * c2);
-            L = fmaf(f, stats[w][row][1], L);
-            acc = fmaf(f, mw == -INFINITY ? 0.f : red0[w * WSTRIDE + row * D + dd], acc);
+            const bool some = st[w].x != -INFINITY;
+            const float f = some ? __builtin_amdgcn_exp2f((st[w].x - M) * c2) : 0.f;
+            L = fmaf(f, st[w].y, L);
+            acc.x = fmaf(f, some ? v[w].x : 0.f, acc.x);
+            acc.y = fmaf(f, some ? v[w].y : 0.f, acc.y);
+            acc.z = fmaf(f, some ? v[w].z : 0.f, acc.z);
+            acc.w = fmaf(f, some ? v[w].w : 0.f, acc.w);
         }
         const bool empty = M == -INFINITY;
-        part_o[(part_base + row) * D + dd] = empty ? 0.f : acc / L;
-        if (dd == 0) part_lse[part_base + row] = empty ? -INFINITY : M * c2 + __builtin_amdgcn_logf(L);
+        *(float4*)(part_o + (part_base + row) * D + c4 * 4) =
+            empty ? make_float4(0.f, 0.f, 0.f, 0.f) : make_float4(acc.x / L, acc.y / L, acc.z / L, acc.w / L);
+        if (c4 == 0) part_lse[part_base + row] = empty ? -INFINITY : M * c2 + __builtin_amdgcn_logf(L);
     }
 }
 
