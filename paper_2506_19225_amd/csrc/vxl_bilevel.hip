@@ -275,13 +275,17 @@ __global__ __launch_bounds__(512) void topk_from_scores_kernel(const float* __re
 // group m = rows [floor(m*len/cnt), floor((m+1)*len/cnt)); pooled row soff[c] + m is the mean of
 // the group's rows, K and V alike.  LPR lanes per pooled row (a 16-byte piece each), fp32 sums in
 // row order, one division, one rounding to the storage dtype.
+// Bound by HBM (dense K and V once), as long as enough loads are in flight: four rows of K and of V
+// are requested before the first addition (clamped to the group's last row, which is not added
+// again), a result is stored as one piece, and the chunk of a row is found by two or three probes of
+// its LPR lanes instead of a chain of halvings.  K and V of 131,328 tokens (303 MB in and out):
+// 64.5 us with one row at a time and stores of two bytes, 62.5 so (4.8 TB/s).
 // ------------------------------------------------------------------------------------------
 __device__ __forceinline__ void st_round(float* p, float v) { *p = v; }
 __device__ __forceinline__ void st_round(uint16_t* p, float v) {
-    uint32_t b = __float_as_uint(v);
-    if ((b & 0x7fffffffu) > 0x7f800000u) { *p = 0x7fc0; return; }
-    b += 0x7fffu + ((b >> 16) & 1u);
-    *p = (uint16_t)(b >> 16);
+    const uint32_t b = __float_as_uint(v);
+    const uint32_t up = b + 0x7fffu + ((b >> 16) & 1u);
+    *p = (b & 0x7fffffffu) > 0x7f800000u ? 0x7fc0 : (uint16_t)(up >> 16);
 }
 
 template <typename T, int D>
@@ -295,11 +299,14 @@ __global__ __launch_bounds__(256) void pool_sparse_kernel(const T* __restrict__ 
     constexpr int LPR = D / EPC;                    // lanes per row
     constexpr int ROWS = 256 / LPR;
     const int r = blockIdx.x * ROWS + threadIdx.x / LPR, part = threadIdx.x % LPR, g = blockIdx.y;
-    if (r >= s_total) return;
-    int c = 0, hi_c = n_chunks;                     // last chunk with soff[c] <= r (its range holds r)
-    while (hi_c - c > 1) {
-        const int mid = (c + hi_c) >> 1;
-        if (soff[mid] <= r) c = mid; else hi_c = mid;
+    if (r >= s_total) return;                       // (all lanes of the row)
+    int c = 0;                                      // last chunk with soff[c] <= r: it lies in [c, c + span)
+    for (int span = n_chunks; span > 1;) {
+        const int step = (span + LPR - 1) / LPR;
+        const unsigned long long hit = __ballot(part * step < span && soff[min(c + part * step, n_chunks)] <= r);
+        const int last = __popcll((hit >> (threadIdx.x & 63 & ~(LPR - 1))) & ((1ull << LPR) - 1)) - 1;   // (soff ascends, soff[c] <= r)
+        c += last * step;
+        span = min(step, span - last * step);
     }
     const long long len = bounds[c + 1] - bounds[c], cnt = soff[c + 1] - soff[c], m = r - soff[c];
     const int lo = bounds[c] + (int)((m * len) / cnt), hi = bounds[c] + (int)(((m + 1) * len) / cnt);
@@ -308,18 +315,31 @@ __global__ __launch_bounds__(256) void pool_sparse_kernel(const T* __restrict__ 
     for (int i = 0; i < EPC; ++i) ak[i] = av[i] = 0.f;
     const uint4* kp = (const uint4*)K + (size_t)g * kv_head_u4 + part;   // (K, V strides in 16-byte units)
     const uint4* vp = (const uint4*)V + (size_t)g * kv_head_u4 + part;
-    for (int t = lo; t < hi; ++t) {
-        const uint4 kq = kp[(size_t)t * kv_tok_u4], vq = vp[(size_t)t * kv_tok_u4];
-        const T* ke = (const T*)&kq;
-        const T* ve = (const T*)&vq;
+    for (int t = lo; t < hi; t += 4) {
+        uint4 kq[4], vq[4];
 #pragma unroll
-        for (int i = 0; i < EPC; ++i) { ak[i] += ld(ke + i); av[i] += ld(ve + i); }
+        for (int u = 0; u < 4; ++u) {
+            const size_t at = (size_t)min(t + u, hi - 1) * kv_tok_u4;
+            kq[u] = kp[at];
+            vq[u] = vp[at];
+        }
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            if (t + u < hi) {
+                const T* ke = (const T*)&kq[u];
+                const T* ve = (const T*)&vq[u];
+#pragma unroll
+                for (int i = 0; i < EPC; ++i) { ak[i] += ld(ke + i); av[i] += ld(ve + i); }
+            }
+        }
     }
     const float n = (float)(hi - lo);
-    T* ko = Ksp + ((size_t)g * s_total + r) * D + part * EPC;
-    T* vo = Vsp + ((size_t)g * s_total + r) * D + part * EPC;
+    __attribute__((aligned(16))) T ko[EPC], vo[EPC];
 #pragma unroll
     for (int i = 0; i < EPC; ++i) { st_round(ko + i, ak[i] / n); st_round(vo + i, av[i] / n); }
+    const size_t out = ((size_t)g * s_total + r) * LPR + part;
+    ((uint4*)Ksp)[out] = *(const uint4*)ko;
+    ((uint4*)Vsp)[out] = *(const uint4*)vo;
 }
 
 // ------------------------------------------------------------------------------------------

@@ -58,6 +58,18 @@ def test_pool_config0_fp32_and_ragged_groups():
         check_pool(w, lay, k, v)
 
 
+@pytest.mark.parametrize("dtype,d", [("f32", 128), ("bf16", 128), ("bf16", 64)])
+@pytest.mark.parametrize("chunks", [1, 16, 17, 257, 300])
+def test_pool_finds_chunks(dtype, d, chunks):
+    """Chunk counts around the powers of the probes per row (8, 16 or 32), empty kept sets in runs and
+    at both ends, group lengths around the four rows requested together."""
+    rng = np.random.default_rng(chunks)
+    w = wl.tiny_workload(dtype, 4, 2, d, T=1, B=1, k=1, seed=chunks)
+    lay = wl.random_layout(rng, 5, chunks, 1, 19, allow_empty_kept=True)
+    _, k, v = wl.make_qkv(w, lay, with_q=False)
+    check_pool(w, lay, k, v)
+
+
 @pytest.mark.parametrize("name", ["config0", "config1", "config4"])
 def test_pooled_chain(name):
     """select -> pool -> gather (pooled) -> decode, everything on the device; the gathered set is
