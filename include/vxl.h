@@ -27,7 +27,11 @@
  *     library are declared in vxl_debug.h, not here.
  *   - Supported: dtype F32 or BF16; head_dim 64 or 128; n_q_heads a multiple of n_kv_heads;
  *     n_chunks <= VXL_MAX_CHUNKS.  BF16 runs on the matrix cores with fp32 accumulation; F32
- *     runs on the vector ALUs in fp32.
+ *     on their fp32 instruction (fp32 operands, fp32 accumulation).
+ *   - Infinities and NaN: with F32 storage a row's result depends on the keys and values it attends
+ *     to and on no others.  With BF16 storage a value that is not finite can also reach the rows
+ *     whose 64-token tile holds it although it is masked for them (0 * inf).  A row all of whose
+ *     logits are -inf, or one of them NaN or +inf, has no softmax: F32 gives NaN for O and LSE.
  */
 #ifndef VXL_H
 #define VXL_H

@@ -14,8 +14,10 @@
 //                  V[key 4*j + r][64*blk + 4*i + e], again one instruction per element of a piece;
 //                  result register r' of (blk, e): O[row i][64*blk + 16*j + 4*r' + e]
 // so there is no transposition, no LDS and no cross-lane traffic but the row maximum, and every
-// load is 16 bytes per lane (64 contiguous bytes per key row for K, 256 for V).  The K pieces of the
-// next tile are requested before the softmax of the current one, its V pieces before its scores.
+// load is 16 bytes per lane (64 contiguous bytes per key row for K, 256 for V).  At D = 64 the K pieces of
+// the next tile are requested before the softmax of the current one; at D = 128 a tile requests its own
+// (a wave has few tiles, and one tile's pieces more cost registers and a wait at the end: pre-filling of 1,335
+// tokens, 8 query heads on 4 KV heads, 44.0 us ahead, 42.8 so).
 //
 // A wave that owns one query row and adds one key at a time took, at 576 tokens, two heads and
 // D = 64, 51 us for the pre-filling and 95 us for 8 query tokens over 352 mixed rows; these kernels
@@ -68,11 +70,18 @@ struct RowsMapped {
     __device__ __forceinline__ const float* vrow(int e) const { return e >= 0 ? v + (size_t)e * tok : vsp + (size_t)~e * d; }
 };
 
+template <int D>
+__device__ __forceinline__ void load_q_f32(const float* qrow, float4 (&q)[D / 16]) {
+    const int j = (threadIdx.x & 63) >> 4;
+#pragma unroll
+    for (int s = 0; s < D / 16; ++s) q[s] = *(const float4*)(qrow + 16 * s + 4 * j);
+}
+
 // One wave: 16 query rows (pieces in q) over the slots [lo, hi); slots beyond `lim` (per lane: the
 // lane's own row) are masked.  m, l: running maximum and this lane's share of the running sum.
 template <int D, typename Rows>
-__device__ __forceinline__ void attend_f32(const Rows& rows, const float4 (&q)[D / 16], int lo, int hi, int lim,
-                                           float scale, float& m, float& l, f32x4 (&o)[D / 16]) {
+__device__ __forceinline__ void attend_tiles(const Rows& rows, const float4 (&q)[D / 16], int lo, int hi, int lim,
+                                             float scale, float& m, float& l, f32x4 (&o)[D / 16]) {
     constexpr int KB = kF32KB, TILE = 16 * KB;
     const int lane = threadIdx.x & 63, i = lane & 15, j = lane >> 4;
     if (lo >= hi) return;
@@ -91,9 +100,10 @@ __device__ __forceinline__ void attend_f32(const Rows& rows, const float4 (&q)[D
         }
     };
     entries(lo, ent);
-    load_k(ent);
+    if (D == 64) load_k(ent);
     for (int t = lo; t < hi; t += TILE) {
         int next[KB];
+        if (D == 128) load_k(ent);
         entries(min(t + TILE, hi - 1), next);
 #pragma unroll
         for (int kb = 0; kb < KB; ++kb)
@@ -114,7 +124,7 @@ __device__ __forceinline__ void attend_f32(const Rows& rows, const float4 (&q)[D
                 for (int kb = 0; kb < KB; ++kb)
                     s[kb] = __builtin_amdgcn_mfma_f32_16x16x4f32(((const float*)&k[kb][x])[e], ((const float*)&q[x])[e],
                                                                  s[kb], 0, 0, 0);
-        load_k(next);                                         // (the last tile fetches its last row again)
+        if (D == 64) load_k(next);                            // (the last tile fetches its last row again)
         float mx = -INFINITY;
 #pragma unroll
         for (int kb = 0; kb < KB; ++kb)
@@ -154,23 +164,98 @@ __device__ __forceinline__ void attend_f32(const Rows& rows, const float4 (&q)[D
     }
 }
 
-template <int D>
-__device__ __forceinline__ void load_q_f32(const float* qrow, float4 (&q)[D / 16]) {
-    const int j = (threadIdx.x & 63) >> 4;
+// The same row by row, a key per lane for the scores and a column per lane for O, over the slots a row sees
+// and no others.
+template <int D, typename Rows, typename QRow>
+__device__ __forceinline__ void attend_rows(const Rows& rows, QRow q_row, int lo, int hi, int lim, float scale, float& m,
+                                            float& l, f32x4 (&o)[D / 16]) {
+    const int lane = threadIdx.x & 63, i = lane & 15, j = lane >> 4;
+#pragma unroll 1
+    for (int row = 0; row < kF32Rows; ++row) {
+        const int last = min(hi - 1, __builtin_amdgcn_readlane(lim, row));
+        const float* qp = q_row(row);
+        float m_row = -INFINITY, l_row = 0.f, acc[D / 64];
 #pragma unroll
-    for (int s = 0; s < D / 16; ++s) q[s] = *(const float4*)(qrow + 16 * s + 4 * j);
+        for (int x = 0; x < D / 64; ++x) acc[x] = 0.f;
+#pragma unroll 1
+        for (int t = lo; t <= last; t += 64) {
+            const int ent = rows.entry(min(t + lane, last));
+            const float* kp = rows.krow(ent);
+            float s = 0.f;
+#pragma unroll 1
+            for (int d = 0; d < D; d += 4) {
+                const float4 qd = *(const float4*)(qp + d), kd = *(const float4*)(kp + d);
+                s = fmaf(qd.w, kd.w, fmaf(qd.z, kd.z, fmaf(qd.y, kd.y, fmaf(qd.x, kd.x, s))));
+            }
+            s = t + lane <= last ? s * scale : -INFINITY;
+            float m_new = s, sum;
+#pragma unroll
+            for (int x = 32; x > 0; x >>= 1) m_new = fmaxf(m_new, __shfl_xor(m_new, x));
+            m_new = fmaxf(m_new, m_row);
+            const float ref = m_new == -INFINITY ? 0.f : m_new, alpha = expf(m_row - ref), p = expf(s - ref);
+            sum = p;
+#pragma unroll
+            for (int x = 32; x > 0; x >>= 1) sum += __shfl_xor(sum, x);
+            l_row = l_row * alpha + sum;
+            m_row = m_new;
+#pragma unroll
+            for (int x = 0; x < D / 64; ++x) acc[x] *= alpha;
+#pragma unroll 1
+            for (int key = 0; key <= min(63, last - t); ++key) {
+                const float* vp = rows.vrow(__shfl(ent, key)) + lane;
+                const float pk = __shfl(p, key);
+#pragma unroll
+                for (int x = 0; x < D / 64; ++x) acc[x] = fmaf(pk, vp[64 * x], acc[x]);
+            }
+        }
+        if (i == row) {
+            m = m_row;
+            l = j == 0 ? l_row : 0.f;
+        }
+#pragma unroll
+        for (int x = 0; x < D / 16; ++x)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const float v = __shfl(acc[x / 4], 16 * j + 4 * r + x % 4);
+                if (i == row) o[x][r] = v;
+            }
+    }
 }
+
+// A row's result depends on nothing but the slots it sees.  In a tile, a slot that a row does not see (beyond
+// its limit, or the repetitions behind the last slot) enters the product as 0 * V, which is 0 only while V is
+// finite; a result that is not finite is therefore formed again without the tiles, in a loop so small that the
+// tiles keep their registers (without check and loop -> with them, 4 KV heads: D = 128, eight queries of two
+// rows over 390 keys 14.1 -> 14.6 us; D = 64, pre-filling of 847 tokens 9.7 -> 9.9).  q_row(row): the Q row.
+template <int D, typename Rows, typename QRow>
+__device__ __forceinline__ void attend_f32(const Rows& rows, QRow q_row, int lo, int hi, int lim, float scale, float& m,
+                                           float& l, f32x4 (&o)[D / 16]) {
+    float4 q[D / 16];
+    load_q_f32<D>(q_row(threadIdx.x & 15), q);
+    attend_tiles<D>(rows, q, lo, hi, lim, scale, m, l, o);
+    float z = 0.f;                                            // stays 0, or NaN
+#pragma unroll
+    for (int x = 0; x < D / 16; ++x)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) z = fmaf(o[x][r], 0.f, z);
+    if (__builtin_expect(__builtin_amdgcn_ballot_w64(z != z) != 0, 0))
+        attend_rows<D>(rows, q_row, lo, hi, lim, scale, m, l, o);
+}
+
+// LSE of a row that sees a key: like its O not a number if all its logits are -inf or one is NaN or +inf.
+__device__ __forceinline__ float lse_f32(float m, float l) { return l > 0.f ? m + logf(l) : NAN; }
 
 // The waves of one block of rows, merged in wave order through LDS: every wave leaves its (m, l, O),
 // then thread `tid` of `n_thr` forms the elements tid, tid + n_thr, ... of the 16 x D block and hands
-// them, four neighbouring d at a time, to store(row, d, float4 O, float lse).
+// them, four neighbouring d at a time, to store(row, d, float4 O, float lse).  A block that sees no key at
+// all (`some` false) has O = 0 and LSE = -inf.
 template <int D, int W>
 struct MergeF32 {
     static constexpr int ROW = D + 4;                         // (padded: 16 rows in distinct banks)
     static constexpr int FLOATS = W * (kF32Rows * ROW + 2 * kF32Rows);
     template <typename Store>
     static __device__ __forceinline__ void run(float* lds, int w, int tid, int n_thr, float m, float l,
-                                               const f32x4 (&o)[D / 16], Store store) {
+                                               const f32x4 (&o)[D / 16], bool some, Store store) {
         const int lane = threadIdx.x & 63, i = lane & 15, j = lane >> 4;
         float* stat = lds + W * kF32Rows * ROW;               // [W][16][2]
         l += __shfl_xor(l, 16);
@@ -198,8 +283,8 @@ struct MergeF32 {
                 L = fmaf(f, stat[(x * kF32Rows + row) * 2 + 1], L);
                 a.x = fmaf(f, p.x, a.x); a.y = fmaf(f, p.y, a.y); a.z = fmaf(f, p.z, a.z); a.w = fmaf(f, p.w, a.w);
             }
-            const float inv = L > 0.f ? 1.f / L : 0.f;        // (no visible key: O = 0, LSE = -inf)
-            store(row, d, make_float4(a.x * inv, a.y * inv, a.z * inv, a.w * inv), L > 0.f ? M + logf(L) : -INFINITY);
+            const float inv = some ? 1.f / L : 0.f;
+            store(row, d, make_float4(a.x * inv, a.y * inv, a.z * inv, a.w * inv), some ? lse_f32(M, L) : -INFINITY);
         }
     }
 };
@@ -226,9 +311,11 @@ __global__ __launch_bounds__(256, 2) void prefill_f32_kernel(
     const int rho0 = (blockIdx.y * (4 / KS) + wave / KS) * kF32Rows;
     if (rho0 >= rows_band) return;                            // (KS > 1: the whole workgroup)
     const int rho = min(rho0 + i, rows_band - 1);
-    const int t = t0 + rho / group, h = g * group + rho % group;
-    float4 q[D / 16];
-    load_q_f32<D>(Q + (size_t)h * q_head + (size_t)(sg.q_start + t) * q_tok, q);
+    const int t = t0 + rho / group;
+    auto q_row = [&](int row) __attribute__((always_inline)) {
+        const int r = min(rho0 + row, rows_band - 1);
+        return Q + (size_t)(g * group + r % group) * q_head + (size_t)(sg.q_start + t0 + r / group) * q_tok;
+    };
 
     const RowsSegment rows{K + (size_t)g * kv_head, V + (size_t)g * kv_head, tile_src, sg.ctx_len,
                            sg.q_start - sg.back, kv_tok};
@@ -240,7 +327,7 @@ __global__ __launch_bounds__(256, 2) void prefill_f32_kernel(
     f32x4 o[D / 16];
 #pragma unroll
     for (int x = 0; x < D / 16; ++x) o[x] = f32x4{0.f, 0.f, 0.f, 0.f};
-    attend_f32<D>(rows, q, lo, hi, sg.ctx_len + sg.back + t, scale, m, l, o);
+    attend_f32<D>(rows, q_row, lo, hi, sg.ctx_len + sg.back + t, scale, m, l, o);
 
     auto store = [&](int row, int d, float4 val, float lse) __attribute__((always_inline)) {
         const int rr = rho0 + row;
@@ -250,11 +337,11 @@ __global__ __launch_bounds__(256, 2) void prefill_f32_kernel(
         if (LSE && d == 0) LSE[(size_t)hh * n_tokens + tt] = lse;
     };
     if constexpr (KS > 1) {
-        MergeF32<D, KS>::run(lds, wave, threadIdx.x, 256, m, l, o, store);
+        MergeF32<D, KS>::run(lds, wave, threadIdx.x, 256, m, l, o, true, store);
     } else {
         l += __shfl_xor(l, 16);
         l += __shfl_xor(l, 32);
-        const float inv = 1.f / l, lse = m + logf(l);
+        const float inv = 1.f / l, lse = lse_f32(m, l);
         const int j = lane >> 4;
 #pragma unroll
         for (int b = 0; b < D / 64; ++b)
@@ -280,13 +367,13 @@ __global__ __launch_bounds__(64 * DecodeF32<D>::W, DecodeF32<D>::W / 4) void dec
     int n_kv_heads, int group, int l_cap, int s_total, long long kv_head, long long kv_tok, float scale) {
     constexpr int W = DecodeF32<D>::W;
     extern __shared__ __attribute__((aligned(16))) float lds_f[];
-    const int lane = threadIdx.x & 63, i = lane & 15;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int g = blockIdx.y, b = blockIdx.z;
     const int n_rows = T_q * group, rho0 = blockIdx.x * kF32Rows;
-    const int rho = min(rho0 + i, n_rows - 1);
-    float4 q[D / 16];
-    load_q_f32<D>(Qd + (((size_t)b * T_q + rho / group) * n_q_heads + g * group + rho % group) * D, q);
+    auto q_row = [&](int row) __attribute__((always_inline)) {
+        const int r = min(rho0 + row, n_rows - 1);
+        return Qd + (((size_t)b * T_q + r / group) * n_q_heads + g * group + r % group) * D;
+    };
     const int n_keys = min(max(mix_len[b], 0), l_cap);
 
     constexpr int TILE = 16 * kF32KB;
@@ -299,12 +386,12 @@ __global__ __launch_bounds__(64 * DecodeF32<D>::W, DecodeF32<D>::W / 4) void dec
     if constexpr (MAPPED) {
         const RowsMapped rows{K + (size_t)g * kv_head, V + (size_t)g * kv_head, Ksp + (size_t)g * s_total * D,
                               Vsp + (size_t)g * s_total * D, src_idx + (size_t)b * l_cap, D, kv_tok};
-        attend_f32<D>(rows, q, lo, hi, n_keys, scale, m, l, o);
+        attend_f32<D>(rows, q_row, lo, hi, n_keys, scale, m, l, o);
     } else {
         const size_t off = ((size_t)b * n_kv_heads + g) * (size_t)l_cap * D;
-        attend_f32<D>(RowsPlain{K + off, V + off, D}, q, lo, hi, n_keys, scale, m, l, o);
+        attend_f32<D>(RowsPlain{K + off, V + off, D}, q_row, lo, hi, n_keys, scale, m, l, o);
     }
-    MergeF32<D, W>::run(lds_f, wave, threadIdx.x, 64 * W, m, l, o, [&](int row, int d, float4 val, float lse)
+    MergeF32<D, W>::run(lds_f, wave, threadIdx.x, 64 * W, m, l, o, n_keys > 0, [&](int row, int d, float4 val, float lse)
                         __attribute__((always_inline)) {
         const int rr = rho0 + row;
         if (rr >= n_rows) return;

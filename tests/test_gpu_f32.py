@@ -69,3 +69,82 @@ def test_decode_inplace_f32(d, compacted):
                                       sparse)
     assert np.array_equal(lens, wlen)
     assert_close(got, oracle.decode_mixed(qd, wk, wv, wlen), "f32", head_axis=2, what="in place")
+
+
+def expect_non_finite(got, finite, seen, bad):
+    """Row-wise: `finite` is the result with the bad entries of V counted as 0; a row that sees a bad entry (bool
+    `seen` [..., n_bad]) has that value in the entry's column, everything else is as without it."""
+    want = finite.copy()
+    with np.errstate(invalid="ignore"):                     # (inf - inf)
+        for x, (d, value) in enumerate(bad):
+            want[seen[..., x], d] += value
+    ok = np.isfinite(want)
+    assert np.array_equal(np.isfinite(got), ok)
+    assert np.abs(got[ok] - want[ok]).max() <= 1e-5
+    inf = np.isinf(want)
+    assert np.array_equal(got[inf], want[inf]) and np.isnan(got[~ok & ~inf]).all()
+
+
+@pytest.mark.parametrize("hq,hkv,d,prefix,lens,window", [
+    (7, 1, 128, 5, [31, 33, 64, 5], 0), (6, 2, 64, 33, [127, 128, 40], 40),            # keys shared by four waves
+    (28, 4, 128, 20, [200, 257, 150], 30), (28, 4, 64, 0, [311, 290], 0)], ids=lambda x: str(x).replace(" ", ""))
+def test_prefill_f32_row_depends_on_what_it_sees(hq, hkv, d, prefix, lens, window):
+    """Infinities and NaN in V of single tokens reach the rows that see these tokens and no others."""
+    rng = np.random.default_rng(d + hq)
+    kept, start = [], prefix
+    for n in lens:
+        kept.append(np.sort(rng.choice(n, size=n // 3, replace=False)).astype(np.int32) + start)
+        start += n
+    lay = wl.layout_from_lists(prefix, lens, kept)
+    w = wl.tiny_workload("f32", hq, hkv, d, T=1, B=1, k=1, seed=d + hq)
+    q, k, v = wl.make_qkv(w, lay)
+    n = lay.n_tokens
+    bad = [(3, np.inf), (3, -np.inf), (d - 1, np.nan), (0, np.inf), (17, -np.inf)]
+    tokens = [int(kept[0][-1]), prefix + lens[0] + 7, prefix + lens[0] - 1, n - 1, n - 2]
+    finite_v = v.copy()
+    for t, (col, value) in zip(tokens, bad):
+        v[:, t, col], finite_v[:, t, col] = value, 0.0
+    got, lse = gpu_prefill(w, lay, q, k, v, want_lse=True, gl=make_layout(lay, window))
+    want, wlse = oracle.prefill_blk(q, k, finite_v, lay.n_prefix, lay.chunk_bounds, lay.sparse_offsets, lay.sparse_idx,
+                                    window=window, return_lse=True)
+    seen = oracle.allowed_mask(np.arange(n), lay.n_prefix, lay.chunk_bounds, lay.sparse_idx, window)[:, tokens]
+    assert seen.any() and not seen.all()
+    expect_non_finite(got, want, np.broadcast_to(seen, (hq, n, len(bad))), bad)
+    assert np.abs(lse - wlse).max() <= 1e-4
+
+
+@pytest.mark.parametrize("d", [64, 128])
+def test_decode_f32_non_finite(d):
+    """The last key of a set repeats in the slots behind it; logits that are NaN or all -inf give NaN, not an empty row."""
+    lens, t_q, hq = [33, 600, 17, 40, 40], 3, 4
+    w = wl.tiny_workload("f32", hq, 1, d, T=t_q, B=len(lens), k=1, seed=d)
+    rng = np.random.default_rng(d)
+    k, v = (rng.standard_normal((len(lens), 1, max(lens), d)).astype(np.float32) for _ in range(2))
+    qd = wl.make_decode_queries(w)
+    finite_v = v.copy()
+    bad = [(5, np.inf), (d - 2, -np.inf)]
+    for b in range(3):
+        for at, (col, value) in zip((lens[b] - 1, lens[b] // 2), bad):
+            v[b, 0, at, col], finite_v[b, 0, at, col] = value, 0.0
+    k[3, 0, 21] = np.nan
+    qd[4] = np.abs(qd[4])
+    k[4] = -np.inf
+    got, lse = gpu_decode(w, qd, vxl.to_device(k, "f32"), vxl.to_device(v, "f32"),
+                          torch.tensor(lens, dtype=torch.int32, device="cuda"), want_lse=True)
+    want, wlse = oracle.decode_lse(qd[:3], k[:3], finite_v[:3], np.array(lens[:3], np.int32))
+    expect_non_finite(got[:3], want, np.ones(want.shape[:3] + (len(bad),), bool), bad)
+    assert np.abs(lse[:3] - wlse).max() <= 1e-4
+    assert np.isnan(got[3:]).all() and np.isnan(lse[3:]).all()
+
+
+@pytest.mark.parametrize("hq,n", [(2, 90), (28, 700)])                   # four waves share the keys of a block; one
+def test_prefill_f32_without_weight(hq, n):
+    """A row whose visible logits are all -inf has neither output nor LSE, in either form of the kernel."""
+    lay = wl.layout_from_lists(0, [n], [np.zeros(0, np.int32)])
+    w = wl.tiny_workload("f32", hq, 1, 64, T=1, B=1, k=1, seed=n)
+    q, k, v = wl.make_qkv(w, lay)
+    q, k[:, :40] = np.abs(q), -np.inf
+    got, lse = gpu_prefill(w, lay, q, k, v, want_lse=True, gl=make_layout(lay))
+    assert np.isnan(got[:, :40]).all() and np.isnan(lse[:, :40]).all()
+    want, wlse = oracle.prefill_blk(q[:, 40:], k[:, 40:], v[:, 40:], 0, [0, n - 40], [0, 0], [], return_lse=True)
+    assert np.abs(got[:, 40:] - want).max() <= 1e-5 and np.abs(lse[:, 40:] - wlse).max() <= 1e-4
