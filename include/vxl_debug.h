@@ -11,6 +11,8 @@
 
 #include <stddef.h>
 
+#include "vxl.h"
+
 #ifdef __cplusplus
 extern "C" {
 #endif
@@ -29,6 +31,11 @@ void vxl_debug_prefill_variant(int variant);
 /* Step-mode decode kernel form: 0 = the library chooses (4 double-buffered waves), 8 = eight
  * single-buffered waves, 4 = force the default.  Size the decode workspace after setting it. */
 void vxl_debug_decode_step_waves(int waves);
+
+/* Decode kernel that a BF16 call of these sizes takes: 0 = 128 rows per workgroup, 1 = the 256-row
+ * ring, 2 = 32-row blocks whose waves own the keys (step mode).  n_split: its key splits.  Host only. */
+int vxl_debug_decode_plan(const vxl_attn_desc* desc, int batch, int n_q_tokens, int l_cap, int in_place,
+                          int* n_split);
 
 /* When both are non-NULL hipEvent_t handles, every following vxl_chunk_prefill records them on
  * its stream right before and right after its main attention kernel (the compaction pre-pass is

@@ -118,15 +118,24 @@ DecodePlan decode_plan(const vxl_attn_desc* d, int batch, int T, int l_cap, bool
         n_split = (tiles32 + kWaves * tpw - 1) / (kWaves * tpw);
         // More than one row block: this form reads the mixed set once per block, but from the L2 of one
         // XCD, and starts as fast as the one-row-block call; the 128-row kernel moves its tiles through
-        // registers and barriers.  One round of workgroups or none (us per call, before -> with row blocks, G = 7,
-        // four KV heads; keys): 224 rows, 4,096 keys 23.4 -> 18.0; 56 rows, 7,936 keys 23.8 -> 16.0 and
-        // 45,312 keys 49.8 -> 25.3; 112 rows, 45,312 keys 60.2 -> 33.0; in place, 224 rows, 4,096 keys (with
-        // pooling and map) 51.8 -> 43.4.  Against the ring kernel it wins while that one's launch is small
-        // (448 rows: 72 workgroups 25.9 -> 22.7, but 136 workgroups 27.4 -> 28.7; 140 rows at 248 workgroups
-        // 18.5 -> 19.4).  Up to 64 rows at one tile per wave the 128-row kernel stays (56 rows, 1,031 keys:
-        // 12.7 against 13.4).
+        // registers and barriers.  (us per call, before -> with row blocks, G = 7, four KV heads; keys): 224
+        // rows, 4,096 keys 23.4 -> 18.0; 56 rows, 7,936 keys 23.8 -> 16.0 and 45,312 keys 49.8 -> 25.3; 112
+        // rows, 45,312 keys 60.2 -> 33.0; in place, 224 rows, 4,096 keys (with pooling and map) 51.8 -> 43.4.
+        // Up to 64 rows at one tile per wave the 128-row kernel stays (56 rows, 1,031 keys: 12.7 against 13.4).
         const bool fits = units * n_split * n_rtile <= 256 && (gathered || tpw <= 32);
-        const bool few = p.use_ring ? (long)batch * d->n_kv_heads * ((rows + 255) / 256) * p.n_split < 100 : rows > 64 || tpw > 1;
+        bool few = rows > 64 || tpw > 1;
+        if (p.use_ring) {
+            // Against the ring kernel it wins while that one's launch is small (448 rows: 72 workgroups 25.9 ->
+            // 22.7, but 136 workgroups 27.4 -> 28.7; 140 rows at 248 workgroups 18.5 -> 19.4) and a wave walks
+            // fewer keys: a share of 1 / n_split there; here a quarter of that per round of workgroups, and the
+            // busiest XCD (32 compute units, LDS for one workgroup each at D = 128, two at D = 64) may take
+            // several rounds.  D = 128, ring -> here, splits: 1,280 rows on one KV head, 16,384 keys, 12 splits
+            // against two rounds of 1: 47.8 -> 219.8; 12 units of 672 rows, 2,000 keys, 2 against two rounds of
+            // 1: 47.3 -> 49.6, 1,300 keys, 1 against two rounds of 1: 53.5 -> 41.3.
+            const long ring_launch = units * ((rows + 255) / 256) * p.n_split;
+            const long per_xcd = (units * n_split + 7) / 8 * n_rtile, resident = 32 * (d->head_dim == 64 ? 2 : 1);
+            few = ring_launch < 100 && (per_xcd + resident - 1) / resident * p.n_split < 4 * n_split;
+        }
         if (rows <= kRowBlock || (fits && few)) {
             p.use_ring = 0;
             p.step_waves = kWaves;
@@ -141,6 +150,14 @@ DecodePlan decode_plan(const vxl_attn_desc* d, int batch, int T, int l_cap, bool
     off += align_up((size_t)batch * d->n_kv_heads * p.n_split * rows * sizeof(float), 256);
     p.total = off;
     return p;
+}
+
+// Test hook (vxl_debug.h).
+extern "C" int vxl_debug_decode_plan(const vxl_attn_desc* d, int batch, int n_q_tokens, int l_cap, int in_place,
+                                     int* n_split) {
+    const DecodePlan p = decode_plan(d, batch, n_q_tokens, l_cap, !in_place);
+    *n_split = p.n_split;
+    return p.step_waves ? 2 : p.use_ring;
 }
 
 // Workspace of the in-place decode: split-KV partial results, then the row map and the lengths.

@@ -1,0 +1,56 @@
+"""The choice between the decode kernels, which is made on the host and needs no GPU: where 32-row blocks take the place
+of the 256-row ring, a wave walks fewer keys than a wave of the ring would, counted over the rounds that the busiest
+XCD needs."""
+import numpy as np
+import pytest
+
+from paper_2506_19225_amd import vxl
+
+RING, BLOCKS = 1, 2
+
+
+def plan(hq, hkv, d, b, t, l_cap, in_place=False):
+    return vxl.debug_decode_plan(vxl.make_desc(hq, hkv, d, "bf16"), b, t, l_cap, in_place)
+
+
+def ring_splits(units, rows, l_cap):
+    """Key splits of the ring kernel: as many as give each of 256 compute units a workgroup, no more partial rows than keys."""
+    tiles, want = -(-l_cap // 64), -(-256 // (units * -(-rows // 256)))
+    per = -(-tiles // max(1, min(want, l_cap // rows, tiles)))
+    return -(-tiles // per)
+
+
+@pytest.mark.parametrize("in_place", [False, True])
+@pytest.mark.parametrize("d", [64, 128])
+def test_row_blocks_walk_fewer_keys_than_the_ring(d, in_place):
+    chosen = 0
+    for g, hkv in [(8, 1), (7, 1), (7, 2), (7, 4), (16, 1), (1, 8)]:
+        for b in (1, 2, 3, 5, 9, 12):
+            for t in (37, 64, 92, 128, 129, 160, 256, 512, 2000):
+                rows, units = g * t, hkv * b
+                if rows <= 256:                    # (fewer rows: the 128-row kernel may be the other choice)
+                    continue
+                for l_cap in (300, 1000, 1300, 1800, 4096, 16384, 45000):
+                    kernel, n_split = plan(g * hkv, hkv, d, b, t, l_cap, in_place)
+                    n_ring = ring_splits(units, rows, l_cap)
+                    if kernel == RING:
+                        assert n_split == n_ring
+                        continue
+                    assert kernel == BLOCKS
+                    chosen += 1
+                    blocks = -(-rows // 32)
+                    per_xcd = np.bincount(np.arange(units * n_split) % 8).max() * blocks
+                    rounds = -(-per_xcd // (32 * (128 // d)))     # (a workgroup's LDS: all of a compute unit's at D = 128)
+                    assert rounds * n_ring < 4 * n_split, (g, hkv, b, t, l_cap, n_split)
+                    assert n_split <= n_ring and units * n_split * blocks <= 256
+    assert chosen > 50
+
+
+@pytest.mark.parametrize("hq,hkv,d,b,t,l_cap,kernel", [
+    (8, 1, 128, 1, 128, 4096, BLOCKS), (8, 1, 128, 1, 160, 4096, RING), (8, 1, 128, 1, 160, 16384, RING),
+    (8, 1, 64, 1, 160, 4096, BLOCKS), (8, 1, 64, 1, 160, 16384, RING), (8, 1, 128, 1, 512, 4096, RING),
+    (28, 4, 128, 3, 96, 1300, BLOCKS), (28, 4, 128, 3, 96, 2000, RING), (28, 4, 64, 3, 96, 2000, BLOCKS),
+    (7, 1, 128, 9, 128, 1300, BLOCKS), (28, 4, 128, 1, 160, 4096, RING), (28, 4, 128, 1, 32, 4352, BLOCKS)])
+def test_measured_sides_of_the_line(hq, hkv, d, b, t, l_cap, kernel):
+    """Shapes on either side whose two kernels were timed against each other."""
+    assert plan(hq, hkv, d, b, t, l_cap)[0] == kernel

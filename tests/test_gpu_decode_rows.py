@@ -23,6 +23,11 @@ pytestmark = pytest.mark.gpu
     (28, 4, 36, 128, [1029, 515]),                 # 252 rows, units that do not divide by eight
     (28, 4, 64, 128, [1031]),                      # 448 rows
     (7, 1, 128, 64, [300]),                        # 896 rows: 28 blocks on one XCD
+    (28, 4, 96, 128, [700, 33, 0]),                # twelve units of 21 blocks: two on some XCDs
+    (28, 4, 96, 64, [1400, 1399, 5]),
+    (7, 1, 96, 128, [450, 1, 31, 32, 33, 64, 449, 0, 128]),       # nine units of 21 blocks
+    (8, 1, 160, 128, [2600]),                      # 40 blocks: the ring kernel
+    (8, 1, 160, 64, [1290]),                       # 40 blocks on one XCD, two per compute unit
 ])
 def test_row_blocks_match_the_oracle(hq, hkv, t, d, lens):
     rng = np.random.default_rng(81 + t)
