@@ -266,6 +266,11 @@ vxl_status vxl_layout_create_windowed(int32_t n_tokens, int32_t n_prefix, int32_
     }
     L->pair_count = pairs;
     L->n_seg = (int32_t)L->segs.size();
+    for (const Segment& sg : L->segs) {
+        const int b = (sg.q_len + kRowBlock - 1) / kRowBlock;
+        L->row_blocks8 += b / 8;
+        ++L->segs_mod8[b % 8];
+    }
     L->n_own_tiles = tile_base;
     L->l_ctx = n_prefix + s_total;
     L->n_ctx_tiles = (L->l_ctx + kKeyTile - 1) / kKeyTile;
