@@ -126,13 +126,18 @@ def _ptr(t: Optional[torch.Tensor]) -> Optional[int]:
 
 
 # The handle of the current stream without the Stream object that torch.cuda.current_stream() builds for it:
-# 0.1 us instead of 2.8 us per call, a fifth of what a generated token's decode call took on the host.
-_raw_stream, _current_device = torch._C._cuda_getCurrentRawStream, torch._C._cuda_getDevice
+# 0.1 us instead of 2.8 us per call, a fifth of what a generated token's decode call took on the host.  The two
+# names are torch's private ones: a build that lacks them, or a process in which torch has not set the device up
+# (the first call, a forked child), takes the public way, which sets it up or says why it cannot.
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+_current_device = getattr(torch._C, "_cuda_getDevice", None)
 
 
 def _stream(stream) -> Optional[int]:
     if stream is None:
-        return _raw_stream(_current_device()) or None
+        if _raw_stream is not None and _current_device is not None and torch.cuda.is_initialized():
+            return _raw_stream(_current_device()) or None
+        stream = torch.cuda.current_stream()
     return stream.cuda_stream or None
 
 
