@@ -1,5 +1,7 @@
 """Helpers of the GPU parity tests: run the four C-ABI calls through the ctypes binding on
 seeded inputs and return host arrays; tolerance checks as stated for the path."""
+import contextlib
+
 import numpy as np
 import torch
 
@@ -44,12 +46,32 @@ def assert_close(got, want, dtype, head_axis=0, what=""):
         f"{what}: worst row {worst} has ||err||/||row|| = {ratio.max():.3e} (bound {TOL_BF16_ROW})"
 
 
+@contextlib.contextmanager
+def prefill_variant(variant: int):
+    """The bf16 pre-filling instance: 0 = the library chooses (4 waves for small prompts), 1 = two 4-wave workgroups per
+    compute unit, 2 = 8 waves, which every larger prompt takes, whatever the size."""
+    vxl.debug_prefill_variant(variant)
+    try:
+        yield
+    finally:
+        vxl.debug_prefill_variant(0)
+
+
 def make_layout(lay: wl.Layout, window: int = 0) -> vxl.Layout:
     return vxl.Layout(lay.n_prefix, lay.chunk_bounds, lay.sparse_offsets, lay.sparse_idx, window=window)
 
 
 def desc_of(w: wl.Workload, scale: float = 0.0):
     return vxl.make_desc(w.n_q_heads, w.n_kv_heads, w.head_dim, w.dtype, scale)
+
+
+DECODE_128, DECODE_RING, DECODE_BLOCKS = range(3)
+
+
+def decode_kernel(w, batch, t, l_cap, in_place=False):
+    """The kernel a bf16 decode of these sizes takes: 128 rows per workgroup, the 256-row ring, 32-row blocks (one row
+    block: the step kernel)."""
+    return vxl.debug_decode_plan(desc_of(w), batch, t, l_cap, in_place)[0]
 
 
 def gpu_prefill(w, lay, q, k, v, scale=0.0, want_lse=False, gl=None, dev=None):

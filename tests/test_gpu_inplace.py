@@ -10,8 +10,8 @@ import torch
 import oracle
 from paper_2506_19225_amd import vxl, workloads as wl
 
-from gpu_util import (assert_close, desc_of, gpu_decode, gpu_decode_inplace as inplace, gpu_gather, kept_rows,
-                      make_layout, storage_round)
+from gpu_util import (DECODE_128, DECODE_BLOCKS, DECODE_RING, assert_close, decode_kernel, desc_of, gpu_decode,
+                      gpu_decode_inplace as inplace, gpu_gather, kept_rows, make_layout, storage_round)
 
 pytestmark = pytest.mark.gpu
 
@@ -64,12 +64,14 @@ def test_inplace_config0_fp32(mode):
 
 
 @pytest.mark.parametrize("mode", MODES)
-@pytest.mark.parametrize("t_q,bsz,d", [(1, 2, 128), (4, 1, 64), (5, 3, 64), (18, 2, 128), (40, 1, 128), (30, 2, 64)],
-                         ids=lambda x: str(x))
-def test_inplace_ragged_bf16(mode, t_q, bsz, d):
-    """Stacked rows 14 and 56 (step kernel: <= 32 rows... 14, 28), 70 and 252 (128-row kernel, one
-    and two row tiles), 560 (five row tiles) and 420; ragged chunks, some without kept rows, random
-    selections including none and all."""
+@pytest.mark.parametrize("t_q,bsz,d,kernel", [
+    (1, 2, 128, DECODE_BLOCKS), (4, 1, 64, DECODE_BLOCKS), (5, 3, 64, DECODE_128), (18, 2, 128, DECODE_BLOCKS),
+    (40, 1, 128, DECODE_BLOCKS), (30, 2, 64, DECODE_BLOCKS), (16, 33, 64, DECODE_128), (36, 20, 128, DECODE_128),
+    (36, 27, 64, DECODE_RING), (40, 13, 128, DECODE_RING)], ids=lambda x: str(x))
+def test_inplace_ragged_bf16(mode, t_q, bsz, d, kernel):
+    """Stacked rows 7 and 28 (step kernel), 126, 280 and 210 (its form of several 32-row blocks), 35, 112 and 252
+    (128-row kernel, one and two row tiles), 252 and 280 (256-row ring, one and two); ragged chunks, some without kept
+    rows, random selections including none and all."""
     rng = np.random.default_rng(1000 + 7 * t_q + d)
     w = wl.tiny_workload("bf16", 14, 2, d, T=t_q, B=bsz, k=2, seed=1000 + t_q, value_scale=0.5)
     lay = wl.random_layout(rng, 17, 11, 1, 150)
@@ -79,6 +81,7 @@ def test_inplace_ragged_bf16(mode, t_q, bsz, d):
     masks[0] = 0
     if bsz > 1:
         masks[1] = 1
+    assert decode_kernel(w, bsz, t_q, lay.n_tokens, in_place=True) == kernel
     got = check_case(w, lay, k, v, qd, masks, mode)
     if mode == "kept_in_place":                      # and against gather + decode on the device
         kmix, vmix, mix_len, _ = gpu_gather(w, lay, k, v, masks, lay.n_tokens)

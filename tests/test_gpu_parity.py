@@ -8,8 +8,8 @@ import torch
 import oracle
 from paper_2506_19225_amd import vxl, workloads as wl
 
-from gpu_util import (assert_close, desc_of, gpu_decode, gpu_gather, gpu_prefill, gpu_score_topk,
-                      make_layout)
+from gpu_util import (DECODE_128, DECODE_BLOCKS, DECODE_RING, assert_close, decode_kernel, desc_of, gpu_decode, gpu_gather, gpu_prefill, gpu_score_topk,
+                      make_layout, prefill_variant)
 
 pytestmark = pytest.mark.gpu
 
@@ -48,7 +48,7 @@ TINY_CASES = [
 
 
 @pytest.mark.parametrize("case", TINY_CASES, ids=lambda c: f"{c[0]}-h{c[1]}-d{c[3]}-p{c[4]}-s{c[8]}")
-@pytest.mark.parametrize("qb", [0, 1])
+@pytest.mark.parametrize("qb", [0, 1, 2])
 def test_prefill_ragged_layouts(case, qb):
     dtype, hq, hkv, d, p, nc, lo, hi, seed = case
     if dtype == "f32" and qb != 0:
@@ -67,7 +67,8 @@ def test_prefill_ragged_layouts(case, qb):
     assert np.abs(lse - wlse).max() < (1e-4 if dtype == "f32" else 2e-2)
 
 
-def test_prefill_edge_layouts_bf16():
+@pytest.mark.parametrize("qb", [0, 2])
+def test_prefill_edge_layouts_bf16(qb):
     """No prefix and no kept tokens (block diagonal); everything kept (dense causal); one chunk;
     prefix only."""
     w = wl.tiny_workload("bf16", 4, 2, 128, T=1, B=1, k=1, seed=7, value_scale=0.5)
@@ -82,11 +83,12 @@ def test_prefill_edge_layouts_bf16():
                 wl.layout_from_lists(0, [200], [np.zeros(0, np.int32)]),
                 wl.layout_from_lists(150, [], [])):
         q, k, v = wl.make_qkv(w, lay)
-        got = gpu_prefill(w, lay, q, k, v)
+        with prefill_variant(qb):
+            got = gpu_prefill(w, lay, q, k, v)
         assert_close(got, oracle_prefill(q, k, v, lay), "bf16", what="edge layout")
 
 
-@pytest.mark.parametrize("qb", [0, 1])
+@pytest.mark.parametrize("qb", [0, 1, 2])
 def test_prefill_medium_bf16_sharp_softmax(qb):
     """Several 256-token chunks at GQA 14/2, with logits of std ~3 so that the running maximum
     moves and the rescaling path is exercised."""
@@ -109,12 +111,14 @@ def test_prefill_medium_bf16_sharp_softmax(qb):
     assert np.abs(lse - wlse).max() < 2e-2
 
 
-def test_prefill_matrix_core_kernel_agrees_with_vector_kernel_on_device():
+@pytest.mark.parametrize("qb", [0, 2])
+def test_prefill_matrix_core_kernel_agrees_with_vector_kernel_on_device(qb):
     w = wl.tiny_workload("bf16", 8, 2, 128, T=1, B=1, k=1, seed=31, value_scale=0.3)
     rng = np.random.default_rng(31)
     lay = wl.random_layout(rng, 33, 6, 30, 260)
     q, k, v = wl.make_qkv(w, lay)
-    a = gpu_prefill(w, lay, q, k, v)
+    with prefill_variant(qb):
+        a = gpu_prefill(w, lay, q, k, v)
     vxl.debug_force_simple(True)
     try:
         b = gpu_prefill(w, lay, q, k, v)
@@ -138,7 +142,7 @@ def config1_oracle(window=0):
     return _CONFIG1_ORACLE[window]
 
 
-@pytest.mark.parametrize("qb", [0, 1])
+@pytest.mark.parametrize("qb", [0, 1, 2])
 def test_prefill_config1_all_rows(qb):
     w, lay, q, k, v, want = config1_oracle()
     vxl.debug_prefill_variant(qb)
@@ -149,7 +153,8 @@ def test_prefill_config1_all_rows(qb):
     assert_close(got, want, "bf16", what="config1 prefill, all rows")
 
 
-def test_prefill_locality_and_determinism_bit_exact():
+@pytest.mark.parametrize("qb", [0, 2])
+def test_prefill_locality_and_determinism_bit_exact(qb):
     """Changing K/V of a token that is not kept changes only later rows of its own chunk, bit
     for bit; two runs on the same inputs are bit-identical."""
     w = wl.tiny_workload("bf16", 4, 2, 128, T=1, B=1, k=1, seed=41, value_scale=0.3)
@@ -157,14 +162,16 @@ def test_prefill_locality_and_determinism_bit_exact():
     kept = [np.array([40, 41, 99]), np.array([140, 200]), np.array([281])]
     lay = wl.layout_from_lists(40, lens, kept)
     q, k, v = wl.make_qkv(w, lay)
-    base = gpu_prefill(w, lay, q, k, v)
-    again = gpu_prefill(w, lay, q, k, v)
+    with prefill_variant(qb):
+        base = gpu_prefill(w, lay, q, k, v)
+        again = gpu_prefill(w, lay, q, k, v)
     assert np.array_equal(base, again)
     j = 170                                            # chunk 1 = [140, 280), not kept
     k2, v2 = k.copy(), v.copy()
     k2[:, j] = wl.round_to_bf16(k2[:, j] + 1.0)
     v2[:, j] = wl.round_to_bf16(v2[:, j] - 2.0)
-    pert = gpu_prefill(w, lay, q, k2, v2)
+    with prefill_variant(qb):
+        pert = gpu_prefill(w, lay, q, k2, v2)
     changed = (pert != base).any(axis=(0, 2))
     assert changed[170:280].any()
     assert not changed[:170].any() and not changed[280:].any()
@@ -182,7 +189,7 @@ WINDOW_CASES = [
 
 
 @pytest.mark.parametrize("case", WINDOW_CASES, ids=lambda c: f"{c[0]}-d{c[3]}-p{c[4]}-w{c[8]}")
-@pytest.mark.parametrize("qb", [0, 1])
+@pytest.mark.parametrize("qb", [0, 1, 2])
 def test_prefill_sliding_window(case, qb):
     dtype, hq, hkv, d, p, nc, lo, hi, window, seed = case
     if dtype == "f32" and qb != 0:
@@ -405,13 +412,17 @@ def test_decode_config0_fp32_and_tiny_bf16():
     want, wlse = oracle.decode_lse(qd, wk, wv, wlen)
     assert_close(got, want, "f32", head_axis=2, what="config0 decode")
     assert np.abs(lse - wlse).max() < 1e-4
-    # stacked rows 7 (wave kernel), 35 (split kernel), 280 and 210 (ring kernel, both head dims)
-    for t_q, bsz, d in ((1, 2, 128), (5, 3, 64), (40, 1, 128), (30, 2, 64)):
+    # stacked rows 7 (step kernel), 35 and 252 (128-row kernel, one and two row tiles), 280 and 210 (32-row blocks), 280
+    # and 560 (256-row ring)
+    for t_q, bsz, d, kernel in ((1, 2, 128, DECODE_BLOCKS), (5, 3, 64, DECODE_128), (36, 20, 128, DECODE_128),
+                                (40, 1, 128, DECODE_BLOCKS), (30, 2, 64, DECODE_BLOCKS), (40, 20, 128, DECODE_RING),
+                                (80, 20, 64, DECODE_RING)):
         w = wl.tiny_workload("bf16", 14, 2, d, T=t_q, B=bsz, k=2, seed=72 + t_q)
         lay = wl.random_layout(rng, 17, 9, 5, 120)
         _, k, v = wl.make_qkv(w, lay, with_q=False)
         qd = wl.make_decode_queries(w)
         masks = rng.integers(0, 2, size=(bsz, lay.n_chunks)).astype(np.uint8)
+        assert decode_kernel(w, bsz, t_q, lay.n_tokens) == kernel
         kmix, vmix, mix_len = check_gather(w, lay, k, v, masks, lay.n_tokens)
         got, lse = gpu_decode(w, qd, kmix, vmix, mix_len, want_lse=True)
         wk, wv, wlen, _ = oracle.gather_bilevel(k, v, masks, *lay_args(lay), l_cap=lay.n_tokens)
@@ -625,16 +636,19 @@ def test_decode_step_mode_more_splits_than_the_merge_prefetches(d, lens):
     assert np.abs(lse - wlse).max() < 2e-2
 
 
-@pytest.mark.parametrize("t_q,d,lens", [(1, 128, [1000, 37, 4096]), (4, 64, [33, 2047]), (1, 64, [1, 64]),
-                                        (10, 128, [500, 1]), (40, 128, [777]), (30, 64, [1500, 90])],
-                         ids=lambda x: str(x))
-def test_decode_never_uses_rows_past_the_mixed_length(t_q, d, lens):
+@pytest.mark.parametrize("t_q,d,lens,kernel", [
+    (1, 128, [1000, 37, 4096], DECODE_BLOCKS), (4, 64, [33, 2047], DECODE_BLOCKS), (1, 64, [1, 64], DECODE_BLOCKS),
+    (10, 128, [500, 1], DECODE_BLOCKS), (40, 128, [777], DECODE_BLOCKS), (30, 64, [1500, 90], DECODE_BLOCKS),
+    (8, 64, [500, 1], DECODE_128), (9, 128, [4033, 777], DECODE_128), (40, 128, [777, 4033, 1], DECODE_RING),
+    (72, 64, [1500, 90, 4096, 64, 1, 65], DECODE_RING)], ids=lambda x: str(x))
+def test_decode_never_uses_rows_past_the_mixed_length(t_q, d, lens, kernel):
     """Rows of the mixed buffers at and past mix_len[b] are NaN (what an uninitialised buffer may
-    hold): no kernel form (step, 128-row, 256-row ring) may let them reach O or LSE, also where
+    hold): no kernel form (step, row blocks, 128-row, 256-row ring) may let them reach O or LSE, also where
     the length falls inside a tile, at a tile border and in a wave's first tile."""
     rng = np.random.default_rng(900 + t_q + d)
     hq, hkv, l_cap, bsz = 14, 2, 4096, len(lens)
     w = wl.tiny_workload("bf16", hq, hkv, d, T=t_q, B=bsz, k=1, seed=900 + d)
+    assert decode_kernel(w, bsz, t_q, l_cap) == kernel
     kmix = wl.round_to_bf16(rng.standard_normal((bsz, hkv, l_cap, d)).astype(np.float32) * np.float32(0.5))
     vmix = wl.round_to_bf16(rng.standard_normal((bsz, hkv, l_cap, d)).astype(np.float32) * np.float32(0.5))
     qd = wl.round_to_bf16(rng.standard_normal((bsz, t_q, hq, d)).astype(np.float32) * np.float32(0.5))

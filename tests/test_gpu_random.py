@@ -10,13 +10,13 @@ from paper_2506_19225_amd import vxl, workloads as wl
 
 from gpu_util import (assert_close, check_selection_valid, desc_of, full_sort_selection, gpu_decode,
                       gpu_decode_inplace, gpu_gather, gpu_score_topk, gpu_score_topk_mass, kept_rows, make_layout,
-                      storage_round)
+                      prefill_variant, storage_round)
 
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("seed", [11, 12, 13])
-def test_prefill_random_sweep(seed):
+@pytest.mark.parametrize("seed,variant", [(11, 0), (12, 0), (13, 0), (11, 2), (12, 2), (13, 2)])
+def test_prefill_random_sweep(seed, variant):
     rng = np.random.default_rng(seed)
     for case in range(12):
         dtype = "bf16" if rng.random() < 0.8 else "f32"
@@ -44,7 +44,8 @@ def test_prefill_random_sweep(seed):
             dq, dk, dv = (x.permute(1, 0, 2).contiguous() for x in (dq, dk, dv))
         out = torch.full_like(dq, float("nan"))
         ws = vxl.alloc_workspace(vxl.workspace_bytes(vxl.OP_PREFILL, gl, desc))
-        vxl.chunk_prefill(gl, desc, dq, dk, dv, out, None, ws)
+        with prefill_variant(variant):
+            vxl.chunk_prefill(gl, desc, dq, dk, dv, out, None, ws)
         torch.cuda.synchronize()
         got = vxl.to_host(out.permute(1, 0, 2).contiguous() if tokmaj else out)
         want = oracle.prefill_blk(q, k, v, lay.n_prefix, lay.chunk_bounds, lay.sparse_offsets, lay.sparse_idx,

@@ -8,7 +8,7 @@ import torch
 import oracle
 from paper_2506_19225_amd import vxl, workloads as wl
 
-from gpu_util import assert_close, make_layout
+from gpu_util import assert_close, make_layout, prefill_variant
 
 pytestmark = pytest.mark.gpu
 
@@ -40,7 +40,10 @@ def setup(case):
 
 
 @pytest.mark.parametrize("case", CASES, ids=lambda c: f"{c[0]}-h{c[1]}-d{c[3]}")
-def test_prefill_token_major(case):
+@pytest.mark.parametrize("qb", [0, 2])
+def test_prefill_token_major(case, qb):
+    if case[0] == "f32" and qb != 0:
+        pytest.skip("kernel instances only exist for the matrix-core path")
     w, lay, q, k, v = setup(case)
     gl = make_layout(lay)
     dh, dt = descs(w)
@@ -50,8 +53,9 @@ def test_prefill_token_major(case):
     ot = torch.full_like(qt, float("nan"))
     lse_h = torch.full(qh.shape[:2], float("nan"), dtype=torch.float32, device="cuda")
     lse_t = torch.full_like(lse_h, float("nan"))
-    vxl.chunk_prefill(gl, dh, qh, kh, vh, oh, lse_h, ws)
-    vxl.chunk_prefill(gl, dt, qt, kt, vt, ot, lse_t, ws)
+    with prefill_variant(qb):
+        vxl.chunk_prefill(gl, dh, qh, kh, vh, oh, lse_h, ws)
+        vxl.chunk_prefill(gl, dt, qt, kt, vt, ot, lse_t, ws)
     torch.cuda.synchronize()
     got = vxl.to_host(ot.permute(1, 0, 2).contiguous())
     want = oracle.prefill_blk(q, k, v, lay.n_prefix, lay.chunk_bounds, lay.sparse_offsets, lay.sparse_idx)
