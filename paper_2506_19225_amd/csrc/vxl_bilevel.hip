@@ -351,7 +351,7 @@ __global__ __launch_bounds__(256) void pool_sparse_kernel(const T* __restrict__ 
 // `groups` consecutive passes of 256 / LPR rows (chosen by the host so that small gathers still
 // fill the chip and large ones amortise the scan).  Bound by HBM when large: the pieces of four KV heads
 // are requested before the first store (a head's two loads and two stores in turn: 158 us for the eight
-// mixed sets of 25k rows, 860 MB in and out; 140 us, 6.1 TB/s, so).  Block 0 of a query writes mix_len; a query whose
+// mixed sets of 25k rows, 835 MB in and out; 140 us, 6.0 TB/s, so).  Block 0 of a query writes mix_len; a query whose
 // mixed set does not fit l_cap gets mix_len = -(rows needed) and none of its rows is copied.
 // With Kmix == nullptr nothing is copied at all: the call only writes mix_len and src_idx (the row
 // map the in-place decode reads the dense and sparse rows through).

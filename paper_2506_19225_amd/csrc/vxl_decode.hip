@@ -379,7 +379,6 @@ __global__ __launch_bounds__(512, 2) void decode_ring_kernel(
 // tile (the default: 3-8 % faster on long streams, 5 % at a single tile per wave, where it spreads
 // over twice as many compute units) -- and NW = 8 waves with one tile pair each (cross-check).
 constexpr int kStepTile = 32;       // keys per wave tile
-constexpr int kXcds = 8;
 constexpr int kMaxStepTpw = 32;     // in-place form: tiles per wave whose row map fits the wave's LDS area
 
 template <int D, int NW, int NBUF, bool IND = false, bool ROWS = false>

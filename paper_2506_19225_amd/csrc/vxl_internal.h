@@ -14,6 +14,7 @@ namespace vxl {
 
 constexpr int kKeyTile = 64;      // keys per K/V tile of the matrix-core kernels
 constexpr int kRowBlock = 32;     // query rows per MFMA block (one 32x32 tile side)
+constexpr int kXcds = 8;          // XCDs, each with an L2 of its own; workgroups go to them in turn
 
 // One pre-filling segment: the prefix (if any) or a chunk.  Queries of a segment attend to the
 // first ctx_len rows of the compacted history buffer, to the `back` tokens right before the

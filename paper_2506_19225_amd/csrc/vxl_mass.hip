@@ -54,7 +54,6 @@ struct KTileRegs {
 };
 
 constexpr int kMassRowTile = 128;                     // stacked query rows per workgroup (4 waves x 32)
-constexpr int kXcds = 8;
 constexpr float kMassGrow = 1073741824.f;             // 2^30: a lane's sum over a tile from which the reference is raised
 
 // bf16, matrix cores: S^T = K.Q^T per 64-key tile, running (m, l) per query column.

@@ -47,10 +47,11 @@ __global__ __launch_bounds__(256) void compact_kv_kernel(const uint4* __restrict
 }
 
 // ------------------------------------------------------------------------------------------
-// Main kernel: 8 waves = 256 query rows per workgroup (one workgroup per
-// compute unit, two waves per SIMD), K/V tiles brought in by direct global->LDS loads into a ring
-// of NS stages, two tiles ahead of the arithmetic: the staging stays out of the VALU/VGPR budget
-// and the memory latency hides behind several tiles of arithmetic.
+// Main kernel: 8 waves = 256 query rows per workgroup (one workgroup per compute unit, two waves per
+// SIMD), for small prompts 4 waves = 128 rows (the line is at launch_prefill_bf16).  K/V tiles are
+// brought in by direct global->LDS loads into a ring of NS stages, two tiles ahead of the arithmetic:
+// the staging stays out of the VALU/VGPR budget and the memory latency hides behind several tiles of
+// arithmetic.
 //
 // The loads are issued from inline assembly: the compiler cannot see them, so it neither orders
 // them against the LDS reads of other stages nor counts them in its own vmcnt bookkeeping; the
@@ -61,7 +62,7 @@ __global__ __launch_bounds__(256) void compact_kv_kernel(const uint4* __restrict
 // ------------------------------------------------------------------------------------------
 template <int D, int NS, int NW = 8>
 struct PrefillDmaCfg {
-    static constexpr int WAVES = NW;                          // 8 (one workgroup per compute unit) or 4 (two)
+    static constexpr int WAVES = NW;                          // 8 or 4: two or one per SIMD
     static constexpr int BM = 32 * WAVES;
     static constexpr int TILE = kKeyTile * D;                 // elements of one unpadded K (or V) tile
     static constexpr int STAGE = 2 * TILE;                    // K tile then V tile
@@ -73,9 +74,10 @@ struct PrefillDmaCfg {
     static constexpr int GROUP = 2 * IPW;                     // loads per wave per tile (K and V)
 };
 
-// The kernel is persistent: the grid is one workgroup per compute unit, and every workgroup keeps
-// taking the next (band of query rows, part of its row-block x head grid) pair of its queue from a
-// counter in global memory until the queue is empty.  The work list is sorted heaviest first, so this is greedy longest-first
+// The kernel is persistent: the grid is as many workgroups as the chip holds at once (one per compute
+// unit; two of 4 waves where their rings fit its LDS), and every workgroup keeps taking the next (band
+// of query rows, part of its row-block x head grid) pair of its queue from a counter in global memory
+// until the queue is empty.  The work list is sorted heaviest first, so this is greedy longest-first
 // scheduling without gaps between workgroups.  With xpg > 0 there is one queue per KV head group,
 // served by the xpg XCDs (blockIdx.x % 8, the order workgroups are dealt out in) whose L2 then
 // holds that group's K and V; otherwise a single queue.  The counters must be zero at launch.
@@ -363,7 +365,7 @@ static vxl_status run_prefill_dma(const vxl_layout* L, const vxl_attn_desc* d, f
         return a != VXL_OK ? a : enable_big_lds(prefill_dma_kernel<D, NS, true, NW>, C::LDS_BYTES);
     });
     if (st != VXL_OK) return st;
-    int n_cus = 0;                                            // one persistent workgroup per compute unit
+    int n_cus = 0;                                            // per_cu persistent workgroups on each
     st = device_cu_count(&n_cus);
     if (st != VXL_OK) return st;
     hipEvent_t ev_start = g_ev_start, ev_stop = g_ev_stop;

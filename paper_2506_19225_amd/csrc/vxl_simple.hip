@@ -28,9 +28,9 @@ __device__ __forceinline__ float wave_sum(float v) {
 
 // Softmax attention of one query row over n_keys keys; krow(slot) / vrow(slot) return the K and
 // the V row of key `slot`.  q_lds: this wave's D floats of LDS.
-template <typename T, int D, typename KRowFn, typename VRowFn>
-__device__ __forceinline__ void attend_row(const T* qrow, KRowFn krow, VRowFn vrow, int n_keys, float scale,
-                                           float* q_lds, T* orow, float* lse_out) {
+template <int D, typename KRowFn, typename VRowFn>
+__device__ __forceinline__ void attend_row(const uint16_t* qrow, KRowFn krow, VRowFn vrow, int n_keys, float scale,
+                                           float* q_lds, uint16_t* orow, float* lse_out) {
     const int lane = threadIdx.x & 63;
     constexpr int X = D / 64;
 #pragma unroll
@@ -45,7 +45,7 @@ __device__ __forceinline__ void attend_row(const T* qrow, KRowFn krow, VRowFn vr
         const bool valid = slot < n_keys;
         float s = -INFINITY;
         if (valid) {
-            const T* kp = krow(slot);
+            const uint16_t* kp = krow(slot);
             float a = 0.f;
 #pragma unroll 8
             for (int d = 0; d < D; ++d) a = fmaf(q_lds[d], ld(kp + d), a);
@@ -60,7 +60,7 @@ __device__ __forceinline__ void attend_row(const T* qrow, KRowFn krow, VRowFn vr
         const int cnt = min(64, n_keys - base);
         for (int j = 0; j < cnt; ++j) {
             const float pj = __shfl(p, j);
-            const T* vp = vrow(base + j);
+            const uint16_t* vp = vrow(base + j);
 #pragma unroll
             for (int x = 0; x < X; ++x) acc[x] = fmaf(pj, ld(vp + lane + 64 * x), acc[x]);
         }
@@ -72,10 +72,10 @@ __device__ __forceinline__ void attend_row(const T* qrow, KRowFn krow, VRowFn vr
     if (lse_out && lane == 0) *lse_out = m + logf(l);
 }
 
-template <typename T, int D>
+template <int D>
 __global__ __launch_bounds__(256) void prefill_simple_kernel(
-    const T* __restrict__ Q, const T* __restrict__ K, const T* __restrict__ V, T* __restrict__ O,
-    float* __restrict__ LSE, const int32_t* __restrict__ bounds, const int32_t* __restrict__ soff,
+    const uint16_t* __restrict__ Q, const uint16_t* __restrict__ K, const uint16_t* __restrict__ V,
+    uint16_t* __restrict__ O, float* __restrict__ LSE, const int32_t* __restrict__ bounds, const int32_t* __restrict__ soff,
     const int32_t* __restrict__ sidx, int n_tokens, int n_prefix, int n_chunks, int group,
     float scale, int window, long long q_head, long long q_tok, long long kv_head_stride, long long kv_tok) {
     __shared__ float q_lds[4][D];
@@ -108,17 +108,17 @@ __global__ __launch_bounds__(256) void prefill_simple_kernel(
         else tok = own_start + (slot - n_hist);
         return (size_t)tok * kv_tok;
     };
-    const T* kh = K + (size_t)g * kv_head_stride;
-    const T* vh = V + (size_t)g * kv_head_stride;
+    const uint16_t* kh = K + (size_t)g * kv_head_stride;
+    const uint16_t* vh = V + (size_t)g * kv_head_stride;
     const size_t q_off = (size_t)h * q_head + (size_t)i * q_tok;
-    attend_row<T, D>(Q + q_off, [=](int slot) { return kh + key(slot); }, [=](int slot) { return vh + key(slot); },
+    attend_row<D>(Q + q_off, [=](int slot) { return kh + key(slot); }, [=](int slot) { return vh + key(slot); },
                      n_keys, scale, q_lds[wave], O + q_off, LSE ? LSE + (size_t)h * n_tokens + i : nullptr);
 }
 
-template <typename T, int D>
+template <int D>
 __global__ __launch_bounds__(256) void decode_simple_kernel(
-    const T* __restrict__ Qd, const T* __restrict__ Kmix, const T* __restrict__ Vmix,
-    T* __restrict__ O, float* __restrict__ LSE, const int32_t* __restrict__ mix_len, int batch, int T_q,
+    const uint16_t* __restrict__ Qd, const uint16_t* __restrict__ Kmix, const uint16_t* __restrict__ Vmix,
+    uint16_t* __restrict__ O, float* __restrict__ LSE, const int32_t* __restrict__ mix_len, int batch, int T_q,
     int n_q_heads, int group, int l_cap, float scale) {
     __shared__ float q_lds[4][D];
     const int wave = threadIdx.x >> 6;
@@ -138,18 +138,19 @@ __global__ __launch_bounds__(256) void decode_simple_kernel(
         if (LSE && lane == 0) LSE[row] = -INFINITY;
         return;
     }
-    const T* kh = Kmix + kv_off;
-    const T* vh = Vmix + kv_off;
-    attend_row<T, D>(Qd + row * D, [=](int slot) { return kh + key(slot); }, [=](int slot) { return vh + key(slot); },
+    const uint16_t* kh = Kmix + kv_off;
+    const uint16_t* vh = Vmix + kv_off;
+    attend_row<D>(Qd + row * D, [=](int slot) { return kh + key(slot); }, [=](int slot) { return vh + key(slot); },
                      n_keys, scale, q_lds[wave], O + row * D, LSE ? LSE + row : nullptr);
 }
 
 // The same over the mixed KV set read in place: mixed row `slot` of query b is token src_idx[b, slot]
 // of K / V, or (src < 0) row -1 - src of the sparse buffers Ksp / Vsp [Hkv, S_total, D].
-template <typename T, int D>
+template <int D>
 __global__ __launch_bounds__(256) void decode_inplace_simple_kernel(
-    const T* __restrict__ Qd, const T* __restrict__ K, const T* __restrict__ V, const T* __restrict__ Ksp,
-    const T* __restrict__ Vsp, const int32_t* __restrict__ src_idx, T* __restrict__ O, float* __restrict__ LSE,
+    const uint16_t* __restrict__ Qd, const uint16_t* __restrict__ K, const uint16_t* __restrict__ V,
+    const uint16_t* __restrict__ Ksp, const uint16_t* __restrict__ Vsp, const int32_t* __restrict__ src_idx,
+    uint16_t* __restrict__ O, float* __restrict__ LSE,
     const int32_t* __restrict__ mix_len, int batch, int T_q, int n_q_heads, int group, int l_cap, int s_total,
     long long kv_head_stride, long long kv_tok, float scale) {
     __shared__ float q_lds[4][D];
@@ -168,13 +169,13 @@ __global__ __launch_bounds__(256) void decode_inplace_simple_kernel(
         return;
     }
     const int32_t* src = src_idx + (size_t)b * l_cap;
-    const T* kh = K + (size_t)g * kv_head_stride;
-    const T* vh = V + (size_t)g * kv_head_stride;
-    const T* ksh = Ksp ? Ksp + (size_t)g * s_total * D : nullptr;
-    const T* vsh = Vsp ? Vsp + (size_t)g * s_total * D : nullptr;
+    const uint16_t* kh = K + (size_t)g * kv_head_stride;
+    const uint16_t* vh = V + (size_t)g * kv_head_stride;
+    const uint16_t* ksh = Ksp ? Ksp + (size_t)g * s_total * D : nullptr;
+    const uint16_t* vsh = Vsp ? Vsp + (size_t)g * s_total * D : nullptr;
     auto krow = [=](int slot) { const int t = src[slot]; return t >= 0 ? kh + (size_t)t * kv_tok : ksh + (size_t)(-1 - t) * D; };
     auto vrow = [=](int slot) { const int t = src[slot]; return t >= 0 ? vh + (size_t)t * kv_tok : vsh + (size_t)(-1 - t) * D; };
-    attend_row<T, D>(Qd + row * D, krow, vrow, n_keys, scale, q_lds[wave], O + row * D, LSE ? LSE + row : nullptr);
+    attend_row<D>(Qd + row * D, krow, vrow, n_keys, scale, q_lds[wave], O + row * D, LSE ? LSE + row : nullptr);
 }
 
 }  // namespace
@@ -185,11 +186,12 @@ vxl_status launch_prefill_simple(const vxl_layout* L, const vxl_attn_desc* d, fl
     const dim3 grid((L->n_tokens + 3) / 4, d->n_q_heads), block(256);
     const int group = d->n_q_heads / d->n_kv_heads;
     const TokStrides ts = tok_strides(d, L->n_tokens);
-#define VXL_LAUNCH(T, D)                                                                          \
-    hipLaunchKernelGGL((prefill_simple_kernel<T, D>), grid, block, 0, s, (const T*)Q, (const T*)K, \
-                       (const T*)V, (T*)O, LSE, L->d_bounds, L->d_soff, L->d_sidx, L->n_tokens,   \
-                       L->n_prefix, L->n_chunks, group, scale, L->window, ts.qh, ts.qt, ts.kh, ts.kt)
-    if (d->head_dim == 64) VXL_LAUNCH(uint16_t, 64); else VXL_LAUNCH(uint16_t, 128);
+#define VXL_LAUNCH(D)                                                                                \
+    hipLaunchKernelGGL((prefill_simple_kernel<D>), grid, block, 0, s, (const uint16_t*)Q,            \
+                       (const uint16_t*)K, (const uint16_t*)V, (uint16_t*)O, LSE, L->d_bounds,       \
+                       L->d_soff, L->d_sidx, L->n_tokens, L->n_prefix, L->n_chunks, group, scale,    \
+                       L->window, ts.qh, ts.qt, ts.kh, ts.kt)
+    if (d->head_dim == 64) VXL_LAUNCH(64); else VXL_LAUNCH(128);
 #undef VXL_LAUNCH
     VXL_HIP_TRY(hipGetLastError());
     return VXL_OK;
@@ -201,11 +203,11 @@ vxl_status launch_decode_simple(const vxl_attn_desc* d, float scale, const void*
     const long n_rows = (long)batch * T * d->n_q_heads;
     const dim3 grid((unsigned)((n_rows + 3) / 4)), block(256);
     const int group = d->n_q_heads / d->n_kv_heads;
-#define VXL_LAUNCH(T_, D)                                                                            \
-    hipLaunchKernelGGL((decode_simple_kernel<T_, D>), grid, block, 0, s, (const T_*)Qd,              \
-                       (const T_*)Kmix, (const T_*)Vmix, (T_*)O, LSE, mix_len, batch, T, d->n_q_heads, \
-                       group, l_cap, scale)
-    if (d->head_dim == 64) VXL_LAUNCH(uint16_t, 64); else VXL_LAUNCH(uint16_t, 128);
+#define VXL_LAUNCH(D)                                                                                \
+    hipLaunchKernelGGL((decode_simple_kernel<D>), grid, block, 0, s, (const uint16_t*)Qd,            \
+                       (const uint16_t*)Kmix, (const uint16_t*)Vmix, (uint16_t*)O, LSE, mix_len,     \
+                       batch, T, d->n_q_heads, group, l_cap, scale)
+    if (d->head_dim == 64) VXL_LAUNCH(64); else VXL_LAUNCH(128);
 #undef VXL_LAUNCH
     VXL_HIP_TRY(hipGetLastError());
     return VXL_OK;
@@ -219,11 +221,12 @@ vxl_status launch_decode_inplace_simple(const vxl_layout* L, const vxl_attn_desc
     const dim3 grid((unsigned)((n_rows + 3) / 4)), block(256);
     const int group = d->n_q_heads / d->n_kv_heads;
     const TokStrides ts = tok_strides(d, L->n_tokens);
-#define VXL_LAUNCH(T_, D)                                                                                    \
-    hipLaunchKernelGGL((decode_inplace_simple_kernel<T_, D>), grid, block, 0, s, (const T_*)Qd, (const T_*)K,  \
-                       (const T_*)V, (const T_*)Ksp, (const T_*)Vsp, src_idx, (T_*)O, LSE, mix_len, batch, T,   \
+#define VXL_LAUNCH(D)                                                                                \
+    hipLaunchKernelGGL((decode_inplace_simple_kernel<D>), grid, block, 0, s, (const uint16_t*)Qd,    \
+                       (const uint16_t*)K, (const uint16_t*)V, (const uint16_t*)Ksp,                 \
+                       (const uint16_t*)Vsp, src_idx, (uint16_t*)O, LSE, mix_len, batch, T,          \
                        d->n_q_heads, group, l_cap, L->s_total, ts.kh, ts.kt, scale)
-    if (d->head_dim == 64) VXL_LAUNCH(uint16_t, 64); else VXL_LAUNCH(uint16_t, 128);
+    if (d->head_dim == 64) VXL_LAUNCH(64); else VXL_LAUNCH(128);
 #undef VXL_LAUNCH
     VXL_HIP_TRY(hipGetLastError());
     return VXL_OK;
