@@ -349,15 +349,17 @@ __global__ __launch_bounds__(256) void pool_sparse_kernel(const T* __restrict__ 
 // share of the mixed rows: a group of LPR lanes per row (all KV heads, K and V, 16-byte
 // accesses), the source row found by binary search in the scanned offsets.  A block handles
 // `groups` consecutive passes of 256 / LPR rows (chosen by the host so that small gathers still
-// fill the chip and large ones amortise the scan).  Bound by HBM when large: the pieces of four KV heads
-// are requested before the first store (a head's two loads and two stores in turn: 158 us for the eight
-// mixed sets of 25k rows, 835 MB in and out; 140 us, 6.0 TB/s, so).  Block 0 of a query writes mix_len; a query whose
+// fill the chip and large ones amortise the scan).  Block 0 of a query writes mix_len; a query whose
 // mixed set does not fit l_cap gets mix_len = -(rows needed) and none of its rows is copied.
+// Bound by HBM when large.  A head's two loads and two stores follow one another, at eight waves per SIMD;
+// FOUR (exactly four KV heads): the pieces of all heads are requested before the first store, at four waves
+// per SIMD (the line is at launch_gather).  835 MB in and out, eight mixed sets of 25k rows: 158 us one head
+// after the other, 140 us (6.0 TB/s) at four heads together; with eight waves per SIMD 148.
 // With Kmix == nullptr nothing is copied at all: the call only writes mix_len and src_idx (the row
 // map the in-place decode reads the dense and sparse rows through).
 // ------------------------------------------------------------------------------------------
-template <int ROW_BYTES>
-__global__ __launch_bounds__(256) void gather_kernel(
+template <int ROW_BYTES, bool FOUR>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(FOUR ? 4 : 8, FOUR ? 4 : 8))) void gather_kernel(
     const uint4* __restrict__ K, const uint4* __restrict__ V, const uint8_t* __restrict__ dense_mask,
     const int32_t* __restrict__ bounds, const int32_t* __restrict__ soff, const int32_t* __restrict__ sidx,
     int n_chunks, int n_prefix, long long kv_head_u4, long long kv_tok_u4,   // K, V strides in 16-byte units
@@ -437,24 +439,24 @@ __global__ __launch_bounds__(256) void gather_kernel(
         const size_t row_u4 = src >= 0 ? (size_t)src * kv_tok_u4 : (size_t)(-1 - src) * LPR;
         const size_t s_off = row_u4 + part, d_off = ((size_t)b * n_kv_heads * l_cap + r) * LPR + part;
         const size_t d_head = (size_t)l_cap * LPR;
-        int g = 0;
-        for (; g + 4 <= n_kv_heads; g += 4) {                 // eight loads in flight, then the stores
+        if constexpr (FOUR) {
             uint4 kq[4], vq[4];
 #pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                kq[u] = ks[s_off + (g + u) * head_u4];
-                vq[u] = vs[s_off + (g + u) * head_u4];
+            for (int g = 0; g < 4; ++g) {
+                kq[g] = ks[s_off + g * head_u4];
+                vq[g] = vs[s_off + g * head_u4];
             }
 #pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                Kmix[d_off + (g + u) * d_head] = kq[u];
-                Vmix[d_off + (g + u) * d_head] = vq[u];
+            for (int g = 0; g < 4; ++g) {
+                Kmix[d_off + g * d_head] = kq[g];
+                Vmix[d_off + g * d_head] = vq[g];
             }
-        }
-        for (; g < n_kv_heads; ++g) {
-            const uint4 kq = ks[s_off + g * head_u4], vq = vs[s_off + g * head_u4];
-            Kmix[d_off + g * d_head] = kq;
-            Vmix[d_off + g * d_head] = vq;
+        } else {
+            for (int g = 0; g < n_kv_heads; ++g) {
+                const uint4 kq = ks[s_off + g * head_u4], vq = vs[s_off + g * head_u4];
+                Kmix[d_off + g * d_head] = kq;
+                Vmix[d_off + g * d_head] = vq;
+            }
         }
     }
 }
@@ -541,6 +543,12 @@ vxl_status launch_gather(const vxl_layout* L, const vxl_attn_desc* d, const void
                          void* Vmix, int l_cap, int32_t* mix_len, int32_t* src_idx, hipStream_t s) {
     const int row_bytes = d->head_dim * (d->dtype == VXL_BF16 ? 2 : 4);
     const size_t smem = (size_t)(L->n_chunks + 1) * sizeof(int);
+    // Four heads together where there are four and the mixed buffers do not fit the on-package cache (256 MB).
+    // One head after the other -> together, us: bf16, D = 128, 520 MB 183 -> 165 and 635 MB 231 -> 197; D = 64,
+    // 247 MB 105 -> 91; fp32, D = 128, 328 MB 129 -> 114, 1,266 MB 437 -> 441.  Below the line 42.0 -> 43.7
+    // (120 MB) and 68 -> 72 (238 MB), but also 66 -> 60 (153 MB).  Other head counts in groups of four lose up to
+    // 18 %: eight heads, D = 128, 987 MB 347 -> 377; sixteen, D = 64, 1,958 MB 602 -> 725.
+    const bool four = Kmix && d->n_kv_heads == 4 && 8ll * batch * l_cap * row_bytes > (256ll << 20);
     const TokStrides ts = tok_strides(d, L->n_tokens);
     const long long epc = d->dtype == VXL_BF16 ? 8 : 4;
 #define VXL_LAUNCH(RB)                                                                             \
@@ -549,7 +557,8 @@ vxl_status launch_gather(const vxl_layout* L, const vxl_attn_desc* d, const void
         const long passes = (l_cap + rows - 1) / rows;                                             \
         const int groups = (int)std::max<long>(1, std::min<long>(8, passes * batch / 512));        \
         const dim3 grid((unsigned)((passes + groups - 1) / groups), batch);                        \
-        hipLaunchKernelGGL((gather_kernel<RB>), grid, dim3(256), smem, s, (const uint4*)K,         \
+        hipLaunchKernelGGL((four ? gather_kernel<RB, true> : gather_kernel<RB, false>), grid,      \
+                           dim3(256), smem, s, (const uint4*)K,                                    \
                            (const uint4*)V, dense_mask, L->d_bounds, L->d_soff, L->d_sidx,         \
                            L->n_chunks, L->n_prefix, ts.kh / epc, ts.kt / epc, d->n_kv_heads,      \
                            l_cap, groups,                                                         \

@@ -143,6 +143,38 @@ def test_gather_head_counts(dtype, d, n_kv_heads):
         assert (hk[b, :, n:] == 7.0).all() and (hv[b, :, n:] == 7.0).all()
 
 
+@pytest.mark.parametrize("pooled", [False, True])
+@pytest.mark.parametrize("dtype,d", [("f32", 128), ("bf16", 64), ("bf16", 128)])
+def test_gather_four_heads_into_large_buffers(dtype, d, pooled):
+    """Mixed buffers of more than 256 MB (capacity; the sets are small) with four KV heads, which takes the instance that
+    moves all heads together: its rows and lengths, and what lies behind them, as in small buffers, bit for bit."""
+    w = wl.tiny_workload(dtype, 4, 4, d, T=1, B=3, k=2, seed=94)
+    lay = wl.random_layout(np.random.default_rng(94), 5, 300, 1, 61)
+    _, k, v = wl.make_qkv(w, lay, with_q=False)
+    gl, desc = make_layout(lay), desc_of(w)
+    dk, dv = vxl.to_device(k, w.dtype), vxl.to_device(v, w.dtype)
+    masks = np.random.default_rng(95).random((3, 300)) < np.array([[0.3], [0.0], [1.0]])
+    dm = torch.from_numpy(masks.astype(np.uint8)).cuda()
+    need = lay.n_tokens
+    sparse = ()
+    if pooled:
+        sparse = tuple(torch.empty((4, int(lay.sparse_offsets[-1]), d), dtype=dk.dtype, device="cuda") for _ in range(2))
+        vxl.pool_sparse_kv(gl, desc, dk, dv, *sparse)
+    call = vxl.gather_bilevel_kv_pooled if pooled else vxl.gather_bilevel_kv
+    got = []
+    for l_cap in (need, max(need, (256 << 20) // (8 * 3 * d * dk.element_size()) + 1)):
+        kmix = torch.full((3, 4, l_cap, d), 7.0, dtype=dk.dtype, device="cuda")
+        vmix = torch.full_like(kmix, 7.0)
+        mix_len = torch.zeros((3,), dtype=torch.int32, device="cuda")
+        call(gl, desc, dk, dv, *sparse, dm, kmix, vmix, mix_len)
+        torch.cuda.synchronize()
+        assert (kmix[:, :, need:] == 7.0).all() and (vmix[:, :, need:] == 7.0).all()
+        got.append((mix_len, kmix[:, :, :need].clone(), vmix[:, :, :need].clone()))
+    assert got[0][0].tolist() == [5 + sum(int(b - a) if m else int(t - s) for m, a, b, s, t in zip(
+        masks[q], lay.chunk_bounds, lay.chunk_bounds[1:], lay.sparse_offsets, lay.sparse_offsets[1:])) for q in range(3)]
+    assert all(torch.equal(x, y) for x, y in zip(*got))
+
+
 def test_pooled_gather_without_sparse_rows_and_all_dense():
     w = wl.tiny_workload("bf16", 4, 2, 128, T=1, B=1, k=1, seed=92)
     lay = wl.layout_from_lists(4, [40, 24], [np.zeros(0, np.int32)] * 2)           # nothing kept: S_total = 0
