@@ -3,6 +3,7 @@
 #include <math.h>
 
 #include <algorithm>
+#include <type_traits>
 
 #include "vxl_internal.h"
 
@@ -276,10 +277,12 @@ __global__ __launch_bounds__(512) void topk_from_scores_kernel(const float* __re
 // the group's rows, K and V alike.  LPR lanes per pooled row (a 16-byte piece each), fp32 sums in
 // row order, one division, one rounding to the storage dtype.
 // Bound by HBM (dense K and V once), as long as enough loads are in flight: four rows of K and of V
-// are requested before the first addition (clamped to the group's last row, which is not added
-// again), a result is stored as one piece, and the chunk of a row is found by two or three probes of
-// its LPR lanes instead of a chain of halvings.  K and V of 131,328 tokens (303 MB in and out):
-// 64.5 us with one row at a time and stores of two bytes, 62.5 so (4.8 TB/s).
+// are requested before the first addition, the last two or one of a group by themselves (a whole four
+// with repeated rows made groups of one row 10 % slower than one row at a time), a result is stored as
+// one piece, and the chunk of a row is found by two or three probes of its LPR lanes instead of a
+// chain of halvings.  Eight waves per SIMD: the compiler would widen all rows of a batch first (90
+// registers).  K and V of 131,328 tokens (303 MB in and out): 64.5 us with one row at a time and stores
+// of two bytes, 61.4 so; 16,384 groups of one row of four heads, D = 128: 18.7 -> 17.6 (repeated rows 20.4).
 // ------------------------------------------------------------------------------------------
 __device__ __forceinline__ void st_round(float* p, float v) { *p = v; }
 __device__ __forceinline__ void st_round(uint16_t* p, float v) {
@@ -289,7 +292,7 @@ __device__ __forceinline__ void st_round(uint16_t* p, float v) {
 }
 
 template <typename T, int D>
-__global__ __launch_bounds__(256) void pool_sparse_kernel(const T* __restrict__ K, const T* __restrict__ V,
+__global__ __launch_bounds__(256, 8) void pool_sparse_kernel(const T* __restrict__ K, const T* __restrict__ V,
                                                           const int32_t* __restrict__ bounds,
                                                           const int32_t* __restrict__ soff, int n_chunks,
                                                           long long kv_head_u4, long long kv_tok_u4,
@@ -313,26 +316,31 @@ __global__ __launch_bounds__(256) void pool_sparse_kernel(const T* __restrict__ 
     float ak[EPC], av[EPC];
 #pragma unroll
     for (int i = 0; i < EPC; ++i) ak[i] = av[i] = 0.f;
-    const uint4* kp = (const uint4*)K + (size_t)g * kv_head_u4 + part;   // (K, V strides in 16-byte units)
-    const uint4* vp = (const uint4*)V + (size_t)g * kv_head_u4 + part;
-    for (int t = lo; t < hi; t += 4) {
-        uint4 kq[4], vq[4];
+    const size_t first = (size_t)g * kv_head_u4 + (size_t)lo * kv_tok_u4 + part;   // (K, V strides in 16-byte units)
+    const uint4 *kp = (const uint4*)K + first, *vp = (const uint4*)V + first;
+    auto rows = [&](auto n) __attribute__((always_inline)) {   // the loads of n rows, then their additions
+        constexpr int N = decltype(n)::value;
+        uint4 kq[N], vq[N];
 #pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            const size_t at = (size_t)min(t + u, hi - 1) * kv_tok_u4;
-            kq[u] = kp[at];
-            vq[u] = vp[at];
+        for (int u = 0; u < N; ++u) {
+            kq[u] = kp[u * kv_tok_u4];
+            vq[u] = vp[u * kv_tok_u4];
         }
 #pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            if (t + u < hi) {
-                const T* ke = (const T*)&kq[u];
-                const T* ve = (const T*)&vq[u];
+        for (int u = 0; u < N; ++u) {
+            const T* ke = (const T*)&kq[u];
+            const T* ve = (const T*)&vq[u];
 #pragma unroll
-                for (int i = 0; i < EPC; ++i) { ak[i] += ld(ke + i); av[i] += ld(ve + i); }
-            }
+            for (int i = 0; i < EPC; ++i) { ak[i] += ld(ke + i); av[i] += ld(ve + i); }
         }
-    }
+        kp += N * kv_tok_u4;
+        vp += N * kv_tok_u4;
+    };
+    int left = hi - lo;
+#pragma unroll 1
+    for (; left >= 4; left -= 4) rows(std::integral_constant<int, 4>{});
+    if (left & 2) rows(std::integral_constant<int, 2>{});
+    if (left & 1) rows(std::integral_constant<int, 1>{});
     const float n = (float)(hi - lo);
     __attribute__((aligned(16))) T ko[EPC], vo[EPC];
 #pragma unroll

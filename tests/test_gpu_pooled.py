@@ -70,6 +70,20 @@ def test_pool_finds_chunks(dtype, d, chunks):
     check_pool(w, lay, k, v)
 
 
+@pytest.mark.parametrize("dtype,d", [("f32", 64), ("bf16", 128)])
+def test_pool_group_lengths(dtype, d):
+    """Groups of 1 to 13 rows, which end in every remainder of the four rows requested together, side by side."""
+    w = wl.tiny_workload(dtype, 2, 2, d, T=1, B=1, k=1, seed=96)
+    lens = list(range(1, 14)) + [26, 7, 3]
+    kept, start = [], 3
+    for i, n in enumerate(lens):
+        kept.append(np.arange(start, start + (1 if i < 13 else 2), dtype=np.int32))
+        start += n
+    lay = wl.layout_from_lists(3, lens, kept)
+    _, k, v = wl.make_qkv(w, lay, with_q=False)
+    check_pool(w, lay, k, v)
+
+
 @pytest.mark.parametrize("name", ["config0", "config1", "config4"])
 def test_pooled_chain(name):
     """select -> pool -> gather (pooled) -> decode, everything on the device; the gathered set is
