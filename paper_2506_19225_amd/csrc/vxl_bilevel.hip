@@ -131,16 +131,15 @@ __global__ __launch_bounds__(256) void chunk_summarize_kernel(const T* __restric
 // p, p + 16, ... of the flattened (kv head, d) range (256 contiguous bytes per step), in that
 // order, and the sixteen partial dot products are added in a fixed tree.  A chunk's score thus
 // depends on nothing but its mean keys, whichever kernel computes it: equal chunks tie exactly.
-// Latency bound (2 KiB per chunk): the pieces of eight steps of both operands are requested
-// before the first multiply-add.  Every lane of the group returns the score.
+// Latency bound (2 KiB per chunk): the pieces of U steps of both operands are requested before the
+// first multiply-add (U changes no bit).  Every lane of the group returns the score.
 // ------------------------------------------------------------------------------------------
 constexpr int kScoreLanes = 16;
 
-template <int D>
+template <int D, int U = 8>
 __device__ __forceinline__ float chunk_score(const float* __restrict__ qbar_b, const float* __restrict__ kbar,
                                              int c, int n_kv_heads, int n_chunks, int p) {
     constexpr int PPH = D / 4;                                // 16-byte pieces per KV head
-    constexpr int U = 8;
     const int n_pieces = n_kv_heads * PPH;
     const float4* q4 = (const float4*)qbar_b;
     const float4* k4 = (const float4*)kbar + (size_t)c * PPH;
@@ -233,28 +232,35 @@ __global__ __launch_bounds__(256) void chunk_score_kernel(const float* __restric
 // price of one compute unit reading all mean keys of a query (2 KiB per chunk at four KV heads):
 // 4.1 us at 64 chunks (9.6 with 256 threads and one load at a time), against 4.7 for each of the
 // two launches of the separate form.
+// A block has threads for no more chunks than there are (16, 32 or 64 at once: starting 16 waves costs more
+// than a few chunks take) and requests no more steps than a row has (two up to 32 pieces, otherwise eight).
+// us of the whole call with the mean keys there, one form of 16 waves and eight steps -> so: two KV heads,
+// D = 64, 4 chunks 6.5 -> 4.8, 19 chunks 6.5 -> 5.0, 64 chunks 6.6 -> 5.3, 128 chunks 8.6 -> 6.0; four KV heads,
+// D = 128, 4 chunks 6.5 -> 5.2, 32 chunks 6.5 -> 5.7.
 constexpr int kFusedChunks = 128;
 
-template <int D>
-__global__ __launch_bounds__(1024) void score_topk_kernel(
+template <int D, int THREADS, int U>
+__global__ __launch_bounds__(THREADS) void score_topk_kernel(
     const float* __restrict__ qbar, const float* __restrict__ kbar, int n_kv_heads, int n_chunks, int k, float scale,
     int32_t* __restrict__ topk_idx, uint8_t* __restrict__ dense_mask, float* __restrict__ scores) {
-    __shared__ __attribute__((aligned(16))) unsigned long long keys[kFusedChunks];
-    __shared__ int part[1024];
+    constexpr int AT_ONCE = THREADS / kScoreLanes, MAX = AT_ONCE < 64 ? AT_ONCE : kFusedChunks;
+    constexpr int GROUPS = (MAX + 63) / 64;
+    __shared__ __attribute__((aligned(16))) unsigned long long keys[MAX];
+    __shared__ int part[THREADS];
     const int b = blockIdx.x, tid = threadIdx.x, p = tid % kScoreLanes;
 #pragma unroll
-    for (int base = 0; base < kFusedChunks; base += 1024 / kScoreLanes) {
+    for (int base = 0; base < MAX; base += AT_ONCE) {
         const int c = base + tid / kScoreLanes;
         if (base >= n_chunks) break;                          // (uniform)
-        const float a = chunk_score<D>(qbar + (size_t)b * n_kv_heads * D, kbar, min(c, n_chunks - 1), n_kv_heads,
-                                       n_chunks, p) * (scale / (float)n_kv_heads);
+        const float a = chunk_score<D, U>(qbar + (size_t)b * n_kv_heads * D, kbar, min(c, n_chunks - 1), n_kv_heads,
+                                          n_chunks, p) * (scale / (float)n_kv_heads);
         if (p == 0) {
             if (c < n_chunks && scores) scores[(size_t)b * n_chunks + c] = a;
             keys[c] = c < n_chunks ? rank_key(a, c) : 0ull;
         }
     }
     __syncthreads();
-    rank_select<16, kFusedChunks / 64>(keys, part, n_chunks, 0, k, b, topk_idx, dense_mask);
+    rank_select<THREADS / 64, GROUPS>(keys, part, n_chunks, 0, k, b, topk_idx, dense_mask);
 }
 
 // Selection alone, from scores some other kernel has written: 64 chunks per block (grid: chunk
@@ -508,13 +514,20 @@ vxl_status launch_score_topk(const vxl_layout* L, const vxl_attn_desc* d, float 
         VXL_HIP_TRY(hipGetLastError());
         return launch_topk_from_scores(L, sc, batch, k, topk_idx, dense_mask, s);
     }
-    const dim3 grid(batch), block(1024);
-    if (d->head_dim == 64)
-        hipLaunchKernelGGL((score_topk_kernel<64>), grid, block, 0, s, qbar, kbar, d->n_kv_heads, L->n_chunks, k,
-                           scale, topk_idx, dense_mask, scores);
-    else
-        hipLaunchKernelGGL((score_topk_kernel<128>), grid, block, 0, s, qbar, kbar, d->n_kv_heads, L->n_chunks, k,
-                           scale, topk_idx, dense_mask, scores);
+#define VXL_LAUNCH(D, THREADS, U)                                                                              \
+    hipLaunchKernelGGL((score_topk_kernel<D, THREADS, U>), dim3(batch), dim3(THREADS), 0, s, qbar, kbar,         \
+                       d->n_kv_heads, L->n_chunks, k, scale, topk_idx, dense_mask, scores)
+#define VXL_BY_CHUNKS(D, U)                                                                                     \
+    do {                                                                                                        \
+        if (L->n_chunks <= 256 / kScoreLanes) VXL_LAUNCH(D, 256, U);                                            \
+        else if (L->n_chunks <= 512 / kScoreLanes) VXL_LAUNCH(D, 512, U);                                       \
+        else VXL_LAUNCH(D, 1024, U);                                                                            \
+    } while (0)
+    const bool short_rows = d->n_kv_heads * d->head_dim <= 2 * kScoreLanes * 4;
+    if (d->head_dim == 64) { if (short_rows) VXL_BY_CHUNKS(64, 2); else VXL_BY_CHUNKS(64, 8); }
+    else { if (short_rows) VXL_BY_CHUNKS(128, 2); else VXL_BY_CHUNKS(128, 8); }
+#undef VXL_BY_CHUNKS
+#undef VXL_LAUNCH
     VXL_HIP_TRY(hipGetLastError());
     return VXL_OK;
 }

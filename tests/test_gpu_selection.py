@@ -1,5 +1,6 @@
 """Scores and selection at the chunk counts where the kernels change form or a block, wave or key pair is only
-partly filled: one launch up to 128 chunks, 16 chunks per score block and 64 per selection block beyond."""
+partly filled: one launch up to 128 chunks (blocks for 16, 32 and 64 chunks at once), 16 chunks per score block and
+64 per selection block beyond."""
 import numpy as np
 import pytest
 import torch
@@ -12,7 +13,7 @@ from gpu_util import full_sort_selection, gpu_score_topk
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("n_chunks", [1, 2, 63, 64, 65, 127, 128, 129, 143, 640, 1025, 4095, 4096])
+@pytest.mark.parametrize("n_chunks", [1, 2, 15, 16, 17, 18, 31, 32, 33, 34, 63, 64, 65, 127, 128, 129, 143, 640, 1025, 4095, 4096])
 def test_selection_is_a_full_sort_of_the_scores(n_chunks):
     """Every third chunk repeats one of a few contents, so that many scores tie exactly; the scores agree with the
     oracle to the rounding of 3 x 128 fp32 products (2e-5 of the largest), the selection is the full sort of them."""
@@ -32,3 +33,19 @@ def test_selection_is_a_full_sort_of_the_scores(n_chunks):
         assert np.abs(scores - want).max() <= 2e-5 * np.abs(want).max()
         own_idx, own_mask = full_sort_selection(scores, top_k)
         assert np.array_equal(idx, own_idx) and np.array_equal(mask, own_mask)
+
+
+@pytest.mark.parametrize("hkv,d", [(1, 64), (2, 64), (1, 128), (3, 64), (2, 128), (16, 128)])
+def test_a_score_does_not_depend_on_the_number_of_chunks(hkv, d):
+    """The first chunks of a prompt get the same bits from every form of the score kernel (rows of 16 to 512 pieces)."""
+    rng = np.random.default_rng(hkv * d)
+    counts, ln = (16, 17, 32, 33, 64, 65, 128, 129, 300), 2
+    w = wl.tiny_workload("f32", 2 * hkv, hkv, d, T=3, B=2, k=1, seed=d)
+    k = rng.standard_normal((hkv, 300 * ln, d)).astype(np.float32)
+    qd = wl.make_decode_queries(w)
+    want = None
+    for n_chunks in counts:
+        lay = wl.layout_from_lists(0, [ln] * n_chunks, [np.zeros(0, np.int32)] * n_chunks)
+        _, _, scores = gpu_score_topk(w, lay, qd, np.ascontiguousarray(k[:, :n_chunks * ln]), 1)
+        want = scores[:, :16].copy() if want is None else want
+        assert np.array_equal(scores[:, :16].view(np.uint32), want.view(np.uint32)), n_chunks
