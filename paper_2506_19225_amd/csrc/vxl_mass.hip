@@ -220,18 +220,17 @@ __global__ __launch_bounds__(256) void mass_partial_simple_kernel(
 
 // Per stacked row (b, g, rho): M = max over the items of m, 1/L with L = sum l * 2^(m - M).  A block
 // handles 32 consecutive rows of one (b, g): thread (ig, r) folds the items ig, ig + GROUPS, ... of
-// row r into a running (M, L), eight items at a time whose loads are all requested first (coalesced
-// over the rows), and the GROUPS partial pairs of a row are folded in group order -- a fixed
-// summation order.  Bound by latency: few rows, hundreds of items each.  32 groups beyond 64 items
-// (448 rows x 4 heads, 257 items: 14.3 us with eight groups taking their items one by one, 6.7 so);
-// up to 64 items eight groups hold them all in one batch.
-template <int GROUPS>
+// row r into a running (M, L), U items at a time whose loads are all requested first (coalesced
+// over the rows); then the maximum over the GROUPS partial pairs of a row, and their sum in group
+// order -- a fixed summation order without a chain of exponentials.  Bound by latency: few rows, up
+// to hundreds of items each.  Per launch, 448 rows x 4 heads, items taken one by one by eight groups
+// and folded pair by pair -> so: 8 items 2.5 -> 2.1 us, 64 items 3.7 -> 2.5, 257 items 8.2 -> 3.8.
+template <int GROUPS, int U>
 __global__ __launch_bounds__(32 * GROUPS) void mass_rowstat_kernel(const float* __restrict__ part_m,
                                                                    const float* __restrict__ part_l,
                                                                    float* __restrict__ row_m,
                                                                    float* __restrict__ row_il, int n_items,
                                                                    int n_rows) {
-    constexpr int U = 8;
     __shared__ float sm[GROUPS][32], sl[GROUPS][32];
     const int r = threadIdx.x & 31, ig = threadIdx.x >> 5;
     const int rho = blockIdx.x * 32 + r;
@@ -261,15 +260,14 @@ __global__ __launch_bounds__(32 * GROUPS) void mass_rowstat_kernel(const float* 
     sl[ig][r] = L;
     __syncthreads();
     if (ig == 0 && rho < n_rows) {
-        for (int k = 1; k < GROUPS; ++k) {
-            const float m = sm[k][r], l = sl[k][r];
-            if (m == -INFINITY) continue;                      // a group without items
-            const float Mn = fmaxf(M, m);
-            L = L * exp2f(M - Mn) + l * exp2f(m - Mn);
-            M = Mn;
-        }
-        row_m[bg * n_rows + rho] = M;
-        row_il[bg * n_rows + rho] = 1.f / L;
+        float Mr = M;
+#pragma unroll
+        for (int k = 1; k < GROUPS; ++k) Mr = fmaxf(Mr, sm[k][r]);
+        float Lr = L * exp2f(M - Mr);
+#pragma unroll
+        for (int k = 1; k < GROUPS; ++k) Lr += sl[k][r] * exp2f(sm[k][r] - Mr);   // (a group without items: 0 * 2^-inf)
+        row_m[bg * n_rows + rho] = Mr;
+        row_il[bg * n_rows + rho] = 1.f / Lr;
     }
 }
 
@@ -362,11 +360,18 @@ vxl_status launch_score_mass(const vxl_layout* L, const vxl_attn_desc* d, float 
     }
     VXL_HIP_TRY(hipGetLastError());
     const dim3 stat_grid((n_rows + 31) / 32, batch * d->n_kv_heads);
-    if (n_items > 64)
-        hipLaunchKernelGGL((mass_rowstat_kernel<32>), stat_grid, dim3(32 * 32), 0, s, part_m, part_l, row_m, row_il,
+    // Up to 16 items eight groups hold them in one batch; more loads per thread or groups only cost there
+    // (1 row, 8 items: 2.1 us, with sixteen groups of four loads 2.5).  Sixteen groups of four up to a few
+    // hundred items (1 row, 64 items 2.6 against 3.2 with 32 groups; 448 rows, 257 items 3.8 against 4.0),
+    // 32 groups beyond (1 row, 641 items 6.9 against 9.2; 896 rows x 8 heads 7.1 against 7.9).
+    if (n_items > 512)
+        hipLaunchKernelGGL((mass_rowstat_kernel<32, 4>), stat_grid, dim3(32 * 32), 0, s, part_m, part_l, row_m, row_il,
+                           n_items, n_rows);
+    else if (n_items > 16)
+        hipLaunchKernelGGL((mass_rowstat_kernel<16, 4>), stat_grid, dim3(32 * 16), 0, s, part_m, part_l, row_m, row_il,
                            n_items, n_rows);
     else
-        hipLaunchKernelGGL((mass_rowstat_kernel<8>), stat_grid, dim3(32 * 8), 0, s, part_m, part_l, row_m, row_il,
+        hipLaunchKernelGGL((mass_rowstat_kernel<8, 2>), stat_grid, dim3(32 * 8), 0, s, part_m, part_l, row_m, row_il,
                            n_items, n_rows);
     VXL_HIP_TRY(hipGetLastError());
     hipLaunchKernelGGL(mass_chunk_kernel, dim3(L->n_chunks, batch),

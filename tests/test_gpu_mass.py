@@ -123,3 +123,15 @@ def test_mass_reference_raised_inside_an_item(d, t, lens):
     k = wl.round_to_bf16(k * 0.1 + ramp[None, :, None].astype(np.float32) * np.sign(k[:, :1, :]))
     qd = wl.round_to_bf16((np.sign(qd) * np.float32(0.2) + np.sign(k[0, 0])) * 3)
     check_mass(w, lay, qd, k, 2, scale=1.0)
+
+
+@pytest.mark.parametrize("n_items", [1, 8, 9, 16, 17, 63, 64, 65, 128, 130, 512, 513, 641])
+def test_mass_row_statistics_at_the_edges_of_their_batches(n_items):
+    """The items of a row are folded by 8 groups of 2 at a time, 16 groups of 4 or 32 of 4: around one batch of each, with
+    items whose mass differs by orders of magnitude; 33 stacked rows, one more than a block holds."""
+    rng = np.random.default_rng(76 + n_items)
+    w = wl.tiny_workload("bf16", 6, 2, 64, T=11, B=2, k=1, seed=76)
+    lay = wl.layout_from_lists(0, rng.integers(1, 40, n_items).tolist(), [np.zeros(0, np.int32)] * n_items)
+    _, k, _ = wl.make_qkv(w, lay, with_q=False)
+    k = wl.round_to_bf16(k * np.repeat(rng.uniform(0.2, 6.0, n_items), np.diff(lay.chunk_bounds))[None, :, None].astype(np.float32))
+    check_mass(w, lay, wl.make_decode_queries(w), k, min(3, n_items))
