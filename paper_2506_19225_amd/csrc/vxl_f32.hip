@@ -353,8 +353,8 @@ __global__ __launch_bounds__(256, 2) void prefill_f32_kernel(
 }
 
 // Decode over the mixed KV set, gathered (rows of Kmix / Vmix) or in place (MAPPED, rows of K / V /
-// Ksp / Vsp through src_idx).  grid: row blocks x KV heads x queries; all W waves of the workgroup
-// share the keys of the block.  No scratch memory: the call takes no workspace for this storage type.
+// Ksp / Vsp through src_idx).  grid: row blocks x KV heads x queries, in one dimension (folded_grid);
+// all W waves of the workgroup share the keys of the block.  No scratch memory: the call takes no workspace for this storage type.
 template <int D> struct DecodeF32 {
     static constexpr int W = D == 64 ? 16 : 8;                // (registers: 96 / 192 for operands and output)
     static constexpr int LDS_BYTES = MergeF32<D, W>::FLOATS * 4;
@@ -364,12 +364,14 @@ __global__ __launch_bounds__(64 * DecodeF32<D>::W, DecodeF32<D>::W / 4) void dec
     const float* __restrict__ Qd, const float* __restrict__ K, const float* __restrict__ V,
     const float* __restrict__ Ksp, const float* __restrict__ Vsp, const int32_t* __restrict__ src_idx,
     float* __restrict__ O, float* __restrict__ LSE, const int32_t* __restrict__ mix_len, int T_q, int n_q_heads,
-    int n_kv_heads, int group, int l_cap, int s_total, long long kv_head, long long kv_tok, float scale) {
+    int n_kv_heads, int group, int batch, int l_cap, int s_total, long long kv_head, long long kv_tok, float scale) {
     constexpr int W = DecodeF32<D>::W;
     extern __shared__ __attribute__((aligned(16))) float lds_f[];
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int g = blockIdx.y, b = blockIdx.z;
-    const int n_rows = T_q * group, rho0 = blockIdx.x * kF32Rows;
+    const int n_rows = T_q * group;
+    const unsigned blocks = (n_rows + kF32Rows - 1) / kF32Rows, id = folded_id(), unit = id / blocks;
+    const int rho0 = id % blocks * kF32Rows, g = unit % n_kv_heads, b = unit / n_kv_heads;
+    if (b >= batch) return;
     auto q_row = [&](int row) __attribute__((always_inline)) {
         const int r = min(rho0 + row, n_rows - 1);
         return Qd + (((size_t)b * T_q + r / group) * n_q_heads + g * group + r % group) * D;
@@ -441,11 +443,11 @@ static vxl_status run_decode_f32(const vxl_attn_desc* d, float scale, const void
         return VXL_OK;
     });
     if (st != VXL_OK) return st;
-    const dim3 grid((group * T + kF32Rows - 1) / kF32Rows, d->n_kv_heads, batch);
+    const dim3 grid = folded_grid((long long)((group * T + kF32Rows - 1) / kF32Rows) * d->n_kv_heads * batch);
 #define VXL_LAUNCH(MAPPED)                                                                                          \
     hipLaunchKernelGGL((decode_f32_kernel<D, MAPPED>), grid, dim3(64 * DecodeF32<D>::W), lds_bytes, s,              \
                        (const float*)Qd, (const float*)K, (const float*)V, (const float*)Ksp, (const float*)Vsp,    \
-                       src_idx, (float*)O, LSE, mix_len, T, d->n_q_heads, d->n_kv_heads, group, l_cap, s_total,     \
+                       src_idx, (float*)O, LSE, mix_len, T, d->n_q_heads, d->n_kv_heads, group, batch, l_cap, s_total, \
                        ts.kh, ts.kt, scale)
     if (src_idx) VXL_LAUNCH(true); else VXL_LAUNCH(false);
 #undef VXL_LAUNCH

@@ -16,6 +16,14 @@ constexpr int kKeyTile = 64;      // keys per K/V tile of the matrix-core kernel
 constexpr int kRowBlock = 32;     // query rows per MFMA block (one 32x32 tile side)
 constexpr int kXcds = 8;          // XCDs, each with an L2 of its own; workgroups go to them in turn
 
+// A one-dimensional launch of `n` workgroups of at most 1,024 threads, folded where x alone does not hold
+// them (2^32 threads): the workgroup's number is folded_id(), numbers >= n exist and return at once.
+constexpr unsigned kMaxGridX = 1u << 21;
+inline dim3 folded_grid(long long n, unsigned z = 1) {
+    return n <= kMaxGridX ? dim3((unsigned)n, 1, z) : dim3(kMaxGridX, (unsigned)((n + kMaxGridX - 1) / kMaxGridX), z);
+}
+__device__ __forceinline__ unsigned folded_id() { return blockIdx.y * gridDim.x + blockIdx.x; }
+
 // One pre-filling segment: the prefix (if any) or a chunk.  Queries of a segment attend to the
 // first ctx_len rows of the compacted history buffer, to the `back` tokens right before the
 // segment (the sliding chunk window's dense look-back range; 0 without a window) and, causally,

@@ -75,11 +75,11 @@ __global__ __launch_bounds__(256, 2) void mass_partial_kernel(
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     // workgroup id -> (unit = (item, KV head), row tile): id = (unit / 8 * n_rt + rt) * 8 + unit % 8
     const int n_rows = group * T_q, n_rt = (n_rows + kMassRowTile - 1) / kMassRowTile;
-    const int xcd = blockIdx.x % kXcds, seq = blockIdx.x / kXcds;
-    const int rt = seq % n_rt, unit = seq / n_rt * kXcds + xcd;
-    if (unit >= n_items * n_kv_heads) return;
-    const int item = unit / n_kv_heads, g = unit % n_kv_heads;
-    const int b = blockIdx.y;
+    const unsigned id = folded_id(), xcd = id % kXcds, seq = id / kXcds;
+    const unsigned unit = seq / n_rt * kXcds + xcd;
+    if (unit >= (unsigned)n_items * n_kv_heads) return;
+    const int rt = seq % n_rt, item = unit / n_kv_heads, g = unit % n_kv_heads;
+    const int b = blockIdx.z;
     const int k_lo = items[item].key_lo, k_hi = items[item].key_hi;
     const int wrow0 = rt * kMassRowTile + wave * 32;
     const bool wave_active = wrow0 < n_rows;          // waves without rows only help with the copies
@@ -341,7 +341,7 @@ vxl_status launch_score_mass(const vxl_layout* L, const vxl_attn_desc* d, float 
     const TokStrides ts = tok_strides(d, L->n_tokens);
     if (d->dtype == VXL_BF16 && !force_simple) {
         const int n_rt = (n_rows + kMassRowTile - 1) / kMassRowTile;
-        const dim3 grid((n_items * d->n_kv_heads + kXcds - 1) / kXcds * kXcds * n_rt, batch);
+        const dim3 grid = folded_grid(((long long)n_items * d->n_kv_heads + kXcds - 1) / kXcds * kXcds * n_rt, batch);
 #define VXL_LAUNCH(D)                                                                                   \
     hipLaunchKernelGGL((mass_partial_kernel<D>), grid, dim3(256), 0, s, (const uint16_t*)Qd,            \
                        (const uint16_t*)K, L->d_mass_items, part_m, part_l, T, d->n_q_heads,            \

@@ -149,3 +149,21 @@ def test_prefill_f32_without_weight(hq, n):
     assert np.isnan(got[:, :40]).all() and np.isnan(lse[:, :40]).all()
     want, wlse = oracle.prefill_blk(q[:, 40:], k[:, 40:], v[:, 40:], 0, [0, n - 40], [0, 0], [], return_lse=True)
     assert np.abs(got[:, 40:] - want).max() <= 1e-5 and np.abs(lse[:, 40:] - wlse).max() <= 1e-4
+
+
+def test_decode_f32_more_queries_than_a_grid_dimension_holds():
+    """70,000 queries of one token over sets of 0 to 3 rows: past the 65,535 workgroups of a grid's y or z."""
+    b, cap, d = 70000, 3, 64
+    gen = torch.Generator(device="cuda").manual_seed(5)
+    qd, km, vm = (torch.empty(s, device="cuda").normal_(generator=gen) for s in ((b, 1, 2, d), (b, 1, cap, d), (b, 1, cap, d)))
+    ml = (torch.arange(b, device="cuda") % 4).to(torch.int32)
+    desc = vxl.make_desc(2, 1, d, "f32")
+    out, lse = torch.full_like(qd, float("nan")), torch.full((b, 1, 2), float("nan"), device="cuda")
+    vxl.bilevel_decode(desc, qd, km, vm, ml, out, lse, vxl.alloc_workspace(vxl.workspace_bytes(vxl.OP_DECODE, None, desc, b, 1, cap)))
+    s = (qd[:, 0, :, None].double() * km.double()).sum(-1) / d ** 0.5                    # [b, 2, cap]
+    s = s.masked_fill(torch.arange(cap, device="cuda")[None, None] >= ml[:, None, None], float("-inf"))
+    want = (torch.softmax(s, -1).nan_to_num(0.0)[..., None] * vm.double()).sum(-2)
+    assert (out[:, 0].double() - want).abs().max().item() <= 1e-5
+    some = ml > 0
+    assert (lse[some, 0].double() - torch.logsumexp(s[some], -1)).abs().max().item() <= 1e-5
+    assert (lse[~some] == float("-inf")).all()

@@ -4,6 +4,7 @@ a full sort of the device's own fp32 scores (both sides decide in fp32) and, whe
 margin of the oracle's scores exceeds the score tolerance, with the oracle's selection."""
 import numpy as np
 import pytest
+import torch
 
 import oracle
 from paper_2506_19225_amd import vxl, workloads as wl
@@ -135,3 +136,22 @@ def test_mass_row_statistics_at_the_edges_of_their_batches(n_items):
     _, k, _ = wl.make_qkv(w, lay, with_q=False)
     k = wl.round_to_bf16(k * np.repeat(rng.uniform(0.2, 6.0, n_items), np.diff(lay.chunk_bounds))[None, :, None].astype(np.float32))
     check_mass(w, lay, wl.make_decode_queries(w), k, min(3, n_items))
+
+
+def test_mass_more_workgroups_than_a_grid_dimension_holds():
+    """4,104 heads over 4,096 chunks of one token: 2^24 workgroups of 256 threads are 2^32 threads, a grid's limit in x."""
+    h, c, d = 4104, 4096, 64
+    gen = torch.Generator(device="cuda").manual_seed(6)
+    k = torch.empty((h, c, d), dtype=torch.bfloat16, device="cuda").normal_(generator=gen)
+    qd = torch.empty((1, 1, h, d), dtype=torch.bfloat16, device="cuda").normal_(generator=gen)
+    layout = vxl.Layout(0, np.arange(c + 1, dtype=np.int32), np.zeros(c + 1, np.int32), np.zeros(0, np.int32))
+    desc = vxl.make_desc(h, h, d, "bf16")
+    idx, mask = torch.zeros((1, 1), dtype=torch.int32, device="cuda"), torch.zeros((1, c), dtype=torch.uint8, device="cuda")
+    scores = torch.full((1, c), float("nan"), device="cuda")
+    vxl.chunk_score_topk_mass(layout, desc, qd, k, 1, idx, mask, scores,
+                              workspace=vxl.alloc_workspace(vxl.workspace_bytes(vxl.OP_SCORE_MASS, layout, desc, batch=1, n_q_tokens=1)))
+    want = torch.zeros(c, dtype=torch.float64, device="cuda")
+    for g in range(0, h, 216):
+        logits = (k[g:g + 216].float() * qd[0, 0, g:g + 216, None].float()).sum(-1).double() / d ** 0.5
+        want += torch.softmax(logits, -1).sum(0) / h
+    assert (scores[0].double() - want).abs().max().item() <= RTOL * want.max().item()
