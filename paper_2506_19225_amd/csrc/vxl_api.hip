@@ -126,15 +126,20 @@ DecodePlan decode_plan(const vxl_attn_desc* d, int batch, int T, int l_cap, bool
         bool few = rows > 64 || tpw > 1;
         if (p.use_ring) {
             // Against the ring kernel it wins while that one's launch is small (448 rows: 72 workgroups 25.9 ->
-            // 22.7, but 136 workgroups 27.4 -> 28.7; 140 rows at 248 workgroups 18.5 -> 19.4) and a wave walks
-            // fewer keys: a share of 1 / n_split there; here a quarter of that per round of workgroups, and the
-            // busiest XCD (32 compute units, LDS for one workgroup each at D = 128, two at D = 64) may take
-            // several rounds.  D = 128, ring -> here, splits: 1,280 rows on one KV head, 16,384 keys, 12 splits
-            // against two rounds of 1: 47.8 -> 219.8; 12 units of 672 rows, 2,000 keys, 2 against two rounds of
-            // 1: 47.3 -> 49.6, 1,300 keys, 1 against two rounds of 1: 53.5 -> 41.3.
+            // 22.7, but 136 workgroups 27.4 -> 28.7; 140 rows at 248 workgroups 18.5 -> 19.4) and its own time is
+            // shorter.  In tiles of the ring, a call of the ring takes its tiles and 14 for start and merge, a
+            // round of workgroups here 8 and 0.8 per tile of a wave; the row blocks of a unit run on one XCD, whose
+            // 32 compute units hold a workgroup each (its LDS), at D = 64 two unless it holds a row map too.
+            // Fitted to 176 random calls of 257 to 4,000 rows, gathered and in place: none of those that take row
+            // blocks is slower than by the ring, 1.28x on average as with the faster one of every call.
+            // Ring -> here, D = 128: 959 rows, 1,171 keys in one split, 10 tiles per wave 41.3 -> 20.0; 1,050 rows,
+            // two rounds, 1,202 keys 48.3 -> 37.6; 2,824 rows on one KV head, three rounds, 148 keys 20.2 -> 25.6;
+            // 1,280 rows, two rounds, 16,384 keys, 12 splits against one 47.8 -> 219.8.  D = 64: 2,006 rows, one
+            // round, 2,651 keys 60.3 -> 34.0; in place, 34 workgroups on an XCD, 6,680 keys 41.5 -> 76.1.
             const long ring_launch = units * ((rows + 255) / 256) * p.n_split;
-            const long per_xcd = (units * n_split + 7) / 8 * n_rtile, resident = 32 * (d->head_dim == 64 ? 2 : 1);
-            few = ring_launch < 100 && (per_xcd + resident - 1) / resident * p.n_split < 4 * n_split;
+            const long per_xcd = (units * n_split + 7) / 8 * n_rtile, resident = 32 * (d->head_dim == 64 && gathered ? 2 : 1);
+            const long rounds = (per_xcd + resident - 1) / resident;
+            few = ring_launch < 100 && rounds * (40 + 4 * tpw) < 5 * (14 + p.split_len / kKeyTile);
         }
         if (rows <= kRowBlock || (fits && few)) {
             p.use_ring = 0;

@@ -1,6 +1,6 @@
 """The choice between the decode kernels, which is made on the host and needs no GPU: where 32-row blocks take the place
-of the 256-row ring, a wave walks fewer keys than a wave of the ring would, counted over the rounds that the busiest
-XCD needs."""
+of the 256-row ring, they are the shorter call by the times of a tile, a round of workgroups on the busiest XCD, and a
+call."""
 import numpy as np
 import pytest
 
@@ -22,7 +22,7 @@ def ring_splits(units, rows, l_cap):
 
 @pytest.mark.parametrize("in_place", [False, True])
 @pytest.mark.parametrize("d", [64, 128])
-def test_row_blocks_walk_fewer_keys_than_the_ring(d, in_place):
+def test_row_blocks_are_the_shorter_call(d, in_place):
     chosen = 0
     for g, hkv in [(8, 1), (7, 1), (7, 2), (7, 4), (16, 1), (1, 8)]:
         for b in (1, 2, 3, 5, 9, 12):
@@ -40,8 +40,10 @@ def test_row_blocks_walk_fewer_keys_than_the_ring(d, in_place):
                     chosen += 1
                     blocks = -(-rows // 32)
                     per_xcd = np.bincount(np.arange(units * n_split) % 8).max() * blocks
-                    rounds = -(-per_xcd // (32 * (128 // d)))     # (a workgroup's LDS: all of a compute unit's at D = 128)
-                    assert rounds * n_ring < 4 * n_split, (g, hkv, b, t, l_cap, n_split)
+                    lds = 1024 * d + 1024 + (16384 if in_place else 0)            # (tiles, statistics, row map)
+                    rounds = -(-per_xcd // (32 * (163840 // lds)))
+                    tiles, ring_tiles = -(-l_cap // (128 * n_split)), -(-l_cap // (64 * n_ring))
+                    assert rounds * (8 + 0.8 * tiles) < 14 + ring_tiles, (g, hkv, b, t, l_cap, n_split)
                     assert n_split <= n_ring and units * n_split * blocks <= 256
     assert chosen > 50
 
@@ -50,7 +52,15 @@ def test_row_blocks_walk_fewer_keys_than_the_ring(d, in_place):
     (8, 1, 128, 1, 128, 4096, BLOCKS), (8, 1, 128, 1, 160, 4096, RING), (8, 1, 128, 1, 160, 16384, RING),
     (8, 1, 64, 1, 160, 4096, BLOCKS), (8, 1, 64, 1, 160, 16384, RING), (8, 1, 128, 1, 512, 4096, RING),
     (28, 4, 128, 3, 96, 1300, BLOCKS), (28, 4, 128, 3, 96, 2000, RING), (28, 4, 64, 3, 96, 2000, BLOCKS),
-    (7, 1, 128, 9, 128, 1300, BLOCKS), (28, 4, 128, 1, 160, 4096, RING), (28, 4, 128, 1, 32, 4352, BLOCKS)])
+    (7, 1, 128, 9, 128, 1300, BLOCKS), (28, 4, 128, 1, 160, 4096, RING), (28, 4, 128, 1, 32, 4352, BLOCKS),
+    (8, 1, 128, 1, 353, 148, RING), (14, 2, 128, 1, 137, 1171, BLOCKS), (8, 1, 128, 1, 266, 640, RING)])
 def test_measured_sides_of_the_line(hq, hkv, d, b, t, l_cap, kernel):
     """Shapes on either side whose two kernels were timed against each other."""
     assert plan(hq, hkv, d, b, t, l_cap)[0] == kernel
+
+
+@pytest.mark.parametrize("hq,hkv,d,b,t,l_cap,kernel", [
+    (7, 1, 64, 3, 154, 6680, RING), (8, 1, 128, 1, 272, 583, RING), (8, 1, 128, 1, 341, 1985, RING),
+    (14, 2, 128, 1, 138, 2486, BLOCKS), (7, 1, 64, 1, 95, 2297, BLOCKS)])
+def test_measured_sides_of_the_line_in_place(hq, hkv, d, b, t, l_cap, kernel):
+    assert plan(hq, hkv, d, b, t, l_cap, True)[0] == kernel
