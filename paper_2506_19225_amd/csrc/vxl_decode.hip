@@ -381,7 +381,7 @@ __global__ __launch_bounds__(512, 2) void decode_ring_kernel(
 constexpr int kStepTile = 32;       // keys per wave tile
 constexpr int kMaxStepTpw = 32;     // in-place form: tiles per wave whose row map fits the wave's LDS area
 
-template <int D, int NW, int NBUF, bool IND = false, bool ROWS = false>
+template <int D, int NW, int NBUF, bool IND = false, bool ROWS = false, int MF = 4>
 __global__ __launch_bounds__(64 * NW, 2) void decode_wave_kernel(
     const uint16_t* __restrict__ Qd, const uint16_t* __restrict__ Kmix, const uint16_t* __restrict__ Vmix,
     const int32_t* __restrict__ mix_len, float* __restrict__ part_o, float* __restrict__ part_lse, int T_q,
@@ -598,10 +598,12 @@ __global__ __launch_bounds__(64 * NW, 2) void decode_wave_kernel(
     }
 
     // ---- merge the waves (their tile buffers are free now): area [32 rows][D] floats per wave ----
-    // A chain of LDS round trips at the end of every call, so it moves 16 bytes per lane and step: piece c4
+    // A chain of LDS round trips at the end of every call, so it moves MF = 4 floats per lane and step: piece c4
     // of a row lies at c4 ^ row (mod the D / 4 pieces), which spreads the rows that a wave writes side by
-    // side over all banks (unswizzled they all start at the same one).
-    // Against one float per lane and step: one layer of a generated token over 18,176 keys (with the merge
+    // side over all banks (unswizzled they all start at the same one).  One float (MF = 1) where the rows have
+    // no more floats than the workgroup has threads: one step either way, and a quarter of the divisions (one
+    // row, 4 KV heads of D = 64, 652 keys 7.0 -> 6.8 us; chosen inside the kernel the other calls pay 0.2).
+    // Four floats against one: one layer of a generated token over 18,176 keys (with the merge
     // of the splits) 14.5 -> 13.7 us, a question of 224 rows on a 16k prompt, selection to decode, 33.5 -> 32.0.
     static_assert(32 * D * 4 <= 2 * TILE_ELEMS * 2, "merge area must fit a wave's tile pair");
     constexpr int PPR4 = D / 4;                                // 16-byte pieces per row
@@ -620,35 +622,36 @@ __global__ __launch_bounds__(64 * NW, 2) void decode_wave_kernel(
         if (hi == 0) stats[wave][l32] = make_float2(m_run, l_tot);
     }
     __syncthreads();
-    constexpr int WSTRIDE = NBUF * 2 * TILE_ELEMS / 8;         // 16-byte pieces between the waves' areas
-    const float4* red0 = (const float4*)lds;
-    for (int e = tid; e < n_rows * PPR4; e += 64 * NW) {
-        const int row = e / PPR4, c4 = e % PPR4, at = row * PPR4 + (c4 ^ (row & (PPR4 - 1)));
+    constexpr int WSTRIDE = NBUF * 2 * TILE_ELEMS / 2;         // floats between the waves' areas
+    const float* red0 = (const float*)lds;
+    typedef __attribute__((ext_vector_type(MF))) float Vec;
+    for (int e = tid; e < n_rows * (D / MF); e += 64 * NW) {
+        const int row = e / (D / MF), dd = e % (D / MF) * MF;
+        const int at = (row * PPR4 + ((dd >> 2) ^ (row & (PPR4 - 1)))) * 4 + (dd & 3);
         float2 st[NW];
-        float4 v[NW];
+        Vec v[NW];
         float M = -INFINITY;
 #pragma unroll
         for (int w = 0; w < NW; ++w) {
             st[w] = stats[w][row];
-            v[w] = red0[w * WSTRIDE + at];
+            v[w] = *(const Vec*)(red0 + w * WSTRIDE + at);
             M = fmaxf(M, st[w].x);
         }
-        float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
+        Vec acc = {};
         float L = 0.f;
 #pragma unroll
         for (int w = 0; w < NW; ++w) {
             const bool some = st[w].x != -INFINITY;
             const float f = some ? __builtin_amdgcn_exp2f((st[w].x - M) * c2) : 0.f;
             L = fmaf(f, st[w].y, L);
-            acc.x = fmaf(f, some ? v[w].x : 0.f, acc.x);
-            acc.y = fmaf(f, some ? v[w].y : 0.f, acc.y);
-            acc.z = fmaf(f, some ? v[w].z : 0.f, acc.z);
-            acc.w = fmaf(f, some ? v[w].w : 0.f, acc.w);
+#pragma unroll
+            for (int i = 0; i < MF; ++i) acc[i] = fmaf(f, some ? v[w][i] : 0.f, acc[i]);
         }
         const bool empty = M == -INFINITY;
-        *(float4*)(part_o + (part_base + row) * D + c4 * 4) =
-            empty ? make_float4(0.f, 0.f, 0.f, 0.f) : make_float4(acc.x / L, acc.y / L, acc.z / L, acc.w / L);
-        if (c4 == 0) part_lse[part_base + row] = empty ? -INFINITY : M * c2 + __builtin_amdgcn_logf(L);
+#pragma unroll
+        for (int i = 0; i < MF; ++i) acc[i] = empty ? 0.f : acc[i] / L;
+        *(Vec*)(part_o + (part_base + row) * D + dd) = acc;
+        if (dd == 0) part_lse[part_base + row] = empty ? -INFINITY : M * c2 + __builtin_amdgcn_logf(L);
     }
 }
 
@@ -847,6 +850,10 @@ static vxl_status run_decode_wave(const vxl_attn_desc* d, float scale, const voi
                                         hipFuncAttributeMaxDynamicSharedMemorySize, lds_bytes));
         VXL_HIP_TRY(hipFuncSetAttribute((const void*)decode_wave_kernel<D, 4, 2, true>,
                                         hipFuncAttributeMaxDynamicSharedMemorySize, lds_bytes));
+        VXL_HIP_TRY(hipFuncSetAttribute((const void*)decode_wave_kernel<D, 4, 2, false, false, 1>,
+                                        hipFuncAttributeMaxDynamicSharedMemorySize, lds_bytes));
+        VXL_HIP_TRY(hipFuncSetAttribute((const void*)decode_wave_kernel<D, 4, 2, true, false, 1>,
+                                        hipFuncAttributeMaxDynamicSharedMemorySize, lds_bytes));
         VXL_HIP_TRY(hipFuncSetAttribute((const void*)decode_wave_kernel<D, 4, 2, false, true>,
                                         hipFuncAttributeMaxDynamicSharedMemorySize, lds_bytes));
         VXL_HIP_TRY(hipFuncSetAttribute((const void*)decode_wave_kernel<D, 4, 2, true, true>,
@@ -862,9 +869,15 @@ static vxl_status run_decode_wave(const vxl_attn_desc* d, float scale, const voi
                        (const uint16_t*)Qd, (const uint16_t*)Kmix, (const uint16_t*)Vmix, mix_len, part_o, \
                        part_lse, T, d->n_q_heads, d->n_kv_heads, group, l_cap, tpw, p.n_split, units, n_rtile, \
                        scale, rm ? *rm : RowMap{})
-    if (rm) { if (n_rtile > 1) VXL_LAUNCH(4, 2, true, true); else VXL_LAUNCH(4, 2, true); }
+    const bool few = n_rows * D <= 64 * 4;                     // (see the merge of the waves)
+    if (rm) {
+        if (n_rtile > 1) VXL_LAUNCH(4, 2, true, true);
+        else if (few) VXL_LAUNCH(4, 2, true, false, 1);
+        else VXL_LAUNCH(4, 2, true);
+    }
     else if (p.step_waves == 8) VXL_LAUNCH(8, 1);
     else if (n_rtile > 1) VXL_LAUNCH(4, 2, false, true);
+    else if (few) VXL_LAUNCH(4, 2, false, false, 1);
     else VXL_LAUNCH(4, 2);
 #undef VXL_LAUNCH
     VXL_HIP_TRY(hipGetLastError());

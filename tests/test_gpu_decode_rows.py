@@ -28,6 +28,11 @@ pytestmark = pytest.mark.gpu
     (7, 1, 96, 128, [450, 1, 31, 32, 33, 64, 449, 0, 128]),       # nine units of 21 blocks
     (8, 1, 160, 128, [2600]),                      # 40 blocks: the ring kernel
     (8, 1, 160, 64, [1290]),                       # 40 blocks on one XCD, two per compute unit
+    (2, 2, 1, 128, [700, 1, 0, 33]),               # one row: fewer floats than threads to merge them
+    (2, 1, 1, 128, [300, 31]),                     # two rows: as many
+    (3, 1, 1, 128, [300, 31]),                     # three: more
+    (1, 1, 4, 64, [1100, 0, 65]),
+    (5, 1, 1, 64, [1100, 0, 65]),
 ])
 def test_row_blocks_match_the_oracle(hq, hkv, t, d, lens):
     rng = np.random.default_rng(81 + t)
@@ -56,10 +61,11 @@ def test_row_blocks_match_the_oracle(hq, hkv, t, d, lens):
 
 
 @pytest.mark.parametrize("mode", ["kept_in_place", "pooled"])
-@pytest.mark.parametrize("t,bsz,d", [(6, 3, 128), (11, 1, 64), (23, 2, 128)])
-def test_row_blocks_in_place(mode, t, bsz, d):
+@pytest.mark.parametrize("hq,t,bsz,d", [(14, 6, 3, 128), (14, 11, 1, 64), (14, 23, 2, 128), (2, 1, 2, 128), (2, 3, 2, 128),
+                                        (2, 4, 1, 64)])
+def test_row_blocks_in_place(mode, hq, t, bsz, d):
     rng = np.random.default_rng(83 + t)
-    w = wl.tiny_workload("bf16", 14, 2, d, T=t, B=bsz, k=3, seed=83, value_scale=0.5)
+    w = wl.tiny_workload("bf16", hq, 2, d, T=t, B=bsz, k=3, seed=83, value_scale=0.5)
     lay = wl.random_layout(rng, 9, 12, 1, 300)
     _, k, v = wl.make_qkv(w, lay, with_q=False)
     masks = (rng.random((bsz, 12)) < 0.4).astype(np.uint8)
