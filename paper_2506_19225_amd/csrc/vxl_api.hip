@@ -275,6 +275,7 @@ vxl_status vxl_layout_create_windowed(int32_t n_tokens, int32_t n_prefix, int32_
         const int b = (sg.q_len + kRowBlock - 1) / kRowBlock;
         L->row_blocks8 += b / 8;
         ++L->segs_mod8[b % 8];
+        L->seg_tiles += ((int64_t)sg.ctx_len + sg.back + sg.q_len) / kKeyTile + 1;
     }
     L->n_own_tiles = tile_base;
     L->l_ctx = n_prefix + s_total;

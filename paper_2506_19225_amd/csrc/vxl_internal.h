@@ -76,6 +76,7 @@ struct vxl_layout {
     int32_t n_work[2] = {0, 0};
     int64_t pair_count = 0;
     int64_t row_blocks8 = 0, segs_mod8[8] = {};      // of the segments' 32-row blocks: whole groups of eight, segments by the rest
+    int64_t seg_tiles = 0;                           // key tiles that the last row of a segment sees, over all segments
     // attention-mass score: item table and, per chunk, its range of items
     int32_t n_mass_items = 0;
     vxl::MassItem* d_mass_items = nullptr;   // [n_mass_items]

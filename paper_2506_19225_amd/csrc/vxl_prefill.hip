@@ -337,7 +337,8 @@ extern "C" void vxl_debug_prefill_events(void* start, void* stop) {
 
 template <int D, int NS, int NW = 8>
 static vxl_status run_prefill_dma(const vxl_layout* L, const vxl_attn_desc* d, float scale, const void* Q,
-                                  const void* K, const void* V, void* O, float* LSE, void* ws, hipStream_t s) {
+                                  const void* K, const void* V, void* O, float* LSE, void* ws, hipStream_t s,
+                                  bool spread = false) {
     using C = PrefillDmaCfg<D, NS, NW>;
     const TokStrides ts = tok_strides(d, L->n_tokens);
     // 32-bit byte offsets inside a segment's rows (longest segment plus its look-back)
@@ -374,7 +375,8 @@ static vxl_status run_prefill_dma(const vxl_layout* L, const vxl_attn_desc* d, f
     const int group = d->n_q_heads / d->n_kv_heads;
     const int xpg = 8 % d->n_kv_heads == 0 ? 8 / d->n_kv_heads : 0;
     constexpr int wl_i = NW == 8 ? 1 : 0;                     // the work list cut in bands of 32 * NW rows
-    constexpr int per_cu = std::min(8 / NW, 163840 / C::LDS_BYTES);   // workgroups per compute unit
+    // workgroups per compute unit (`spread`: one, so that two of them do not take parts where another has none)
+    const int per_cu = spread ? 1 : std::min(8 / NW, 163840 / C::LDS_BYTES);
     const long long n_pairs = (long long)L->n_work[wl_i] * d->n_q_heads;
     // no more workgroups than pairs (rounded up to whole rounds over the 8 XCDs when queues are per XCD group)
     const unsigned n_blocks = (unsigned)std::min<long long>((long long)per_cu * (n_cus / 8 * 8),
@@ -431,15 +433,22 @@ vxl_status launch_prefill_bf16(const vxl_layout* L, const vxl_attn_desc* d, floa
     // (chunks of two cells make as many parts either way).  At D = 64 two such workgroups fit a compute
     // unit and share it as well as one of eight waves does once that form needs a second round (896 parts
     // 51.5 -> 47.7 us, 512 parts 52.9 -> 48.5; 1,792 and 2,048 parts 1 % and 3 % slower), but not where it
-    // gets by with one (452 parts, 226 of eight waves: 25.7 -> 28.7).
+    // gets by with one (452 parts, 226 of eight waves: 25.7 -> 28.7) or walks fewer than some six tiles per
+    // segment (880 parts of 3 tiles 27.8 -> 32.6, 832 parts of 7 tiles 40.2 -> 36.7).  Where the parts take most
+    // compute units but walk few tiles, segments of four and more cells stay with eight waves, which read the
+    // keys half as often (D = 128, five chunks of 192 tokens: 120 parts 18.5, 220 parts of four waves 20.8; D =
+    // 64, nine chunks of 170: 13.3 and 14.9; but chunks of 92, 240 parts: 20.8 -> 19.0).
     if (g_prefill_variant == 0) {
         int n_cus = 0;
         const vxl_status st = device_cu_count(&n_cus);
         if (st != VXL_OK) return st;
         const long long parts4 = part_count(L, d, 4), parts8 = part_count(L, d, 8);
-        if ((parts4 <= n_cus && parts4 > parts8) || (d->head_dim == 64 && parts8 > n_cus && parts4 <= 4ll * n_cus && parts4 > parts8))
+        const bool few_keys = parts4 * 16 > n_cus * 11ll && L->n_tokens > 96ll * L->n_seg && 4 * L->seg_tiles <= 21ll * L->n_seg;
+        const bool one_round = parts4 <= n_cus && !few_keys;
+        const bool shared = d->head_dim == 64 && parts8 > n_cus && parts4 <= 4ll * n_cus && L->seg_tiles > 6ll * L->n_seg;
+        if (parts4 > parts8 && (one_round || shared))
             return d->head_dim == 128 ? run_prefill_dma<128, 4, 4>(L, d, scale, Q, K, V, O, LSE, ws, s)
-                                      : run_prefill_dma<64, 4, 4>(L, d, scale, Q, K, V, O, LSE, ws, s);
+                                      : run_prefill_dma<64, 4, 4>(L, d, scale, Q, K, V, O, LSE, ws, s, one_round);
     }
     return d->head_dim == 128 ? run_prefill_dma<128, 4>(L, d, scale, Q, K, V, O, LSE, ws, s)
                               : run_prefill_dma<64, 4>(L, d, scale, Q, K, V, O, LSE, ws, s);

@@ -25,6 +25,8 @@ pytestmark = pytest.mark.gpu
     (4, 4, 64, 17, [200] * 5 + [64], 64),          # one head per KV head
     (14, 2, 64, 0, [97, 400], 0),
     (14, 2, 64, 30, [256] * 19, 0),                # two 4-wave workgroups per compute unit
+    (8, 8, 64, 17, [97, 63, 200], 0),              # at most one, though two would fit
+    (28, 4, 128, 0, [192] * 5, 0),                 # few keys for 220 parts: eight waves
 ])
 def test_small_prompts_match_the_oracle(variant, hq, hkv, d, prefix, lens, window):
     rng = np.random.default_rng(91 + sum(lens))
