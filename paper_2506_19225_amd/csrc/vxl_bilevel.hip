@@ -564,12 +564,13 @@ vxl_status launch_gather(const vxl_layout* L, const vxl_attn_desc* d, const void
                          void* Vmix, int l_cap, int32_t* mix_len, int32_t* src_idx, hipStream_t s) {
     const int row_bytes = d->head_dim * (d->dtype == VXL_BF16 ? 2 : 4);
     const size_t smem = (size_t)(L->n_chunks + 1) * sizeof(int);
-    // Four heads together where there are four and the mixed buffers do not fit the on-package cache (256 MB).
-    // One head after the other -> together, us: bf16, D = 128, 520 MB 183 -> 165 and 635 MB 231 -> 197; D = 64,
-    // 247 MB 105 -> 91; fp32, D = 128, 328 MB 129 -> 114, 1,266 MB 437 -> 441.  Below the line 42.0 -> 43.7
-    // (120 MB) and 68 -> 72 (238 MB), but also 66 -> 60 (153 MB).  Other head counts in groups of four lose up to
-    // 18 %: eight heads, D = 128, 987 MB 347 -> 377; sixteen, D = 64, 1,958 MB 602 -> 725.
-    const bool four = Kmix && d->n_kv_heads == 4 && 8ll * batch * l_cap * row_bytes > (256ll << 20);
+    // Exactly four heads go together: one head after the other waits for its own loads four times, which small calls
+    // spend most of their time on, and it keeps fewer bytes in flight.  Over 96 sizes of one to eight queries with
+    // buffers in turn 1.05x, with the same buffers every time 1.01x.  One head after the other -> together, us:
+    // D = 128, bf16, one query of 4,128 rows 10.1 -> 8.1, of 2,368 rows 7.2 -> 5.9; eight of 6,912 rows 51.6 -> 45.1;
+    // at worst (20 to 50 MB of mixed rows in HBM) 13.4 -> 13.8 and, D = 64, 12.9 -> 13.7.  Other head counts in
+    // groups of four lose up to 18 %: eight heads, D = 128, 987 MB 347 -> 377; sixteen, D = 64, 1,958 MB 602 -> 725.
+    const bool four = Kmix && d->n_kv_heads == 4;
     const TokStrides ts = tok_strides(d, L->n_tokens);
     const long long epc = d->dtype == VXL_BF16 ? 8 : 4;
 #define VXL_LAUNCH(RB)                                                                             \

@@ -159,9 +159,10 @@ def test_gather_head_counts(dtype, d, n_kv_heads):
 
 @pytest.mark.parametrize("pooled", [False, True])
 @pytest.mark.parametrize("dtype,d", [("f32", 128), ("bf16", 64), ("bf16", 128)])
-def test_gather_four_heads_into_large_buffers(dtype, d, pooled):
-    """Mixed buffers of more than 256 MB (capacity; the sets are small) with four KV heads, which takes the instance that
-    moves all heads together: its rows and lengths, and what lies behind them, as in small buffers, bit for bit."""
+def test_gather_four_heads_as_two_and_two(dtype, d, pooled):
+    """Four KV heads take the instance that moves all heads of a row together, two heads the one that moves them one
+    after the other: the same rows, lengths and untouched bytes behind them, bit for bit, also into buffers (by
+    capacity; the sets are small) beyond the on-package cache."""
     w = wl.tiny_workload(dtype, 4, 4, d, T=1, B=3, k=2, seed=94)
     lay = wl.random_layout(np.random.default_rng(94), 5, 300, 1, 61)
     _, k, v = wl.make_qkv(w, lay, with_q=False)
@@ -176,17 +177,22 @@ def test_gather_four_heads_into_large_buffers(dtype, d, pooled):
         vxl.pool_sparse_kv(gl, desc, dk, dv, *sparse)
     call = vxl.gather_bilevel_kv_pooled if pooled else vxl.gather_bilevel_kv
     got = []
-    for l_cap in (need, max(need, (256 << 20) // (8 * 3 * d * dk.element_size()) + 1)):
-        kmix = torch.full((3, 4, l_cap, d), 7.0, dtype=dk.dtype, device="cuda")
+    for heads, l_cap in ((slice(0, 4), need), (slice(0, 4), max(need, (256 << 20) // (8 * 3 * d * dk.element_size()) + 1)),
+                         (slice(0, 2), need), (slice(2, 4), need)):
+        hkv = heads.stop - heads.start
+        kmix = torch.full((3, hkv, l_cap, d), 7.0, dtype=dk.dtype, device="cuda")
         vmix = torch.full_like(kmix, 7.0)
         mix_len = torch.zeros((3,), dtype=torch.int32, device="cuda")
-        call(gl, desc, dk, dv, *sparse, dm, kmix, vmix, mix_len)
+        call(gl, vxl.make_desc(hkv, hkv, d, dtype), dk[heads], dv[heads], *(x[heads] for x in sparse), dm, kmix, vmix, mix_len)
         torch.cuda.synchronize()
         assert (kmix[:, :, need:] == 7.0).all() and (vmix[:, :, need:] == 7.0).all()
         got.append((mix_len, kmix[:, :, :need].clone(), vmix[:, :, :need].clone()))
+    (n2, k2, v2), (n3, k3, v3) = got[2:]
+    assert torch.equal(n2, n3)
+    got[2:] = [(n2, torch.cat([k2, k3], 1), torch.cat([v2, v3], 1))]
     assert got[0][0].tolist() == [5 + sum(int(b - a) if m else int(t - s) for m, a, b, s, t in zip(
         masks[q], lay.chunk_bounds, lay.chunk_bounds[1:], lay.sparse_offsets, lay.sparse_offsets[1:])) for q in range(3)]
-    assert all(torch.equal(x, y) for x, y in zip(*got))
+    assert all(torch.equal(x, y) for other in got[1:] for x, y in zip(got[0], other))
 
 
 def test_pooled_gather_without_sparse_rows_and_all_dense():
