@@ -225,7 +225,8 @@ def chunk_prefill(layout: Layout, desc: AttnDesc, q, k, v, out, lse=None, worksp
 def chunk_score_topk(layout: Layout, desc: AttnDesc, qd, k, top_k: int, topk_idx, dense_mask,
                      scores=None, kbar=None, kbar_ready: bool = False, workspace=None, stream=None):
     """vxl_chunk_score_topk: qd [B,T,Hq,D]; topk_idx int32 [B,min(k,C)]; dense_mask uint8 [B,C]."""
-    b, t = int(qd.shape[0]), int(qd.shape[1])
+    shape = qd.shape                                         # (torch builds it anew each time it is asked for)
+    b, t = shape[0], shape[1]
     st = lib().vxl_chunk_score_topk(layout.handle, C.byref(desc), _ptr(qd), b, t, _ptr(k), int(top_k),
                                     _ptr(kbar), int(bool(kbar_ready)), _ptr(topk_idx), _ptr(dense_mask),
                                     _ptr(scores), _ptr(workspace),
@@ -236,7 +237,8 @@ def chunk_score_topk(layout: Layout, desc: AttnDesc, qd, k, top_k: int, topk_idx
 def chunk_score_topk_mass(layout: Layout, desc: AttnDesc, qd, k, top_k: int, topk_idx, dense_mask,
                           scores=None, workspace=None, stream=None):
     """vxl_chunk_score_topk_mass: arguments as chunk_score_topk, softmax attention-mass score."""
-    b, t = int(qd.shape[0]), int(qd.shape[1])
+    shape = qd.shape
+    b, t = shape[0], shape[1]
     st = lib().vxl_chunk_score_topk_mass(layout.handle, C.byref(desc), _ptr(qd), b, t, _ptr(k), int(top_k),
                                          _ptr(topk_idx), _ptr(dense_mask), _ptr(scores), _ptr(workspace),
                                          workspace.numel() if workspace is not None else 0, _stream(stream))
@@ -246,7 +248,8 @@ def chunk_score_topk_mass(layout: Layout, desc: AttnDesc, qd, k, top_k: int, top
 def gather_bilevel_kv(layout: Layout, desc: AttnDesc, k, v, dense_mask, kmix, vmix, mix_len,
                       src_idx=None, stream=None):
     """vxl_gather_bilevel_kv: kmix/vmix [B,Hkv,Lcap,D]; mix_len int32 [B]; src_idx int32 [B,Lcap]."""
-    b, l_cap = int(kmix.shape[0]), int(kmix.shape[2])
+    shape = kmix.shape
+    b, l_cap = shape[0], shape[2]
     st = lib().vxl_gather_bilevel_kv(layout.handle, C.byref(desc), _ptr(k), _ptr(v), _ptr(dense_mask), b,
                                      _ptr(kmix), _ptr(vmix), l_cap, _ptr(mix_len), _ptr(src_idx),
                                      _stream(stream))
@@ -263,7 +266,8 @@ def pool_sparse_kv(layout: Layout, desc: AttnDesc, k, v, ksp, vsp, stream=None):
 def gather_bilevel_kv_pooled(layout: Layout, desc: AttnDesc, k, v, ksp, vsp, dense_mask, kmix, vmix, mix_len,
                              src_idx=None, stream=None):
     """vxl_gather_bilevel_kv_pooled: as gather_bilevel_kv, sparse rows taken from ksp/vsp."""
-    b, l_cap = int(kmix.shape[0]), int(kmix.shape[2])
+    shape = kmix.shape
+    b, l_cap = shape[0], shape[2]
     st = lib().vxl_gather_bilevel_kv_pooled(layout.handle, C.byref(desc), _ptr(k), _ptr(v), _ptr(ksp), _ptr(vsp),
                                             _ptr(dense_mask), b, _ptr(kmix), _ptr(vmix), l_cap, _ptr(mix_len),
                                             _ptr(src_idx), _stream(stream))
@@ -272,8 +276,9 @@ def gather_bilevel_kv_pooled(layout: Layout, desc: AttnDesc, k, v, ksp, vsp, den
 
 def bilevel_decode(desc: AttnDesc, qd, kmix, vmix, mix_len, out, lse=None, workspace=None, stream=None):
     """vxl_bilevel_decode: qd/out [B,T,Hq,D]; kmix/vmix [B,Hkv,Lcap,D]; mix_len int32 [B]."""
-    b, t = int(qd.shape[0]), int(qd.shape[1])
-    l_cap = int(kmix.shape[2])
+    shape = qd.shape
+    b, t = shape[0], shape[1]
+    l_cap = kmix.shape[2]
     st = lib().vxl_bilevel_decode(C.byref(desc), _ptr(qd), b, t, _ptr(kmix), _ptr(vmix), l_cap,
                                   _ptr(mix_len), _ptr(out), _ptr(lse), _ptr(workspace),
                                   workspace.numel() if workspace is not None else 0, _stream(stream))
@@ -284,7 +289,8 @@ def bilevel_decode(desc: AttnDesc, qd, kmix, vmix, mix_len, out, lse=None, works
 def bilevel_decode_inplace(layout: Layout, desc: AttnDesc, qd, k, v, ksp, vsp, dense_mask, l_cap: int, out,
                            lse=None, mix_len=None, workspace=None, map_ready: bool = False, stream=None):
     """vxl_bilevel_decode_inplace: gather-free decode; ksp/vsp [Hkv,S_total,D] or None (kept rows in place)."""
-    b, t = int(qd.shape[0]), int(qd.shape[1])
+    shape = qd.shape
+    b, t = shape[0], shape[1]
     st = lib().vxl_bilevel_decode_inplace(layout.handle, C.byref(desc), _ptr(qd), b, t, _ptr(k), _ptr(v), _ptr(ksp),
                                           _ptr(vsp), _ptr(dense_mask), int(l_cap), int(bool(map_ready)), _ptr(out), _ptr(lse),
                                           _ptr(mix_len), _ptr(workspace),
@@ -298,8 +304,9 @@ STATIC_SCRATCH_BYTES = 32 << 20
 
 def bilevel_decode_static(desc: AttnDesc, qd, kmix, vmix, mix_len, out, lse=None, stream=None):
     """vxl_bilevel_decode_static: vxl_bilevel_decode without a workspace (the library's static scratch)."""
-    b, t = int(qd.shape[0]), int(qd.shape[1])
-    l_cap = int(kmix.shape[2])
+    shape = qd.shape
+    b, t = shape[0], shape[1]
+    l_cap = kmix.shape[2]
     st = lib().vxl_bilevel_decode_static(C.byref(desc), _ptr(qd), b, t, _ptr(kmix), _ptr(vmix), l_cap,
                                          _ptr(mix_len), _ptr(out), _ptr(lse), _stream(stream))
     _check(st, "vxl_bilevel_decode_static")
@@ -336,7 +343,8 @@ class KvStore:
     def reload(self, dense_mask_host: np.ndarray, kmix, vmix, mix_len=None, stream=None) -> np.ndarray:
         """dense_mask_host: numpy uint8 [B, C]; returns the mixed lengths (numpy int32 [B])."""
         m = np.ascontiguousarray(dense_mask_host, dtype=np.uint8)
-        b, l_cap = int(kmix.shape[0]), int(kmix.shape[2])
+        shape = kmix.shape
+        b, l_cap = shape[0], shape[2]
         assert m.shape == (b, self.n_chunks)
         lens = np.zeros((b,), dtype=np.int32)
         st = lib().vxl_kv_store_reload(self.handle, m.ctypes.data if m.size else None, b, _ptr(kmix), _ptr(vmix),
