@@ -662,96 +662,134 @@ __device__ __forceinline__ uint16_t f32_to_bf16(float v) {
     return (uint16_t)(b >> 16);
 }
 
-// One workgroup per query row.  Weights w_s = exp2(lse_s - max) go to LDS; the thread grid
-// (split group sg, float4 column) accumulates the splits s = sg, sg + SG, ... in that order and
-// the SG partial sums are added in group order; the weights are summed per wave by butterfly and
-// then over the four waves: fixed summation trees, so a call gives the same bits every time.
-// The first PRE partial rows of every thread are requested together with the LSEs, before the
-// weights exist, so the kernel waits for memory once rather than twice (its duration is
-// latency, not volume); rows of splits with weight 0 are loaded but never used.
-template <int D>
+// The fixed-order merge of the key splits.  WPR waves per query row (4, one workgroup per row, or 1, four rows
+// per workgroup): a thread takes four columns of every SG-th split, at most PRE of them requested together
+// with their LSEs before the first weight exists, and folds them relative to the largest LSE it has seen; the
+// SUB split groups of a wave are folded by lane exchange, the waves of a row through LDS, in an order that
+// depends on the split index alone: a call gives the same bits every time.  Rows of splits with weight 0 are
+// loaded but never used.
+// Bound by latency, not volume: with the weights in LDS and three barriers in a chain, one workgroup per row, a
+// call of 7 rows x 4 heads over 161 keys took 7.3 us, over 4,000 keys 8.7, of 448 rows x 8 over 512 keys 17.7;
+// so 6.6, 8.3 and 13.4.
+template <int D, int WPR, int PRE>
 __global__ __launch_bounds__(256) void decode_merge_kernel(const float* __restrict__ part_o,
                                                            const float* __restrict__ part_lse,
                                                            uint16_t* __restrict__ O, float* __restrict__ LSE,
                                                            int T_q, int n_q_heads, int n_kv_heads, int group,
                                                            int n_split) {
-    constexpr int NV = D / 4;                       // float4 columns per row
-    constexpr int SG = 256 / NV;                    // split groups
-    constexpr int PRE = 8;                          // partial rows per thread requested up front
-    extern __shared__ float sm[];
-    float* w = sm;                                  // [n_split]
-    float* red = sm + ((n_split + 3) & ~3);         // [SG][D]
-    __shared__ float wave_max[4], wave_sum[4];
-    const int n_rows = group * T_q;
-    const int rho = blockIdx.x, g = blockIdx.y, b = blockIdx.z, tid = threadIdx.x;
+    constexpr int NV = D / 4;                       // lanes per row: a float4 each
+    constexpr int SUB = 64 / NV, SG = WPR * SUB;    // split groups of a wave, of a row
+    __shared__ __attribute__((aligned(16))) float red[WPR][D];
+    __shared__ float2 stat[WPR];
+    const int n_rows = group * T_q, lane = threadIdx.x & 63, dq = lane % NV;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int rho = blockIdx.x * (4 / WPR) + wave / WPR, g = blockIdx.y, b = blockIdx.z;
+    if (rho >= n_rows) return;                      // (whole waves; with WPR = 4 none)
     const size_t base = ((size_t)b * n_kv_heads + g) * n_split;
-    const int sg = tid / NV, dq = tid % NV;
+    const float* po = part_o + (base * n_rows + rho) * D + dq * 4;      // split s: s * n_rows rows further
+    const float* pl = part_lse + base * n_rows + rho;
+    const unsigned split_stride = (unsigned)n_rows * D;
+    const size_t out_row = ((size_t)b * T_q + rho / group) * n_q_heads + g * group + rho % group;
 
-    float4 pre[PRE];
-#pragma unroll
-    for (int i = 0; i < PRE; ++i) {
-        const int s = min(sg + i * SG, n_split - 1);          // clamped: always a row of this (b, g)
-        pre[i] = *(const float4*)(part_o + ((base + s) * n_rows + rho) * D + dq * 4);
-    }
-    float mx = -INFINITY;
-    for (int s = tid; s < n_split; s += 256) {
-        const float v = part_lse[(base + s) * n_rows + rho];
-        w[s] = v;
-        mx = fmaxf(mx, v);
-    }
-    for (int o = 32; o > 0; o >>= 1) mx = fmaxf(mx, __shfl_xor(mx, o));
-    if ((tid & 63) == 0) wave_max[tid >> 6] = mx;
-    __syncthreads();
-    mx = fmaxf(fmaxf(wave_max[0], wave_max[1]), fmaxf(wave_max[2], wave_max[3]));
-    float wpart = 0.f;                              // this thread's weights, then its wave's
-    for (int s = tid; s < n_split; s += 256) {
-        const float ws = w[s] == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(w[s] - mx);
-        w[s] = ws;
-        wpart += ws;
-    }
-    for (int o = 32; o > 0; o >>= 1) wpart += __shfl_xor(wpart, o);
-    if ((tid & 63) == 0) wave_sum[tid >> 6] = wpart;
-    __syncthreads();
-
+    // (a part without weight counts 0 whatever it holds; a sum that is not a number stays one)
+    auto part_weight = [](float m_part, float l_part, float m_all) __attribute__((always_inline)) {
+        return l_part == 0.f ? 0.f : __builtin_amdgcn_exp2f(m_part - m_all);
+    };
+    auto scaled = [](float w, float x) __attribute__((always_inline)) { return w == 0.f ? 0.f : w * x; };
+    float m = -INFINITY, l = 0.f;
     float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
+    for (int s0 = wave % WPR * SUB + lane / NV; s0 < n_split; s0 += PRE * SG) {
+        float4 v[PRE];
+        float e[PRE];
 #pragma unroll
-    for (int i = 0; i < PRE; ++i) {
-        const int s = sg + i * SG;
-        const float ws = s < n_split ? w[s] : 0.f;
-        if (ws != 0.f) {
-            acc.x = fmaf(ws, pre[i].x, acc.x);
-            acc.y = fmaf(ws, pre[i].y, acc.y);
-            acc.z = fmaf(ws, pre[i].z, acc.z);
-            acc.w = fmaf(ws, pre[i].w, acc.w);
+        for (int i = 0; i < PRE; ++i) e[i] = pl[(size_t)min(s0 + i * SG, n_split - 1) * n_rows];   // clamped: always a row of this (b, g)
+#pragma unroll
+        for (int i = 0; i < PRE; ++i) v[i] = *(const float4*)(po + (size_t)min(s0 + i * SG, n_split - 1) * split_stride);
+        __builtin_amdgcn_sched_barrier(0);
+        float m_new = m;
+#pragma unroll
+        for (int i = 0; i < PRE; ++i) {
+            if (s0 + i * SG >= n_split) e[i] = -INFINITY;
+            m_new = fmaxf(m_new, e[i]);
+        }
+        const float f = part_weight(m, l, m_new);
+        l *= f;
+        acc.x = scaled(f, acc.x); acc.y = scaled(f, acc.y); acc.z = scaled(f, acc.z); acc.w = scaled(f, acc.w);
+        m = m_new;
+#pragma unroll
+        for (int i = 0; i < PRE; ++i) {
+            const float w = e[i] == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(e[i] - m);
+            l += w;
+            if (w != 0.f) {
+                acc.x = fmaf(w, v[i].x, acc.x);
+                acc.y = fmaf(w, v[i].y, acc.y);
+                acc.z = fmaf(w, v[i].z, acc.z);
+                acc.w = fmaf(w, v[i].w, acc.w);
+            }
         }
     }
-    for (int s = sg + PRE * SG; s < n_split; s += SG) {
-        const float ws = w[s];
-        if (ws != 0.f) {
-            const float4 v = *(const float4*)(part_o + ((base + s) * n_rows + rho) * D + dq * 4);
-            acc.x = fmaf(ws, v.x, acc.x);
-            acc.y = fmaf(ws, v.y, acc.y);
-            acc.z = fmaf(ws, v.z, acc.z);
-            acc.w = fmaf(ws, v.w, acc.w);
-        }
-    }
-    *(float4*)(red + sg * D + dq * 4) = acc;
-    __syncthreads();
-    if (tid < D) {
-        float a = 0.f;
 #pragma unroll
-        for (int i = 0; i < SG; ++i) a += red[i * D + tid];
-        const float wsum = (wave_sum[0] + wave_sum[1]) + (wave_sum[2] + wave_sum[3]);
-        const int t = rho / group, hg = rho % group;
-        const size_t row = ((size_t)b * T_q + t) * n_q_heads + g * group + hg;
-        // an empty mixed set (every split recorded weight 0): O = 0, LSE = -inf
-        const bool empty = !(wsum > 0.f);
-        O[row * D + tid] = empty ? (uint16_t)0 : f32_to_bf16(a / wsum);
-        if (LSE && tid == 0) LSE[row] = empty ? -INFINITY : (mx + __builtin_amdgcn_logf(wsum)) * kLn2;
+    for (int o = NV; o < 64; o <<= 1) {
+        const float m_o = __shfl_xor(m, o), l_o = __shfl_xor(l, o), M = fmaxf(m, m_o);
+        const float4 a_o = make_float4(__shfl_xor(acc.x, o), __shfl_xor(acc.y, o), __shfl_xor(acc.z, o), __shfl_xor(acc.w, o));
+        const float f = part_weight(m, l, M), f_o = part_weight(m_o, l_o, M);
+        l = l * f + l_o * f_o;
+        acc.x = scaled(f, acc.x) + scaled(f_o, a_o.x);
+        acc.y = scaled(f, acc.y) + scaled(f_o, a_o.y);
+        acc.z = scaled(f, acc.z) + scaled(f_o, a_o.z);
+        acc.w = scaled(f, acc.w) + scaled(f_o, a_o.w);
+        m = M;
+    }
+    // an empty mixed set (every split recorded weight 0): O = 0, LSE = -inf
+    if constexpr (WPR > 1) {                        // a column per thread: one division in the chain
+        if (lane < NV) *(float4*)(&red[wave][dq * 4]) = acc;
+        if (lane == 0) stat[wave] = make_float2(m, l);
+        __syncthreads();
+        if (threadIdx.x >= D) return;
+        float M = stat[0].x, a = 0.f;
+#pragma unroll
+        for (int w = 1; w < WPR; ++w) M = fmaxf(M, stat[w].x);
+        l = 0.f;
+#pragma unroll
+        for (int w = 0; w < WPR; ++w) {
+            const float f = part_weight(stat[w].x, stat[w].y, M);
+            l = fmaf(f, stat[w].y, l);
+            a += scaled(f, red[w][threadIdx.x]);
+        }
+        const bool empty = !(l > 0.f);
+        O[out_row * D + threadIdx.x] = empty ? (uint16_t)0 : f32_to_bf16(a / l);
+        if (LSE && threadIdx.x == 0) LSE[out_row] = empty ? -INFINITY : (M + __builtin_amdgcn_logf(l)) * kLn2;
+    } else if (lane < NV) {
+        const bool empty = !(l > 0.f);
+        const float a[4] = {acc.x, acc.y, acc.z, acc.w};
+        __attribute__((aligned(8))) uint16_t out[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) out[i] = empty ? (uint16_t)0 : f32_to_bf16(a[i] / l);
+        *(uint2*)(O + out_row * D + dq * 4) = *(const uint2*)out;
+        if (LSE && dq == 0) LSE[out_row] = empty ? -INFINITY : (m + __builtin_amdgcn_logf(l)) * kLn2;
     }
 }
 
 }  // namespace
+
+// The merge of a call: one wave per row while a thread's share of the splits is one batch of loads (8 splits: all
+// 84 sizes measured 0 to 14 % faster so than with four), and where the rows alone fill the chip (448 rows x 8 heads,
+// 16 splits 30.2 -> 28.4 us); otherwise four (28 rows of 16 and 31 splits: 8.4 -> 7.5 us and 9.4 -> 8.3).
+template <int D>
+static vxl_status launch_merge(const DecodePlan& p, const float* part_o, const float* part_lse, void* O, float* LSE, int T,
+                               const vxl_attn_desc* d, int batch, hipStream_t s) {
+    const int group = d->n_q_heads / d->n_kv_heads, n_rows = group * T;
+#define VXL_LAUNCH(WPR, PRE)                                                                                          \
+    hipLaunchKernelGGL((decode_merge_kernel<D, WPR, PRE>), dim3((n_rows * WPR + 3) / 4, d->n_kv_heads, batch), dim3(256), \
+                       0, s, part_o, part_lse, (uint16_t*)O, LSE, T, d->n_q_heads, d->n_kv_heads, group, p.n_split)
+    if (p.n_split <= 8) VXL_LAUNCH(1, 4);
+    else if ((long long)n_rows * d->n_kv_heads * batch >= 1024) VXL_LAUNCH(1, 8);
+    else if (p.n_split <= 32) VXL_LAUNCH(4, 4);
+    else VXL_LAUNCH(4, 8);
+#undef VXL_LAUNCH
+    VXL_HIP_TRY(hipGetLastError());
+    return VXL_OK;
+}
 
 template <int D, int QB>
 static vxl_status run_decode(const vxl_attn_desc* d, float scale, const void* Qd, int batch, int T,
@@ -784,11 +822,7 @@ static vxl_status run_decode(const vxl_attn_desc* d, float scale, const void* Qd
                            (const uint16_t*)Vmix, mix_len, part_o, part_lse, T, d->n_q_heads, d->n_kv_heads, group,
                            l_cap, n_rtile, p.split_len, scale, RowMap{});
     VXL_HIP_TRY(hipGetLastError());
-    const size_t merge_lds = (size_t)(((p.n_split + 3) & ~3) + 256 / (D / 4) * D) * sizeof(float);
-    hipLaunchKernelGGL((decode_merge_kernel<D>), dim3(n_rows, d->n_kv_heads, batch), dim3(256), merge_lds, s,
-                       part_o, part_lse, (uint16_t*)O, LSE, T, d->n_q_heads, d->n_kv_heads, group, p.n_split);
-    VXL_HIP_TRY(hipGetLastError());
-    return VXL_OK;
+    return launch_merge<D>(p, part_o, part_lse, O, LSE, T, d, batch, s);
 }
 
 template <int D>
@@ -822,11 +856,7 @@ static vxl_status run_decode_ring(const vxl_attn_desc* d, float scale, const voi
                            (const uint16_t*)Vmix, mix_len, part_o, part_lse, T, d->n_q_heads, d->n_kv_heads, group,
                            l_cap, n_rtile, p.split_len, scale, RowMap{});
     VXL_HIP_TRY(hipGetLastError());
-    const size_t merge_lds = (size_t)(((p.n_split + 3) & ~3) + 256 / (D / 4) * D) * sizeof(float);
-    hipLaunchKernelGGL((decode_merge_kernel<D>), dim3(n_rows, d->n_kv_heads, batch), dim3(256), merge_lds, s,
-                       part_o, part_lse, (uint16_t*)O, LSE, T, d->n_q_heads, d->n_kv_heads, group, p.n_split);
-    VXL_HIP_TRY(hipGetLastError());
-    return VXL_OK;
+    return launch_merge<D>(p, part_o, part_lse, O, LSE, T, d, batch, s);
 }
 
 template <int D>
@@ -881,11 +911,7 @@ static vxl_status run_decode_wave(const vxl_attn_desc* d, float scale, const voi
     else VXL_LAUNCH(4, 2);
 #undef VXL_LAUNCH
     VXL_HIP_TRY(hipGetLastError());
-    const size_t merge_lds = (size_t)(((p.n_split + 3) & ~3) + 256 / (D / 4) * D) * sizeof(float);
-    hipLaunchKernelGGL((decode_merge_kernel<D>), dim3(n_rows, d->n_kv_heads, batch), dim3(256), merge_lds, s,
-                       part_o, part_lse, (uint16_t*)O, LSE, T, d->n_q_heads, d->n_kv_heads, group, p.n_split);
-    VXL_HIP_TRY(hipGetLastError());
-    return VXL_OK;
+    return launch_merge<D>(p, part_o, part_lse, O, LSE, T, d, batch, s);
 }
 
 // Scratch of the entry point that allocates nothing: one array per device, held until the process

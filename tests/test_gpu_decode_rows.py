@@ -70,3 +70,23 @@ def test_row_blocks_in_place(mode, hq, t, bsz, d):
     _, k, v = wl.make_qkv(w, lay, with_q=False)
     masks = (rng.random((bsz, 12)) < 0.4).astype(np.uint8)
     check_case(w, lay, k, v, wl.make_decode_queries(w), masks, mode)
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("l_cap", [1, 129, 1024, 1025, 2048, 2049, 4096, 4097, 8192, 12289, 32768])
+def test_merge_of_every_number_of_splits(l_cap, d):
+    """One row per KV head, a key split per 128 keys: one to 256 partial rows (the edges of the merge's batches of
+    loads and of its choice of waves per row), some of them without keys."""
+    rng = np.random.default_rng(l_cap)
+    lens = [l_cap, max(1, l_cap // 3), 0] if l_cap < 20000 else [l_cap]
+    w = wl.tiny_workload("bf16", 2 if l_cap < 20000 else 1, 2 if l_cap < 20000 else 1, d, T=1, B=len(lens), k=1, seed=82)
+    shape = (len(lens), w.n_kv_heads, l_cap, d)
+    kmix, vmix = (wl.round_to_bf16(rng.standard_normal(shape).astype(np.float32)) for _ in range(2))
+    qd = wl.round_to_bf16(rng.standard_normal((len(lens), 1, w.n_q_heads, d)).astype(np.float32) * np.float32(0.5))
+    got, lse = gpu_decode(w, qd, vxl.to_device(kmix, "bf16"), vxl.to_device(vmix, "bf16"),
+                          torch.tensor(lens, dtype=torch.int32, device="cuda"), want_lse=True)
+    live = np.array(lens) > 0
+    want, wlse = oracle.decode_lse(qd[live], kmix[live], vmix[live], np.array(lens, np.int32)[live])
+    assert_close(got[live], want, "bf16", head_axis=2, what=f"{l_cap} keys, d={d}")
+    assert np.abs(lse[live] - wlse).max() < 2e-2
+    assert not got[~live].any() and np.isneginf(lse[~live]).all()
