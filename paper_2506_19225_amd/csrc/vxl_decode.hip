@@ -8,6 +8,8 @@
 // Each workgroup writes a normalised partial output and the base-2 log-sum-exp of its scaled
 // logits; the merge kernel combines the splits of a row with weights and a summation order
 // that depend only on the split index, so the result does not depend on scheduling.
+#include <algorithm>
+
 #include "vxl_internal.h"
 #include "vxl_mfma.h"
 
@@ -38,11 +40,24 @@ struct RowMap {
     int s_total;
 };
 
+// The keys of a split in the two kernels of larger row counts: whole 64-key tiles, dealt out evenly by the length
+// of the query's mixed set.  Cut by the capacity of its buffers, which variable chunk lengths leave partly empty,
+// the last splits of a query had no keys and the others more than their share: eight questions of 224 rows over
+// 25,500 of 35,410 rows (64 of 256 workgroups without keys), gather included, 285 -> 263 us.
+// (The step kernel below keeps the cut by capacity: its first request does not wait for the length, and dealing
+// its tiles out by workgroup or by wave in turn won 1 % on ragged sets and lost 1 to 4 % on full ones.)
+struct KeyRange { int lo, hi; };
+__device__ __forceinline__ KeyRange split_keys(int len, int split, int n_split) {
+    const int tiles = (len + kKeyTile - 1) / kKeyTile, per = tiles / n_split, more = tiles % n_split;
+    const int first = split * per + min(split, more);
+    return {first * kKeyTile, min((first + per + (split < more ? 1 : 0)) * kKeyTile, len)};
+}
+
 template <int D, int QB, bool IND = false>
 __global__ __launch_bounds__(256, (QB == 1 ? 2 : 1)) void decode_split_kernel(
     const uint16_t* __restrict__ Qd, const uint16_t* __restrict__ Kmix, const uint16_t* __restrict__ Vmix,
     const int32_t* __restrict__ mix_len, float* __restrict__ part_o, float* __restrict__ part_lse, int T_q,
-    int n_q_heads, int n_kv_heads, int group, int l_cap, int n_rtile, int split_len, float scale, RowMap rm) {
+    int n_q_heads, int n_kv_heads, int group, int l_cap, float scale, RowMap rm) {
     using C = DecodeCfg<D, QB>;
     extern __shared__ __attribute__((aligned(16))) uint16_t lds[];
     uint16_t* Ks = lds;
@@ -54,9 +69,8 @@ __global__ __launch_bounds__(256, (QB == 1 ? 2 : 1)) void decode_split_kernel(
     const int g = blockIdx.y % n_kv_heads, rt = blockIdx.y / n_kv_heads;
     const int b = blockIdx.z;
     const int n_rows = group * T_q;
-    const int len = min(max(mix_len[b], 0), l_cap);
-    const int k_lo = split * split_len;
-    const int k_hi = min(k_lo + split_len, len);
+    const KeyRange keys = split_keys(min(max(mix_len[b], 0), l_cap), split, n_split);
+    const int k_lo = keys.lo, k_hi = keys.hi;
     const int wrow0 = rt * C::RT + wave * 32 * QB;
     const size_t part_base = (((size_t)b * n_kv_heads + g) * n_split + split) * (size_t)n_rows;
 
@@ -201,7 +215,7 @@ template <int D, int NS, bool IND = false>
 __global__ __launch_bounds__(512, 2) void decode_ring_kernel(
     const uint16_t* __restrict__ Qd, const uint16_t* __restrict__ Kmix, const uint16_t* __restrict__ Vmix,
     const int32_t* __restrict__ mix_len, float* __restrict__ part_o, float* __restrict__ part_lse, int T_q,
-    int n_q_heads, int n_kv_heads, int group, int l_cap, int n_rtile, int split_len, float scale, RowMap rm) {
+    int n_q_heads, int n_kv_heads, int group, int l_cap, float scale, RowMap rm) {
     using C = DecodeRingCfg<D, NS>;
     extern __shared__ __attribute__((aligned(16))) uint16_t lds[];
     const uint32_t lds_base = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) void*)lds;
@@ -212,9 +226,8 @@ __global__ __launch_bounds__(512, 2) void decode_ring_kernel(
     const int g = blockIdx.y % n_kv_heads, rt = blockIdx.y / n_kv_heads;
     const int b = blockIdx.z;
     const int n_rows = group * T_q;
-    const int len = __builtin_amdgcn_readfirstlane(min(max(mix_len[b], 0), l_cap));
-    const int k_lo = split * split_len;
-    const int k_hi = min(k_lo + split_len, len);
+    const KeyRange keys = split_keys(__builtin_amdgcn_readfirstlane(min(max(mix_len[b], 0), l_cap)), split, n_split);
+    const int k_lo = __builtin_amdgcn_readfirstlane(keys.lo), k_hi = __builtin_amdgcn_readfirstlane(keys.hi);
     const int wrow0 = rt * C::RT + wave * 32;
     const size_t part_base = (((size_t)b * n_kv_heads + g) * n_split + split) * (size_t)n_rows;
 
@@ -776,15 +789,15 @@ __global__ __launch_bounds__(256) void decode_merge_kernel(const float* __restri
 // 84 sizes measured 0 to 14 % faster so than with four), and where the rows alone fill the chip (448 rows x 8 heads,
 // 16 splits 30.2 -> 28.4 us); otherwise four (28 rows of 16 and 31 splits: 8.4 -> 7.5 us and 9.4 -> 8.3).
 template <int D>
-static vxl_status launch_merge(const DecodePlan& p, const float* part_o, const float* part_lse, void* O, float* LSE, int T,
+static vxl_status launch_merge(int n_split, const float* part_o, const float* part_lse, void* O, float* LSE, int T,
                                const vxl_attn_desc* d, int batch, hipStream_t s) {
     const int group = d->n_q_heads / d->n_kv_heads, n_rows = group * T;
 #define VXL_LAUNCH(WPR, PRE)                                                                                          \
     hipLaunchKernelGGL((decode_merge_kernel<D, WPR, PRE>), dim3((n_rows * WPR + 3) / 4, d->n_kv_heads, batch), dim3(256), \
-                       0, s, part_o, part_lse, (uint16_t*)O, LSE, T, d->n_q_heads, d->n_kv_heads, group, p.n_split)
-    if (p.n_split <= 8) VXL_LAUNCH(1, 4);
+                       0, s, part_o, part_lse, (uint16_t*)O, LSE, T, d->n_q_heads, d->n_kv_heads, group, n_split)
+    if (n_split <= 8) VXL_LAUNCH(1, 4);
     else if ((long long)n_rows * d->n_kv_heads * batch >= 1024) VXL_LAUNCH(1, 8);
-    else if (p.n_split <= 32) VXL_LAUNCH(4, 4);
+    else if (n_split <= 32) VXL_LAUNCH(4, 4);
     else VXL_LAUNCH(4, 8);
 #undef VXL_LAUNCH
     VXL_HIP_TRY(hipGetLastError());
@@ -815,14 +828,14 @@ static vxl_status run_decode(const vxl_attn_desc* d, float scale, const void* Qd
         hipLaunchKernelGGL((decode_split_kernel<D, QB, true>), dim3(p.n_split, n_rtile * d->n_kv_heads, batch),
                            dim3(256), C::LDS_BYTES, s, (const uint16_t*)Qd, (const uint16_t*)Kmix,
                            (const uint16_t*)Vmix, mix_len, part_o, part_lse, T, d->n_q_heads, d->n_kv_heads, group,
-                           l_cap, n_rtile, p.split_len, scale, *rm);
+                           l_cap, scale, *rm);
     else
         hipLaunchKernelGGL((decode_split_kernel<D, QB, false>), dim3(p.n_split, n_rtile * d->n_kv_heads, batch),
                            dim3(256), C::LDS_BYTES, s, (const uint16_t*)Qd, (const uint16_t*)Kmix,
                            (const uint16_t*)Vmix, mix_len, part_o, part_lse, T, d->n_q_heads, d->n_kv_heads, group,
-                           l_cap, n_rtile, p.split_len, scale, RowMap{});
+                           l_cap, scale, RowMap{});
     VXL_HIP_TRY(hipGetLastError());
-    return launch_merge<D>(p, part_o, part_lse, O, LSE, T, d, batch, s);
+    return launch_merge<D>(p.n_split, part_o, part_lse, O, LSE, T, d, batch, s);
 }
 
 template <int D>
@@ -836,6 +849,14 @@ static vxl_status run_decode_ring(const vxl_attn_desc* d, float scale, const voi
     const int group = d->n_q_heads / d->n_kv_heads;
     const int n_rows = group * T;
     const int n_rtile = (n_rows + C::RT - 1) / C::RT;
+    // One workgroup per compute unit: of the planned splits, which give every unit at least one, as many as run in
+    // one round (gather included: 896 rows on six KV heads, 264 workgroups of 11 splits 118 us, 240 of 10 103; D =
+    // 64, 700 rows on four, 264 workgroups 85, 252 62).
+    int n_cus = 0;
+    const vxl_status cst = device_cu_count(&n_cus);
+    if (cst != VXL_OK) return cst;
+    const int per_split = n_rtile * d->n_kv_heads * batch;
+    const int n_split = std::max(1, std::min(p.n_split, n_cus / per_split));
     static PerDeviceOnce attr;
     const vxl_status ast = attr.run([] {
         VXL_HIP_TRY(hipFuncSetAttribute((const void*)decode_ring_kernel<D, 4, false>,
@@ -846,17 +867,17 @@ static vxl_status run_decode_ring(const vxl_attn_desc* d, float scale, const voi
     });
     if (ast != VXL_OK) return ast;
     if (rm)
-        hipLaunchKernelGGL((decode_ring_kernel<D, 4, true>), dim3(p.n_split, n_rtile * d->n_kv_heads, batch),
+        hipLaunchKernelGGL((decode_ring_kernel<D, 4, true>), dim3(n_split, n_rtile * d->n_kv_heads, batch),
                            dim3(512), C::LDS_BYTES, s, (const uint16_t*)Qd, (const uint16_t*)Kmix,
                            (const uint16_t*)Vmix, mix_len, part_o, part_lse, T, d->n_q_heads, d->n_kv_heads, group,
-                           l_cap, n_rtile, p.split_len, scale, *rm);
+                           l_cap, scale, *rm);
     else
-        hipLaunchKernelGGL((decode_ring_kernel<D, 4, false>), dim3(p.n_split, n_rtile * d->n_kv_heads, batch),
+        hipLaunchKernelGGL((decode_ring_kernel<D, 4, false>), dim3(n_split, n_rtile * d->n_kv_heads, batch),
                            dim3(512), C::LDS_BYTES, s, (const uint16_t*)Qd, (const uint16_t*)Kmix,
                            (const uint16_t*)Vmix, mix_len, part_o, part_lse, T, d->n_q_heads, d->n_kv_heads, group,
-                           l_cap, n_rtile, p.split_len, scale, RowMap{});
+                           l_cap, scale, RowMap{});
     VXL_HIP_TRY(hipGetLastError());
-    return launch_merge<D>(p, part_o, part_lse, O, LSE, T, d, batch, s);
+    return launch_merge<D>(n_split, part_o, part_lse, O, LSE, T, d, batch, s);
 }
 
 template <int D>
@@ -911,7 +932,7 @@ static vxl_status run_decode_wave(const vxl_attn_desc* d, float scale, const voi
     else VXL_LAUNCH(4, 2);
 #undef VXL_LAUNCH
     VXL_HIP_TRY(hipGetLastError());
-    return launch_merge<D>(p, part_o, part_lse, O, LSE, T, d, batch, s);
+    return launch_merge<D>(p.n_split, part_o, part_lse, O, LSE, T, d, batch, s);
 }
 
 // Scratch of the entry point that allocates nothing: one array per device, held until the process

@@ -90,3 +90,26 @@ def test_merge_of_every_number_of_splits(l_cap, d):
     assert_close(got[live], want, "bf16", head_axis=2, what=f"{l_cap} keys, d={d}")
     assert np.abs(lse[live] - wlse).max() < 2e-2
     assert not got[~live].any() and np.isneginf(lse[~live]).all()
+
+
+@pytest.mark.parametrize("t,d,lens,l_cap", [
+    (64, 128, [3000, 1, 63, 64, 65, 0], 3000),        # 448 rows, the ring: fewer tiles than splits, none, a ragged last one
+    (64, 64, [700, 2500, 129], 9000),                 # lengths far below the capacity
+    (100, 64, [15500, 4000], 15500),                  # 700 rows on four KV heads: more planned splits than one round holds
+    (16, 128, [700, 650, 64] * 11, 800),              # 112 rows on 66 KV heads: the 128-row kernel
+])
+def test_keys_dealt_out_by_length(t, d, lens, l_cap):
+    rng = np.random.default_rng(t + l_cap)
+    w = wl.tiny_workload("bf16", 14, 2, d, T=t, B=len(lens), k=1, seed=84)
+    kmix, vmix = (wl.round_to_bf16(rng.standard_normal((len(lens), 2, l_cap, d)).astype(np.float32)) for _ in range(2))
+    qd = wl.round_to_bf16(rng.standard_normal((len(lens), t, 14, d)).astype(np.float32) * np.float32(0.5))
+    dk, dv = vxl.to_device(kmix, "bf16"), vxl.to_device(vmix, "bf16")
+    for b, n in enumerate(lens):
+        dk[b, :, n:] = float("nan")
+        dv[b, :, n:] = float("nan")
+    got, lse = gpu_decode(w, qd, dk, dv, torch.tensor(lens, dtype=torch.int32, device="cuda"), want_lse=True)
+    live = np.array(lens) > 0
+    want, wlse = oracle.decode_lse(qd[live], kmix[live], vmix[live], np.array(lens, np.int32)[live])
+    assert_close(got[live], want, "bf16", head_axis=2, what=f"{7 * t} rows, d={d}")
+    assert np.abs(lse[live] - wlse).max() < 2e-2
+    assert not got[~live].any() and np.isneginf(lse[~live]).all()
