@@ -36,6 +36,7 @@ def _hipcc() -> str:
 # a compile in which one of them uses scratch memory.
 NO_SCRATCH = {"vxl_prefill.hip": ("prefill_dma_kernel",),
               "vxl_decode.hip": ("decode_ring_kernel", "decode_wave_kernel"),
+              "vxl_mass.hip": ("mass_partial_kernel",),
               "vxl_debug.hip": ("tile_loop_kernel",)}
 
 

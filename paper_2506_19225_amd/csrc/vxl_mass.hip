@@ -14,6 +14,7 @@
 #include <math.h>
 
 #include <algorithm>
+#include <type_traits>
 
 #include "vxl_internal.h"
 #include "vxl_mfma.h"
@@ -25,65 +26,74 @@ namespace {
 __device__ __forceinline__ float ldf(const float* p) { return *p; }
 __device__ __forceinline__ float ldf(const uint16_t* p) { return __uint_as_float((uint32_t)(*p) << 16); }
 
-// Register staging of one 64-key K tile by a 256-thread workgroup (D/32 16-byte pieces per thread).
-template <int D>
-struct KTileRegs {
-    static constexpr int LD = D / 32;
-    static constexpr int RPP = 256 / (D / 8);         // rows covered by one pass of the 256 threads
-    uint4 k0, k1, k2, k3;
-    // kb: wave-uniform byte pointer to row 0 of the tile; rows beyond rlim are clamped to it (the
-    // caller masks their scores).
-    __device__ __forceinline__ void fetch(const char* kb, int ld_r, int ld_part, int rlim, uint32_t row_bytes) {
-#define VXL_TILE_OFF(i_) ((uint32_t)min(ld_r + (i_) * RPP, rlim) * row_bytes + ld_part * 16)
-        k0 = *(const uint4*)(kb + VXL_TILE_OFF(0));
-        k1 = *(const uint4*)(kb + VXL_TILE_OFF(1));
-        if constexpr (LD > 2) {
-            k2 = *(const uint4*)(kb + VXL_TILE_OFF(2));
-            k3 = *(const uint4*)(kb + VXL_TILE_OFF(3));
-        }
-#undef VXL_TILE_OFF
-    }
-    __device__ __forceinline__ void stage(uint16_t* kt, int ld_r, int ld_part) const {
-        *(uint4*)(kt + k_tile_off<D>(ld_r, ld_part)) = k0;
-        *(uint4*)(kt + k_tile_off<D>(ld_r + RPP, ld_part)) = k1;
-        if constexpr (LD > 2) {
-            *(uint4*)(kt + k_tile_off<D>(ld_r + 2 * RPP, ld_part)) = k2;
-            *(uint4*)(kt + k_tile_off<D>(ld_r + 3 * RPP, ld_part)) = k3;
-        }
-    }
-};
-
-constexpr int kMassRowTile = 128;                     // stacked query rows per workgroup (4 waves x 32)
 constexpr float kMassGrow = 1073741824.f;             // 2^30: a lane's sum over a tile from which the reference is raised
+constexpr int kMassRowTile = 128;                     // stacked query rows per workgroup (4 waves x 32)
 
 // bf16, matrix cores: S^T = K.Q^T per 64-key tile, running (m, l) per query column.
 // Bound by the exponentials of a tile (a multiply-add, an exponential and an addition per logit,
 // as many issue slots as the matrix instructions take), once the keys come from L2: the row tiles
 // of one (item, KV head) are neighbours in the launch order of one XCD (workgroups go to the eight
-// XCDs in turn), so that HBM delivers a key once and not once per row tile.  The maximum of a tile
-// is formed only when the tile's sum says that the reference no longer fits (`kMassGrow`).
-// 448 rows x 4 heads over 131,328 keys: 87 us with the row tiles a whole pass apart and a maximum per
-// tile, 81 so.  The whole score and selection: 115 -> 92 us; 896 rows over 164,096 keys 305 -> 210.
-// A register-only loop of the same instructions at four waves per SIMD takes 43 us on this many tiles.
-template <int D>
-__global__ __launch_bounds__(256, 2) void mass_partial_kernel(
+// XCDs in turn), so that HBM delivers a key once and not once per row tile.  An item's reference is the
+// logit of its first key; a maximum is formed only when a tile's sum says that the reference no longer
+// fits (`kMassGrow`).  The tiles come by direct loads into two stages, the next one in flight while a tile
+// is worked on (through registers the compiler placed the loads behind the arithmetic), four waves per SIMD.
+// Where a launch has enough workgroups, CHAIN, one takes several short items in turn and loads its
+// queries once.  The whole score and selection, loads behind the arithmetic -> so, us: 448 rows x 4 heads
+// over 131,328 keys in 256 chunks 91.7 -> 79.6; 896 rows over 164,096 keys in 640 chunks 217 -> 171 (an item
+// per workgroup 186); 56 rows over 131,328 keys 42.9 -> 38.1; 7 rows over 164,096 keys 48.3 -> 45.6.
+// Two row blocks per wave (half the operand reads, three waves per SIMD): 79.9 and 182, and slower on
+// small calls; a third stage at three waves per SIMD 85 and 204.
+template <int D, bool CHAIN>
+__global__ __launch_bounds__(256, 4) void mass_partial_kernel(
     const uint16_t* __restrict__ Qd, const uint16_t* __restrict__ K, const MassItem* __restrict__ items,
     float* __restrict__ part_m, float* __restrict__ part_l, int T_q, int n_q_heads, int n_kv_heads, int group,
-    long long kv_head, long long kv_tok, int n_items, float scale) {   // K strides in elements
-    __shared__ __attribute__((aligned(16))) uint16_t Ks[2][kKeyTile * D];
+    long long kv_head, long long kv_tok, int n_items, int per_wg, float scale) {   // K strides in elements
+    constexpr int TILE = kKeyTile * D;                // elements of one unpadded K tile
+    constexpr int PPR = D / 8, RPI = 64 / PPR;        // 16-byte pieces per row, rows per load instruction (1 KiB)
+    constexpr int IPW = kKeyTile / RPI / 4;           // load instructions per wave and tile
+    __shared__ __attribute__((aligned(16))) uint16_t Ks[2][TILE];
+    const uint32_t lds_base = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) void*)&Ks[0][0];
     const int tid = threadIdx.x, lane = tid & 63, l32 = lane & 31, hi = lane >> 5;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    // workgroup id -> (unit = (item, KV head), row tile): id = (unit / 8 * n_rt + rt) * 8 + unit % 8
+    // workgroup id -> (unit = (items, KV head), row tile): id = (unit / 8 * n_rt + rt) * 8 + unit % 8
     const int n_rows = group * T_q, n_rt = (n_rows + kMassRowTile - 1) / kMassRowTile;
     const unsigned id = folded_id(), xcd = id % kXcds, seq = id / kXcds;
     const unsigned unit = seq / n_rt * kXcds + xcd;
-    if (unit >= (unsigned)n_items * n_kv_heads) return;
-    const int rt = seq % n_rt, item = unit / n_kv_heads, g = unit % n_kv_heads;
+    const int rt = seq % n_rt, g = unit % n_kv_heads;
+    int item = unit / n_kv_heads * per_wg;
+    if (item >= n_items) return;
+    const int item_end = CHAIN ? min(item + per_wg, n_items) : item + 1;
     const int b = blockIdx.z;
-    const int k_lo = items[item].key_lo, k_hi = items[item].key_hi;
     const int wrow0 = rt * kMassRowTile + wave * 32;
-    const bool wave_active = wrow0 < n_rows;          // waves without rows only help with the copies
+    const bool wave_active = wrow0 < n_rows;          // waves without rows only help with the loads
 
+    const char* kbase = (const char*)(K + (size_t)g * kv_head);
+    const uint32_t row_bytes = (uint32_t)kv_tok * 2;
+    const int r_in = lane / PPR, pp = lane % PPR;
+    uint32_t koff[IPW];                               // row and (swizzled) piece of this lane in a full tile
+#pragma unroll
+    for (int i = 0; i < IPW; ++i) {
+        const int row = (wave + i * 4) * RPI + r_in;
+        koff[i] = (uint32_t)row * row_bytes + (pp ^ ((row / (16 / PPR)) & (PPR - 1))) * 16;
+    }
+    // The tile of the keys [key0, key_end) -> stage; rows past the last key repeat it (their scores are masked).
+    auto issue = [&](int key0, int key_end, int stage) __attribute__((always_inline)) {
+        const int rlim = min(kKeyTile - 1, key_end - 1 - key0);
+        const char* kb = kbase + (size_t)key0 * row_bytes;
+        const uint32_t st = lds_base + (uint32_t)stage * (TILE * 2);
+        if (rlim == kKeyTile - 1) {
+#pragma unroll
+            for (int i = 0; i < IPW; ++i) dma16(kb, koff[i], st + (wave + i * 4) * 1024);
+        } else {
+#pragma unroll
+            for (int i = 0; i < IPW; ++i) {
+                const int row = (wave + i * 4) * RPI + r_in;
+                dma16(kb, koff[i] - (uint32_t)(row - min(row, rlim)) * row_bytes, st + (wave + i * 4) * 1024);
+            }
+        }
+    };
+    int k_lo = items[item].key_lo, k_hi = items[item].key_hi;
+    issue(k_lo, k_hi, 0);
     bf16x8 qreg[1][D / 16];
     {
         const int rho = min(wrow0 + l32, n_rows - 1);
@@ -91,29 +101,32 @@ __global__ __launch_bounds__(256, 2) void mass_partial_kernel(
         const uint4* src = (const uint4*)(Qd + (((size_t)b * T_q + t) * n_q_heads + g * group + hg) * D);
 #pragma unroll
         for (int ks = 0; ks < D / 16; ++ks) qreg[0][ks] = __builtin_bit_cast(bf16x8, src[ks * 2 + hi]);
-    }
-    float m_run = -INFINITY, l_run = 0.f;
-    const float c2 = scale * kLog2e;
-
-    const char* kbase = (const char*)(K + (size_t)g * kv_head);
-    const uint32_t row_bytes = (uint32_t)kv_tok * 2;
-    const int ld_r = tid / (D / 8), ld_part = tid % (D / 8);
-    KTileRegs<D> tr;
-    const int n_t = (k_hi - k_lo + kKeyTile - 1) / kKeyTile;
-    tr.fetch(kbase + (size_t)k_lo * row_bytes, ld_r, ld_part, min(kKeyTile - 1, k_hi - 1 - k_lo), row_bytes);
-    tr.stage(Ks[0], ld_r, ld_part);
-    __syncthreads();
-    for (int ti = 0; ti < n_t; ++ti) {
-        const int buf = ti & 1;
-        const int key0 = k_lo + ti * kKeyTile;
-        {   // next tile (the last iteration re-reads its own), in flight during the arithmetic
-            const int nk0 = k_lo + min(ti + 1, n_t - 1) * kKeyTile;
-            tr.fetch(kbase + (size_t)nk0 * row_bytes, ld_r, ld_part, min(kKeyTile - 1, k_hi - 1 - nk0), row_bytes);
-            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int ks = 0; ks < D / 16; ++ks) {             // complete here: no load the compiler knows of is in flight below
+            typedef __attribute__((ext_vector_type(4))) unsigned u32x4;
+            asm volatile("" :: "v"(__builtin_bit_cast(u32x4, qreg[0][ks])));
         }
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    float m_run = 0.f, l_run = 0.f;
+    const float c2 = scale * kLog2e;
+    int key0 = k_lo;                                  // first key of the tile at hand
+
+    // one tile; false behind the last tile of the last item
+    auto step = [&](auto stage) __attribute__((always_inline)) {
+        const bool item_ends = key0 + kKeyTile >= k_hi;
+        int nk_lo = 0, nk_hi = 0;
+        if (CHAIN && item_ends && item + 1 < item_end) {
+            nk_lo = items[item + 1].key_lo;
+            nk_hi = items[item + 1].key_hi;
+        }
+        wait_vmcnt<0>();                              // this wave's part of the tile has landed ...
+        __builtin_amdgcn_s_barrier();                 // ... and everyone's; the other stage is free
+        if (!item_ends) issue(key0 + kKeyTile, k_hi, stage ^ 1);
+        else if (CHAIN && item + 1 < item_end) issue(nk_lo, nk_hi, stage ^ 1);
         if (wave_active) {
             f32x16 s[1][2];
-            qk_tile<D, 1, D>(Ks[buf], qreg, l32, hi, s);
+            qk_tile_ahead<D, 1>(Ks[stage], qreg, l32, hi, s);
             if (key0 + kKeyTile > k_hi) {
                 const int lim = k_hi - key0 - 1;
 #pragma unroll
@@ -122,18 +135,25 @@ __global__ __launch_bounds__(256, 2) void mass_partial_kernel(
                     for (int r = 0; r < 16; ++r)
                         s[0][kb][r] = acc_key(kb, r, hi) <= lim ? s[0][kb][r] : -INFINITY;
             }
+            // the reference of an item is the logit of its first key, for both lanes of a row
+            if (key0 == k_lo) { m_run = __shfl(s[0][0][0], l32); l_run = 0.f; }
             auto exp_sum = [&](float mc) __attribute__((always_inline)) {
-                float sum[4] = {0.f, 0.f, 0.f, 0.f};
+                float sum[4];
 #pragma unroll
-                for (int kb = 0; kb < 2; ++kb)
+                for (int r = 0; r < 32; r += 8) {
+                    float e[8];
 #pragma unroll
-                    for (int r = 0; r < 16; ++r)
-                        sum[r & 3] += __builtin_amdgcn_exp2f(fmaf(s[0][kb][r], c2, -mc));
+                    for (int i = 0; i < 8; ++i) e[i] = fmaf(s[0][(r + i) >> 4][(r + i) & 15], c2, -mc);
+#pragma unroll
+                    for (int i = 0; i < 8; ++i) e[i] = __builtin_amdgcn_exp2f(e[i]);
+#pragma unroll
+                    for (int i = 0; i < 8; ++i) sum[i & 3] = r + i < 4 ? e[i] : sum[i & 3] + e[i];
+                }
                 return (sum[0] + sum[1]) + (sum[2] + sum[3]);
             };
-            // (the first tile, a sum that is too large or not a number: the whole wave takes the maximum,
-            // so the two lanes of a row keep the same reference)
-            float sum = ti == 0 ? INFINITY : exp_sum(m_run * c2);
+            // (a sum that is too large or not a number: the whole wave takes the maximum, so the two lanes of
+            // a row keep the same reference)
+            float sum = exp_sum(m_run * c2);
             if (__builtin_amdgcn_ballot_w64(!(sum <= kMassGrow)) != 0) {
                 float mx = s[0][0][0];
 #pragma unroll
@@ -142,23 +162,29 @@ __global__ __launch_bounds__(256, 2) void mass_partial_kernel(
                     for (int r = 0; r < 16; ++r) mx = fmaxf(mx, s[0][kb][r]);
                 mx = fmaxf(mx, __shfl_xor(mx, 32));   // every tile holds at least one valid key
                 const float m_new = fmaxf(m_run, mx);
-                l_run *= __builtin_amdgcn_exp2f((m_run - m_new) * c2);              // 0 on the first tile
+                l_run *= __builtin_amdgcn_exp2f((m_run - m_new) * c2);
                 m_run = m_new;
                 sum = exp_sum(m_run * c2);
             }
             l_run += sum;
+            if (item_ends) {
+                const int rho = wrow0 + l32;
+                const float l_tot = l_run + __shfl_xor(l_run, 32);
+                if (rho < n_rows && hi == 0) {
+                    const size_t idx = (((size_t)b * n_kv_heads + g) * n_items + item) * (size_t)n_rows + rho;
+                    part_m[idx] = m_run * c2;
+                    part_l[idx] = l_tot;
+                }
+            }
         }
-        tr.stage(Ks[buf ^ 1], ld_r, ld_part);
-        __syncthreads();
-    }
-    if (!wave_active) return;
-    const int rho = wrow0 + l32;
-    const float l_tot = l_run + __shfl_xor(l_run, 32);
-    if (rho < n_rows && hi == 0) {
-        const size_t idx = (((size_t)b * n_kv_heads + g) * n_items + item) * (size_t)n_rows + rho;
-        part_m[idx] = m_run * c2;
-        part_l[idx] = l_tot;
-    }
+        if (!item_ends) { key0 += kKeyTile; return true; }
+        if (!CHAIN) return false;
+        k_lo = key0 = nk_lo;
+        k_hi = nk_hi;
+        return ++item < item_end;
+    };
+    if constexpr (CHAIN) while (step(std::integral_constant<int, 0>{}) && step(std::integral_constant<int, 1>{})) {}
+    else for (int stage = 0; step(stage); stage ^= 1) {}
 }
 
 __device__ __forceinline__ float wave_max(float v) {
@@ -327,6 +353,13 @@ MassPlan mass_plan(const vxl_layout* L, const vxl_attn_desc* d, int batch, int T
     return p;
 }
 
+// Items that a workgroup takes one after the other: up to some 16 tiles of keys, while the launch keeps 2,048
+// workgroups (twice what the chip holds).
+static int mass_items_per_workgroup(const vxl_layout* L, long long workgroups) {
+    const long long tiles = std::max<long long>(1, (long long)L->n_tokens / kKeyTile / L->n_mass_items);
+    return (int)std::max<long long>(1, std::min((16 + tiles - 1) / tiles, workgroups / 2048));
+}
+
 vxl_status launch_score_mass(const vxl_layout* L, const vxl_attn_desc* d, float scale, const void* Qd,
                              int batch, int T, const void* K, float* scores, void* ws, bool force_simple,
                              hipStream_t s) {
@@ -341,12 +374,15 @@ vxl_status launch_score_mass(const vxl_layout* L, const vxl_attn_desc* d, float 
     const TokStrides ts = tok_strides(d, L->n_tokens);
     if (d->dtype == VXL_BF16 && !force_simple) {
         const int n_rt = (n_rows + kMassRowTile - 1) / kMassRowTile;
-        const dim3 grid = folded_grid(((long long)n_items * d->n_kv_heads + kXcds - 1) / kXcds * kXcds * n_rt, batch);
-#define VXL_LAUNCH(D)                                                                                   \
-    hipLaunchKernelGGL((mass_partial_kernel<D>), grid, dim3(256), 0, s, (const uint16_t*)Qd,            \
+        const int per_wg = mass_items_per_workgroup(L, (long long)n_items * d->n_kv_heads * n_rt * batch);
+        const long long units = (long long)((n_items + per_wg - 1) / per_wg) * d->n_kv_heads;
+        const dim3 grid = folded_grid((units + kXcds - 1) / kXcds * kXcds * n_rt, batch);
+#define VXL_LAUNCH(D, CHAIN)                                                                            \
+    hipLaunchKernelGGL((mass_partial_kernel<D, CHAIN>), grid, dim3(256), 0, s, (const uint16_t*)Qd,     \
                        (const uint16_t*)K, L->d_mass_items, part_m, part_l, T, d->n_q_heads,            \
-                       d->n_kv_heads, group, ts.kh, ts.kt, n_items, scale)
-        if (d->head_dim == 64) VXL_LAUNCH(64); else VXL_LAUNCH(128);
+                       d->n_kv_heads, group, ts.kh, ts.kt, n_items, per_wg, scale)
+        if (d->head_dim == 64) { if (per_wg > 1) VXL_LAUNCH(64, true); else VXL_LAUNCH(64, false); }
+        else { if (per_wg > 1) VXL_LAUNCH(128, true); else VXL_LAUNCH(128, false); }
 #undef VXL_LAUNCH
     } else {
         const dim3 grid(n_items, d->n_kv_heads, batch);

@@ -155,3 +155,17 @@ def test_mass_more_workgroups_than_a_grid_dimension_holds():
         logits = (k[g:g + 216].float() * qd[0, 0, g:g + 216, None].float()).sum(-1).double() / d ** 0.5
         want += torch.softmax(logits, -1).sum(0) / h
     assert (scores[0].double() - want).abs().max().item() <= RTOL * want.max().item()
+
+
+@pytest.mark.parametrize("hq,hkv,t,bsz,d", [(8, 8, 1, 4, 128), (8, 8, 1, 4, 64), (32, 4, 33, 3, 128), (32, 4, 33, 3, 64),
+                                            (8, 1, 3, 2, 128)])
+def test_mass_items_in_turn_and_first_keys_far_off(hq, hkv, t, bsz, d):
+    """Chunks of 1 to 130 keys, enough of them for a workgroup to take several in turn (the last case: too few), their
+    first keys, whose logits an item's sums start from, tens of units above and below the others'."""
+    rng = np.random.default_rng(77 + d)
+    w = wl.tiny_workload("bf16", hq, hkv, d, T=t, B=bsz, k=5, seed=77, value_scale=1.0)
+    lay = wl.random_layout(rng, 70, 140, 1, 130)
+    _, k, _ = wl.make_qkv(w, lay, with_q=False)
+    first = lay.chunk_bounds[:-1]
+    k[:, first] = wl.round_to_bf16(k[:, first] * rng.choice([-30.0, 1.0, 30.0], size=len(first)).astype(np.float32)[None, :, None])
+    check_mass(w, lay, wl.make_decode_queries(w), k, 5)
