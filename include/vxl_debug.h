@@ -22,10 +22,11 @@ extern "C" {
  * NULL).  An on-device cross-check of the matrix-core path. */
 void vxl_debug_force_simple(int on);
 
-/* Pre-filling instance: 0 = default (8 waves, 256-row bands, one workgroup per compute unit; for
- * small prompts 4 waves, 128-row bands); 1 = the same kernel template as two independent 4-wave
- * workgroups per compute unit (128-row bands, a 2-stage ring each); 2 = the 8-wave instance
- * whatever the size.  Any other value selects 0. */
+/* Pre-filling instance: 0 = the library chooses (8 waves, 256-row bands, one workgroup per compute
+ * unit, parts from a queue; for small prompts without pre-pass and queue, the smallest with 4 waves,
+ * 128-row bands); 1 = the same kernel template as two independent 4-wave workgroups per compute unit
+ * (128-row bands, a 2-stage ring each); 2 = the 8-wave instance of large prompts whatever the size;
+ * 3 = the same with the next part claimed late.  Any other value selects 0. */
 void vxl_debug_prefill_variant(int variant);
 
 /* Step-mode decode kernel form: 0 = the library chooses (4 double-buffered waves), 8 = eight

@@ -1,7 +1,7 @@
 // Chunk-based pre-filling attention on the gfx950 matrix cores (bf16 inputs, fp32 accumulate).
 //
-// Pre-pass (once per call): the K and V rows every later chunk may see -- the prefix rows
-// followed by the kept rows of all chunks in chunk order -- are compacted into two contiguous
+// Pre-pass (once per call; small prompts do without): the K and V rows every later chunk may see -- the
+// prefix rows followed by the kept rows of all chunks in chunk order -- are compacted into two contiguous
 // buffers, so the history of chunk c is simply their first P + sparse_offsets[c] rows.
 //
 // Main kernel (prefill_dma_kernel): a persistent workgroup takes bands of query rows of one
@@ -26,7 +26,7 @@ __device__ __forceinline__ uint4 zero4() { return make_uint4(0u, 0u, 0u, 0u); }
 
 // ------------------------------------------------------------------------------------------
 // Pre-pass: Kctx[g, r, :] = K[g, tile_src[r], :], same for V (zero rows where tile_src is -1).
-// Its first workgroup also zeroes the work-queue counters of the persistent main kernel (when
+// Its first workgroup also sets the work-queue counters of the persistent main kernel to `queue_start` (when
 // `queue` is given), which saves that kernel's callers a launch of their own.
 // ------------------------------------------------------------------------------------------
 template <int D>
@@ -34,9 +34,9 @@ __global__ __launch_bounds__(256) void compact_kv_kernel(const uint4* __restrict
                                                          const int32_t* __restrict__ tile_src,
                                                          uint4* __restrict__ Kctx, uint4* __restrict__ Vctx,
                                                          int n_rows_pad, long long kv_head_u4, long long kv_tok_u4,
-                                                         int* __restrict__ queue) {
+                                                         int* __restrict__ queue, int queue_start) {
     constexpr int LPR = D * 2 / 16, ROWS = 256 / LPR;
-    if (queue && blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x < 8) queue[threadIdx.x] = 0;
+    if (queue && blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x < 8) queue[threadIdx.x] = queue_start;
     const int r = blockIdx.x * ROWS + threadIdx.x / LPR, part = threadIdx.x % LPR, g = blockIdx.y;
     if (r >= n_rows_pad) return;
     const int src = tile_src[r];
@@ -74,21 +74,32 @@ struct PrefillDmaCfg {
     static constexpr int GROUP = 2 * IPW;                     // loads per wave per tile (K and V)
 };
 
-// The kernel is persistent: the grid is as many workgroups as the chip holds at once (one per compute
+// The kernel is persistent (except kDirect): the grid is as many workgroups as the chip holds at once (one per compute
 // unit; two of 4 waves where their rings fit its LDS), and every workgroup keeps taking the next (band
 // of query rows, part of its row-block x head grid) pair of its queue from a counter in global memory
 // until the queue is empty.  The work list is sorted heaviest first, so this is greedy longest-first
 // scheduling without gaps between workgroups.  With xpg > 0 there is one queue per KV head group,
 // served by the xpg XCDs (blockIdx.x % 8, the order workgroups are dealt out in) whose L2 then
-// holds that group's K and V; otherwise a single queue.  The counters must be zero at launch.
-template <int D, int NS, bool STRIDED, int NW = 8>
+// holds that group's K and V; otherwise a single queue.  The counters must be zero at launch (kLate: the
+// number of the queue's workgroups, whose first parts are their own numbers).
+// How a workgroup comes by its parts (the lines are at launch_prefill_bf16):
+//   kEarly   from the queue, the next part claimed as a part begins, which costs nothing: large prompts
+//   kLate    from the queue, the next part claimed shortly before a part ends: with a few parts per workgroup it
+//            goes to the one that is done first and not to the one that began first
+//   kDirect  one part by its number in the launch; no queue and no pre-pass: history rows are read where they are,
+//            prefix rows by their number and kept rows through the layout's table of source tokens, whose share of
+//            a part lies in LDS behind the ring
+enum { kEarly, kLate, kDirect };
+template <int D, int NS, bool STRIDED, int NW = 8, int TAKE = kEarly>
 __global__ __launch_bounds__(NW * 64, 2) void prefill_dma_kernel(
     const uint16_t* __restrict__ Q, const uint16_t* __restrict__ K, const uint16_t* __restrict__ V,
     const uint16_t* __restrict__ Kctx, const uint16_t* __restrict__ Vctx, uint16_t* __restrict__ O,
     float* __restrict__ LSE, const Segment* __restrict__ segs, const WorkItem* __restrict__ work,
     int n_tokens, int n_q_heads, int group, int ctx_rows_pad, float scale, int n_items, int xpg,
-    int* __restrict__ queue, long long q_head_arg, int q_tok_arg, long long kv_head_arg, int kv_tok_arg) {
+    int* __restrict__ queue, long long q_head_arg, int q_tok_arg, long long kv_head_arg, int kv_tok_arg,
+    const int32_t* __restrict__ hist_src, int n_prefix) {      // (DIRECT: source token of every history row)
     using C = PrefillDmaCfg<D, NS, NW>;
+    constexpr bool DIRECT = TAKE == kDirect, LATE = TAKE == kLate;
     // Element strides of Q/O and K/V rows: the arguments, or (STRIDED false, the dense head-major
     // layout) constants, so that the dense instance carries no stride arithmetic or registers.
     const long long q_head = STRIDED ? q_head_arg : (long long)n_tokens * D;
@@ -98,6 +109,7 @@ __global__ __launch_bounds__(NW * 64, 2) void prefill_dma_kernel(
     extern __shared__ __attribute__((aligned(16))) uint16_t lds[];
     const uint32_t lds_base = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) void*)lds;
     int* next_slot = (int*)(lds + NS * C::STAGE);
+    int* kept = next_slot + 4;                                // DIRECT: source tokens of the history rows behind the prefix
 
     const int tid = threadIdx.x, lane = tid & 63, l32 = lane & 31, hi = lane >> 5;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -122,9 +134,14 @@ __global__ __launch_bounds__(NW * 64, 2) void prefill_dma_kernel(
         voff_own[i] = STRIDED ? (uint32_t)row * (uint32_t)(kv_tok * 2) + vp * 16 : voff_ctx[i];
     }
 
-    if (tid == 0) next_slot[0] = atomicAdd(queue + qid, 1);
-    __syncthreads();
-    int j = __builtin_amdgcn_readfirstlane(next_slot[0]);
+    int j;
+    if constexpr (TAKE == kEarly) {
+        if (tid == 0) next_slot[0] = atomicAdd(queue + qid, 1);
+        __syncthreads();
+        j = __builtin_amdgcn_readfirstlane(next_slot[0]);
+    } else {
+        j = xpg > 0 ? (int)(blockIdx.x >> 3) * xpg + (int)(blockIdx.x & 7) % xpg : (int)blockIdx.x;
+    }
     // The descriptors of an item (two dependent scalar loads) are fetched while the item before it
     // runs, as soon as its index is known.
     auto item_of = [&](int jj) { return xpg > 0 ? jj / group : jj / n_q_heads; };
@@ -144,7 +161,8 @@ __global__ __launch_bounds__(NW * 64, 2) void prefill_dma_kernel(
     // Parts left without cells walk one tile and write nothing.
     const int part_id = xpg > 0 ? qid * group + j % group : j % n_q_heads;
     const int g = part_id / group;                            // KV head
-    const int part = part_id - g * group;
+    int part = part_id - g * group;
+    if (DIRECT) part = (part + item_of(j)) % group;           // (in turn over the XCDs: a part's place decides its length)
     const WorkItem wi = wi_next;
     const Segment sg = sg_next;
     const int m0 = wi.m_tile * C::BM;
@@ -154,6 +172,7 @@ __global__ __launch_bounds__(NW * 64, 2) void prefill_dma_kernel(
     const int h = g * group + (cell - rb * group);
     const bool idle = rb >= band_blocks;                      // (the grid of a ragged last band is smaller)
     const int wrow0 = m0 + rb * 32;
+    if (DIRECT && part * C::WAVES >= band_blocks * group) return;
     const int n_ctx_t = (sg.ctx_len + kKeyTile - 1) / kKeyTile;
     const int rb_last = min(band_blocks - 1, (part * C::WAVES + C::WAVES - 1) / group);
     const int last_row = min(m0 + (rb_last + 1) * 32, sg.q_len) - 1;
@@ -162,6 +181,8 @@ __global__ __launch_bounds__(NW * 64, 2) void prefill_dma_kernel(
 
     const char* kctx_g = (const char*)(Kctx + (size_t)g * ctx_rows_pad * D);
     const char* vctx_g = (const char*)(Vctx + (size_t)g * ctx_rows_pad * D);
+    const char* kall = (const char*)(K + (size_t)g * kv_head);        // (DIRECT) token 0
+    const char* vall = (const char*)(V + (size_t)g * kv_head);
     const char* kown = (const char*)(K + (size_t)g * kv_head + (size_t)(sg.q_start - sg.back) * kv_tok);
     const char* vown = (const char*)(V + (size_t)g * kv_head + (size_t)(sg.q_start - sg.back) * kv_tok);
 
@@ -170,11 +191,23 @@ __global__ __launch_bounds__(NW * 64, 2) void prefill_dma_kernel(
         const bool ctx = t < n_ctx_t;
         const int row0 = ctx ? t * kKeyTile : (t - n_ctx_t) * kKeyTile;
         const int rlim = ctx ? kKeyTile - 1 : min(kKeyTile - 1, sg.back + sg.q_len - 1 - row0);
-        const uint32_t row_bytes = ctx ? D * 2 : (uint32_t)kv_tok * 2;
-        const char* kb = (ctx ? kctx_g : kown) + (size_t)row0 * row_bytes;
-        const char* vb = (ctx ? vctx_g : vown) + (size_t)row0 * row_bytes;
+        const uint32_t row_bytes = ctx && !DIRECT ? D * 2 : (uint32_t)kv_tok * 2;
+        const char* kb = (ctx ? DIRECT ? kall : kctx_g : kown) + (size_t)row0 * row_bytes;
+        const char* vb = (ctx ? DIRECT ? vall : vctx_g : vown) + (size_t)row0 * row_bytes;
         const uint32_t st = lds_base + (uint32_t)(t % NS) * (C::STAGE * 2);
-        if (STRIDED && ctx) {
+        if (DIRECT && ctx && row0 + kKeyTile > n_prefix) {    // rows past the history's last repeat it (their scores are masked)
+#pragma unroll
+            for (int i = 0; i < C::IPW; ++i) {
+                const int slot = wave + i * C::WAVES, row = slot * C::RPI + r_in;
+                const int r = min(row0 + row, sg.ctx_len - 1);
+                const int src = r < n_prefix ? r : kept[r - n_prefix];
+                const uint32_t moved = (uint32_t)(src - row) * row_bytes;
+                dma16(kall, koff_own[i] + moved, st + slot * 1024);
+                dma16(vall, voff_own[i] + moved, st + C::TILE * 2 + slot * 1024);
+            }
+            return;
+        }
+        if (STRIDED && ctx && !DIRECT) {
 #pragma unroll
             for (int i = 0; i < C::IPW; ++i) {
                 const int slot = wave + i * C::WAVES;
@@ -213,8 +246,11 @@ __global__ __launch_bounds__(NW * 64, 2) void prefill_dma_kernel(
     // with the same bytes, which is harmless.
     constexpr int TPB = NS / 2;                               // tiles per workgroup barrier: 2, or 1 with a 2-stage ring
     static_assert(NS == 2 * TPB && (TPB == 1 || TPB == 2), "two groups of TPB stages");
+    // (DIRECT: a tile that needs the table is requested behind it)
+    auto needs_table = [&](int t) { return DIRECT && t < n_ctx_t && (t + 1) * kKeyTile > n_prefix; };
 #pragma unroll
-    for (int t = 0; t < TPB; ++t) issue(min(t, n_t - 1));
+    for (int t = 0; t < TPB; ++t)
+        if (!needs_table(min(t, n_t - 1))) issue(min(t, n_t - 1));
 
     // The query rows are loaded after the ring has been started (both latencies then overlap) and
     // forced complete here: the compiler's wait for them covers the older ring loads as well, and
@@ -227,8 +263,10 @@ __global__ __launch_bounds__(NW * 64, 2) void prefill_dma_kernel(
 #pragma unroll
         for (int ks = 0; ks < D / 16; ++ks)
             qreg[0][ks] = __builtin_bit_cast(bf16x8, *(const uint4*)(qbase + qoff + ks * 32));
+        if constexpr (DIRECT)
+            for (int i = tid; i < sg.ctx_len - n_prefix; i += C::WAVES * 64) kept[i] = hist_src[n_prefix + i];
         // the index of the item after this one is fetched in the same wait and read when this item is done
-        if (tid == 0) next_slot[par] = atomicAdd(queue + qid, 1);
+        if (TAKE == kEarly && tid == 0) next_slot[par] = atomicAdd(queue + qid, 1);
 #pragma unroll
         for (int ks = 0; ks < D / 16; ++ks) {
             typedef __attribute__((ext_vector_type(4))) unsigned u32x4;
@@ -236,6 +274,12 @@ __global__ __launch_bounds__(NW * 64, 2) void prefill_dma_kernel(
         }
     }
     __builtin_amdgcn_sched_barrier(0);
+    if constexpr (DIRECT) {
+        if (sg.ctx_len > n_prefix) __syncthreads();           // (the table; without kept rows nothing of it is read)
+#pragma unroll
+        for (int t = 0; t < TPB; ++t)
+            if (needs_table(min(t, n_t - 1))) issue(min(t, n_t - 1));
+    }
 
     auto process = [&](int ti) {
         const bool is_ctx = ti < n_ctx_t;
@@ -260,12 +304,15 @@ __global__ __launch_bounds__(NW * 64, 2) void prefill_dma_kernel(
             pv_tile_ahead<D, 2>(vt, pb, lane, o);
         }
     };
+    const int claim_t = max((n_t - 1) / TPB - 1, 0) * TPB;    // kLate: the meeting before the last one
     for (int t0 = 0; t0 < n_t; t0 += TPB) {
         // this wave's parts of tiles t0, t0+1 have landed -- and, at the item's first meeting, the
         // next item's index (an LDS store of wave 0, read by everybody right behind the barrier)
         wait_vmcnt0_lgkmcnt0();
         __builtin_amdgcn_s_barrier();                         // ... and everyone's; the other group is free
-        if (t0 == 0) {                                        // the next item's index was written before this barrier
+        int claimed = 0;
+        if (LATE && t0 == claim_t && tid == 0) claimed = atomicAdd(queue + qid, 1);
+        if (!DIRECT && t0 == (LATE ? claim_t + TPB : 0)) {    // the next item's index was written before this barrier
             const int jn = __builtin_amdgcn_readfirstlane(next_slot[par]);
             if (jn < q_len_items) {
                 wi_next = work[item_of(jn)];
@@ -274,6 +321,7 @@ __global__ __launch_bounds__(NW * 64, 2) void prefill_dma_kernel(
         }
         if (t0 + TPB < n_t) issue(t0 + TPB);                  // (all waits are vmcnt(0): nothing is issued past the last tile,
         process(t0);                                          //  so the item does not end waiting for loads nobody reads)
+        if (LATE && t0 == claim_t && tid == 0) next_slot[par] = claimed;
         if constexpr (TPB == 2) {
             if (t0 + TPB + 1 < n_t) issue(t0 + TPB + 1);      // the second refill between the two tiles
             if (t0 + 1 < n_t) process(t0 + 1);
@@ -301,15 +349,20 @@ __global__ __launch_bounds__(NW * 64, 2) void prefill_dma_kernel(
             if (LSE && hi == 0) (LSE + (size_t)h * n_tokens + sg.q_start)[q_off] = m_run * scale + logf(l_tot);
         }
     }
+    if constexpr (DIRECT) return;
     __syncthreads();                    // every wave is done with this item's tiles; next_slot[par] is written
     j = __builtin_amdgcn_readfirstlane(next_slot[par]);
+    if (LATE && n_t <= TPB && j < q_len_items) {                   // (an item of one meeting)
+        wi_next = work[item_of(j)];
+        sg_next = segs[wi_next.seg];
+    }
   }
 }
 
-// Zeroes the queue counters of the persistent kernel (a kernel, not a memset: the call may be
+// Sets the queue counters of the persistent kernel (a kernel, not a memset: the call may be
 // captured into a graph).
-__global__ void reset_queue_kernel(int* queue) {
-    if (threadIdx.x < 8) queue[threadIdx.x] = 0;
+__global__ void reset_queue_kernel(int* queue, int queue_start) {
+    if (threadIdx.x < 8) queue[threadIdx.x] = queue_start;
 }
 
 template <typename F>
@@ -325,8 +378,8 @@ static std::atomic<hipEvent_t> g_ev_start{nullptr}, g_ev_stop{nullptr};
 // Cross-check only (declared in vxl_debug.h): 0 = choose (8 waves, 256-row bands, one workgroup per
 // compute unit; for small prompts 4 waves, 128-row bands); 1 = the same kernel as two independent
 // 4-wave workgroups per compute unit (128-row bands, a 2-stage ring each, one meeting per tile); 2 = the
-// 8-wave instance whatever the size.
-extern "C" void vxl_debug_prefill_variant(int v) { g_prefill_variant = v == 1 || v == 2 ? v : 0; }
+// 8-wave instance with the pre-pass and early claims whatever the size; 3 = with late claims.
+extern "C" void vxl_debug_prefill_variant(int v) { g_prefill_variant = v >= 1 && v <= 3 ? v : 0; }
 // Measurement hook (declared in vxl_debug.h): when both events are set, every vxl_chunk_prefill
 // records them on its stream immediately before and after the main attention kernel (the pre-pass
 // is outside the bracket).
@@ -335,43 +388,28 @@ extern "C" void vxl_debug_prefill_events(void* start, void* stop) {
     g_ev_stop = (hipEvent_t)stop;
 }
 
-template <int D, int NS, int NW = 8>
+// 32-bit byte offsets inside a segment's rows (longest segment plus its look-back)
+static bool segments_fit_32_bits(const vxl_layout* L, const TokStrides& ts) {
+    long long max_rows = 0;
+    for (const Segment& sg : L->segs) max_rows = std::max<long long>(max_rows, (long long)sg.q_len + sg.back);
+    return max_rows * std::max(ts.qt, ts.kt) * 2 < (1ll << 32) && ts.qt < (1ll << 30) && ts.kt < (1ll << 30);
+}
+
+template <int D, int NS, int NW = 8, int TAKE = kEarly>
 static vxl_status run_prefill_dma(const vxl_layout* L, const vxl_attn_desc* d, float scale, const void* Q,
                                   const void* K, const void* V, void* O, float* LSE, void* ws, hipStream_t s,
                                   bool spread = false) {
     using C = PrefillDmaCfg<D, NS, NW>;
     const TokStrides ts = tok_strides(d, L->n_tokens);
-    // 32-bit byte offsets inside a segment's rows (longest segment plus its look-back)
-    long long max_rows = 0;
-    for (const Segment& sg : L->segs) max_rows = std::max<long long>(max_rows, (long long)sg.q_len + sg.back);
-    if (max_rows * std::max(ts.qt, ts.kt) * 2 >= (1ll << 32) || ts.qt >= (1ll << 30) || ts.kt >= (1ll << 30))
-        return VXL_ERR_UNSUPPORTED;
+    if (!segments_fit_32_bits(L, ts)) return VXL_ERR_UNSUPPORTED;
     const PrefillWorkspace w = prefill_workspace(L, d);
     uint16_t* kctx = (uint16_t*)((char*)ws + w.kctx);
     uint16_t* vctx = (uint16_t*)((char*)ws + w.vctx);
     int* queue = (int*)((char*)ws + w.queue);
     const int n_rows_pad = L->n_ctx_tiles * kKeyTile;
-    if (L->n_ctx_tiles > 0) {
-        constexpr int rows = 256 / (D * 2 / 16);
-        hipLaunchKernelGGL((compact_kv_kernel<D>), dim3((n_rows_pad + rows - 1) / rows, d->n_kv_heads),
-                           dim3(256), 0, s, (const uint4*)K, (const uint4*)V, L->d_tile_src, (uint4*)kctx,
-                           (uint4*)vctx, n_rows_pad, ts.kh / 8, ts.kt / 8, queue);
-    } else {
-        hipLaunchKernelGGL(reset_queue_kernel, dim3(1), dim3(64), 0, s, queue);
-    }
-    VXL_HIP_TRY(hipGetLastError());
-    static PerDeviceOnce attr;
-    vxl_status st = attr.run([] {
-        const vxl_status a = enable_big_lds(prefill_dma_kernel<D, NS, false, NW>, C::LDS_BYTES);
-        return a != VXL_OK ? a : enable_big_lds(prefill_dma_kernel<D, NS, true, NW>, C::LDS_BYTES);
-    });
-    if (st != VXL_OK) return st;
     int n_cus = 0;                                            // per_cu persistent workgroups on each
-    st = device_cu_count(&n_cus);
+    vxl_status st = device_cu_count(&n_cus);
     if (st != VXL_OK) return st;
-    hipEvent_t ev_start = g_ev_start, ev_stop = g_ev_stop;
-    const bool timed = ev_start && ev_stop;
-    if (timed) VXL_HIP_TRY(hipEventRecord(ev_start, s));
     const int group = d->n_q_heads / d->n_kv_heads;
     const int xpg = 8 % d->n_kv_heads == 0 ? 8 / d->n_kv_heads : 0;
     constexpr int wl_i = NW == 8 ? 1 : 0;                     // the work list cut in bands of 32 * NW rows
@@ -381,12 +419,67 @@ static vxl_status run_prefill_dma(const vxl_layout* L, const vxl_attn_desc* d, f
     // no more workgroups than pairs (rounded up to whole rounds over the 8 XCDs when queues are per XCD group)
     const unsigned n_blocks = (unsigned)std::min<long long>((long long)per_cu * (n_cus / 8 * 8),
                                                             xpg ? (n_pairs + 7) / 8 * 8 : n_pairs);
+    const int queue_start = TAKE != kLate ? 0 : xpg ? (int)(n_blocks / 8) * xpg : (int)n_blocks;      // the workgroups' first pairs
+    if (L->n_ctx_tiles > 0) {
+        constexpr int rows = 256 / (D * 2 / 16);
+        hipLaunchKernelGGL((compact_kv_kernel<D>), dim3((n_rows_pad + rows - 1) / rows, d->n_kv_heads),
+                           dim3(256), 0, s, (const uint4*)K, (const uint4*)V, L->d_tile_src, (uint4*)kctx,
+                           (uint4*)vctx, n_rows_pad, ts.kh / 8, ts.kt / 8, queue, queue_start);
+    } else {
+        hipLaunchKernelGGL(reset_queue_kernel, dim3(1), dim3(64), 0, s, queue, queue_start);
+    }
+    VXL_HIP_TRY(hipGetLastError());
+    static PerDeviceOnce attr;
+    st = attr.run([] {
+        const vxl_status a = enable_big_lds(prefill_dma_kernel<D, NS, false, NW, TAKE>, C::LDS_BYTES);
+        return a != VXL_OK ? a : enable_big_lds(prefill_dma_kernel<D, NS, true, NW, TAKE>, C::LDS_BYTES);
+    });
+    if (st != VXL_OK) return st;
+    hipEvent_t ev_start = g_ev_start, ev_stop = g_ev_stop;
+    const bool timed = ev_start && ev_stop;
+    if (timed) VXL_HIP_TRY(hipEventRecord(ev_start, s));
 #define VXL_LAUNCH(STRIDED_)                                                                             \
-    hipLaunchKernelGGL((prefill_dma_kernel<D, NS, STRIDED_, NW>), dim3(n_blocks), dim3(NW * 64),          \
+    hipLaunchKernelGGL((prefill_dma_kernel<D, NS, STRIDED_, NW, TAKE>), dim3(n_blocks), dim3(NW * 64),          \
                        C::LDS_BYTES, s, (const uint16_t*)Q, (const uint16_t*)K, (const uint16_t*)V, kctx,  \
                        vctx, (uint16_t*)O, LSE, L->d_segs, L->d_work[wl_i], L->n_tokens, d->n_q_heads,     \
                        group, n_rows_pad, scale, L->n_work[wl_i], xpg, queue, ts.qh, (int)ts.qt, ts.kh,    \
-                       (int)ts.kt)
+                       (int)ts.kt, nullptr, 0)
+    if (dense_layout(d)) VXL_LAUNCH(false); else VXL_LAUNCH(true);
+#undef VXL_LAUNCH
+    VXL_HIP_TRY(hipGetLastError());
+    if (timed) VXL_HIP_TRY(hipEventRecord(ev_stop, s));
+    return VXL_OK;
+}
+
+// The instances without a pre-pass: `spread` keeps two workgroups of D = 64 off one compute unit by their LDS.
+template <int D, int NW>
+static vxl_status run_prefill_direct(const vxl_layout* L, const vxl_attn_desc* d, float scale, const void* Q, const void* K,
+                                     const void* V, void* O, float* LSE, hipStream_t s, bool spread) {
+    using C = PrefillDmaCfg<D, 4, NW>;
+    constexpr int kMaxLds = 163840;
+    const TokStrides ts = tok_strides(d, L->n_tokens);
+    if (!segments_fit_32_bits(L, ts)) return VXL_ERR_UNSUPPORTED;
+    static PerDeviceOnce attr;
+    const vxl_status st = attr.run([] {
+        const vxl_status a = enable_big_lds(prefill_dma_kernel<D, 4, false, NW, kDirect>, kMaxLds);
+        return a != VXL_OK ? a : enable_big_lds(prefill_dma_kernel<D, 4, true, NW, kDirect>, kMaxLds);
+    });
+    if (st != VXL_OK) return st;
+    hipEvent_t ev_start = g_ev_start, ev_stop = g_ev_stop;
+    const bool timed = ev_start && ev_stop;
+    if (timed) VXL_HIP_TRY(hipEventRecord(ev_start, s));
+    const int group = d->n_q_heads / d->n_kv_heads;
+    const int xpg = 8 % d->n_kv_heads == 0 ? 8 / d->n_kv_heads : 0;
+    constexpr int wl_i = NW == 8 ? 1 : 0;
+    const long long per_queue = (long long)L->n_work[wl_i] * (xpg ? group : d->n_q_heads);
+    const unsigned n_blocks = (unsigned)(xpg ? (per_queue + xpg - 1) / xpg * 8 : per_queue);
+    const int lds = std::max(spread ? kMaxLds / 2 + 16 : 0, C::LDS_BYTES + L->s_total * 4);
+#define VXL_LAUNCH(STRIDED_)                                                                             \
+    hipLaunchKernelGGL((prefill_dma_kernel<D, 4, STRIDED_, NW, kDirect>), dim3(n_blocks), dim3(NW * 64), lds, s, \
+                       (const uint16_t*)Q, (const uint16_t*)K, (const uint16_t*)V, nullptr, nullptr,     \
+                       (uint16_t*)O, LSE, L->d_segs, L->d_work[wl_i], L->n_tokens, d->n_q_heads, group, 0, \
+                       scale, L->n_work[wl_i], xpg, nullptr, ts.qh, (int)ts.qt, ts.kh, (int)ts.kt,       \
+                       L->d_tile_src, L->n_prefix)
     if (dense_layout(d)) VXL_LAUNCH(false); else VXL_LAUNCH(true);
 #undef VXL_LAUNCH
     VXL_HIP_TRY(hipGetLastError());
@@ -425,31 +518,52 @@ vxl_status launch_prefill_bf16(const vxl_layout* L, const vxl_attn_desc* d, floa
     if (g_prefill_variant == 1)
         return d->head_dim == 128 ? run_prefill_dma<128, 2, 4>(L, d, scale, Q, K, V, O, LSE, ws, s)
                                   : run_prefill_dma<64, 2, 4>(L, d, scale, Q, K, V, O, LSE, ws, s);
-    // Small prompts: bands of 128 rows, so that twice as many compute units have work, and one wave per
-    // SIMD, which walks its tiles at twice the speed of two; the ring keeps its four stages.  Better
-    // while every part has a compute unit of its own (D = 128, before -> after: 14 heads over 900 ragged
-    // tokens 20.6 -> 16.6 us, 28 heads over 664 tokens 19.7 -> 15.7, 8 heads over 2,112 tokens 25.0 ->
-    // 19.1; but 328 parts 23.0 -> 26.7, 264 parts 34.6 -> 38.9), and as long as parts gain on bands at all
-    // (chunks of two cells make as many parts either way).  At D = 64 two such workgroups fit a compute
-    // unit and share it as well as one of eight waves does once that form needs a second round (896 parts
-    // 51.5 -> 47.7 us, 512 parts 52.9 -> 48.5; 1,792 and 2,048 parts 1 % and 3 % slower), but not where it
-    // gets by with one (452 parts, 226 of eight waves: 25.7 -> 28.7) or walks fewer than some six tiles per
-    // segment (880 parts of 3 tiles 27.8 -> 32.6, 832 parts of 7 tiles 40.2 -> 36.7).  Where the parts take most
-    // compute units but walk few tiles, segments of four and more cells stay with eight waves, which read the
-    // keys half as often (D = 128, five chunks of 192 tokens: 120 parts 18.5, 220 parts of four waves 20.8; D =
-    // 64, nine chunks of 170: 13.3 and 14.9; but chunks of 92, 240 parts: 20.8 -> 19.0).
+    bool late = g_prefill_variant == 3;
     if (g_prefill_variant == 0) {
         int n_cus = 0;
         const vxl_status st = device_cu_count(&n_cus);
         if (st != VXL_OK) return st;
         const long long parts4 = part_count(L, d, 4), parts8 = part_count(L, d, 8);
+        const bool d64 = d->head_dim == 64;
+        // No pre-pass and no queue (kDirect) while the compute units have some thirty tiles each and four parts at most;
+        // the table of kept rows has to fit beside the ring, and a token's row a 32-bit offset.  Beyond that the table
+        // costs more than the pre-pass, and the queue deals better: the next part is claimed late (kLate) up to four
+        // parts per compute unit, early above.  us, pre-pass and early claims -> direct / late, D = 128 unless said: 56
+        // parts 16.9 -> 14.2; D = 64, 168 parts of four waves 15.0 -> 10.6; 280 parts, 12 tiles per unit 59.1 -> 46.2 /
+        // 49.2; 804 parts, 10 tiles 70.3 -> 58.5 / 69.6; 428 parts, 25 tiles 95.1 -> 77.3 / 78.2; 492 parts, 51 tiles
+        // 142.1 -> 128.3 / 116.4; 598 parts, 36 tiles 113.4 -> 125.8 / 106.9; 956 parts, 49 tiles 138.5 -> 151.5 / 136.1;
+        // 1,820 parts, 154 tiles 342 -> 357 / 343; 4,104 parts, 685 tiles 1,379 -> 1,514 / 1,422.
+        const bool small = L->pair_count * d->n_q_heads <= 30ll * 16384 * n_cus &&
+                           (long long)L->n_tokens * tok_strides(d, L->n_tokens).kt * 2 < (1ll << 32);
+        const auto fits = [&](int lds) { return 4ll * L->s_total <= lds - (d64 ? 65552 : 131088); };   // (the ring, 16 bytes)
+        // Bands of 128 rows, so that twice as many compute units have work, and one wave per SIMD, which walks its tiles at
+        // twice the speed of two: while every part has a compute unit of its own (D = 128, eight waves -> four: 228
+        // parts 21.9 -> 17.4 us, 216 parts 15.9 -> 12.7, 44 parts 22.9 -> 17.0), and at D = 64, where two such
+        // workgroups fit a compute unit, up to four parts for each (404 parts 26.2 -> 23.3; 612 parts 18.9 -> 17.8;
+        // 1,198 parts 52.6 -> 52.3), unless chunks of one or two cells make as many parts either way (256 and 252
+        // parts 24.4 -> 25.8).
+        const bool own_unit = parts4 <= n_cus;
+        if (small && 8 * parts4 > 9 * parts8 && (own_unit ? fits(163840) : d64 && parts4 <= 4ll * n_cus && fits(81920)))
+            return d64 ? run_prefill_direct<64, 4>(L, d, scale, Q, K, V, O, LSE, s, own_unit)
+                       : run_prefill_direct<128, 4>(L, d, scale, Q, K, V, O, LSE, s, false);
+        if (small && parts8 <= 4ll * n_cus && fits(163840))
+            return d64 ? run_prefill_direct<64, 8>(L, d, scale, Q, K, V, O, LSE, s, false)
+                       : run_prefill_direct<128, 8>(L, d, scale, Q, K, V, O, LSE, s, false);
+        // Four waves with the pre-pass, where the table does not fit: while every part has a compute unit of its own
+        // (D = 128: 328 parts 23.0 -> 26.7 us), segments of four and more cells only if they walk enough tiles or leave
+        // units idle (five chunks of 192 tokens: 120 parts 18.5, 220 of four waves 20.8); D = 64, where two share a
+        // unit, once eight waves need a second round (896 parts 51.5 -> 47.7) and with some six tiles per segment.
         const bool few_keys = parts4 * 16 > n_cus * 11ll && L->n_tokens > 96ll * L->n_seg && 4 * L->seg_tiles <= 21ll * L->n_seg;
-        const bool one_round = parts4 <= n_cus && !few_keys;
-        const bool shared = d->head_dim == 64 && parts8 > n_cus && parts4 <= 4ll * n_cus && L->seg_tiles > 6ll * L->n_seg;
+        const bool one_round = own_unit && !few_keys;
+        const bool shared = d64 && parts8 > n_cus && parts4 <= 4ll * n_cus && L->seg_tiles > 6ll * L->n_seg;
         if (parts4 > parts8 && (one_round || shared))
-            return d->head_dim == 128 ? run_prefill_dma<128, 4, 4>(L, d, scale, Q, K, V, O, LSE, ws, s)
-                                      : run_prefill_dma<64, 4, 4>(L, d, scale, Q, K, V, O, LSE, ws, s, one_round);
+            return d64 ? run_prefill_dma<64, 4, 4>(L, d, scale, Q, K, V, O, LSE, ws, s, one_round)
+                       : run_prefill_dma<128, 4, 4>(L, d, scale, Q, K, V, O, LSE, ws, s);
+        late = parts8 <= 4ll * n_cus;
     }
+    if (late)
+        return d->head_dim == 128 ? run_prefill_dma<128, 4, 8, kLate>(L, d, scale, Q, K, V, O, LSE, ws, s)
+                                  : run_prefill_dma<64, 4, 8, kLate>(L, d, scale, Q, K, V, O, LSE, ws, s);
     return d->head_dim == 128 ? run_prefill_dma<128, 4>(L, d, scale, Q, K, V, O, LSE, ws, s)
                               : run_prefill_dma<64, 4>(L, d, scale, Q, K, V, O, LSE, ws, s);
 }

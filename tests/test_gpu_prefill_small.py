@@ -9,7 +9,7 @@ import torch
 
 from paper_2506_19225_amd import vxl, workloads as wl
 
-from gpu_util import assert_close, desc_of, gpu_prefill, make_layout
+from gpu_util import assert_close, desc_of, gpu_prefill, make_layout, prefill_variant
 from test_gpu_parity import oracle_prefill
 
 pytestmark = pytest.mark.gpu
@@ -43,6 +43,45 @@ def test_small_prompts_match_the_oracle(variant, hq, hkv, d, prefix, lens, windo
     want, wlse = oracle_prefill(q, k, v, lay, return_lse=True, window=window)
     assert_close(got, want, "bf16", what=f"{lens[:4]} variant {variant}")
     assert np.abs(lse - wlse).max() < 2e-2
+
+
+@pytest.mark.parametrize("hq,hkv,d,prefix,lens,window,every", [
+    (14, 2, 128, 0, [70, 1, 200, 64], 0, 3),           # four waves: history without a prefix, tile edges inside it
+    (14, 2, 128, 63, [70, 1, 200, 64], 0, 3),          # a tile of prefix and kept rows
+    (7, 1, 64, 64, [65, 129, 300], 0, 2),              # the prefix ends with a tile
+    (7, 1, 64, 65, [65, 129, 300], 90, 2),
+    (28, 4, 128, 17, [20] * 24, 0, 20),                # eight waves: many short segments, one kept row each
+    (28, 4, 128, 130, [300] * 5 + [31], 256, 7),       # history that ends inside the prefix's last tile
+    (8, 1, 128, 1, [256] * 17, 0, 8),                  # parts dealt to the XCDs in turn (eight heads on one KV head)
+    (5, 1, 64, 40, [90] * 12, 33, 4),                  # row tiles of five heads
+    (3, 3, 128, 40, [190] * 4, 0, 4),                  # KV heads that do not divide the eight XCDs
+    (1, 1, 128, 0, [700] * 12 + [100], 0, 1),          # 8,500 kept rows: no room for their table
+])
+def test_parts_and_history_without_queue_and_pre_pass(hq, hkv, d, prefix, lens, window, every):
+    """What the library chooses, and the queue with late claims, against the oracle and against the instance of large
+    prompts, whose tiles and row blocks are the same."""
+    rng = np.random.default_rng(95 + sum(lens))
+    starts = prefix + np.concatenate([[0], np.cumsum(lens)[:-1]])
+    kept = [np.sort(s + rng.choice(n, max(1, n // every), replace=False)).astype(np.int32) for s, n in zip(starts, lens)]
+    lay = wl.layout_from_lists(prefix, lens, kept)
+    w = wl.tiny_workload("bf16", hq, hkv, d, T=1, B=1, k=1, seed=95, value_scale=1.0)
+    q, k, v = wl.make_qkv(w, lay)
+    gl = make_layout(lay, window=window)
+    res = []
+    for variant in (0, 3, 2):
+        with prefill_variant(variant):
+            res.append(gpu_prefill(w, lay, q, k, v, want_lse=True, gl=gl))
+    want, wlse = oracle_prefill(q, k, v, lay, return_lse=True, window=window)
+    for got, lse in res:
+        assert_close(got, want, "bf16", what=f"{prefix} + {lens[:4]}")
+        assert np.abs(lse - wlse).max() < 2e-2
+        assert np.array_equal(got, res[-1][0]) and np.array_equal(lse, res[-1][1])
+    # token-major storage reads and writes the same rows
+    desc = vxl.make_desc(hq, hkv, d, "bf16", token_major=True)
+    ten = [vxl.to_device(x, "bf16").transpose(0, 1).contiguous() for x in (q, k, v)]
+    out = torch.full_like(ten[0], float("nan"))
+    vxl.chunk_prefill(gl, desc, *ten, out, None, vxl.alloc_workspace(vxl.workspace_bytes(vxl.OP_PREFILL, gl, desc)))
+    assert np.array_equal(vxl.to_host(out.transpose(0, 1)), res[-1][0])
 
 
 @pytest.mark.parametrize("d", [64, 128])
