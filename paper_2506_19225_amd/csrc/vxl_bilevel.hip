@@ -14,18 +14,28 @@ namespace {
 __device__ __forceinline__ float ld(const float* p) { return *p; }
 __device__ __forceinline__ float ld(const uint16_t* p) { return __uint_as_float((uint32_t)(*p) << 16); }
 
+// 16 bytes that are read once (NT: not kept in the caches)
+template <bool NT>
+__device__ __forceinline__ uint4 load16(const uint4* p) {
+    typedef __attribute__((ext_vector_type(4))) unsigned u32x4;
+    if constexpr (NT) return __builtin_bit_cast(uint4, __builtin_nontemporal_load((const u32x4*)p));
+    else return *p;
+}
+
 // ------------------------------------------------------------------------------------------
 // kbar[g, c, :] = mean of the dense key rows of chunk c.  One block per (chunk, kv head).
 // A thread owns one 16-byte column piece and the rows rg, rg + RG, ... of the chunk, which it
 // sums in row order (four independent accumulators: rows 0,4,8.. / 1,5,9.. of its sequence);
-// the RG partial sums are then added in group order.  The summation tree depends only on the
+// the RG partial sums are then added in a fixed tree.  The summation tree depends only on the
 // values and their offsets inside the chunk: two chunks with equal contents get bit-identical
-// means, hence exactly tied scores.
+// means, hence exactly tied scores.  Bound by HBM when large, otherwise by a block's chain of round
+// trips: the last rows of a thread are requested together as well (114 chunks of 128 to 1,024 tokens, one
+// by one -> so, 25.6 -> 24.1 us with the selection).  How many threads, and whether past the caches: launch_summaries.
 // ------------------------------------------------------------------------------------------
 // qbar[b, g, :] = mean over the T query tokens and the query heads of KV head g of Qd[b, t, h, :].
 // One block per (b, g): a thread owns one 16-byte column piece of one head and adds its T tokens in
 // token order (16 loads in flight at a time); the heads of the group are then added in head order.
-template <typename T, int D>
+template <typename T, int D, int THREADS>
 __device__ __forceinline__ void query_mean_block(const T* __restrict__ Qd, float* __restrict__ qbar, int b, int g,
                                                  int T_q, int n_q_heads, int n_kv_heads, float* hsum /*[group][D]*/) {
     constexpr int EPC = 16 / (int)sizeof(T);
@@ -33,7 +43,7 @@ __device__ __forceinline__ void query_mean_block(const T* __restrict__ Qd, float
     const int group = n_q_heads / n_kv_heads, tid = threadIdx.x;
     const T* qb = Qd + (size_t)b * T_q * n_q_heads * D;
     const int row_pieces = n_q_heads * PPR;
-    for (int p = tid; p < group * PPR; p += 256) {
+    for (int p = tid; p < group * PPR; p += THREADS) {
         const int gp = g * group * PPR + p;                    // piece index inside a token's [Hq*D] row
         float acc[EPC];
 #pragma unroll
@@ -58,7 +68,7 @@ __device__ __forceinline__ void query_mean_block(const T* __restrict__ Qd, float
         for (int i = 0; i < EPC; ++i) hsum[p * EPC + i] = acc[i];
     }
     __syncthreads();
-    for (int dd = tid; dd < D; dd += 256) {
+    for (int dd = tid; dd < D; dd += THREADS) {
         float a = 0.f;
         for (int hg = 0; hg < group; ++hg) a += hsum[hg * D + dd];
         qbar[((size_t)b * n_kv_heads + g) * D + dd] = a / (float)(T_q * group);
@@ -67,8 +77,8 @@ __device__ __forceinline__ void query_mean_block(const T* __restrict__ Qd, float
 
 // Blocks x < n_chunks summarise chunk x; blocks x >= n_chunks (when Qd is given) form the mean
 // query of query x - n_chunks: both feed the scoring kernel, one launch serves both.
-template <typename T, int D>
-__global__ __launch_bounds__(256) void chunk_summarize_kernel(const T* __restrict__ K,
+template <typename T, int D, int THREADS, bool NT>
+__global__ __launch_bounds__(THREADS) void chunk_summarize_kernel(const T* __restrict__ K,
                                                               const int32_t* __restrict__ bounds,
                                                               float* __restrict__ kbar, long long kv_head_u4,
                                                               long long kv_tok_u4,   // K strides, 16-byte units
@@ -77,11 +87,11 @@ __global__ __launch_bounds__(256) void chunk_summarize_kernel(const T* __restric
                                                               int n_kv_heads) {
     constexpr int EPC = 16 / (int)sizeof(T);        // elements per 16-byte piece
     constexpr int PPR = D / EPC;                    // pieces per row
-    constexpr int RG = 256 / PPR;                   // row groups
+    constexpr int RG = THREADS / PPR, U = 4;        // row groups; rows that a thread requests together
     extern __shared__ float dyn[];                  // [group][D] for the query blocks
     __shared__ float part[RG][D];
     if ((int)blockIdx.x >= n_chunks) {
-        query_mean_block<T, D>(Qd, qbar, blockIdx.x - n_chunks, blockIdx.y, T_q, n_q_heads, n_kv_heads, dyn);
+        query_mean_block<T, D, THREADS>(Qd, qbar, blockIdx.x - n_chunks, blockIdx.y, T_q, n_q_heads, n_kv_heads, dyn);
         return;
     }
     const int c = blockIdx.x, g = blockIdx.y;
@@ -94,34 +104,37 @@ __global__ __launch_bounds__(256) void chunk_summarize_kernel(const T* __restric
 #pragma unroll
         for (int i = 0; i < EPC; ++i) acc[u][i] = 0.f;
     int r = lo + rg;
-    for (; r + 3 * RG < hi; r += 4 * RG) {
-        uint4 v[4];
+    for (; r + (U - 1) * RG < hi; r += U * RG) {
+        uint4 v[U];
 #pragma unroll
-        for (int u = 0; u < 4; ++u) v[u] = base[(size_t)(r + u * RG) * kv_tok_u4];
+        for (int u = 0; u < U; ++u) v[u] = load16<NT>(base + (size_t)(r + u * RG) * kv_tok_u4);
 #pragma unroll
-        for (int u = 0; u < 4; ++u) {
+        for (int u = 0; u < U; ++u) {
             const T* e = (const T*)&v[u];
 #pragma unroll
-            for (int i = 0; i < EPC; ++i) acc[u][i] += ld(e + i);
+            for (int i = 0; i < EPC; ++i) acc[u & 3][i] += ld(e + i);
         }
     }
-    for (int u = 0; r < hi; r += RG, ++u) {
-        const uint4 v = base[(size_t)r * kv_tok_u4];
-        const T* e = (const T*)&v;
+    if (r < hi) {                                             // the last rows, requested together as well (a repeated one is not added)
+        uint4 v[U - 1];
 #pragma unroll
-        for (int i = 0; i < EPC; ++i) {
-            if (u == 0) acc[0][i] += ld(e + i);
-            else if (u == 1) acc[1][i] += ld(e + i);
-            else acc[2][i] += ld(e + i);
-        }
+        for (int u = 0; u < U - 1; ++u) v[u] = load16<NT>(base + (size_t)min(r + u * RG, hi - 1) * kv_tok_u4);
+#pragma unroll
+        for (int u = 0; u < U - 1; ++u)
+            if (r + u * RG < hi) {
+                const T* e = (const T*)&v[u];
+#pragma unroll
+                for (int i = 0; i < EPC; ++i) acc[u & 3][i] += ld(e + i);
+            }
     }
 #pragma unroll
     for (int i = 0; i < EPC; ++i) part[rg][piece * EPC + i] = (acc[0][i] + acc[1][i]) + (acc[2][i] + acc[3][i]);
     __syncthreads();
     if (threadIdx.x < D) {
-        float s = part[0][threadIdx.x];
+        float q[4];
 #pragma unroll
-        for (int i = 1; i < RG; ++i) s += part[i][threadIdx.x];
+        for (int i = 0; i < RG; ++i) q[i & 3] = i < 4 ? part[i][threadIdx.x] : q[i & 3] + part[i][threadIdx.x];
+        const float s = (q[0] + q[1]) + (q[2] + q[3]);
         kbar[((size_t)g * n_chunks + c) * D + threadIdx.x] = s / (float)(hi - lo);
     }
 }
@@ -297,7 +310,7 @@ __device__ __forceinline__ void st_round(uint16_t* p, float v) {
     *p = (b & 0x7fffffffu) > 0x7f800000u ? 0x7fc0 : (uint16_t)(up >> 16);
 }
 
-template <typename T, int D>
+template <typename T, int D, bool NT>
 __global__ __launch_bounds__(256, 8) void pool_sparse_kernel(const T* __restrict__ K, const T* __restrict__ V,
                                                           const int32_t* __restrict__ bounds,
                                                           const int32_t* __restrict__ soff, int n_chunks,
@@ -329,8 +342,8 @@ __global__ __launch_bounds__(256, 8) void pool_sparse_kernel(const T* __restrict
         uint4 kq[N], vq[N];
 #pragma unroll
         for (int u = 0; u < N; ++u) {
-            kq[u] = kp[u * kv_tok_u4];
-            vq[u] = vp[u * kv_tok_u4];
+            kq[u] = load16<NT>(kp + u * kv_tok_u4);
+            vq[u] = load16<NT>(vp + u * kv_tok_u4);
         }
 #pragma unroll
         for (int u = 0; u < N; ++u) {
@@ -482,17 +495,33 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(FOUR ? 4 : 
 vxl_status launch_summaries(const vxl_layout* L, const vxl_attn_desc* d, const void* K, float* kbar,
                             bool do_chunks, const void* Qd, int batch, int T, float* qbar, hipStream_t s) {
     const int nc = do_chunks ? L->n_chunks : 0;
-    const dim3 grid(nc + batch, d->n_kv_heads), block(256);
+    const dim3 grid(nc + batch, d->n_kv_heads);
     const size_t smem = (size_t)(d->n_q_heads / d->n_kv_heads) * d->head_dim * sizeof(float);
     const TokStrides ts = tok_strides(d, L->n_tokens);
     const long long epc = d->dtype == VXL_BF16 ? 8 : 4;       // elements per 16 bytes
-#define VXL_LAUNCH(T_, D)                                                                         \
-    hipLaunchKernelGGL((chunk_summarize_kernel<T_, D>), grid, block, smem, s, (const T_*)K, L->d_bounds, \
-                       kbar, ts.kh / epc, ts.kt / epc, nc, (const T_*)Qd, qbar, T, d->n_q_heads,   \
+    // 512 threads per chunk and KV head where there are few of them, long ones of rows of 256 bytes and more: a block is
+    // a chain of round trips (28 heads, D = 128, 256 -> 512 threads: 20 chunks of 1,000 tokens 16.0 -> 10.9 us with the
+    // selection, 60 of 700 17.8 -> 14.8; but 64 of 256 10.1 -> 11.1, and 160 of 1,000, 640 blocks, 36.8 -> 41.0).
+    // Keys that the eight L2s (32 MB) do not hold are streamed past them: 164,096 tokens 45.5 -> 40.0, 34 MB 15.6
+    // -> 14.8; but 17 MB 10.1 -> 10.7.  (The choice depends on layout and descriptor alone: means that a caller keeps are
+    // those of every later call.)
+    const long long elem = d->dtype == VXL_BF16 ? 2 : 4, row = d->head_dim * elem;
+    const bool wide = row >= 256 && (long long)L->n_chunks * d->n_kv_heads <= 512 &&
+                      (long long)L->n_tokens * row >= 19ll * 256 * 16 * L->n_chunks;
+    const bool once = L->n_tokens * (row * d->n_kv_heads) > (32 << 20);
+#define VXL_LAUNCH_AS(T_, D, THREADS, NT)                                                                        \
+    hipLaunchKernelGGL((chunk_summarize_kernel<T_, D, THREADS, NT>), grid, dim3(THREADS), smem, s, (const T_*)K,  \
+                       L->d_bounds, kbar, ts.kh / epc, ts.kt / epc, nc, (const T_*)Qd, qbar, T, d->n_q_heads,     \
                        d->n_kv_heads)
+#define VXL_LAUNCH(T_, D)                                                                                        \
+    do {                                                                                                         \
+        if (wide) { if (once) VXL_LAUNCH_AS(T_, D, 512, true); else VXL_LAUNCH_AS(T_, D, 512, false); }          \
+        else { if (once) VXL_LAUNCH_AS(T_, D, 256, true); else VXL_LAUNCH_AS(T_, D, 256, false); }               \
+    } while (0)
     if (d->dtype == VXL_F32) { if (d->head_dim == 64) VXL_LAUNCH(float, 64); else VXL_LAUNCH(float, 128); }
     else { if (d->head_dim == 64) VXL_LAUNCH(uint16_t, 64); else VXL_LAUNCH(uint16_t, 128); }
 #undef VXL_LAUNCH
+#undef VXL_LAUNCH_AS
     VXL_HIP_TRY(hipGetLastError());
     return VXL_OK;
 }
@@ -548,10 +577,16 @@ vxl_status launch_pool_sparse(const vxl_layout* L, const vxl_attn_desc* d, const
     const int rows = 256 / (d->head_dim / epc);
     const dim3 grid((L->s_total + rows - 1) / rows, d->n_kv_heads), block(256);
     const TokStrides ts = tok_strides(d, L->n_tokens);
-#define VXL_LAUNCH(T, D)                                                                            \
-    hipLaunchKernelGGL((pool_sparse_kernel<T, D>), grid, block, 0, s, (const T*)K, (const T*)V,      \
-                       L->d_bounds, L->d_soff, L->n_chunks, ts.kh / epc, ts.kt / epc, L->s_total,   \
-                       (T*)Ksp, (T*)Vsp)
+    // K and V that the 256 MB of the on-package cache do not hold are streamed past it (131,328 tokens, 269 MB, with
+    // the in-place decode behind it 123 -> 116 us; but 66,000 tokens, 136 MB, whose rows the decode then reads from
+    // there, 113 -> 122).
+    const bool once = 2ll * L->n_tokens * d->n_kv_heads * d->head_dim * (16 / epc) > (256ll << 20);
+#define VXL_LAUNCH(T, D)                                                                                       \
+    do {                                                                                                       \
+        hipLaunchKernelGGL((once ? pool_sparse_kernel<T, D, true> : pool_sparse_kernel<T, D, false>), grid, block, 0, s, \
+                           (const T*)K, (const T*)V, L->d_bounds, L->d_soff, L->n_chunks, ts.kh / epc, ts.kt / epc, \
+                           L->s_total, (T*)Ksp, (T*)Vsp);                                                      \
+    } while (0)
     if (d->dtype == VXL_F32) { if (d->head_dim == 64) VXL_LAUNCH(float, 64); else VXL_LAUNCH(float, 128); }
     else { if (d->head_dim == 64) VXL_LAUNCH(uint16_t, 64); else VXL_LAUNCH(uint16_t, 128); }
 #undef VXL_LAUNCH

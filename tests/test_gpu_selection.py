@@ -49,3 +49,27 @@ def test_a_score_does_not_depend_on_the_number_of_chunks(hkv, d):
         _, _, scores = gpu_score_topk(w, lay, qd, np.ascontiguousarray(k[:, :n_chunks * ln]), 1)
         want = scores[:, :16].copy() if want is None else want
         assert np.array_equal(scores[:, :16].view(np.uint32), want.view(np.uint32)), n_chunks
+
+
+@pytest.mark.parametrize("dtype,hkv,d,lens", [
+    ("bf16", 2, 128, [700, 64, 1000, 333, 1, 31, 480, 481, 495, 1024]),    # 512 threads: every number of last rows
+    ("f32", 2, 128, [400, 16, 47, 48, 49, 64, 300, 301]),
+    ("f32", 1, 64, [900, 15, 500]),
+    ("bf16", 3, 64, [900, 15, 500, 97]),                                   # short rows: 256 threads
+    ("bf16", 2, 128, [300, 15, 16, 17, 63, 64, 65, 47]),                   # 256 threads: short chunks
+])
+def test_mean_keys_of_long_and_ragged_chunks(dtype, hkv, d, lens):
+    """Scores of chunks whose rows leave threads with every remainder, the first two equal where they are as long; the
+    rounding of sums of up to 1,024 fp32 values in parts of at most 32 is below 2e-6 of a mean's terms."""
+    lens = lens[:1] + lens                                                 # (equal contents below: an exact tie)
+    w = wl.tiny_workload(dtype, 2 * hkv, hkv, d, T=5, B=2, k=3, seed=d, value_scale=1.0)
+    lay = wl.layout_from_lists(3, lens, [np.zeros(0, np.int32)] * len(lens))
+    _, k, _ = wl.make_qkv(w, lay, with_q=False)
+    k[:, 3 + lens[0]:3 + 2 * lens[0]] = k[:, 3:3 + lens[0]]
+    qd = wl.make_decode_queries(w)
+    want = oracle.chunk_scores(qd, k, lay.chunk_bounds)
+    idx, mask, scores = gpu_score_topk(w, lay, qd, k, 3)
+    assert np.abs(scores - want).max() <= 2e-5 * np.abs(want).max()
+    assert np.array_equal(scores[:, 0], scores[:, 1])
+    own_idx, own_mask = full_sort_selection(scores, 3)
+    assert np.array_equal(idx, own_idx) and np.array_equal(mask, own_mask)
