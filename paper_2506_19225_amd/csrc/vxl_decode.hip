@@ -211,7 +211,7 @@ struct DecodeRingCfg {
 // entry per load slot and tile; the entries of tiles t+2, t+3 are fetched (by loads issued from
 // inline assembly, so that they ride in the hand-kept vmcnt count) when the loads of tiles t, t+1 are
 // issued, and are complete behind the same vmcnt(0) that tiles t, t+1 wait for.
-template <int D, int NS, bool IND = false>
+template <int D, int NS, bool IND = false, bool ONCE = false>
 __global__ __launch_bounds__(512, 2) void decode_ring_kernel(
     const uint16_t* __restrict__ Qd, const uint16_t* __restrict__ Kmix, const uint16_t* __restrict__ Vmix,
     const int32_t* __restrict__ mix_len, float* __restrict__ part_o, float* __restrict__ part_lse, int T_q,
@@ -279,8 +279,8 @@ __global__ __launch_bounds__(512, 2) void decode_ring_kernel(
                 dma16_addr(vbase + vo + vp * 16, st + C::TILE * 2 + slot * 1024);
             } else {
                 const uint32_t roff = (uint32_t)min(row, rlim) * (D * 2);
-                dma16(kb, roff + kp * 16, st + slot * 1024);
-                dma16(vb, roff + vp * 16, st + C::TILE * 2 + slot * 1024);
+                dma16_as<ONCE>(kb, roff + kp * 16, st + slot * 1024);
+                dma16_as<ONCE>(vb, roff + vp * 16, st + C::TILE * 2 + slot * 1024);
             }
         }
     };
@@ -394,7 +394,7 @@ __global__ __launch_bounds__(512, 2) void decode_ring_kernel(
 constexpr int kStepTile = 32;       // keys per wave tile
 constexpr int kMaxStepTpw = 32;     // in-place form: tiles per wave whose row map fits the wave's LDS area
 
-template <int D, int NW, int NBUF, bool IND = false, bool ROWS = false, int MF = 4>
+template <int D, int NW, int NBUF, bool IND = false, bool ROWS = false, int MF = 4, bool ONCE = false>
 __global__ __launch_bounds__(64 * NW, 2) void decode_wave_kernel(
     const uint16_t* __restrict__ Qd, const uint16_t* __restrict__ Kmix, const uint16_t* __restrict__ Vmix,
     const int32_t* __restrict__ mix_len, float* __restrict__ part_o, float* __restrict__ part_lse, int T_q,
@@ -525,8 +525,8 @@ __global__ __launch_bounds__(64 * NW, 2) void decode_wave_kernel(
                 dma16_addr(vbase + vo + vp * 16, vdst);
             } else {
                 const uint32_t roff = (uint32_t)min(row, rlim_) * (D * 2);
-                dma16(kb, roff + kp * 16, kdst);
-                dma16(vb, roff + vp * 16, vdst);
+                dma16_as<ONCE>(kb, roff + kp * 16, kdst);
+                dma16_as<ONCE>(vb, roff + vp * 16, vdst);
             }
         }
     };
@@ -785,6 +785,13 @@ __global__ __launch_bounds__(256) void decode_merge_kernel(const float* __restri
 
 }  // namespace
 
+// Mixed sets that one row tile reads once and the eight L2s (32 MB) do not hold are streamed past the caches: 8 queries of
+// 7 rows over 54 MB of mixed rows 28.0 -> 25.9 us, over 1.1 GB 227 -> 206, of 224 rows over 580 MB, gather included, 265 ->
+// 255; but 8 MB, which the next call finds there, 8.0 -> 8.6.
+static bool beyond_l2(const vxl_attn_desc* d, int batch, int l_cap) {
+    return 4ll * batch * d->n_kv_heads * l_cap * d->head_dim > (32 << 20);
+}
+
 // The merge of a call: one wave per row while a thread's share of the splits is one batch of loads (8 splits: all
 // 84 sizes measured 0 to 14 % faster so than with four), and where the rows alone fill the chip (448 rows x 8 heads,
 // 16 splits 30.2 -> 28.4 us); otherwise four (28 rows of 16 and 31 splits: 8.4 -> 7.5 us and 9.4 -> 8.3).
@@ -861,6 +868,8 @@ static vxl_status run_decode_ring(const vxl_attn_desc* d, float scale, const voi
     const vxl_status ast = attr.run([] {
         VXL_HIP_TRY(hipFuncSetAttribute((const void*)decode_ring_kernel<D, 4, false>,
                                         hipFuncAttributeMaxDynamicSharedMemorySize, C::LDS_BYTES));
+        VXL_HIP_TRY(hipFuncSetAttribute((const void*)decode_ring_kernel<D, 4, false, true>,
+                                        hipFuncAttributeMaxDynamicSharedMemorySize, C::LDS_BYTES));
         VXL_HIP_TRY(hipFuncSetAttribute((const void*)decode_ring_kernel<D, 4, true>,
                                         hipFuncAttributeMaxDynamicSharedMemorySize, C::LDS_BYTES));
         return VXL_OK;
@@ -872,7 +881,9 @@ static vxl_status run_decode_ring(const vxl_attn_desc* d, float scale, const voi
                            (const uint16_t*)Vmix, mix_len, part_o, part_lse, T, d->n_q_heads, d->n_kv_heads, group,
                            l_cap, scale, *rm);
     else
-        hipLaunchKernelGGL((decode_ring_kernel<D, 4, false>), dim3(n_split, n_rtile * d->n_kv_heads, batch),
+        hipLaunchKernelGGL((n_rtile == 1 && beyond_l2(d, batch, l_cap) ? decode_ring_kernel<D, 4, false, true>
+                                                                       : decode_ring_kernel<D, 4, false>),
+                           dim3(n_split, n_rtile * d->n_kv_heads, batch),
                            dim3(512), C::LDS_BYTES, s, (const uint16_t*)Qd, (const uint16_t*)Kmix,
                            (const uint16_t*)Vmix, mix_len, part_o, part_lse, T, d->n_q_heads, d->n_kv_heads, group,
                            l_cap, scale, RowMap{});
@@ -898,6 +909,10 @@ static vxl_status run_decode_wave(const vxl_attn_desc* d, float scale, const voi
         VXL_HIP_TRY(hipFuncSetAttribute((const void*)decode_wave_kernel<D, 8, 1>,
                                         hipFuncAttributeMaxDynamicSharedMemorySize, lds_bytes));
         VXL_HIP_TRY(hipFuncSetAttribute((const void*)decode_wave_kernel<D, 4, 2>,
+                                        hipFuncAttributeMaxDynamicSharedMemorySize, lds_bytes));
+        VXL_HIP_TRY(hipFuncSetAttribute((const void*)decode_wave_kernel<D, 4, 2, false, false, 4, true>,
+                                        hipFuncAttributeMaxDynamicSharedMemorySize, lds_bytes));
+        VXL_HIP_TRY(hipFuncSetAttribute((const void*)decode_wave_kernel<D, 4, 2, false, false, 1, true>,
                                         hipFuncAttributeMaxDynamicSharedMemorySize, lds_bytes));
         VXL_HIP_TRY(hipFuncSetAttribute((const void*)decode_wave_kernel<D, 4, 2, true>,
                                         hipFuncAttributeMaxDynamicSharedMemorySize, lds_bytes));
@@ -928,6 +943,7 @@ static vxl_status run_decode_wave(const vxl_attn_desc* d, float scale, const voi
     }
     else if (p.step_waves == 8) VXL_LAUNCH(8, 1);
     else if (n_rtile > 1) VXL_LAUNCH(4, 2, false, true);
+    else if (beyond_l2(d, batch, l_cap)) { if (few) VXL_LAUNCH(4, 2, false, false, 1, true); else VXL_LAUNCH(4, 2, false, false, 4, true); }
     else if (few) VXL_LAUNCH(4, 2, false, false, 1);
     else VXL_LAUNCH(4, 2);
 #undef VXL_LAUNCH

@@ -311,6 +311,17 @@ __device__ __forceinline__ void dma16(const void* base, uint32_t off, uint32_t l
                  :: "s"(lds_off), "v"(off), "s"(base) : "memory");
 }
 
+// The same for what is read once: streamed past the caches.
+__device__ __forceinline__ void dma16_once(const void* base, uint32_t off, uint32_t lds_off) {
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2 nt"
+                 :: "s"(lds_off), "v"(off), "s"(base) : "memory");
+}
+
+template <bool ONCE>
+__device__ __forceinline__ void dma16_as(const void* base, uint32_t off, uint32_t lds_off) {
+    if constexpr (ONCE) dma16_once(base, off, lds_off); else dma16(base, off, lds_off);
+}
+
 // The same from a per-lane 64-bit address (rows gathered from anywhere in memory).
 __device__ __forceinline__ void dma16_addr(const void* addr, uint32_t lds_off) {
     asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off"
