@@ -5,8 +5,8 @@
 //
 // One pass over the dense keys.  The token range is cut into items (the prefix and every chunk,
 // each in pieces of at most kMassPiece keys; table built with the layout).  A workgroup owns one
-// (item, KV head, row tile, query b) and produces for each of its stacked query rows
-// rho = t*G + hg the pair (m, l): m = a reference logit of the item in base-2 units (no logit of the
+// (item, KV head, row tile) and produces for each of its stacked query rows, those of all queries one
+// after the other, rho = (b*T + t)*G + hg, the pair (m, l): m = a reference logit of the item in base-2 units (no logit of the
 // item lies more than 2^30 above it in the exp2 domain), l = sum over the item's keys of
 // 2^(logit2 - m).  Two small kernels then combine the items of a row (M = max m,
 // L = sum l*2^(m-M)) and add up, per chunk, l*2^(m-M)/L over the rows; both use fixed summation
@@ -37,17 +37,19 @@ constexpr int kMassRowTile = 128;                     // stacked query rows per 
 // logit of its first key; a maximum is formed only when a tile's sum says that the reference no longer
 // fits (`kMassGrow`).  The tiles come by direct loads into two stages, the next one in flight while a tile
 // is worked on (through registers the compiler placed the loads behind the arithmetic), four waves per SIMD.
+// The queries of a batch score the same keys, so their rows are stacked too (eight queries of 7 rows over
+// 164,096 keys, a launch of row tiles per query 206 us, so 46; of 427 rows over 36,000 keys 167 -> 150).
 // Where a launch has enough workgroups, CHAIN, one takes several short items in turn and loads its
 // queries once.  The whole score and selection, loads behind the arithmetic -> so, us: 448 rows x 4 heads
 // over 131,328 keys in 256 chunks 91.7 -> 79.6; 896 rows over 164,096 keys in 640 chunks 217 -> 171 (an item
-// per workgroup 186); 56 rows over 131,328 keys 42.9 -> 38.1; 7 rows over 164,096 keys 48.3 -> 45.6.
+// per workgroup 186); 56 rows over 131,328 keys 42.9 -> 34.8; 7 rows over 164,096 keys 48.3 -> 40.2.
 // Two row blocks per wave (half the operand reads, three waves per SIMD): 79.9 and 182, and slower on
 // small calls; a third stage at three waves per SIMD 85 and 204.
-template <int D, bool CHAIN>
+template <int D, bool CHAIN, bool ONCE>
 __global__ __launch_bounds__(256, 4) void mass_partial_kernel(
     const uint16_t* __restrict__ Qd, const uint16_t* __restrict__ K, const MassItem* __restrict__ items,
     float* __restrict__ part_m, float* __restrict__ part_l, int T_q, int n_q_heads, int n_kv_heads, int group,
-    long long kv_head, long long kv_tok, int n_items, int per_wg, float scale) {   // K strides in elements
+    long long kv_head, long long kv_tok, int n_items, int per_wg, int batch, float scale) {   // K strides in elements
     constexpr int TILE = kKeyTile * D;                // elements of one unpadded K tile
     constexpr int PPR = D / 8, RPI = 64 / PPR;        // 16-byte pieces per row, rows per load instruction (1 KiB)
     constexpr int IPW = kKeyTile / RPI / 4;           // load instructions per wave and tile
@@ -56,16 +58,15 @@ __global__ __launch_bounds__(256, 4) void mass_partial_kernel(
     const int tid = threadIdx.x, lane = tid & 63, l32 = lane & 31, hi = lane >> 5;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     // workgroup id -> (unit = (items, KV head), row tile): id = (unit / 8 * n_rt + rt) * 8 + unit % 8
-    const int n_rows = group * T_q, n_rt = (n_rows + kMassRowTile - 1) / kMassRowTile;
+    const int n_rows = group * T_q, all_rows = batch * n_rows, n_rt = (all_rows + kMassRowTile - 1) / kMassRowTile;
     const unsigned id = folded_id(), xcd = id % kXcds, seq = id / kXcds;
     const unsigned unit = seq / n_rt * kXcds + xcd;
     const int rt = seq % n_rt, g = unit % n_kv_heads;
     int item = unit / n_kv_heads * per_wg;
     if (item >= n_items) return;
     const int item_end = CHAIN ? min(item + per_wg, n_items) : item + 1;
-    const int b = blockIdx.z;
     const int wrow0 = rt * kMassRowTile + wave * 32;
-    const bool wave_active = wrow0 < n_rows;          // waves without rows only help with the loads
+    const bool wave_active = wrow0 < all_rows;          // waves without rows only help with the loads
 
     const char* kbase = (const char*)(K + (size_t)g * kv_head);
     const uint32_t row_bytes = (uint32_t)kv_tok * 2;
@@ -83,7 +84,7 @@ __global__ __launch_bounds__(256, 4) void mass_partial_kernel(
         const uint32_t st = lds_base + (uint32_t)stage * (TILE * 2);
         if (rlim == kKeyTile - 1) {
 #pragma unroll
-            for (int i = 0; i < IPW; ++i) dma16(kb, koff[i], st + (wave + i * 4) * 1024);
+            for (int i = 0; i < IPW; ++i) dma16_as<ONCE>(kb, koff[i], st + (wave + i * 4) * 1024);
         } else {
 #pragma unroll
             for (int i = 0; i < IPW; ++i) {
@@ -95,10 +96,11 @@ __global__ __launch_bounds__(256, 4) void mass_partial_kernel(
     int k_lo = items[item].key_lo, k_hi = items[item].key_hi;
     issue(k_lo, k_hi, 0);
     bf16x8 qreg[1][D / 16];
+    size_t part_row;                                  // place of this lane's row in the results of item 0
     {
-        const int rho = min(wrow0 + l32, n_rows - 1);
-        const int t = rho / group, hg = rho % group;
-        const uint4* src = (const uint4*)(Qd + (((size_t)b * T_q + t) * n_q_heads + g * group + hg) * D);
+        const int row = min(wrow0 + l32, all_rows - 1);       // (query b, token t, head in group hg), hg fastest
+        part_row = (((size_t)(row / n_rows) * n_kv_heads + g) * n_items) * n_rows + row % n_rows;
+        const uint4* src = (const uint4*)(Qd + ((size_t)(row / group) * n_q_heads + g * group + row % group) * D);
 #pragma unroll
         for (int ks = 0; ks < D / 16; ++ks) qreg[0][ks] = __builtin_bit_cast(bf16x8, src[ks * 2 + hi]);
 #pragma unroll
@@ -168,10 +170,9 @@ __global__ __launch_bounds__(256, 4) void mass_partial_kernel(
             }
             l_run += sum;
             if (item_ends) {
-                const int rho = wrow0 + l32;
                 const float l_tot = l_run + __shfl_xor(l_run, 32);
-                if (rho < n_rows && hi == 0) {
-                    const size_t idx = (((size_t)b * n_kv_heads + g) * n_items + item) * (size_t)n_rows + rho;
+                if (wrow0 + l32 < all_rows && hi == 0) {
+                    const size_t idx = part_row + (size_t)item * n_rows;
                     part_m[idx] = m_run * c2;
                     part_l[idx] = l_tot;
                 }
@@ -373,16 +374,26 @@ vxl_status launch_score_mass(const vxl_layout* L, const vxl_attn_desc* d, float 
     const int n_items = L->n_mass_items;
     const TokStrides ts = tok_strides(d, L->n_tokens);
     if (d->dtype == VXL_BF16 && !force_simple) {
-        const int n_rt = (n_rows + kMassRowTile - 1) / kMassRowTile;
-        const int per_wg = mass_items_per_workgroup(L, (long long)n_items * d->n_kv_heads * n_rt * batch);
+        const long long all_rows = (long long)batch * n_rows, n_rt = (all_rows + kMassRowTile - 1) / kMassRowTile;
+        // One row tile reads a key once: keys that the eight L2s (32 MB) do not hold are streamed past the caches
+        // (164,096 tokens, 7 rows 45.2 -> 41.7 us, 84 rows 49.7 -> 45.5; 77,056 tokens, 126 rows 31.9 -> 30.7; but two
+        // row tiles and more 83.4 -> 87.3, and 4 MB 15.7 -> 16.0).
+        const bool once = n_rt == 1 && 2ll * L->n_tokens * d->n_kv_heads * d->head_dim > (32 << 20);
+        const int per_wg = once ? 1 : mass_items_per_workgroup(L, n_items * d->n_kv_heads * n_rt);
         const long long units = (long long)((n_items + per_wg - 1) / per_wg) * d->n_kv_heads;
-        const dim3 grid = folded_grid((units + kXcds - 1) / kXcds * kXcds * n_rt, batch);
-#define VXL_LAUNCH(D, CHAIN)                                                                            \
-    hipLaunchKernelGGL((mass_partial_kernel<D, CHAIN>), grid, dim3(256), 0, s, (const uint16_t*)Qd,     \
+        const dim3 grid = folded_grid((units + kXcds - 1) / kXcds * kXcds * n_rt);
+#define VXL_LAUNCH_AS(D, CHAIN, ONCE)                                                                   \
+    hipLaunchKernelGGL((mass_partial_kernel<D, CHAIN, ONCE>), grid, dim3(256), 0, s, (const uint16_t*)Qd, \
                        (const uint16_t*)K, L->d_mass_items, part_m, part_l, T, d->n_q_heads,            \
-                       d->n_kv_heads, group, ts.kh, ts.kt, n_items, per_wg, scale)
-        if (d->head_dim == 64) { if (per_wg > 1) VXL_LAUNCH(64, true); else VXL_LAUNCH(64, false); }
-        else { if (per_wg > 1) VXL_LAUNCH(128, true); else VXL_LAUNCH(128, false); }
+                       d->n_kv_heads, group, ts.kh, ts.kt, n_items, per_wg, batch, scale)
+#define VXL_LAUNCH(D)                                                                                   \
+    do {                                                                                                \
+        if (once) VXL_LAUNCH_AS(D, false, true);                                                        \
+        else if (per_wg > 1) VXL_LAUNCH_AS(D, true, false);                                             \
+        else VXL_LAUNCH_AS(D, false, false);                                                            \
+    } while (0)
+        if (d->head_dim == 64) VXL_LAUNCH(64); else VXL_LAUNCH(128);
+#undef VXL_LAUNCH_AS
 #undef VXL_LAUNCH
     } else {
         const dim3 grid(n_items, d->n_kv_heads, batch);
