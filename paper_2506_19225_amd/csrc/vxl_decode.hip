@@ -40,6 +40,20 @@ struct RowMap {
     int s_total;
 };
 
+__device__ __forceinline__ uint16_t f32_to_bf16(float v) {
+    uint32_t b = __float_as_uint(v);
+    if ((b & 0x7fffffffu) > 0x7f800000u) return 0x7fc0;
+    b += 0x7fffu + ((b >> 16) & 1u);
+    return (uint16_t)(b >> 16);
+}
+
+// Four results of a row that has one split, whose merge is the value itself (`some`: the row's LSE is a number;
+// like the merge, a row without keys or with an LSE that is none gives 0).
+__device__ __forceinline__ void store_row4(uint16_t* p, float a, float b, float c, float d, bool some) {
+    __attribute__((aligned(8))) uint16_t out[4] = {f32_to_bf16(a), f32_to_bf16(b), f32_to_bf16(c), f32_to_bf16(d)};
+    *(uint2*)p = some ? *(const uint2*)out : make_uint2(0, 0);
+}
+
 // The keys of a split in the two kernels of larger row counts: whole 64-key tiles, dealt out evenly by the length
 // of the query's mixed set.  Cut by the capacity of its buffers, which variable chunk lengths leave partly empty,
 // the last splits of a query had no keys and the others more than their share: eight questions of 224 rows over
@@ -57,7 +71,7 @@ template <int D, int QB, bool IND = false>
 __global__ __launch_bounds__(256, (QB == 1 ? 2 : 1)) void decode_split_kernel(
     const uint16_t* __restrict__ Qd, const uint16_t* __restrict__ Kmix, const uint16_t* __restrict__ Vmix,
     const int32_t* __restrict__ mix_len, float* __restrict__ part_o, float* __restrict__ part_lse, int T_q,
-    int n_q_heads, int n_kv_heads, int group, int l_cap, float scale, RowMap rm) {
+    int n_q_heads, int n_kv_heads, int group, int l_cap, float scale, RowMap rm, uint16_t* __restrict__ O, float* __restrict__ LSE) {
     using C = DecodeCfg<D, QB>;
     extern __shared__ __attribute__((aligned(16))) uint16_t lds[];
     uint16_t* Ks = lds;
@@ -75,8 +89,16 @@ __global__ __launch_bounds__(256, (QB == 1 ? 2 : 1)) void decode_split_kernel(
     const size_t part_base = (((size_t)b * n_kv_heads + g) * n_split + split) * (size_t)n_rows;
 
     if (k_lo >= k_hi) {                            // empty split: only its weight (zero) is recorded
-        for (int r = rt * C::RT + tid; r < min(n_rows, (rt + 1) * C::RT); r += 256)
-            part_lse[part_base + r] = -INFINITY;
+        if (n_split > 1) {
+            for (int r = rt * C::RT + tid; r < min(n_rows, (rt + 1) * C::RT); r += 256) part_lse[part_base + r] = -INFINITY;
+        } else {
+            for (int e = tid; e < min(n_rows - rt * C::RT, C::RT) * (D / 4); e += 256) {
+                const int rho = rt * C::RT + e / (D / 4);
+                const size_t row = ((size_t)b * T_q + rho / group) * n_q_heads + g * group + rho % group;
+                store_row4(O + row * D + e % (D / 4) * 4, 0.f, 0.f, 0.f, 0.f, false);
+                if (LSE && e % (D / 4) == 0) LSE[row] = -INFINITY;
+            }
+        }
         return;
     }
 
@@ -167,7 +189,19 @@ __global__ __launch_bounds__(256, (QB == 1 ? 2 : 1)) void decode_split_kernel(
         const int rho = wrow0 + qb * 32 + l32;
         const float l_tot = l_run[qb] + __shfl_xor(l_run[qb], 32);
         if (rho >= n_rows) continue;
-        const float inv = 1.f / l_tot;
+        const float inv = 1.f / l_tot, lse = m_run[qb] * c2 + __builtin_amdgcn_logf(l_tot);
+        if (n_split == 1) {
+            const size_t row = ((size_t)b * T_q + rho / group) * n_q_heads + g * group + rho % group;
+            const bool some = fabsf(lse) < INFINITY;
+#pragma unroll
+            for (int db = 0; db < D / 32; ++db)
+#pragma unroll
+                for (int rq = 0; rq < 4; ++rq)
+                    store_row4(O + row * D + db * 32 + rq * 8 + hi * 4, o[qb][db][rq * 4] * inv, o[qb][db][rq * 4 + 1] * inv,
+                               o[qb][db][rq * 4 + 2] * inv, o[qb][db][rq * 4 + 3] * inv, some);
+            if (LSE && hi == 0) LSE[row] = some ? lse * kLn2 : -INFINITY;
+            continue;
+        }
         float* orow = part_o + (part_base + rho) * D;
 #pragma unroll
         for (int db = 0; db < D / 32; ++db)
@@ -180,7 +214,7 @@ __global__ __launch_bounds__(256, (QB == 1 ? 2 : 1)) void decode_split_kernel(
                 v.w = o[qb][db][rq * 4 + 3] * inv;
                 *(float4*)(orow + db * 32 + rq * 8 + hi * 4) = v;
             }
-        if (hi == 0) part_lse[part_base + rho] = m_run[qb] * c2 + __builtin_amdgcn_logf(l_tot);
+        if (hi == 0) part_lse[part_base + rho] = lse;
     }
 }
 
@@ -215,7 +249,7 @@ template <int D, int NS, bool IND = false, bool ONCE = false>
 __global__ __launch_bounds__(512, 2) void decode_ring_kernel(
     const uint16_t* __restrict__ Qd, const uint16_t* __restrict__ Kmix, const uint16_t* __restrict__ Vmix,
     const int32_t* __restrict__ mix_len, float* __restrict__ part_o, float* __restrict__ part_lse, int T_q,
-    int n_q_heads, int n_kv_heads, int group, int l_cap, float scale, RowMap rm) {
+    int n_q_heads, int n_kv_heads, int group, int l_cap, float scale, RowMap rm, uint16_t* __restrict__ O, float* __restrict__ LSE) {
     using C = DecodeRingCfg<D, NS>;
     extern __shared__ __attribute__((aligned(16))) uint16_t lds[];
     const uint32_t lds_base = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) void*)lds;
@@ -232,8 +266,16 @@ __global__ __launch_bounds__(512, 2) void decode_ring_kernel(
     const size_t part_base = (((size_t)b * n_kv_heads + g) * n_split + split) * (size_t)n_rows;
 
     if (k_lo >= k_hi) {                            // empty split: only its weight (zero) is recorded
-        for (int r = rt * C::RT + tid; r < min(n_rows, (rt + 1) * C::RT); r += 512)
-            part_lse[part_base + r] = -INFINITY;
+        if (n_split > 1) {
+            for (int r = rt * C::RT + tid; r < min(n_rows, (rt + 1) * C::RT); r += 512) part_lse[part_base + r] = -INFINITY;
+        } else {
+            for (int e = tid; e < min(n_rows - rt * C::RT, C::RT) * (D / 4); e += 512) {
+                const int rho = rt * C::RT + e / (D / 4);
+                const size_t row = ((size_t)b * T_q + rho / group) * n_q_heads + g * group + rho % group;
+                store_row4(O + row * D + e % (D / 4) * 4, 0.f, 0.f, 0.f, 0.f, false);
+                if (LSE && e % (D / 4) == 0) LSE[row] = -INFINITY;
+            }
+        }
         return;
     }
     const int n_t = (k_hi - k_lo + kKeyTile - 1) / kKeyTile;
@@ -364,7 +406,19 @@ __global__ __launch_bounds__(512, 2) void decode_ring_kernel(
     const int rho = wrow0 + l32;
     const float l_tot = l_run + __shfl_xor(l_run, 32);
     if (rho >= n_rows) return;
-    const float inv = 1.f / l_tot;
+    const float inv = 1.f / l_tot, lse = m_run * c2 + __builtin_amdgcn_logf(l_tot);
+    if (n_split == 1) {
+        const size_t row = ((size_t)b * T_q + rho / group) * n_q_heads + g * group + rho % group;
+        const bool some = fabsf(lse) < INFINITY;
+#pragma unroll
+        for (int db = 0; db < D / 32; ++db)
+#pragma unroll
+            for (int rq = 0; rq < 4; ++rq)
+                store_row4(O + row * D + db * 32 + rq * 8 + hi * 4, o[0][db][rq * 4] * inv, o[0][db][rq * 4 + 1] * inv,
+                           o[0][db][rq * 4 + 2] * inv, o[0][db][rq * 4 + 3] * inv, some);
+        if (LSE && hi == 0) LSE[row] = some ? lse * kLn2 : -INFINITY;
+        return;
+    }
     float* orow = part_o + (part_base + rho) * D;
 #pragma unroll
     for (int db = 0; db < D / 32; ++db)
@@ -377,7 +431,7 @@ __global__ __launch_bounds__(512, 2) void decode_ring_kernel(
             v.w = o[0][db][rq * 4 + 3] * inv;
             *(float4*)(orow + db * 32 + rq * 8 + hi * 4) = v;
         }
-    if (hi == 0) part_lse[part_base + rho] = m_run * c2 + __builtin_amdgcn_logf(l_tot);
+    if (hi == 0) part_lse[part_base + rho] = lse;
 }
 
 // ------------------------------------------------------------------------------------------
@@ -399,7 +453,7 @@ __global__ __launch_bounds__(64 * NW, 2) void decode_wave_kernel(
     const uint16_t* __restrict__ Qd, const uint16_t* __restrict__ Kmix, const uint16_t* __restrict__ Vmix,
     const int32_t* __restrict__ mix_len, float* __restrict__ part_o, float* __restrict__ part_lse, int T_q,
     int n_q_heads, int n_kv_heads, int group, int l_cap, int tiles_per_wave, int n_split, int n_units, int n_rtile, float scale,
-    RowMap rm) {
+    RowMap rm, uint16_t* __restrict__ O, float* __restrict__ LSE) {
     static_assert(!IND || NBUF == 2, "the in-place form exists for the double-buffered kernel only");
     constexpr int TK = kStepTile;
     constexpr int TILE_ELEMS = TK * D;                         // one unpadded tile
@@ -663,16 +717,19 @@ __global__ __launch_bounds__(64 * NW, 2) void decode_wave_kernel(
         const bool empty = M == -INFINITY;
 #pragma unroll
         for (int i = 0; i < MF; ++i) acc[i] = empty ? 0.f : acc[i] / L;
+        const float lse = empty ? -INFINITY : M * c2 + __builtin_amdgcn_logf(L);
+        if (n_split == 1) {
+            const int rho = row0 + row;
+            const size_t out = ((size_t)b * T_q + rho / group) * n_q_heads + g * group + rho % group;
+            const bool some = fabsf(lse) < INFINITY;
+            if constexpr (MF == 4) store_row4(O + out * D + dd, acc[0], acc[1], acc[2], acc[3], some);
+            else O[out * D + dd] = some ? f32_to_bf16(acc[0]) : (uint16_t)0;
+            if (LSE && dd == 0) LSE[out] = some ? lse * kLn2 : -INFINITY;
+            continue;
+        }
         *(Vec*)(part_o + (part_base + row) * D + dd) = acc;
-        if (dd == 0) part_lse[part_base + row] = empty ? -INFINITY : M * c2 + __builtin_amdgcn_logf(L);
+        if (dd == 0) part_lse[part_base + row] = lse;
     }
-}
-
-__device__ __forceinline__ uint16_t f32_to_bf16(float v) {
-    uint32_t b = __float_as_uint(v);
-    if ((b & 0x7fffffffu) > 0x7f800000u) return 0x7fc0;
-    b += 0x7fffu + ((b >> 16) & 1u);
-    return (uint16_t)(b >> 16);
 }
 
 // The fixed-order merge of the key splits.  WPR waves per query row (4, one workgroup per row, or 1, four rows
@@ -798,6 +855,7 @@ static bool beyond_l2(const vxl_attn_desc* d, int batch, int l_cap) {
 template <int D>
 static vxl_status launch_merge(int n_split, const float* part_o, const float* part_lse, void* O, float* LSE, int T,
                                const vxl_attn_desc* d, int batch, hipStream_t s) {
+    if (n_split == 1) return VXL_OK;                          // (the kernel of the one split has written the results)
     const int group = d->n_q_heads / d->n_kv_heads, n_rows = group * T;
 #define VXL_LAUNCH(WPR, PRE)                                                                                          \
     hipLaunchKernelGGL((decode_merge_kernel<D, WPR, PRE>), dim3((n_rows * WPR + 3) / 4, d->n_kv_heads, batch), dim3(256), \
@@ -835,12 +893,12 @@ static vxl_status run_decode(const vxl_attn_desc* d, float scale, const void* Qd
         hipLaunchKernelGGL((decode_split_kernel<D, QB, true>), dim3(p.n_split, n_rtile * d->n_kv_heads, batch),
                            dim3(256), C::LDS_BYTES, s, (const uint16_t*)Qd, (const uint16_t*)Kmix,
                            (const uint16_t*)Vmix, mix_len, part_o, part_lse, T, d->n_q_heads, d->n_kv_heads, group,
-                           l_cap, scale, *rm);
+                           l_cap, scale, *rm, (uint16_t*)O, LSE);
     else
         hipLaunchKernelGGL((decode_split_kernel<D, QB, false>), dim3(p.n_split, n_rtile * d->n_kv_heads, batch),
                            dim3(256), C::LDS_BYTES, s, (const uint16_t*)Qd, (const uint16_t*)Kmix,
                            (const uint16_t*)Vmix, mix_len, part_o, part_lse, T, d->n_q_heads, d->n_kv_heads, group,
-                           l_cap, scale, RowMap{});
+                           l_cap, scale, RowMap{}, (uint16_t*)O, LSE);
     VXL_HIP_TRY(hipGetLastError());
     return launch_merge<D>(p.n_split, part_o, part_lse, O, LSE, T, d, batch, s);
 }
@@ -879,14 +937,14 @@ static vxl_status run_decode_ring(const vxl_attn_desc* d, float scale, const voi
         hipLaunchKernelGGL((decode_ring_kernel<D, 4, true>), dim3(n_split, n_rtile * d->n_kv_heads, batch),
                            dim3(512), C::LDS_BYTES, s, (const uint16_t*)Qd, (const uint16_t*)Kmix,
                            (const uint16_t*)Vmix, mix_len, part_o, part_lse, T, d->n_q_heads, d->n_kv_heads, group,
-                           l_cap, scale, *rm);
+                           l_cap, scale, *rm, (uint16_t*)O, LSE);
     else
         hipLaunchKernelGGL((n_rtile == 1 && beyond_l2(d, batch, l_cap) ? decode_ring_kernel<D, 4, false, true>
                                                                        : decode_ring_kernel<D, 4, false>),
                            dim3(n_split, n_rtile * d->n_kv_heads, batch),
                            dim3(512), C::LDS_BYTES, s, (const uint16_t*)Qd, (const uint16_t*)Kmix,
                            (const uint16_t*)Vmix, mix_len, part_o, part_lse, T, d->n_q_heads, d->n_kv_heads, group,
-                           l_cap, scale, RowMap{});
+                           l_cap, scale, RowMap{}, (uint16_t*)O, LSE);
     VXL_HIP_TRY(hipGetLastError());
     return launch_merge<D>(n_split, part_o, part_lse, O, LSE, T, d, batch, s);
 }
@@ -934,7 +992,7 @@ static vxl_status run_decode_wave(const vxl_attn_desc* d, float scale, const voi
     hipLaunchKernelGGL((decode_wave_kernel<D, NW, __VA_ARGS__>), grid, dim3(64 * NW), lds_bytes, s,       \
                        (const uint16_t*)Qd, (const uint16_t*)Kmix, (const uint16_t*)Vmix, mix_len, part_o, \
                        part_lse, T, d->n_q_heads, d->n_kv_heads, group, l_cap, tpw, p.n_split, units, n_rtile, \
-                       scale, rm ? *rm : RowMap{})
+                       scale, rm ? *rm : RowMap{}, (uint16_t*)O, LSE)
     const bool few = n_rows * D <= 64 * 4;                     // (see the merge of the waves)
     if (rm) {
         if (n_rtile > 1) VXL_LAUNCH(4, 2, true, true);

@@ -113,3 +113,40 @@ def test_keys_dealt_out_by_length(t, d, lens, l_cap):
     assert_close(got[live], want, "bf16", head_axis=2, what=f"{7 * t} rows, d={d}")
     assert np.abs(lse[live] - wlse).max() < 2e-2
     assert not got[~live].any() and np.isneginf(lse[~live]).all()
+
+
+@pytest.mark.parametrize("hq,hkv,t,d,lens", [
+    (14, 2, 1, 128, [512, 1, 0, 129]),             # 7 rows: four tiles per wave
+    (14, 2, 1, 128, [513, 481]),                   # one tile more: two splits and their merge
+    (14, 2, 8, 128, [512, 33]),                    # 56 rows
+    (28, 4, 36, 128, [31, 500, 0]),                # 252 rows, empty sets among them
+    (8, 1, 8, 64, [384, 5]),                       # 64 rows, D = 64
+    (8, 1, 9, 64, [768, 400]),                     # 72 rows
+    (1, 1, 1, 64, [768]),                          # one row: fewer floats than threads
+    (2, 2, 1, 128, [90, 0]),
+    (14, 2, 40, 128, [300, 0, 64]),                # 280 rows
+    (8, 1, 100, 128, [200, 0, 7, 64] * 16),        # 800 rows, one split: the ring
+    (14, 2, 16, 64, [100, 0] * 17),                # 112 rows, one split: the 128-row kernel
+])
+def test_calls_without_a_merge(hq, hkv, t, d, lens):
+    """Mixed sets that one key split covers: the kernel writes O and LSE itself; O may be the buffer of the queries."""
+    rng = np.random.default_rng(85 + t)
+    l_cap, bsz = max(lens), len(lens)
+    w = wl.tiny_workload("bf16", hq, hkv, d, T=t, B=bsz, k=1, seed=85)
+    kmix, vmix = (wl.round_to_bf16(rng.standard_normal((bsz, hkv, l_cap, d)).astype(np.float32)) for _ in range(2))
+    qd = wl.round_to_bf16(rng.standard_normal((bsz, t, hq, d)).astype(np.float32) * np.float32(0.5))
+    dk, dv = vxl.to_device(kmix, "bf16"), vxl.to_device(vmix, "bf16")
+    for b, n in enumerate(lens):
+        dk[b, :, n:] = float("nan")
+        dv[b, :, n:] = float("nan")
+    dl = torch.tensor(lens, dtype=torch.int32, device="cuda")
+    got, lse = gpu_decode(w, qd, dk, dv, dl, want_lse=True)
+    live = np.array(lens) > 0
+    want, wlse = oracle.decode_lse(qd[live], kmix[live], vmix[live], np.array(lens, np.int32)[live])
+    assert_close(got[live], want, "bf16", head_axis=2, what=f"{hq * t // hkv} rows, d={d}")
+    assert np.abs(lse[live] - wlse).max() < 2e-2
+    assert not got[~live].any() and np.isneginf(lse[~live]).all()
+    desc, q = desc_of(w), vxl.to_device(qd, "bf16")
+    vxl.bilevel_decode(desc, q, dk, dv, dl, q, None, vxl.alloc_workspace(
+        vxl.workspace_bytes(vxl.OP_DECODE, None, desc, bsz, t, l_cap)))
+    assert np.array_equal(vxl.to_host(q), got)
