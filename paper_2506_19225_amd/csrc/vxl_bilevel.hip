@@ -21,6 +21,13 @@ __device__ __forceinline__ uint4 load16(const uint4* p) {
     if constexpr (NT) return __builtin_bit_cast(uint4, __builtin_nontemporal_load((const u32x4*)p));
     else return *p;
 }
+// 16 bytes that the caches need not keep (NT)
+template <bool NT>
+__device__ __forceinline__ void store16(uint4* p, uint4 v) {
+    typedef __attribute__((ext_vector_type(4))) unsigned u32x4;
+    if constexpr (NT) __builtin_nontemporal_store(__builtin_bit_cast(u32x4, v), (u32x4*)p);
+    else *p = v;
+}
 
 // ------------------------------------------------------------------------------------------
 // kbar[g, c, :] = mean of the dense key rows of chunk c.  One block per (chunk, kv head).
@@ -371,91 +378,104 @@ __global__ __launch_bounds__(256, 8) void pool_sparse_kernel(const T* __restrict
 
 // ------------------------------------------------------------------------------------------
 // Gather, one launch.  Every block first forms, in LDS, the exclusive scan of the rows every chunk
-// of its query contributes (its length if dense, its sparse-row count otherwise) -- C <= 4096
-// entries, a few hundred nanoseconds, cheaper than a launch of its own -- and then copies its
+// of its query contributes (its length if dense, its sparse-row count otherwise) and where they come from --
+// C <= 4096 entries, a few hundred nanoseconds, cheaper than a launch of its own -- and then copies its
 // share of the mixed rows: a group of LPR lanes per row (all KV heads, K and V, 16-byte
-// accesses), the source row found by binary search in the scanned offsets.  A block handles
+// accesses), the chunk of a row found by a few probes of its lanes in the scanned offsets.  A block handles
 // `groups` consecutive passes of 256 / LPR rows (chosen by the host so that small gathers still
-// fill the chip and large ones amortise the scan).  Block 0 of a query writes mix_len; a query whose
+// fill the chip and large ones amortise the scan).  The first block of a query writes mix_len; a query whose
 // mixed set does not fit l_cap gets mix_len = -(rows needed) and none of its rows is copied.
-// Bound by HBM when large.  A head's two loads and two stores follow one another, at eight waves per SIMD;
-// FOUR (exactly four KV heads): the pieces of all heads are requested before the first store, at four waves
-// per SIMD (the line is at launch_gather).  835 MB in and out, eight mixed sets of 25k rows: 158 us one head
+// Small calls are a chain of memory round trips: mask, bounds and offsets of a chunk are requested together and
+// the rows find them in LDS (one after the other, and again per row -> so, with the decode: three questions on a
+// 16k prompt 23.0 -> 22.2 us, 1,000 chunks 34.9 -> 32.7).  Bound by HBM when large.  A head's two loads and two stores follow one another, at
+// eight waves per SIMD; FOUR (exactly four KV heads): the pieces of all heads are requested before the first store, at
+// four waves per SIMD (the line is at launch_gather).  835 MB in and out, eight mixed sets of 25k rows: 158 us one head
 // after the other, 140 us (6.0 TB/s) at four heads together; with eight waves per SIMD 148.
+// ONCE: the mixed rows are stored past the caches and the queries of a batch take turns (block id = block of the
+// query * batch + query), so that K and V stay in the on-package cache for all of them (the line is at launch_gather).
 // With Kmix == nullptr nothing is copied at all: the call only writes mix_len and src_idx (the row
 // map the in-place decode reads the dense and sparse rows through).
 // ------------------------------------------------------------------------------------------
-template <int ROW_BYTES, bool FOUR>
+template <int ROW_BYTES, bool FOUR, bool ONCE>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(FOUR ? 4 : 8, FOUR ? 4 : 8))) void gather_kernel(
     const uint4* __restrict__ K, const uint4* __restrict__ V, const uint8_t* __restrict__ dense_mask,
     const int32_t* __restrict__ bounds, const int32_t* __restrict__ soff, const int32_t* __restrict__ sidx,
     int n_chunks, int n_prefix, long long kv_head_u4, long long kv_tok_u4,   // K, V strides in 16-byte units
     int n_kv_heads, int l_cap, int groups, uint4* __restrict__ Kmix,
     uint4* __restrict__ Vmix, int32_t* __restrict__ mix_len, int32_t* __restrict__ src_idx,
-    const uint4* __restrict__ Ksp, const uint4* __restrict__ Vsp, int s_total) {
+    const uint4* __restrict__ Ksp, const uint4* __restrict__ Vsp, int s_total, int batch) {
     constexpr int LPR = ROW_BYTES / 16;                       // lanes per row
     constexpr int ROWS = 256 / LPR;                           // rows per pass
-    extern __shared__ int off[];                              // [n_chunks + 1] first mixed row of every chunk
-    __shared__ int wave_tot[4];
-    __shared__ int carry;
-    const int b = blockIdx.y, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    extern __shared__ int off[];                              // [n_chunks] first mixed row of every chunk, then [n_chunks]
+    int* from = off + n_chunks;                               // its first token, or -1 - its first kept row
+    __shared__ int wave_tot[4][4];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int b = ONCE ? blockIdx.x % batch : blockIdx.y, block = ONCE ? blockIdx.x / batch : blockIdx.x;
     const uint8_t* mask = dense_mask + (size_t)b * n_chunks;
-    if (tid == 0) carry = n_prefix;
-    __syncthreads();
-    // The rows every chunk contributes, four 256-chunk passes at a time: their loads are all
-    // requested before the first scan (one memory round trip per 1024 chunks, not per 256).
+    int len = n_prefix;                                       // rows of the chunks so far
+    // The rows every chunk contributes, four 256-chunk passes at a time: their loads are all requested before the
+    // first scan and do not wait for the mask (one memory round trip and one barrier per 1,024 chunks).
     for (int base4 = 0; base4 < n_chunks; base4 += 1024) {
-        int v4[4];
+        int rows[4], inc[4];
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
             const int c = base4 + u * 256 + tid;
-            v4[u] = 0;
-            if (c < n_chunks) v4[u] = mask[c] ? bounds[c + 1] - bounds[c] : soff[c + 1] - soff[c];
+            rows[u] = 0;
+            if (c < n_chunks) {
+                const int lo = bounds[c], hi = bounds[c + 1], s_lo = soff[c], s_hi = soff[c + 1];
+                const bool dense = mask[c] != 0;
+                rows[u] = dense ? hi - lo : s_hi - s_lo;
+                from[c] = dense ? lo : -1 - s_lo;
+            }
         }
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
-            const int base = base4 + u * 256;
-            if (base >= n_chunks) break;                      // (uniform)
-            const int c = base + tid;
-            const int v = v4[u];
-            int inc = v;                                      // inclusive scan inside the wave
+            if (base4 + u * 256 >= n_chunks) break;           // (uniform)
+            inc[u] = rows[u];                                 // inclusive scan inside the wave
             for (int o = 1; o < 64; o <<= 1) {
-                const int t = __shfl_up(inc, o);
-                if (lane >= o) inc += t;
+                const int t = __shfl_up(inc[u], o);
+                if (lane >= o) inc[u] += t;
             }
-            if (lane == 63) wave_tot[wave] = inc;
-            __syncthreads();
-            int before = carry;
-            for (int w = 0; w < wave; ++w) before += wave_tot[w];
-            if (c < n_chunks) off[c] = before + inc - v;
-            __syncthreads();
-            if (tid == 0) carry += wave_tot[0] + wave_tot[1] + wave_tot[2] + wave_tot[3];
-            __syncthreads();
+            if (lane == 63) wave_tot[u][wave] = inc[u];
         }
+        __syncthreads();
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            if (base4 + u * 256 >= n_chunks) break;
+            const int c = base4 + u * 256 + tid;
+            int before = len;
+#pragma unroll
+            for (int w = 0; w < 4; ++w) {
+                const int t = wave_tot[u][w];
+                before += w < wave ? t : 0;
+                len += t;
+            }
+            if (c < n_chunks) off[c] = before + inc[u] - rows[u];
+        }
+        __syncthreads();                                      // off is there; wave_tot may be written again
     }
-    if (tid == 0) {
-        off[n_chunks] = carry;
-        // a mixed set that does not fit l_cap is reported, not truncated: minus the rows it needs
-        if (blockIdx.x == 0) mix_len[b] = carry <= l_cap ? carry : -carry;
-    }
-    __syncthreads();
-    const int len = off[n_chunks] <= l_cap ? off[n_chunks] : 0;
+    // a mixed set that does not fit l_cap is reported, not truncated: minus the rows it needs
+    if (block == 0 && tid == 0) mix_len[b] = len <= l_cap ? len : -len;
+    if (len > l_cap) return;
     const int part = tid % LPR;
     for (int gi = 0; gi < groups; ++gi) {
-        const int r = (blockIdx.x * groups + gi) * ROWS + tid / LPR;
-        if (r >= len) break;                                  // (rows ascend with gi)
+        const int r = (block * groups + gi) * ROWS + tid / LPR;
+        if (r >= len) break;                                  // (rows ascend with gi; the lanes of a row together)
         int src;                                              // token id, or -1 - pooled row
         if (r < n_prefix) {
             src = r;
         } else {
-            int lo = 0, hi = n_chunks;                        // last chunk with off[c] <= r
-            while (hi - lo > 1) {
-                const int mid = (lo + hi) >> 1;
-                if (off[mid] <= r) lo = mid; else hi = mid;
+            int c = 0;                                        // last chunk with off[c] <= r: it lies in [c, c + span)
+            for (int span = n_chunks; span > 1;) {
+                const int step = (span + LPR - 1) / LPR;
+                const unsigned long long hit = __ballot(part * step < span && off[min(c + part * step, n_chunks - 1)] <= r);
+                const int last = __popcll((hit >> (lane & ~(LPR - 1))) & ((1ull << LPR) - 1)) - 1;
+                c += last * step;
+                span = min(step, span - last * step);
             }
-            const int o = r - off[lo];
-            if (mask[lo]) src = bounds[lo] + o;
-            else src = Ksp ? -1 - (soff[lo] + o) : sidx[soff[lo] + o];
+            const int first = from[c], o = r - off[c];
+            if (first >= 0) src = first + o;
+            else src = Ksp ? first - o : sidx[-1 - first + o];
         }
         if (src_idx && part == 0) src_idx[(size_t)b * l_cap + r] = src;
         if (!Kmix) continue;                                  // index-only call: no rows are copied
@@ -475,14 +495,14 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(FOUR ? 4 : 
             }
 #pragma unroll
             for (int g = 0; g < 4; ++g) {
-                Kmix[d_off + g * d_head] = kq[g];
-                Vmix[d_off + g * d_head] = vq[g];
+                store16<ONCE>(Kmix + d_off + g * d_head, kq[g]);
+                store16<ONCE>(Vmix + d_off + g * d_head, vq[g]);
             }
         } else {
             for (int g = 0; g < n_kv_heads; ++g) {
                 const uint4 kq = ks[s_off + g * head_u4], vq = vs[s_off + g * head_u4];
-                Kmix[d_off + g * d_head] = kq;
-                Vmix[d_off + g * d_head] = vq;
+                store16<ONCE>(Kmix + d_off + g * d_head, kq);
+                store16<ONCE>(Vmix + d_off + g * d_head, vq);
             }
         }
     }
@@ -598,7 +618,7 @@ vxl_status launch_gather(const vxl_layout* L, const vxl_attn_desc* d, const void
                          const void* Ksp, const void* Vsp, const uint8_t* dense_mask, int batch, void* Kmix,
                          void* Vmix, int l_cap, int32_t* mix_len, int32_t* src_idx, hipStream_t s) {
     const int row_bytes = d->head_dim * (d->dtype == VXL_BF16 ? 2 : 4);
-    const size_t smem = (size_t)(L->n_chunks + 1) * sizeof(int);
+    const size_t smem = (size_t)L->n_chunks * 2 * sizeof(int);
     // Exactly four heads go together: one head after the other waits for its own loads four times, which small calls
     // spend most of their time on, and it keeps fewer bytes in flight.  Over 96 sizes of one to eight queries with
     // buffers in turn 1.05x, with the same buffers every time 1.01x.  One head after the other -> together, us:
@@ -606,26 +626,33 @@ vxl_status launch_gather(const vxl_layout* L, const vxl_attn_desc* d, const void
     // at worst (20 to 50 MB of mixed rows in HBM) 13.4 -> 13.8 and, D = 64, 12.9 -> 13.7.  Other head counts in
     // groups of four lose up to 18 %: eight heads, D = 128, 987 MB 347 -> 377; sixteen, D = 64, 1,958 MB 602 -> 725.
     const bool four = Kmix && d->n_kv_heads == 4;
+    // Mixed sets that would push K and V out of the 256 MB of the on-package cache go past it, queries in turn.  With the
+    // decode behind it, us: eight queries of 388 MB over 131,328 tokens 228 -> 200, of 344 MB 182 -> 175, of 418 MB on a
+    // ragged prompt 250 -> 246; three of 190 MB 119.7 -> 118; one of 336 MB 206 -> 203; but three of 146 MB 103.8 -> 106,
+    // one of 134 MB 86 -> 91 (the decode then reads the mixed rows from that cache).
+    const bool once = Kmix && 2ll * batch * d->n_kv_heads * l_cap * row_bytes > (160ll << 20);
     const TokStrides ts = tok_strides(d, L->n_tokens);
     const long long epc = d->dtype == VXL_BF16 ? 8 : 4;
+#define VXL_LAUNCH_AS(RB, FOUR, ONCE)                                                              \
+    hipLaunchKernelGGL((gather_kernel<RB, FOUR, ONCE>), ONCE ? dim3(blocks * batch) : dim3(blocks, batch), dim3(256), smem, \
+                       s, (const uint4*)K, (const uint4*)V, dense_mask, L->d_bounds, L->d_soff, L->d_sidx,  \
+                       L->n_chunks, L->n_prefix, ts.kh / epc, ts.kt / epc, d->n_kv_heads, l_cap, groups,    \
+                       (uint4*)Kmix, (uint4*)Vmix, mix_len, src_idx, (const uint4*)Ksp, (const uint4*)Vsp,  \
+                       L->s_total, batch)
 #define VXL_LAUNCH(RB)                                                                             \
     do {                                                                                           \
         constexpr int rows = 256 / (RB / 16);                                                      \
         const long passes = (l_cap + rows - 1) / rows;                                             \
         const int groups = (int)std::max<long>(1, std::min<long>(8, passes * batch / 512));        \
-        const dim3 grid((unsigned)((passes + groups - 1) / groups), batch);                        \
-        hipLaunchKernelGGL((four ? gather_kernel<RB, true> : gather_kernel<RB, false>), grid,      \
-                           dim3(256), smem, s, (const uint4*)K,                                    \
-                           (const uint4*)V, dense_mask, L->d_bounds, L->d_soff, L->d_sidx,         \
-                           L->n_chunks, L->n_prefix, ts.kh / epc, ts.kt / epc, d->n_kv_heads,      \
-                           l_cap, groups,                                                         \
-                           (uint4*)Kmix, (uint4*)Vmix, mix_len, src_idx, (const uint4*)Ksp,        \
-                           (const uint4*)Vsp, L->s_total);                                         \
+        const unsigned blocks = (unsigned)((passes + groups - 1) / groups);                        \
+        if (four) { if (once) VXL_LAUNCH_AS(RB, true, true); else VXL_LAUNCH_AS(RB, true, false); } \
+        else { if (once) VXL_LAUNCH_AS(RB, false, true); else VXL_LAUNCH_AS(RB, false, false); }   \
     } while (0)
     if (row_bytes == 128) VXL_LAUNCH(128);
     else if (row_bytes == 256) VXL_LAUNCH(256);
     else VXL_LAUNCH(512);
 #undef VXL_LAUNCH
+#undef VXL_LAUNCH_AS
     VXL_HIP_TRY(hipGetLastError());
     return VXL_OK;
 }

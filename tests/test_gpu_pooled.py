@@ -195,6 +195,36 @@ def test_gather_four_heads_as_two_and_two(dtype, d, pooled):
     assert all(torch.equal(x, y) for other in got[1:] for x, y in zip(got[0], other))
 
 
+@pytest.mark.parametrize("dtype,d,n_kv_heads", [("f32", 64, 3), ("bf16", 64, 2), ("bf16", 128, 3), ("bf16", 128, 4)])
+def test_gather_beyond_the_on_package_cache(dtype, d, n_kv_heads):
+    """Mixed buffers from 160 MB on, whose queries take turns: head counts that go one after the other and four, chunks of
+    more than one scan round with empty ones among them, and a query that does not fit; every row bit for bit."""
+    row, n_q = n_kv_heads * d * (4 if dtype == "f32" else 2), 13
+    l_cap = (160 << 20) // (2 * n_q * row) + 1
+    lens = np.random.default_rng(97).integers(1, 2 * l_cap // 1100 + 3, size=1100)
+    lens[0] += max(0, l_cap + 1 - 5 - int(lens.sum()))                       # all chunks dense: does not fit
+    starts = 5 + np.concatenate([[0], np.cumsum(lens)[:-1]])
+    kept = [s + 1 + np.arange(n // 5, dtype=np.int32) for s, n in zip(starts, lens)]
+    w = wl.tiny_workload(dtype, n_kv_heads, n_kv_heads, d, T=1, B=n_q, k=2, seed=96)
+    lay = wl.layout_from_lists(5, lens.tolist(), kept)
+    _, k, v = wl.make_qkv(w, lay, with_q=False)
+    masks = (np.random.default_rng(98).random((n_q, 1100)) < np.linspace(0.0, 0.3, n_q)[:, None]).astype(np.uint8)
+    masks[7] = 1
+    kmix = torch.full((n_q, n_kv_heads, l_cap, d), 7.0, dtype=vxl.to_device(k[:, :1], dtype).dtype, device="cuda")
+    vmix = torch.full_like(kmix, 7.0)
+    mix_len = torch.zeros((n_q,), dtype=torch.int32, device="cuda")
+    vxl.gather_bilevel_kv(make_layout(lay), desc_of(w), vxl.to_device(k, dtype), vxl.to_device(v, dtype),
+                          torch.from_numpy(masks).cuda(), kmix, vmix, mix_len)
+    torch.cuda.synchronize()
+    for b in range(n_q):
+        src = oracle.mixed_source_index(masks[b], lay.n_prefix, lay.chunk_bounds, lay.sparse_offsets, lay.sparse_idx)
+        n = len(src) if len(src) <= l_cap else 0
+        assert int(mix_len[b]) == (n if n else -len(src)) and (n > 0) == (b != 7)
+        hk, hv = vxl.to_host(kmix[b]), vxl.to_host(vmix[b])
+        assert np.array_equal(hk[:, :n], k[:, src[:n]]) and np.array_equal(hv[:, :n], v[:, src[:n]])
+        assert (hk[:, n:] == 7.0).all() and (hv[:, n:] == 7.0).all()
+
+
 def test_pooled_gather_without_sparse_rows_and_all_dense():
     w = wl.tiny_workload("bf16", 4, 2, 128, T=1, B=1, k=1, seed=92)
     lay = wl.layout_from_lists(4, [40, 24], [np.zeros(0, np.int32)] * 2)           # nothing kept: S_total = 0
