@@ -94,7 +94,8 @@ __global__ __launch_bounds__(THREADS) void chunk_summarize_kernel(const T* __res
                                                               int n_kv_heads) {
     constexpr int EPC = 16 / (int)sizeof(T);        // elements per 16-byte piece
     constexpr int PPR = D / EPC;                    // pieces per row
-    constexpr int RG = THREADS / PPR, U = 4;        // row groups; rows that a thread requests together
+    constexpr int RG = THREADS / PPR;               // row groups
+    constexpr int U = THREADS == 512 && !NT ? 8 : 4;      // rows that a thread requests together
     extern __shared__ float dyn[];                  // [group][D] for the query blocks
     __shared__ float part[RG][D];
     if ((int)blockIdx.x >= n_chunks) {
@@ -521,7 +522,9 @@ vxl_status launch_summaries(const vxl_layout* L, const vxl_attn_desc* d, const v
     const long long epc = d->dtype == VXL_BF16 ? 8 : 4;       // elements per 16 bytes
     // 512 threads per chunk and KV head where there are few of them, long ones of rows of 256 bytes and more: a block is
     // a chain of round trips (28 heads, D = 128, 256 -> 512 threads: 20 chunks of 1,000 tokens 16.0 -> 10.9 us with the
-    // selection, 60 of 700 17.8 -> 14.8; but 64 of 256 10.1 -> 11.1, and 160 of 1,000, 640 blocks, 36.8 -> 41.0).
+    // selection, 60 of 700 17.8 -> 14.8; but 64 of 256 10.1 -> 11.1, and 160 of 1,000, 640 blocks, 36.8 -> 41.0), eight
+    // rows of a thread at once instead of four unless they are streamed (those 20 chunks 11.4 -> 10.1; 100 of 1,200,
+    // streamed, 28.3 -> 28.8; 256 threads: 64 of 256 28.3 -> 28.7 with the rest of a query).
     // Keys that the eight L2s (32 MB) do not hold are streamed past them: 164,096 tokens 45.5 -> 40.0, 34 MB 15.6
     // -> 14.8; but 17 MB 10.1 -> 10.7.  (The choice depends on layout and descriptor alone: means that a caller keeps are
     // those of every later call.)
