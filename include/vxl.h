@@ -255,6 +255,8 @@ vxl_status vxl_gather_bilevel_kv_pooled(const vxl_layout* layout, const vxl_attn
  *            [batch, n_q_tokens, n_q_heads] or NULL
  *   mix_len  device int32 [batch]; entries above l_cap are read as l_cap, entries <= 0 (an empty
  *            set, or the overflow report of vxl_gather_bilevel_kv) give O = 0 and LSE = -inf
+ *   workspace  VXL_F32: may be NULL, misaligned or too small; the call then cuts no keys, which is slower for long
+ *            sets and sums in another order (the same result within the tolerance of the path)
  */
 vxl_status vxl_bilevel_decode(const vxl_attn_desc* desc, const void* Qd, int32_t batch,
                               int32_t n_q_tokens, const void* Kmix, const void* Vmix,
@@ -289,6 +291,7 @@ vxl_status vxl_bilevel_decode(const vxl_attn_desc* desc, const void* Qd, int32_t
  *   mix_len     device int32 [batch] (the mixed lengths: written when map_ready == 0, read
  *               otherwise) or NULL (they are then kept in the workspace)
  *   workspace   sized by vxl_workspace_bytes(VXL_OP_DECODE_INPLACE, layout, desc, batch, n_q_tokens, l_cap)
+ *               (VXL_F32: one that holds the map and 256 bytes is enough; see vxl_bilevel_decode)
  * The set of rows a query attends to is exactly that of the gathered path; the summation order
  * differs, so results agree with it within the tolerance of the path, not bit for bit.
  * Errors: VXL_ERR_INVALID_ARG, VXL_ERR_UNSUPPORTED, VXL_ERR_WORKSPACE, VXL_ERR_HIP.

@@ -67,7 +67,7 @@ extern "C" void vxl_debug_decode_step_waves(int w) { g_decode_step_waves = (w ==
 
 DecodePlan decode_plan(const vxl_attn_desc* d, int batch, int T, int l_cap, bool gathered) {
     DecodePlan p{};
-    if (d->dtype != VXL_BF16) { p.n_split = 1; p.split_len = l_cap; p.total = 0; return p; }
+    if (d->dtype != VXL_BF16) return decode_f32_plan(d, batch, T, l_cap);
     const int rows = (d->n_q_heads / d->n_kv_heads) * T;
     const int tiles = (l_cap + kKeyTile - 1) / kKeyTile;
     if (rows > kRowBlock) {
@@ -544,6 +544,11 @@ vxl_status vxl_gather_bilevel_kv_pooled(const vxl_layout* L, const vxl_attn_desc
                          batch, Kmix, Vmix, l_cap, mix_len, src_idx, (hipStream_t)stream);
 }
 
+// fp32: scratch for the split form, or null, which is the form without (no workspace, a small or a misaligned one).
+static void* f32_scratch(void* workspace, size_t bytes, size_t need) {
+    return need > 0 && workspace && bytes >= need && aligned16(workspace) ? workspace : nullptr;
+}
+
 vxl_status vxl_bilevel_decode(const vxl_attn_desc* d, const void* Qd, int32_t batch,
                               int32_t n_q_tokens, const void* Kmix, const void* Vmix, int32_t l_cap,
                               const int32_t* mix_len, void* O, float* LSE, void* workspace,
@@ -561,7 +566,9 @@ vxl_status vxl_bilevel_decode(const vxl_attn_desc* d, const void* Qd, int32_t ba
                                   LSE, workspace, (hipStream_t)stream);
     }
     if (d->dtype == VXL_F32)
-        return launch_decode_f32(d, scale, Qd, batch, n_q_tokens, Kmix, Vmix, l_cap, mix_len, O, LSE, (hipStream_t)stream);
+        return launch_decode_f32(d, scale, Qd, batch, n_q_tokens, Kmix, Vmix, l_cap, mix_len, O, LSE,
+                                 f32_scratch(workspace, workspace_bytes, decode_f32_plan(d, batch, n_q_tokens, l_cap).total),
+                                 (hipStream_t)stream);
     return launch_decode_simple(d, scale, Qd, batch, n_q_tokens, Kmix, Vmix, l_cap, mix_len, O, LSE,
                                 (hipStream_t)stream);
 }
@@ -581,7 +588,9 @@ vxl_status vxl_bilevel_decode_inplace(const vxl_layout* L, const vxl_attn_desc* 
         return VXL_ERR_INVALID_ARG;
     if (l_cap < vxl_mixed_kv_capacity(L, 0)) return VXL_ERR_INVALID_ARG;
     const InplaceWorkspace w = inplace_workspace(d, batch, n_q_tokens, l_cap);
-    if (!workspace || workspace_bytes < w.total || !aligned16(workspace)) return VXL_ERR_WORKSPACE;
+    // (fp32: the row map is needed, room for partial results is not)
+    const size_t need = d->dtype == VXL_F32 ? w.partials + 256 : w.total;
+    if (!workspace || workspace_bytes < need || !aligned16(workspace)) return VXL_ERR_WORKSPACE;
     hipStream_t s = (hipStream_t)stream;
     int32_t* src_idx = (int32_t*)((char*)workspace + w.src_idx);
     int32_t* len = mix_len ? mix_len : (int32_t*)((char*)workspace + w.mix_len);
@@ -596,7 +605,9 @@ vxl_status vxl_bilevel_decode_inplace(const vxl_layout* L, const vxl_attn_desc* 
         return launch_decode_bf16_inplace(L, d, scale, Qd, batch, n_q_tokens, K, V, Ksp, Vsp, src_idx, l_cap, len, O,
                                           LSE, (char*)workspace + w.partials, s);
     if (d->dtype == VXL_F32)
-        return launch_decode_f32_inplace(L, d, scale, Qd, batch, n_q_tokens, K, V, Ksp, Vsp, src_idx, l_cap, len, O, LSE, s);
+        return launch_decode_f32_inplace(L, d, scale, Qd, batch, n_q_tokens, K, V, Ksp, Vsp, src_idx, l_cap, len, O, LSE,
+                                         f32_scratch((char*)workspace + w.partials, workspace_bytes - w.partials,
+                                                     decode_f32_plan(d, batch, n_q_tokens, l_cap).total), s);
     return launch_decode_inplace_simple(L, d, scale, Qd, batch, n_q_tokens, K, V, Ksp, Vsp, src_idx, l_cap, len, O,
                                         LSE, s);
 }
@@ -624,8 +635,13 @@ vxl_status vxl_bilevel_decode_static(const vxl_attn_desc* d, const void* Qd, int
         return launch_decode_bf16(d, scale, Qd, batch, n_q_tokens, Kmix, Vmix, l_cap, mix_len, O, LSE, ws,
                                   (hipStream_t)stream);
     }
-    if (d->dtype == VXL_F32)
-        return launch_decode_f32(d, scale, Qd, batch, n_q_tokens, Kmix, Vmix, l_cap, mix_len, O, LSE, (hipStream_t)stream);
+    if (d->dtype == VXL_F32) {
+        const size_t need = decode_f32_plan(d, batch, n_q_tokens, l_cap).total;      // (4.3 MB at most)
+        void* ws = nullptr;
+        if (need > 0 && (st = decode_static_scratch(&ws)) != VXL_OK) return st;
+        return launch_decode_f32(d, scale, Qd, batch, n_q_tokens, Kmix, Vmix, l_cap, mix_len, O, LSE,
+                                 f32_scratch(ws, VXL_STATIC_SCRATCH_BYTES, need), (hipStream_t)stream);
+    }
     return launch_decode_simple(d, scale, Qd, batch, n_q_tokens, Kmix, Vmix, l_cap, mix_len, O, LSE,
                                 (hipStream_t)stream);
 }

@@ -36,7 +36,7 @@ namespace {
 typedef __attribute__((ext_vector_type(4))) float f32x4;
 
 constexpr int kF32Rows = 16;         // stacked query rows per block
-constexpr int kF32KB = 2;            // blocks of 16 keys per tile
+constexpr int kDecodeKB = 2;         // blocks of 16 keys per tile of the decode
 
 // Rows of a contiguous pair of buffers: slot = row.
 struct RowsPlain {
@@ -79,10 +79,10 @@ __device__ __forceinline__ void load_q_f32(const float* qrow, float4 (&q)[D / 16
 
 // One wave: 16 query rows (pieces in q) over the slots [lo, hi); slots beyond `lim` (per lane: the
 // lane's own row) are masked.  m, l: running maximum and this lane's share of the running sum.
-template <int D, typename Rows>
+template <int D, int KB, typename Rows>
 __device__ __forceinline__ void attend_tiles(const Rows& rows, const float4 (&q)[D / 16], int lo, int hi, int lim,
                                              float scale, float& m, float& l, f32x4 (&o)[D / 16]) {
-    constexpr int KB = kF32KB, TILE = 16 * KB;
+    constexpr int TILE = 16 * KB;                             // keys per tile
     const int lane = threadIdx.x & 63, i = lane & 15, j = lane >> 4;
     if (lo >= hi) return;
     float4 k[KB][D / 16], v[KB][4][D / 64];
@@ -227,12 +227,12 @@ __device__ __forceinline__ void attend_rows(const Rows& rows, QRow q_row, int lo
 // finite; a result that is not finite is therefore formed again without the tiles, in a loop so small that the
 // tiles keep their registers (without check and loop -> with them, 4 KV heads: D = 128, eight queries of two
 // rows over 390 keys 14.1 -> 14.6 us; D = 64, pre-filling of 847 tokens 9.7 -> 9.9).  q_row(row): the Q row.
-template <int D, typename Rows, typename QRow>
+template <int D, int KB, typename Rows, typename QRow>
 __device__ __forceinline__ void attend_f32(const Rows& rows, QRow q_row, int lo, int hi, int lim, float scale, float& m,
                                            float& l, f32x4 (&o)[D / 16]) {
     float4 q[D / 16];
     load_q_f32<D>(q_row(threadIdx.x & 15), q);
-    attend_tiles<D>(rows, q, lo, hi, lim, scale, m, l, o);
+    attend_tiles<D, KB>(rows, q, lo, hi, lim, scale, m, l, o);
     float z = 0.f;                                            // stays 0, or NaN
 #pragma unroll
     for (int x = 0; x < D / 16; ++x)
@@ -248,8 +248,8 @@ __device__ __forceinline__ float lse_f32(float m, float l) { return l > 0.f ? m 
 // The waves of one block of rows, merged in wave order through LDS: every wave leaves its (m, l, O),
 // then thread `tid` of `n_thr` forms the elements tid, tid + n_thr, ... of the 16 x D block and hands
 // them, four neighbouring d at a time, to store(row, d, float4 O, float lse).  A block that sees no key at
-// all (`some` false) has O = 0 and LSE = -inf.
-template <int D, int W>
+// all (`some` false) has O = 0 and LSE = -inf.  RAW: store(row, d, sum of O, (reference, sum)), for a later merge.
+template <int D, int W, bool RAW = false>
 struct MergeF32 {
     static constexpr int ROW = D + 4;                         // (padded: 16 rows in distinct banks)
     static constexpr int FLOATS = W * (kF32Rows * ROW + 2 * kF32Rows);
@@ -283,8 +283,12 @@ struct MergeF32 {
                 L = fmaf(f, stat[(x * kF32Rows + row) * 2 + 1], L);
                 a.x = fmaf(f, p.x, a.x); a.y = fmaf(f, p.y, a.y); a.z = fmaf(f, p.z, a.z); a.w = fmaf(f, p.w, a.w);
             }
-            const float inv = some ? 1.f / L : 0.f;
-            store(row, d, make_float4(a.x * inv, a.y * inv, a.z * inv, a.w * inv), some ? lse_f32(M, L) : -INFINITY);
+            if constexpr (RAW) {
+                store(row, d, a, make_float2(M, L));
+            } else {
+                const float inv = some ? 1.f / L : 0.f;
+                store(row, d, make_float4(a.x * inv, a.y * inv, a.z * inv, a.w * inv), some ? lse_f32(M, L) : -INFINITY);
+            }
         }
     }
 };
@@ -320,14 +324,14 @@ __global__ __launch_bounds__(256, 2) void prefill_f32_kernel(
     const RowsSegment rows{K + (size_t)g * kv_head, V + (size_t)g * kv_head, tile_src, sg.ctx_len,
                            sg.q_start - sg.back, kv_tok};
     const int n_keys = sg.ctx_len + sg.back + t0 + (min(rho0 + kF32Rows, rows_band) - 1) / group + 1;
-    constexpr int TILE = 16 * kF32KB;
+    constexpr int TILE = 16 * kDecodeKB;
     const int per = ((n_keys + TILE - 1) / TILE + KS - 1) / KS * TILE;
     const int lo = (wave % KS) * per, hi = min(lo + per, n_keys);
     float m = -INFINITY, l = 0.f;
     f32x4 o[D / 16];
 #pragma unroll
     for (int x = 0; x < D / 16; ++x) o[x] = f32x4{0.f, 0.f, 0.f, 0.f};
-    attend_f32<D>(rows, q_row, lo, hi, sg.ctx_len + sg.back + t, scale, m, l, o);
+    attend_f32<D, kDecodeKB>(rows, q_row, lo, hi, sg.ctx_len + sg.back + t, scale, m, l, o);
 
     auto store = [&](int row, int d, float4 val, float lse) __attribute__((always_inline)) {
         const int rr = rho0 + row;
@@ -353,24 +357,30 @@ __global__ __launch_bounds__(256, 2) void prefill_f32_kernel(
 }
 
 // Decode over the mixed KV set, gathered (rows of Kmix / Vmix) or in place (MAPPED, rows of K / V /
-// Ksp / Vsp through src_idx).  grid: row blocks x KV heads x queries, in one dimension (folded_grid);
-// all W waves of the workgroup share the keys of the block.  No scratch memory: the call takes no workspace for this storage type.
-template <int D> struct DecodeF32 {
-    static constexpr int W = D == 64 ? 16 : 8;                // (registers: 96 / 192 for operands and output)
+// Ksp / Vsp through src_idx).  grid: key splits x row blocks x KV heads x queries, in one dimension (folded_grid);
+// all W waves of the workgroup share the keys of its split.  One split: the workgroup writes the results, no scratch
+// memory.  SPLIT: it writes the sum of O, the reference and the sum of every row, and decode_f32_merge_kernel the
+// results.  Bound by the matrix instruction (a 32-key tile takes a SIMD 0.9 us at D = 64, 1.7 at D = 128), so a long
+// mixed set on few row blocks wants many compute units: the line is at decode_f32_plan.
+template <int D, bool SPLIT> struct DecodeF32 {
+    static constexpr int W = SPLIT ? 4 : D == 64 ? 16 : 8;    // (registers: 96 / 192 for operands and output)
+    static constexpr int THREADS = 64 * W, WAVES_PER_SIMD = SPLIT ? 2 : W / 4;
     static constexpr int LDS_BYTES = MergeF32<D, W>::FLOATS * 4;
 };
-template <int D, bool MAPPED>
-__global__ __launch_bounds__(64 * DecodeF32<D>::W, DecodeF32<D>::W / 4) void decode_f32_kernel(
+template <int D, bool MAPPED, bool SPLIT>
+__global__ __launch_bounds__((DecodeF32<D, SPLIT>::THREADS), (DecodeF32<D, SPLIT>::WAVES_PER_SIMD)) void decode_f32_kernel(
     const float* __restrict__ Qd, const float* __restrict__ K, const float* __restrict__ V,
     const float* __restrict__ Ksp, const float* __restrict__ Vsp, const int32_t* __restrict__ src_idx,
     float* __restrict__ O, float* __restrict__ LSE, const int32_t* __restrict__ mix_len, int T_q, int n_q_heads,
-    int n_kv_heads, int group, int batch, int l_cap, int s_total, long long kv_head, long long kv_tok, float scale) {
-    constexpr int W = DecodeF32<D>::W;
+    int n_kv_heads, int group, int batch, int l_cap, int s_total, long long kv_head, long long kv_tok, float scale,
+    int n_split, float* __restrict__ part_o, float2* __restrict__ part_ml) {
+    constexpr int W = DecodeF32<D, SPLIT>::W;
     extern __shared__ __attribute__((aligned(16))) float lds_f[];
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int n_rows = T_q * group;
-    const unsigned blocks = (n_rows + kF32Rows - 1) / kF32Rows, id = folded_id(), unit = id / blocks;
-    const int rho0 = id % blocks * kF32Rows, g = unit % n_kv_heads, b = unit / n_kv_heads;
+    const unsigned blocks = (n_rows + kF32Rows - 1) / kF32Rows, id = folded_id();
+    const unsigned split = SPLIT ? id % n_split : 0, rest = SPLIT ? id / n_split : id, unit = rest / blocks;
+    const int rho0 = rest % blocks * kF32Rows, g = unit % n_kv_heads, b = unit / n_kv_heads;
     if (b >= batch) return;
     auto q_row = [&](int row) __attribute__((always_inline)) {
         const int r = min(rho0 + row, n_rows - 1);
@@ -378,9 +388,11 @@ __global__ __launch_bounds__(64 * DecodeF32<D>::W, DecodeF32<D>::W / 4) void dec
     };
     const int n_keys = min(max(mix_len[b], 0), l_cap);
 
-    constexpr int TILE = 16 * kF32KB;
-    const int per = ((n_keys + TILE - 1) / TILE + W - 1) / W * TILE;
-    const int lo = wave * per, hi = min(lo + per, n_keys);
+    // (dealt out by the length, over the waves of all splits)
+    constexpr int TILE = 16 * kDecodeKB;
+    const int n_w = SPLIT ? n_split * W : W;
+    const int per = ((n_keys + TILE - 1) / TILE + n_w - 1) / n_w * TILE;
+    const int lo = min((int)(split * W + wave) * per, n_keys), hi = min(lo + per, n_keys);
     float m = -INFINITY, l = 0.f;
     f32x4 o[D / 16];
 #pragma unroll
@@ -388,19 +400,93 @@ __global__ __launch_bounds__(64 * DecodeF32<D>::W, DecodeF32<D>::W / 4) void dec
     if constexpr (MAPPED) {
         const RowsMapped rows{K + (size_t)g * kv_head, V + (size_t)g * kv_head, Ksp + (size_t)g * s_total * D,
                               Vsp + (size_t)g * s_total * D, src_idx + (size_t)b * l_cap, D, kv_tok};
-        attend_f32<D>(rows, q_row, lo, hi, n_keys, scale, m, l, o);
+        attend_f32<D, kDecodeKB>(rows, q_row, lo, hi, n_keys, scale, m, l, o);
     } else {
         const size_t off = ((size_t)b * n_kv_heads + g) * (size_t)l_cap * D;
-        attend_f32<D>(RowsPlain{K + off, V + off, D}, q_row, lo, hi, n_keys, scale, m, l, o);
+        attend_f32<D, kDecodeKB>(RowsPlain{K + off, V + off, D}, q_row, lo, hi, n_keys, scale, m, l, o);
     }
-    MergeF32<D, W>::run(lds_f, wave, threadIdx.x, 64 * W, m, l, o, n_keys > 0, [&](int row, int d, float4 val, float lse)
-                        __attribute__((always_inline)) {
-        const int rr = rho0 + row;
-        if (rr >= n_rows) return;
-        const size_t dst = ((size_t)b * T_q + rr / group) * n_q_heads + g * group + rr % group;
-        *(float4*)(O + dst * D + d) = val;
-        if (LSE && d == 0) LSE[dst] = lse;
-    });
+    if constexpr (SPLIT) {
+        const size_t part = (((size_t)b * n_kv_heads + g) * n_split + split) * n_rows + rho0;
+        MergeF32<D, W, true>::run(lds_f, wave, threadIdx.x, 64 * W, m, l, o, true, [&](int row, int d, float4 val, float2 ml)
+                                  __attribute__((always_inline)) {
+            if (rho0 + row >= n_rows) return;
+            *(float4*)(part_o + (part + row) * D + d) = val;
+            if (d == 0) part_ml[part + row] = ml;
+        });
+    } else {
+        MergeF32<D, W>::run(lds_f, wave, threadIdx.x, 64 * W, m, l, o, n_keys > 0, [&](int row, int d, float4 val, float lse)
+                            __attribute__((always_inline)) {
+            const int rr = rho0 + row;
+            if (rr >= n_rows) return;
+            const size_t dst = ((size_t)b * T_q + rr / group) * n_q_heads + g * group + rr % group;
+            *(float4*)(O + dst * D + d) = val;
+            if (LSE && d == 0) LSE[dst] = lse;
+        });
+    }
+}
+
+// The merge of the splits, one workgroup per query row: SG groups of D / 4 lanes take every SG-th split, U of them
+// requested together, and are folded through LDS; the order depends on the split index alone.  A split that a row
+// has no key in holds reference -inf and sums of 0.
+template <int D>
+__global__ __launch_bounds__(256) void decode_f32_merge_kernel(const float* __restrict__ part_o,
+                                                               const float2* __restrict__ part_ml, float* __restrict__ O,
+                                                               float* __restrict__ LSE, const int32_t* __restrict__ mix_len,
+                                                               int T_q, int n_q_heads, int n_kv_heads, int group, int n_split) {
+    constexpr int NV = D / 4, SG = 256 / NV, U = 4;
+    __shared__ __attribute__((aligned(16))) float red[SG][D];
+    __shared__ float2 stat[SG];
+    const int n_rows = T_q * group, sg = threadIdx.x / NV, d = threadIdx.x % NV * 4;
+    const int rho = blockIdx.x % n_rows, g = blockIdx.x / n_rows % n_kv_heads, b = blockIdx.x / n_rows / n_kv_heads;
+    const size_t base = ((size_t)b * n_kv_heads + g) * n_split * n_rows + rho;
+    float M = -INFINITY, L = 0.f;
+    float4 a = make_float4(0.f, 0.f, 0.f, 0.f);
+    for (int s0 = sg; s0 < n_split; s0 += U * SG) {
+        float2 ml[U];
+        float4 v[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {                         // (behind the last split its own values again, not counted)
+            const size_t at = base + (size_t)min(s0 + u * SG, n_split - 1) * n_rows;
+            ml[u] = part_ml[at];
+            v[u] = *(const float4*)(part_o + at * D + d);
+        }
+        float m_new = M;
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+            if (s0 + u * SG < n_split) m_new = fmaxf(m_new, ml[u].x);
+        const float ref = m_new == -INFINITY ? 0.f : m_new, f0 = expf(M - ref);
+        M = m_new;
+        L *= f0;
+        a.x *= f0; a.y *= f0; a.z *= f0; a.w *= f0;
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+            if (s0 + u * SG < n_split) {
+                const float f = expf(ml[u].x - ref);
+                L = fmaf(f, ml[u].y, L);
+                a.x = fmaf(f, v[u].x, a.x); a.y = fmaf(f, v[u].y, a.y);
+                a.z = fmaf(f, v[u].z, a.z); a.w = fmaf(f, v[u].w, a.w);
+            }
+    }
+    *(float4*)(&red[sg][d]) = a;
+    if (d == 0) stat[sg] = make_float2(M, L);
+    __syncthreads();
+    if (threadIdx.x >= D) return;
+    M = stat[0].x;
+#pragma unroll
+    for (int i = 1; i < SG; ++i) M = fmaxf(M, stat[i].x);
+    const float ref = M == -INFINITY ? 0.f : M;
+    float sum = 0.f;
+    L = 0.f;
+#pragma unroll
+    for (int i = 0; i < SG; ++i) {
+        const float f = expf(stat[i].x - ref);
+        L = fmaf(f, stat[i].y, L);
+        sum = fmaf(f, red[i][threadIdx.x], sum);
+    }
+    const bool some = mix_len[b] > 0;
+    const size_t row = ((size_t)b * T_q + rho / group) * n_q_heads + g * group + rho % group;
+    O[row * D + threadIdx.x] = some ? sum * (1.f / L) : 0.f;
+    if (LSE && threadIdx.x == 0) LSE[row] = some ? lse_f32(M, L) : -INFINITY;
 }
 
 }  // namespace
@@ -427,52 +513,82 @@ vxl_status launch_prefill_f32(const vxl_layout* L, const vxl_attn_desc* d, float
     return VXL_OK;
 }
 
+// Splits of the keys: as many workgroups of four waves as there are tiles for, 512 over all row blocks (two per compute
+// unit; against 256: eight queries of 64 rows x 4 heads over 2,064 keys, D = 64, 45.8 -> 39.2 us, others equal).  Short
+// sets stay with one workgroup per row block and no second launch; us with the gather, one workgroup -> splits,
+// D = 64: 16 rows, 512 keys 15.5 -> 16.2, 768 keys 18.6 -> 16.4; 16 rows x 4 heads, 2,064 keys 39.4 -> 16.3.  D = 128:
+// 256 keys 15.7 -> 16.3, 352 keys 20.1 -> 16.2, 16 rows x 4 heads, 2,064 keys 65.7 -> 18.4, 11,300 keys 297 -> 35.6.
+DecodePlan decode_f32_plan(const vxl_attn_desc* d, int batch, int T, int l_cap) {
+    DecodePlan p{};
+    const long long rows = (long long)(d->n_q_heads / d->n_kv_heads) * T, units = (long long)batch * d->n_kv_heads;
+    const long long blocks = (rows + kF32Rows - 1) / kF32Rows * units, tiles = ((long long)l_cap + 16 * kDecodeKB - 1) / (16 * kDecodeKB);
+    const long long n_split = tiles <= (d->head_dim == 64 ? 18 : 8) ? 1 : std::min<long long>((tiles + 3) / 4, 512 / blocks);
+    p.n_split = (int)std::max<long long>(1, n_split);
+    p.split_len = l_cap;
+    if (p.n_split > 1) {
+        p.part_ml = align_up((size_t)(units * p.n_split * rows) * d->head_dim * sizeof(float), 256);
+        p.total = p.part_ml + align_up((size_t)(units * p.n_split * rows) * sizeof(float2), 256);
+    }
+    return p;
+}
+
+// ws: scratch of decode_f32_plan(...).total bytes, or null (one split).
 template <int D>
 static vxl_status run_decode_f32(const vxl_attn_desc* d, float scale, const void* Qd, int batch, int T, const void* K,
                                  const void* V, const void* Ksp, const void* Vsp, const int32_t* src_idx, int l_cap,
-                                 int s_total, const TokStrides& ts, const int32_t* mix_len, void* O, float* LSE,
+                                 int s_total, const TokStrides& ts, const int32_t* mix_len, void* O, float* LSE, void* ws,
                                  hipStream_t s) {
     const int group = d->n_q_heads / d->n_kv_heads;
-    constexpr int lds_bytes = DecodeF32<D>::LDS_BYTES;
     static PerDeviceOnce attr;
     const vxl_status st = attr.run([] {
-        VXL_HIP_TRY(hipFuncSetAttribute((const void*)decode_f32_kernel<D, false>,
-                                        hipFuncAttributeMaxDynamicSharedMemorySize, lds_bytes));
-        VXL_HIP_TRY(hipFuncSetAttribute((const void*)decode_f32_kernel<D, true>,
-                                        hipFuncAttributeMaxDynamicSharedMemorySize, lds_bytes));
+        VXL_HIP_TRY(hipFuncSetAttribute((const void*)decode_f32_kernel<D, false, false>,
+                                        hipFuncAttributeMaxDynamicSharedMemorySize, DecodeF32<D, false>::LDS_BYTES));
+        VXL_HIP_TRY(hipFuncSetAttribute((const void*)decode_f32_kernel<D, true, false>,
+                                        hipFuncAttributeMaxDynamicSharedMemorySize, DecodeF32<D, false>::LDS_BYTES));
         return VXL_OK;
     });
     if (st != VXL_OK) return st;
-    const dim3 grid = folded_grid((long long)((group * T + kF32Rows - 1) / kF32Rows) * d->n_kv_heads * batch);
-#define VXL_LAUNCH(MAPPED)                                                                                          \
-    hipLaunchKernelGGL((decode_f32_kernel<D, MAPPED>), grid, dim3(64 * DecodeF32<D>::W), lds_bytes, s,              \
+    const DecodePlan p = decode_f32_plan(d, batch, T, l_cap);
+    const int n_split = ws ? p.n_split : 1;
+    float* part_o = (float*)ws;
+    float2* part_ml = (float2*)((char*)ws + (ws ? p.part_ml : 0));
+    const dim3 grid = folded_grid((long long)((group * T + kF32Rows - 1) / kF32Rows) * d->n_kv_heads * batch * n_split);
+#define VXL_LAUNCH(MAPPED, SPLIT)                                                                                   \
+    hipLaunchKernelGGL((decode_f32_kernel<D, MAPPED, SPLIT>), grid, dim3(DecodeF32<D, SPLIT>::THREADS),             \
+                       (DecodeF32<D, SPLIT>::LDS_BYTES), s,                                                         \
                        (const float*)Qd, (const float*)K, (const float*)V, (const float*)Ksp, (const float*)Vsp,    \
                        src_idx, (float*)O, LSE, mix_len, T, d->n_q_heads, d->n_kv_heads, group, batch, l_cap, s_total, \
-                       ts.kh, ts.kt, scale)
-    if (src_idx) VXL_LAUNCH(true); else VXL_LAUNCH(false);
+                       ts.kh, ts.kt, scale, n_split, part_o, part_ml)
+    if (n_split > 1) { if (src_idx) VXL_LAUNCH(true, true); else VXL_LAUNCH(false, true); }
+    else { if (src_idx) VXL_LAUNCH(true, false); else VXL_LAUNCH(false, false); }
 #undef VXL_LAUNCH
+    VXL_HIP_TRY(hipGetLastError());
+    if (n_split == 1) return VXL_OK;
+    hipLaunchKernelGGL(decode_f32_merge_kernel<D>, dim3(d->n_kv_heads * group * T * batch), dim3(256), 0, s, part_o, part_ml,
+                       (float*)O, LSE, mix_len, T, d->n_q_heads, d->n_kv_heads, group, n_split);
     VXL_HIP_TRY(hipGetLastError());
     return VXL_OK;
 }
 
 vxl_status launch_decode_f32(const vxl_attn_desc* d, float scale, const void* Qd, int batch, int T, const void* Kmix,
-                             const void* Vmix, int l_cap, const int32_t* mix_len, void* O, float* LSE, hipStream_t s) {
+                             const void* Vmix, int l_cap, const int32_t* mix_len, void* O, float* LSE, void* ws,
+                             hipStream_t s) {
     const TokStrides none{};
     return d->head_dim == 64 ? run_decode_f32<64>(d, scale, Qd, batch, T, Kmix, Vmix, nullptr, nullptr, nullptr, l_cap,
-                                                  0, none, mix_len, O, LSE, s)
+                                                  0, none, mix_len, O, LSE, ws, s)
                              : run_decode_f32<128>(d, scale, Qd, batch, T, Kmix, Vmix, nullptr, nullptr, nullptr, l_cap,
-                                                   0, none, mix_len, O, LSE, s);
+                                                   0, none, mix_len, O, LSE, ws, s);
 }
 
 vxl_status launch_decode_f32_inplace(const vxl_layout* L, const vxl_attn_desc* d, float scale, const void* Qd, int batch,
                                      int T, const void* K, const void* V, const void* Ksp, const void* Vsp,
                                      const int32_t* src_idx, int l_cap, const int32_t* mix_len, void* O, float* LSE,
-                                     hipStream_t s) {
+                                     void* ws, hipStream_t s) {
     const TokStrides ts = tok_strides(d, L->n_tokens);
     return d->head_dim == 64 ? run_decode_f32<64>(d, scale, Qd, batch, T, K, V, Ksp, Vsp, src_idx, l_cap, L->s_total, ts,
-                                                  mix_len, O, LSE, s)
+                                                  mix_len, O, LSE, ws, s)
                              : run_decode_f32<128>(d, scale, Qd, batch, T, K, V, Ksp, Vsp, src_idx, l_cap, L->s_total,
-                                                   ts, mix_len, O, LSE, s);
+                                                   ts, mix_len, O, LSE, ws, s);
 }
 
 }  // namespace vxl

@@ -192,6 +192,8 @@ struct DecodePlan {
 };
 // gathered = false plans the in-place form (always the 4-wave step kernel, splits bounded by its row-map area)
 DecodePlan decode_plan(const vxl_attn_desc* d, int batch, int T, int l_cap, bool gathered = true);
+// fp32, either form: total == 0 with one split; a call without this much scratch memory takes one split
+DecodePlan decode_f32_plan(const vxl_attn_desc* d, int batch, int T, int l_cap);
 
 struct InplaceWorkspace {      // byte offsets into the caller's workspace (vxl_bilevel_decode_inplace)
     size_t partials;           // the decode plan's partial results
@@ -209,11 +211,11 @@ vxl_status launch_decode_bf16_inplace(const vxl_layout* L, const vxl_attn_desc* 
                                       const void* Vsp, const int32_t* src_idx, int l_cap, const int32_t* mix_len,
                                       void* O, float* LSE, void* ws, hipStream_t s);
 vxl_status launch_decode_f32(const vxl_attn_desc* d, float scale, const void* Qd, int batch, int T, const void* Kmix,
-                             const void* Vmix, int l_cap, const int32_t* mix_len, void* O, float* LSE, hipStream_t s);
+                             const void* Vmix, int l_cap, const int32_t* mix_len, void* O, float* LSE, void* ws, hipStream_t s);
 vxl_status launch_decode_f32_inplace(const vxl_layout* L, const vxl_attn_desc* d, float scale, const void* Qd, int batch,
                                      int T, const void* K, const void* V, const void* Ksp, const void* Vsp,
                                      const int32_t* src_idx, int l_cap, const int32_t* mix_len, void* O, float* LSE,
-                                     hipStream_t s);
+                                     void* ws, hipStream_t s);
 // bf16 cross-check (vxl_debug_force_simple)
 vxl_status launch_decode_inplace_simple(const vxl_layout* L, const vxl_attn_desc* d, float scale, const void* Qd,
                                         int batch, int T, const void* K, const void* V, const void* Ksp,

@@ -1,6 +1,6 @@
 """The fp32 matrix-instruction kernels at the sizes where a row block (16 stacked rows), a key tile (32) or the
 slices of the waves that share a block's keys are partly filled or empty, and on both sides of the line between
-shared and unshared keys (16 rows per SIMD of the chip).  Tolerance: the path's 1e-5 for fp32 storage."""
+one workgroup per row block and key splits in the decode.  Tolerance: the path's 1e-5 for fp32 storage."""
 import numpy as np
 import pytest
 import torch
@@ -8,7 +8,7 @@ import torch
 import oracle
 from paper_2506_19225_amd import vxl, workloads as wl
 
-from gpu_util import assert_close, gpu_decode, gpu_decode_inplace, gpu_prefill, kept_rows, make_layout
+from gpu_util import assert_close, desc_of, gpu_decode, gpu_decode_inplace, gpu_prefill, kept_rows, make_layout
 
 pytestmark = pytest.mark.gpu
 
@@ -53,6 +53,63 @@ def test_decode_f32_edges(d, hq, t_q, lens):
         want, wlse = oracle.decode_lse(qd[b:b + 1], k[b:b + 1], v[b:b + 1], np.array([n], np.int32))
         assert_close(got[b:b + 1], want, "f32", head_axis=2, what=f"decode, {n} rows")
         assert np.abs(lse[b] - wlse[0]).max() <= 1e-5
+
+
+@pytest.mark.parametrize("d,cap", [(64, 576), (64, 577), (128, 256), (128, 257), (64, 5000), (128, 5000)])
+@pytest.mark.parametrize("hq,t_q", [(2, 1), (6, 11), (8, 16)])
+def test_decode_f32_splits(d, cap, hq, t_q):
+    """Both sides of the line, splits without keys among them (lengths far below the capacity), scratch full of NaN: the
+    oracle's rows; the call without a workspace agrees within the tolerance, the one with static scratch bit for bit."""
+    lens = [cap, 0, 1, cap // 2 + 1, 40]
+    w = wl.tiny_workload("f32", hq, 2, d, T=t_q, B=len(lens), k=1, seed=d + cap)
+    rng = np.random.default_rng(d + cap + t_q)
+    k, v = (rng.standard_normal((len(lens), 2, cap, d)).astype(np.float32) for _ in range(2))
+    dq = vxl.to_device(wl.make_decode_queries(w), "f32")
+    dk, dv, ml = vxl.to_device(k, "f32"), vxl.to_device(v, "f32"), torch.tensor(lens, dtype=torch.int32, device="cuda")
+    desc = desc_of(w)
+    nbytes = vxl.workspace_bytes(vxl.OP_DECODE, None, desc, len(lens), t_q, cap)
+    assert (nbytes > 256) == (cap > (576 if d == 64 else 256)) and nbytes <= 5 << 20
+    ws = torch.full((nbytes,), 255, dtype=torch.uint8, device="cuda")
+    res = []
+    for call in (lambda o, e: vxl.bilevel_decode(desc, dq, dk, dv, ml, o, e, ws),
+                 lambda o, e: vxl.bilevel_decode_static(desc, dq, dk, dv, ml, o, e),
+                 lambda o, e: vxl.bilevel_decode(desc, dq, dk, dv, ml, o, e, None)):
+        out, lse = torch.full_like(dq, float("nan")), torch.full(dq.shape[:3], float("nan"), device="cuda")
+        call(out, lse)
+        res.append((vxl.to_host(out), vxl.to_host(lse)))
+    (got, lse), (got_s, lse_s), (got_1, lse_1) = res
+    assert np.array_equal(got, got_s) and np.array_equal(lse, lse_s)
+    assert (got[1] == 0).all() and np.isneginf(lse[1]).all() and (got_1[1] == 0).all() and np.isneginf(lse_1[1]).all()
+    some = [0, 2, 3, 4]
+    want, wlse = oracle.decode_lse(vxl.to_host(dq)[some], k[some], v[some], np.array(lens, np.int32)[some])
+    for o, e in ((got, lse), (got_1, lse_1)):
+        assert_close(o[some], want, "f32", head_axis=2, what=f"decode, {cap} rows")
+        assert np.abs(e[some] - wlse).max() <= 1e-5
+
+
+def test_decode_inplace_f32_without_room_for_partials():
+    """A workspace that holds the row map and no partial results still serves the call, within the tolerance of the one
+    with room; one that does not hold the map is refused."""
+    rng = np.random.default_rng(8)
+    w = wl.tiny_workload("f32", 4, 2, 128, T=3, B=2, k=1, seed=8)
+    lay = wl.random_layout(rng, 19, 9, 30, 90)
+    _, k, v = wl.make_qkv(w, lay, with_q=False)
+    masks = torch.from_numpy(rng.integers(0, 2, size=(2, lay.n_chunks)).astype(np.uint8)).cuda()
+    dq, dk, dv = (vxl.to_device(x, "f32") for x in (wl.make_decode_queries(w), k, v))
+    gl, desc = make_layout(lay), desc_of(w)
+    full = vxl.workspace_bytes(vxl.OP_DECODE_INPLACE, gl, desc, 2, 3, lay.n_tokens)
+    map_only = (2 * lay.n_tokens * 4 + 255) // 256 * 256 + 256 + 256
+    assert map_only < full
+    outs = []
+    for n in (full, map_only, map_only - 1):
+        ws, out = torch.full((n,), 255, dtype=torch.uint8, device="cuda"), torch.full_like(dq, float("nan"))
+        try:
+            vxl.bilevel_decode_inplace(gl, desc, dq, dk, dv, None, None, masks, lay.n_tokens, out, None, None, ws)
+        except vxl.VxlError as e:
+            assert e.status == vxl.VXL_ERR_WORKSPACE and n < map_only
+            continue
+        outs.append(vxl.to_host(out))
+    assert len(outs) == 2 and np.isfinite(outs[0]).all() and np.abs(outs[0] - outs[1]).max() <= 1e-5
 
 
 @pytest.mark.parametrize("d,compacted", [(64, False), (128, True), (128, False)])
@@ -138,9 +195,9 @@ def test_decode_f32_non_finite(d):
     assert np.isnan(got[3:]).all() and np.isnan(lse[3:]).all()
 
 
-@pytest.mark.parametrize("hq,n", [(2, 90), (28, 700)])                   # four waves share the keys of a block; one
+@pytest.mark.parametrize("hq,n", [(2, 90), (28, 700)])
 def test_prefill_f32_without_weight(hq, n):
-    """A row whose visible logits are all -inf has neither output nor LSE, in either form of the kernel."""
+    """A row whose visible logits are all -inf has neither output nor LSE."""
     lay = wl.layout_from_lists(0, [n], [np.zeros(0, np.int32)])
     w = wl.tiny_workload("f32", hq, 1, 64, T=1, B=1, k=1, seed=n)
     q, k, v = wl.make_qkv(w, lay)
