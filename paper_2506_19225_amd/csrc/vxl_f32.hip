@@ -293,27 +293,34 @@ struct MergeF32 {
     }
 };
 
-// Pre-filling.  grid: (128-token bands of the work list, heaviest first) x (row blocks of a band, over
-// the workgroup's 4 / KS blocks) x KV heads.  KS waves share the keys of a block: 4 while the call
-// has fewer blocks than the chip has SIMDs, otherwise 1 (no merge, the waves of a workgroup read the
-// same keys at about the same time).
-template <int D, int KS>
-__global__ __launch_bounds__(256, 2) void prefill_f32_kernel(
+// Pre-filling.  grid: row blocks of a full 128-token band, last one first, x bands of the work list, heaviest first, x
+// KV heads, in one dimension (folded_grid): a workgroup's walk over the keys is long against the call, so the long ones
+// begin first (bands, then row blocks from the first on, then heads 56.0 -> 51.6 us at 2,064 tokens, 8 heads on 4 KV
+// heads, D = 128; 26.0 -> 22.6 at 864; band by band, whose unused blocks come in a regular pattern, 53.2, but 54 -> 67
+// with chunks of 40 tokens).  The four waves of a workgroup share the keys of a block: loads go unhidden while few waves
+// are in flight (one wave per block from 4 blocks per compute unit on -> four waves: D = 64, 2,064 tokens 53.1 -> 31.3,
+// 20,064 tokens 876 -> 733; D = 128 92.2 -> 59.3 and 1,731 -> 1,565).  Tiles of 16 keys: a wave's share is a whole number
+// of tiles, so 32 leave more of them waiting (21.7 -> 19.9 at 1,264 tokens, D = 64; D = 128, 2,064 tokens 59.3 -> 56.1).
+// Matrix pipes 30 % busy at 2,064 tokens, D = 128.
+template <int D>
+__global__ __launch_bounds__(256, 3) void prefill_f32_kernel(
     const float* __restrict__ Q, const float* __restrict__ K, const float* __restrict__ V, float* __restrict__ O,
     float* __restrict__ LSE, const Segment* __restrict__ segs, const WorkItem* __restrict__ work,
-    const int32_t* __restrict__ tile_src, int n_tokens, int group, float scale, long long q_head, long long q_tok,
-    long long kv_head, long long kv_tok) {
-    constexpr int BAND = 128;
-    __shared__ __attribute__((aligned(16))) float lds[KS > 1 ? MergeF32<D, KS>::FLOATS : 4];
+    const int32_t* __restrict__ tile_src, int n_work, int n_tokens, int n_kv_heads, int group, float scale, long long q_head,
+    long long q_tok, long long kv_head, long long kv_tok) {
+    constexpr int BAND = 128, KS = 4, KB = 1, TILE = 16 * KB;
+    __shared__ __attribute__((aligned(16))) float lds[MergeF32<D, KS>::FLOATS];
     const int lane = threadIdx.x & 63, i = lane & 15;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const WorkItem wi = work[blockIdx.x];
+    const unsigned blocks = BAND * group / kF32Rows, id = folded_id(), band = id / n_kv_heads % n_work, below = id / n_kv_heads / n_work;
+    if (below >= blocks) return;
+    const int g = id % n_kv_heads;
+    const WorkItem wi = work[band];
     const Segment sg = segs[wi.seg];
-    const int g = blockIdx.z;
     const int t0 = wi.m_tile * BAND;
     const int rows_band = min(BAND, sg.q_len - t0) * group;
-    const int rho0 = (blockIdx.y * (4 / KS) + wave / KS) * kF32Rows;
-    if (rho0 >= rows_band) return;                            // (KS > 1: the whole workgroup)
+    const int rho0 = (blocks - 1 - below) * kF32Rows;
+    if (rho0 >= rows_band) return;
     const int rho = min(rho0 + i, rows_band - 1);
     const int t = t0 + rho / group;
     auto q_row = [&](int row) __attribute__((always_inline)) {
@@ -324,14 +331,13 @@ __global__ __launch_bounds__(256, 2) void prefill_f32_kernel(
     const RowsSegment rows{K + (size_t)g * kv_head, V + (size_t)g * kv_head, tile_src, sg.ctx_len,
                            sg.q_start - sg.back, kv_tok};
     const int n_keys = sg.ctx_len + sg.back + t0 + (min(rho0 + kF32Rows, rows_band) - 1) / group + 1;
-    constexpr int TILE = 16 * kDecodeKB;
     const int per = ((n_keys + TILE - 1) / TILE + KS - 1) / KS * TILE;
-    const int lo = (wave % KS) * per, hi = min(lo + per, n_keys);
+    const int lo = wave * per, hi = min(lo + per, n_keys);
     float m = -INFINITY, l = 0.f;
     f32x4 o[D / 16];
 #pragma unroll
     for (int x = 0; x < D / 16; ++x) o[x] = f32x4{0.f, 0.f, 0.f, 0.f};
-    attend_f32<D, kDecodeKB>(rows, q_row, lo, hi, sg.ctx_len + sg.back + t, scale, m, l, o);
+    attend_f32<D, KB>(rows, q_row, lo, hi, sg.ctx_len + sg.back + t, scale, m, l, o);
 
     auto store = [&](int row, int d, float4 val, float lse) __attribute__((always_inline)) {
         const int rr = rho0 + row;
@@ -340,20 +346,7 @@ __global__ __launch_bounds__(256, 2) void prefill_f32_kernel(
         *(float4*)(O + (size_t)hh * q_head + (size_t)tt * q_tok + d) = val;
         if (LSE && d == 0) LSE[(size_t)hh * n_tokens + tt] = lse;
     };
-    if constexpr (KS > 1) {
-        MergeF32<D, KS>::run(lds, wave, threadIdx.x, 256, m, l, o, true, store);
-    } else {
-        l += __shfl_xor(l, 16);
-        l += __shfl_xor(l, 32);
-        const float inv = 1.f / l, lse = lse_f32(m, l);
-        const int j = lane >> 4;
-#pragma unroll
-        for (int b = 0; b < D / 64; ++b)
-#pragma unroll
-            for (int r = 0; r < 4; ++r)
-                store(i, 64 * b + 16 * j + 4 * r, make_float4(o[b * 4][r] * inv, o[b * 4 + 1][r] * inv,
-                                                              o[b * 4 + 2][r] * inv, o[b * 4 + 3][r] * inv), lse);
-    }
+    MergeF32<D, KS>::run(lds, wave, threadIdx.x, 256, m, l, o, true, store);
 }
 
 // Decode over the mixed KV set, gathered (rows of Kmix / Vmix) or in place (MAPPED, rows of K / V /
@@ -495,19 +488,12 @@ vxl_status launch_prefill_f32(const vxl_layout* L, const vxl_attn_desc* d, float
                               const void* V, void* O, float* LSE, hipStream_t s) {
     const int group = d->n_q_heads / d->n_kv_heads;
     const TokStrides ts = tok_strides(d, L->n_tokens);
-    const int blocks = 128 * group / kF32Rows;                // row blocks of a full band
-    // blocks that hold rows: keys shared by four waves while these leave SIMDs idle
-    const long long rows = (long long)L->n_tokens * d->n_q_heads;
-    int n_cus = 0;
-    const vxl_status st = device_cu_count(&n_cus);
-    if (st != VXL_OK) return st;
-    const bool share = rows / kF32Rows < 4ll * n_cus;
-#define VXL_LAUNCH(D, KS)                                                                                       \
-    hipLaunchKernelGGL((prefill_f32_kernel<D, KS>), dim3(L->n_work[0], (blocks + 4 / KS - 1) / (4 / KS), d->n_kv_heads), \
-                       dim3(256), 0, s, (const float*)Q, (const float*)K, (const float*)V, (float*)O, LSE, L->d_segs,  \
-                       L->d_work[0], L->d_tile_src, L->n_tokens, group, scale, ts.qh, ts.qt, ts.kh, ts.kt)
-    if (d->head_dim == 64) { if (share) VXL_LAUNCH(64, 4); else VXL_LAUNCH(64, 1); }
-    else { if (share) VXL_LAUNCH(128, 4); else VXL_LAUNCH(128, 1); }
+    const dim3 grid = folded_grid((long long)L->n_work[0] * (128 * group / kF32Rows) * d->n_kv_heads);   // (row blocks of a full band)
+#define VXL_LAUNCH(D)                                                                                           \
+    hipLaunchKernelGGL((prefill_f32_kernel<D>), grid, dim3(256), 0, s, (const float*)Q, (const float*)K, (const float*)V,  \
+                       (float*)O, LSE, L->d_segs, L->d_work[0], L->d_tile_src, L->n_work[0], L->n_tokens,                  \
+                       d->n_kv_heads, group, scale, ts.qh, ts.qt, ts.kh, ts.kt)
+    if (d->head_dim == 64) VXL_LAUNCH(64); else VXL_LAUNCH(128);
 #undef VXL_LAUNCH
     VXL_HIP_TRY(hipGetLastError());
     return VXL_OK;
