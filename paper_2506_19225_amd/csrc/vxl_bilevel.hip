@@ -249,7 +249,7 @@ __global__ __launch_bounds__(256) void chunk_score_kernel(const float* __restric
     if (p == 0 && c < n_chunks) scores[(size_t)b * n_chunks + c] = a * (scale / (float)n_kv_heads);
 }
 
-// Scores and selection of up to kFusedChunks chunks in one block per query: a launch less, at the
+// Scores and selection of up to fused_chunks() chunks in one block per query: a launch less, at the
 // price of one compute unit reading all mean keys of a query (2 KiB per chunk at four KV heads):
 // 4.1 us at 64 chunks (9.6 with 256 threads and one load at a time), against 4.7 for each of the
 // two launches of the separate form.
@@ -258,13 +258,17 @@ __global__ __launch_bounds__(256) void chunk_score_kernel(const float* __restric
 // us of the whole call with the mean keys there, one form of 16 waves and eight steps -> so: two KV heads,
 // D = 64, 4 chunks 6.5 -> 4.8, 19 chunks 6.5 -> 5.0, 64 chunks 6.6 -> 5.3, 128 chunks 8.6 -> 6.0; four KV heads,
 // D = 128, 4 chunks 6.5 -> 5.2, 32 chunks 6.5 -> 5.7.
-constexpr int kFusedChunks = 128;
+// The line is what one compute unit reads in the time of a launch: 128 chunks, of short rows (512 bytes a chunk) 192 (two
+// KV heads, D = 64, with their mean keys: 150 chunks 11.6 -> 8.4 us, eight queries over 200 chunks 11.4 -> 9.7, but 256
+// chunks of 512 tokens 14.2 -> 14.9; rows of 2 KiB: 130 chunks 11.2 -> 12.4, 200 chunks 11.0 -> 15.4).
+constexpr int kShortSteps = 2;                                // steps of a row of up to 32 pieces
+constexpr int fused_chunks(int steps) { return steps == kShortSteps ? 192 : 128; }
 
 template <int D, int THREADS, int U>
 __global__ __launch_bounds__(THREADS) void score_topk_kernel(
     const float* __restrict__ qbar, const float* __restrict__ kbar, int n_kv_heads, int n_chunks, int k, float scale,
     int32_t* __restrict__ topk_idx, uint8_t* __restrict__ dense_mask, float* __restrict__ scores) {
-    constexpr int AT_ONCE = THREADS / kScoreLanes, MAX = AT_ONCE < 64 ? AT_ONCE : kFusedChunks;
+    constexpr int AT_ONCE = THREADS / kScoreLanes, MAX = AT_ONCE < 64 ? AT_ONCE : (fused_chunks(U) + 127) / 128 * 128;
     constexpr int GROUPS = (MAX + 63) / 64;
     __shared__ __attribute__((aligned(16))) unsigned long long keys[MAX];
     __shared__ int part[THREADS];
@@ -552,9 +556,10 @@ vxl_status launch_summaries(const vxl_layout* L, const vxl_attn_desc* d, const v
 vxl_status launch_score_topk(const vxl_layout* L, const vxl_attn_desc* d, float scale, int batch, int k,
                              const float* qbar, const float* kbar, int32_t* topk_idx, uint8_t* dense_mask,
                              float* scores, float* scores_ws, hipStream_t s) {
-    // One block per query reads all its mean keys through one compute unit, so beyond kFusedChunks
+    // One block per query reads all its mean keys through one compute unit, so beyond fused_chunks()
     // chunks the scores are formed by 16 chunks per block and the selection reads them back.
-    if (L->n_chunks > kFusedChunks) {
+    const bool short_rows = d->n_kv_heads * d->head_dim <= kShortSteps * kScoreLanes * 4;
+    if (L->n_chunks > fused_chunks(short_rows ? kShortSteps : 8)) {
         float* sc = scores ? scores : scores_ws;
         const dim3 grid((L->n_chunks + 256 / kScoreLanes - 1) / (256 / kScoreLanes), batch);
         if (d->head_dim == 64)
@@ -575,9 +580,8 @@ vxl_status launch_score_topk(const vxl_layout* L, const vxl_attn_desc* d, float 
         else if (L->n_chunks <= 512 / kScoreLanes) VXL_LAUNCH(D, 512, U);                                       \
         else VXL_LAUNCH(D, 1024, U);                                                                            \
     } while (0)
-    const bool short_rows = d->n_kv_heads * d->head_dim <= 2 * kScoreLanes * 4;
-    if (d->head_dim == 64) { if (short_rows) VXL_BY_CHUNKS(64, 2); else VXL_BY_CHUNKS(64, 8); }
-    else { if (short_rows) VXL_BY_CHUNKS(128, 2); else VXL_BY_CHUNKS(128, 8); }
+    if (d->head_dim == 64) { if (short_rows) VXL_BY_CHUNKS(64, kShortSteps); else VXL_BY_CHUNKS(64, 8); }
+    else { if (short_rows) VXL_BY_CHUNKS(128, kShortSteps); else VXL_BY_CHUNKS(128, 8); }
 #undef VXL_BY_CHUNKS
 #undef VXL_LAUNCH
     VXL_HIP_TRY(hipGetLastError());

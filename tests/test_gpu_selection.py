@@ -1,5 +1,5 @@
 """Scores and selection at the chunk counts where the kernels change form or a block, wave or key pair is only
-partly filled: one launch up to 128 chunks (blocks for 16, 32 and 64 chunks at once), 16 chunks per score block and
+partly filled: one launch up to 128 chunks, of short rows 192 (blocks for 16, 32 and 64 chunks at once), 16 chunks per score block and
 64 per selection block beyond."""
 import numpy as np
 import pytest
@@ -13,7 +13,7 @@ from gpu_util import full_sort_selection, gpu_score_topk
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("n_chunks", [1, 2, 15, 16, 17, 18, 31, 32, 33, 34, 63, 64, 65, 127, 128, 129, 143, 640, 1025, 4095, 4096])
+@pytest.mark.parametrize("n_chunks", [1, 2, 15, 16, 17, 18, 31, 32, 33, 34, 63, 64, 65, 127, 128, 129, 143, 191, 193, 640, 1025, 4095, 4096])
 def test_selection_is_a_full_sort_of_the_scores(n_chunks):
     """Every third chunk repeats one of a few contents, so that many scores tie exactly; the scores agree with the
     oracle to the rounding of 3 x 128 fp32 products (2e-5 of the largest), the selection is the full sort of them."""
