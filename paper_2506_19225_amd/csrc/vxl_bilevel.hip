@@ -259,8 +259,8 @@ __global__ __launch_bounds__(256) void chunk_score_kernel(const float* __restric
 // D = 64, 4 chunks 6.5 -> 4.8, 19 chunks 6.5 -> 5.0, 64 chunks 6.6 -> 5.3, 128 chunks 8.6 -> 6.0; four KV heads,
 // D = 128, 4 chunks 6.5 -> 5.2, 32 chunks 6.5 -> 5.7.
 // The line is what one compute unit reads in the time of a launch: 128 chunks, of short rows (512 bytes a chunk) 192 (two
-// KV heads, D = 64, with their mean keys: 150 chunks 11.6 -> 8.4 us, eight queries over 200 chunks 11.4 -> 9.7, but 256
-// chunks of 512 tokens 14.2 -> 14.9; rows of 2 KiB: 130 chunks 11.2 -> 12.4, 200 chunks 11.0 -> 15.4).
+// KV heads, D = 64, with their mean keys: 150 chunks 11.6 -> 8.4 us, eight queries over 200 chunks still 11.4 -> 9.7, but
+// 256 chunks of 512 tokens 14.2 -> 14.9; rows of 2 KiB: 130 chunks 11.2 -> 12.4, 200 chunks 11.0 -> 15.4).
 constexpr int kShortSteps = 2;                                // steps of a row of up to 32 pieces
 constexpr int fused_chunks(int steps) { return steps == kShortSteps ? 192 : 128; }
 
