@@ -319,6 +319,8 @@ vxl_status vxl_layout_create_windowed(int32_t n_tokens, int32_t n_prefix, int32_
         L->n_work[v] = (int32_t)work[v].size();
     }
 
+    for (const Segment& sg : L->segs) L->longest = std::max(L->longest, sg.q_len);
+
     // Items of the attention-mass score: the prefix and every chunk in even pieces of whole key tiles, at most kMassPiece
     // keys; of a prompt below 32 times that, whose items leave compute units idle, down to 512.  A workgroup walks an item
     // alone, and uneven pieces leave short ones behind: with the selection, 10 chunks of 1,000 tokens, 112 rows 23.3 ->

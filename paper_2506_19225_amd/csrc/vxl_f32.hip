@@ -36,6 +36,7 @@ namespace {
 typedef __attribute__((ext_vector_type(4))) float f32x4;
 
 constexpr int kF32Rows = 16;         // stacked query rows per block
+constexpr int kF32Band = 128;        // query tokens per entry of the pre-filling's work list
 constexpr int kDecodeKB = 2;         // blocks of 16 keys per tile of the decode
 
 // Rows of a contiguous pair of buffers: slot = row.
@@ -293,33 +294,41 @@ struct MergeF32 {
     }
 };
 
-// Pre-filling.  grid: row blocks of a full 128-token band, last one first, x bands of the work list, heaviest first, x
-// KV heads, in one dimension (folded_grid): a workgroup's walk over the keys is long against the call, so the long ones
-// begin first (bands, then row blocks from the first on, then heads 56.0 -> 51.6 us at 2,064 tokens, 8 heads on 4 KV
-// heads, D = 128; 26.0 -> 22.6 at 864; band by band, whose unused blocks come in a regular pattern, 53.2, but 54 -> 67
-// with chunks of 40 tokens).  The four waves of a workgroup share the keys of a block: loads go unhidden while few waves
-// are in flight (one wave per block from 4 blocks per compute unit on -> four waves: D = 64, 2,064 tokens 53.1 -> 31.3,
-// 20,064 tokens 876 -> 733; D = 128 92.2 -> 59.3 and 1,731 -> 1,565).  Tiles of 16 keys: a wave's share is a whole number
-// of tiles, so 32 leave more of them waiting (21.7 -> 19.9 at 1,264 tokens, D = 64; D = 128, 2,064 tokens 59.3 -> 56.1).
+// Pre-filling.  grid: bands of 128 tokens of the work list, heaviest first, x row blocks of the longest band x KV heads;
+// LONG_FIRST: row blocks x bands x heads in one dimension (folded_grid).  The four waves of a workgroup share the keys of a block: loads go unhidden while few waves
+// are in flight (one wave per block from 4 blocks per compute unit on -> four waves, 8 heads on 4 KV heads, us: D = 64,
+// 2,064 tokens 53.1 -> 31.3, 20,064 tokens 876 -> 733; D = 128 92.2 -> 59.3 and 1,731 -> 1,565).
+// LONG_FIRST, more blocks than compute units: a workgroup's walk over the keys is long against the call, so the long ones
+// begin first: the last row blocks of all bands and heads, and so on (bands, then row blocks from the first on, then
+// heads 56.0 -> 51.6 us at 2,064 tokens, D = 128; 26.0 -> 22.6 at 864); and tiles of 16 keys, since a wave's share is a
+// whole number of tiles and 32 leave more waves waiting (21.7 -> 19.9 at 1,264 tokens, D = 64; D = 128, 2,064 tokens 59.3
+// -> 56.1).  Otherwise all run at once, spread evenly in the plain order, and a tile is a round trip: 2 heads on one KV
+// head, 576 tokens, D = 64, 8.1 us against 8.5, 4 heads on two, 877 tokens 12.7 against 14.9.
+// Blocks that no band has are not launched: 2,064 tokens in chunks of 50, D = 64, 28.4 -> 22.4.
 // Matrix pipes 30 % busy at 2,064 tokens, D = 128.
-template <int D>
-__global__ __launch_bounds__(256, 3) void prefill_f32_kernel(
+template <int D, bool LONG_FIRST>
+__global__ __launch_bounds__(256, LONG_FIRST ? 3 : 2) void prefill_f32_kernel(
     const float* __restrict__ Q, const float* __restrict__ K, const float* __restrict__ V, float* __restrict__ O,
     float* __restrict__ LSE, const Segment* __restrict__ segs, const WorkItem* __restrict__ work,
-    const int32_t* __restrict__ tile_src, int n_work, int n_tokens, int n_kv_heads, int group, float scale, long long q_head,
+    const int32_t* __restrict__ tile_src, int n_work, int blocks, int n_tokens, int n_kv_heads, int group, float scale, long long q_head,
     long long q_tok, long long kv_head, long long kv_tok) {
-    constexpr int BAND = 128, KS = 4, KB = 1, TILE = 16 * KB;
+    constexpr int BAND = kF32Band, KS = 4, KB = LONG_FIRST ? 1 : 2, TILE = 16 * KB;
     __shared__ __attribute__((aligned(16))) float lds[MergeF32<D, KS>::FLOATS];
     const int lane = threadIdx.x & 63, i = lane & 15;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const unsigned blocks = BAND * group / kF32Rows, id = folded_id(), band = id / n_kv_heads % n_work, below = id / n_kv_heads / n_work;
-    if (below >= blocks) return;
-    const int g = id % n_kv_heads;
+    unsigned band = blockIdx.x, block = blockIdx.y, g = blockIdx.z;
+    if constexpr (LONG_FIRST) {
+        const unsigned id = folded_id(), at = id / n_kv_heads;
+        g = id % n_kv_heads;
+        band = at % n_work;
+        block = blocks - 1 - at / n_work;
+        if (at / n_work >= (unsigned)blocks) return;
+    }
     const WorkItem wi = work[band];
     const Segment sg = segs[wi.seg];
     const int t0 = wi.m_tile * BAND;
     const int rows_band = min(BAND, sg.q_len - t0) * group;
-    const int rho0 = (blocks - 1 - below) * kF32Rows;
+    const int rho0 = block * kF32Rows;
     if (rho0 >= rows_band) return;
     const int rho = min(rho0 + i, rows_band - 1);
     const int t = t0 + rho / group;
@@ -488,12 +497,19 @@ vxl_status launch_prefill_f32(const vxl_layout* L, const vxl_attn_desc* d, float
                               const void* V, void* O, float* LSE, hipStream_t s) {
     const int group = d->n_q_heads / d->n_kv_heads;
     const TokStrides ts = tok_strides(d, L->n_tokens);
-    const dim3 grid = folded_grid((long long)L->n_work[0] * (128 * group / kF32Rows) * d->n_kv_heads);   // (row blocks of a full band)
-#define VXL_LAUNCH(D)                                                                                           \
-    hipLaunchKernelGGL((prefill_f32_kernel<D>), grid, dim3(256), 0, s, (const float*)Q, (const float*)K, (const float*)V,  \
-                       (float*)O, LSE, L->d_segs, L->d_work[0], L->d_tile_src, L->n_work[0], L->n_tokens,                  \
+    int n_cus = 0;
+    const vxl_status st = device_cu_count(&n_cus);
+    if (st != VXL_OK) return st;
+    const int blocks = (std::min(L->longest, kF32Band) * group + kF32Rows - 1) / kF32Rows;       // of the longest band
+    const bool long_first = (long long)L->n_tokens * d->n_q_heads > (long long)kF32Rows * n_cus;
+    const dim3 grid = long_first ? folded_grid((long long)L->n_work[0] * blocks * d->n_kv_heads)
+                                 : dim3(L->n_work[0], blocks, d->n_kv_heads);
+#define VXL_LAUNCH(D, LONG_FIRST)                                                                               \
+    hipLaunchKernelGGL((prefill_f32_kernel<D, LONG_FIRST>), grid, dim3(256), 0, s, (const float*)Q, (const float*)K, (const float*)V,  \
+                       (float*)O, LSE, L->d_segs, L->d_work[0], L->d_tile_src, L->n_work[0], blocks, L->n_tokens,          \
                        d->n_kv_heads, group, scale, ts.qh, ts.qt, ts.kh, ts.kt)
-    if (d->head_dim == 64) VXL_LAUNCH(64); else VXL_LAUNCH(128);
+    if (d->head_dim == 64) { if (long_first) VXL_LAUNCH(64, true); else VXL_LAUNCH(64, false); }
+    else { if (long_first) VXL_LAUNCH(128, true); else VXL_LAUNCH(128, false); }
 #undef VXL_LAUNCH
     VXL_HIP_TRY(hipGetLastError());
     return VXL_OK;

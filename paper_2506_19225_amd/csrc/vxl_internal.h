@@ -54,6 +54,7 @@ struct MassItem {
 
 struct vxl_layout {
     int32_t n_tokens = 0, n_prefix = 0, n_chunks = 0, s_total = 0, window = 0;
+    int32_t longest = 0;                              // query tokens of the longest segment
     std::vector<int32_t> bounds, soff, sidx;          // host copies
     int device = 0;
 

@@ -15,7 +15,8 @@ pytestmark = pytest.mark.gpu
 
 @pytest.mark.parametrize("hq,hkv,d,prefix,lens,window", [
     (1, 1, 64, 0, [1, 2, 15, 16, 17], 0), (7, 1, 128, 1, [31, 32, 33, 5], 0), (6, 2, 64, 33, [127, 128, 129, 300], 40),
-    (8, 1, 128, 130, [640, 700, 641], 0), (28, 4, 64, 64, [257, 1, 511], 100)], ids=lambda x: str(x).replace(" ", ""))
+    (8, 1, 128, 130, [640, 700, 641], 0), (28, 4, 64, 64, [257, 1, 511], 100),
+    (32, 1, 64, 0, [127, 1], 0), (32, 1, 64, 0, [128, 1], 0), (32, 1, 128, 5, [15, 17, 64, 3, 40], 20)], ids=lambda x: str(x).replace(" ", ""))
 def test_prefill_f32_edges(hq, hkv, d, prefix, lens, window):
     rng = np.random.default_rng(len(lens) + d + hq)
     kept, start = [], prefix
