@@ -529,13 +529,14 @@ vxl_status launch_summaries(const vxl_layout* L, const vxl_attn_desc* d, const v
     // selection, 60 of 700 17.8 -> 14.8; but 64 of 256 10.1 -> 11.1, and 160 of 1,000, 640 blocks, 36.8 -> 41.0), eight
     // rows of a thread at once instead of four unless they are streamed (those 20 chunks 11.4 -> 10.1; 100 of 1,200,
     // streamed, 28.3 -> 28.8; 256 threads: 64 of 256 28.3 -> 28.7 with the rest of a query).
-    // Keys that the eight L2s (32 MB) do not hold are streamed past them: 164,096 tokens 45.5 -> 40.0, 34 MB 15.6
-    // -> 14.8; but 17 MB 10.1 -> 10.7.  (The choice depends on layout and descriptor alone: means that a caller keeps are
-    // those of every later call.)
+    // Keys beyond 96 MB are streamed past the caches: 164,096 tokens 45.5 -> 40.0; six layers in turn, 104 MB 28.1 -> 24.0,
+    // two 23.7 -> 23.3.  Of fewer the on-package cache holds two or three layers, which is then the faster source: 79 MB,
+    // two layers in turn 18.6 -> 19.4 (six 22.1 -> 20.1), 42 MB 13.2 -> 13.7, 17 MB 10.1 -> 10.7.
+    // (The choice depends on layout and descriptor alone: means that a caller keeps are those of every later call.)
     const long long elem = d->dtype == VXL_BF16 ? 2 : 4, row = d->head_dim * elem;
     const bool wide = row >= 256 && (long long)L->n_chunks * d->n_kv_heads <= 512 &&
                       (long long)L->n_tokens * row >= 19ll * 256 * 16 * L->n_chunks;
-    const bool once = L->n_tokens * (row * d->n_kv_heads) > (32 << 20);
+    const bool once = L->n_tokens * (row * d->n_kv_heads) > (96 << 20);
 #define VXL_LAUNCH_AS(T_, D, THREADS, NT)                                                                        \
     hipLaunchKernelGGL((chunk_summarize_kernel<T_, D, THREADS, NT>), grid, dim3(THREADS), smem, s, (const T_*)K,  \
                        L->d_bounds, kbar, ts.kh / epc, ts.kt / epc, nc, (const T_*)Qd, qbar, T, d->n_q_heads,     \
