@@ -546,7 +546,11 @@ vxl_status launch_prefill_bf16(const vxl_layout* L, const vxl_attn_desc* d, floa
         if (small && 8 * parts4 > 9 * parts8 && (own_unit ? fits(163840) : d64 && parts4 <= 4ll * n_cus && fits(81920)))
             return d64 ? run_prefill_direct<64, 4>(L, d, scale, Q, K, V, O, LSE, s, own_unit)
                        : run_prefill_direct<128, 4>(L, d, scale, Q, K, V, O, LSE, s, false);
-        if (small && parts8 <= 4ll * n_cus && fits(163840))
+        const bool shared = d64 && parts8 > n_cus && parts4 <= 4ll * n_cus && L->seg_tiles > 6ll * L->n_seg;
+        // (D = 64, chunks of three and four cells, which leave half of eight waves without rows, stay with the four-wave
+        // form below from two parts per unit on: 170 chunks of 72 tokens on four heads, 684 parts, 55.4 against 59.6, 250
+        // chunks 75.3 against 86.9; but 100 chunks, 404 parts, 36.2 against 31.2)
+        if (small && parts8 <= 4ll * n_cus && fits(163840) && !(shared && parts8 > 2ll * n_cus && parts4 > parts8 && 8 * parts4 <= 9 * parts8))
             return d64 ? run_prefill_direct<64, 8>(L, d, scale, Q, K, V, O, LSE, s, false)
                        : run_prefill_direct<128, 8>(L, d, scale, Q, K, V, O, LSE, s, false);
         // Four waves with the pre-pass, where the table does not fit: while every part has a compute unit of its own
@@ -555,7 +559,6 @@ vxl_status launch_prefill_bf16(const vxl_layout* L, const vxl_attn_desc* d, floa
         // unit, once eight waves need a second round (896 parts 51.5 -> 47.7) and with some six tiles per segment.
         const bool few_keys = parts4 * 16 > n_cus * 11ll && L->n_tokens > 96ll * L->n_seg && 4 * L->seg_tiles <= 21ll * L->n_seg;
         const bool one_round = own_unit && !few_keys;
-        const bool shared = d64 && parts8 > n_cus && parts4 <= 4ll * n_cus && L->seg_tiles > 6ll * L->n_seg;
         if (parts4 > parts8 && (one_round || shared))
             return d64 ? run_prefill_dma<64, 4, 4>(L, d, scale, Q, K, V, O, LSE, ws, s, one_round)
                        : run_prefill_dma<128, 4, 4>(L, d, scale, Q, K, V, O, LSE, ws, s);
