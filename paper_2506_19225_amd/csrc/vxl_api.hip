@@ -143,17 +143,19 @@ DecodePlan decode_plan(const vxl_attn_desc* d, int batch, int T, int l_cap, bool
         }
         // Short mixed sets: one workgroup per row block walks all keys and writes the results, without partials and without
         // the launch of their merge, up to 16 tiles (D = 64: 24) and while the row blocks are no more than the compute units.
-        // Us, splits and merge -> one workgroup, G = 7, four KV heads, D = 128: 7 rows, 251 keys 6.8 -> 5.0 and 501 keys
-        // 7.0 -> 6.9, but 641 keys 7.0 -> 8.3; 56 rows, 251 keys 11.0 -> 7.5; 8 queries of 112 rows, 501 keys 12.5 -> 10.0.
-        // D = 64: three queries of 140 rows, 761 keys 8.6 -> 7.3, but one row, 1,001 keys 5.9 -> 6.9.  In place, where a wave
-        // pays for the row map on every tile, 12 and 16.  33 to 64 rows of D = 64 go to 12 tiles only: above, this range is
-        // the one that exercises the 128-row kernel.
+        // Us in a replayed graph, splits and merge -> one workgroup, G = 7, four KV heads, D = 128: 7 rows, 251 keys 6.9 ->
+        // 5.5, 384 keys 6.9 -> 6.7, 501 keys 7.2 -> 7.8, but submitted call by call, where the second launch costs the host
+        // 3, 9.8 -> 7.5; 56 rows, 251 keys 10.9 -> 7.9, 501 keys 11.6 -> 10.2; 8 queries of 112 rows, 501 keys 13.4 -> 11.4.
+        // D = 64: 7 rows, 500 keys 6.2 -> 5.6, 700 keys 6.3 -> 6.9 (call by call 9.8 -> 7.0); three queries of 140 rows, 761
+        // keys 8.7 -> 8.4.  In place, where a wave pays for the row map on every tile, 12 and 16.  33 to 64 rows of D = 64
+        // go to 12 tiles only: above, this range is the one that exercises the 128-row kernel.
         const bool d64 = d->head_dim == 64;
         const int one = d64 && rows > kRowBlock && rows <= 64 ? 12 : gathered ? (d64 ? 24 : 16) : (d64 ? 16 : 12);
         const bool single = rows <= 256 && tiles32 <= one && units * n_rtile <= 256;
         if (rows <= kRowBlock || (fits && few) || single) {
             p.use_ring = 0;
             p.step_waves = kWaves;
+            p.one = single && tiles32 > kWaves;
             p.n_split = single ? 1 : (int)n_split;
             p.split_len = kWaves * (single ? (tiles32 + kWaves - 1) / kWaves : tpw) * kTile;
         }

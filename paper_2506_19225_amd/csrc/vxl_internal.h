@@ -187,6 +187,7 @@ struct DecodePlan {
     int split_len;      // keys per split (multiple of 64)
     int use_ring;       // step_waves == 0: 1 = the 256-row ring kernel, 0 = the 128-row 4-wave kernel
     int step_waves;     // step mode: waves per workgroup (8 single-buffered or 4 double-buffered); 0 = another kernel
+    int one;            // step mode: one workgroup walks all keys of its rows, several tiles per wave
     size_t part_o;      // byte offsets into the workspace
     size_t part_ml;
     size_t total;

@@ -230,6 +230,32 @@ __device__ __forceinline__ void softmax_tile(f32x16 (&s)[KB], float c2, float& m
     l_run += sum0 + sum1;
 }
 
+// Before softmax_tile: makes the next tile's own largest logit the reference of its row, also where that is lower than
+// the present one (by at most 2^8 below the largest logit so far, m_top, so that sums stay in the range that
+// softmax_tile keeps).  The weight of a tile's heaviest key is then exactly 1, as where every tile has a wave of its
+// own; against an older reference it is rounded like any other.  A row's error against float64 with several tiles per
+// wave, reference kept -> so: 501 keys 2.25e-3 -> 2.02e-3.
+template <int DB, int KB>
+__device__ __forceinline__ void refer_to_tile(const f32x16 (&s)[KB], float c2, float& m_top, float& m_run, float& l_run,
+                                              f32x16 (&o)[DB]) {
+    float mx = s[0][0];
+#pragma unroll
+    for (int kb = 0; kb < KB; ++kb)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) mx = fmaxf(mx, s[kb][r]);
+    mx = fmaxf(mx, __shfl_xor(mx, 32));
+    m_top = fmaxf(fmaxf(m_top, m_run), mx);
+    float m_new = fmaxf(mx, m_top - 8.f / c2);
+    if (m_new == -INFINITY) m_new = m_run;                    // (no logit that is a number, or a scale near 0)
+    const float alpha = m_new == -INFINITY ? 1.f : __builtin_amdgcn_exp2f((m_run - m_new) * c2);
+    l_run *= alpha;
+    m_run = m_new;
+#pragma unroll
+    for (int db = 0; db < DB; ++db)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) o[db][r] *= alpha;
+}
+
 // Element offset of 16-byte piece `piece` of row `row` in an UNPADDED V tile (row stride D).
 // The 64-byte chunks of a row are XOR-ed with the row's index inside a group of four 256-byte
 // lines, so the four rows a half-wave touches in one transposing read fall into distinct banks.

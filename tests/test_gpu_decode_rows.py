@@ -8,7 +8,7 @@ import torch
 import oracle
 from paper_2506_19225_amd import vxl, workloads as wl
 
-from gpu_util import assert_close, desc_of, gpu_decode, make_layout
+from gpu_util import assert_close, desc_of, gpu_decode, gpu_decode_inplace, make_layout
 from test_gpu_inplace import check_case
 
 pytestmark = pytest.mark.gpu
@@ -150,3 +150,47 @@ def test_calls_without_a_merge(hq, hkv, t, d, lens):
     vxl.bilevel_decode(desc, q, dk, dv, dl, q, None, vxl.alloc_workspace(
         vxl.workspace_bytes(vxl.OP_DECODE, None, desc, bsz, t, l_cap)))
     assert np.array_equal(vxl.to_host(q), got)
+
+
+def _rounded_tiles(qd, kmix, vmix, n, tile=32):
+    """[B, T, Hq, D] attention over the first n rows as one tile of 32 keys per wave computes it: weights relative to the
+    tile's own largest logit, rounded to bf16, everything else in float64."""
+    b, t, hq, d = qd.shape
+    g = hq // kmix.shape[1]
+    out = np.empty(qd.shape)
+    for i in range(b):
+        for h in range(hq):
+            x = qd[i, :, h].astype(np.float64) @ kmix[i, h // g, :n].astype(np.float64).T / d ** 0.5
+            top, num, den = x.max(axis=1, keepdims=True), 0.0, 0.0
+            for lo in range(0, n, tile):
+                own = x[:, lo:lo + tile].max(axis=1, keepdims=True)
+                p = wl.round_to_bf16(np.exp(x[:, lo:lo + tile] - own).astype(np.float32)).astype(np.float64)
+                num = num + np.exp(own - top) * (p @ vmix[i, h // g, lo:min(lo + tile, n)].astype(np.float64))
+                den = den + np.exp(own - top) * p.sum(axis=1, keepdims=True)
+            out[i, :, h] = num / den
+    return out
+
+
+@pytest.mark.parametrize("in_place", [False, True])
+@pytest.mark.parametrize("hq,hkv,t,bsz,d,n", [
+    (28, 4, 1, 2, 128, 384), (28, 4, 8, 1, 128, 251), (7, 1, 16, 2, 128, 380), (2, 2, 1, 4, 128, 501),
+    (14, 2, 1, 3, 64, 500), (14, 2, 20, 1, 64, 511), (4, 4, 3, 2, 64, 767), (8, 1, 8, 2, 64, 384)])
+def test_one_workgroup_is_as_precise_as_a_tile_per_wave(hq, hkv, t, bsz, d, n, in_place):
+    """Short sets that one workgroup walks, several tiles per wave: every tile's weights are rounded against the tile's
+    own maximum.  Rounded alike, two results differ by fp32 sums, which move an output to its neighbour in bf16 (2^-8)
+    in fewer than one of 2^8 elements: 2.5e-4 relative at most.  Rounded against another reference the weights differ by
+    up to 2^-8 each, the results by 1e-3 and more."""
+    rng = np.random.default_rng(n + hq)
+    w = wl.tiny_workload("bf16", hq, hkv, d, T=t, B=bsz, k=1, seed=n, value_scale=1.0)
+    qd = wl.round_to_bf16(rng.standard_normal((bsz, t, hq, d)).astype(np.float32))
+    k, v = (wl.round_to_bf16(rng.standard_normal((bsz, hkv, n, d)).astype(np.float32)) for _ in range(2))
+    if in_place:                                                   # (all queries read the same rows)
+        lay = wl.layout_from_lists(0, [n], [np.zeros(0, np.int32)])
+        k[:], v[:] = k[:1], v[:1]
+        got = gpu_decode_inplace(w, lay, qd, vxl.to_device(k[0], "bf16"), vxl.to_device(v[0], "bf16"),
+                                 np.ones((bsz, 1), np.uint8), n)[0]
+    else:
+        got = gpu_decode(w, qd, vxl.to_device(k, "bf16"), vxl.to_device(v, "bf16"),
+                         torch.full((bsz,), n, dtype=torch.int32, device="cuda"))
+    want = wl.round_to_bf16(_rounded_tiles(qd, k, v, n).astype(np.float32)).astype(np.float64)
+    assert np.linalg.norm(got - want) <= 2.5e-4 * np.linalg.norm(want)
