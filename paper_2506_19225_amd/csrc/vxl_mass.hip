@@ -153,18 +153,20 @@ __global__ __launch_bounds__(256, 4) void mass_partial_kernel(
                 }
                 return (sum[0] + sum[1]) + (sum[2] + sum[3]);
             };
-            // (a sum that is too large or not a number: the whole wave takes the maximum, so the two lanes of
-            // a row keep the same reference)
+            // (a sum that is too large or not a number; a row, both its lanes, decides for itself: the rows of a
+            // wave may belong to several queries, whose scores do not depend on one another)
             float sum = exp_sum(m_run * c2);
-            if (__builtin_amdgcn_ballot_w64(!(sum <= kMassGrow)) != 0) {
+            const uint64_t lanes = __builtin_amdgcn_ballot_w64(!(sum <= kMassGrow));
+            if (lanes != 0) {
+                const bool row_grows = (((uint32_t)lanes | (uint32_t)(lanes >> 32)) >> l32 & 1) != 0;
                 float mx = s[0][0][0];
 #pragma unroll
                 for (int kb = 0; kb < 2; ++kb)
 #pragma unroll
                     for (int r = 0; r < 16; ++r) mx = fmaxf(mx, s[0][kb][r]);
                 mx = fmaxf(mx, __shfl_xor(mx, 32));   // every tile holds at least one valid key
-                const float m_new = fmaxf(m_run, mx);
-                l_run *= __builtin_amdgcn_exp2f((m_run - m_new) * c2);
+                const float m_new = row_grows ? fmaxf(m_run, mx) : m_run;
+                l_run *= row_grows ? __builtin_amdgcn_exp2f((m_run - m_new) * c2) : 1.f;
                 m_run = m_new;
                 sum = exp_sum(m_run * c2);
             }

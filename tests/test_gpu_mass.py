@@ -169,3 +169,20 @@ def test_mass_items_in_turn_and_first_keys_far_off(hq, hkv, t, bsz, d):
     first = lay.chunk_bounds[:-1]
     k[:, first] = wl.round_to_bf16(k[:, first] * rng.choice([-30.0, 1.0, 30.0], size=len(first)).astype(np.float32)[None, :, None])
     check_mass(w, lay, wl.make_decode_queries(w), k, 5)
+
+
+@pytest.mark.parametrize("hq,hkv,t,d", [(14, 2, 1, 128), (8, 1, 3, 64), (28, 4, 5, 128)])
+def test_mass_of_a_query_does_not_depend_on_its_neighbours(hq, hkv, t, d):
+    """Queries whose rows share a wave, every other one with logits that make it raise its references (tens of octaves):
+    each query's scores are those of a call of its own, bit for bit."""
+    rng = np.random.default_rng(99 + d)
+    bsz = 6
+    w = wl.tiny_workload("bf16", hq, hkv, d, T=t, B=bsz, k=3, seed=99, value_scale=1.0)
+    lay = wl.random_layout(rng, 9, 24, 1, 400)
+    _, k, _ = wl.make_qkv(w, lay, with_q=False)
+    qd = wl.make_decode_queries(w)
+    qd[1::2] = wl.round_to_bf16(qd[1::2] * np.float32(20.0))
+    _, _, scores = check_mass(w, lay, qd, k, 3)
+    for b in range(bsz):
+        _, _, own = gpu_score_topk_mass(w, lay, qd[b:b + 1], k, 3)
+        assert np.array_equal(own[0].view(np.uint32), scores[b].view(np.uint32)), b
