@@ -26,7 +26,7 @@ namespace {
 __device__ __forceinline__ float ldf(const float* p) { return *p; }
 __device__ __forceinline__ float ldf(const uint16_t* p) { return __uint_as_float((uint32_t)(*p) << 16); }
 
-constexpr float kMassGrow = 1073741824.f;             // 2^30: a lane's sum over a tile from which the reference is raised
+constexpr float kMassGrow = 1073741824.f;             // 2^30: a lane's sum over a tile from which its row's reference is raised
 constexpr int kMassRowTile = 128;                     // stacked query rows per workgroup (4 waves x 32)
 
 // bf16, matrix cores: S^T = K.Q^T per 64-key tile, running (m, l) per query column.
@@ -34,15 +34,16 @@ constexpr int kMassRowTile = 128;                     // stacked query rows per 
 // as many issue slots as the matrix instructions take), once the keys come from L2: the row tiles
 // of one (item, KV head) are neighbours in the launch order of one XCD (workgroups go to the eight
 // XCDs in turn), so that HBM delivers a key once and not once per row tile.  An item's reference is the
-// logit of its first key; a maximum is formed only when a tile's sum says that the reference no longer
-// fits (`kMassGrow`).  The tiles come by direct loads into two stages, the next one in flight while a tile
+// largest logit of its first tile; another maximum is formed only when a tile's sum says that the reference no longer
+// fits (`kMassGrow`).  (The logit of the first key instead saves up to 1 %, 173.1 -> 171.2 us at the largest size below, but rounds the
+// exponents that count: the error against float64 grew by up to 12 %, to 2.7e-7 where first keys lie 19 octaves below.)  The tiles come by direct loads into two stages, the next one in flight while a tile
 // is worked on (through registers the compiler placed the loads behind the arithmetic), four waves per SIMD.
 // The queries of a batch score the same keys, so their rows are stacked too (eight queries of 7 rows over
 // 164,096 keys, a launch of row tiles per query 206 us, so 46; of 427 rows over 36,000 keys 167 -> 150).
 // Where a launch has enough workgroups, CHAIN, one takes several short items in turn and loads its
 // queries once.  The whole score and selection, loads behind the arithmetic -> so, us: 448 rows x 4 heads
-// over 131,328 keys in 256 chunks 91.7 -> 79.6; 896 rows over 164,096 keys in 640 chunks 217 -> 171 (an item
-// per workgroup 186); 56 rows over 131,328 keys 42.9 -> 34.8; 7 rows over 164,096 keys 48.3 -> 40.2.
+// over 131,328 keys in 256 chunks 91.7 -> 80.0; 896 rows over 164,096 keys in 640 chunks 217 -> 173 (an item
+// per workgroup 186); 56 rows over 131,328 keys 42.9 -> 34.9; 7 rows over 164,096 keys 48.3 -> 40.2.
 // Two row blocks per wave (half the operand reads, three waves per SIMD): 79.9 and 182, and slower on
 // small calls; a third stage at three waves per SIMD 85 and 204.
 template <int D, bool CHAIN, bool ONCE>
@@ -137,8 +138,15 @@ __global__ __launch_bounds__(256, 4) void mass_partial_kernel(
                     for (int r = 0; r < 16; ++r)
                         s[0][kb][r] = acc_key(kb, r, hi) <= lim ? s[0][kb][r] : -INFINITY;
             }
-            // the reference of an item is the logit of its first key, for both lanes of a row
-            if (key0 == k_lo) { m_run = __shfl(s[0][0][0], l32); l_run = 0.f; }
+            auto row_max = [&]() __attribute__((always_inline)) {     // (every tile holds at least one valid key)
+                float mx = s[0][0][0];
+#pragma unroll
+                for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) mx = fmaxf(mx, s[0][kb][r]);
+                return fmaxf(mx, __shfl_xor(mx, 32));
+            };
+            if (key0 == k_lo) { m_run = row_max(); l_run = 0.f; }
             auto exp_sum = [&](float mc) __attribute__((always_inline)) {
                 float sum[4];
 #pragma unroll
@@ -159,12 +167,7 @@ __global__ __launch_bounds__(256, 4) void mass_partial_kernel(
             const uint64_t lanes = __builtin_amdgcn_ballot_w64(!(sum <= kMassGrow));
             if (lanes != 0) {
                 const bool row_grows = (((uint32_t)lanes | (uint32_t)(lanes >> 32)) >> l32 & 1) != 0;
-                float mx = s[0][0][0];
-#pragma unroll
-                for (int kb = 0; kb < 2; ++kb)
-#pragma unroll
-                    for (int r = 0; r < 16; ++r) mx = fmaxf(mx, s[0][kb][r]);
-                mx = fmaxf(mx, __shfl_xor(mx, 32));   // every tile holds at least one valid key
+                const float mx = row_max();
                 const float m_new = row_grows ? fmaxf(m_run, mx) : m_run;
                 l_run *= row_grows ? __builtin_amdgcn_exp2f((m_run - m_new) * c2) : 1.f;
                 m_run = m_new;

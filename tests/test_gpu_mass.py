@@ -186,3 +186,23 @@ def test_mass_of_a_query_does_not_depend_on_its_neighbours(hq, hkv, t, d):
     for b in range(bsz):
         _, _, own = gpu_score_topk_mass(w, lay, qd[b:b + 1], k, 3)
         assert np.array_equal(own[0].view(np.uint32), scores[b].view(np.uint32)), b
+
+
+@pytest.mark.parametrize("hq,t", [(1, 1), (1, 40)])
+def test_mass_error_where_first_keys_lie_far_below(hq, t):
+    """Chunks of a few keys whose first logit lies 19 octaves below the others, logits exact in fp32: against the largest
+    logit of a tile the exponents that count are near 0 and exact, and the rest is some eight roundings of 2^-24 (the
+    exponentials of a key, of its item and of its row, and the products), 1.7e-7 in root mean square.  An exponent
+    of 19 is rounded by up to 2^-20, 3.8e-7 of the value in root mean square."""
+    rng = np.random.default_rng(55 + t)
+    lens = rng.integers(2, 6, size=200)
+    w = wl.tiny_workload("bf16", hq, 1, 64, T=t, B=2, k=3, seed=55)
+    lay = wl.layout_from_lists(0, lens.tolist(), [np.zeros(0, np.int32)] * len(lens))
+    k = np.zeros((1, lay.n_tokens, 64), np.float32)
+    k[0, :, 0] = rng.integers(208, 224, size=lay.n_tokens) / 16.0                  # exact in bf16: 13 to 14
+    k[0, lay.chunk_bounds[:-1], 0] = 0.0
+    qd = np.zeros((2, t, hq, 64), np.float32)
+    qd[..., 0] = 1.0
+    _, _, scores = check_mass(w, lay, qd, k, 3, scale=1.0)
+    want = oracle.chunk_scores_mass(qd, k, 0, lay.chunk_bounds, scale=1.0)
+    assert np.sqrt((((scores - want) / want) ** 2).mean()) <= 1.7e-7
