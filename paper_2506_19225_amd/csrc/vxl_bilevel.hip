@@ -396,11 +396,16 @@ __global__ __launch_bounds__(256, 8) void pool_sparse_kernel(const T* __restrict
 // eight waves per SIMD; FOUR (exactly four KV heads): the pieces of all heads are requested before the first store, at
 // four waves per SIMD (the line is at launch_gather).  835 MB in and out, eight mixed sets of 25k rows: 158 us one head
 // after the other, 140 us (6.0 TB/s) at four heads together; with eight waves per SIMD 148.
-// ONCE: the mixed rows are stored past the caches and the queries of a batch take turns (block id = block of the
-// query * batch + query), so that K and V stay in the on-package cache for all of them (the line is at launch_gather).
+// ONCE, buffers that could exceed the on-package cache: the queries of a batch take turns (block id = block of the query *
+// batch + query), so that K and V stay in that cache for all of them, and a query whose rows, times the batch, are more
+// than kPastCaches stores them past it (the line is at launch_gather).  By its rows, since the host knows the capacity
+// only: with the decode, rows stored past the cache by capacity -> so, eight sets of 5,344 rows in buffers for 30,000
+// 87.9 -> 75.5 us, of 8,320 rows 128.1 -> 109.0, one of 36,096 in 100,000 64.7 -> 57.5; full sets unchanged.
 // With Kmix == nullptr nothing is copied at all: the call only writes mix_len and src_idx (the row
 // map the in-place decode reads the dense and sparse rows through).
 // ------------------------------------------------------------------------------------------
+constexpr long long kPastCaches = 160ll << 20;
+
 template <int ROW_BYTES, bool FOUR, bool ONCE>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(FOUR ? 4 : 8, FOUR ? 4 : 8))) void gather_kernel(
     const uint4* __restrict__ K, const uint4* __restrict__ V, const uint8_t* __restrict__ dense_mask,
@@ -462,6 +467,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(FOUR ? 4 : 
     // a mixed set that does not fit l_cap is reported, not truncated: minus the rows it needs
     if (block == 0 && tid == 0) mix_len[b] = len <= l_cap ? len : -len;
     if (len > l_cap) return;
+    const bool past = ONCE && 2ll * batch * n_kv_heads * len * ROW_BYTES > kPastCaches;
     const int part = tid % LPR;
     for (int gi = 0; gi < groups; ++gi) {
         const int r = (block * groups + gi) * ROWS + tid / LPR;
@@ -498,17 +504,23 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(FOUR ? 4 : 
                 kq[g] = ks[s_off + g * head_u4];
                 vq[g] = vs[s_off + g * head_u4];
             }
+            auto store = [&](auto nt) __attribute__((always_inline)) {
 #pragma unroll
-            for (int g = 0; g < 4; ++g) {
-                store16<ONCE>(Kmix + d_off + g * d_head, kq[g]);
-                store16<ONCE>(Vmix + d_off + g * d_head, vq[g]);
-            }
+                for (int g = 0; g < 4; ++g) {
+                    store16<nt>(Kmix + d_off + g * d_head, kq[g]);
+                    store16<nt>(Vmix + d_off + g * d_head, vq[g]);
+                }
+            };
+            if (past) store(std::true_type{}); else store(std::false_type{});
         } else {
-            for (int g = 0; g < n_kv_heads; ++g) {
-                const uint4 kq = ks[s_off + g * head_u4], vq = vs[s_off + g * head_u4];
-                store16<ONCE>(Kmix + d_off + g * d_head, kq);
-                store16<ONCE>(Vmix + d_off + g * d_head, vq);
-            }
+            auto copy = [&](auto nt) __attribute__((always_inline)) {
+                for (int g = 0; g < n_kv_heads; ++g) {
+                    const uint4 kq = ks[s_off + g * head_u4], vq = vs[s_off + g * head_u4];
+                    store16<nt>(Kmix + d_off + g * d_head, kq);
+                    store16<nt>(Vmix + d_off + g * d_head, vq);
+                }
+            };
+            if (past) copy(std::true_type{}); else copy(std::false_type{});
         }
     }
 }
@@ -634,11 +646,12 @@ vxl_status launch_gather(const vxl_layout* L, const vxl_attn_desc* d, const void
     // at worst (20 to 50 MB of mixed rows in HBM) 13.4 -> 13.8 and, D = 64, 12.9 -> 13.7.  Other head counts in
     // groups of four lose up to 18 %: eight heads, D = 128, 987 MB 347 -> 377; sixteen, D = 64, 1,958 MB 602 -> 725.
     const bool four = Kmix && d->n_kv_heads == 4;
-    // Mixed sets that would push K and V out of the 256 MB of the on-package cache go past it, queries in turn.  With the
+    // Mixed sets that would push K and V out of the 256 MB of the on-package cache go past it, queries in turn (here by the
+    // capacity, in the kernel by the rows).  With the
     // decode behind it, us: eight queries of 388 MB over 131,328 tokens 228 -> 200, of 344 MB 182 -> 175, of 418 MB on a
     // ragged prompt 250 -> 246; three of 190 MB 119.7 -> 118; one of 336 MB 206 -> 203; but three of 146 MB 103.8 -> 106,
     // one of 134 MB 86 -> 91 (the decode then reads the mixed rows from that cache).
-    const bool once = Kmix && 2ll * batch * d->n_kv_heads * l_cap * row_bytes > (160ll << 20);
+    const bool once = Kmix && 2ll * batch * d->n_kv_heads * l_cap * row_bytes > kPastCaches;
     const TokStrides ts = tok_strides(d, L->n_tokens);
     const long long epc = d->dtype == VXL_BF16 ? 8 : 4;
 #define VXL_LAUNCH_AS(RB, FOUR, ONCE)                                                              \

@@ -10,7 +10,7 @@ import torch
 import oracle
 from paper_2506_19225_amd import vxl, workloads as wl
 
-from gpu_util import assert_close, desc_of, gpu_decode, make_layout, storage_round
+from gpu_util import assert_close, desc_of, gpu_decode, gpu_gather, make_layout, storage_round
 
 pytestmark = pytest.mark.gpu
 
@@ -242,3 +242,28 @@ def test_pooled_gather_without_sparse_rows_and_all_dense():
     torch.cuda.synchronize()
     assert int(mix_len[0]) == 44
     assert np.array_equal(vxl.to_host(kmix)[0, :, :44], k[:, :44])
+
+
+@pytest.mark.parametrize("dtype,d,n_kv_heads", [("f32", 64, 1), ("bf16", 64, 2), ("bf16", 128, 3), ("bf16", 128, 4)])
+def test_gather_past_the_caches_goes_by_rows(dtype, d, n_kv_heads):
+    """Buffers from 160 MB on: a query that fills its own goes past the caches, one of few rows beside it does not."""
+    row, n_q = n_kv_heads * d * (4 if dtype == "f32" else 2), 6
+    l_cap = (160 << 20) // (2 * n_q * row) + 40
+    lens = np.full(40, (l_cap - 39) // 40)
+    lens[-1] += l_cap - 7 - int(lens.sum())
+    kept = [s + np.arange(3, dtype=np.int32) for s in 7 + np.concatenate([[0], np.cumsum(lens)[:-1]])]
+    w = wl.tiny_workload(dtype, n_kv_heads, n_kv_heads, d, T=1, B=n_q, k=2, seed=97)
+    lay = wl.layout_from_lists(7, lens.tolist(), kept)
+    rng = np.random.default_rng(97)
+    shape = (n_kv_heads, lay.n_tokens, d)
+    k, v = (wl.round_to_bf16(rng.random(shape, dtype=np.float32)) for _ in range(2))
+    masks = np.ones((n_q, 40), np.uint8)
+    masks[1::2] = rng.random((n_q // 2, 40)) < 0.3
+    kmix, vmix, mix_len, _ = gpu_gather(w, lay, k, v, masks, l_cap)
+    for b in range(n_q):
+        src = oracle.mixed_source_index(masks[b], lay.n_prefix, lay.chunk_bounds, lay.sparse_offsets, lay.sparse_idx)
+        n = len(src)
+        assert int(mix_len[b]) == n and (2 * n_q * n * row > 160 << 20) == (b % 2 == 0)
+        hk, hv = vxl.to_host(kmix[b]), vxl.to_host(vmix[b])
+        assert np.array_equal(hk[:, :n], k[:, src]) and np.array_equal(hv[:, :n], v[:, src])
+        assert (hk[:, n:] == 7.0).all() and (hv[:, n:] == 7.0).all()
