@@ -255,6 +255,11 @@ vxl_status vxl_gather_bilevel_kv_pooled(const vxl_layout* layout, const vxl_attn
  *            [batch, n_q_tokens, n_q_heads] or NULL
  *   mix_len  device int32 [batch]; entries above l_cap are read as l_cap, entries <= 0 (an empty
  *            set, or the overflow report of vxl_gather_bilevel_kv) give O = 0 and LSE = -inf
+ *   l_cap    rows that the buffers hold per query.  The lengths are on the device, so l_cap and not they chooses the
+ *            kernel, the number of key splits and whether rows are read past the caches (buffers of more than 32 MB):
+ *            vxl_mixed_kv_capacity gives the value to pass.  Sets far shorter than l_cap give the same results more
+ *            slowly than buffers of their own size would (one token over 4,000 rows of 40,000: 5 %; VXL_F32, 40 rows
+ *            of 5,000: a second launch, which a NULL workspace avoids)
  *   workspace  VXL_F32: may be NULL, misaligned or too small; the call then cuts no keys, which is slower for long
  *            sets and sums in another order (the same result within the tolerance of the path)
  */

@@ -520,6 +520,8 @@ vxl_status launch_prefill_f32(const vxl_layout* L, const vxl_attn_desc* d, float
 // sets stay with one workgroup per row block and no second launch; us with the gather, one workgroup -> splits,
 // D = 64: 16 rows, 512 keys 15.5 -> 16.2, 768 keys 18.6 -> 16.4; 16 rows x 4 heads, 2,064 keys 39.4 -> 16.3.  D = 128:
 // 256 keys 15.7 -> 16.3, 352 keys 20.1 -> 16.2, 16 rows x 4 heads, 2,064 keys 65.7 -> 18.4, 11,300 keys 297 -> 35.6.
+// By the capacity, which is what the host knows: 40 keys in buffers for 5,000 pay for the second launch (6.1 -> 9.4, D =
+// 128 6.6 -> 10.6, call by call) unless the caller gives no workspace.
 DecodePlan decode_f32_plan(const vxl_attn_desc* d, int batch, int T, int l_cap) {
     DecodePlan p{};
     const long long rows = (long long)(d->n_q_heads / d->n_kv_heads) * T, units = (long long)batch * d->n_kv_heads;
