@@ -405,6 +405,11 @@ __global__ __launch_bounds__(256, 8) void pool_sparse_kernel(const T* __restrict
 // map the in-place decode reads the dense and sparse rows through).
 // ------------------------------------------------------------------------------------------
 constexpr long long kPastCaches = 160ll << 20;
+// Chunks up to which a block keeps where a chunk's rows come from in LDS beside the offsets: more would leave room for
+// fewer than the eight blocks per compute unit that the heads one after the other run at (FOUR, at four, always does).
+// Beyond, a row asks memory for it.  Eight queries, one head, 3,000 chunks of 40 tokens 55.0 -> 42.3 us, three, two heads
+// of D = 64, 4,096 of 40, 2,000 dense 74.9 -> 56.7; one query, one head, 4,096 of 32 22.3 -> 23.0.
+constexpr int kTableChunks = 2500;
 
 template <int ROW_BYTES, bool FOUR, bool ONCE>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(FOUR ? 4 : 8, FOUR ? 4 : 8))) void gather_kernel(
@@ -416,8 +421,10 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(FOUR ? 4 : 
     const uint4* __restrict__ Ksp, const uint4* __restrict__ Vsp, int s_total, int batch) {
     constexpr int LPR = ROW_BYTES / 16;                       // lanes per row
     constexpr int ROWS = 256 / LPR;                           // rows per pass
-    extern __shared__ int off[];                              // [n_chunks] first mixed row of every chunk, then [n_chunks]
-    int* from = off + n_chunks;                               // its first token, or -1 - its first kept row
+    extern __shared__ int off[];                              // [n_chunks] first mixed row of every chunk, top bit: dense; then
+    int* from = off + n_chunks;                               // (table) [n_chunks] its first token, or -1 - its first kept row
+    const bool table = FOUR || n_chunks <= kTableChunks;
+    constexpr int DENSE = INT32_MIN;
     __shared__ int wave_tot[4][4];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int b = ONCE ? blockIdx.x % batch : blockIdx.y, block = ONCE ? blockIdx.x / batch : blockIdx.x;
@@ -426,16 +433,17 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(FOUR ? 4 : 
     // The rows every chunk contributes, four 256-chunk passes at a time: their loads are all requested before the
     // first scan and do not wait for the mask (one memory round trip and one barrier per 1,024 chunks).
     for (int base4 = 0; base4 < n_chunks; base4 += 1024) {
-        int rows[4], inc[4];
+        int rows[4], inc[4], flag[4];
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
             const int c = base4 + u * 256 + tid;
-            rows[u] = 0;
+            rows[u] = flag[u] = 0;
             if (c < n_chunks) {
                 const int lo = bounds[c], hi = bounds[c + 1], s_lo = soff[c], s_hi = soff[c + 1];
                 const bool dense = mask[c] != 0;
                 rows[u] = dense ? hi - lo : s_hi - s_lo;
-                from[c] = dense ? lo : -1 - s_lo;
+                flag[u] = dense ? DENSE : 0;
+                if (table) from[c] = dense ? lo : -1 - s_lo;
             }
         }
 #pragma unroll
@@ -460,7 +468,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(FOUR ? 4 : 
                 before += w < wave ? t : 0;
                 len += t;
             }
-            if (c < n_chunks) off[c] = before + inc[u] - rows[u];
+            if (c < n_chunks) off[c] = (before + inc[u] - rows[u]) | flag[u];
         }
         __syncthreads();                                      // off is there; wave_tot may be written again
     }
@@ -479,12 +487,13 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(FOUR ? 4 : 
             int c = 0;                                        // last chunk with off[c] <= r: it lies in [c, c + span)
             for (int span = n_chunks; span > 1;) {
                 const int step = (span + LPR - 1) / LPR;
-                const unsigned long long hit = __ballot(part * step < span && off[min(c + part * step, n_chunks - 1)] <= r);
+                const unsigned long long hit = __ballot(part * step < span && (off[min(c + part * step, n_chunks - 1)] & ~DENSE) <= r);
                 const int last = __popcll((hit >> (lane & ~(LPR - 1))) & ((1ull << LPR) - 1)) - 1;
                 c += last * step;
                 span = min(step, span - last * step);
             }
-            const int first = from[c], o = r - off[c];
+            const int at = off[c], o = r - (at & ~DENSE);
+            const int first = table ? from[c] : at < 0 ? bounds[c] : -1 - soff[c];
             if (first >= 0) src = first + o;
             else src = Ksp ? first - o : sidx[-1 - first + o];
         }
@@ -638,7 +647,6 @@ vxl_status launch_gather(const vxl_layout* L, const vxl_attn_desc* d, const void
                          const void* Ksp, const void* Vsp, const uint8_t* dense_mask, int batch, void* Kmix,
                          void* Vmix, int l_cap, int32_t* mix_len, int32_t* src_idx, hipStream_t s) {
     const int row_bytes = d->head_dim * (d->dtype == VXL_BF16 ? 2 : 4);
-    const size_t smem = (size_t)L->n_chunks * 2 * sizeof(int);
     // Exactly four heads go together: one head after the other waits for its own loads four times, which small calls
     // spend most of their time on, and it keeps fewer bytes in flight.  Over 96 sizes of one to eight queries with
     // buffers in turn 1.05x, with the same buffers every time 1.01x.  One head after the other -> together, us:
@@ -646,6 +654,7 @@ vxl_status launch_gather(const vxl_layout* L, const vxl_attn_desc* d, const void
     // at worst (20 to 50 MB of mixed rows in HBM) 13.4 -> 13.8 and, D = 64, 12.9 -> 13.7.  Other head counts in
     // groups of four lose up to 18 %: eight heads, D = 128, 987 MB 347 -> 377; sixteen, D = 64, 1,958 MB 602 -> 725.
     const bool four = Kmix && d->n_kv_heads == 4;
+    const size_t smem = (size_t)L->n_chunks * (four || L->n_chunks <= kTableChunks ? 2 : 1) * sizeof(int);
     // Mixed sets that would push K and V out of the 256 MB of the on-package cache go past it, queries in turn (here by the
     // capacity, in the kernel by the rows).  With the
     // decode behind it, us: eight queries of 388 MB over 131,328 tokens 228 -> 200, of 344 MB 182 -> 175, of 418 MB on a

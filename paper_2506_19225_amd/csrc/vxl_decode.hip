@@ -850,7 +850,7 @@ __global__ __launch_bounds__(256) void decode_merge_kernel(const float* __restri
 // caches: 8 queries of 7 rows over 54 MB of mixed rows 28.0 -> 25.9 us, over 1.1 GB 227 -> 206, of 224 rows over 580 MB,
 // gather included, 265 -> 255; but 8 MB, which the next call finds there, 8.0 -> 8.6, and 8 MB of rows in buffers for 80
 // 11.3 -> 12.0.  (By the rows, decided in the kernel: those 11.8, but full sets 54.3 -> 55.3 and, a token of eight
-// layers over 50,000 rows, 26.1 -> 26.9 a layer.)
+// layers over 61,440 rows, 26.1 -> 26.9 a layer.)
 static bool beyond_l2(const vxl_attn_desc* d, int batch, int l_cap) {
     return 4ll * batch * d->n_kv_heads * l_cap * d->head_dim > (32 << 20);
 }

@@ -10,7 +10,7 @@ import torch
 import oracle
 from paper_2506_19225_amd import vxl, workloads as wl
 
-from gpu_util import assert_close, desc_of, gpu_decode, gpu_gather, make_layout, storage_round
+from gpu_util import assert_close, desc_of, gpu_decode, gpu_gather, kept_rows, make_layout, storage_round
 
 pytestmark = pytest.mark.gpu
 
@@ -267,3 +267,44 @@ def test_gather_past_the_caches_goes_by_rows(dtype, d, n_kv_heads):
         hk, hv = vxl.to_host(kmix[b]), vxl.to_host(vmix[b])
         assert np.array_equal(hk[:, :n], k[:, src]) and np.array_equal(hv[:, :n], v[:, src])
         assert (hk[:, n:] == 7.0).all() and (hv[:, n:] == 7.0).all()
+
+
+@pytest.mark.parametrize("pooled", [False, True])
+@pytest.mark.parametrize("n_kv_heads,d", [(1, 128), (3, 64), (4, 64)])
+@pytest.mark.parametrize("n_chunks", [2499, 2500, 2501, 4096])
+def test_gather_on_both_sides_of_the_chunk_table(n_chunks, n_kv_heads, d, pooled):
+    """Where the source of a chunk's rows is kept beside the offsets, and where it is asked for (other head counts than
+    four, more than 2,500 chunks): rows, lengths and the row map bit for bit, chunks without kept rows among them."""
+    rng = np.random.default_rng(n_chunks + d)
+    w = wl.tiny_workload("bf16", n_kv_heads, n_kv_heads, d, T=1, B=3, k=2, seed=98)
+    lens = rng.integers(1, 5, size=n_chunks)
+    starts = 11 + np.concatenate([[0], np.cumsum(lens)[:-1]])
+    lay = wl.layout_from_lists(11, lens.tolist(), [s + np.arange(n // 2, dtype=np.int32) for s, n in zip(starts, lens)])
+    _, k, v = wl.make_qkv(w, lay, with_q=False)
+    masks = (rng.random((3, n_chunks)) < np.array([0.0, 0.4, 1.0])[:, None]).astype(np.uint8)
+    l_cap = lay.n_tokens
+    if not pooled:
+        kmix, vmix, mix_len, src_idx = gpu_gather(w, lay, k, v, masks, l_cap)
+        ksp, vsp = (kept_rows(x, lay) for x in (k, v))
+    else:
+        dev = [vxl.to_device(x, "bf16") for x in (k, v)]
+        gl, desc = make_layout(lay), desc_of(w)
+        ksp, vsp = (wl.round_to_bf16(rng.standard_normal((n_kv_heads, len(lay.sparse_idx), d)).astype(np.float32)) for _ in range(2))
+        kmix = torch.full((3, n_kv_heads, l_cap, d), 7.0, dtype=torch.bfloat16, device="cuda")
+        vmix, mix_len = torch.full_like(kmix, 7.0), torch.zeros((3,), dtype=torch.int32, device="cuda")
+        src_idx = torch.full((3, l_cap), -5, dtype=torch.int32, device="cuda")
+        vxl.gather_bilevel_kv_pooled(gl, desc, *dev, vxl.to_device(ksp, "bf16"), vxl.to_device(vsp, "bf16"),
+                                     torch.from_numpy(masks).cuda(), kmix, vmix, mix_len, src_idx)
+    for b in range(3):
+        src, sparse = [np.arange(11)], [np.full(11, -1)]            # token of every row; its kept row, or -1
+        for c in range(n_chunks):
+            lo, hi = lay.sparse_offsets[c], lay.sparse_offsets[c + 1]
+            src.append(np.arange(lay.chunk_bounds[c], lay.chunk_bounds[c + 1]) if masks[b, c] else lay.sparse_idx[lo:hi])
+            sparse.append(np.full(lens[c], -1) if masks[b, c] else np.arange(lo, hi))
+        src, sparse = np.concatenate(src), np.concatenate(sparse)
+        n = len(src)
+        assert int(mix_len[b]) == n
+        assert np.array_equal(src_idx[b, :n].cpu().numpy(), np.where(sparse >= 0, -1 - sparse, src) if pooled else src)
+        for got, x, xs in ((kmix, k, ksp), (vmix, v, vsp)):
+            want = np.where((sparse >= 0)[None, :, None], xs[:, np.maximum(sparse, 0)], x[:, src]) if pooled else x[:, src]
+            assert np.array_equal(vxl.to_host(got[b])[:, :n], want) and (vxl.to_host(got[b])[:, n:] == 7.0).all()
