@@ -321,7 +321,10 @@ vxl_status vxl_layout_create_windowed(int32_t n_tokens, int32_t n_prefix, int32_
         L->n_work[v] = (int32_t)work[v].size();
     }
 
-    for (const Segment& sg : L->segs) L->longest = std::max(L->longest, sg.q_len);
+    for (int s = 0; s < L->n_seg; ++s) {
+        L->longest = std::max(L->longest, L->segs[s].q_len);
+        if (s > 0 || n_prefix == 0) L->longest_chunk = std::max(L->longest_chunk, L->segs[s].q_len);
+    }
 
     // Items of the attention-mass score: the prefix and every chunk in even pieces of whole key tiles, at most kMassPiece
     // keys; of a prompt below 32 times that, whose items leave compute units idle, down to 512.  A workgroup walks an item

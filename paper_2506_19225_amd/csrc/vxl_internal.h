@@ -54,7 +54,7 @@ struct MassItem {
 
 struct vxl_layout {
     int32_t n_tokens = 0, n_prefix = 0, n_chunks = 0, s_total = 0, window = 0;
-    int32_t longest = 0;                              // query tokens of the longest segment
+    int32_t longest = 0, longest_chunk = 0;           // query tokens of the longest segment, of the longest chunk
     std::vector<int32_t> bounds, soff, sidx;          // host copies
     int device = 0;
 

@@ -97,7 +97,7 @@ __global__ __launch_bounds__(NW * 64, 2) void prefill_dma_kernel(
     float* __restrict__ LSE, const Segment* __restrict__ segs, const WorkItem* __restrict__ work,
     int n_tokens, int n_q_heads, int group, int ctx_rows_pad, float scale, int n_items, int xpg,
     int* __restrict__ queue, long long q_head_arg, int q_tok_arg, long long kv_head_arg, int kv_tok_arg,
-    const int32_t* __restrict__ hist_src, int n_prefix) {      // (DIRECT: source token of every history row)
+    const int32_t* __restrict__ hist_src, int n_prefix, int places_arg, int extra) {      // DIRECT: source token of every history row; PartPlaces
     using C = PrefillDmaCfg<D, NS, NW>;
     constexpr bool DIRECT = TAKE == kDirect, LATE = TAKE == kLate;
     // Element strides of Q/O and K/V rows: the arguments, or (STRIDED false, the dense head-major
@@ -114,7 +114,10 @@ __global__ __launch_bounds__(NW * 64, 2) void prefill_dma_kernel(
     const int tid = threadIdx.x, lane = tid & 63, l32 = lane & 31, hi = lane >> 5;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int qid = xpg > 0 ? (int)(blockIdx.x & 7) / xpg : 0;            // this workgroup's queue
-    const int q_len_items = xpg > 0 ? n_items * group : n_items * n_q_heads;
+    // parts of an item (and of all its KV heads where they share a queue) that the launch has places for
+    const int places = DIRECT ? places_arg : group, all_places = DIRECT ? n_q_heads / group * places : n_q_heads;
+    const int listed = xpg > 0 ? n_items * places : n_items * all_places;
+    const int q_len_items = DIRECT ? listed + (n_prefix + C::BM - 1) / C::BM * extra * (xpg > 0 ? 1 : n_q_heads / group) : listed;
     const float c2 = scale * kLog2e;
     const int r_in = lane / C::PPR, pp = lane % C::PPR;
 
@@ -144,11 +147,12 @@ __global__ __launch_bounds__(NW * 64, 2) void prefill_dma_kernel(
     }
     // The descriptors of an item (two dependent scalar loads) are fetched while the item before it
     // runs, as soon as its index is known.
-    auto item_of = [&](int jj) { return xpg > 0 ? jj / group : jj / n_q_heads; };
+    auto item_of = [&](int jj) { return xpg > 0 ? jj / places : jj / all_places; };
     WorkItem wi_next = {0, 0};
     Segment sg_next = {0, 0, 0, 0, 0};
     if (j < q_len_items) {
-        wi_next = work[item_of(j)];
+        if (DIRECT && j >= listed) wi_next = {0, (j - listed) / (xpg > 0 ? extra : n_q_heads / group * extra)};
+        else wi_next = work[item_of(j)];
         sg_next = segs[wi_next.seg];
     }
   for (int par = 1; j < q_len_items; par ^= 1) {
@@ -159,10 +163,17 @@ __global__ __launch_bounds__(NW * 64, 2) void prefill_dma_kernel(
     // the cells of a ragged last band fill as few parts as possible: cut head by head, every
     // part of such a band would run with most of its waves idle (variable chunk lengths: +11 %).
     // Parts left without cells walk one tile and write nothing.
-    const int part_id = xpg > 0 ? qid * group + j % group : j % n_q_heads;
-    const int g = part_id / group;                            // KV head
-    int part = part_id - g * group;
-    if (DIRECT) part = (part + item_of(j)) % group;           // (in turn over the XCDs: a part's place decides its length)
+    const int part_id = xpg > 0 ? qid * places + j % places : j % all_places;
+    int g = part_id / places;                                 // KV head
+    int part = part_id - g * places;
+    if (DIRECT) {
+        if (j < listed) {
+            part = (part + item_of(j)) % places;              // (in turn over the XCDs: a part's place decides its length)
+        } else {
+            g = xpg > 0 ? qid : (j - listed) / extra % (n_q_heads / group);
+            part = places + (j - listed) % extra;
+        }
+    }
     const WorkItem wi = wi_next;
     const Segment sg = sg_next;
     const int m0 = wi.m_tile * C::BM;
@@ -443,12 +454,24 @@ static vxl_status run_prefill_dma(const vxl_layout* L, const vxl_attn_desc* d, f
                        C::LDS_BYTES, s, (const uint16_t*)Q, (const uint16_t*)K, (const uint16_t*)V, kctx,  \
                        vctx, (uint16_t*)O, LSE, L->d_segs, L->d_work[wl_i], L->n_tokens, d->n_q_heads,     \
                        group, n_rows_pad, scale, L->n_work[wl_i], xpg, queue, ts.qh, (int)ts.qt, ts.kh,    \
-                       (int)ts.kt, nullptr, 0)
+                       (int)ts.kt, nullptr, 0, 0, 0)
     if (dense_layout(d)) VXL_LAUNCH(false); else VXL_LAUNCH(true);
 #undef VXL_LAUNCH
     VXL_HIP_TRY(hipGetLastError());
     if (timed) VXL_HIP_TRY(hipEventRecord(ev_stop, s));
     return VXL_OK;
+}
+
+// Parts of `waves` cells per item and KV head that a launch of kDirect has places for: those of the longest band of a
+// chunk, and behind all of them the others (`extra`) of the prefix's bands.  A workgroup that finds no cells ends at once,
+// but the next ones have gone to other compute units by then: with places for a whole band's parts, a few units got all the
+// parts of short chunks (eight waves, 250 chunks of 40 tokens, D = 64, four heads on two 50.7 -> 27.5 us, D = 128, four on
+// one 105.1 -> 41.3).
+struct PartPlaces { int places, extra; };
+static PartPlaces direct_places(const vxl_layout* L, int group, int waves) {
+    auto parts = [&](int tokens) { return (std::min((tokens + 31) / 32, waves) * group + waves - 1) / waves; };
+    const int of_chunks = L->longest_chunk > 0 ? parts(L->longest_chunk) : parts(L->n_prefix);
+    return {of_chunks, std::max(0, parts(L->n_prefix) - of_chunks)};
 }
 
 // The instances without a pre-pass: `spread` keeps two workgroups of D = 64 off one compute unit by their LDS.
@@ -471,7 +494,9 @@ static vxl_status run_prefill_direct(const vxl_layout* L, const vxl_attn_desc* d
     const int group = d->n_q_heads / d->n_kv_heads;
     const int xpg = 8 % d->n_kv_heads == 0 ? 8 / d->n_kv_heads : 0;
     constexpr int wl_i = NW == 8 ? 1 : 0;
-    const long long per_queue = (long long)L->n_work[wl_i] * (xpg ? group : d->n_q_heads);
+    const PartPlaces p = direct_places(L, group, NW);
+    const long long per_queue = ((long long)L->n_work[wl_i] * p.places + (long long)(L->n_prefix + C::BM - 1) / C::BM * p.extra) *
+                                (xpg ? 1 : d->n_kv_heads);
     const unsigned n_blocks = (unsigned)(xpg ? (per_queue + xpg - 1) / xpg * 8 : per_queue);
     const int lds = std::max(spread ? kMaxLds / 2 + 16 : 0, C::LDS_BYTES + L->s_total * 4);
 #define VXL_LAUNCH(STRIDED_)                                                                             \
@@ -479,7 +504,7 @@ static vxl_status run_prefill_direct(const vxl_layout* L, const vxl_attn_desc* d
                        (const uint16_t*)Q, (const uint16_t*)K, (const uint16_t*)V, nullptr, nullptr,     \
                        (uint16_t*)O, LSE, L->d_segs, L->d_work[wl_i], L->n_tokens, d->n_q_heads, group, 0, \
                        scale, L->n_work[wl_i], xpg, nullptr, ts.qh, (int)ts.qt, ts.kh, (int)ts.kt,       \
-                       L->d_tile_src, L->n_prefix)
+                       L->d_tile_src, L->n_prefix, p.places, p.extra)
     if (dense_layout(d)) VXL_LAUNCH(false); else VXL_LAUNCH(true);
 #undef VXL_LAUNCH
     VXL_HIP_TRY(hipGetLastError());

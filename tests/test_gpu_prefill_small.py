@@ -56,6 +56,10 @@ def test_small_prompts_match_the_oracle(variant, hq, hkv, d, prefix, lens, windo
     (5, 1, 64, 40, [90] * 12, 33, 4),                  # row tiles of five heads
     (3, 3, 128, 40, [190] * 4, 0, 4),                  # KV heads that do not divide the eight XCDs
     (1, 1, 128, 0, [700] * 12 + [100], 0, 1),          # 8,500 kept rows: no room for their table
+    (4, 2, 64, 256, [40] * 30, 0, 8),                  # chunks of one part, a prefix of two (four waves: of four)
+    (12, 1, 128, 300, [33, 20, 64] * 6, 0, 8),         # a prefix of two bands, the last one ragged
+    (6, 3, 64, 700, [50] * 12, 20, 8),                 # the same where one queue serves all heads
+    (7, 1, 128, 130, [300, 20, 500], 0, 8),            # chunks with more parts than the prefix
 ])
 def test_parts_and_history_without_queue_and_pre_pass(hq, hkv, d, prefix, lens, window, every):
     """What the library chooses, and the queue with late claims, against the oracle and against the instance of large
