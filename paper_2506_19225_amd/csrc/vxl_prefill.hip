@@ -90,6 +90,9 @@ struct PrefillDmaCfg {
 //            prefix rows by their number and kept rows through the layout's table of source tokens, whose share of
 //            a part lies in LDS behind the ring
 enum { kEarly, kLate, kDirect };
+// kDirect: the parts of an item and KV head that a launch has places for (direct_places), what the prefix's bands have more,
+// and the KV heads that share a numbering (1, or all where they do not divide the XCDs).
+struct PartPlaces { int places, extra, heads; };
 template <int D, int NS, bool STRIDED, int NW = 8, int TAKE = kEarly>
 __global__ __launch_bounds__(NW * 64, 2) void prefill_dma_kernel(
     const uint16_t* __restrict__ Q, const uint16_t* __restrict__ K, const uint16_t* __restrict__ V,
@@ -97,7 +100,7 @@ __global__ __launch_bounds__(NW * 64, 2) void prefill_dma_kernel(
     float* __restrict__ LSE, const Segment* __restrict__ segs, const WorkItem* __restrict__ work,
     int n_tokens, int n_q_heads, int group, int ctx_rows_pad, float scale, int n_items, int xpg,
     int* __restrict__ queue, long long q_head_arg, int q_tok_arg, long long kv_head_arg, int kv_tok_arg,
-    const int32_t* __restrict__ hist_src, int n_prefix, int places_arg, int extra) {      // DIRECT: source token of every history row; PartPlaces
+    const int32_t* __restrict__ hist_src, int n_prefix, PartPlaces pp) {      // (DIRECT; hist_src: source token of every history row)
     using C = PrefillDmaCfg<D, NS, NW>;
     constexpr bool DIRECT = TAKE == kDirect, LATE = TAKE == kLate;
     // Element strides of Q/O and K/V rows: the arguments, or (STRIDED false, the dense head-major
@@ -114,12 +117,10 @@ __global__ __launch_bounds__(NW * 64, 2) void prefill_dma_kernel(
     const int tid = threadIdx.x, lane = tid & 63, l32 = lane & 31, hi = lane >> 5;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int qid = xpg > 0 ? (int)(blockIdx.x & 7) / xpg : 0;            // this workgroup's queue
-    // parts of an item (and of all its KV heads where they share a queue) that the launch has places for
-    const int places = DIRECT ? places_arg : group, all_places = DIRECT ? n_q_heads / group * places : n_q_heads;
-    const int listed = xpg > 0 ? n_items * places : n_items * all_places;
-    const int q_len_items = DIRECT ? listed + (n_prefix + C::BM - 1) / C::BM * extra * (xpg > 0 ? 1 : n_q_heads / group) : listed;
+    const int listed = DIRECT ? n_items * pp.heads * pp.places : xpg > 0 ? n_items * group : n_items * n_q_heads;
+    const int q_len_items = DIRECT ? listed + (n_prefix + C::BM - 1) / C::BM * pp.heads * pp.extra : listed;
     const float c2 = scale * kLog2e;
-    const int r_in = lane / C::PPR, pp = lane % C::PPR;
+    const int r_in = lane / C::PPR, piece = lane % C::PPR;
 
     // Lane-constant parts of the refill addresses of a full tile: row and (swizzled) 16-byte piece
     // of this lane in each of the wave's load instructions -- for the compact history tiles
@@ -128,9 +129,9 @@ __global__ __launch_bounds__(NW * 64, 2) void prefill_dma_kernel(
 #pragma unroll
     for (int i = 0; i < C::IPW; ++i) {
         const int row = (wave + i * C::WAVES) * C::RPI + r_in;
-        const int kp = pp ^ ((row / (16 / C::PPR)) & (C::PPR - 1));
+        const int kp = piece ^ ((row / (16 / C::PPR)) & (C::PPR - 1));
         constexpr int CPR = D * 2 / 64, RPL = D == 128 ? 1 : 2;
-        const int vp = (((pp >> 2) ^ ((row / RPL) & (CPR - 1))) << 2) | (pp & 3);
+        const int vp = (((piece >> 2) ^ ((row / RPL) & (CPR - 1))) << 2) | (piece & 3);
         koff_ctx[i] = (uint32_t)row * (D * 2) + kp * 16;
         voff_ctx[i] = (uint32_t)row * (D * 2) + vp * 16;
         koff_own[i] = STRIDED ? (uint32_t)row * (uint32_t)(kv_tok * 2) + kp * 16 : koff_ctx[i];
@@ -147,11 +148,11 @@ __global__ __launch_bounds__(NW * 64, 2) void prefill_dma_kernel(
     }
     // The descriptors of an item (two dependent scalar loads) are fetched while the item before it
     // runs, as soon as its index is known.
-    auto item_of = [&](int jj) { return xpg > 0 ? jj / places : jj / all_places; };
+    auto item_of = [&](int jj) { return jj / (DIRECT ? pp.heads * pp.places : xpg > 0 ? group : n_q_heads); };
     WorkItem wi_next = {0, 0};
     Segment sg_next = {0, 0, 0, 0, 0};
     if (j < q_len_items) {
-        if (DIRECT && j >= listed) wi_next = {0, (j - listed) / (xpg > 0 ? extra : n_q_heads / group * extra)};
+        if (DIRECT && j >= listed) wi_next = {0, (j - listed) / (pp.heads * pp.extra)};
         else wi_next = work[item_of(j)];
         sg_next = segs[wi_next.seg];
     }
@@ -163,16 +164,18 @@ __global__ __launch_bounds__(NW * 64, 2) void prefill_dma_kernel(
     // the cells of a ragged last band fill as few parts as possible: cut head by head, every
     // part of such a band would run with most of its waves idle (variable chunk lengths: +11 %).
     // Parts left without cells walk one tile and write nothing.
-    const int part_id = xpg > 0 ? qid * places + j % places : j % all_places;
-    int g = part_id / places;                                 // KV head
-    int part = part_id - g * places;
-    if (DIRECT) {
-        if (j < listed) {
-            part = (part + item_of(j)) % places;              // (in turn over the XCDs: a part's place decides its length)
-        } else {
-            g = xpg > 0 ? qid : (j - listed) / extra % (n_q_heads / group);
-            part = places + (j - listed) % extra;
-        }
+    int g, part;                                              // KV head, part
+    if constexpr (DIRECT) {
+        const int item = item_of(j), places = j < listed ? pp.places : pp.extra;
+        const int at = j < listed ? j - item * pp.heads * places : (j - listed) % (pp.heads * places);
+        g = xpg > 0 ? qid : at / places;
+        part = xpg > 0 ? at : at - g * places;
+        // (in turn over the XCDs: a part's place decides its length)
+        part = j < listed ? (part + item) % places : part + pp.places;
+    } else {
+        const int part_id = xpg > 0 ? qid * group + j % group : j % n_q_heads;
+        g = part_id / group;
+        part = part_id - g * group;
     }
     const WorkItem wi = wi_next;
     const Segment sg = sg_next;
@@ -454,7 +457,7 @@ static vxl_status run_prefill_dma(const vxl_layout* L, const vxl_attn_desc* d, f
                        C::LDS_BYTES, s, (const uint16_t*)Q, (const uint16_t*)K, (const uint16_t*)V, kctx,  \
                        vctx, (uint16_t*)O, LSE, L->d_segs, L->d_work[wl_i], L->n_tokens, d->n_q_heads,     \
                        group, n_rows_pad, scale, L->n_work[wl_i], xpg, queue, ts.qh, (int)ts.qt, ts.kh,    \
-                       (int)ts.kt, nullptr, 0, 0, 0)
+                       (int)ts.kt, nullptr, 0, PartPlaces{})
     if (dense_layout(d)) VXL_LAUNCH(false); else VXL_LAUNCH(true);
 #undef VXL_LAUNCH
     VXL_HIP_TRY(hipGetLastError());
@@ -467,11 +470,10 @@ static vxl_status run_prefill_dma(const vxl_layout* L, const vxl_attn_desc* d, f
 // but the next ones have gone to other compute units by then: with places for a whole band's parts, a few units got all the
 // parts of short chunks (eight waves, 250 chunks of 40 tokens, D = 64, four heads on two 50.7 -> 27.5 us, D = 128, four on
 // one 105.1 -> 41.3).
-struct PartPlaces { int places, extra; };
-static PartPlaces direct_places(const vxl_layout* L, int group, int waves) {
+static PartPlaces direct_places(const vxl_layout* L, int group, int waves, int heads) {
     auto parts = [&](int tokens) { return (std::min((tokens + 31) / 32, waves) * group + waves - 1) / waves; };
     const int of_chunks = L->longest_chunk > 0 ? parts(L->longest_chunk) : parts(L->n_prefix);
-    return {of_chunks, std::max(0, parts(L->n_prefix) - of_chunks)};
+    return {of_chunks, std::max(0, parts(L->n_prefix) - of_chunks), heads};
 }
 
 // The instances without a pre-pass: `spread` keeps two workgroups of D = 64 off one compute unit by their LDS.
@@ -494,9 +496,8 @@ static vxl_status run_prefill_direct(const vxl_layout* L, const vxl_attn_desc* d
     const int group = d->n_q_heads / d->n_kv_heads;
     const int xpg = 8 % d->n_kv_heads == 0 ? 8 / d->n_kv_heads : 0;
     constexpr int wl_i = NW == 8 ? 1 : 0;
-    const PartPlaces p = direct_places(L, group, NW);
-    const long long per_queue = ((long long)L->n_work[wl_i] * p.places + (long long)(L->n_prefix + C::BM - 1) / C::BM * p.extra) *
-                                (xpg ? 1 : d->n_kv_heads);
+    const PartPlaces pp = direct_places(L, group, NW, xpg ? 1 : d->n_kv_heads);
+    const long long per_queue = ((long long)L->n_work[wl_i] * pp.places + (L->n_prefix + C::BM - 1) / C::BM * pp.extra) * pp.heads;
     const unsigned n_blocks = (unsigned)(xpg ? (per_queue + xpg - 1) / xpg * 8 : per_queue);
     const int lds = std::max(spread ? kMaxLds / 2 + 16 : 0, C::LDS_BYTES + L->s_total * 4);
 #define VXL_LAUNCH(STRIDED_)                                                                             \
@@ -504,7 +505,7 @@ static vxl_status run_prefill_direct(const vxl_layout* L, const vxl_attn_desc* d
                        (const uint16_t*)Q, (const uint16_t*)K, (const uint16_t*)V, nullptr, nullptr,     \
                        (uint16_t*)O, LSE, L->d_segs, L->d_work[wl_i], L->n_tokens, d->n_q_heads, group, 0, \
                        scale, L->n_work[wl_i], xpg, nullptr, ts.qh, (int)ts.qt, ts.kh, (int)ts.kt,       \
-                       L->d_tile_src, L->n_prefix, p.places, p.extra)
+                       L->d_tile_src, L->n_prefix, pp)
     if (dense_layout(d)) VXL_LAUNCH(false); else VXL_LAUNCH(true);
 #undef VXL_LAUNCH
     VXL_HIP_TRY(hipGetLastError());
