@@ -26,7 +26,8 @@ void vxl_debug_force_simple(int on);
  * unit, parts from a queue; for small prompts without pre-pass and queue, the smallest with 4 waves,
  * 128-row bands); 1 = the same kernel template as two independent 4-wave workgroups per compute unit
  * (128-row bands, a 2-stage ring each); 2 = the 8-wave instance of large prompts whatever the size;
- * 3 = the same with the next part claimed late.  Any other value selects 0. */
+ * 3 = the same with the next part claimed late; 4 = 4 waves, 128-row bands, with pre-pass and queue.  Any other
+ * value selects 0. */
 void vxl_debug_prefill_variant(int variant);
 
 /* Step-mode decode kernel form: 0 = the library chooses (4 double-buffered waves), 8 = eight

@@ -392,8 +392,9 @@ static std::atomic<hipEvent_t> g_ev_start{nullptr}, g_ev_stop{nullptr};
 // Cross-check only (declared in vxl_debug.h): 0 = choose (8 waves, 256-row bands, one workgroup per
 // compute unit; for small prompts 4 waves, 128-row bands); 1 = the same kernel as two independent
 // 4-wave workgroups per compute unit (128-row bands, a 2-stage ring each, one meeting per tile); 2 = the
-// 8-wave instance with the pre-pass and early claims whatever the size; 3 = with late claims.
-extern "C" void vxl_debug_prefill_variant(int v) { g_prefill_variant = v >= 1 && v <= 3 ? v : 0; }
+// 8-wave instance with the pre-pass and early claims whatever the size; 3 = with late claims; 4 = 4 waves, 128-row bands,
+// with the pre-pass and the 4-stage ring.
+extern "C" void vxl_debug_prefill_variant(int v) { g_prefill_variant = v >= 1 && v <= 4 ? v : 0; }
 // Measurement hook (declared in vxl_debug.h): when both events are set, every vxl_chunk_prefill
 // records them on its stream immediately before and after the main attention kernel (the pre-pass
 // is outside the bracket).
@@ -545,50 +546,57 @@ vxl_status launch_prefill_bf16(const vxl_layout* L, const vxl_attn_desc* d, floa
         return d->head_dim == 128 ? run_prefill_dma<128, 2, 4>(L, d, scale, Q, K, V, O, LSE, ws, s)
                                   : run_prefill_dma<64, 2, 4>(L, d, scale, Q, K, V, O, LSE, ws, s);
     bool late = g_prefill_variant == 3;
-    if (g_prefill_variant == 0) {
+    if (g_prefill_variant == 0 || g_prefill_variant == 4) {
         int n_cus = 0;
         const vxl_status st = device_cu_count(&n_cus);
         if (st != VXL_OK) return st;
         const long long parts4 = part_count(L, d, 4), parts8 = part_count(L, d, 8);
-        const bool d64 = d->head_dim == 64;
-        // No pre-pass and no queue (kDirect) while the compute units have some thirty tiles each and four parts at most;
-        // the table of kept rows has to fit beside the ring, and a token's row a 32-bit offset.  Beyond that the table
-        // costs more than the pre-pass, and the queue deals better: the next part is claimed late (kLate) up to four
-        // parts per compute unit, early above.  us, pre-pass and early claims -> direct / late, D = 128 unless said: 56
-        // parts 16.9 -> 14.2; D = 64, 168 parts of four waves 15.0 -> 10.6; 280 parts, 12 tiles per unit 59.1 -> 46.2 /
-        // 49.2; 804 parts, 10 tiles 70.3 -> 58.5 / 69.6; 428 parts, 25 tiles 95.1 -> 77.3 / 78.2; 492 parts, 51 tiles
-        // 142.1 -> 128.3 / 116.4; 598 parts, 36 tiles 113.4 -> 125.8 / 106.9; 956 parts, 49 tiles 138.5 -> 151.5 / 136.1;
-        // 1,820 parts, 154 tiles 342 -> 357 / 343; 4,104 parts, 685 tiles 1,379 -> 1,514 / 1,422.
-        const bool small = L->pair_count * d->n_q_heads <= 30ll * 16384 * n_cus &&
-                           (long long)L->n_tokens * tok_strides(d, L->n_tokens).kt * 2 < (1ll << 32);
+        const bool d64 = d->head_dim == 64, own_unit = parts4 <= n_cus;
+        const bool half = 8 * parts4 <= 9 * parts8;            // most bands have four cells at most: eight waves are half idle
+        // No pre-pass and no queue (kDirect) while the compute units have some thirty tiles each; the table of kept rows
+        // has to fit beside the ring, and a token's row a 32-bit offset.  Beyond that the table costs more than the
+        // pre-pass, and the queue deals better.  us, pre-pass and early claims -> direct, D = 128 unless said: 56 parts 16.9
+        // -> 14.2; D = 64, 168 parts of four waves 15.0 -> 10.6; 280 parts, 12 tiles per unit 59.1 -> 46.2; 428 parts, 25
+        // tiles 95.1 -> 77.3; but 492 parts, 51 tiles 128.3 against 116.4 with late claims; 598 parts, 36 tiles 125.8 and
+        // 106.9; 1,820 parts, 154 tiles 357 and 343.
+        const long long tiles = L->pair_count * d->n_q_heads / (16384ll * n_cus);
+        const bool direct = g_prefill_variant == 0 && tiles < 30 &&
+                            (long long)L->n_tokens * tok_strides(d, L->n_tokens).kt * 2 < (1ll << 32);
         const auto fits = [&](int lds) { return 4ll * L->s_total <= lds - (d64 ? 65552 : 131088); };   // (the ring, 16 bytes)
+        const int hist_tiles = L->l_ctx / kKeyTile;            // of the last chunk
         // Bands of 128 rows, so that twice as many compute units have work, and one wave per SIMD, which walks its tiles at
-        // twice the speed of two: while every part has a compute unit of its own (D = 128, eight waves -> four: 228
-        // parts 21.9 -> 17.4 us, 216 parts 15.9 -> 12.7, 44 parts 22.9 -> 17.0), and at D = 64, where two such
-        // workgroups fit a compute unit, up to four parts for each (404 parts 26.2 -> 23.3; 612 parts 18.9 -> 17.8;
-        // 1,198 parts 52.6 -> 52.3), unless chunks of one or two cells make as many parts either way (256 and 252
-        // parts 24.4 -> 25.8).
-        const bool own_unit = parts4 <= n_cus;
-        if (small && 8 * parts4 > 9 * parts8 && (own_unit ? fits(163840) : d64 && parts4 <= 4ll * n_cus && fits(81920)))
-            return d64 ? run_prefill_direct<64, 4>(L, d, scale, Q, K, V, O, LSE, s, own_unit)
+        // twice the speed of two.  While every part has a compute unit of its own (D = 128, eight waves -> four: 228 parts
+        // 21.9 -> 17.4, 216 parts 15.9 -> 12.7), unless chunks of four cells make as many parts either way (240 parts of
+        // D = 64 11.6 -> 11.9); D = 128 with the pre-pass from 48 tiles of history on (60 tiles 77.4 -> 75.5, 95 tiles 118.3
+        // -> 113.3, but 32 tiles 45.0 -> 45.8).  At D = 64, where two such workgroups fit a compute unit, up to eight parts
+        // for each (14 heads on two, 150 chunks of 72 tokens, 1,800 parts 74.0 -> 66.2, of 40 tokens 38.5 -> 32.7; 4 on 4,
+        // 250 of 72, 1,004 parts 77.2 -> 59.1, with the queue 80.2), but few parts of four cells over a longer history are
+        // as well off with eight waves (404 parts, 28 tiles of history 29.2 -> 31.9; 11 tiles 20.2 -> 15.9).
+        if (direct && own_unit && !half && fits(163840) && (d64 || hist_tiles <= 48))
+            return d64 ? run_prefill_direct<64, 4>(L, d, scale, Q, K, V, O, LSE, s, true)
                        : run_prefill_direct<128, 4>(L, d, scale, Q, K, V, O, LSE, s, false);
-        const bool shared = d64 && parts8 > n_cus && parts4 <= 4ll * n_cus && L->seg_tiles > 6ll * L->n_seg;
-        // (D = 64, chunks of three and four cells, which leave half of eight waves without rows, stay with the four-wave
-        // form below from two parts per unit on: 170 chunks of 72 tokens on four heads, 684 parts, 55.4 against 59.6, 250
-        // chunks 75.3 against 86.9; but 100 chunks, 404 parts, 36.2 against 31.2)
-        if (small && parts8 <= 4ll * n_cus && fits(163840) && !(shared && parts8 > 2ll * n_cus && parts4 > parts8 && 8 * parts4 <= 9 * parts8))
+        if (direct && d64 && !own_unit && parts4 <= 8ll * n_cus && fits(81920) && !(half && 4 * parts4 <= 7ll * n_cus && hist_tiles > 12))
+            return run_prefill_direct<64, 4>(L, d, scale, Q, K, V, O, LSE, s, false);
+        // Eight waves up to two parts per compute unit, at D = 128 four, of prompts with one head per KV head, whose queue
+        // has no parts without cells, if they have few tiles (800 parts, 16 tiles 138.2 against 136.0 with the queue).
+        // Beyond, and where the table does not fit, they lose to the queue or to four waves with the pre-pass (4 heads on
+        // 4, 250 chunks of 40 tokens, half of them kept, 142.9 against 139.4 and 123.0).
+        const bool alone = own_unit && !half;
+        if (direct && !alone && parts8 <= (d64 || (d->n_q_heads == d->n_kv_heads && tiles >= 12) ? 2ll : 4ll) * n_cus && fits(163840))
             return d64 ? run_prefill_direct<64, 8>(L, d, scale, Q, K, V, O, LSE, s, false)
                        : run_prefill_direct<128, 8>(L, d, scale, Q, K, V, O, LSE, s, false);
-        // Four waves with the pre-pass, where the table does not fit: while every part has a compute unit of its own
-        // (D = 128: 328 parts 23.0 -> 26.7 us), segments of four and more cells only if they walk enough tiles or leave
-        // units idle (five chunks of 192 tokens: 120 parts 18.5, 220 of four waves 20.8); D = 64, where two share a
-        // unit, once eight waves need a second round (896 parts 51.5 -> 47.7) and with some six tiles per segment.
-        const bool few_keys = parts4 * 16 > n_cus * 11ll && L->n_tokens > 96ll * L->n_seg && 4 * L->seg_tiles <= 21ll * L->n_seg;
-        const bool one_round = own_unit && !few_keys;
-        if (parts4 > parts8 && (one_round || shared))
-            return d64 ? run_prefill_dma<64, 4, 4>(L, d, scale, Q, K, V, O, LSE, ws, s, one_round)
+        // Four waves with the pre-pass: while every part has a compute unit of its own (D = 128: 328 parts 23.0 -> 26.7),
+        // and at D = 64, where two share a unit, with some six tiles per segment where the eight-wave form just needs a
+        // second round (302 parts 107.1 -> 98.9) or many (802 parts 242 -> 204; but 402 parts 139.2 -> 147.6).
+        const bool shared = d64 && !own_unit && parts4 <= 4ll * n_cus && L->seg_tiles > 6ll * L->n_seg &&
+                            (4 * parts8 <= 5ll * n_cus || parts8 > 2ll * n_cus);
+        if (g_prefill_variant == 4 || (own_unit && parts4 > parts8) || shared)
+            return d64 ? run_prefill_dma<64, 4, 4>(L, d, scale, Q, K, V, O, LSE, ws, s, own_unit)
                        : run_prefill_dma<128, 4, 4>(L, d, scale, Q, K, V, O, LSE, ws, s);
-        late = parts8 <= 4ll * n_cus;
+        // The next part is claimed late up to four parts per compute unit, early above (1,820 parts 342 against 343, 4,104
+        // parts 1,379 against 1,422); with one head per KV head up to two and a half (D = 64, 1,004 parts 315 -> 345, 684
+        // parts 182.6 -> 186.0, but 604 parts 148.6 -> 137.5; D = 128, 964 parts 124.8 -> 126.9).
+        late = 2 * parts8 <= (d->n_q_heads > d->n_kv_heads ? 8ll : 5ll) * n_cus;
     }
     if (late)
         return d->head_dim == 128 ? run_prefill_dma<128, 4, 8, kLate>(L, d, scale, Q, K, V, O, LSE, ws, s)

@@ -399,7 +399,8 @@ def debug_decode_plan(desc: AttnDesc, batch: int, n_q_tokens: int, l_cap: int, i
 def debug_prefill_variant(variant: int) -> None:
     """Cross-check only: 0 = the library chooses (8 waves, one workgroup per compute unit, parts from a queue; small
     prompts without pre-pass and queue, the smallest with 4 waves); 1 = the same kernel as two independent 4-wave
-    workgroups per compute unit; 2 = the 8-wave instance of large prompts whatever the size; 3 = with late claims."""
+    workgroups per compute unit; 2 = the 8-wave instance of large prompts whatever the size; 3 = with late claims;
+    4 = 4 waves with pre-pass and queue."""
     lib().vxl_debug_prefill_variant(int(variant))
 
 

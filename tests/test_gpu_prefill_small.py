@@ -1,6 +1,6 @@
-"""Small prompts, which take the 4-wave pre-filling instance: both instances against the oracle on layouts on either
-side of the line between them (256 parts at D = 128) and on ragged ones, with a look-back window and token-major
-storage."""
+"""Small prompts, which take the pre-filling instances of four and eight waves without pre-pass and queue: the instance
+that the library chooses and that of large prompts against the oracle on layouts on either side of the line between four
+and eight waves (256 parts at D = 128) and on ragged ones, with a look-back window and token-major storage."""
 import time
 
 import numpy as np
@@ -26,7 +26,7 @@ pytestmark = pytest.mark.gpu
     (14, 2, 64, 0, [97, 400], 0),
     (14, 2, 64, 30, [256] * 19, 0),                # two 4-wave workgroups per compute unit
     (8, 8, 64, 17, [97, 63, 200], 0),              # at most one, though two would fit
-    (28, 4, 128, 0, [192] * 5, 0),                 # few keys for 220 parts: eight waves
+    (28, 4, 128, 0, [192] * 5, 0),                 # few keys for 220 parts
 ])
 def test_small_prompts_match_the_oracle(variant, hq, hkv, d, prefix, lens, window):
     rng = np.random.default_rng(91 + sum(lens))
@@ -135,3 +135,46 @@ def test_host_time_does_not_grow_with_the_chunks():
             torch.cuda.synchronize()
         best.append(min(took))
     assert best[1] < best[0] + 8e-6, best
+
+
+@pytest.mark.parametrize("hq,hkv,d,prefix,lens,window,every", [
+    (7, 1, 64, 65, [65, 129, 300], 90, 2), (4, 4, 64, 17, [200] * 5 + [64], 0, 1), (14, 2, 128, 63, [70, 1, 200, 64], 0, 3),
+    (3, 3, 128, 0, [128, 129], 0, 8)])
+def test_four_waves_with_pre_pass(hq, hkv, d, prefix, lens, window, every):
+    """The instance of four waves with pre-pass and queue against the oracle and, bit for bit, the one of large prompts."""
+    rng = np.random.default_rng(96 + sum(lens))
+    starts = prefix + np.concatenate([[0], np.cumsum(lens)[:-1]])
+    kept = [np.sort(s + rng.choice(n, max(1, n // every), replace=False)).astype(np.int32) for s, n in zip(starts, lens)]
+    lay = wl.layout_from_lists(prefix, lens, kept)
+    w = wl.tiny_workload("bf16", hq, hkv, d, T=1, B=1, k=1, seed=96, value_scale=1.0)
+    q, k, v = wl.make_qkv(w, lay)
+    res = []
+    for variant in (4, 2):
+        with prefill_variant(variant):
+            res.append(gpu_prefill(w, lay, q, k, v, want_lse=True, gl=make_layout(lay, window=window)))
+    want, wlse = oracle_prefill(q, k, v, lay, return_lse=True, window=window)
+    assert_close(res[0][0], want, "bf16", what=f"{lens[:4]}")
+    assert np.abs(res[0][1] - wlse).max() < 2e-2
+    assert np.array_equal(res[0][0], res[1][0]) and np.array_equal(res[0][1], res[1][1])
+
+
+@pytest.mark.parametrize("hq,hkv,d,prefix,chunks,length,every", [
+    (4, 4, 64, 0, 170, 72, 8), (4, 4, 64, 256, 170, 72, 8),       # chunks of four cells at most, two workgroups per unit
+    (4, 4, 64, 64, 100, 72, 4),                                    # the same, few of them: eight waves
+    (4, 4, 64, 64, 250, 40, 2),                                    # no room for the kept rows of two: with the pre-pass
+    (4, 2, 64, 0, 150, 72, 2),                                     # the same, 302 parts of eight waves
+    (14, 2, 64, 256, 150, 40, 8),                                  # 1,200 parts of four waves
+    (2, 1, 128, 256, 43, 160, 2),                                  # 60 tiles of history, a compute unit for every part
+    (4, 4, 128, 64, 200, 40, 2), (4, 4, 128, 64, 240, 100, 8)])    # three parts per unit, one head per KV head: early claims
+def test_chosen_instance_of_many_short_chunks(hq, hkv, d, prefix, chunks, length, every):
+    """Prompts on the sides of the lines between the instances: bit for bit what the instance of large prompts gives."""
+    lay = wl.layout_from_lists(prefix, [length] * chunks,
+                               [wl.strided_kept(prefix + i * length, length, length // every) for i in range(chunks)])
+    w = wl.tiny_workload("bf16", hq, hkv, d, T=1, B=1, k=1, seed=97, value_scale=1.0)
+    gen = torch.Generator(device="cuda").manual_seed(chunks + d)
+    dev = [torch.empty((h, lay.n_tokens, d), dtype=torch.bfloat16, device="cuda").normal_(0, 1, generator=gen) for h in (hq, hkv, hkv)]
+    res = []
+    for variant in (0, 2):
+        with prefill_variant(variant):
+            res.append(gpu_prefill(w, lay, None, None, None, want_lse=True, dev=dev))
+    assert np.array_equal(res[0][0], res[1][0]) and np.array_equal(res[0][1], res[1][1])
