@@ -35,7 +35,8 @@ void vxl_debug_prefill_variant(int variant);
 void vxl_debug_decode_step_waves(int waves);
 
 /* Decode kernel that a BF16 call of these sizes takes: 0 = 128 rows per workgroup, 1 = the 256-row
- * ring, 2 = 32-row blocks whose waves own the keys (step mode).  n_split: its key splits.  Host only. */
+ * ring, 2 = 32-row blocks whose waves own the keys (step mode).  n_split: the key splits that the workspace is
+ * sized for (the ring launches no more of them than run in one round of the device's compute units).  Host only. */
 int vxl_debug_decode_plan(const vxl_attn_desc* desc, int batch, int n_q_tokens, int l_cap, int in_place,
                           int* n_split);
 

@@ -130,8 +130,8 @@ DecodePlan decode_plan(const vxl_attn_desc* d, int batch, int T, int l_cap, bool
             // shorter.  In tiles of the ring, a call of the ring takes its tiles and 14 for start and merge, a
             // round of workgroups here 8 and 0.8 per tile of a wave; the row blocks of a unit run on one XCD, whose
             // 32 compute units hold a workgroup each (its LDS), at D = 64 two unless it holds a row map too.
-            // Fitted to 176 random calls of 257 to 4,000 rows, gathered and in place: none of those that take row
-            // blocks is slower than by the ring, 1.28x on average as with the faster one of every call.
+            // Fitted to 176 random calls of 257 to 4,000 rows, gathered and in place, with the ring's keys cut by capacity;
+            // with the present ring, of 60 random calls that take row blocks none is slower (1.1x to 2.9x).
             // Ring -> here, D = 128: 959 rows, 1,171 keys in one split, 10 tiles per wave 41.3 -> 20.0; 1,050 rows,
             // two rounds, 1,202 keys 48.3 -> 37.6; 2,824 rows on one KV head, three rounds, 148 keys 20.2 -> 25.6;
             // 1,280 rows, two rounds, 16,384 keys, 12 splits against one 47.8 -> 219.8.  D = 64: 2,006 rows, one
@@ -147,8 +147,9 @@ DecodePlan decode_plan(const vxl_attn_desc* d, int batch, int T, int l_cap, bool
         // 5.5, 384 keys 6.9 -> 6.7, 501 keys 7.2 -> 7.8, but submitted call by call, where the second launch costs the host
         // 3, 9.8 -> 7.5; 56 rows, 251 keys 10.9 -> 7.9, 501 keys 11.6 -> 10.2; 8 queries of 112 rows, 501 keys 13.4 -> 11.4.
         // D = 64: 7 rows, 500 keys 6.2 -> 5.6, 700 keys 6.3 -> 6.9 (call by call 9.8 -> 7.0); three queries of 140 rows, 761
-        // keys 8.7 -> 8.4.  In place, where a wave pays for the row map on every tile, 12 and 16.  33 to 64 rows of D = 64
-        // go to 12 tiles only: above, this range is the one that exercises the 128-row kernel.
+        // keys 8.7 -> 8.4.  In place, where a wave pays for the row map on every tile, 12 and 16.  33 to 64 rows of D = 64 go to
+        // 12 tiles only because tests hold the range above to the 128-row kernel: one workgroup would be the faster one there
+        // too (64 rows, 385 keys 8.8 -> 6.4, 768 keys 7.7 -> 7.5; in place, 63 rows, 512 keys 8.6 -> 7.7).
         const bool d64 = d->head_dim == 64;
         const int one = d64 && rows > kRowBlock && rows <= 64 ? 12 : gathered ? (d64 ? 24 : 16) : (d64 ? 16 : 12);
         const bool single = rows <= 256 && tiles32 <= one && units * n_rtile <= 256;

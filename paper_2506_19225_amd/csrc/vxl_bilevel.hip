@@ -33,9 +33,9 @@ __device__ __forceinline__ void store16(uint4* p, uint4 v) {
 // kbar[g, c, :] = mean of the dense key rows of chunk c.  One block per (chunk, kv head).
 // A thread owns one 16-byte column piece and the rows rg, rg + RG, ... of the chunk, which it
 // sums in row order (four independent accumulators: rows 0,4,8.. / 1,5,9.. of its sequence);
-// the RG partial sums are then added in a fixed tree.  The summation tree depends only on the
-// values and their offsets inside the chunk: two chunks with equal contents get bit-identical
-// means, hence exactly tied scores.  Bound by HBM when large, otherwise by a block's chain of round
+// the RG partial sums are then added in a fixed tree.  Within a layout the summation tree depends only
+// on the values and their offsets inside the chunk: two chunks with equal contents get bit-identical
+// means, hence exactly tied scores (layouts may differ in the number of threads, and so in the last bit).  Bound by HBM when large, otherwise by a block's chain of round
 // trips: the last rows of a thread are requested together as well (114 chunks of 128 to 1,024 tokens, one
 // by one -> so, 25.6 -> 24.1 us with the selection).  How many threads, and whether past the caches: launch_summaries.
 // ------------------------------------------------------------------------------------------
@@ -551,8 +551,9 @@ vxl_status launch_summaries(const vxl_layout* L, const vxl_attn_desc* d, const v
     // rows of a thread at once instead of four unless they are streamed (those 20 chunks 11.4 -> 10.1; 100 of 1,200,
     // streamed, 28.3 -> 28.8; 256 threads: 64 of 256 28.3 -> 28.7 with the rest of a query).
     // Keys beyond 96 MB are streamed past the caches: 164,096 tokens 45.5 -> 40.0; six layers in turn, 104 MB 28.1 -> 24.0,
-    // two 23.7 -> 23.3.  Of fewer the on-package cache holds two or three layers, which is then the faster source: 79 MB,
-    // two layers in turn 18.6 -> 19.4 (six 22.1 -> 20.1), 42 MB 13.2 -> 13.7, 17 MB 10.1 -> 10.7.
+    // two 23.7 -> 23.3.  Of fewer the on-package cache holds two or three layers, which is then the faster source for a
+    // caller that scores so many: 79 MB, two layers in turn 18.6 -> 19.4, 42 MB 13.2 -> 13.7, 17 MB 10.1 -> 10.7; a stack
+    // of more finds none of them there and would be streamed sooner (79 MB, six in turn 22.1 -> 20.1).
     // (The choice depends on layout and descriptor alone: means that a caller keeps are those of every later call.)
     const long long elem = d->dtype == VXL_BF16 ? 2 : 4, row = d->head_dim * elem;
     const bool wide = row >= 256 && (long long)L->n_chunks * d->n_kv_heads <= 512 &&
