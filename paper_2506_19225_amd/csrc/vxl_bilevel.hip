@@ -32,10 +32,10 @@ __device__ __forceinline__ void store16(uint4* p, uint4 v) {
 // ------------------------------------------------------------------------------------------
 // kbar[g, c, :] = mean of the dense key rows of chunk c.  One block per (chunk, kv head).
 // A thread owns one 16-byte column piece and the rows rg, rg + RG, ... of the chunk, which it
-// sums in row order (four independent accumulators: rows 0,4,8.. / 1,5,9.. of its sequence);
-// the RG partial sums are then added in a fixed tree.  Within a layout the summation tree depends only
-// on the values and their offsets inside the chunk: two chunks with equal contents get bit-identical
-// means, hence exactly tied scores (layouts may differ in the number of threads, and so in the last bit).  Bound by HBM when large, otherwise by a block's chain of round
+// sums in row order in four (512 threads: two) independent accumulators; all partial sums are then added in a
+// fixed tree.  The summation tree depends only on the values and their offsets inside the chunk, not on the
+// number of threads: two chunks with equal contents get bit-identical means, hence exactly tied scores, also
+// in different layouts.  Bound by HBM when large, otherwise by a block's chain of round
 // trips: the last rows of a thread are requested together as well (114 chunks of 128 to 1,024 tokens, one
 // by one -> so, 25.6 -> 24.1 us with the selection).  How many threads, and whether past the caches: launch_summaries.
 // ------------------------------------------------------------------------------------------
@@ -96,8 +96,12 @@ __global__ __launch_bounds__(THREADS) void chunk_summarize_kernel(const T* __res
     constexpr int PPR = D / EPC;                    // pieces per row
     constexpr int RG = THREADS / PPR;               // row groups
     constexpr int U = THREADS == 512 && !NT ? 8 : 4;      // rows that a thread requests together
+    // Partial sums of the rows of equal place mod CHAINS, which is the same for either number of threads: a thread has A
+    // of them, and they are added in the same tree.
+    constexpr int A = THREADS == 512 ? 2 : 4, CHAINS = A * RG, GROUPS = CHAINS / 4;
+    constexpr int KEPT = THREADS == 512 ? CHAINS : GROUPS;      // (256 threads: a thread adds the four of its group)
     extern __shared__ float dyn[];                  // [group][D] for the query blocks
-    __shared__ float part[RG][D];
+    __shared__ float part[KEPT][D];
     if ((int)blockIdx.x >= n_chunks) {
         query_mean_block<T, D, THREADS>(Qd, qbar, blockIdx.x - n_chunks, blockIdx.y, T_q, n_q_heads, n_kv_heads, dyn);
         return;
@@ -106,9 +110,9 @@ __global__ __launch_bounds__(THREADS) void chunk_summarize_kernel(const T* __res
     const int piece = threadIdx.x % PPR, rg = threadIdx.x / PPR;
     const int lo = bounds[c], hi = bounds[c + 1];
     const uint4* base = (const uint4*)K + (size_t)g * kv_head_u4 + piece;
-    float acc[4][EPC];
+    float acc[A][EPC];
 #pragma unroll
-    for (int u = 0; u < 4; ++u)
+    for (int u = 0; u < A; ++u)
 #pragma unroll
         for (int i = 0; i < EPC; ++i) acc[u][i] = 0.f;
     int r = lo + rg;
@@ -120,7 +124,7 @@ __global__ __launch_bounds__(THREADS) void chunk_summarize_kernel(const T* __res
         for (int u = 0; u < U; ++u) {
             const T* e = (const T*)&v[u];
 #pragma unroll
-            for (int i = 0; i < EPC; ++i) acc[u & 3][i] += ld(e + i);
+            for (int i = 0; i < EPC; ++i) acc[u % A][i] += ld(e + i);
         }
     }
     if (r < hi) {                                             // the last rows, requested together as well (a repeated one is not added)
@@ -132,16 +136,28 @@ __global__ __launch_bounds__(THREADS) void chunk_summarize_kernel(const T* __res
             if (r + u * RG < hi) {
                 const T* e = (const T*)&v[u];
 #pragma unroll
-                for (int i = 0; i < EPC; ++i) acc[u & 3][i] += ld(e + i);
+                for (int i = 0; i < EPC; ++i) acc[u % A][i] += ld(e + i);
             }
     }
 #pragma unroll
-    for (int i = 0; i < EPC; ++i) part[rg][piece * EPC + i] = (acc[0][i] + acc[1][i]) + (acc[2][i] + acc[3][i]);
+    for (int i = 0; i < EPC; ++i) {
+        if constexpr (A == 4) {
+            part[rg][piece * EPC + i] = (acc[0][i] + acc[1][i]) + (acc[2][i] + acc[3][i]);
+        } else {
+            part[rg][piece * EPC + i] = acc[0][i];
+            part[rg + RG][piece * EPC + i] = acc[1][i];
+        }
+    }
     __syncthreads();
     if (threadIdx.x < D) {
+        auto group = [&](int i) __attribute__((always_inline)) {
+            if constexpr (A == 4) return part[i][threadIdx.x];
+            else return (part[i][threadIdx.x] + part[i + GROUPS][threadIdx.x]) +
+                        (part[i + 2 * GROUPS][threadIdx.x] + part[i + 3 * GROUPS][threadIdx.x]);
+        };
         float q[4];
 #pragma unroll
-        for (int i = 0; i < RG; ++i) q[i & 3] = i < 4 ? part[i][threadIdx.x] : q[i & 3] + part[i][threadIdx.x];
+        for (int i = 0; i < GROUPS; ++i) q[i & 3] = i < 4 ? group(i) : q[i & 3] + group(i);
         const float s = (q[0] + q[1]) + (q[2] + q[3]);
         kbar[((size_t)g * n_chunks + c) * D + threadIdx.x] = s / (float)(hi - lo);
     }

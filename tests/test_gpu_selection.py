@@ -6,9 +6,9 @@ import pytest
 import torch
 
 import oracle
-from paper_2506_19225_amd import workloads as wl
+from paper_2506_19225_amd import vxl, workloads as wl
 
-from gpu_util import full_sort_selection, gpu_score_topk
+from gpu_util import desc_of, full_sort_selection, gpu_score_topk, make_layout
 
 pytestmark = pytest.mark.gpu
 
@@ -73,3 +73,30 @@ def test_mean_keys_of_long_and_ragged_chunks(dtype, hkv, d, lens):
     assert np.array_equal(scores[:, 0], scores[:, 1])
     own_idx, own_mask = full_sort_selection(scores, 3)
     assert np.array_equal(idx, own_idx) and np.array_equal(mask, own_mask)
+
+
+@pytest.mark.parametrize("dtype,hkv,d,lens", [
+    ("bf16", 4, 128, [400, 333, 700, 1, 31, 32, 33, 64, 65, 127, 500]),     # 512 threads up to 128 chunks, then 256
+    ("f32", 2, 128, [300, 1, 15, 16, 17, 31, 33, 500, 499]),                # 256 chunks
+])
+def test_means_do_not_depend_on_the_number_of_chunks(dtype, hkv, d, lens):
+    """The first chunks' mean keys and scores have the same bits in a prompt of few long chunks, which 512 threads sum,
+    and in one of more of them, which 256 do."""
+    rng = np.random.default_rng(d + hkv)
+    w = wl.tiny_workload(dtype, 2 * hkv, hkv, d, T=3, B=1, k=1, seed=d, value_scale=1.0)
+    many = 512 // hkv + 1 - len(lens)
+    k = rng.standard_normal((hkv, sum(lens) + 700 * many, d)).astype(np.float32)
+    k = wl.round_to_bf16(k) if dtype == "bf16" else k
+    qd, res = wl.make_decode_queries(w), []
+    for all_lens in (lens + [700] * 4, lens + [700] * many):
+        lay = wl.layout_from_lists(0, all_lens, [np.zeros(0, np.int32)] * len(all_lens))
+        gl, desc = make_layout(lay), desc_of(w)
+        dk, dq = vxl.to_device(np.ascontiguousarray(k[:, :lay.n_tokens]), dtype), vxl.to_device(qd, dtype)
+        idx, mask = torch.zeros((1, 1), dtype=torch.int32, device="cuda"), torch.zeros((1, lay.n_chunks), dtype=torch.uint8, device="cuda")
+        scores = torch.zeros((1, lay.n_chunks), device="cuda")
+        kbar = torch.zeros((hkv, lay.n_chunks, d), device="cuda")
+        vxl.chunk_score_topk(gl, desc, dq, dk, 1, idx, mask, scores, kbar,
+                             workspace=vxl.alloc_workspace(vxl.workspace_bytes(vxl.OP_SCORE_TOPK, gl, desc, 1)))
+        res.append((kbar[:, :len(lens)].cpu().numpy(), scores[:, :len(lens)].cpu().numpy()))
+    for a, b in zip(*res):
+        assert np.array_equal(a.view(np.uint32), b.view(np.uint32))
