@@ -194,3 +194,28 @@ def test_one_workgroup_is_as_precise_as_a_tile_per_wave(hq, hkv, t, bsz, d, n, i
                          torch.full((bsz,), n, dtype=torch.int32, device="cuda"))
     want = wl.round_to_bf16(_rounded_tiles(qd, k, v, n).astype(np.float32)).astype(np.float64)
     assert np.linalg.norm(got - want) <= 2.5e-4 * np.linalg.norm(want)
+
+
+@pytest.mark.parametrize("hq,hkv,d,bsz,t,l_cap,n,scale", [
+    (28, 4, 128, 2, 32, 35410, 25500, 1.0), (28, 4, 128, 2, 32, 8000, 5000, 1.0), (14, 2, 64, 2, 95, 9000, 7000, 1.0),     # the ring
+    (28, 4, 128, 8, 32, 9000, 6000, 0.0884), (28, 4, 128, 8, 16, 2000, 1500, 1.0), (28, 4, 128, 4, 1, 6000, 4000, 1.0),
+    (28, 4, 128, 4, 8, 251, 251, 1.0), (14, 2, 64, 4, 20, 761, 700, 1.0), (28, 4, 128, 8, 1, 512, 501, 1.0)])
+def test_decode_error_is_that_of_two_roundings(hq, hkv, d, bsz, t, l_cap, n, scale):
+    """Wherever the keys are cut: the weights and the result are rounded to bf16 once.  Half a unit is 2^-8 of a value at
+    most, 2^-8 * 0.42 of it in root mean square over mantissas that are uniform in their logarithm; the rows add the
+    weights' roundings up as they do the weights.  sqrt(2) * 0.42 * 2^-8 = 2.35e-3, and 2 % for the sample."""
+    w = wl.tiny_workload("bf16", hq, hkv, d, T=t, B=bsz, k=1, seed=1)
+    desc, g, num, den = desc_of(w), hq // hkv, 0.0, 0.0
+    gen = torch.Generator(device="cuda").manual_seed(l_cap)
+    q, k, v = (torch.empty(s, dtype=torch.bfloat16, device="cuda").normal_(0, scale, generator=gen)
+               for s in ((bsz, t, hq, d), (bsz, hkv, l_cap, d), (bsz, hkv, l_cap, d)))
+    out = torch.empty_like(q)
+    vxl.bilevel_decode(desc, q, k, v, torch.full((bsz,), n, dtype=torch.int32, device="cuda"), out, None,
+                       vxl.alloc_workspace(vxl.workspace_bytes(vxl.OP_DECODE, None, desc, bsz, t, l_cap)))
+    for b in range(bsz):
+        for h in range(hkv):
+            s = q[b, :, h * g:(h + 1) * g].reshape(-1, d).double() @ k[b, h, :n].double().T / d ** 0.5
+            want = torch.softmax(s, -1) @ v[b, h, :n].double()
+            num += (out[b, :, h * g:(h + 1) * g].reshape(-1, d).double() - want).pow(2).sum().item()
+            den += want.pow(2).sum().item()
+    assert (num / den) ** 0.5 <= 2.4e-3
