@@ -219,17 +219,24 @@ __global__ __launch_bounds__(256, (QB == 1 ? 2 : 1)) void decode_split_kernel(
 }
 
 // ------------------------------------------------------------------------------------------
-// Batched kernel for more than 128 stacked query rows: 256 rows and 8 waves per workgroup (one row
-// block of 32 per wave, two waves per SIMD), the split's 64-key tiles streamed into a ring of NS
+// Batched kernel for more than 128 stacked query rows: 32 rows per wave, 8 waves (two per SIMD) or 4 (one) per
+// workgroup (choose_ring draws the line), the split's 64-key tiles streamed into a ring of NS
 // LDS stages by direct global->LDS loads, two tiles ahead of the arithmetic -- the structure of
-// the streaming pre-filling kernel, without its causal part.  The loads are issued from inline
+// the streaming pre-filling kernel, without its causal part.
+// Eight waves are bound by matrix and vector issue with the clock they draw (1.6 us per tile), which a long split
+// repays.  Four walk a tile in 1.05 us, half the rows, so that a launch that fills the chip has half the splits: short
+// splits are bound by start and end -- a call takes 9 us besides, and 0.5 us per MB of fp32 partial rows, written and
+// merged.  With one wave per SIMD nothing hides its LDS reads, so their order is pinned as in the pre-filling kernel
+// (1,456 tiles of 224 rows in 256 workgroups 45.7 -> 43.1 us; with eight waves 122.6 -> 124.5 on 418 MB).  The refills
+// wait their turn between two tiles: both at the meeting delay the first one (238 -> 242 us with the gather), and one
+// meeting per tile with three tiles ahead is no faster.  The loads are issued from inline
 // assembly and counted by hand (every wave issues the same number per tile and waits with
 // vmcnt = loads still allowed in flight), so the kernel must not spill, and the query registers
 // are forced complete before the first ring load.  Same partials as decode_split_kernel.
 // ------------------------------------------------------------------------------------------
-template <int D, int NS>
+template <int D, int NS, int NW>
 struct DecodeRingCfg {
-    static constexpr int WAVES = 8;
+    static constexpr int WAVES = NW;
     static constexpr int RT = 32 * WAVES;                     // query rows per workgroup
     static constexpr int TILE = kKeyTile * D;                 // elements of one unpadded K (or V) tile
     static constexpr int STAGE = 2 * TILE;                    // K tile then V tile
@@ -245,12 +252,12 @@ struct DecodeRingCfg {
 // entry per load slot and tile; the entries of tiles t+2, t+3 are fetched (by loads issued from
 // inline assembly, so that they ride in the hand-kept vmcnt count) when the loads of tiles t, t+1 are
 // issued, and are complete behind the same vmcnt(0) that tiles t, t+1 wait for.
-template <int D, int NS, bool IND = false, bool ONCE = false>
-__global__ __launch_bounds__(512, 2) void decode_ring_kernel(
+template <int D, int NS, int NW, bool IND = false, bool ONCE = false>
+__global__ __launch_bounds__(64 * NW, 2) void decode_ring_kernel(
     const uint16_t* __restrict__ Qd, const uint16_t* __restrict__ Kmix, const uint16_t* __restrict__ Vmix,
     const int32_t* __restrict__ mix_len, float* __restrict__ part_o, float* __restrict__ part_lse, int T_q,
     int n_q_heads, int n_kv_heads, int group, int l_cap, float scale, RowMap rm, uint16_t* __restrict__ O, float* __restrict__ LSE) {
-    using C = DecodeRingCfg<D, NS>;
+    using C = DecodeRingCfg<D, NS, NW>;
     extern __shared__ __attribute__((aligned(16))) uint16_t lds[];
     const uint32_t lds_base = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) void*)lds;
 
@@ -267,9 +274,9 @@ __global__ __launch_bounds__(512, 2) void decode_ring_kernel(
 
     if (k_lo >= k_hi) {                            // empty split: only its weight (zero) is recorded
         if (n_split > 1) {
-            for (int r = rt * C::RT + tid; r < min(n_rows, (rt + 1) * C::RT); r += 512) part_lse[part_base + r] = -INFINITY;
+            for (int r = rt * C::RT + tid; r < min(n_rows, (rt + 1) * C::RT); r += 64 * NW) part_lse[part_base + r] = -INFINITY;
         } else {
-            for (int e = tid; e < min(n_rows - rt * C::RT, C::RT) * (D / 4); e += 512) {
+            for (int e = tid; e < min(n_rows - rt * C::RT, C::RT) * (D / 4); e += 64 * NW) {
                 const int rho = rt * C::RT + e / (D / 4);
                 const size_t row = ((size_t)b * T_q + rho / group) * n_q_heads + g * group + rho % group;
                 store_row4(O + row * D + e % (D / 4) * 4, 0.f, 0.f, 0.f, 0.f, false);
@@ -374,7 +381,8 @@ __global__ __launch_bounds__(512, 2) void decode_ring_kernel(
         const uint16_t* kt = lds + (ti % NS) * C::STAGE;
         const int key0 = k_lo + ti * kKeyTile;
         f32x16 s[1][2];
-        qk_tile<D, 1, D>(kt, qreg, l32, hi, s);
+        if constexpr (NW == 4) qk_tile_ahead<D, 1>(kt, qreg, l32, hi, s);
+        else qk_tile<D, 1, D>(kt, qreg, l32, hi, s);
         if (key0 + kKeyTile > k_hi) {
             const int lim = k_hi - key0 - 1;
 #pragma unroll
@@ -384,7 +392,8 @@ __global__ __launch_bounds__(512, 2) void decode_ring_kernel(
         }
         bf16x8 pb[1][2][2];
         softmax_tile<D / 32>(s[0], c2, m_run, l_run, o[0], pb[0]);
-        pv_tile<D, 1, D>(kt + C::TILE, pb, lane, o);
+        if constexpr (NW == 4) pv_tile_ahead<D, 2>(kt + C::TILE, pb, lane, o);
+        else pv_tile<D, 1, D>(kt + C::TILE, pb, lane, o);
     };
     for (int t0 = 0; t0 < n_t; t0 += TPB) {
         wait_vmcnt<0>();                                      // this wave's parts of tiles t0, t0+1 have landed
@@ -909,50 +918,103 @@ static vxl_status run_decode(const vxl_attn_desc* d, float scale, const void* Qd
     return launch_merge<D>(p.n_split, part_o, part_lse, O, LSE, T, d, batch, s);
 }
 
+// How a call goes to the ring kernel of 8 or 4 waves (256 or 128 rows per workgroup).
+struct RingLaunch {
+    int waves, n_split, n_rtile;
+    bool spread;                // no two workgroups on a compute unit
+    float us;                   // estimate of kernel and merge
+};
+static RingLaunch ring_launch(const vxl_attn_desc* d, int batch, int rows, int l_cap, int most_splits, int n_cus, int waves,
+                              bool in_place) {
+    RingLaunch r{};
+    const bool d64 = d->head_dim == 64;
+    const int pairs = d->n_kv_heads * batch, tiles = (l_cap + kKeyTile - 1) / kKeyTile;
+    r.waves = waves;
+    r.n_rtile = (rows + 32 * waves - 1) / (32 * waves);
+    const long long per_split = (long long)r.n_rtile * pairs;
+    // One workgroup per compute unit: of the planned splits, which give every unit at least one, as many as run in
+    // one round (gather included: 896 rows on six KV heads, 264 workgroups of 11 splits 118 us, 240 of 10 103; D =
+    // 64, 700 rows on four, 264 workgroups 85, 252 62).  At D = 64 a unit holds two: kept apart by their LDS while every
+    // workgroup has one of its own (301 rows, six heads, 252 of four waves over 23,178 keys 38.5 -> 28.6).
+    r.n_split = (int)std::max(1ll, std::min<long long>(most_splits, n_cus / per_split));
+    r.spread = d64 && r.n_split * per_split <= n_cus;
+    const int slots = d64 && !r.spread ? 2 * n_cus : n_cus;
+    const long long rounds = (r.n_split * per_split + slots - 1) / slots;
+    // us of start, a tile and a MB of partial rows: least squares over 139 (D = 128) and 120 (D = 64) random calls of 129 to
+    // 1,400 rows, off by 4 to 7 % (rms), and over 53 and 7 in place, off by 4.
+    static constexpr float kUs[2][2][2][3] = {{{{8.9f, 1.62f, 0.51f}, {7.3f, 1.05f, 0.61f}},          // gathered
+                                               {{7.2f, 1.08f, 0.70f}, {5.8f, 0.72f, 0.91f}}},
+                                              {{{18.5f, 1.69f, 0.22f}, {15.0f, 1.09f, 0.46f}},        // in place
+                                               {{13.7f, 1.19f, 0.51f}, {12.9f, 0.85f, 0.50f}}}};      // [D = 64][4 waves]
+    const float* us = kUs[in_place][d64][waves == 4];
+    const float walk = (float)((tiles + r.n_split - 1) / r.n_split * rounds);
+    const float mb = r.n_split > 1 ? 4e-6f * pairs * rows * r.n_split * d->head_dim : 0.f;
+    r.us = us[0] + us[1] * walk + us[2] * mb;
+    return r;
+}
+
+// Four waves where they are the shorter call by these estimates: over 160 random calls the time is 0.91 of that of always
+// eight (0.72 to 1.00), in place over 70 0.94 (0.81 to 1.04).  448 rows, 10,368 keys 29.4 -> 25.7 us; 588 rows x 8 queries, 674 keys, one split
+// 26.2 -> 18.8; but 301 rows x 8, 23,830 keys 174.9 against 202 with four.
+static RingLaunch choose_ring(const vxl_attn_desc* d, int batch, int rows, int l_cap, int most_splits, int n_cus,
+                              bool in_place) {
+    const RingLaunch eight = ring_launch(d, batch, rows, l_cap, most_splits, n_cus, 8, in_place);
+    const RingLaunch four = ring_launch(d, batch, rows, l_cap, most_splits, n_cus, 4, in_place);
+    return four.us < 0.98f * eight.us && (long long)four.n_rtile * d->n_kv_heads <= 65535 ? four : eight;
+}
+
+// Test hook (vxl_debug.h): the waves of the ring kernel's workgroups on 256 compute units.
+extern "C" int vxl_debug_decode_ring_waves(const vxl_attn_desc* d, int batch, int n_q_tokens, int l_cap, int in_place) {
+    const DecodePlan p = decode_plan(d, batch, n_q_tokens, l_cap, !in_place);
+    return choose_ring(d, batch, d->n_q_heads / d->n_kv_heads * n_q_tokens, l_cap, p.n_split, 256, in_place != 0)
+        .waves;
+}
+
+template <int D, int NW>
+static vxl_status launch_ring(const RingLaunch& rl, const vxl_attn_desc* d, float scale, const void* Qd, int batch, int T,
+                              const void* Kmix, const void* Vmix, int l_cap, const int32_t* mix_len, void* O, float* LSE,
+                              float* part_o, float* part_lse, hipStream_t s, const RowMap* rm) {
+    constexpr int kHalfLds = 81920;                           // of a compute unit
+    constexpr int kRing = DecodeRingCfg<D, 4, NW>::LDS_BYTES, kApart = std::max(kRing, kHalfLds + 16);
+    const int lds = rl.spread ? kApart : kRing;
+    static PerDeviceOnce attr;
+    const vxl_status ast = attr.run([] {
+        VXL_HIP_TRY(hipFuncSetAttribute((const void*)decode_ring_kernel<D, 4, NW, false>,
+                                        hipFuncAttributeMaxDynamicSharedMemorySize, kApart));
+        VXL_HIP_TRY(hipFuncSetAttribute((const void*)decode_ring_kernel<D, 4, NW, false, true>,
+                                        hipFuncAttributeMaxDynamicSharedMemorySize, kApart));
+        VXL_HIP_TRY(hipFuncSetAttribute((const void*)decode_ring_kernel<D, 4, NW, true>,
+                                        hipFuncAttributeMaxDynamicSharedMemorySize, kApart));
+        return VXL_OK;
+    });
+    if (ast != VXL_OK) return ast;
+    const dim3 grid(rl.n_split, rl.n_rtile * d->n_kv_heads, batch);
+#define VXL_LAUNCH(...)                                                                                              \
+    hipLaunchKernelGGL((decode_ring_kernel<D, 4, NW, __VA_ARGS__>), grid, dim3(64 * NW), lds, s, (const uint16_t*)Qd, \
+                       (const uint16_t*)Kmix, (const uint16_t*)Vmix, mix_len, part_o, part_lse, T, d->n_q_heads,     \
+                       d->n_kv_heads, d->n_q_heads / d->n_kv_heads, l_cap, scale, rm ? *rm : RowMap{}, (uint16_t*)O, LSE)
+    if (rm) VXL_LAUNCH(true);
+    else if (rl.n_rtile == 1 && beyond_l2(d, batch, l_cap)) VXL_LAUNCH(false, true);
+    else VXL_LAUNCH(false);
+#undef VXL_LAUNCH
+    VXL_HIP_TRY(hipGetLastError());
+    return launch_merge<D>(rl.n_split, part_o, part_lse, O, LSE, T, d, batch, s);
+}
+
 template <int D>
 static vxl_status run_decode_ring(const vxl_attn_desc* d, float scale, const void* Qd, int batch, int T,
                                   const void* Kmix, const void* Vmix, int l_cap, const int32_t* mix_len, void* O,
                                   float* LSE, void* ws, hipStream_t s, const RowMap* rm = nullptr) {
-    using C = DecodeRingCfg<D, 4>;
     const DecodePlan p = decode_plan(d, batch, T, l_cap, rm == nullptr);
     float* part_o = (float*)((char*)ws + p.part_o);
     float* part_lse = (float*)((char*)ws + p.part_ml);
-    const int group = d->n_q_heads / d->n_kv_heads;
-    const int n_rows = group * T;
-    const int n_rtile = (n_rows + C::RT - 1) / C::RT;
-    // One workgroup per compute unit: of the planned splits, which give every unit at least one, as many as run in
-    // one round (gather included: 896 rows on six KV heads, 264 workgroups of 11 splits 118 us, 240 of 10 103; D =
-    // 64, 700 rows on four, 264 workgroups 85, 252 62).
     int n_cus = 0;
     const vxl_status cst = device_cu_count(&n_cus);
     if (cst != VXL_OK) return cst;
-    const int per_split = n_rtile * d->n_kv_heads * batch;
-    const int n_split = std::max(1, std::min(p.n_split, n_cus / per_split));
-    static PerDeviceOnce attr;
-    const vxl_status ast = attr.run([] {
-        VXL_HIP_TRY(hipFuncSetAttribute((const void*)decode_ring_kernel<D, 4, false>,
-                                        hipFuncAttributeMaxDynamicSharedMemorySize, C::LDS_BYTES));
-        VXL_HIP_TRY(hipFuncSetAttribute((const void*)decode_ring_kernel<D, 4, false, true>,
-                                        hipFuncAttributeMaxDynamicSharedMemorySize, C::LDS_BYTES));
-        VXL_HIP_TRY(hipFuncSetAttribute((const void*)decode_ring_kernel<D, 4, true>,
-                                        hipFuncAttributeMaxDynamicSharedMemorySize, C::LDS_BYTES));
-        return VXL_OK;
-    });
-    if (ast != VXL_OK) return ast;
-    if (rm)
-        hipLaunchKernelGGL((decode_ring_kernel<D, 4, true>), dim3(n_split, n_rtile * d->n_kv_heads, batch),
-                           dim3(512), C::LDS_BYTES, s, (const uint16_t*)Qd, (const uint16_t*)Kmix,
-                           (const uint16_t*)Vmix, mix_len, part_o, part_lse, T, d->n_q_heads, d->n_kv_heads, group,
-                           l_cap, scale, *rm, (uint16_t*)O, LSE);
-    else
-        hipLaunchKernelGGL((n_rtile == 1 && beyond_l2(d, batch, l_cap) ? decode_ring_kernel<D, 4, false, true>
-                                                                       : decode_ring_kernel<D, 4, false>),
-                           dim3(n_split, n_rtile * d->n_kv_heads, batch),
-                           dim3(512), C::LDS_BYTES, s, (const uint16_t*)Qd, (const uint16_t*)Kmix,
-                           (const uint16_t*)Vmix, mix_len, part_o, part_lse, T, d->n_q_heads, d->n_kv_heads, group,
-                           l_cap, scale, RowMap{}, (uint16_t*)O, LSE);
-    VXL_HIP_TRY(hipGetLastError());
-    return launch_merge<D>(n_split, part_o, part_lse, O, LSE, T, d, batch, s);
+    const RingLaunch rl = choose_ring(d, batch, d->n_q_heads / d->n_kv_heads * T, l_cap, p.n_split, n_cus, rm != nullptr);
+    return rl.waves == 8
+               ? launch_ring<D, 8>(rl, d, scale, Qd, batch, T, Kmix, Vmix, l_cap, mix_len, O, LSE, part_o, part_lse, s, rm)
+               : launch_ring<D, 4>(rl, d, scale, Qd, batch, T, Kmix, Vmix, l_cap, mix_len, O, LSE, part_o, part_lse, s, rm);
 }
 
 template <int D>

@@ -99,6 +99,8 @@ def lib() -> C.CDLL:
     L.vxl_debug_decode_step_waves.argtypes = [C.c_int]
     L.vxl_debug_decode_plan.argtypes = [dp, C.c_int, C.c_int, C.c_int, C.c_int, C.POINTER(C.c_int)]
     L.vxl_debug_decode_plan.restype = C.c_int
+    L.vxl_debug_decode_ring_waves.argtypes = [dp, C.c_int, C.c_int, C.c_int, C.c_int]
+    L.vxl_debug_decode_ring_waves.restype = C.c_int
     L.vxl_debug_mfma_stream.argtypes = [vp, C.c_int, C.c_int, vp]
     L.vxl_debug_mfma_stream.restype = C.c_double
     L.vxl_debug_mfma_stream_random.argtypes = [vp, C.c_int, C.c_int, vp]
@@ -390,10 +392,15 @@ def debug_decode_step_waves(waves: int) -> None:
 
 
 def debug_decode_plan(desc: AttnDesc, batch: int, n_q_tokens: int, l_cap: int, in_place: bool = False):
-    """(kernel, key splits) of a BF16 decode call; kernel: 0 = 128-row, 1 = 256-row ring, 2 = 32-row blocks.  Needs no GPU."""
+    """(kernel, key splits) of a BF16 decode call; kernel: 0 = 128-row, 1 = ring, 2 = 32-row blocks.  Needs no GPU."""
     n_split = C.c_int(0)
     kernel = lib().vxl_debug_decode_plan(C.byref(desc), batch, n_q_tokens, l_cap, int(in_place), C.byref(n_split))
     return kernel, n_split.value
+
+
+def debug_decode_ring_waves(desc: AttnDesc, batch: int, n_q_tokens: int, l_cap: int, in_place: bool = False) -> int:
+    """Waves (8 or 4) of the ring's workgroups for such a call on 256 compute units.  Needs no GPU."""
+    return lib().vxl_debug_decode_ring_waves(C.byref(desc), batch, n_q_tokens, l_cap, int(in_place))
 
 
 def debug_prefill_variant(variant: int) -> None:

@@ -1,0 +1,69 @@
+"""The ring decode with eight and with four waves per workgroup, gathered and in place, against the oracle: rows at the
+edges of a wave's and a workgroup's rows, sets of few and of no keys, more splits than tiles, one split, both head
+dimensions."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from paper_2506_19225_amd import vxl, workloads as wl
+
+from gpu_util import DECODE_RING, assert_close, decode_kernel, desc_of, gpu_decode
+from test_gpu_inplace import check_case
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("hq,hkv,t,d,waves,lens,l_cap", [
+    (28, 4, 43, 128, 4, [5300, 0], 5300),                  # 301 rows: a last workgroup of 45, two waves without rows
+    (14, 2, 55, 128, 4, [9000, 130, 1], 9000),             # 385 rows: one in the last workgroup
+    (8, 1, 160, 128, 4, [5000, 4937, 63], 5000),           # 1,280: whole workgroups
+    (8, 1, 33, 64, 4, [9000, 64, 65], 9000),               # 264 rows, D = 64
+    (14, 2, 77, 64, 4, [3000, 2999, 1, 0], 3000),          # 539
+    (7, 1, 257, 128, 4, [70, 64, 1, 0] * 8, 70),           # 1,799 rows, one split
+    (28, 4, 36, 128, 8, [8000, 7937] * 4, 8000),           # 252 rows of eight queries: longer walks
+    (14, 2, 129, 64, 8, [30000, 29937], 30000)])
+def test_either_number_of_waves(hq, hkv, t, d, waves, lens, l_cap):
+    rng = np.random.default_rng(t + l_cap)
+    bsz = len(lens)
+    w = wl.tiny_workload("bf16", hq, hkv, d, T=t, B=bsz, k=1, seed=86)
+    assert decode_kernel(w, bsz, t, l_cap) == DECODE_RING
+    assert vxl.debug_decode_ring_waves(desc_of(w), bsz, t, l_cap) == waves
+    k, v = (torch.empty((bsz, hkv, l_cap, d), dtype=torch.bfloat16, device="cuda").normal_(0, 1) for _ in range(2))
+    qd = wl.round_to_bf16(rng.standard_normal((bsz, t, hq, d)).astype(np.float32) * np.float32(0.5))
+    for b, n in enumerate(lens):                           # what lies past a length is never used
+        k[b, :, n:] = float("nan")
+        v[b, :, n:] = float("nan")
+    dl = torch.tensor(lens, dtype=torch.int32, device="cuda")
+    got, lse = gpu_decode(w, qd, k, v, dl, want_lse=True)
+    again, _ = gpu_decode(w, qd, k, v, dl, want_lse=True)
+    assert np.array_equal(got, again)
+    live = np.array(lens) > 0
+    q = torch.from_numpy(qd).cuda().double()
+    g = hq // hkv
+    for b in np.flatnonzero(live):
+        for h in range(hkv):
+            s = q[b, :, h * g:(h + 1) * g].reshape(-1, d) @ k[b, h, :lens[b]].double().T / d ** 0.5
+            want = (torch.softmax(s, -1) @ v[b, h, :lens[b]].double()).reshape(t, g, d).cpu().numpy()
+            assert_close(got[b, :, h * g:(h + 1) * g], want, "bf16", head_axis=1, what=f"query {b}, {lens[b]} keys")
+            wlse = torch.logsumexp(s, -1).reshape(t, g).cpu().numpy()
+            assert np.abs(lse[b, :, h * g:(h + 1) * g] - wlse).max() < 2e-2
+    assert not got[~live].any() and np.isneginf(lse[~live]).all()
+
+
+@pytest.mark.parametrize("mode", ["kept_in_place", "pooled"])
+@pytest.mark.parametrize("hq,t,d,waves,chunks,length", [
+    (14, 150, 128, 4, 15, 800), (14, 300, 64, 4, 20, 800), (14, 55, 128, 8, 90, 900)])
+def test_either_number_of_waves_in_place(mode, hq, t, d, waves, chunks, length):
+    rng = np.random.default_rng(87 + t)
+    w = wl.tiny_workload("bf16", hq, 2, d, T=t, B=1, k=3, seed=87, value_scale=0.5)
+    lay = wl.random_layout(rng, 9, chunks, max(1, length // 2), length)
+    masks = np.ones((1, chunks), np.uint8)
+    masks[0, rng.choice(chunks, chunks // 4, replace=False)] = 0
+    desc = desc_of(w)
+    lengths = np.where(masks[0], np.diff(lay.chunk_bounds), np.diff(lay.sparse_offsets))
+    l_cap = int(lay.n_prefix + lengths.sum())
+    assert decode_kernel(w, 1, t, l_cap, True) == DECODE_RING
+    assert vxl.debug_decode_ring_waves(desc, 1, t, l_cap, True) == waves
+    _, k, v = wl.make_qkv(w, lay, with_q=False)
+    check_case(w, lay, k, v, wl.make_decode_queries(w), masks, mode, l_cap=l_cap)
