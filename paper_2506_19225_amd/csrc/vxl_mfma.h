@@ -157,27 +157,27 @@ __device__ __forceinline__ void qk_tile(const uint16_t* kt, const bf16x8 (&qreg)
 // then per step two matrix instructions followed by the two reads of step + AHEAD + 1.  Left to
 // itself the compiler reads an operand pair right before its two instructions and, depending on
 // unrelated code, waits for both reads before the first instruction.
-template <int D, int AHEAD>
+template <int D, int AHEAD, int KB = 2>
 __device__ __forceinline__ void qk_tile_ahead(const uint16_t* kt, const bf16x8 (&qreg)[1][D / 16], int l32, int hi,
-                                              f32x16 (&s)[1][2]) {
+                                              f32x16 (&s)[1][KB]) {
     constexpr int NK = D / 16;
-    s[0][0] = zero16();
-    s[0][1] = zero16();
-    bf16x8 a[NK][2];
+#pragma unroll
+    for (int kb = 0; kb < KB; ++kb) s[0][kb] = zero16();
+    bf16x8 a[NK][KB];
 #pragma unroll
     for (int ks = 0; ks < NK; ++ks)
 #pragma unroll
-        for (int kb = 0; kb < 2; ++kb) a[ks][kb] = *(const bf16x8*)(kt + k_tile_off<D>(kb * 32 + l32, ks * 2 + hi));
+        for (int kb = 0; kb < KB; ++kb) a[ks][kb] = *(const bf16x8*)(kt + k_tile_off<D>(kb * 32 + l32, ks * 2 + hi));
 #pragma unroll
     for (int ks = 0; ks < NK; ++ks)
 #pragma unroll
-        for (int kb = 0; kb < 2; ++kb)
+        for (int kb = 0; kb < KB; ++kb)
             s[0][kb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[ks][kb], qreg[0][ks], s[0][kb], 0, 0, 0);
-    __builtin_amdgcn_sched_group_barrier(0x100, 2 * (AHEAD + 1), 0);          // LDS reads
+    __builtin_amdgcn_sched_group_barrier(0x100, KB * (AHEAD + 1), 0);         // LDS reads
 #pragma unroll
     for (int ks = 0; ks < NK; ++ks) {
-        __builtin_amdgcn_sched_group_barrier(0x008, 2, 0);                    // matrix instructions
-        if (ks + AHEAD + 1 < NK) __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
+        __builtin_amdgcn_sched_group_barrier(0x008, KB, 0);                   // matrix instructions
+        if (ks + AHEAD + 1 < NK) __builtin_amdgcn_sched_group_barrier(0x100, KB, 0);
     }
 }
 
@@ -408,12 +408,12 @@ __device__ __forceinline__ void pv_tile(const uint16_t* vt, const bf16x8 (&pb)[Q
 // instructions before their use (two transposing reads per instruction).  The vector work the
 // compiler weaves in between (exponentials of later keys) is left where it puts it: a fixed share
 // after every matrix instruction measured 5 % slower.
-template <int D, int AHEAD>
-__device__ __forceinline__ void pv_tile_ahead(const uint16_t* vt, const bf16x8 (&pb)[1][2][2], int lane,
+template <int D, int AHEAD, int KB = 2>
+__device__ __forceinline__ void pv_tile_ahead(const uint16_t* vt, const bf16x8 (&pb)[1][KB][2], int lane,
                                               f32x16 (&o)[1][D / 32]) {
-    constexpr int NM = 4 * (D / 32);
+    constexpr int NM = 2 * KB * (D / 32);
 #pragma unroll
-    for (int kb = 0; kb < 2; ++kb)
+    for (int kb = 0; kb < KB; ++kb)
 #pragma unroll
         for (int j = 0; j < 2; ++j)
 #pragma unroll
