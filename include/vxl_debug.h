@@ -34,8 +34,8 @@ void vxl_debug_prefill_variant(int variant);
  * single-buffered waves, 4 = force the default.  Size the decode workspace after setting it. */
 void vxl_debug_decode_step_waves(int waves);
 
-/* Decode kernel that a BF16 call of these sizes takes: 0 = 128 rows per workgroup, 1 = the
- * ring, 2 = 32-row blocks whose waves own the keys (step mode).  n_split: the key splits that the workspace is
+/* Decode kernel that a BF16 call of these sizes takes: 0 = the ring with 128 rows per
+ * workgroup, 1 = the ring with 128 or 256, 2 = 32-row blocks whose waves own the keys (step mode).  n_split: the key splits that the workspace is
  * sized for (the ring launches no more of them than run in one round of the device's compute units).  Host only. */
 int vxl_debug_decode_plan(const vxl_attn_desc* desc, int batch, int n_q_tokens, int l_cap, int in_place,
                           int* n_split);

@@ -71,11 +71,9 @@ DecodePlan decode_plan(const vxl_attn_desc* d, int batch, int T, int l_cap, bool
     const int rows = (d->n_q_heads / d->n_kv_heads) * T;
     const int tiles = (l_cap + kKeyTile - 1) / kKeyTile;
     if (rows > kRowBlock) {
-        // 129-256 stacked rows fit one 256-row workgroup of the ring kernel or two 128-row workgroups
-        // of the 4-wave kernel.  The ring kernel streams better, but only when its launch covers the
-        // chip; at short mixed sets the split cap below leaves it a fraction of the compute units
-        // (measured at 224 rows: 64 and 120 workgroups, 4-wave kernel 9 % and 5 % faster; 176 and
-        // 256 workgroups, ring kernel 5 % and 8 % faster).
+        // The ring kernel, with 128 rows per workgroup or (use_ring) whichever of 128 and 256 is the shorter call: 129-256
+        // rows take the former where a launch of 256-row workgroups, whose splits the cap below holds, leaves compute
+        // units without any.
         bool ring = rows > 128;
         if (ring && rows <= 256) {
             const long blocks = (long)batch * d->n_kv_heads;
@@ -87,7 +85,7 @@ DecodePlan decode_plan(const vxl_attn_desc* d, int batch, int T, int l_cap, bool
         const int row_tile = ring ? 256 : 128;
         const int n_rtile = (rows + row_tile - 1) / row_tile;
         // Split the keys until every compute unit has its workgroups (one of the 8-wave ring kernel,
-        // two of the 4-wave kernel), but keep the partial results (fp32 rows per split) below roughly
+        // two planned of the 4-wave one), but keep the partial results (fp32 rows per split) below roughly
         // the KV bytes they summarise (measured at 224 rows over 4,096 keys: 16 splits 20.0 us per
         // call, 32 splits 21.3, 22 splits 21.2, 8 splits 24.0).
         const long base_blocks = (long)batch * d->n_kv_heads * n_rtile;
@@ -117,9 +115,8 @@ DecodePlan decode_plan(const vxl_attn_desc* d, int batch, int T, int l_cap, bool
         const int tpw = (int)((tiles32 + kWaves * n_split - 1) / (kWaves * n_split));
         n_split = (tiles32 + kWaves * tpw - 1) / (kWaves * tpw);
         // More than one row block: this form reads the mixed set once per block, but from the L2 of one
-        // XCD, and starts as fast as the one-row-block call; the 128-row kernel moves its tiles through
-        // registers and barriers.  (us per call, before -> with row blocks, G = 7, four KV heads; keys): 224
-        // rows, 4,096 keys 23.4 -> 18.0; 56 rows, 7,936 keys 23.8 -> 16.0 and 45,312 keys 49.8 -> 25.3; 112
+        // XCD, and starts as fast as the one-row-block call.  (us per call, by a 128-row kernel since replaced -> with row
+        // blocks, G = 7, four KV heads; keys): 224 rows, 4,096 keys 23.4 -> 18.0; 56 rows, 7,936 keys 23.8 -> 16.0 and 45,312 keys 49.8 -> 25.3; 112
         // rows, 45,312 keys 60.2 -> 33.0; in place, 224 rows, 4,096 keys (with pooling and map) 51.8 -> 43.4.
         // Up to 64 rows at one tile per wave the 128-row kernel stays (56 rows, 1,031 keys: 12.7 against 13.4).
         const bool fits = units * n_split * n_rtile <= 256 && (gathered || tpw <= 32);

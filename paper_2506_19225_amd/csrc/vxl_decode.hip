@@ -3,8 +3,7 @@
 //
 // The G*T query rows that share one KV head (G = query heads per KV head) are stacked along the
 // query dimension: row rho = t*G + hg.  A workgroup owns one (query b, KV head g, row tile,
-// key split) and streams its slice of Kmix/Vmix exactly once through LDS (64-key tiles, double
-// buffered, next tile prefetched into registers); every wave owns QB blocks of 32 query rows.
+// key split) and streams its slice of Kmix/Vmix exactly once through LDS.
 // Each workgroup writes a normalised partial output and the base-2 log-sum-exp of its scaled
 // logits; the merge kernel combines the splits of a row with weights and a summation order
 // that depend only on the split index, so the result does not depend on scheduling.
@@ -16,16 +15,6 @@
 namespace vxl {
 
 namespace {
-
-template <int D, int QB>
-struct DecodeCfg {
-    static constexpr int RT = 128 * QB;            // query rows per workgroup
-    static constexpr int KROW = LdsRows<D>::K;     // LDS row strides (elements)
-    static constexpr int VROW = LdsRows<D>::V;
-    static constexpr int K_ELEMS = kKeyTile * KROW;
-    static constexpr int V_ELEMS = kKeyTile * VROW;
-    static constexpr int LDS_BYTES = 2 * (K_ELEMS + V_ELEMS) * 2;
-};
 
 // Row map of the in-place form (IND instances of the kernels below): the mixed KV set is not a
 // buffer but a list of rows -- mixed row r of query b is token src_idx[b, r] of the dense K / V
@@ -54,7 +43,7 @@ __device__ __forceinline__ void store_row4(uint16_t* p, float a, float b, float 
     *(uint2*)p = some ? *(const uint2*)out : make_uint2(0, 0);
 }
 
-// The keys of a split in the two kernels of larger row counts: whole 64-key tiles, dealt out evenly by the length
+// The keys of a split in the ring kernel: whole 64-key tiles, dealt out evenly by the length
 // of the query's mixed set.  Cut by the capacity of its buffers, which variable chunk lengths leave partly empty,
 // the last splits of a query had no keys and the others more than their share: eight questions of 224 rows over
 // 25,500 of 35,410 rows (64 of 256 workgroups without keys), gather included, 285 -> 263 us.
@@ -67,160 +56,9 @@ __device__ __forceinline__ KeyRange split_keys(int len, int split, int n_split) 
     return {first * kKeyTile, min((first + per + (split < more ? 1 : 0)) * kKeyTile, len)};
 }
 
-template <int D, int QB, bool IND = false>
-__global__ __launch_bounds__(256, (QB == 1 ? 2 : 1)) void decode_split_kernel(
-    const uint16_t* __restrict__ Qd, const uint16_t* __restrict__ Kmix, const uint16_t* __restrict__ Vmix,
-    const int32_t* __restrict__ mix_len, float* __restrict__ part_o, float* __restrict__ part_lse, int T_q,
-    int n_q_heads, int n_kv_heads, int group, int l_cap, float scale, RowMap rm, uint16_t* __restrict__ O, float* __restrict__ LSE) {
-    using C = DecodeCfg<D, QB>;
-    extern __shared__ __attribute__((aligned(16))) uint16_t lds[];
-    uint16_t* Ks = lds;
-    uint16_t* Vs = lds + 2 * C::K_ELEMS;
-
-    const int tid = threadIdx.x, lane = tid & 63, l32 = lane & 31, hi = lane >> 5;
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);      // wave-uniform: scalar control flow
-    const int split = blockIdx.x, n_split = gridDim.x;
-    const int g = blockIdx.y % n_kv_heads, rt = blockIdx.y / n_kv_heads;
-    const int b = blockIdx.z;
-    const int n_rows = group * T_q;
-    const KeyRange keys = split_keys(min(max(mix_len[b], 0), l_cap), split, n_split);
-    const int k_lo = keys.lo, k_hi = keys.hi;
-    const int wrow0 = rt * C::RT + wave * 32 * QB;
-    const size_t part_base = (((size_t)b * n_kv_heads + g) * n_split + split) * (size_t)n_rows;
-
-    if (k_lo >= k_hi) {                            // empty split: only its weight (zero) is recorded
-        if (n_split > 1) {
-            for (int r = rt * C::RT + tid; r < min(n_rows, (rt + 1) * C::RT); r += 256) part_lse[part_base + r] = -INFINITY;
-        } else {
-            for (int e = tid; e < min(n_rows - rt * C::RT, C::RT) * (D / 4); e += 256) {
-                const int rho = rt * C::RT + e / (D / 4);
-                const size_t row = ((size_t)b * T_q + rho / group) * n_q_heads + g * group + rho % group;
-                store_row4(O + row * D + e % (D / 4) * 4, 0.f, 0.f, 0.f, 0.f, false);
-                if (LSE && e % (D / 4) == 0) LSE[row] = -INFINITY;
-            }
-        }
-        return;
-    }
-
-    bf16x8 qreg[QB][D / 16];
-#pragma unroll
-    for (int qb = 0; qb < QB; ++qb) {
-        const int rho = min(wrow0 + qb * 32 + l32, n_rows - 1);
-        const int t = rho / group, hg = rho % group;
-        const uint4* src = (const uint4*)(Qd + (((size_t)b * T_q + t) * n_q_heads + g * group + hg) * D);
-#pragma unroll
-        for (int ks = 0; ks < D / 16; ++ks) qreg[qb][ks] = __builtin_bit_cast(bf16x8, src[ks * 2 + hi]);
-    }
-    f32x16 o[QB][D / 32];
-    float m_run[QB], l_run[QB];
-#pragma unroll
-    for (int qb = 0; qb < QB; ++qb) {
-        m_run[qb] = -INFINITY;
-        l_run[qb] = 0.f;
-#pragma unroll
-        for (int db = 0; db < D / 32; ++db) o[qb][db] = zero16();
-    }
-    const float c2 = scale * kLog2e;
-    const bool wave_active = wrow0 < n_rows;       // waves without rows only help with the copies
-
-    // (IND: Kmix / Vmix are the dense K / V of the layer, read through the row map)
-    const char* kbase = IND ? (const char*)(Kmix + (size_t)g * rm.kv_head)
-                            : (const char*)(Kmix + ((size_t)b * n_kv_heads + g) * (size_t)l_cap * D);
-    const char* vbase = IND ? (const char*)(Vmix + (size_t)g * rm.kv_head)
-                            : (const char*)(Vmix + ((size_t)b * n_kv_heads + g) * (size_t)l_cap * D);
-    const long long ksp_delta = IND ? (const char*)(rm.Ksp + (size_t)g * rm.s_total * D) - kbase : 0;
-    const long long vsp_delta = IND ? (const char*)(rm.Vsp + (size_t)g * rm.s_total * D) - vbase : 0;
-    const int32_t* src_b = IND ? rm.src_idx + (size_t)b * l_cap : nullptr;
-    const int ld_r = tid / (D / 8), ld_part = tid % (D / 8);
-    TileRegs<D, C::VROW> tr;
-    const int n_t = (k_hi - k_lo + kKeyTile - 1) / kKeyTile;
-    // rows past the end of the split are clamped to its last row (scores masked, V finite)
-    // IND: the rows of tile t are fetched through the map entries loaded one call earlier, and the
-    // entries of tile t + 1 (clamped to the last tile) are requested in the same call
-    auto load_map = [&](int key0_) {
-        tr.load_map(src_b + key0_, ld_r, min(kKeyTile - 1, k_hi - 1 - key0_));
-    };
-    auto fetch = [&](int key0_, int key0_after_) {
-        const int rlim_ = min(kKeyTile - 1, k_hi - 1 - key0_);
-        if constexpr (IND) {
-            tr.fetch_mapped(kbase, vbase, ksp_delta, vsp_delta, rm.kv_tok * 2, ld_part);
-            load_map(key0_after_);
-        } else {
-            tr.fetch(kbase + (size_t)key0_ * (D * 2), vbase + (size_t)key0_ * (D * 2), ld_r, ld_part, rlim_);
-        }
-    };
-    if constexpr (IND) load_map(k_lo);
-    fetch(k_lo, k_lo + min(1, n_t - 1) * kKeyTile);
-    tr.stage(Ks, Vs, ld_r, ld_part);
-    __syncthreads();
-    for (int ti = 0; ti < n_t; ++ti) {
-        const int buf = ti & 1;
-        const int key0 = k_lo + ti * kKeyTile;
-        {   // next tile (the last iteration re-reads its own): unconditional, fenced, in flight below
-            fetch(k_lo + min(ti + 1, n_t - 1) * kKeyTile, k_lo + min(ti + 2, n_t - 1) * kKeyTile);
-            __builtin_amdgcn_sched_barrier(0);
-        }
-        if (wave_active) {
-            f32x16 s[QB][2];
-            qk_tile<D, QB, C::KROW>(Ks + buf * C::K_ELEMS, qreg, l32, hi, s);
-            if (key0 + kKeyTile > k_hi) {
-                const int lim = k_hi - key0 - 1;
-#pragma unroll
-                for (int qb = 0; qb < QB; ++qb)
-#pragma unroll
-                    for (int kb = 0; kb < 2; ++kb)
-#pragma unroll
-                        for (int r = 0; r < 16; ++r)
-                            s[qb][kb][r] = acc_key(kb, r, hi) <= lim ? s[qb][kb][r] : -INFINITY;
-            }
-            bf16x8 pb[QB][2][2];
-#pragma unroll
-            for (int qb = 0; qb < QB; ++qb)
-                softmax_tile<D / 32>(s[qb], c2, m_run[qb], l_run[qb], o[qb], pb[qb]);
-            pv_tile<D, QB, C::VROW>(Vs + buf * C::V_ELEMS, pb, lane, o);
-        }
-        tr.stage(Ks + (buf ^ 1) * C::K_ELEMS, Vs + (buf ^ 1) * C::V_ELEMS, ld_r, ld_part);
-        __syncthreads();
-    }
-
-    if (!wave_active) return;
-#pragma unroll
-    for (int qb = 0; qb < QB; ++qb) {
-        const int rho = wrow0 + qb * 32 + l32;
-        const float l_tot = l_run[qb] + __shfl_xor(l_run[qb], 32);
-        if (rho >= n_rows) continue;
-        const float inv = 1.f / l_tot, lse = m_run[qb] * c2 + __builtin_amdgcn_logf(l_tot);
-        if (n_split == 1) {
-            const size_t row = ((size_t)b * T_q + rho / group) * n_q_heads + g * group + rho % group;
-            const bool some = fabsf(lse) < INFINITY;
-#pragma unroll
-            for (int db = 0; db < D / 32; ++db)
-#pragma unroll
-                for (int rq = 0; rq < 4; ++rq)
-                    store_row4(O + row * D + db * 32 + rq * 8 + hi * 4, o[qb][db][rq * 4] * inv, o[qb][db][rq * 4 + 1] * inv,
-                               o[qb][db][rq * 4 + 2] * inv, o[qb][db][rq * 4 + 3] * inv, some);
-            if (LSE && hi == 0) LSE[row] = some ? lse * kLn2 : -INFINITY;
-            continue;
-        }
-        float* orow = part_o + (part_base + rho) * D;
-#pragma unroll
-        for (int db = 0; db < D / 32; ++db)
-#pragma unroll
-            for (int rq = 0; rq < 4; ++rq) {
-                float4 v;
-                v.x = o[qb][db][rq * 4 + 0] * inv;
-                v.y = o[qb][db][rq * 4 + 1] * inv;
-                v.z = o[qb][db][rq * 4 + 2] * inv;
-                v.w = o[qb][db][rq * 4 + 3] * inv;
-                *(float4*)(orow + db * 32 + rq * 8 + hi * 4) = v;
-            }
-        if (hi == 0) part_lse[part_base + rho] = lse;
-    }
-}
-
 // ------------------------------------------------------------------------------------------
-// Batched kernel for more than 128 stacked query rows: 32 rows per wave, 8 waves (two per SIMD) or 4 (one) per
-// workgroup (choose_ring draws the line), the split's 64-key tiles streamed into a ring of NS
+// Kernel of the calls with many stacked query rows: 32 rows per wave, 4 waves (one per SIMD) or, beyond 128 rows, 8 (two)
+// per workgroup (choose_ring draws the line), the split's 64-key tiles streamed into a ring of NS
 // LDS stages by direct global->LDS loads, two tiles ahead of the arithmetic -- the structure of
 // the streaming pre-filling kernel, without its causal part.
 // Eight waves are bound by matrix and vector issue with the clock they draw (1.6 us per tile), which a long split
@@ -232,7 +70,10 @@ __global__ __launch_bounds__(256, (QB == 1 ? 2 : 1)) void decode_split_kernel(
 // meeting per tile with three tiles ahead is no faster.  The loads are issued from inline
 // assembly and counted by hand (every wave issues the same number per tile and waits with
 // vmcnt = loads still allowed in flight), so the kernel must not spill, and the query registers
-// are forced complete before the first ring load.  Same partials as decode_split_kernel.
+// are forced complete before the first ring load.
+// Up to 128 rows, and up to 256 where a launch of eight waves is small, four waves took the place of a kernel that moved
+// its tiles through registers into two LDS buffers, two workgroups per compute unit: faster in all of 110 random calls
+// (D = 128: 49 rows, 3,982 keys 15.6 -> 13.3 us; 33 queries of 35 rows over 12,426 keys 417 -> 199).
 // ------------------------------------------------------------------------------------------
 template <int D, int NS, int NW>
 struct DecodeRingCfg {
@@ -382,7 +223,7 @@ __global__ __launch_bounds__(64 * NW, 2) void decode_ring_kernel(
         const int key0 = k_lo + ti * kKeyTile;
         f32x16 s[1][2];
         if constexpr (NW == 4) qk_tile_ahead<D, 1>(kt, qreg, l32, hi, s);
-        else qk_tile<D, 1, D>(kt, qreg, l32, hi, s);
+        else qk_tile<D, 1>(kt, qreg, l32, hi, s);
         if (key0 + kKeyTile > k_hi) {
             const int lim = k_hi - key0 - 1;
 #pragma unroll
@@ -393,7 +234,7 @@ __global__ __launch_bounds__(64 * NW, 2) void decode_ring_kernel(
         bf16x8 pb[1][2][2];
         softmax_tile<D / 32>(s[0], c2, m_run, l_run, o[0], pb[0]);
         if constexpr (NW == 4) pv_tile_ahead<D, 2>(kt + C::TILE, pb, lane, o);
-        else pv_tile<D, 1, D>(kt + C::TILE, pb, lane, o);
+        else pv_tile<D, 1>(kt + C::TILE, pb, lane, o);
     };
     for (int t0 = 0; t0 < n_t; t0 += TPB) {
         wait_vmcnt<0>();                                      // this wave's parts of tiles t0, t0+1 have landed
@@ -640,7 +481,7 @@ __global__ __launch_bounds__(64 * NW, 2) void decode_wave_kernel(
         // use them: 224 rows over 4,096 keys 14.2 -> 13.9 us, 112 over 10,000 15.1 -> 14.7; one row block, which waits for
         // memory, 0.99 to 1.01)
         if constexpr (ROWS) qk_tile_ahead<D, 3, 1>(kt, qreg, l32, hi, s);
-        else qk_tile<D, 1, D, 1>(kt, qreg, l32, hi, s);
+        else qk_tile<D, 1, 1>(kt, qreg, l32, hi, s);
         if (rlim < TK - 1) {
 #pragma unroll
             for (int r = 0; r < 16; ++r) s[0][0][r] = acc_key(0, r, hi) <= rlim ? s[0][0][r] : -INFINITY;
@@ -649,7 +490,7 @@ __global__ __launch_bounds__(64 * NW, 2) void decode_wave_kernel(
         if (ONE && !first) refer_to_tile<D / 32, 1>(s[0], c2, m_top, m_run, l_run, o[0]);
         softmax_tile<D / 32, 1>(s[0], c2, m_run, l_run, o[0], pb[0]);
         if constexpr (ROWS) pv_tile_ahead<D, 3, 1>(vt, pb, lane, o);
-        else pv_tile<D, 1, D, 1>(vt, pb, lane, o);
+        else pv_tile<D, 1, 1>(vt, pb, lane, o);
     };
     if constexpr (NBUF == 1) {
         for (int i = 0; i < tiles_per_wave; ++i) {
@@ -889,41 +730,7 @@ static vxl_status launch_merge(int n_split, const float* part_o, const float* pa
     return VXL_OK;
 }
 
-template <int D, int QB>
-static vxl_status run_decode(const vxl_attn_desc* d, float scale, const void* Qd, int batch, int T,
-                             const void* Kmix, const void* Vmix, int l_cap, const int32_t* mix_len, void* O,
-                             float* LSE, void* ws, hipStream_t s, const RowMap* rm = nullptr) {
-    using C = DecodeCfg<D, QB>;
-    const DecodePlan p = decode_plan(d, batch, T, l_cap, rm == nullptr);
-    float* part_o = (float*)((char*)ws + p.part_o);
-    float* part_lse = (float*)((char*)ws + p.part_ml);
-    const int group = d->n_q_heads / d->n_kv_heads;
-    const int n_rows = group * T;
-    const int n_rtile = (n_rows + C::RT - 1) / C::RT;
-    static PerDeviceOnce attr;
-    const vxl_status ast = attr.run([] {
-        VXL_HIP_TRY(hipFuncSetAttribute((const void*)decode_split_kernel<D, QB, false>,
-                                        hipFuncAttributeMaxDynamicSharedMemorySize, C::LDS_BYTES));
-        VXL_HIP_TRY(hipFuncSetAttribute((const void*)decode_split_kernel<D, QB, true>,
-                                        hipFuncAttributeMaxDynamicSharedMemorySize, C::LDS_BYTES));
-        return VXL_OK;
-    });
-    if (ast != VXL_OK) return ast;
-    if (rm)
-        hipLaunchKernelGGL((decode_split_kernel<D, QB, true>), dim3(p.n_split, n_rtile * d->n_kv_heads, batch),
-                           dim3(256), C::LDS_BYTES, s, (const uint16_t*)Qd, (const uint16_t*)Kmix,
-                           (const uint16_t*)Vmix, mix_len, part_o, part_lse, T, d->n_q_heads, d->n_kv_heads, group,
-                           l_cap, scale, *rm, (uint16_t*)O, LSE);
-    else
-        hipLaunchKernelGGL((decode_split_kernel<D, QB, false>), dim3(p.n_split, n_rtile * d->n_kv_heads, batch),
-                           dim3(256), C::LDS_BYTES, s, (const uint16_t*)Qd, (const uint16_t*)Kmix,
-                           (const uint16_t*)Vmix, mix_len, part_o, part_lse, T, d->n_q_heads, d->n_kv_heads, group,
-                           l_cap, scale, RowMap{}, (uint16_t*)O, LSE);
-    VXL_HIP_TRY(hipGetLastError());
-    return launch_merge<D>(p.n_split, part_o, part_lse, O, LSE, T, d, batch, s);
-}
-
-// How a call goes to the ring kernel of 8 or 4 waves (256 or 128 rows per workgroup).
+// How a call goes to the ring kernel of 8 or 4 waves (256 or 128 rows per workgroup; up to 128 rows always 4).
 struct RingLaunch {
     int waves, n_split, n_rtile;
     bool spread;                // no two workgroups on a compute unit
@@ -1016,7 +823,9 @@ static vxl_status run_decode_ring(const vxl_attn_desc* d, float scale, const voi
     int n_cus = 0;
     const vxl_status cst = device_cu_count(&n_cus);
     if (cst != VXL_OK) return cst;
-    const RingLaunch rl = choose_ring(d, batch, d->n_q_heads / d->n_kv_heads * T, l_cap, p.n_split, n_cus, rm != nullptr);
+    const int rows = d->n_q_heads / d->n_kv_heads * T;
+    const RingLaunch rl = p.use_ring ? choose_ring(d, batch, rows, l_cap, p.n_split, n_cus, rm != nullptr)
+                                     : ring_launch(d, batch, rows, l_cap, p.n_split, n_cus, 4, rm != nullptr);
     return rl.waves == 8
                ? launch_ring<D, 8>(rl, d, scale, Qd, batch, T, Kmix, Vmix, l_cap, mix_len, O, LSE, part_o, part_lse, s, rm)
                : launch_ring<D, 4>(rl, d, scale, Qd, batch, T, Kmix, Vmix, l_cap, mix_len, O, LSE, part_o, part_lse, s, rm);
@@ -1134,12 +943,9 @@ vxl_status launch_decode_bf16(const vxl_attn_desc* d, float scale, const void* Q
         return d->head_dim == 128
                    ? run_decode_wave<128>(d, scale, Qd, batch, T, Kmix, Vmix, l_cap, mix_len, O, LSE, ws, s)
                    : run_decode_wave<64>(d, scale, Qd, batch, T, Kmix, Vmix, l_cap, mix_len, O, LSE, ws, s);
-    const bool big = p.use_ring != 0;
-    if (d->head_dim == 128)
-        return big ? run_decode_ring<128>(d, scale, Qd, batch, T, Kmix, Vmix, l_cap, mix_len, O, LSE, ws, s)
-                   : run_decode<128, 1>(d, scale, Qd, batch, T, Kmix, Vmix, l_cap, mix_len, O, LSE, ws, s);
-    return big ? run_decode_ring<64>(d, scale, Qd, batch, T, Kmix, Vmix, l_cap, mix_len, O, LSE, ws, s)
-               : run_decode<64, 1>(d, scale, Qd, batch, T, Kmix, Vmix, l_cap, mix_len, O, LSE, ws, s);
+    return d->head_dim == 128
+               ? run_decode_ring<128>(d, scale, Qd, batch, T, Kmix, Vmix, l_cap, mix_len, O, LSE, ws, s)
+               : run_decode_ring<64>(d, scale, Qd, batch, T, Kmix, Vmix, l_cap, mix_len, O, LSE, ws, s);
 }
 
 // In-place form: K / V are the dense tensors of the layer, rows reached through src_idx.
@@ -1154,12 +960,9 @@ vxl_status launch_decode_bf16_inplace(const vxl_layout* L, const vxl_attn_desc* 
         return d->head_dim == 128
                    ? run_decode_wave<128>(d, scale, Qd, batch, T, K, V, l_cap, mix_len, O, LSE, ws, s, &rm)
                    : run_decode_wave<64>(d, scale, Qd, batch, T, K, V, l_cap, mix_len, O, LSE, ws, s, &rm);
-    const bool big = p.use_ring != 0;
-    if (d->head_dim == 128)
-        return big ? run_decode_ring<128>(d, scale, Qd, batch, T, K, V, l_cap, mix_len, O, LSE, ws, s, &rm)
-                   : run_decode<128, 1>(d, scale, Qd, batch, T, K, V, l_cap, mix_len, O, LSE, ws, s, &rm);
-    return big ? run_decode_ring<64>(d, scale, Qd, batch, T, K, V, l_cap, mix_len, O, LSE, ws, s, &rm)
-               : run_decode<64, 1>(d, scale, Qd, batch, T, K, V, l_cap, mix_len, O, LSE, ws, s, &rm);
+    return d->head_dim == 128
+               ? run_decode_ring<128>(d, scale, Qd, batch, T, K, V, l_cap, mix_len, O, LSE, ws, s, &rm)
+               : run_decode_ring<64>(d, scale, Qd, batch, T, K, V, l_cap, mix_len, O, LSE, ws, s, &rm);
 }
 
 }  // namespace vxl

@@ -185,7 +185,7 @@ vxl_status launch_pool_sparse(const vxl_layout* L, const vxl_attn_desc* d, const
 struct DecodePlan {
     int n_split;        // key splits per (batch, kv head)
     int split_len;      // keys per split (multiple of 64)
-    int use_ring;       // step_waves == 0: 1 = the 256-row ring kernel, 0 = the 128-row 4-wave kernel
+    int use_ring;       // step_waves == 0: the ring kernel, 0 = with 4 waves (128 rows), 1 = with 4 or 8
     int step_waves;     // step mode: waves per workgroup (8 single-buffered or 4 double-buffered); 0 = another kernel
     int one;            // step mode: one workgroup walks all keys of its rows, several tiles per wave
     size_t part_o;      // byte offsets into the workspace

@@ -25,18 +25,10 @@ typedef __attribute__((ext_vector_type(4))) short s16x4;
 typedef __attribute__((ext_vector_type(8))) short s16x8;
 typedef __attribute__((ext_vector_type(16))) float f32x16;
 
-// LDS row strides (in elements) of the row-major K and V tiles.  Measured on gfx950, the LDS
-// behaves as 32 banks of 8 bytes, each half-wave (lanes 0-31, lanes 32-63) served separately:
-// an access pattern runs at full rate when the 8-byte pieces touched by the 32 lanes of a
-// half-wave fall into distinct banks.  The K operand read (lane = row, 16 bytes at a common
-// column) needs an odd stride in 8-byte units: D*2 + 8 bytes.  The transposing V read (4 rows x
-// 64 contiguous bytes per half-wave) needs the stride to be 8 or 24 (mod 32) units: 320 bytes
-// for D = 128, 192 bytes for D = 64.
-template <int D> struct LdsRows {
-    static constexpr int K = D;                       // unpadded; pieces are XOR-swizzled instead
-    static constexpr int V = D == 128 ? 160 : 96;
-};
-
+// Measured on gfx950, the LDS behaves as 32 banks of 8 bytes, each half-wave (lanes 0-31, lanes 32-63) served
+// separately: an access pattern runs at full rate when the 8-byte pieces touched by the 32 lanes of a half-wave fall
+// into distinct banks.
+//
 // Element offset of 16-byte piece `piece` of row `row` in the K tile.  Rows are unpadded (so
 // every piece stays 16-byte aligned) and the piece index is XOR-ed with the row's position
 // inside a group of 16 256-byte lines: the 32 rows a half-wave reads at one logical piece then
@@ -47,75 +39,6 @@ __device__ __forceinline__ int k_tile_off(int row, int piece) {
     constexpr int RPL = 16 / PPR;                     // rows per 256-byte line
     return row * D + ((piece ^ ((row / RPL) & (PPR - 1))) << 3);
 }
-
-// Register staging of one 64-key K tile and V tile by a 256-thread workgroup: every thread
-// carries D/32 16-byte pieces of each.  The pieces are named members, not an array: they have to
-// live in VGPRs across a scheduling fence between the global loads and the LDS stores.
-template <int D, int VROW>
-struct TileRegs {
-    static constexpr int LD = D / 32;
-    static constexpr int RPP = 256 / (D / 8);         // rows covered by one pass of the 256 threads
-    uint4 k0, k1, k2, k3, v0, v1, v2, v3;
-
-    // kb / vb: wave-uniform byte pointers to row 0 of the tile; rows beyond rlim are clamped to it
-    // (the caller masks their scores; a clamped V row is finite, so 0 * v stays 0).
-    __device__ __forceinline__ void fetch(const char* kb, const char* vb, int ld_r, int ld_part, int rlim) {
-#define VXL_TILE_OFF(i_) ((uint32_t)min(ld_r + (i_) * RPP, rlim) * (D * 2) + ld_part * 16)
-        k0 = *(const uint4*)(kb + VXL_TILE_OFF(0));
-        v0 = *(const uint4*)(vb + VXL_TILE_OFF(0));
-        k1 = *(const uint4*)(kb + VXL_TILE_OFF(1));
-        v1 = *(const uint4*)(vb + VXL_TILE_OFF(1));
-        if constexpr (LD > 2) {
-            k2 = *(const uint4*)(kb + VXL_TILE_OFF(2));
-            v2 = *(const uint4*)(vb + VXL_TILE_OFF(2));
-            k3 = *(const uint4*)(kb + VXL_TILE_OFF(3));
-            v3 = *(const uint4*)(vb + VXL_TILE_OFF(3));
-        }
-#undef VXL_TILE_OFF
-    }
-    // The same for rows reached through a row map: tile row r is token src[r] of the dense tensors
-    // (rows kv_tok_bytes apart from kd / vd) or, if src[r] < 0, row -1 - src[r] of the sparse
-    // buffers (rows D * 2 bytes apart, ks_delta / vs_delta bytes from kd / vd).  The map entries of a
-    // tile are requested one tile before its rows (load_map), so that the two dependent loads of a
-    // row do not both fall into one tile's arithmetic.  src points at the tile's first entry.
-    int m0_, m1_, m2_, m3_;
-    __device__ __forceinline__ void load_map(const int32_t* src, int ld_r, int rlim) {
-        m0_ = src[min(ld_r, rlim)];
-        m1_ = src[min(ld_r + RPP, rlim)];
-        if constexpr (LD > 2) {
-            m2_ = src[min(ld_r + 2 * RPP, rlim)];
-            m3_ = src[min(ld_r + 3 * RPP, rlim)];
-        }
-    }
-    __device__ __forceinline__ void fetch_mapped(const char* kd, const char* vd, long long ks_delta,
-                                                 long long vs_delta, long long kv_tok_bytes, int ld_part) {
-#define VXL_TILE_ROW(t_, k_, v_)                                                                      \
-        do {                                                                                          \
-            const long long r_ = (t_) >= 0 ? (long long)(t_) * kv_tok_bytes : (long long)(-1 - (t_)) * (D * 2); \
-            k_ = *(const uint4*)(kd + ((t_) >= 0 ? 0 : ks_delta) + r_ + ld_part * 16);                \
-            v_ = *(const uint4*)(vd + ((t_) >= 0 ? 0 : vs_delta) + r_ + ld_part * 16);                \
-        } while (0)
-        VXL_TILE_ROW(m0_, k0, v0);
-        VXL_TILE_ROW(m1_, k1, v1);
-        if constexpr (LD > 2) {
-            VXL_TILE_ROW(m2_, k2, v2);
-            VXL_TILE_ROW(m3_, k3, v3);
-        }
-#undef VXL_TILE_ROW
-    }
-    __device__ __forceinline__ void stage(uint16_t* kt, uint16_t* vt, int ld_r, int ld_part) const {
-        *(uint4*)(kt + k_tile_off<D>(ld_r, ld_part)) = k0;
-        *(uint4*)(vt + ld_r * VROW + ld_part * 8) = v0;
-        *(uint4*)(kt + k_tile_off<D>(ld_r + RPP, ld_part)) = k1;
-        *(uint4*)(vt + (ld_r + RPP) * VROW + ld_part * 8) = v1;
-        if constexpr (LD > 2) {
-            *(uint4*)(kt + k_tile_off<D>(ld_r + 2 * RPP, ld_part)) = k2;
-            *(uint4*)(vt + (ld_r + 2 * RPP) * VROW + ld_part * 8) = v2;
-            *(uint4*)(kt + k_tile_off<D>(ld_r + 3 * RPP, ld_part)) = k3;
-            *(uint4*)(vt + (ld_r + 3 * RPP) * VROW + ld_part * 8) = v3;
-        }
-    }
-};
 
 constexpr int kKeyTileRows = 64;                    // keys per tile (same as kKeyTile)
 constexpr float kLog2e = 1.4426950408889634f;
@@ -134,7 +57,7 @@ __device__ __forceinline__ constexpr int acc_key(int kb, int r, int hi) {
 }
 
 // S^T[qb][kb] = K tile (64 keys, row-major in LDS, pieces placed by k_tile_off) times Q^T.
-template <int D, int QB, int KROW, int KB = 2>
+template <int D, int QB, int KB = 2>
 __device__ __forceinline__ void qk_tile(const uint16_t* kt, const bf16x8 (&qreg)[QB][D / 16], int l32,
                                         int hi, f32x16 (&s)[QB][KB]) {
 #pragma unroll
@@ -267,22 +190,16 @@ __device__ __forceinline__ int v_tile_off(int row, int piece) {
 }
 
 // A operand of the second product for the 16-key step (kb, j) and the 32-wide d block db, read
-// transposed from a row-major V tile in LDS: row stride VROW elements when VROW > D (padded
-// layout), or the unpadded swizzled layout of v_tile_off when VROW == D.
-template <int D, int VROW>
+// transposed from a row-major V tile in LDS (the layout of v_tile_off).
+template <int D>
 __device__ __forceinline__ bf16x8 load_vt_operand(const uint16_t* vt, int kb, int j, int db, int lane) {
     const int hi = lane >> 5, dhalf = (lane >> 4) & 1, s = lane & 15;
     const int row = kb * 32 + j * 16 + 4 * hi + (s >> 2);
-    const uint16_t* p;
-    if constexpr (VROW == D) {
-        constexpr int CPR = D * 2 / 64, RPL = D == 128 ? 1 : 2;
-        p = vt + row * D + ((db ^ ((row / RPL) & (CPR - 1))) << 5) + dhalf * 16 + 4 * (s & 3);
-    } else {
-        p = vt + row * VROW + db * 32 + dhalf * 16 + 4 * (s & 3);
-    }
+    constexpr int CPR = D * 2 / 64, RPL = D == 128 ? 1 : 2;
+    const uint16_t* p = vt + row * D + ((db ^ ((row / RPL) & (CPR - 1))) << 5) + dhalf * 16 + 4 * (s & 3);
     typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
     const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)p);
-    const s16x4 hi4 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)(p + 8 * VROW));   // row + 8: same swizzle
+    const s16x4 hi4 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)(p + 8 * D));   // row + 8: same swizzle
     const s16x8 both = __builtin_shufflevector(lo, hi4, 0, 1, 2, 3, 4, 5, 6, 7);
     return __builtin_bit_cast(bf16x8, both);
 }
@@ -388,7 +305,7 @@ __device__ __forceinline__ void lds_read_i32_hidden(uint32_t byte_addr, uint32_t
 }
 
 // O^T[qb][db] += V^T . P^T over the 64 keys of the tile.
-template <int D, int QB, int VROW, int KB = 2>
+template <int D, int QB, int KB = 2>
 __device__ __forceinline__ void pv_tile(const uint16_t* vt, const bf16x8 (&pb)[QB][KB][2], int lane,
                                         f32x16 (&o)[QB][D / 32]) {
 #pragma unroll
@@ -397,7 +314,7 @@ __device__ __forceinline__ void pv_tile(const uint16_t* vt, const bf16x8 (&pb)[Q
         for (int j = 0; j < 2; ++j)
 #pragma unroll
             for (int db = 0; db < D / 32; ++db) {
-                const bf16x8 a = load_vt_operand<D, VROW>(vt, kb, j, db, lane);
+                const bf16x8 a = load_vt_operand<D>(vt, kb, j, db, lane);
 #pragma unroll
                 for (int qb = 0; qb < QB; ++qb)
                     o[qb][db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, pb[qb][kb][j], o[qb][db], 0, 0, 0);
@@ -418,7 +335,7 @@ __device__ __forceinline__ void pv_tile_ahead(const uint16_t* vt, const bf16x8 (
         for (int j = 0; j < 2; ++j)
 #pragma unroll
             for (int db = 0; db < D / 32; ++db) {
-                const bf16x8 a = load_vt_operand<D, D>(vt, kb, j, db, lane);
+                const bf16x8 a = load_vt_operand<D>(vt, kb, j, db, lane);
                 o[0][db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, pb[0][kb][j], o[0][db], 0, 0, 0);
             }
     __builtin_amdgcn_sched_group_barrier(0x100, 2 * (AHEAD + 1), 1);

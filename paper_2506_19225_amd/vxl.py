@@ -392,7 +392,7 @@ def debug_decode_step_waves(waves: int) -> None:
 
 
 def debug_decode_plan(desc: AttnDesc, batch: int, n_q_tokens: int, l_cap: int, in_place: bool = False):
-    """(kernel, key splits) of a BF16 decode call; kernel: 0 = 128-row, 1 = ring, 2 = 32-row blocks.  Needs no GPU."""
+    """(kernel, key splits) of a BF16 decode call; kernel: 0 = ring of 128 rows, 1 = of 128 or 256, 2 = 32-row blocks.  Needs no GPU."""
     n_split = C.c_int(0)
     kernel = lib().vxl_debug_decode_plan(C.byref(desc), batch, n_q_tokens, l_cap, int(in_place), C.byref(n_split))
     return kernel, n_split.value

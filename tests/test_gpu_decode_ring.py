@@ -8,7 +8,7 @@ import torch
 import oracle
 from paper_2506_19225_amd import vxl, workloads as wl
 
-from gpu_util import DECODE_RING, assert_close, decode_kernel, desc_of, gpu_decode
+from gpu_util import DECODE_128, DECODE_RING, assert_close, decode_kernel, desc_of, gpu_decode
 from test_gpu_inplace import check_case
 
 pytestmark = pytest.mark.gpu
@@ -22,13 +22,17 @@ pytestmark = pytest.mark.gpu
     (14, 2, 77, 64, 4, [3000, 2999, 1, 0], 3000),          # 539
     (7, 1, 257, 128, 4, [70, 64, 1, 0] * 8, 70),           # 1,799 rows, one split
     (28, 4, 36, 128, 8, [8000, 7937] * 4, 8000),           # 252 rows of eight queries: longer walks
-    (14, 2, 129, 64, 8, [30000, 29937], 30000)])
+    (14, 2, 129, 64, 8, [30000, 29937], 30000),
+    (28, 4, 5, 128, 4, [1500, 0, 64, 65] * 6, 1500),       # 35 rows: two waves without any
+    (28, 4, 18, 64, 4, [777, 1, 63] * 9, 777),             # 126 rows
+    (14, 2, 19, 128, 4, [200, 129] * 17, 200)])            # 133 rows in two workgroups, one split
 def test_either_number_of_waves(hq, hkv, t, d, waves, lens, l_cap):
     rng = np.random.default_rng(t + l_cap)
     bsz = len(lens)
     w = wl.tiny_workload("bf16", hq, hkv, d, T=t, B=bsz, k=1, seed=86)
-    assert decode_kernel(w, bsz, t, l_cap) == DECODE_RING
-    assert vxl.debug_decode_ring_waves(desc_of(w), bsz, t, l_cap) == waves
+    kernel = decode_kernel(w, bsz, t, l_cap)
+    assert kernel in (DECODE_128, DECODE_RING)
+    assert (4 if kernel == DECODE_128 else vxl.debug_decode_ring_waves(desc_of(w), bsz, t, l_cap)) == waves
     k, v = (torch.empty((bsz, hkv, l_cap, d), dtype=torch.bfloat16, device="cuda").normal_(0, 1) for _ in range(2))
     qd = wl.round_to_bf16(rng.standard_normal((bsz, t, hq, d)).astype(np.float32) * np.float32(0.5))
     for b, n in enumerate(lens):                           # what lies past a length is never used
