@@ -23,7 +23,7 @@ pytestmark = pytest.mark.gpu
     (7, 1, 257, 128, 4, [70, 64, 1, 0] * 8, 70),           # 1,799 rows, one split
     (28, 4, 36, 128, 8, [8000, 7937] * 4, 8000),           # 252 rows of eight queries: longer walks
     (14, 2, 129, 64, 8, [30000, 29937], 30000),
-    (28, 4, 5, 128, 4, [1500, 0, 64, 65] * 6, 1500),       # 35 rows: two waves without any
+    (28, 4, 5, 128, 4, [1500, 0, 64, 65] * 9, 1500),       # 35 rows: two waves without any
     (28, 4, 18, 64, 4, [777, 1, 63] * 9, 777),             # 126 rows
     (14, 2, 19, 128, 4, [200, 129] * 17, 200)])            # 133 rows in two workgroups, one split
 def test_either_number_of_waves(hq, hkv, t, d, waves, lens, l_cap):
