@@ -65,11 +65,14 @@ PrefillWorkspace prefill_workspace(const vxl_layout* L, const vxl_attn_desc* d) 
 static std::atomic<int> g_decode_step_waves{0};     // cross-check hook (vxl_debug.h): 0 = choose, 4 or 8 = force
 extern "C" void vxl_debug_decode_step_waves(int w) { g_decode_step_waves = (w == 4 || w == 8) ? w : 0; }
 
-DecodePlan decode_plan(const vxl_attn_desc* d, int batch, int T, int l_cap, bool gathered) {
+DecodePlan decode_plan(const vxl_attn_desc* d, int batch, int T, int l_cap, bool gathered, size_t have) {
     DecodePlan p{};
     if (d->dtype != VXL_BF16) return decode_f32_plan(d, batch, T, l_cap);
     const int rows = (d->n_q_heads / d->n_kv_heads) * T;
     const int tiles = (l_cap + kKeyTile - 1) / kKeyTile;
+    const auto part_o_bytes = [&](int n_split) { return align_up((size_t)batch * d->n_kv_heads * n_split * rows * d->head_dim * sizeof(float), 256); };
+    const auto part_l_bytes = [&](int n_split) { return align_up((size_t)batch * d->n_kv_heads * n_split * rows * sizeof(float), 256); };
+    const auto partials = [&](int n_split) { return part_o_bytes(n_split) + part_l_bytes(n_split); };
     if (rows > kRowBlock) {
         // The ring kernel, with 128 rows per workgroup or (use_ring) whichever of 128 and 256 is the shorter call: 129-256
         // rows take the former where a launch of 256-row workgroups, whose splits the cap below holds, leaves compute
@@ -150,6 +153,21 @@ DecodePlan decode_plan(const vxl_attn_desc* d, int batch, int T, int l_cap, bool
         const bool d64 = d->head_dim == 64;
         const int one = d64 && rows > kRowBlock && rows <= 64 ? 12 : gathered ? (d64 ? 24 : 16) : (d64 ? 16 : 12);
         const bool single = rows <= 256 && tiles32 <= one && units * n_rtile <= 256;
+        // Where a wave would walk many tiles, the ring with 128 rows per workgroup: it has four times the keys in flight that
+        // row blocks sharing them have, and reads them once.  From 20 tiles per wave on, D = 64 28 and more than 64 rows
+        // (blocks -> ring, us: 70 rows, 50,500 keys, 20 tiles 34.1 -> 32.0; 8 queries of 91 rows, 34,847 keys, 136 tiles 168.6
+        // -> 104.7; D = 64, 8 of 70, 7,795 keys, 30 tiles 27.0 -> 22.7; but 91 rows, 38,299 keys, 15 tiles 28.1 against 29.1, 49
+        // rows, 19 tiles 36.7 and 37.1, D = 64, 8 of 35 rows, 42 tiles 38.6 and 40.6).  As many splits as give every
+        // compute unit a workgroup, if the scratch memory holds them.
+        if (!p.use_ring && fits && few && !single && rows > (d64 ? 64 : kRowBlock) && tpw >= (d64 ? 28 : 20)) {
+            const long base_blocks = units * ((rows + 127) / 128);
+            const int want = (int)std::max<long>(1, std::min<long>(p.n_split, 256 / base_blocks));
+            if (partials(want) <= have) {
+                p.n_split = want;
+                p.split_len = (tiles + want - 1) / want * kKeyTile;
+                few = false;
+            }
+        }
         if (rows <= kRowBlock || (fits && few) || single) {
             p.use_ring = 0;
             p.step_waves = kWaves;
@@ -158,12 +176,9 @@ DecodePlan decode_plan(const vxl_attn_desc* d, int batch, int T, int l_cap, bool
             p.split_len = kWaves * (single ? (tiles32 + kWaves - 1) / kWaves : tpw) * kTile;
         }
     }
-    size_t off = 0;
-    p.part_o = off;
-    off += align_up((size_t)batch * d->n_kv_heads * p.n_split * rows * d->head_dim * sizeof(float), 256);
-    p.part_ml = off;
-    off += align_up((size_t)batch * d->n_kv_heads * p.n_split * rows * sizeof(float), 256);
-    p.total = off;
+    p.part_o = 0;
+    p.part_ml = part_o_bytes(p.n_split);
+    p.total = partials(p.n_split);
     return p;
 }
 
@@ -573,9 +588,9 @@ vxl_status vxl_bilevel_decode(const vxl_attn_desc* d, const void* Qd, int32_t ba
     if (!aligned16(Qd) || !aligned16(Kmix) || !aligned16(Vmix) || !aligned16(O)) return VXL_ERR_INVALID_ARG;
     const float scale = resolve_scale(d);
     if (d->dtype == VXL_BF16 && !g_force_simple) {
-        const size_t need = decode_plan(d, batch, n_q_tokens, l_cap).total;
-        if (!workspace || workspace_bytes < need || !aligned16(workspace)) return VXL_ERR_WORKSPACE;
-        return launch_decode_bf16(d, scale, Qd, batch, n_q_tokens, Kmix, Vmix, l_cap, mix_len, O,
+        const DecodePlan p = decode_plan(d, batch, n_q_tokens, l_cap, true, workspace_bytes);
+        if (!workspace || workspace_bytes < p.total || !aligned16(workspace)) return VXL_ERR_WORKSPACE;
+        return launch_decode_bf16(p, d, scale, Qd, batch, n_q_tokens, Kmix, Vmix, l_cap, mix_len, O,
                                   LSE, workspace, (hipStream_t)stream);
     }
     if (d->dtype == VXL_F32)
@@ -602,7 +617,8 @@ vxl_status vxl_bilevel_decode_inplace(const vxl_layout* L, const vxl_attn_desc* 
     if (l_cap < vxl_mixed_kv_capacity(L, 0)) return VXL_ERR_INVALID_ARG;
     const InplaceWorkspace w = inplace_workspace(d, batch, n_q_tokens, l_cap);
     // (fp32: the row map is needed, room for partial results is not)
-    const size_t need = d->dtype == VXL_F32 ? w.partials + 256 : w.total;
+    const DecodePlan p = decode_plan(d, batch, n_q_tokens, l_cap, false, workspace_bytes > w.partials ? workspace_bytes - w.partials : 0);
+    const size_t need = w.partials + (d->dtype == VXL_F32 ? 256 : align_up(std::max<size_t>(256, p.total), 256));
     if (!workspace || workspace_bytes < need || !aligned16(workspace)) return VXL_ERR_WORKSPACE;
     hipStream_t s = (hipStream_t)stream;
     int32_t* src_idx = (int32_t*)((char*)workspace + w.src_idx);
@@ -615,7 +631,7 @@ vxl_status vxl_bilevel_decode_inplace(const vxl_layout* L, const vxl_attn_desc* 
     }
     const float scale = resolve_scale(d);
     if (d->dtype == VXL_BF16 && !g_force_simple)
-        return launch_decode_bf16_inplace(L, d, scale, Qd, batch, n_q_tokens, K, V, Ksp, Vsp, src_idx, l_cap, len, O,
+        return launch_decode_bf16_inplace(p, L, d, scale, Qd, batch, n_q_tokens, K, V, Ksp, Vsp, src_idx, l_cap, len, O,
                                           LSE, (char*)workspace + w.partials, s);
     if (d->dtype == VXL_F32)
         return launch_decode_f32_inplace(L, d, scale, Qd, batch, n_q_tokens, K, V, Ksp, Vsp, src_idx, l_cap, len, O, LSE,
@@ -635,17 +651,17 @@ vxl_status vxl_bilevel_decode_static(const vxl_attn_desc* d, const void* Qd, int
     if (!aligned16(Qd) || !aligned16(Kmix) || !aligned16(Vmix) || !aligned16(O)) return VXL_ERR_INVALID_ARG;
     const float scale = resolve_scale(d);
     if (d->dtype == VXL_BF16 && !g_force_simple) {
-        const size_t need = decode_plan(d, batch, n_q_tokens, l_cap).total;
-        if (need > (size_t)VXL_STATIC_SCRATCH_BYTES) {
+        const DecodePlan p = decode_plan(d, batch, n_q_tokens, l_cap, true, VXL_STATIC_SCRATCH_BYTES);
+        if (p.total > (size_t)VXL_STATIC_SCRATCH_BYTES) {
             snprintf(g_last_error, sizeof(g_last_error),
                      "vxl_bilevel_decode_static: the split-KV partial results of this call need %zu bytes, the "
-                     "static scratch holds %zu", need, (size_t)VXL_STATIC_SCRATCH_BYTES);
+                     "static scratch holds %zu", p.total, (size_t)VXL_STATIC_SCRATCH_BYTES);
             return VXL_ERR_WORKSPACE;
         }
         void* ws = nullptr;
         st = decode_static_scratch(&ws);
         if (st != VXL_OK) return st;
-        return launch_decode_bf16(d, scale, Qd, batch, n_q_tokens, Kmix, Vmix, l_cap, mix_len, O, LSE, ws,
+        return launch_decode_bf16(p, d, scale, Qd, batch, n_q_tokens, Kmix, Vmix, l_cap, mix_len, O, LSE, ws,
                                   (hipStream_t)stream);
     }
     if (d->dtype == VXL_F32) {

@@ -814,10 +814,9 @@ static vxl_status launch_ring(const RingLaunch& rl, const vxl_attn_desc* d, floa
 }
 
 template <int D>
-static vxl_status run_decode_ring(const vxl_attn_desc* d, float scale, const void* Qd, int batch, int T,
+static vxl_status run_decode_ring(const DecodePlan& p, const vxl_attn_desc* d, float scale, const void* Qd, int batch, int T,
                                   const void* Kmix, const void* Vmix, int l_cap, const int32_t* mix_len, void* O,
                                   float* LSE, void* ws, hipStream_t s, const RowMap* rm = nullptr) {
-    const DecodePlan p = decode_plan(d, batch, T, l_cap, rm == nullptr);
     float* part_o = (float*)((char*)ws + p.part_o);
     float* part_lse = (float*)((char*)ws + p.part_ml);
     int n_cus = 0;
@@ -832,10 +831,9 @@ static vxl_status run_decode_ring(const vxl_attn_desc* d, float scale, const voi
 }
 
 template <int D>
-static vxl_status run_decode_wave(const vxl_attn_desc* d, float scale, const void* Qd, int batch, int T,
+static vxl_status run_decode_wave(const DecodePlan& p, const vxl_attn_desc* d, float scale, const void* Qd, int batch, int T,
                                   const void* Kmix, const void* Vmix, int l_cap, const int32_t* mix_len, void* O,
                                   float* LSE, void* ws, hipStream_t s, const RowMap* rm = nullptr) {
-    const DecodePlan p = decode_plan(d, batch, T, l_cap, rm == nullptr);
     float* part_o = (float*)((char*)ws + p.part_o);
     float* part_lse = (float*)((char*)ws + p.part_ml);
     const int group = d->n_q_heads / d->n_kv_heads;
@@ -935,34 +933,32 @@ vxl_status decode_static_scratch(void** ptr) {
     return VXL_OK;
 }
 
-vxl_status launch_decode_bf16(const vxl_attn_desc* d, float scale, const void* Qd, int batch, int T,
+vxl_status launch_decode_bf16(const DecodePlan& p, const vxl_attn_desc* d, float scale, const void* Qd, int batch, int T,
                               const void* Kmix, const void* Vmix, int l_cap, const int32_t* mix_len, void* O,
                               float* LSE, void* ws, hipStream_t s) {
-    const DecodePlan p = decode_plan(d, batch, T, l_cap);
     if (p.step_waves != 0)
         return d->head_dim == 128
-                   ? run_decode_wave<128>(d, scale, Qd, batch, T, Kmix, Vmix, l_cap, mix_len, O, LSE, ws, s)
-                   : run_decode_wave<64>(d, scale, Qd, batch, T, Kmix, Vmix, l_cap, mix_len, O, LSE, ws, s);
+                   ? run_decode_wave<128>(p, d, scale, Qd, batch, T, Kmix, Vmix, l_cap, mix_len, O, LSE, ws, s)
+                   : run_decode_wave<64>(p, d, scale, Qd, batch, T, Kmix, Vmix, l_cap, mix_len, O, LSE, ws, s);
     return d->head_dim == 128
-               ? run_decode_ring<128>(d, scale, Qd, batch, T, Kmix, Vmix, l_cap, mix_len, O, LSE, ws, s)
-               : run_decode_ring<64>(d, scale, Qd, batch, T, Kmix, Vmix, l_cap, mix_len, O, LSE, ws, s);
+               ? run_decode_ring<128>(p, d, scale, Qd, batch, T, Kmix, Vmix, l_cap, mix_len, O, LSE, ws, s)
+               : run_decode_ring<64>(p, d, scale, Qd, batch, T, Kmix, Vmix, l_cap, mix_len, O, LSE, ws, s);
 }
 
 // In-place form: K / V are the dense tensors of the layer, rows reached through src_idx.
-vxl_status launch_decode_bf16_inplace(const vxl_layout* L, const vxl_attn_desc* d, float scale, const void* Qd,
+vxl_status launch_decode_bf16_inplace(const DecodePlan& p, const vxl_layout* L, const vxl_attn_desc* d, float scale, const void* Qd,
                                       int batch, int T, const void* K, const void* V, const void* Ksp,
                                       const void* Vsp, const int32_t* src_idx, int l_cap, const int32_t* mix_len,
                                       void* O, float* LSE, void* ws, hipStream_t s) {
     const TokStrides ts = tok_strides(d, L->n_tokens);
     const RowMap rm{src_idx, (const uint16_t*)Ksp, (const uint16_t*)Vsp, ts.kh, ts.kt, L->s_total};
-    const DecodePlan p = decode_plan(d, batch, T, l_cap, false);
     if (p.step_waves != 0)
         return d->head_dim == 128
-                   ? run_decode_wave<128>(d, scale, Qd, batch, T, K, V, l_cap, mix_len, O, LSE, ws, s, &rm)
-                   : run_decode_wave<64>(d, scale, Qd, batch, T, K, V, l_cap, mix_len, O, LSE, ws, s, &rm);
+                   ? run_decode_wave<128>(p, d, scale, Qd, batch, T, K, V, l_cap, mix_len, O, LSE, ws, s, &rm)
+                   : run_decode_wave<64>(p, d, scale, Qd, batch, T, K, V, l_cap, mix_len, O, LSE, ws, s, &rm);
     return d->head_dim == 128
-               ? run_decode_ring<128>(d, scale, Qd, batch, T, K, V, l_cap, mix_len, O, LSE, ws, s, &rm)
-               : run_decode_ring<64>(d, scale, Qd, batch, T, K, V, l_cap, mix_len, O, LSE, ws, s, &rm);
+               ? run_decode_ring<128>(p, d, scale, Qd, batch, T, K, V, l_cap, mix_len, O, LSE, ws, s, &rm)
+               : run_decode_ring<64>(p, d, scale, Qd, batch, T, K, V, l_cap, mix_len, O, LSE, ws, s, &rm);
 }
 
 }  // namespace vxl

@@ -193,7 +193,8 @@ struct DecodePlan {
     size_t total;
 };
 // gathered = false plans the in-place form (always the 4-wave step kernel, splits bounded by its row-map area)
-DecodePlan decode_plan(const vxl_attn_desc* d, int batch, int T, int l_cap, bool gathered = true);
+// `have`: scratch bytes there are; a plan that the shorter call needs more for is given up for one that takes less.
+DecodePlan decode_plan(const vxl_attn_desc* d, int batch, int T, int l_cap, bool gathered = true, size_t have = SIZE_MAX);
 // fp32, either form: total == 0 with one split; a call without this much scratch memory takes one split
 DecodePlan decode_f32_plan(const vxl_attn_desc* d, int batch, int T, int l_cap);
 
@@ -205,10 +206,10 @@ struct InplaceWorkspace {      // byte offsets into the caller's workspace (vxl_
 };
 InplaceWorkspace inplace_workspace(const vxl_attn_desc* d, int batch, int T, int l_cap);
 
-vxl_status launch_decode_bf16(const vxl_attn_desc* d, float scale, const void* Qd, int batch, int T,
+vxl_status launch_decode_bf16(const DecodePlan& p, const vxl_attn_desc* d, float scale, const void* Qd, int batch, int T,
                               const void* Kmix, const void* Vmix, int l_cap, const int32_t* mix_len,
                               void* O, float* LSE, void* ws, hipStream_t s);
-vxl_status launch_decode_bf16_inplace(const vxl_layout* L, const vxl_attn_desc* d, float scale, const void* Qd,
+vxl_status launch_decode_bf16_inplace(const DecodePlan& p, const vxl_layout* L, const vxl_attn_desc* d, float scale, const void* Qd,
                                       int batch, int T, const void* K, const void* V, const void* Ksp,
                                       const void* Vsp, const int32_t* src_idx, int l_cap, const int32_t* mix_len,
                                       void* O, float* LSE, void* ws, hipStream_t s);

@@ -71,3 +71,43 @@ def test_either_number_of_waves_in_place(mode, hq, t, d, waves, chunks, length):
     assert vxl.debug_decode_ring_waves(desc, 1, t, l_cap, True) == waves
     _, k, v = wl.make_qkv(w, lay, with_q=False)
     check_case(w, lay, k, v, wl.make_decode_queries(w), masks, mode, l_cap=l_cap)
+
+
+@pytest.mark.parametrize("hq,hkv,t,d,bsz,l_cap,blocks", [
+    (28, 4, 10, 128, 8, 5200, 2),                          # 70 rows, 21 tiles per wave of row blocks in two splits
+    (16, 1, 6, 64, 8, 38000, 10)])                         # 96 rows, 30 tiles in ten splits
+def test_long_walks_and_the_scratch_that_row_blocks_take(hq, hkv, t, d, bsz, l_cap, blocks):
+    """The ring, whose splits need more scratch memory, and with as much as row blocks need those: both against float64; a
+    byte less is refused."""
+    w = wl.tiny_workload("bf16", hq, hkv, d, T=t, B=bsz, k=1, seed=88)
+    desc, g, rows = desc_of(w), hq // hkv, hq // hkv * t
+    kernel, n_split = vxl.debug_decode_plan(desc, bsz, t, l_cap)
+    assert kernel == DECODE_128 and n_split > blocks
+    gen = torch.Generator(device="cuda").manual_seed(l_cap)
+    q, k, v = (torch.empty(s, dtype=torch.bfloat16, device="cuda").normal_(0, 1, generator=gen)
+               for s in ((bsz, t, hq, d), (bsz, hkv, l_cap, d), (bsz, hkv, l_cap, d)))
+    lens = torch.tensor([l_cap, l_cap - 1, 65, 64, 1, l_cap // 2, 0, l_cap - 64], dtype=torch.int32)
+    for b, n in enumerate(lens.tolist()):
+        k[b, :, n:] = float("nan")
+        v[b, :, n:] = float("nan")
+    dl = lens.cuda()
+    small = sum((bsz * hkv * blocks * rows * n * 4 + 255) // 256 * 256 for n in (d, 1))
+    full = vxl.workspace_bytes(vxl.OP_DECODE, None, desc, bsz, t, l_cap)
+    assert small < full
+    with pytest.raises(vxl.VxlError):
+        vxl.bilevel_decode(desc, q, k, v, dl, torch.empty_like(q), None,
+                           torch.empty(small - 1, dtype=torch.uint8, device="cuda"))
+    for size in (full, small):
+        out, lse = torch.full_like(q, float("nan")), torch.full((bsz, t, hq), float("nan"), device="cuda")
+        vxl.bilevel_decode(desc, q, k, v, dl, out, lse, torch.empty(size, dtype=torch.uint8, device="cuda"))
+        for b, n in enumerate(lens.tolist()):
+            if n == 0:
+                assert not out[b].any() and torch.isneginf(lse[b]).all()
+                continue
+            for h in range(hkv):
+                s = q[b, :, h * g:(h + 1) * g].reshape(-1, d).double() @ k[b, h, :n].double().T / d ** 0.5
+                want = (torch.softmax(s, -1) @ v[b, h, :n].double()).reshape(t, g, d).cpu().numpy()
+                got = vxl.to_host(out[b, :, h * g:(h + 1) * g].contiguous())
+                assert_close(got, want, "bf16", head_axis=1, what=f"query {b}, {n} keys, {size} bytes")
+                wlse = torch.logsumexp(s, -1).reshape(t, g)
+                assert (lse[b, :, h * g:(h + 1) * g].double() - wlse).abs().max() < 2e-2
