@@ -40,8 +40,12 @@ __device__ __forceinline__ void store16(uint4* p, uint4 v) {
 // by one -> so, 25.6 -> 24.1 us with the selection).  How many threads, and whether past the caches: launch_summaries.
 // ------------------------------------------------------------------------------------------
 // qbar[b, g, :] = mean over the T query tokens and the query heads of KV head g of Qd[b, t, h, :].
-// One block per (b, g): a thread owns one 16-byte column piece of one head and adds its T tokens in
-// token order (16 loads in flight at a time); the heads of the group are then added in head order.
+// A few tokens: one block per (b, g), a thread owns one 16-byte column piece of one head and adds its T tokens in
+// token order; the heads of the group are then added in head order.  (Eight loads of a thread in flight here and below:
+// sixteen take 82 to 98 registers, which leave the chunks of the launch five or four waves per SIMD instead of eight, 256
+// chunks 18.5 -> 19.8 us; streamed past the caches four are as good as eight and steadier, 640 chunks 35.4 -> 34.6.)
+constexpr int kMeanLoads = 8;
+
 template <typename T, int D, int THREADS>
 __device__ __forceinline__ void query_mean_block(const T* __restrict__ Qd, float* __restrict__ qbar, int b, int g,
                                                  int T_q, int n_q_heads, int n_kv_heads, float* hsum /*[group][D]*/) {
@@ -55,15 +59,15 @@ __device__ __forceinline__ void query_mean_block(const T* __restrict__ Qd, float
         float acc[EPC];
 #pragma unroll
         for (int i = 0; i < EPC; ++i) acc[i] = 0.f;
-        for (int t0 = 0; t0 < T_q; t0 += 16) {
-            uint4 v[16];
+        for (int t0 = 0; t0 < T_q; t0 += kMeanLoads) {
+            uint4 v[kMeanLoads];
 #pragma unroll
-            for (int u = 0; u < 16; ++u) {
+            for (int u = 0; u < kMeanLoads; ++u) {
                 const int t = t0 + u < T_q ? t0 + u : T_q - 1;      // clamped rows are not added below
                 v[u] = ((const uint4*)qb)[(size_t)t * row_pieces + gp];
             }
 #pragma unroll
-            for (int u = 0; u < 16; ++u) {
+            for (int u = 0; u < kMeanLoads; ++u) {
                 if (t0 + u < T_q) {
                     const T* e = (const T*)&v[u];
 #pragma unroll
@@ -82,14 +86,71 @@ __device__ __forceinline__ void query_mean_block(const T* __restrict__ Qd, float
     }
 }
 
-// Blocks x < n_chunks summarise chunk x; blocks x >= n_chunks (when Qd is given) form the mean
-// query of query x - n_chunks: both feed the scoring kernel, one launch serves both.
+// The same for more tokens, one block per (b, g, four pieces of a row), begun before the chunks: a thread owns one piece of
+// one head and every tg_n-th token; the tg_n sums of a piece are added in order, then the heads of the group.  A chain of
+// round trips: with all tokens of a piece in one thread, 128 tokens took eight, behind the chunks of the launch (28 heads on
+// four, D = 128, with the selection: 64 chunks of 256 tokens 17.3 -> 11.3 us, 256 chunks 28.2 -> 20.6, 640 40.1 -> 35.5;
+// 8 of 128 tokens 14.0 -> 8.3; 64 tokens 10.1 -> 8.0, 32 8.4 -> 7.6, 16 7.6 -> 7.5).
+constexpr int kMeanPieces = 4, kMeanTokens = 8;               // pieces of a block; tokens up to which one block takes a row
+
+template <typename T, int D, int THREADS>
+__device__ __forceinline__ void query_mean_part(const T* __restrict__ Qd, float* __restrict__ qbar, int b, int g, int first,
+                                                int T_q, int n_q_heads, int n_kv_heads, float* sums /*[tg_n][group][COLS]*/) {
+    constexpr int EPC = 16 / (int)sizeof(T);
+    constexpr int PPR = D / EPC, COLS = kMeanPieces * EPC;
+    const int group = n_q_heads / n_kv_heads, tid = threadIdx.x, n = group * kMeanPieces;
+    // token groups, this thread's (as many from 512 threads as from 256: a query's mean does not depend on the layout)
+    const int tg_n = max(1, min(256 / n, (T_q + kMeanLoads - 1) / kMeanLoads)), tg = tid / n;
+    const T* qb = Qd + (size_t)b * T_q * n_q_heads * D;
+    const int row_pieces = n_q_heads * PPR;
+    if (tg < tg_n) {
+        for (int p = tid - tg * n; p < n; p += THREADS) {
+            const int gp = (g * group + p / kMeanPieces) * PPR + first + p % kMeanPieces;     // piece inside a token's [Hq*D] row
+            float acc[EPC];
+#pragma unroll
+            for (int i = 0; i < EPC; ++i) acc[i] = 0.f;
+            for (int t0 = tg; t0 < T_q; t0 += kMeanLoads * tg_n) {
+                uint4 v[kMeanLoads];
+#pragma unroll
+                for (int u = 0; u < kMeanLoads; ++u)                   // (clamped rows are not added below)
+                    v[u] = ((const uint4*)qb)[(size_t)min(t0 + u * tg_n, T_q - 1) * row_pieces + gp];
+#pragma unroll
+                for (int u = 0; u < kMeanLoads; ++u) {
+                    if (t0 + u * tg_n < T_q) {
+                        const T* e = (const T*)&v[u];
+#pragma unroll
+                        for (int i = 0; i < EPC; ++i) acc[i] += ld(e + i);
+                    }
+                }
+            }
+#pragma unroll
+            for (int i = 0; i < EPC; ++i) sums[(tg * n + p) * EPC + i] = acc[i];
+        }
+    }
+    __syncthreads();
+    if (tg_n > 1) {                                           // (in one step with the heads, by COLS threads: 0.3 to 1.9 us more)
+        for (int e = tid; e < n * EPC; e += THREADS) {
+            float a = sums[e];
+            for (int k = 1; k < tg_n; ++k) a += sums[k * n * EPC + e];
+            sums[e] = a;
+        }
+        __syncthreads();
+    }
+    for (int dd = tid; dd < COLS; dd += THREADS) {
+        float a = 0.f;
+        for (int hg = 0; hg < group; ++hg) a += sums[hg * COLS + dd];
+        qbar[((size_t)b * n_kv_heads + g) * D + first * EPC + dd] = a / (float)(T_q * group);
+    }
+}
+
+// The first n_mean blocks (more than kMeanTokens tokens), or those behind the chunks, form the mean queries, the others
+// summarise a chunk each: both feed the scoring kernel, one launch serves both.
 template <typename T, int D, int THREADS, bool NT>
-__global__ __launch_bounds__(THREADS) void chunk_summarize_kernel(const T* __restrict__ K,
+__global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(NT ? 4 : 8, NT ? 4 : 8))) void chunk_summarize_kernel(const T* __restrict__ K,
                                                               const int32_t* __restrict__ bounds,
                                                               float* __restrict__ kbar, long long kv_head_u4,
                                                               long long kv_tok_u4,   // K strides, 16-byte units
-                                                              int n_chunks, const T* __restrict__ Qd,
+                                                              int n_chunks, int n_mean, const T* __restrict__ Qd,
                                                               float* __restrict__ qbar, int T_q, int n_q_heads,
                                                               int n_kv_heads) {
     constexpr int EPC = 16 / (int)sizeof(T);        // elements per 16-byte piece
@@ -100,13 +161,19 @@ __global__ __launch_bounds__(THREADS) void chunk_summarize_kernel(const T* __res
     // of them, and they are added in the same tree.
     constexpr int A = THREADS == 512 ? 2 : 4, CHAINS = A * RG, GROUPS = CHAINS / 4;
     constexpr int KEPT = THREADS == 512 ? CHAINS : GROUPS;      // (256 threads: a thread adds the four of its group)
-    extern __shared__ float dyn[];                  // [group][D] for the query blocks
+    extern __shared__ float dyn[];                  // for the query blocks: [group][D], or a piece per thread
     __shared__ float part[KEPT][D];
-    if ((int)blockIdx.x >= n_chunks) {
-        query_mean_block<T, D, THREADS>(Qd, qbar, blockIdx.x - n_chunks, blockIdx.y, T_q, n_q_heads, n_kv_heads, dyn);
+    if ((int)blockIdx.x < n_mean) {
+        constexpr int PARTS = PPR / kMeanPieces;
+        query_mean_part<T, D, THREADS>(Qd, qbar, blockIdx.x / PARTS, blockIdx.y, blockIdx.x % PARTS * kMeanPieces, T_q,
+                                       n_q_heads, n_kv_heads, dyn);
         return;
     }
-    const int c = blockIdx.x, g = blockIdx.y;
+    const int c = blockIdx.x - n_mean, g = blockIdx.y;
+    if (c >= n_chunks) {
+        query_mean_block<T, D, THREADS>(Qd, qbar, c - n_chunks, g, T_q, n_q_heads, n_kv_heads, dyn);
+        return;
+    }
     const int piece = threadIdx.x % PPR, rg = threadIdx.x / PPR;
     const int lo = bounds[c], hi = bounds[c + 1];
     const uint4* base = (const uint4*)K + (size_t)g * kv_head_u4 + piece;
@@ -557,8 +624,6 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(FOUR ? 4 : 
 vxl_status launch_summaries(const vxl_layout* L, const vxl_attn_desc* d, const void* K, float* kbar,
                             bool do_chunks, const void* Qd, int batch, int T, float* qbar, hipStream_t s) {
     const int nc = do_chunks ? L->n_chunks : 0;
-    const dim3 grid(nc + batch, d->n_kv_heads);
-    const size_t smem = (size_t)(d->n_q_heads / d->n_kv_heads) * d->head_dim * sizeof(float);
     const TokStrides ts = tok_strides(d, L->n_tokens);
     const long long epc = d->dtype == VXL_BF16 ? 8 : 4;       // elements per 16 bytes
     // 512 threads per chunk and KV head where there are few of them, long ones of rows of 256 bytes and more: a block is
@@ -575,10 +640,14 @@ vxl_status launch_summaries(const vxl_layout* L, const vxl_attn_desc* d, const v
     const bool wide = row >= 256 && (long long)L->n_chunks * d->n_kv_heads <= 512 &&
                       (long long)L->n_tokens * row >= 19ll * 256 * 16 * L->n_chunks;
     const bool once = L->n_tokens * (row * d->n_kv_heads) > (96 << 20);
+    const int pieces = d->head_dim / (int)epc, n_mean = T > kMeanTokens ? batch * (pieces / kMeanPieces) : 0;
+    const int group = d->n_q_heads / d->n_kv_heads;
+    const dim3 grid(nc + (n_mean ? n_mean : batch), d->n_kv_heads);
+    const size_t smem = (size_t)(n_mean ? std::max(wide ? 512 : 256, group * kMeanPieces) * (int)epc : group * d->head_dim) * sizeof(float);
 #define VXL_LAUNCH_AS(T_, D, THREADS, NT)                                                                        \
     hipLaunchKernelGGL((chunk_summarize_kernel<T_, D, THREADS, NT>), grid, dim3(THREADS), smem, s, (const T_*)K,  \
-                       L->d_bounds, kbar, ts.kh / epc, ts.kt / epc, nc, (const T_*)Qd, qbar, T, d->n_q_heads,     \
-                       d->n_kv_heads)
+                       L->d_bounds, kbar, ts.kh / epc, ts.kt / epc, nc, n_mean, (const T_*)Qd, qbar, T,     \
+                       d->n_q_heads, d->n_kv_heads)
 #define VXL_LAUNCH(T_, D)                                                                                        \
     do {                                                                                                         \
         if (wide) { if (once) VXL_LAUNCH_AS(T_, D, 512, true); else VXL_LAUNCH_AS(T_, D, 512, false); }          \

@@ -100,3 +100,41 @@ def test_means_do_not_depend_on_the_number_of_chunks(dtype, hkv, d, lens):
         res.append((kbar[:, :len(lens)].cpu().numpy(), scores[:, :len(lens)].cpu().numpy()))
     for a, b in zip(*res):
         assert np.array_equal(a.view(np.uint32), b.view(np.uint32))
+
+
+@pytest.mark.parametrize("dtype,hq,hkv,d,bsz,t", [
+    ("bf16", 28, 4, 128, 1, 8), ("bf16", 28, 4, 128, 2, 9),                # the last of one block per row, the first of four
+    ("bf16", 14, 2, 128, 3, 17), ("bf16", 14, 2, 64, 1, 128), ("bf16", 8, 1, 128, 1, 127), ("bf16", 4, 4, 64, 2, 200),
+    ("bf16", 64, 1, 64, 1, 33), ("bf16", 70, 1, 128, 1, 40),               # a piece per thread, more pieces than threads
+    ("f32", 6, 2, 64, 2, 65), ("f32", 6, 2, 128, 1, 130)])
+def test_scores_of_many_query_tokens(dtype, hq, hkv, d, bsz, t):
+    """The mean over query tokens and heads by one thread per piece and by groups of them: rounding of fp32 sums (as above)."""
+    rng = np.random.default_rng(t * d)
+    w = wl.tiny_workload(dtype, hq, hkv, d, T=t, B=bsz, k=2, seed=t, value_scale=1.0)
+    lay = wl.random_layout(rng, 9, 7, 1, 60)
+    _, k, _ = wl.make_qkv(w, lay, with_q=False)
+    qd = rng.standard_normal((bsz, t, hq, d)).astype(np.float32) + rng.standard_normal((1, 1, 1, d)).astype(np.float32)
+    qd = wl.round_to_bf16(qd) if dtype == "bf16" else qd
+    want = oracle.chunk_scores(qd, k, lay.chunk_bounds)
+    _, _, scores = gpu_score_topk(w, lay, qd, k, 2)
+    assert np.abs(scores - want).max() <= 2e-5 * np.abs(want).max()
+
+
+def test_mean_query_does_not_depend_on_the_layout():
+    """40 tokens; 20 long chunks, whose launch has 512 threads per block, and 300, whose has 256: the same scores, bit for bit."""
+    ln, hkv, d = 320, 2, 128
+    w = wl.tiny_workload("bf16", 14, hkv, d, T=40, B=2, k=1, seed=3, value_scale=1.0)
+    gen = torch.Generator(device="cuda").manual_seed(3)
+    k = torch.empty((hkv, 300 * ln, d), dtype=torch.bfloat16, device="cuda").normal_(0, 1, generator=gen)
+    qd = vxl.to_device(wl.make_decode_queries(w), "bf16")
+    got = []
+    for n in (20, 300):
+        lay = wl.layout_from_lists(0, [ln] * n, [np.zeros(0, np.int32)] * n)
+        gl, desc, kn = make_layout(lay), desc_of(w), k[:, :n * ln].contiguous()
+        idx = torch.empty((2, 1), dtype=torch.int32, device="cuda")
+        mask = torch.empty((2, n), dtype=torch.uint8, device="cuda")
+        scores = torch.empty((2, n), dtype=torch.float32, device="cuda")
+        vxl.chunk_score_topk(gl, desc, qd, kn, 1, idx, mask, scores,
+                             workspace=vxl.alloc_workspace(vxl.workspace_bytes(vxl.OP_SCORE_TOPK, gl, desc, 2, 40)))
+        got.append(scores[:, :20].cpu())
+    assert torch.equal(*got)
