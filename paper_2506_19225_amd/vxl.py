@@ -1,10 +1,11 @@
-"""ctypes binding of libvxl.so: the same entry points as include/vxl.h, argument marshalling
-only.  Every step of the path runs in the HIP kernels of the library; torch is used for device
+"""Binding of libvxl.so: the same entry points as include/vxl.h, argument marshalling
+only (the calls of the path through csrc/vxl_torch.cpp, the rest through ctypes).  Every step of the path runs in the HIP kernels of the library; torch is used for device
 memory and streams.  Loading fails loudly when the library has not been built -- there is no
 fallback path."""
 from __future__ import annotations
 
 import ctypes as C
+import importlib.util
 import os
 from typing import Optional
 
@@ -13,6 +14,7 @@ import torch  # imported before the library so that both use the one HIP runtime
 
 _PKG = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_PKG, "libvxl.so")
+BINDING_PATH = os.path.join(_PKG, "_vxl_torch.so")
 
 VXL_OK, VXL_ERR_INVALID_ARG, VXL_ERR_UNSUPPORTED, VXL_ERR_WORKSPACE, VXL_ERR_HIP, VXL_ERR_ALLOC = range(6)
 VXL_F32, VXL_BF16 = 0, 1
@@ -36,6 +38,7 @@ class VxlError(RuntimeError):
 
 
 _lib = None
+_native = None
 
 
 def lib() -> C.CDLL:
@@ -113,6 +116,30 @@ def lib() -> C.CDLL:
     L.vxl_debug_read_stream.restype = C.c_int
     _lib = L
     return L
+
+
+def native():
+    """The loaded binding (raises if it has not been built): the calls of the path over torch tensors."""
+    global _native
+    if _native is None:
+        lib()
+        if not os.path.exists(BINDING_PATH):
+            raise RuntimeError(f"{BINDING_PATH} is missing: run `python -m paper_2506_19225_amd.build` "
+                               "(or __graft_entry__.build()) first; there is no fallback path")
+        spec = importlib.util.spec_from_file_location("_vxl_torch", BINDING_PATH)
+        module = importlib.util.module_from_spec(spec)
+        spec.loader.exec_module(module)
+        module.setup(AttnDesc, C.c_void_p, _stream)
+        _native = module
+    return _native
+
+
+def _size(arg: int, dim: int) -> bytes:
+    """Stands for dimension `dim` of argument `arg` in a call of the binding; _NUMEL: its number of elements."""
+    return bytes((arg, dim))
+
+
+_NUMEL = 255
 
 
 def _check(status: int, where: str) -> None:
@@ -215,11 +242,19 @@ def alloc_workspace(nbytes: int, device="cuda") -> torch.Tensor:
     return torch.empty(max(int(nbytes), 256), dtype=torch.uint8, device=device)
 
 
+_PREFILL = (_size(7, _NUMEL),)
+_SCORE = (_size(2, 0), _size(2, 1), _size(12, _NUMEL))
+_MASS = (_size(2, 0), _size(2, 1), _size(10, _NUMEL))
+_GATHER = (_size(6, 0), _size(6, 2))
+_POOLED = (_size(8, 0), _size(8, 2))
+_DECODE = (_size(1, 0), _size(1, 1), _size(4, 2), _size(10, _NUMEL))
+_INPLACE = (_size(2, 0), _size(2, 1), _size(15, _NUMEL))
+
+
 def chunk_prefill(layout: Layout, desc: AttnDesc, q, k, v, out, lse=None, workspace=None, stream=None):
     """vxl_chunk_prefill: q/out [Hq,N,D], k/v [Hkv,N,D]; lse float32 [Hq,N] or None."""
-    st = lib().vxl_chunk_prefill(layout.handle, C.byref(desc), _ptr(q), _ptr(k), _ptr(v), _ptr(out),
-                                 _ptr(lse), _ptr(workspace), workspace.numel() if workspace is not None else 0,
-                                 _stream(stream))
+    st = (_native or native()).chunk_prefill(layout.handle, desc, q, k, v, out, lse, workspace, _PREFILL[0],
+                                             stream)
     _check(st, "vxl_chunk_prefill")
     return out
 
@@ -227,63 +262,48 @@ def chunk_prefill(layout: Layout, desc: AttnDesc, q, k, v, out, lse=None, worksp
 def chunk_score_topk(layout: Layout, desc: AttnDesc, qd, k, top_k: int, topk_idx, dense_mask,
                      scores=None, kbar=None, kbar_ready: bool = False, workspace=None, stream=None):
     """vxl_chunk_score_topk: qd [B,T,Hq,D]; topk_idx int32 [B,min(k,C)]; dense_mask uint8 [B,C]."""
-    shape = qd.shape                                         # (torch builds it anew each time it is asked for)
-    b, t = shape[0], shape[1]
-    st = lib().vxl_chunk_score_topk(layout.handle, C.byref(desc), _ptr(qd), b, t, _ptr(k), int(top_k),
-                                    _ptr(kbar), int(bool(kbar_ready)), _ptr(topk_idx), _ptr(dense_mask),
-                                    _ptr(scores), _ptr(workspace),
-                                    workspace.numel() if workspace is not None else 0, _stream(stream))
+    b, t, n = _SCORE
+    st = (_native or native()).chunk_score_topk(layout.handle, desc, qd, b, t, k, int(top_k), kbar, int(bool(kbar_ready)),
+                                                topk_idx, dense_mask, scores, workspace, n, stream)
     _check(st, "vxl_chunk_score_topk")
 
 
 def chunk_score_topk_mass(layout: Layout, desc: AttnDesc, qd, k, top_k: int, topk_idx, dense_mask,
                           scores=None, workspace=None, stream=None):
     """vxl_chunk_score_topk_mass: arguments as chunk_score_topk, softmax attention-mass score."""
-    shape = qd.shape
-    b, t = shape[0], shape[1]
-    st = lib().vxl_chunk_score_topk_mass(layout.handle, C.byref(desc), _ptr(qd), b, t, _ptr(k), int(top_k),
-                                         _ptr(topk_idx), _ptr(dense_mask), _ptr(scores), _ptr(workspace),
-                                         workspace.numel() if workspace is not None else 0, _stream(stream))
+    b, t, n = _MASS
+    st = (_native or native()).chunk_score_topk_mass(layout.handle, desc, qd, b, t, k, int(top_k), topk_idx, dense_mask,
+                                                     scores, workspace, n, stream)
     _check(st, "vxl_chunk_score_topk_mass")
 
 
 def gather_bilevel_kv(layout: Layout, desc: AttnDesc, k, v, dense_mask, kmix, vmix, mix_len,
                       src_idx=None, stream=None):
     """vxl_gather_bilevel_kv: kmix/vmix [B,Hkv,Lcap,D]; mix_len int32 [B]; src_idx int32 [B,Lcap]."""
-    shape = kmix.shape
-    b, l_cap = shape[0], shape[2]
-    st = lib().vxl_gather_bilevel_kv(layout.handle, C.byref(desc), _ptr(k), _ptr(v), _ptr(dense_mask), b,
-                                     _ptr(kmix), _ptr(vmix), l_cap, _ptr(mix_len), _ptr(src_idx),
-                                     _stream(stream))
+    st = (_native or native()).gather_bilevel_kv(layout.handle, desc, k, v, dense_mask, _GATHER[0], kmix, vmix, _GATHER[1],
+                                                 mix_len, src_idx, stream)
     _check(st, "vxl_gather_bilevel_kv")
 
 
 def pool_sparse_kv(layout: Layout, desc: AttnDesc, k, v, ksp, vsp, stream=None):
     """vxl_pool_sparse_kv: k/v [Hkv,N,D] -> ksp/vsp [Hkv,S_total,D]."""
-    st = lib().vxl_pool_sparse_kv(layout.handle, C.byref(desc), _ptr(k), _ptr(v), _ptr(ksp), _ptr(vsp),
-                                  _stream(stream))
+    st = (_native or native()).pool_sparse_kv(layout.handle, desc, k, v, ksp, vsp, stream)
     _check(st, "vxl_pool_sparse_kv")
 
 
 def gather_bilevel_kv_pooled(layout: Layout, desc: AttnDesc, k, v, ksp, vsp, dense_mask, kmix, vmix, mix_len,
                              src_idx=None, stream=None):
     """vxl_gather_bilevel_kv_pooled: as gather_bilevel_kv, sparse rows taken from ksp/vsp."""
-    shape = kmix.shape
-    b, l_cap = shape[0], shape[2]
-    st = lib().vxl_gather_bilevel_kv_pooled(layout.handle, C.byref(desc), _ptr(k), _ptr(v), _ptr(ksp), _ptr(vsp),
-                                            _ptr(dense_mask), b, _ptr(kmix), _ptr(vmix), l_cap, _ptr(mix_len),
-                                            _ptr(src_idx), _stream(stream))
+    st = (_native or native()).gather_bilevel_kv_pooled(layout.handle, desc, k, v, ksp, vsp, dense_mask, _POOLED[0], kmix,
+                                                        vmix, _POOLED[1], mix_len, src_idx, stream)
     _check(st, "vxl_gather_bilevel_kv_pooled")
 
 
 def bilevel_decode(desc: AttnDesc, qd, kmix, vmix, mix_len, out, lse=None, workspace=None, stream=None):
     """vxl_bilevel_decode: qd/out [B,T,Hq,D]; kmix/vmix [B,Hkv,Lcap,D]; mix_len int32 [B]."""
-    shape = qd.shape
-    b, t = shape[0], shape[1]
-    l_cap = kmix.shape[2]
-    st = lib().vxl_bilevel_decode(C.byref(desc), _ptr(qd), b, t, _ptr(kmix), _ptr(vmix), l_cap,
-                                  _ptr(mix_len), _ptr(out), _ptr(lse), _ptr(workspace),
-                                  workspace.numel() if workspace is not None else 0, _stream(stream))
+    b, t, l_cap, n = _DECODE
+    st = (_native or native()).bilevel_decode(desc, qd, b, t, kmix, vmix, l_cap, mix_len, out, lse, workspace, n,
+                                              stream)
     _check(st, "vxl_bilevel_decode")
     return out
 
@@ -291,12 +311,10 @@ def bilevel_decode(desc: AttnDesc, qd, kmix, vmix, mix_len, out, lse=None, works
 def bilevel_decode_inplace(layout: Layout, desc: AttnDesc, qd, k, v, ksp, vsp, dense_mask, l_cap: int, out,
                            lse=None, mix_len=None, workspace=None, map_ready: bool = False, stream=None):
     """vxl_bilevel_decode_inplace: gather-free decode; ksp/vsp [Hkv,S_total,D] or None (kept rows in place)."""
-    shape = qd.shape
-    b, t = shape[0], shape[1]
-    st = lib().vxl_bilevel_decode_inplace(layout.handle, C.byref(desc), _ptr(qd), b, t, _ptr(k), _ptr(v), _ptr(ksp),
-                                          _ptr(vsp), _ptr(dense_mask), int(l_cap), int(bool(map_ready)), _ptr(out), _ptr(lse),
-                                          _ptr(mix_len), _ptr(workspace),
-                                          workspace.numel() if workspace is not None else 0, _stream(stream))
+    b, t, n = _INPLACE
+    st = (_native or native()).bilevel_decode_inplace(layout.handle, desc, qd, b, t, k, v, ksp, vsp, dense_mask, int(l_cap),
+                                                      int(bool(map_ready)), out, lse, mix_len, workspace, n,
+                                                      stream)
     _check(st, "vxl_bilevel_decode_inplace")
     return out
 

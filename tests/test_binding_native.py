@@ -1,0 +1,96 @@
+"""The compiled binding: what it refuses, in which order, and which numbers and pointers reach the library (objects that
+answer like device tensors, whose calls end in the library's own argument checks)."""
+import ctypes as C
+
+import numpy as np
+import pytest
+import torch
+
+from paper_2506_19225_amd import vxl
+
+
+class Like:
+    """Answers like a contiguous device tensor."""
+    is_cuda = True
+
+    def __init__(self, shape, ptr=0x1000, contiguous=True):
+        self.shape, self.ptr, self.contiguous = shape, ptr, contiguous
+
+    def is_contiguous(self):
+        return self.contiguous
+
+    def data_ptr(self):
+        return self.ptr
+
+    def numel(self):
+        return int(np.prod(self.shape))
+
+
+DESC = vxl.make_desc(28, 4, 128, "bf16")
+Q, KV, LEN = Like((2, 3, 28, 128)), Like((2, 4, 640, 128)), Like((2,))
+
+
+@pytest.fixture(autouse=True)
+def streams(monkeypatch):
+    asked = []
+    monkeypatch.setattr(torch.cuda, "is_initialized", lambda: True)
+    monkeypatch.setattr(vxl, "_current_device", lambda: 0)
+    monkeypatch.setattr(vxl, "_raw_stream", lambda dev: asked.append(dev) or 0)
+    return asked
+
+
+def decode(desc=DESC, q=Q, k=KV, v=KV, n=LEN, out=Q, lse=None, ws=None, stream=None):
+    return vxl.bilevel_decode(desc, q, k, v, n, out, lse, ws, stream)
+
+
+def status(*args, **kw):
+    with pytest.raises(vxl.VxlError) as e:
+        decode(*args, **kw)
+    return e.value.status
+
+
+@pytest.mark.parametrize("bad", [torch.zeros(2, 3, 28, 128), Like((2, 3, 28, 128), contiguous=False)])
+def test_refuses_what_is_no_contiguous_device_tensor(bad, streams):
+    for kw in (dict(q=bad), dict(k=bad), dict(v=bad), dict(n=bad), dict(out=bad), dict(lse=bad), dict(ws=bad)):
+        with pytest.raises(AssertionError, match="contiguous CUDA tensors"):
+            decode(**kw)
+    assert not streams                                     # (a stream is asked for when all else is found good)
+
+
+def test_refuses_other_objects(streams):
+    for kw, error in ((dict(q=np.zeros((2, 3, 28, 128))), AttributeError), (dict(q=None), AttributeError),
+                      (dict(desc=C.c_int(3)), AttributeError), (dict(desc="text"), AttributeError),
+                      (dict(q=Like((2,))), IndexError), (dict(k=Like((2, 4))), IndexError), (dict(stream=5), AttributeError)):
+        with pytest.raises(error):
+            decode(**kw)
+    with pytest.raises(TypeError, match="arguments expected"):
+        vxl.native().bilevel_decode(DESC)
+
+
+def test_what_reaches_the_library(streams):
+    """A null descriptor, output or length, a misaligned pointer, sizes of 0 and scratch memory too small for the sizes given
+    are told apart by the library, which launches nothing for any of them."""
+    assert status() == vxl.VXL_ERR_WORKSPACE and streams == [0]
+    assert status(desc=None) == status(out=None) == status(n=None) == vxl.VXL_ERR_INVALID_ARG
+    for kw in (dict(q=Like(Q.shape, 0x1008)), dict(k=Like(KV.shape, 0x1008)), dict(v=Like(KV.shape, 0x1008)),
+               dict(out=Like(Q.shape, 0x1008)), dict(q=Like((0, 3, 28, 128))), dict(q=Like((2, 0, 28, 128))),
+               dict(k=Like((2, 4, 0, 128)))):
+        assert status(**kw) == vxl.VXL_ERR_INVALID_ARG
+    need = vxl.workspace_bytes(vxl.OP_DECODE, None, DESC, 2, 3, 640)
+    assert status(ws=Like((need - 1,))) == vxl.VXL_ERR_WORKSPACE
+    assert status(ws=Like((need,), 0x1008)) == vxl.VXL_ERR_WORKSPACE
+    assert status(desc=vxl.make_desc(28, 4, 96, "bf16")) == vxl.VXL_ERR_UNSUPPORTED
+
+
+def test_a_null_layout_is_the_librarys_to_refuse():
+    class Closed:
+        handle = None
+    x = Like((2, 4, 8, 128))
+    for call in (lambda: vxl.chunk_prefill(Closed, DESC, x, x, x, x), lambda: vxl.chunk_score_topk(Closed, DESC, x, x, 1, x, x),
+                 lambda: vxl.chunk_score_topk_mass(Closed, DESC, x, x, 1, x, x), lambda: vxl.pool_sparse_kv(Closed, DESC, x, x, x, x),
+                 lambda: vxl.gather_bilevel_kv(Closed, DESC, x, x, x, x, x, x),
+                 lambda: vxl.gather_bilevel_kv_pooled(Closed, DESC, x, x, x, x, x, x, x, x),
+                 lambda: vxl.bilevel_decode_inplace(Closed, DESC, x, x, x, x, x, x, 8, x)):
+        with pytest.raises(vxl.VxlError) as e:
+            call()
+        assert e.value.status == vxl.VXL_ERR_INVALID_ARG
