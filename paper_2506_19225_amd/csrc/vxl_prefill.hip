@@ -346,21 +346,31 @@ __global__ __launch_bounds__(NW * 64, 2) void prefill_dma_kernel(
     {
         const int q_off = wrow0 + l32;
         const float l_tot = l_run + __shfl_xor(l_run, 32);
-        if (q_off < sg.q_len && !idle) {
+        if (!idle) {
             const float inv = 1.f / l_tot;
             // uniform bases + 32-bit lane offsets, as for the query loads
             char* obase = (char*)(O + (size_t)h * q_head + (size_t)sg.q_start * q_tok);
-            const uint32_t ooff = (uint32_t)q_off * (uint32_t)(q_tok * 2) + hi * 8;
+            const uint32_t ooff = (uint32_t)q_off * (uint32_t)(q_tok * 2) + hi * 16;
 #pragma unroll
             for (int db = 0; db < D / 32; ++db)
 #pragma unroll
-                for (int rq = 0; rq < 4; ++rq) {
-                    bf16x4 v;
+                for (int rq = 0; rq < 4; rq += 2) {
+                    // A lane and its partner lane ^ 32 hold halves of the same 16-byte pieces of their row: of two pieces
+                    // they swap one half each, so that either stores a whole one.
+                    typedef __attribute__((ext_vector_type(2))) unsigned u32x2;
+                    u32x2 half[2];
 #pragma unroll
-                    for (int e = 0; e < 4; ++e) v[e] = (__bf16)(o[0][db][rq * 4 + e] * inv);
-                    *(bf16x4*)(obase + ooff + (db * 32 + rq * 8) * 2) = v;
+                    for (int p = 0; p < 2; ++p) {
+                        bf16x4 v;
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) v[e] = (__bf16)(o[0][db][(rq + p) * 4 + e] * inv);
+                        half[p] = __builtin_bit_cast(u32x2, v);
+                    }
+                    const auto x = __builtin_amdgcn_permlane32_swap(half[0][0], half[1][0], false, false);
+                    const auto y = __builtin_amdgcn_permlane32_swap(half[0][1], half[1][1], false, false);
+                    if (q_off < sg.q_len) *(uint4*)(obase + ooff + (db * 32 + rq * 8) * 2) = make_uint4(x[0], y[0], x[1], y[1]);
                 }
-            if (LSE && hi == 0) (LSE + (size_t)h * n_tokens + sg.q_start)[q_off] = m_run * scale + logf(l_tot);
+            if (LSE && hi == 0 && q_off < sg.q_len) (LSE + (size_t)h * n_tokens + sg.q_start)[q_off] = m_run * scale + logf(l_tot);
         }
     }
     if constexpr (DIRECT) return;
