@@ -617,6 +617,117 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(FOUR ? 4 : 
     }
 }
 
+// ------------------------------------------------------------------------------------------
+// Gather for several queries at once: a row is read once and written to every mixed set that takes it, where the kernel
+// above reads it for each of them (the line is at launch_gather).  A block takes 256 / LPR tokens (prefix rows go to all
+// queries, a chunk's rows to those that have it dense) or, behind all of those, as many kept or pooled rows (to those that
+// have it sparse); rows that nobody takes are not read.  It first forms, in LDS, where every chunk begins in every query's
+// mixed set: a wave per query, scans of 64 chunks, from lengths that all its threads have requested at once.
+// Bound by the writes: eight ragged sets of up to 35,410 rows out of 64,512 tokens (four heads, D = 128) 127.4 -> 92.2 us,
+// sixteen of 28,506 rows 253 -> 188 (934 MB).
+// ------------------------------------------------------------------------------------------
+constexpr int kSharedQueries = 32;
+
+template <int ROW_BYTES, int HEADS>                           // HEADS: KV heads whose pieces are in flight together
+__global__ __launch_bounds__(256) void gather_shared_kernel(
+    const uint4* __restrict__ K, const uint4* __restrict__ V, const uint8_t* __restrict__ dense_mask,
+    const int32_t* __restrict__ bounds, const int32_t* __restrict__ soff, const int32_t* __restrict__ sidx,
+    int n_chunks, int n_prefix, int n_tokens, int s_total, long long kv_head_u4, long long kv_tok_u4,
+    int n_kv_heads, int l_cap, int batch, uint4* __restrict__ Kmix, uint4* __restrict__ Vmix,
+    int32_t* __restrict__ mix_len, int32_t* __restrict__ src_idx, const uint4* __restrict__ Ksp, const uint4* __restrict__ Vsp) {
+    constexpr int LPR = ROW_BYTES / 16, ROWS = 256 / LPR;     // lanes per row, rows per pass
+    constexpr int DENSE = INT32_MIN;
+    extern __shared__ int off[];                              // [batch][n_chunks] first mixed row, top bit: dense; then
+    int* lo = off + batch * n_chunks;                         // [n_chunks] first token and
+    int* so = lo + n_chunks;                                  // [n_chunks] first kept row of every chunk
+    __shared__ int lens[kSharedQueries];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, part = tid % LPR;
+    for (int c = tid; c < n_chunks; c += 256) { lo[c] = bounds[c]; so[c] = soff[c]; }
+    for (int e = tid; e < batch * n_chunks; e += 256) off[e] = dense_mask[e] != 0 ? DENSE : 0;
+    __syncthreads();
+    for (int b = wave; b < batch; b += 4) {
+        int len = n_prefix;
+        for (int base = 0; base < n_chunks; base += 64) {
+            const int c = base + lane;
+            int flag = 0, rows = 0;
+            if (c < n_chunks) {
+                flag = off[b * n_chunks + c];
+                const int* first = flag ? lo : so;
+                rows = (c + 1 < n_chunks ? first[c + 1] : flag ? n_tokens : s_total) - first[c];
+            }
+            int inc = rows;
+            for (int o = 1; o < 64; o <<= 1) {
+                const int t = __shfl_up(inc, o);
+                if (lane >= o) inc += t;
+            }
+            if (c < n_chunks) off[b * n_chunks + c] = (len + inc - rows) | flag;
+            len += __shfl(inc, 63);
+        }
+        if (lane == 0) {
+            lens[b] = len;
+            // a mixed set that does not fit l_cap is reported, not truncated: minus the rows it needs
+            if (blockIdx.x == 0) mix_len[b] = len <= l_cap ? len : -len;
+        }
+    }
+    __syncthreads();
+    unsigned fits = 0;                                        // queries that get rows
+    bool past = false;
+    for (int b = 0; b < batch; ++b) {
+        if (lens[b] <= l_cap) fits |= 1u << b;
+        past |= lens[b] <= l_cap && 2ll * batch * n_kv_heads * lens[b] * ROW_BYTES > kPastCaches;
+    }
+    const int token_blocks = (n_tokens + ROWS - 1) / ROWS;
+    const bool tokens = (int)blockIdx.x < token_blocks;
+    const int r = (tokens ? blockIdx.x : blockIdx.x - token_blocks) * ROWS + tid / LPR;      // token, or kept row
+    if (r >= (tokens ? n_tokens : s_total)) return;
+    const size_t d_head = (size_t)l_cap * LPR;
+    const int* first = tokens ? lo : so;
+    int c = -1, o = r;                                    // its chunk (none: the prefix) and place in it
+    if (!tokens || r >= n_prefix) {
+        c = 0;                                            // last chunk with first[c] <= r: it lies in [c, c + span)
+        for (int span = n_chunks; span > 1;) {
+            const int step = (span + LPR - 1) / LPR;
+            const unsigned long long hit = __ballot(part * step < span && first[min(c + part * step, n_chunks - 1)] <= r);
+            const int last = __popcll((hit >> (lane & ~(LPR - 1))) & ((1ull << LPR) - 1)) - 1;
+            c += last * step;
+            span = min(step, span - last * step);
+        }
+        o = r - first[c];
+    }
+    unsigned takes = fits;                                // queries that take the row
+    if (c >= 0)
+        for (int b = 0; b < batch; ++b)
+            if ((off[b * n_chunks + c] < 0) != tokens) takes &= ~(1u << b);
+    if (!takes) return;
+    const int src = tokens ? r : Ksp ? -1 - r : sidx[r];  // token id, or -1 - pooled row
+    const uint4* ks = src >= 0 ? K : Ksp;
+    const uint4* vs = src >= 0 ? V : Vsp;
+    const size_t head_u4 = src >= 0 ? (size_t)kv_head_u4 : (size_t)s_total * LPR;
+    const size_t s_off = (src >= 0 ? (size_t)src * kv_tok_u4 : (size_t)(-1 - src) * LPR) + part;
+    for (int g0 = 0; g0 < n_kv_heads; g0 += HEADS) {
+        uint4 kq[HEADS], vq[HEADS];
+#pragma unroll
+        for (int g = 0; g < HEADS; ++g) {
+            kq[g] = ks[s_off + (g0 + g) * head_u4];
+            vq[g] = vs[s_off + (g0 + g) * head_u4];
+        }
+        for (unsigned left = takes; left; left &= left - 1) {
+            const int b = __builtin_ctz(left);
+            const int row = c >= 0 ? (off[b * n_chunks + c] & ~DENSE) + o : o;
+            if (src_idx && part == 0 && g0 == 0) src_idx[(size_t)b * l_cap + row] = src;
+            const size_t d_off = ((size_t)b * n_kv_heads * l_cap + row) * LPR + part + g0 * d_head;
+            auto store = [&](auto nt) __attribute__((always_inline)) {
+#pragma unroll
+                for (int g = 0; g < HEADS; ++g) {
+                    store16<nt>(Kmix + d_off + g * d_head, kq[g]);
+                    store16<nt>(Vmix + d_off + g * d_head, vq[g]);
+                }
+            };
+            if (past) store(std::true_type{}); else store(std::false_type{});
+        }
+    }
+}
+
 }  // namespace
 
 // kbar (n_chunks blocks per KV head; skipped when do_chunks is false) and qbar (batch blocks per KV
@@ -739,6 +850,40 @@ vxl_status launch_gather(const vxl_layout* L, const vxl_attn_desc* d, const void
     // D = 128, bf16, one query of 4,128 rows 10.1 -> 8.1, of 2,368 rows 7.2 -> 5.9; eight of 6,912 rows 51.6 -> 45.1;
     // at worst (20 to 50 MB of mixed rows in HBM) 13.4 -> 13.8 and, D = 64, 12.9 -> 13.7.  Other head counts in
     // groups of four lose up to 18 %: eight heads, D = 128, 987 MB 347 -> 377; sixteen, D = 64, 1,958 MB 602 -> 725.
+    const TokStrides ts = tok_strides(d, L->n_tokens);
+    const long long epc = d->dtype == VXL_BF16 ? 8 : 4;
+    // Several queries that take most rows more than once read each row once.  By the sets' capacity: 45 MB together, two rows
+    // per token, 128 blocks of rows per set, and chunks x queries few enough for a block's scans.  us, gather alone / with the
+    // decode behind it: 8 queries of 35,410 rows of 64,512 tokens 127.4 -> 92.2 / 251.3 -> 231.7; 8 of 6,779 rows 33.5 -> 26.0 /
+    // 71.6 -> 64.4; 2 of 43,169 rows (88 MB) 31.9 -> 28.3 / 50.4 -> 44.4; D = 64, 3 of 32,016 rows (49 MB) 20.4 -> 15.8 /
+    // 33.3 -> 28.7; at worst 8 of 3,440 rows 16.6 -> 16.8 / 58.0 -> 59.1, 16 of 8,148 rows of two heads 37.4 -> 30.2 /
+    // 52.6 -> 56.1.  Below the lines: 16 of 1,472 rows 14.5 -> 17.8, 16 of 1,496 of 5,933 tokens 17.0 -> 19.5.  Sets that
+    // leave their capacity nearly empty lose too: 2,700 rows of 136,344 21.1 -> 26.2, a quarter full they gain 1.3 to 1.4.
+    const int rows = 256 / (row_bytes / 16);
+    const long long shared_blocks = ((long long)L->n_tokens + rows - 1) / rows + (L->s_total + rows - 1) / rows;
+    if (Kmix && batch > 1 && batch <= kSharedQueries && (long long)batch * L->n_chunks <= 1024 && shared_blocks <= kMaxGridX &&
+        2ll * batch * d->n_kv_heads * l_cap * row_bytes >= 45000000ll && (long long)batch * l_cap >= 2ll * L->n_tokens &&
+        l_cap >= 128 * rows) {
+        const size_t lds = (size_t)(batch + 2) * L->n_chunks * sizeof(int);
+#define VXL_LAUNCH_AS(RB, HEADS)                                                                                        \
+    hipLaunchKernelGGL((gather_shared_kernel<RB, HEADS>), dim3((unsigned)shared_blocks), dim3(256), lds, s,              \
+                       (const uint4*)K, (const uint4*)V, dense_mask, L->d_bounds, L->d_soff, L->d_sidx, L->n_chunks,     \
+                       L->n_prefix, L->n_tokens, L->s_total, ts.kh / epc, ts.kt / epc, d->n_kv_heads, l_cap, batch,      \
+                       (uint4*)Kmix, (uint4*)Vmix, mix_len, src_idx, (const uint4*)Ksp, (const uint4*)Vsp)
+#define VXL_LAUNCH(RB)                                                                                                  \
+    do {                                                                                                                \
+        if (d->n_kv_heads == 4) VXL_LAUNCH_AS(RB, 4);                                                                   \
+        else if (d->n_kv_heads == 2) VXL_LAUNCH_AS(RB, 2);                                                              \
+        else VXL_LAUNCH_AS(RB, 1);                                                                                      \
+    } while (0)
+        if (row_bytes == 128) VXL_LAUNCH(128);
+        else if (row_bytes == 256) VXL_LAUNCH(256);
+        else VXL_LAUNCH(512);
+#undef VXL_LAUNCH
+#undef VXL_LAUNCH_AS
+        VXL_HIP_TRY(hipGetLastError());
+        return VXL_OK;
+    }
     const bool four = Kmix && d->n_kv_heads == 4;
     const size_t smem = (size_t)L->n_chunks * (four || L->n_chunks <= kTableChunks ? 2 : 1) * sizeof(int);
     // Mixed sets that would push K and V out of the 256 MB of the on-package cache go past it, queries in turn (here by the
@@ -747,8 +892,6 @@ vxl_status launch_gather(const vxl_layout* L, const vxl_attn_desc* d, const void
     // ragged prompt 250 -> 246; three of 190 MB 119.7 -> 118; one of 336 MB 206 -> 203; but three of 146 MB 103.8 -> 106,
     // one of 134 MB 86 -> 91 (the decode then reads the mixed rows from that cache).
     const bool once = Kmix && 2ll * batch * d->n_kv_heads * l_cap * row_bytes > kPastCaches;
-    const TokStrides ts = tok_strides(d, L->n_tokens);
-    const long long epc = d->dtype == VXL_BF16 ? 8 : 4;
 #define VXL_LAUNCH_AS(RB, FOUR, ONCE)                                                              \
     hipLaunchKernelGGL((gather_kernel<RB, FOUR, ONCE>), ONCE ? dim3(blocks * batch) : dim3(blocks, batch), dim3(256), smem, \
                        s, (const uint4*)K, (const uint4*)V, dense_mask, L->d_bounds, L->d_soff, L->d_sidx,  \

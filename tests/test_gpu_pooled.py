@@ -308,3 +308,54 @@ def test_gather_on_both_sides_of_the_chunk_table(n_chunks, n_kv_heads, d, pooled
         for got, x, xs in ((kmix, k, ksp), (vmix, v, vsp)):
             want = np.where((sparse >= 0)[None, :, None], xs[:, np.maximum(sparse, 0)], x[:, src]) if pooled else x[:, src]
             assert np.array_equal(vxl.to_host(got[b])[:, :n], want) and (vxl.to_host(got[b])[:, n:] == 7.0).all()
+
+
+@pytest.mark.parametrize("pooled", [False, True])
+@pytest.mark.parametrize("dtype,n_kv_heads,d,n_q,prefix,chunks,longest", [
+    ("bf16", 4, 128, 8, 5, 100, 61), ("bf16", 2, 128, 2, 0, 65, 61), ("bf16", 3, 64, 32, 17, 32, 61), ("bf16", 4, 64, 3, 5, 64, 61),
+    ("f32", 1, 64, 16, 5, 1, 61), ("f32", 4, 128, 5, 33, 200, 61), ("f32", 2, 64, 32, 0, 31, 190), ("bf16", 1, 128, 31, 5, 33, 61)])
+def test_gather_for_many_queries_is_the_gather_for_each(dtype, n_kv_heads, d, n_q, prefix, chunks, longest, pooled):
+    """Large sets of several queries are copied by the kernel that reads a row once for all of them, one query by the
+    general one: the same rows, lengths, sources and untouched bytes, bit for bit.  Queries that have every chunk dense,
+    none, or do not fit; chunks without kept rows; counts around the 64 of a scan and the 32 queries; both layouts of K
+    and V; token counts that are no multiple of a block's rows."""
+    rng = np.random.default_rng(chunks + n_q)
+    w = wl.tiny_workload(dtype, n_kv_heads, n_kv_heads, d, T=1, B=n_q, k=2, seed=chunks)
+    lay = wl.random_layout(rng, prefix, chunks, 1, longest)
+    _, k, v = wl.make_qkv(w, lay, with_q=False)
+    gl = make_layout(lay)
+    masks = (rng.random((n_q, chunks)) < np.linspace(0.0, 1.0, n_q)[:, None]).astype(np.uint8)
+    need = [prefix + sum(int(b - a) if m else int(t - s) for m, a, b, s, t in zip(
+        mask, lay.chunk_bounds, lay.chunk_bounds[1:], lay.sparse_offsets, lay.sparse_offsets[1:])) for mask in masks]
+    dm = torch.from_numpy(masks).cuda()
+    row = d * (4 if dtype == "f32" else 2)
+    # by capacity: 45 MB together, two rows per token, 128 blocks of 4,096 bytes per set
+    l_cap = max(45_000_000 // (2 * n_q * n_kv_heads * row) + 1, 2 * lay.n_tokens // n_q + 1, 128 * 4096 // row,
+                gl.mixed_kv_capacity(0))
+    assert longest == 61 or max(need) > l_cap                # one shape at least has a query that does not fit
+    for token_major in (False, True):
+        dk, dv = vxl.to_device(k, dtype), vxl.to_device(v, dtype)
+        desc = desc_of(w)
+        if token_major:
+            dk, dv = (x.transpose(0, 1).contiguous() for x in (dk, dv))
+            desc = vxl.make_desc(n_kv_heads, n_kv_heads, d, dtype, token_major=True)
+        sparse = ()
+        if pooled:
+            sparse = tuple(torch.empty((n_kv_heads, int(lay.sparse_offsets[-1]), d), dtype=dk.dtype, device="cuda") for _ in range(2))
+            vxl.pool_sparse_kv(gl, desc, dk, dv, *sparse)
+        call = vxl.gather_bilevel_kv_pooled if pooled else vxl.gather_bilevel_kv
+
+        def run(lo, hi):
+            n = hi - lo
+            kmix = torch.full((n, n_kv_heads, l_cap, d), 7.0, dtype=dk.dtype, device="cuda")
+            vmix = torch.full_like(kmix, 7.0)
+            mix_len = torch.full((n,), -9, dtype=torch.int32, device="cuda")
+            src = torch.full((n, l_cap), -5_000_000, dtype=torch.int32, device="cuda")
+            call(gl, desc, dk, dv, *sparse, dm[lo:hi].contiguous(), kmix, vmix, mix_len, src)
+            torch.cuda.synchronize()
+            return kmix, vmix, mix_len, src
+
+        together = run(0, n_q)
+        assert together[2].tolist() == [x if x <= l_cap else -x for x in need]
+        for b in range(n_q):
+            assert all(torch.equal(x[b], y[0]) for x, y in zip(together, run(b, b + 1))), b
