@@ -262,6 +262,8 @@ vxl_status vxl_gather_bilevel_kv_pooled(const vxl_layout* layout, const vxl_attn
  *            of 5,000: a second launch, which a NULL workspace avoids)
  *   workspace  VXL_F32: may be NULL, misaligned or too small; the call then cuts no keys, which is slower for long
  *            sets and sums in another order (the same result within the tolerance of the path)
+ *            VXL_BF16: 33 to 128 stacked rows over a long l_cap are asked for more bytes than the call must have: with fewer it
+ *            takes a form that needs less and is slower, and is refused only where that does not fit either
  */
 vxl_status vxl_bilevel_decode(const vxl_attn_desc* desc, const void* Qd, int32_t batch,
                               int32_t n_q_tokens, const void* Kmix, const void* Vmix,

@@ -121,7 +121,8 @@ DecodePlan decode_plan(const vxl_attn_desc* d, int batch, int T, int l_cap, bool
         // XCD, and starts as fast as the one-row-block call.  (us per call, by a 128-row kernel since replaced -> with row
         // blocks, G = 7, four KV heads; keys): 224 rows, 4,096 keys 23.4 -> 18.0; 56 rows, 7,936 keys 23.8 -> 16.0 and 45,312 keys 49.8 -> 25.3; 112
         // rows, 45,312 keys 60.2 -> 33.0; in place, 224 rows, 4,096 keys (with pooling and map) 51.8 -> 43.4.
-        // Up to 64 rows at one tile per wave the 128-row kernel stays (56 rows, 1,031 keys: 12.7 against 13.4).
+        // Up to 64 rows at one tile per wave the ring of four waves stays (blocks, ring, us: 35 rows, 750 keys 9.41, 8.69; 49
+        // rows, 1,264 keys 9.81, 9.64; not so two queries of 35 rows, 1,973 keys 11.4, 12.1).
         const bool fits = units * n_split * n_rtile <= 256 && (gathered || tpw <= 32);
         bool few = rows > 64 || tpw > 1;
         if (p.use_ring) {
@@ -148,7 +149,7 @@ DecodePlan decode_plan(const vxl_attn_desc* d, int batch, int T, int l_cap, bool
         // 3, 9.8 -> 7.5; 56 rows, 251 keys 10.9 -> 7.9, 501 keys 11.6 -> 10.2; 8 queries of 112 rows, 501 keys 13.4 -> 11.4.
         // D = 64: 7 rows, 500 keys 6.2 -> 5.6, 700 keys 6.3 -> 6.9 (call by call 9.8 -> 7.0); three queries of 140 rows, 761
         // keys 8.7 -> 8.4.  In place, where a wave pays for the row map on every tile, 12 and 16.  33 to 64 rows of D = 64 go to
-        // 12 tiles only because tests hold the range above to the 128-row kernel: one workgroup would be the faster one there
+        // 12 tiles only because tests hold the range above to 128 rows per workgroup: one workgroup would be the faster one there
         // too (64 rows, 385 keys 8.8 -> 6.4, 768 keys 7.7 -> 7.5; in place, 63 rows, 512 keys 8.6 -> 7.7).
         const bool d64 = d->head_dim == 64;
         const int one = d64 && rows > kRowBlock && rows <= 64 ? 12 : gathered ? (d64 ? 24 : 16) : (d64 ? 16 : 12);

@@ -623,8 +623,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(FOUR ? 4 : 
 // queries, a chunk's rows to those that have it dense) or, behind all of those, as many kept or pooled rows (to those that
 // have it sparse); rows that nobody takes are not read.  It first forms, in LDS, where every chunk begins in every query's
 // mixed set: a wave per query, scans of 64 chunks, from lengths that all its threads have requested at once.
-// Bound by the writes: eight ragged sets of up to 35,410 rows out of 64,512 tokens (four heads, D = 128) 127.4 -> 92.2 us,
-// sixteen of 28,506 rows 253 -> 188 (934 MB).
+// Bound by the writes: eight ragged sets of up to 35,410 rows out of 64,512 tokens (four heads, D = 128) 127.4 -> 92.2 us
+// with two sets of inputs in turn, whose K and V the on-package cache partly holds, 131 -> 114 with three and, under the
+// profiler, 134 -> 121 with four; sixteen of 28,506 rows 253 -> 188 (934 MB, two in turn).
 // ------------------------------------------------------------------------------------------
 constexpr int kSharedQueries = 32;
 
@@ -853,8 +854,8 @@ vxl_status launch_gather(const vxl_layout* L, const vxl_attn_desc* d, const void
     const TokStrides ts = tok_strides(d, L->n_tokens);
     const long long epc = d->dtype == VXL_BF16 ? 8 : 4;
     // Several queries that take most rows more than once read each row once.  By the sets' capacity: 45 MB together, two rows
-    // per token, 128 blocks of rows per set, and chunks x queries few enough for a block's scans.  us, gather alone / with the
-    // decode behind it: 8 queries of 35,410 rows of 64,512 tokens 127.4 -> 92.2 / 251.3 -> 231.7; 8 of 6,779 rows 33.5 -> 26.0 /
+    // per token, 128 blocks of rows per set, and chunks x queries few enough for a block's scans.  us, two sets of inputs in
+    // turn, gather alone / with the decode behind it: 8 queries of 35,410 rows of 64,512 tokens 127.4 -> 92.2 / 251.3 -> 231.7; 8 of 6,779 rows 33.5 -> 26.0 /
     // 71.6 -> 64.4; 2 of 43,169 rows (88 MB) 31.9 -> 28.3 / 50.4 -> 44.4; D = 64, 3 of 32,016 rows (49 MB) 20.4 -> 15.8 /
     // 33.3 -> 28.7; at worst 8 of 3,440 rows 16.6 -> 16.8 / 58.0 -> 59.1, 16 of 8,148 rows of two heads 37.4 -> 30.2 /
     // 52.6 -> 56.1.  Below the lines: 16 of 1,472 rows 14.5 -> 17.8, 16 of 1,496 of 5,933 tokens 17.0 -> 19.5.  Sets that
