@@ -623,9 +623,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(FOUR ? 4 : 
 // queries, a chunk's rows to those that have it dense) or, behind all of those, as many kept or pooled rows (to those that
 // have it sparse); rows that nobody takes are not read.  It first forms, in LDS, where every chunk begins in every query's
 // mixed set: a wave per query, scans of 64 chunks, from lengths that all its threads have requested at once.
-// Bound by the writes: eight ragged sets of up to 35,410 rows out of 64,512 tokens (four heads, D = 128) 127.4 -> 92.2 us
-// with two sets of inputs in turn, whose K and V the on-package cache partly holds, 131 -> 114 with three and, under the
-// profiler, 134 -> 121 with four; sixteen of 28,506 rows 253 -> 188 (934 MB, two in turn).
+// Bound by the writes: eight ragged sets of up to 35,410 rows out of 64,512 tokens (417 MB, four heads, D = 128), inputs not in
+// the caches, 131.9 -> 118.9 us; with two sets of inputs in turn, which the on-package cache partly holds, 127.4 -> 92.2.
+// Sixteen of 28,506 rows (934 MB) 241 -> 213 and 253 -> 188.
 // ------------------------------------------------------------------------------------------
 constexpr int kSharedQueries = 32;
 
@@ -854,12 +854,13 @@ vxl_status launch_gather(const vxl_layout* L, const vxl_attn_desc* d, const void
     const TokStrides ts = tok_strides(d, L->n_tokens);
     const long long epc = d->dtype == VXL_BF16 ? 8 : 4;
     // Several queries that take most rows more than once read each row once.  By the sets' capacity: 45 MB together, two rows
-    // per token, 128 blocks of rows per set, and chunks x queries few enough for a block's scans.  us, two sets of inputs in
-    // turn, gather alone / with the decode behind it: 8 queries of 35,410 rows of 64,512 tokens 127.4 -> 92.2 / 251.3 -> 231.7; 8 of 6,779 rows 33.5 -> 26.0 /
-    // 71.6 -> 64.4; 2 of 43,169 rows (88 MB) 31.9 -> 28.3 / 50.4 -> 44.4; D = 64, 3 of 32,016 rows (49 MB) 20.4 -> 15.8 /
-    // 33.3 -> 28.7; at worst 8 of 3,440 rows 16.6 -> 16.8 / 58.0 -> 59.1, 16 of 8,148 rows of two heads 37.4 -> 30.2 /
-    // 52.6 -> 56.1.  Below the lines: 16 of 1,472 rows 14.5 -> 17.8, 16 of 1,496 of 5,933 tokens 17.0 -> 19.5.  Sets that
-    // leave their capacity nearly empty lose too: 2,700 rows of 136,344 21.1 -> 26.2, a quarter full they gain 1.3 to 1.4.
+    // per token, 128 blocks of rows per set, and chunks x queries few enough for a block's scans.  us, inputs not in the
+    // caches, gather alone / with the decode behind it: 8 queries of 35,410 rows of 64,512 tokens 131.9 -> 118.9 / 243.6 ->
+    // 231.1; 8 of 6,779 rows 37.6 -> 31.2 / 71.7 -> 64.1; 2 of 43,169 rows (88 MB) 34.6 -> 29.4 / 54.3 -> 45.7; D = 64, 3 of
+    // 32,016 rows (49 MB) 21.6 -> 17.0 / 31.2 -> 26.6; of 48 random calls at worst 16 of 2,451 rows 31.2 -> 31.0 / 63.8 ->
+    // 65.0.  With two sets of inputs in turn at worst 8 of 3,440 rows 16.6 -> 16.8.  Below the lines, two in turn: 16 of
+    // 1,472 rows 14.5 -> 17.8, 16 of 1,496 of 5,933 tokens 17.0 -> 19.5.  Sets that leave their capacity nearly empty lose too:
+    // 2,700 rows of 136,344 21.1 -> 26.2, a quarter full they gain 1.3 to 1.4.
     const int rows = 256 / (row_bytes / 16);
     const long long shared_blocks = ((long long)L->n_tokens + rows - 1) / rows + (L->s_total + rows - 1) / rows;
     if (Kmix && batch > 1 && batch <= kSharedQueries && (long long)batch * L->n_chunks <= 1024 && shared_blocks <= kMaxGridX &&
