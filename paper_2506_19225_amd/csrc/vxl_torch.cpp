@@ -3,10 +3,10 @@
 // thirteen arguments converted took 2.5 of the 9.0 us that a generated token's call took to submit, which is 6.5 so (two
 // launches); the four calls of a prompt of 576 tokens 25.7 -> 17.1, a question's three on 16k tokens 22.5 -> 16.2.
 //
-// Arguments in the order of the C functions: a tensor (its data pointer; a contiguous CUDA tensor or AssertionError), None
-// (a null pointer), an int, the descriptor, a layout's c_void_p, and for sizes bytes((i, d)): dimension d of argument i, d
-// = 255 its number of elements (0 for None); last the stream, which vxl._stream makes a handle of when all others are
-// found good.  The result is the vxl_status.
+// Arguments in the order of the C functions, without the sizes, which are read off the tensors; last the stream, which
+// vxl._stream makes a handle of when all others are found good.  What an argument may be goes by its position alone (the
+// kinds at each function below): an object of another kind is refused, never taken for an address.  The result is the
+// vxl_status.
 #include <Python.h>
 #include <torch/csrc/autograd/python_variable.h>
 
@@ -17,7 +17,20 @@
 namespace {
 
 PyObject *desc_type, *handle_type, *stream_of;
-constexpr int kMostArgs = 18, kNumel = 255;
+
+// Kinds of an argument: a layout's c_void_p (or a number or None, the library's to refuse); the descriptor; a tensor (its
+// data pointer; a contiguous CUDA tensor or AssertionError) or None, a null pointer; a number.  Python does not pass
+// kNumel, the number of elements of the tensor before it (0 for None), and size(i, d), dimension d of its argument i.
+enum Kind { kLayout, kDesc, kTensor, kInt, kNumel, kSize };
+constexpr int size(int arg, int dim) { return kSize | arg << 8 | dim << 16; }
+
+// A number that an object answers with (a new reference, or null where it raised).
+bool take(PyObject* r, long long* out) {
+    if (!r) return false;
+    *out = (long long)PyLong_AsUnsignedLongLongMask(r);
+    Py_DECREF(r);
+    return !PyErr_Occurred();
+}
 
 // Pointer of an object that is not a torch.Tensor but answers like one.
 bool like_tensor(PyObject* o, long long* out) {
@@ -36,32 +49,27 @@ bool like_tensor(PyObject* o, long long* out) {
         PyErr_SetString(PyExc_AssertionError, "device tensors must be contiguous CUDA tensors");
         return false;
     }
-    r = PyObject_CallMethod(o, "data_ptr", nullptr);
-    if (!r) return false;
-    *out = (long long)PyLong_AsUnsignedLongLongMask(r);
-    Py_DECREF(r);
-    return !PyErr_Occurred();
+    return take(PyObject_CallMethod(o, "data_ptr", nullptr), out);
 }
 
 bool size_of(PyObject* o, int d, long long* out) {
-    if (o == Py_None && d == kNumel) { *out = 0; return true; }
     if (THPVariable_Check(o)) {
         const at::Tensor& t = THPVariable_Unpack(o);
-        if (d == kNumel) { *out = t.numel(); return true; }
         if (d >= t.dim()) { PyErr_SetString(PyExc_IndexError, "tuple index out of range"); return false; }
         *out = t.size(d);
         return true;
     }
-    PyObject* r = d == kNumel ? PyObject_CallMethod(o, "numel", nullptr) : PyObject_GetAttrString(o, "shape");
-    if (r && d != kNumel) {
-        PyObject* x = PySequence_GetItem(r, d);
-        Py_DECREF(r);
-        r = x;
-    }
-    if (!r) return false;
-    *out = (long long)PyLong_AsUnsignedLongLongMask(r);
-    Py_DECREF(r);
-    return !PyErr_Occurred();
+    PyObject* shape = PyObject_GetAttrString(o, "shape");
+    if (!shape) return false;
+    PyObject* r = PySequence_GetItem(shape, d);
+    Py_DECREF(shape);
+    return take(r, out);
+}
+
+bool numel_of(PyObject* o, long long* out) {
+    if (o == Py_None) { *out = 0; return true; }
+    if (THPVariable_Check(o)) { *out = THPVariable_Unpack(o).numel(); return true; }
+    return take(PyObject_CallMethod(o, "numel", nullptr), out);
 }
 
 // The memory of a ctypes object.
@@ -73,57 +81,77 @@ bool memory_of(PyObject* o, void** out) {
     return true;
 }
 
-bool convert(PyObject* const* args, int n, int i, long long* out) {
-    PyObject* o = args[i];
-    if (o == Py_None) { *out = 0; return true; }
-    if (THPVariable_Check(o)) {
-        const at::Tensor& t = THPVariable_Unpack(o);
-        if (!t.is_cuda() || !t.is_contiguous()) {
-            PyErr_SetString(PyExc_AssertionError, "device tensors must be contiguous CUDA tensors");
-            return false;
-        }
-        *out = (long long)t.data_ptr();
-        return true;
-    }
-    if (PyLong_Check(o)) {
-        *out = (long long)PyLong_AsUnsignedLongLongMask(o);
-        return !PyErr_Occurred();
-    }
-    if (PyBytes_Check(o)) {
-        const unsigned char* b = (const unsigned char*)PyBytes_AS_STRING(o);
-        if (PyBytes_GET_SIZE(o) != 2 || b[0] >= n) { PyErr_SetString(PyExc_ValueError, "size of which argument?"); return false; }
-        return size_of(args[b[0]], b[1], out);
-    }
-    void* p = nullptr;
-    if (PyObject_TypeCheck(o, (PyTypeObject*)desc_type)) {
-        if (!memory_of(o, &p)) return false;
-        *out = (long long)p;
-        return true;
-    }
-    if (PyObject_TypeCheck(o, (PyTypeObject*)handle_type)) {
-        if (!memory_of(o, &p)) return false;
-        *out = (long long)*(void**)p;
-        return true;
-    }
-    return like_tensor(o, out);
+bool refuse(PyObject* o, const char* what) {
+    PyErr_Format(PyExc_TypeError, "%s expected, not '%.100s'", what, Py_TYPE(o)->tp_name);
+    return false;
 }
 
-template <int N, typename F>
+bool int_of(PyObject* o, long long* out) {
+    if (!PyLong_Check(o)) return refuse(o, "a number");
+    *out = (long long)PyLong_AsUnsignedLongLongMask(o);
+    return !PyErr_Occurred();
+}
+
+bool tensor_of(PyObject* o, long long* out) {
+    if (o == Py_None) { *out = 0; return true; }
+    if (!THPVariable_Check(o)) return like_tensor(o, out);
+    const at::Tensor& t = THPVariable_Unpack(o);
+    if (!t.is_cuda() || !t.is_contiguous()) {
+        PyErr_SetString(PyExc_AssertionError, "device tensors must be contiguous CUDA tensors");
+        return false;
+    }
+    *out = (long long)t.data_ptr();
+    return true;
+}
+
+bool desc_of(PyObject* o, long long* out) {
+    void* p = nullptr;
+    if (!PyObject_TypeCheck(o, (PyTypeObject*)desc_type)) return refuse(o, "a descriptor");
+    if (!memory_of(o, &p)) return false;
+    *out = (long long)p;
+    return true;
+}
+
+bool layout_of(PyObject* o, long long* out) {
+    void* p = nullptr;
+    if (o == Py_None) { *out = 0; return true; }
+    if (PyLong_Check(o)) return int_of(o, out);
+    if (!PyObject_TypeCheck(o, (PyTypeObject*)handle_type)) return refuse(o, "a layout's handle");
+    if (!memory_of(o, &p)) return false;
+    *out = (long long)*(void**)p;
+    return true;
+}
+
+constexpr bool passed(int kind) { return kind < kNumel; }
+
+// The argument of this kind: the next of Python's, or a number read off one.
+template <int KIND>
+bool convert(PyObject* const* args, int* next, long long* out) {
+    if constexpr ((KIND & 255) == kSize) return size_of(args[KIND >> 8 & 255], KIND >> 16, out);
+    else if constexpr (KIND == kNumel) return numel_of(args[*next - 1], out);
+    else if constexpr (KIND == kLayout) return layout_of(args[(*next)++], out);
+    else if constexpr (KIND == kDesc) return desc_of(args[(*next)++], out);
+    else if constexpr (KIND == kTensor) return tensor_of(args[(*next)++], out);
+    else return int_of(args[(*next)++], out);
+}
+
+// f over the arguments of these kinds and the stream.
+template <int... KINDS, typename F>
 PyObject* call(PyObject* const* args, Py_ssize_t n, F f) {
-    static_assert(N <= kMostArgs, "");
-    if (n != N) { PyErr_Format(PyExc_TypeError, "%d arguments expected, %zd given", N, n); return nullptr; }
+    constexpr int given = (passed(KINDS) + ...) + 1;
+    if (n != given) { PyErr_Format(PyExc_TypeError, "%d arguments expected, %zd given", given, n); return nullptr; }
     if (!desc_type) { PyErr_SetString(PyExc_RuntimeError, "setup() has not been called"); return nullptr; }
-    long long a[kMostArgs];
+    long long a[sizeof...(KINDS) + 1], *out = a;
+    int next = 0;
     try {
-        for (int i = 0; i < N - 1; ++i)
-            if (!convert(args, N, i, a + i)) return nullptr;
+        if (!(convert<KINDS>(args, &next, out++) && ...)) return nullptr;
     } catch (const std::exception& e) {                       // (a tensor without memory)
         PyErr_SetString(PyExc_RuntimeError, e.what());
         return nullptr;
     }
-    PyObject* s = PyObject_CallFunctionObjArgs(stream_of, args[N - 1], nullptr);
+    PyObject* s = PyObject_CallFunctionObjArgs(stream_of, args[n - 1], nullptr);
     if (!s) return nullptr;
-    a[N - 1] = s == Py_None ? 0 : (long long)PyLong_AsUnsignedLongLongMask(s);
+    *out = s == Py_None ? 0 : (long long)PyLong_AsUnsignedLongLongMask(s);
     Py_DECREF(s);
     if (PyErr_Occurred()) return nullptr;
     vxl_status st;
@@ -138,54 +166,56 @@ const vxl_layout* lay(long long a) { return (const vxl_layout*)a; }
 const vxl_attn_desc* desc(long long a) { return (const vxl_attn_desc*)a; }
 
 PyObject* chunk_prefill(PyObject*, PyObject* const* args, Py_ssize_t n) {
-    return call<10>(args, n, [](const long long* a) {
+    return call<kLayout, kDesc, kTensor, kTensor, kTensor, kTensor, kTensor, kTensor, kNumel>(args, n, [](const long long* a) {
         return vxl_chunk_prefill(lay(a[0]), desc(a[1]), ptr<void>(a[2]), ptr<void>(a[3]), ptr<void>(a[4]), ptr<void>(a[5]),
                                  ptr<float>(a[6]), ptr<void>(a[7]), (size_t)a[8], (vxl_stream)a[9]);
     });
 }
 PyObject* chunk_score_topk(PyObject*, PyObject* const* args, Py_ssize_t n) {
-    return call<15>(args, n, [](const long long* a) {
+    return call<kLayout, kDesc, kTensor, size(2, 0), size(2, 1), kTensor, kInt, kTensor, kInt, kTensor, kTensor, kTensor, kTensor,
+                kNumel>(args, n, [](const long long* a) {
         return vxl_chunk_score_topk(lay(a[0]), desc(a[1]), ptr<void>(a[2]), (int32_t)a[3], (int32_t)a[4], ptr<void>(a[5]),
                                     (int32_t)a[6], ptr<float>(a[7]), (int32_t)a[8], ptr<int32_t>(a[9]), ptr<uint8_t>(a[10]),
                                     ptr<float>(a[11]), ptr<void>(a[12]), (size_t)a[13], (vxl_stream)a[14]);
     });
 }
 PyObject* chunk_score_topk_mass(PyObject*, PyObject* const* args, Py_ssize_t n) {
-    return call<13>(args, n, [](const long long* a) {
+    return call<kLayout, kDesc, kTensor, size(2, 0), size(2, 1), kTensor, kInt, kTensor, kTensor, kTensor, kTensor, kNumel>(args, n, [](const long long* a) {
         return vxl_chunk_score_topk_mass(lay(a[0]), desc(a[1]), ptr<void>(a[2]), (int32_t)a[3], (int32_t)a[4], ptr<void>(a[5]),
                                          (int32_t)a[6], ptr<int32_t>(a[7]), ptr<uint8_t>(a[8]), ptr<float>(a[9]),
                                          ptr<void>(a[10]), (size_t)a[11], (vxl_stream)a[12]);
     });
 }
 PyObject* gather_bilevel_kv(PyObject*, PyObject* const* args, Py_ssize_t n) {
-    return call<12>(args, n, [](const long long* a) {
+    return call<kLayout, kDesc, kTensor, kTensor, kTensor, size(5, 0), kTensor, kTensor, size(5, 2), kTensor, kTensor>(args, n, [](const long long* a) {
         return vxl_gather_bilevel_kv(lay(a[0]), desc(a[1]), ptr<void>(a[2]), ptr<void>(a[3]), ptr<uint8_t>(a[4]), (int32_t)a[5],
                                      ptr<void>(a[6]), ptr<void>(a[7]), (int32_t)a[8], ptr<int32_t>(a[9]), ptr<int32_t>(a[10]),
                                      (vxl_stream)a[11]);
     });
 }
 PyObject* pool_sparse_kv(PyObject*, PyObject* const* args, Py_ssize_t n) {
-    return call<7>(args, n, [](const long long* a) {
+    return call<kLayout, kDesc, kTensor, kTensor, kTensor, kTensor>(args, n, [](const long long* a) {
         return vxl_pool_sparse_kv(lay(a[0]), desc(a[1]), ptr<void>(a[2]), ptr<void>(a[3]), ptr<void>(a[4]), ptr<void>(a[5]),
                                   (vxl_stream)a[6]);
     });
 }
 PyObject* gather_bilevel_kv_pooled(PyObject*, PyObject* const* args, Py_ssize_t n) {
-    return call<14>(args, n, [](const long long* a) {
+    return call<kLayout, kDesc, kTensor, kTensor, kTensor, kTensor, kTensor, size(7, 0), kTensor, kTensor, size(7, 2), kTensor, kTensor>(args, n, [](const long long* a) {
         return vxl_gather_bilevel_kv_pooled(lay(a[0]), desc(a[1]), ptr<void>(a[2]), ptr<void>(a[3]), ptr<void>(a[4]),
                                             ptr<void>(a[5]), ptr<uint8_t>(a[6]), (int32_t)a[7], ptr<void>(a[8]), ptr<void>(a[9]),
                                             (int32_t)a[10], ptr<int32_t>(a[11]), ptr<int32_t>(a[12]), (vxl_stream)a[13]);
     });
 }
 PyObject* bilevel_decode(PyObject*, PyObject* const* args, Py_ssize_t n) {
-    return call<13>(args, n, [](const long long* a) {
+    return call<kDesc, kTensor, size(1, 0), size(1, 1), kTensor, kTensor, size(2, 2), kTensor, kTensor, kTensor, kTensor, kNumel>(args, n, [](const long long* a) {
         return vxl_bilevel_decode(desc(a[0]), ptr<void>(a[1]), (int32_t)a[2], (int32_t)a[3], ptr<void>(a[4]), ptr<void>(a[5]),
                                   (int32_t)a[6], ptr<int32_t>(a[7]), ptr<void>(a[8]), ptr<float>(a[9]), ptr<void>(a[10]),
                                   (size_t)a[11], (vxl_stream)a[12]);
     });
 }
 PyObject* bilevel_decode_inplace(PyObject*, PyObject* const* args, Py_ssize_t n) {
-    return call<18>(args, n, [](const long long* a) {
+    return call<kLayout, kDesc, kTensor, size(2, 0), size(2, 1), kTensor, kTensor, kTensor, kTensor, kTensor, kInt, kInt, kTensor,
+                kTensor, kTensor, kTensor, kNumel>(args, n, [](const long long* a) {
         return vxl_bilevel_decode_inplace(lay(a[0]), desc(a[1]), ptr<void>(a[2]), (int32_t)a[3], (int32_t)a[4], ptr<void>(a[5]),
                                           ptr<void>(a[6]), ptr<void>(a[7]), ptr<void>(a[8]), ptr<uint8_t>(a[9]), (int32_t)a[10],
                                           (int32_t)a[11], ptr<void>(a[12]), ptr<float>(a[13]), ptr<int32_t>(a[14]),

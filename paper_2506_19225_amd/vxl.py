@@ -134,14 +134,6 @@ def native():
     return _native
 
 
-def _size(arg: int, dim: int) -> bytes:
-    """Stands for dimension `dim` of argument `arg` in a call of the binding; _NUMEL: its number of elements."""
-    return bytes((arg, dim))
-
-
-_NUMEL = 255
-
-
 def _check(status: int, where: str) -> None:
     if status != VXL_OK:
         raise VxlError(status, where)
@@ -242,19 +234,9 @@ def alloc_workspace(nbytes: int, device="cuda") -> torch.Tensor:
     return torch.empty(max(int(nbytes), 256), dtype=torch.uint8, device=device)
 
 
-_PREFILL = (_size(7, _NUMEL),)
-_SCORE = (_size(2, 0), _size(2, 1), _size(12, _NUMEL))
-_MASS = (_size(2, 0), _size(2, 1), _size(10, _NUMEL))
-_GATHER = (_size(6, 0), _size(6, 2))
-_POOLED = (_size(8, 0), _size(8, 2))
-_DECODE = (_size(1, 0), _size(1, 1), _size(4, 2), _size(10, _NUMEL))
-_INPLACE = (_size(2, 0), _size(2, 1), _size(15, _NUMEL))
-
-
 def chunk_prefill(layout: Layout, desc: AttnDesc, q, k, v, out, lse=None, workspace=None, stream=None):
     """vxl_chunk_prefill: q/out [Hq,N,D], k/v [Hkv,N,D]; lse float32 [Hq,N] or None."""
-    st = (_native or native()).chunk_prefill(layout.handle, desc, q, k, v, out, lse, workspace, _PREFILL[0],
-                                             stream)
+    st = (_native or native()).chunk_prefill(layout.handle, desc, q, k, v, out, lse, workspace, stream)
     _check(st, "vxl_chunk_prefill")
     return out
 
@@ -262,26 +244,24 @@ def chunk_prefill(layout: Layout, desc: AttnDesc, q, k, v, out, lse=None, worksp
 def chunk_score_topk(layout: Layout, desc: AttnDesc, qd, k, top_k: int, topk_idx, dense_mask,
                      scores=None, kbar=None, kbar_ready: bool = False, workspace=None, stream=None):
     """vxl_chunk_score_topk: qd [B,T,Hq,D]; topk_idx int32 [B,min(k,C)]; dense_mask uint8 [B,C]."""
-    b, t, n = _SCORE
-    st = (_native or native()).chunk_score_topk(layout.handle, desc, qd, b, t, k, int(top_k), kbar, int(bool(kbar_ready)),
-                                                topk_idx, dense_mask, scores, workspace, n, stream)
+    st = (_native or native()).chunk_score_topk(layout.handle, desc, qd, k, int(top_k), kbar, int(bool(kbar_ready)),
+                                                topk_idx, dense_mask, scores, workspace, stream)
     _check(st, "vxl_chunk_score_topk")
 
 
 def chunk_score_topk_mass(layout: Layout, desc: AttnDesc, qd, k, top_k: int, topk_idx, dense_mask,
                           scores=None, workspace=None, stream=None):
     """vxl_chunk_score_topk_mass: arguments as chunk_score_topk, softmax attention-mass score."""
-    b, t, n = _MASS
-    st = (_native or native()).chunk_score_topk_mass(layout.handle, desc, qd, b, t, k, int(top_k), topk_idx, dense_mask,
-                                                     scores, workspace, n, stream)
+    st = (_native or native()).chunk_score_topk_mass(layout.handle, desc, qd, k, int(top_k), topk_idx, dense_mask,
+                                                     scores, workspace, stream)
     _check(st, "vxl_chunk_score_topk_mass")
 
 
 def gather_bilevel_kv(layout: Layout, desc: AttnDesc, k, v, dense_mask, kmix, vmix, mix_len,
                       src_idx=None, stream=None):
     """vxl_gather_bilevel_kv: kmix/vmix [B,Hkv,Lcap,D]; mix_len int32 [B]; src_idx int32 [B,Lcap]."""
-    st = (_native or native()).gather_bilevel_kv(layout.handle, desc, k, v, dense_mask, _GATHER[0], kmix, vmix, _GATHER[1],
-                                                 mix_len, src_idx, stream)
+    st = (_native or native()).gather_bilevel_kv(layout.handle, desc, k, v, dense_mask, kmix, vmix, mix_len,
+                                                 src_idx, stream)
     _check(st, "vxl_gather_bilevel_kv")
 
 
@@ -294,16 +274,14 @@ def pool_sparse_kv(layout: Layout, desc: AttnDesc, k, v, ksp, vsp, stream=None):
 def gather_bilevel_kv_pooled(layout: Layout, desc: AttnDesc, k, v, ksp, vsp, dense_mask, kmix, vmix, mix_len,
                              src_idx=None, stream=None):
     """vxl_gather_bilevel_kv_pooled: as gather_bilevel_kv, sparse rows taken from ksp/vsp."""
-    st = (_native or native()).gather_bilevel_kv_pooled(layout.handle, desc, k, v, ksp, vsp, dense_mask, _POOLED[0], kmix,
-                                                        vmix, _POOLED[1], mix_len, src_idx, stream)
+    st = (_native or native()).gather_bilevel_kv_pooled(layout.handle, desc, k, v, ksp, vsp, dense_mask, kmix, vmix,
+                                                        mix_len, src_idx, stream)
     _check(st, "vxl_gather_bilevel_kv_pooled")
 
 
 def bilevel_decode(desc: AttnDesc, qd, kmix, vmix, mix_len, out, lse=None, workspace=None, stream=None):
     """vxl_bilevel_decode: qd/out [B,T,Hq,D]; kmix/vmix [B,Hkv,Lcap,D]; mix_len int32 [B]."""
-    b, t, l_cap, n = _DECODE
-    st = (_native or native()).bilevel_decode(desc, qd, b, t, kmix, vmix, l_cap, mix_len, out, lse, workspace, n,
-                                              stream)
+    st = (_native or native()).bilevel_decode(desc, qd, kmix, vmix, mix_len, out, lse, workspace, stream)
     _check(st, "vxl_bilevel_decode")
     return out
 
@@ -311,10 +289,8 @@ def bilevel_decode(desc: AttnDesc, qd, kmix, vmix, mix_len, out, lse=None, works
 def bilevel_decode_inplace(layout: Layout, desc: AttnDesc, qd, k, v, ksp, vsp, dense_mask, l_cap: int, out,
                            lse=None, mix_len=None, workspace=None, map_ready: bool = False, stream=None):
     """vxl_bilevel_decode_inplace: gather-free decode; ksp/vsp [Hkv,S_total,D] or None (kept rows in place)."""
-    b, t, n = _INPLACE
-    st = (_native or native()).bilevel_decode_inplace(layout.handle, desc, qd, b, t, k, v, ksp, vsp, dense_mask, int(l_cap),
-                                                      int(bool(map_ready)), out, lse, mix_len, workspace, n,
-                                                      stream)
+    st = (_native or native()).bilevel_decode_inplace(layout.handle, desc, qd, k, v, ksp, vsp, dense_mask, int(l_cap),
+                                                      int(bool(map_ready)), out, lse, mix_len, workspace, stream)
     _check(st, "vxl_bilevel_decode_inplace")
     return out
 

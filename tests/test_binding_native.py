@@ -59,7 +59,7 @@ def test_refuses_what_is_no_contiguous_device_tensor(bad, streams):
 
 def test_refuses_other_objects(streams):
     for kw, error in ((dict(q=np.zeros((2, 3, 28, 128))), AttributeError), (dict(q=None), AttributeError),
-                      (dict(desc=C.c_int(3)), AttributeError), (dict(desc="text"), AttributeError),
+                      (dict(desc=C.c_int(3)), TypeError), (dict(desc="text"), TypeError),
                       (dict(q=Like((2,))), IndexError), (dict(k=Like((2, 4))), IndexError), (dict(stream=5), AttributeError)):
         with pytest.raises(error):
             decode(**kw)
@@ -68,10 +68,10 @@ def test_refuses_other_objects(streams):
 
 
 def test_what_reaches_the_library(streams):
-    """A null descriptor, output or length, a misaligned pointer, sizes of 0 and scratch memory too small for the sizes given
+    """A null output or length, a misaligned pointer, sizes of 0 and scratch memory too small for the sizes given
     are told apart by the library, which launches nothing for any of them."""
     assert status() == vxl.VXL_ERR_WORKSPACE and streams == [0]
-    assert status(desc=None) == status(out=None) == status(n=None) == vxl.VXL_ERR_INVALID_ARG
+    assert status(out=None) == status(n=None) == vxl.VXL_ERR_INVALID_ARG
     for kw in (dict(q=Like(Q.shape, 0x1008)), dict(k=Like(KV.shape, 0x1008)), dict(v=Like(KV.shape, 0x1008)),
                dict(out=Like(Q.shape, 0x1008)), dict(q=Like((0, 3, 28, 128))), dict(q=Like((2, 0, 28, 128))),
                dict(k=Like((2, 4, 0, 128)))):
@@ -94,3 +94,73 @@ def test_a_null_layout_is_the_librarys_to_refuse():
         with pytest.raises(vxl.VxlError) as e:
             call()
         assert e.value.status == vxl.VXL_ERR_INVALID_ARG
+
+
+# Every entry point with its arguments in order, tensors by the letter x (layouts are null ones: the library refuses those);
+# the places of the scratch memory, whose number of elements it takes, and of the tensors that it takes sizes from.
+X = Like((2, 4, 8, 128))
+CALLS = [
+    ("chunk_prefill", "layout desc x x x x x x", 7, ()), ("chunk_score_topk", "layout desc x x 1 x x x x 0 x", 10, (2,)),
+    ("chunk_score_topk_mass", "layout desc x x 1 x x x x", 8, (2,)), ("gather_bilevel_kv", "layout desc x x x x x x x", None, (5,)),
+    ("pool_sparse_kv", "layout desc x x x x", None, ()), ("gather_bilevel_kv_pooled", "layout desc x x x x x x x x x", None, (7,)),
+    ("bilevel_decode", "desc x x x x x x x", 7, (1, 2)), ("bilevel_decode_inplace", "layout desc x x x x x x 8 x x x x", 12, (2,))]
+
+
+class Closed:
+    handle = None
+
+
+@pytest.mark.parametrize("name,form", [c[:2] for c in CALLS])
+def test_no_other_object_passes_for_an_address(name, form, streams):
+    """A number, a truth value, bytes, a descriptor or a ctypes pointer where a tensor belongs, and anything but a descriptor
+    where one belongs, are refused before the library sees them."""
+    call, kinds = getattr(vxl, name), form.split()
+    args = [Closed if x == "layout" else DESC if x == "desc" else X if x == "x" else int(x) for x in kinds]
+    for i, kind in enumerate(kinds):
+        wrong = {"x": (640, 0, True, False, b"\1\0", DESC, C.c_void_p(0x1000), C.byref(DESC), 1.5, "text"),
+                 "desc": (None, 0x1000, True, b"\1\0", X, torch.zeros(4), C.c_void_p(0x1000), C.c_int(3), "text")}
+        for bad in wrong.get(kind, ()):
+            with pytest.raises(AttributeError if kind == "x" else TypeError):
+                call(*args[:i], bad, *args[i + 1:])
+    for bad in (1.5, b"ab", "text", X, DESC) if "layout" in kinds else ():
+        with pytest.raises(TypeError):
+            call(type("Other", (), {"handle": bad}), *args[1:])
+    assert not streams
+    if "layout" in kinds:                                    # (these arguments as they are reach the library)
+        with pytest.raises(vxl.VxlError):
+            call(*args)
+        assert streams == [0]
+
+
+@pytest.mark.parametrize("name,form,workspace,sized", CALLS)
+def test_sizes_come_from_these_tensors(name, form, workspace, sized):
+    class Asked(Like):
+        def __init__(self):
+            super().__init__((2, 4, 8, 128), 0x1008)       # (misaligned: the calls without a layout end here)
+            self.asked = set()
+
+        def __getattribute__(self, what):
+            if what in ("shape", "numel"):
+                self.asked.add(what)
+            return object.__getattribute__(self, what)
+
+    args = [Closed if x == "layout" else DESC if x == "desc" else Asked() if x == "x" else int(x) for x in form.split()]
+    for x in args:
+        if isinstance(x, Asked):
+            x.asked.clear()
+    with pytest.raises(vxl.VxlError) as e:
+        getattr(vxl, name)(*args)
+    assert e.value.status == vxl.VXL_ERR_INVALID_ARG
+    asked = {i: x.asked for i, x in enumerate(args) if isinstance(x, Asked)}
+    assert {i for i, a in asked.items() if "numel" in a} == ({workspace} if workspace else set())
+    assert {i for i, a in asked.items() if "shape" in a} - {workspace} == set(sized)
+
+
+def test_numbers_are_numbers():
+    n = vxl.native()
+    for bad in (None, 1.5, X, b"\1\0", DESC):
+        for at in (4, 6):                                    # top_k, kbar_ready
+            args = [None, DESC, X, X, 1, X, 0, X, X, X, X, None]
+            args[at] = bad
+            with pytest.raises(TypeError, match="a number expected"):
+                n.chunk_score_topk(*args)
