@@ -132,9 +132,9 @@ def _compile_binding() -> str:
 
 
 def _link_binding(obj: str) -> None:
-    """Beside libvxl.so, which it finds there; torch's libraries are in the process before it is loaded."""
+    """It is given libvxl.so's functions when it is loaded; torch's libraries are in the process before."""
     import torch
-    cmd = ["g++", "-shared", "-o", BINDING, obj, "-L", PKG, "-l:libvxl.so", "-Wl,-rpath,$ORIGIN",
+    cmd = ["g++", "-shared", "-o", BINDING, obj,
            "-L", os.path.join(os.path.dirname(torch.__file__), "lib"), "-ltorch_python", "-ltorch_cpu", "-lc10",
            "-Wl,--allow-shlib-undefined"]
     r = subprocess.run(cmd, capture_output=True, text=True)

@@ -18,6 +18,14 @@ namespace {
 
 PyObject *desc_type, *handle_type, *stream_of;
 
+// The functions of the library that vxl.lib() loaded, as setup() is given them: linked against it, the binding of a second
+// copy in the process called the first copy's library, and one of another path than its own was never called.
+#define VXL_PATH(X)                                                                                               \
+    X(chunk_prefill) X(chunk_score_topk) X(chunk_score_topk_mass) X(gather_bilevel_kv) X(pool_sparse_kv)          \
+    X(gather_bilevel_kv_pooled) X(bilevel_decode) X(bilevel_decode_inplace)
+#define VXL_DECLARE(name) decltype(&vxl_##name) lib_##name;
+VXL_PATH(VXL_DECLARE)
+
 // Kinds of an argument: a layout's c_void_p (or a number or None, the library's to refuse); the descriptor; a tensor (its
 // data pointer; a contiguous CUDA tensor or AssertionError) or None, a null pointer; a number.  Python does not pass
 // kNumel, the number of elements of the tensor before it (0 for None), and size(i, d), dimension d of its argument i.
@@ -167,48 +175,48 @@ const vxl_attn_desc* desc(long long a) { return (const vxl_attn_desc*)a; }
 
 PyObject* chunk_prefill(PyObject*, PyObject* const* args, Py_ssize_t n) {
     return call<kLayout, kDesc, kTensor, kTensor, kTensor, kTensor, kTensor, kTensor, kNumel>(args, n, [](const long long* a) {
-        return vxl_chunk_prefill(lay(a[0]), desc(a[1]), ptr<void>(a[2]), ptr<void>(a[3]), ptr<void>(a[4]), ptr<void>(a[5]),
+        return lib_chunk_prefill(lay(a[0]), desc(a[1]), ptr<void>(a[2]), ptr<void>(a[3]), ptr<void>(a[4]), ptr<void>(a[5]),
                                  ptr<float>(a[6]), ptr<void>(a[7]), (size_t)a[8], (vxl_stream)a[9]);
     });
 }
 PyObject* chunk_score_topk(PyObject*, PyObject* const* args, Py_ssize_t n) {
     return call<kLayout, kDesc, kTensor, size(2, 0), size(2, 1), kTensor, kInt, kTensor, kInt, kTensor, kTensor, kTensor, kTensor,
                 kNumel>(args, n, [](const long long* a) {
-        return vxl_chunk_score_topk(lay(a[0]), desc(a[1]), ptr<void>(a[2]), (int32_t)a[3], (int32_t)a[4], ptr<void>(a[5]),
+        return lib_chunk_score_topk(lay(a[0]), desc(a[1]), ptr<void>(a[2]), (int32_t)a[3], (int32_t)a[4], ptr<void>(a[5]),
                                     (int32_t)a[6], ptr<float>(a[7]), (int32_t)a[8], ptr<int32_t>(a[9]), ptr<uint8_t>(a[10]),
                                     ptr<float>(a[11]), ptr<void>(a[12]), (size_t)a[13], (vxl_stream)a[14]);
     });
 }
 PyObject* chunk_score_topk_mass(PyObject*, PyObject* const* args, Py_ssize_t n) {
     return call<kLayout, kDesc, kTensor, size(2, 0), size(2, 1), kTensor, kInt, kTensor, kTensor, kTensor, kTensor, kNumel>(args, n, [](const long long* a) {
-        return vxl_chunk_score_topk_mass(lay(a[0]), desc(a[1]), ptr<void>(a[2]), (int32_t)a[3], (int32_t)a[4], ptr<void>(a[5]),
+        return lib_chunk_score_topk_mass(lay(a[0]), desc(a[1]), ptr<void>(a[2]), (int32_t)a[3], (int32_t)a[4], ptr<void>(a[5]),
                                          (int32_t)a[6], ptr<int32_t>(a[7]), ptr<uint8_t>(a[8]), ptr<float>(a[9]),
                                          ptr<void>(a[10]), (size_t)a[11], (vxl_stream)a[12]);
     });
 }
 PyObject* gather_bilevel_kv(PyObject*, PyObject* const* args, Py_ssize_t n) {
     return call<kLayout, kDesc, kTensor, kTensor, kTensor, size(5, 0), kTensor, kTensor, size(5, 2), kTensor, kTensor>(args, n, [](const long long* a) {
-        return vxl_gather_bilevel_kv(lay(a[0]), desc(a[1]), ptr<void>(a[2]), ptr<void>(a[3]), ptr<uint8_t>(a[4]), (int32_t)a[5],
+        return lib_gather_bilevel_kv(lay(a[0]), desc(a[1]), ptr<void>(a[2]), ptr<void>(a[3]), ptr<uint8_t>(a[4]), (int32_t)a[5],
                                      ptr<void>(a[6]), ptr<void>(a[7]), (int32_t)a[8], ptr<int32_t>(a[9]), ptr<int32_t>(a[10]),
                                      (vxl_stream)a[11]);
     });
 }
 PyObject* pool_sparse_kv(PyObject*, PyObject* const* args, Py_ssize_t n) {
     return call<kLayout, kDesc, kTensor, kTensor, kTensor, kTensor>(args, n, [](const long long* a) {
-        return vxl_pool_sparse_kv(lay(a[0]), desc(a[1]), ptr<void>(a[2]), ptr<void>(a[3]), ptr<void>(a[4]), ptr<void>(a[5]),
+        return lib_pool_sparse_kv(lay(a[0]), desc(a[1]), ptr<void>(a[2]), ptr<void>(a[3]), ptr<void>(a[4]), ptr<void>(a[5]),
                                   (vxl_stream)a[6]);
     });
 }
 PyObject* gather_bilevel_kv_pooled(PyObject*, PyObject* const* args, Py_ssize_t n) {
     return call<kLayout, kDesc, kTensor, kTensor, kTensor, kTensor, kTensor, size(7, 0), kTensor, kTensor, size(7, 2), kTensor, kTensor>(args, n, [](const long long* a) {
-        return vxl_gather_bilevel_kv_pooled(lay(a[0]), desc(a[1]), ptr<void>(a[2]), ptr<void>(a[3]), ptr<void>(a[4]),
+        return lib_gather_bilevel_kv_pooled(lay(a[0]), desc(a[1]), ptr<void>(a[2]), ptr<void>(a[3]), ptr<void>(a[4]),
                                             ptr<void>(a[5]), ptr<uint8_t>(a[6]), (int32_t)a[7], ptr<void>(a[8]), ptr<void>(a[9]),
                                             (int32_t)a[10], ptr<int32_t>(a[11]), ptr<int32_t>(a[12]), (vxl_stream)a[13]);
     });
 }
 PyObject* bilevel_decode(PyObject*, PyObject* const* args, Py_ssize_t n) {
     return call<kDesc, kTensor, size(1, 0), size(1, 1), kTensor, kTensor, size(2, 2), kTensor, kTensor, kTensor, kTensor, kNumel>(args, n, [](const long long* a) {
-        return vxl_bilevel_decode(desc(a[0]), ptr<void>(a[1]), (int32_t)a[2], (int32_t)a[3], ptr<void>(a[4]), ptr<void>(a[5]),
+        return lib_bilevel_decode(desc(a[0]), ptr<void>(a[1]), (int32_t)a[2], (int32_t)a[3], ptr<void>(a[4]), ptr<void>(a[5]),
                                   (int32_t)a[6], ptr<int32_t>(a[7]), ptr<void>(a[8]), ptr<float>(a[9]), ptr<void>(a[10]),
                                   (size_t)a[11], (vxl_stream)a[12]);
     });
@@ -216,18 +224,27 @@ PyObject* bilevel_decode(PyObject*, PyObject* const* args, Py_ssize_t n) {
 PyObject* bilevel_decode_inplace(PyObject*, PyObject* const* args, Py_ssize_t n) {
     return call<kLayout, kDesc, kTensor, size(2, 0), size(2, 1), kTensor, kTensor, kTensor, kTensor, kTensor, kInt, kInt, kTensor,
                 kTensor, kTensor, kTensor, kNumel>(args, n, [](const long long* a) {
-        return vxl_bilevel_decode_inplace(lay(a[0]), desc(a[1]), ptr<void>(a[2]), (int32_t)a[3], (int32_t)a[4], ptr<void>(a[5]),
+        return lib_bilevel_decode_inplace(lay(a[0]), desc(a[1]), ptr<void>(a[2]), (int32_t)a[3], (int32_t)a[4], ptr<void>(a[5]),
                                           ptr<void>(a[6]), ptr<void>(a[7]), ptr<void>(a[8]), ptr<uint8_t>(a[9]), (int32_t)a[10],
                                           (int32_t)a[11], ptr<void>(a[12]), ptr<float>(a[13]), ptr<int32_t>(a[14]),
                                           ptr<void>(a[15]), (size_t)a[16], (vxl_stream)a[17]);
     });
 }
-// setup(type of the descriptor, type of a layout's handle, vxl._stream)
+// setup(type of the descriptor, type of a layout's handle, vxl._stream, the addresses of VXL_PATH)
 PyObject* setup(PyObject*, PyObject* const* args, Py_ssize_t n) {
-    if (n != 3 || !PyType_Check(args[0]) || !PyType_Check(args[1]) || !PyCallable_Check(args[2])) {
-        PyErr_SetString(PyExc_TypeError, "two types and a function expected");
+#define VXL_COUNT(name) + 1
+    if (n != 3 VXL_PATH(VXL_COUNT) || !PyType_Check(args[0]) || !PyType_Check(args[1]) || !PyCallable_Check(args[2])) {
+        PyErr_SetString(PyExc_TypeError, "two types, a function and the library's addresses expected");
         return nullptr;
     }
+    for (int i = 3; i < n; ++i)
+        if (!PyLong_Check(args[i]) || !PyLong_AsVoidPtr(args[i])) {
+            if (!PyErr_Occurred()) PyErr_SetString(PyExc_TypeError, "an address expected");
+            return nullptr;
+        }
+    int i = 3;
+#define VXL_TAKE(name) lib_##name = (decltype(lib_##name))PyLong_AsVoidPtr(args[i++]);
+    VXL_PATH(VXL_TAKE)
     Py_INCREF(args[0]);
     Py_INCREF(args[1]);
     Py_INCREF(args[2]);
@@ -240,11 +257,8 @@ PyObject* setup(PyObject*, PyObject* const* args, Py_ssize_t n) {
     Py_RETURN_NONE;
 }
 
-#define VXL_METHOD(name) {#name, (PyCFunction)(void (*)(void))name, METH_FASTCALL, nullptr}
-PyMethodDef methods[] = {VXL_METHOD(setup), VXL_METHOD(chunk_prefill), VXL_METHOD(chunk_score_topk),
-                         VXL_METHOD(chunk_score_topk_mass), VXL_METHOD(gather_bilevel_kv), VXL_METHOD(pool_sparse_kv),
-                         VXL_METHOD(gather_bilevel_kv_pooled), VXL_METHOD(bilevel_decode), VXL_METHOD(bilevel_decode_inplace),
-                         {nullptr, nullptr, 0, nullptr}};
+#define VXL_METHOD(name) {#name, (PyCFunction)(void (*)(void))name, METH_FASTCALL, nullptr},
+PyMethodDef methods[] = {VXL_METHOD(setup) VXL_PATH(VXL_METHOD){nullptr, nullptr, 0, nullptr}};
 PyModuleDef module = {PyModuleDef_HEAD_INIT, "_vxl_torch", nullptr, -1, methods, nullptr, nullptr, nullptr, nullptr};
 
 }  // namespace

@@ -39,6 +39,9 @@ class VxlError(RuntimeError):
 
 _lib = None
 _native = None
+# The calls of the path, in the order in which the binding takes their addresses.
+_PATH = ("chunk_prefill", "chunk_score_topk", "chunk_score_topk_mass", "gather_bilevel_kv", "pool_sparse_kv",
+         "gather_bilevel_kv_pooled", "bilevel_decode", "bilevel_decode_inplace")
 
 
 def lib() -> C.CDLL:
@@ -122,14 +125,14 @@ def native():
     """The loaded binding (raises if it has not been built): the calls of the path over torch tensors."""
     global _native
     if _native is None:
-        lib()
+        L = lib()
         if not os.path.exists(BINDING_PATH):
             raise RuntimeError(f"{BINDING_PATH} is missing: run `python -m paper_2506_19225_amd.build` "
                                "(or __graft_entry__.build()) first; there is no fallback path")
         spec = importlib.util.spec_from_file_location("_vxl_torch", BINDING_PATH)
         module = importlib.util.module_from_spec(spec)
         spec.loader.exec_module(module)
-        module.setup(AttnDesc, C.c_void_p, _stream)
+        module.setup(AttnDesc, C.c_void_p, _stream, *(C.cast(getattr(L, "vxl_" + n), C.c_void_p).value for n in _PATH))
         _native = module
     return _native
 

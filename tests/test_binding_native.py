@@ -164,3 +164,25 @@ def test_numbers_are_numbers():
             args[at] = bad
             with pytest.raises(TypeError, match="a number expected"):
                 n.chunk_score_topk(*args)
+
+
+def test_calls_end_in_the_library_that_was_loaded(streams):
+    """The binding calls the functions it was given, those of lib(), and none that the dynamic linker finds by the name of
+    the library: another copy of it in the process stays apart."""
+    n, got = vxl.native(), []
+    form = C.CFUNCTYPE(C.c_int, *[C.c_void_p] * 2, *[C.c_int32] * 2, *[C.c_void_p] * 2, C.c_int32, *[C.c_void_p] * 4,
+                       C.c_size_t, C.c_void_p)
+    other = form(lambda *a: got.append(a) or vxl.VXL_ERR_UNSUPPORTED)
+    own = [C.cast(getattr(vxl.lib(), "vxl_" + x), C.c_void_p).value for x in vxl._PATH]
+    given = list(own)
+    given[vxl._PATH.index("bilevel_decode")] = C.cast(other, C.c_void_p).value
+    try:
+        n.setup(vxl.AttnDesc, C.c_void_p, vxl._stream, *given)
+        assert status(lse=Like((2, 3, 28), 0x2000), ws=Like((77,), 0x3000)) == vxl.VXL_ERR_UNSUPPORTED
+    finally:
+        n.setup(vxl.AttnDesc, C.c_void_p, vxl._stream, *own)
+    assert got == [(C.addressof(DESC), 0x1000, 2, 3, 0x1000, 0x1000, 640, 0x1000, 0x1000, 0x2000, 0x3000, 77, None)]
+    assert status() == vxl.VXL_ERR_WORKSPACE
+    for bad in (own[:-1], own[:-1] + [0], own[:-1] + [None]):
+        with pytest.raises(TypeError):
+            n.setup(vxl.AttnDesc, C.c_void_p, vxl._stream, *bad)
