@@ -1,4 +1,4 @@
-"""Build libvxl.so (HIP, gfx950 only) in-tree with hipcc, and its torch binding with g++.  `python -m paper_2506_19225_amd.build`."""
+"""Build libvxl.so (HIP, gfx950 only) in-tree with hipcc, and its torch binding with the same compiler.  `python -m paper_2506_19225_amd.build`."""
 from __future__ import annotations
 
 import concurrent.futures as cf
@@ -13,7 +13,7 @@ ROOT = os.path.dirname(PKG)
 CSRC = os.path.join(PKG, "csrc")
 OBJ = os.path.join(PKG, "_build")
 LIB = os.path.join(PKG, "libvxl.so")
-BINDING = os.path.join(PKG, "_vxl_torch.so")
+BINDING = os.path.join(PKG, "_vxl_torch" + (sysconfig.get_config_var("EXT_SUFFIX") or ".so"))
 
 SOURCES = ["vxl_api.hip", "vxl_simple.hip", "vxl_f32.hip", "vxl_bilevel.hip", "vxl_prefill.hip", "vxl_decode.hip", "vxl_mass.hip", "vxl_store.hip", "vxl_debug.hip"]
 
@@ -115,17 +115,18 @@ def _compile(src: str) -> str:
 
 
 def _compile_binding() -> str:
-    """csrc/vxl_torch.cpp, host code against torch's headers."""
+    """csrc/vxl_torch.cpp, host code against torch's and Python's headers."""
     import torch
     top = os.path.dirname(torch.__file__)
     obj = os.path.join(OBJ, "vxl_torch.o")
-    cmd = ["g++", "-O2", "-std=c++17", "-fPIC", "-Wall", f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
+    cmd = [_hipcc(), "-x", "c++", "-O2", "-std=c++17", "-fPIC", "-Wall",
+           f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}", f'-DVXL_TORCH_VERSION="{torch.__version__}"',
            "-I", os.path.join(ROOT, "include"), "-isystem", os.path.join(top, "include"),
            "-isystem", os.path.join(top, "include", "torch", "csrc", "api", "include"),
            "-isystem", sysconfig.get_paths()["include"], "-c", os.path.join(CSRC, "vxl_torch.cpp"), "-o", obj]
     r = subprocess.run(cmd, capture_output=True, text=True)
     if r.returncode != 0:
-        raise RuntimeError(f"g++ failed on vxl_torch.cpp:\n{r.stderr}")
+        raise RuntimeError(f"hipcc failed on vxl_torch.cpp:\n{r.stderr}")
     if r.stderr.strip():
         sys.stderr.write(r.stderr)
     return obj
@@ -134,7 +135,7 @@ def _compile_binding() -> str:
 def _link_binding(obj: str) -> None:
     """It is given libvxl.so's functions when it is loaded; torch's libraries are in the process before."""
     import torch
-    cmd = ["g++", "-shared", "-o", BINDING, obj,
+    cmd = [_hipcc(), "-no-hip-rt", "-shared", "-o", BINDING, obj,
            "-L", os.path.join(os.path.dirname(torch.__file__), "lib"), "-ltorch_python", "-ltorch_cpu", "-lc10",
            "-Wl,--allow-shlib-undefined"]
     r = subprocess.run(cmd, capture_output=True, text=True)
@@ -147,12 +148,11 @@ def build_lib(verbose: bool = True) -> str:
     with cf.ThreadPoolExecutor(max_workers=min(8, len(SOURCES) + 1)) as ex:
         binding = ex.submit(_compile_binding)
         objs = list(ex.map(_compile, SOURCES))
-        binding_obj = binding.result()
     cmd = [_hipcc(), "--offload-arch=gfx950", "-shared", "-fPIC", "-o", LIB, *objs]
     r = subprocess.run(cmd, capture_output=True, text=True)
     if r.returncode != 0:
         raise RuntimeError(f"link failed:\n{r.stderr}")
-    _link_binding(binding_obj)
+    _link_binding(binding.result())          # (behind the library, which other programs use without it)
     if verbose:
         print(f"built {LIB}")
     return LIB

@@ -263,4 +263,8 @@ PyModuleDef module = {PyModuleDef_HEAD_INIT, "_vxl_torch", nullptr, -1, methods,
 
 }  // namespace
 
-PyMODINIT_FUNC PyInit__vxl_torch(void) { return PyModule_Create(&module); }
+PyMODINIT_FUNC PyInit__vxl_torch(void) {
+    PyObject* m = PyModule_Create(&module);
+    if (m && PyModule_AddStringConstant(m, "torch_version", VXL_TORCH_VERSION) < 0) Py_CLEAR(m);
+    return m;
+}

@@ -7,6 +7,7 @@ from __future__ import annotations
 import ctypes as C
 import importlib.util
 import os
+import sysconfig
 from typing import Optional
 
 import numpy as np
@@ -14,7 +15,7 @@ import torch  # imported before the library so that both use the one HIP runtime
 
 _PKG = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_PKG, "libvxl.so")
-BINDING_PATH = os.path.join(_PKG, "_vxl_torch.so")
+BINDING_PATH = os.path.join(_PKG, "_vxl_torch" + (sysconfig.get_config_var("EXT_SUFFIX") or ".so"))
 
 VXL_OK, VXL_ERR_INVALID_ARG, VXL_ERR_UNSUPPORTED, VXL_ERR_WORKSPACE, VXL_ERR_HIP, VXL_ERR_ALLOC = range(6)
 VXL_F32, VXL_BF16 = 0, 1
@@ -126,12 +127,18 @@ def native():
     global _native
     if _native is None:
         L = lib()
+        build = "run `python -m paper_2506_19225_amd.build` (or __graft_entry__.build())"
         if not os.path.exists(BINDING_PATH):
-            raise RuntimeError(f"{BINDING_PATH} is missing: run `python -m paper_2506_19225_amd.build` "
-                               "(or __graft_entry__.build()) first; there is no fallback path")
+            raise RuntimeError(f"{BINDING_PATH} is missing: {build} first; there is no fallback path")
         spec = importlib.util.spec_from_file_location("_vxl_torch", BINDING_PATH)
-        module = importlib.util.module_from_spec(spec)
-        spec.loader.exec_module(module)
+        try:
+            module = importlib.util.module_from_spec(spec)
+            spec.loader.exec_module(module)
+        except ImportError as e:
+            raise RuntimeError(f"{BINDING_PATH} does not load ({e}): {build} again") from e
+        if module.torch_version != str(torch.__version__):        # (its inlined accesses are of that one's tensors)
+            raise RuntimeError(f"{BINDING_PATH} was built for torch {module.torch_version}, this is {torch.__version__}: "
+                               f"{build} again")
         module.setup(AttnDesc, C.c_void_p, _stream, *(C.cast(getattr(L, "vxl_" + n), C.c_void_p).value for n in _PATH))
         _native = module
     return _native

@@ -186,3 +186,41 @@ def test_calls_end_in_the_library_that_was_loaded(streams):
     for bad in (own[:-1], own[:-1] + [0], own[:-1] + [None]):
         with pytest.raises(TypeError):
             n.setup(vxl.AttnDesc, C.c_void_p, vxl._stream, *bad)
+
+
+def test_the_library_is_built_where_the_binding_cannot_be(monkeypatch, tmp_path):
+    """By the compiler that builds the library; where that fails (no Python headers), the C library is there all the same, and
+    the build says what is missing."""
+    from paper_2506_19225_amd import build
+    ran = []
+
+    def run(cmd, **kw):
+        ran.append(cmd)
+        bad = any("vxl_torch" in x for x in cmd)
+        return type("Done", (), {"returncode": int(bad), "stderr": "Python.h: No such file" if bad else "", "stdout": ""})
+
+    monkeypatch.setattr(build, "OBJ", str(tmp_path))
+    monkeypatch.setattr(build, "_compile", lambda src: src)
+    monkeypatch.setattr(build.subprocess, "run", run)
+    with pytest.raises(RuntimeError, match="(?s)vxl_torch.cpp.*Python.h"):
+        build.build_lib()
+    assert any(cmd[cmd.index("-o") + 1] == build.LIB for cmd in ran)
+    assert {cmd[0] for cmd in ran} == {build._hipcc()}
+
+
+def test_a_binding_of_another_torch_or_python_says_so(monkeypatch, tmp_path):
+    from paper_2506_19225_amd import build
+    import sysconfig
+    assert vxl.BINDING_PATH == build.BINDING and vxl.BINDING_PATH.endswith(sysconfig.get_config_var("EXT_SUFFIX"))
+    vxl.native()
+    monkeypatch.setattr(vxl, "_native", None)
+    with monkeypatch.context() as m:
+        m.setattr(torch, "__version__", "0.0.1+other")
+        with pytest.raises(RuntimeError, match="built for torch .*0.0.1.other.*build"):
+            vxl.native()
+    broken = tmp_path / "broken.so"
+    broken.write_text("no library")
+    for path in (broken, tmp_path / "missing.so"):
+        monkeypatch.setattr(vxl, "BINDING_PATH", str(path))
+        with pytest.raises(RuntimeError, match="paper_2506_19225_amd.build"):
+            vxl.native()
