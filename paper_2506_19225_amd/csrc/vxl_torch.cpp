@@ -16,15 +16,18 @@
 
 namespace {
 
-PyObject *desc_type, *handle_type, *stream_of;
-
 // The functions of the library that vxl.lib() loaded, as setup() is given them: linked against it, the binding of a second
 // copy in the process called the first copy's library, and one of another path than its own was never called.
 #define VXL_PATH(X)                                                                                               \
     X(chunk_prefill) X(chunk_score_topk) X(chunk_score_topk_mass) X(gather_bilevel_kv) X(pool_sparse_kv)          \
     X(gather_bilevel_kv_pooled) X(bilevel_decode) X(bilevel_decode_inplace)
-#define VXL_DECLARE(name) decltype(&vxl_##name) lib_##name;
-VXL_PATH(VXL_DECLARE)
+
+// Of one module object: a vxl.py that is loaded twice has two.
+struct State {
+    PyObject *desc_type, *handle_type, *stream_of;
+#define VXL_DECLARE(name) decltype(&vxl_##name) name;
+    VXL_PATH(VXL_DECLARE)
+};
 
 // Kinds of an argument: a layout's c_void_p (or a number or None, the library's to refuse); the descriptor; a tensor (its
 // data pointer; a contiguous CUDA tensor or AssertionError) or None, a null pointer; a number.  Python does not pass
@@ -112,19 +115,19 @@ bool tensor_of(PyObject* o, long long* out) {
     return true;
 }
 
-bool desc_of(PyObject* o, long long* out) {
+bool desc_of(const State& st, PyObject* o, long long* out) {
     void* p = nullptr;
-    if (!PyObject_TypeCheck(o, (PyTypeObject*)desc_type)) return refuse(o, "a descriptor");
+    if (!PyObject_TypeCheck(o, (PyTypeObject*)st.desc_type)) return refuse(o, "a descriptor");
     if (!memory_of(o, &p)) return false;
     *out = (long long)p;
     return true;
 }
 
-bool layout_of(PyObject* o, long long* out) {
+bool layout_of(const State& st, PyObject* o, long long* out) {
     void* p = nullptr;
     if (o == Py_None) { *out = 0; return true; }
     if (PyLong_Check(o)) return int_of(o, out);
-    if (!PyObject_TypeCheck(o, (PyTypeObject*)handle_type)) return refuse(o, "a layout's handle");
+    if (!PyObject_TypeCheck(o, (PyTypeObject*)st.handle_type)) return refuse(o, "a layout's handle");
     if (!memory_of(o, &p)) return false;
     *out = (long long)*(void**)p;
     return true;
@@ -134,104 +137,113 @@ constexpr bool passed(int kind) { return kind < kNumel; }
 
 // The argument of this kind: the next of Python's, or a number read off one.
 template <int KIND>
-bool convert(PyObject* const* args, int* next, long long* out) {
+bool convert(const State& st, PyObject* const* args, int* next, long long* out) {
     if constexpr ((KIND & 255) == kSize) return size_of(args[KIND >> 8 & 255], KIND >> 16, out);
     else if constexpr (KIND == kNumel) return numel_of(args[*next - 1], out);
-    else if constexpr (KIND == kLayout) return layout_of(args[(*next)++], out);
-    else if constexpr (KIND == kDesc) return desc_of(args[(*next)++], out);
+    else if constexpr (KIND == kLayout) return layout_of(st, args[(*next)++], out);
+    else if constexpr (KIND == kDesc) return desc_of(st, args[(*next)++], out);
     else if constexpr (KIND == kTensor) return tensor_of(args[(*next)++], out);
     else return int_of(args[(*next)++], out);
 }
 
-// f over the arguments of these kinds and the stream.
+// f over the library's functions, the arguments of these kinds and the stream.
 template <int... KINDS, typename F>
-PyObject* call(PyObject* const* args, Py_ssize_t n, F f) {
+PyObject* call(PyObject* self, PyObject* const* args, Py_ssize_t n, F f) {
+    const State& st = *(const State*)PyModule_GetState(self);
     constexpr int given = (passed(KINDS) + ...) + 1;
     if (n != given) { PyErr_Format(PyExc_TypeError, "%d arguments expected, %zd given", given, n); return nullptr; }
-    if (!desc_type) { PyErr_SetString(PyExc_RuntimeError, "setup() has not been called"); return nullptr; }
+    if (!st.desc_type) { PyErr_SetString(PyExc_RuntimeError, "setup() has not been called"); return nullptr; }
     long long a[sizeof...(KINDS) + 1], *out = a;
     int next = 0;
     try {
-        if (!(convert<KINDS>(args, &next, out++) && ...)) return nullptr;
+        if (!(convert<KINDS>(st, args, &next, out++) && ...)) return nullptr;
     } catch (const std::exception& e) {                       // (a tensor without memory)
         PyErr_SetString(PyExc_RuntimeError, e.what());
         return nullptr;
     }
-    PyObject* s = PyObject_CallFunctionObjArgs(stream_of, args[n - 1], nullptr);
+    PyObject* s = PyObject_CallFunctionObjArgs(st.stream_of, args[n - 1], nullptr);
     if (!s) return nullptr;
     *out = s == Py_None ? 0 : (long long)PyLong_AsUnsignedLongLongMask(s);
     Py_DECREF(s);
     if (PyErr_Occurred()) return nullptr;
-    vxl_status st;
+    vxl_status status;
     Py_BEGIN_ALLOW_THREADS
-    st = f(a);
+    status = f(st, a);
     Py_END_ALLOW_THREADS
-    return PyLong_FromLong(st);
+    return PyLong_FromLong(status);
 }
 
 template <typename T> T* ptr(long long a) { return (T*)a; }
 const vxl_layout* lay(long long a) { return (const vxl_layout*)a; }
 const vxl_attn_desc* desc(long long a) { return (const vxl_attn_desc*)a; }
 
-PyObject* chunk_prefill(PyObject*, PyObject* const* args, Py_ssize_t n) {
-    return call<kLayout, kDesc, kTensor, kTensor, kTensor, kTensor, kTensor, kTensor, kNumel>(args, n, [](const long long* a) {
-        return lib_chunk_prefill(lay(a[0]), desc(a[1]), ptr<void>(a[2]), ptr<void>(a[3]), ptr<void>(a[4]), ptr<void>(a[5]),
+PyObject* chunk_prefill(PyObject* self, PyObject* const* args, Py_ssize_t n) {
+    return call<kLayout, kDesc, kTensor, kTensor, kTensor, kTensor, kTensor, kTensor, kNumel>(
+        self, args, n, [](const State& lib, const long long* a) {
+        return lib.chunk_prefill(lay(a[0]), desc(a[1]), ptr<void>(a[2]), ptr<void>(a[3]), ptr<void>(a[4]), ptr<void>(a[5]),
                                  ptr<float>(a[6]), ptr<void>(a[7]), (size_t)a[8], (vxl_stream)a[9]);
     });
 }
-PyObject* chunk_score_topk(PyObject*, PyObject* const* args, Py_ssize_t n) {
+PyObject* chunk_score_topk(PyObject* self, PyObject* const* args, Py_ssize_t n) {
     return call<kLayout, kDesc, kTensor, size(2, 0), size(2, 1), kTensor, kInt, kTensor, kInt, kTensor, kTensor, kTensor, kTensor,
-                kNumel>(args, n, [](const long long* a) {
-        return lib_chunk_score_topk(lay(a[0]), desc(a[1]), ptr<void>(a[2]), (int32_t)a[3], (int32_t)a[4], ptr<void>(a[5]),
+                kNumel>(
+        self, args, n, [](const State& lib, const long long* a) {
+        return lib.chunk_score_topk(lay(a[0]), desc(a[1]), ptr<void>(a[2]), (int32_t)a[3], (int32_t)a[4], ptr<void>(a[5]),
                                     (int32_t)a[6], ptr<float>(a[7]), (int32_t)a[8], ptr<int32_t>(a[9]), ptr<uint8_t>(a[10]),
                                     ptr<float>(a[11]), ptr<void>(a[12]), (size_t)a[13], (vxl_stream)a[14]);
     });
 }
-PyObject* chunk_score_topk_mass(PyObject*, PyObject* const* args, Py_ssize_t n) {
-    return call<kLayout, kDesc, kTensor, size(2, 0), size(2, 1), kTensor, kInt, kTensor, kTensor, kTensor, kTensor, kNumel>(args, n, [](const long long* a) {
-        return lib_chunk_score_topk_mass(lay(a[0]), desc(a[1]), ptr<void>(a[2]), (int32_t)a[3], (int32_t)a[4], ptr<void>(a[5]),
+PyObject* chunk_score_topk_mass(PyObject* self, PyObject* const* args, Py_ssize_t n) {
+    return call<kLayout, kDesc, kTensor, size(2, 0), size(2, 1), kTensor, kInt, kTensor, kTensor, kTensor, kTensor, kNumel>(
+        self, args, n, [](const State& lib, const long long* a) {
+        return lib.chunk_score_topk_mass(lay(a[0]), desc(a[1]), ptr<void>(a[2]), (int32_t)a[3], (int32_t)a[4], ptr<void>(a[5]),
                                          (int32_t)a[6], ptr<int32_t>(a[7]), ptr<uint8_t>(a[8]), ptr<float>(a[9]),
                                          ptr<void>(a[10]), (size_t)a[11], (vxl_stream)a[12]);
     });
 }
-PyObject* gather_bilevel_kv(PyObject*, PyObject* const* args, Py_ssize_t n) {
-    return call<kLayout, kDesc, kTensor, kTensor, kTensor, size(5, 0), kTensor, kTensor, size(5, 2), kTensor, kTensor>(args, n, [](const long long* a) {
-        return lib_gather_bilevel_kv(lay(a[0]), desc(a[1]), ptr<void>(a[2]), ptr<void>(a[3]), ptr<uint8_t>(a[4]), (int32_t)a[5],
+PyObject* gather_bilevel_kv(PyObject* self, PyObject* const* args, Py_ssize_t n) {
+    return call<kLayout, kDesc, kTensor, kTensor, kTensor, size(5, 0), kTensor, kTensor, size(5, 2), kTensor, kTensor>(
+        self, args, n, [](const State& lib, const long long* a) {
+        return lib.gather_bilevel_kv(lay(a[0]), desc(a[1]), ptr<void>(a[2]), ptr<void>(a[3]), ptr<uint8_t>(a[4]), (int32_t)a[5],
                                      ptr<void>(a[6]), ptr<void>(a[7]), (int32_t)a[8], ptr<int32_t>(a[9]), ptr<int32_t>(a[10]),
                                      (vxl_stream)a[11]);
     });
 }
-PyObject* pool_sparse_kv(PyObject*, PyObject* const* args, Py_ssize_t n) {
-    return call<kLayout, kDesc, kTensor, kTensor, kTensor, kTensor>(args, n, [](const long long* a) {
-        return lib_pool_sparse_kv(lay(a[0]), desc(a[1]), ptr<void>(a[2]), ptr<void>(a[3]), ptr<void>(a[4]), ptr<void>(a[5]),
+PyObject* pool_sparse_kv(PyObject* self, PyObject* const* args, Py_ssize_t n) {
+    return call<kLayout, kDesc, kTensor, kTensor, kTensor, kTensor>(
+        self, args, n, [](const State& lib, const long long* a) {
+        return lib.pool_sparse_kv(lay(a[0]), desc(a[1]), ptr<void>(a[2]), ptr<void>(a[3]), ptr<void>(a[4]), ptr<void>(a[5]),
                                   (vxl_stream)a[6]);
     });
 }
-PyObject* gather_bilevel_kv_pooled(PyObject*, PyObject* const* args, Py_ssize_t n) {
-    return call<kLayout, kDesc, kTensor, kTensor, kTensor, kTensor, kTensor, size(7, 0), kTensor, kTensor, size(7, 2), kTensor, kTensor>(args, n, [](const long long* a) {
-        return lib_gather_bilevel_kv_pooled(lay(a[0]), desc(a[1]), ptr<void>(a[2]), ptr<void>(a[3]), ptr<void>(a[4]),
+PyObject* gather_bilevel_kv_pooled(PyObject* self, PyObject* const* args, Py_ssize_t n) {
+    return call<kLayout, kDesc, kTensor, kTensor, kTensor, kTensor, kTensor, size(7, 0), kTensor, kTensor, size(7, 2), kTensor, kTensor>(
+        self, args, n, [](const State& lib, const long long* a) {
+        return lib.gather_bilevel_kv_pooled(lay(a[0]), desc(a[1]), ptr<void>(a[2]), ptr<void>(a[3]), ptr<void>(a[4]),
                                             ptr<void>(a[5]), ptr<uint8_t>(a[6]), (int32_t)a[7], ptr<void>(a[8]), ptr<void>(a[9]),
                                             (int32_t)a[10], ptr<int32_t>(a[11]), ptr<int32_t>(a[12]), (vxl_stream)a[13]);
     });
 }
-PyObject* bilevel_decode(PyObject*, PyObject* const* args, Py_ssize_t n) {
-    return call<kDesc, kTensor, size(1, 0), size(1, 1), kTensor, kTensor, size(2, 2), kTensor, kTensor, kTensor, kTensor, kNumel>(args, n, [](const long long* a) {
-        return lib_bilevel_decode(desc(a[0]), ptr<void>(a[1]), (int32_t)a[2], (int32_t)a[3], ptr<void>(a[4]), ptr<void>(a[5]),
+PyObject* bilevel_decode(PyObject* self, PyObject* const* args, Py_ssize_t n) {
+    return call<kDesc, kTensor, size(1, 0), size(1, 1), kTensor, kTensor, size(2, 2), kTensor, kTensor, kTensor, kTensor, kNumel>(
+        self, args, n, [](const State& lib, const long long* a) {
+        return lib.bilevel_decode(desc(a[0]), ptr<void>(a[1]), (int32_t)a[2], (int32_t)a[3], ptr<void>(a[4]), ptr<void>(a[5]),
                                   (int32_t)a[6], ptr<int32_t>(a[7]), ptr<void>(a[8]), ptr<float>(a[9]), ptr<void>(a[10]),
                                   (size_t)a[11], (vxl_stream)a[12]);
     });
 }
-PyObject* bilevel_decode_inplace(PyObject*, PyObject* const* args, Py_ssize_t n) {
+PyObject* bilevel_decode_inplace(PyObject* self, PyObject* const* args, Py_ssize_t n) {
     return call<kLayout, kDesc, kTensor, size(2, 0), size(2, 1), kTensor, kTensor, kTensor, kTensor, kTensor, kInt, kInt, kTensor,
-                kTensor, kTensor, kTensor, kNumel>(args, n, [](const long long* a) {
-        return lib_bilevel_decode_inplace(lay(a[0]), desc(a[1]), ptr<void>(a[2]), (int32_t)a[3], (int32_t)a[4], ptr<void>(a[5]),
+                kTensor, kTensor, kTensor, kNumel>(
+        self, args, n, [](const State& lib, const long long* a) {
+        return lib.bilevel_decode_inplace(lay(a[0]), desc(a[1]), ptr<void>(a[2]), (int32_t)a[3], (int32_t)a[4], ptr<void>(a[5]),
                                           ptr<void>(a[6]), ptr<void>(a[7]), ptr<void>(a[8]), ptr<uint8_t>(a[9]), (int32_t)a[10],
                                           (int32_t)a[11], ptr<void>(a[12]), ptr<float>(a[13]), ptr<int32_t>(a[14]),
                                           ptr<void>(a[15]), (size_t)a[16], (vxl_stream)a[17]);
     });
 }
 // setup(type of the descriptor, type of a layout's handle, vxl._stream, the addresses of VXL_PATH)
-PyObject* setup(PyObject*, PyObject* const* args, Py_ssize_t n) {
+PyObject* setup(PyObject* self, PyObject* const* args, Py_ssize_t n) {
 #define VXL_COUNT(name) + 1
     if (n != 3 VXL_PATH(VXL_COUNT) || !PyType_Check(args[0]) || !PyType_Check(args[1]) || !PyCallable_Check(args[2])) {
         PyErr_SetString(PyExc_TypeError, "two types, a function and the library's addresses expected");
@@ -242,29 +254,42 @@ PyObject* setup(PyObject*, PyObject* const* args, Py_ssize_t n) {
             if (!PyErr_Occurred()) PyErr_SetString(PyExc_TypeError, "an address expected");
             return nullptr;
         }
+    State& st = *(State*)PyModule_GetState(self);
     int i = 3;
-#define VXL_TAKE(name) lib_##name = (decltype(lib_##name))PyLong_AsVoidPtr(args[i++]);
+#define VXL_TAKE(name) st.name = (decltype(st.name))PyLong_AsVoidPtr(args[i++]);
     VXL_PATH(VXL_TAKE)
-    Py_INCREF(args[0]);
-    Py_INCREF(args[1]);
-    Py_INCREF(args[2]);
-    Py_XDECREF(desc_type);
-    Py_XDECREF(handle_type);
-    Py_XDECREF(stream_of);
-    desc_type = args[0];
-    handle_type = args[1];
-    stream_of = args[2];
+    PyObject** to[] = {&st.desc_type, &st.handle_type, &st.stream_of};
+    for (int j = 0; j < 3; ++j) {
+        Py_INCREF(args[j]);
+        Py_XSETREF(*to[j], args[j]);
+    }
     Py_RETURN_NONE;
 }
 
+int traverse(PyObject* self, visitproc visit, void* arg) {
+    const State* st = (const State*)PyModule_GetState(self);
+    if (!st) return 0;
+    Py_VISIT(st->desc_type);
+    Py_VISIT(st->handle_type);
+    Py_VISIT(st->stream_of);
+    return 0;
+}
+int clear(PyObject* self) {
+    State* st = (State*)PyModule_GetState(self);
+    if (!st) return 0;
+    Py_CLEAR(st->desc_type);
+    Py_CLEAR(st->handle_type);
+    Py_CLEAR(st->stream_of);
+    return 0;
+}
+
+int exec(PyObject* self) { return PyModule_AddStringConstant(self, "torch_version", VXL_TORCH_VERSION); }
+
 #define VXL_METHOD(name) {#name, (PyCFunction)(void (*)(void))name, METH_FASTCALL, nullptr},
 PyMethodDef methods[] = {VXL_METHOD(setup) VXL_PATH(VXL_METHOD){nullptr, nullptr, 0, nullptr}};
-PyModuleDef module = {PyModuleDef_HEAD_INIT, "_vxl_torch", nullptr, -1, methods, nullptr, nullptr, nullptr, nullptr};
+PyModuleDef_Slot slots[] = {{Py_mod_exec, (void*)exec}, {0, nullptr}};
+PyModuleDef module = {PyModuleDef_HEAD_INIT, "_vxl_torch", nullptr, sizeof(State), methods, slots, traverse, clear, nullptr};
 
 }  // namespace
 
-PyMODINIT_FUNC PyInit__vxl_torch(void) {
-    PyObject* m = PyModule_Create(&module);
-    if (m && PyModule_AddStringConstant(m, "torch_version", VXL_TORCH_VERSION) < 0) Py_CLEAR(m);
-    return m;
-}
+PyMODINIT_FUNC PyInit__vxl_torch(void) { return PyModuleDef_Init(&module); }

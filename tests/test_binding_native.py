@@ -224,3 +224,21 @@ def test_a_binding_of_another_torch_or_python_says_so(monkeypatch, tmp_path):
         monkeypatch.setattr(vxl, "BINDING_PATH", str(path))
         with pytest.raises(RuntimeError, match="paper_2506_19225_amd.build"):
             vxl.native()
+
+
+def test_two_modules_in_a_process_stay_apart(streams):
+    """Each with its own types, library and stream function, in either order of their first calls."""
+    import importlib.util
+    spec = importlib.util.spec_from_file_location("vxl_again", vxl.__file__)
+    again = importlib.util.module_from_spec(spec)
+    spec.loader.exec_module(again)
+    again._stream = lambda stream: 0
+    desc = again.make_desc(28, 4, 128, "bf16")
+    for _ in range(2):
+        assert status() == vxl.VXL_ERR_WORKSPACE
+        with pytest.raises(again.VxlError) as e:
+            again.bilevel_decode(desc, Q, KV, KV, LEN, Q)
+        assert e.value.status == vxl.VXL_ERR_WORKSPACE
+    assert len(streams) == 2
+    with pytest.raises(TypeError, match="a descriptor expected"):
+        again.bilevel_decode(DESC, Q, KV, KV, LEN, Q)
