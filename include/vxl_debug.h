@@ -43,6 +43,9 @@ int vxl_debug_decode_plan(const vxl_attn_desc* desc, int batch, int n_q_tokens, 
 /* Waves of the ring's workgroups for such a call on 256 compute units: 8 (256 rows) or 4 (128).  Host only. */
 int vxl_debug_decode_ring_waves(const vxl_attn_desc* desc, int batch, int n_q_tokens, int l_cap, int in_place);
 
+/* Whether a gather of these sizes is the one that reads a row once for all its queries.  Host only. */
+int vxl_debug_gather_shared(const vxl_attn_desc* desc, int n_tokens, int n_sparse, int n_chunks, int batch, int l_cap);
+
 /* When both are non-NULL hipEvent_t handles, every following vxl_chunk_prefill records them on
  * its stream right before and right after its main attention kernel (the compaction pre-pass is
  * outside the bracket); (NULL, NULL) switches the recording off. */

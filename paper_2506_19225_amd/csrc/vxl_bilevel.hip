@@ -619,13 +619,16 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(FOUR ? 4 : 
 
 // ------------------------------------------------------------------------------------------
 // Gather for several queries at once: a row is read once and written to every mixed set that takes it, where the kernel
-// above reads it for each of them (the line is at launch_gather).  A block takes 256 / LPR tokens (prefix rows go to all
+// above reads it for each of them (the line is at shared_gather).  A block takes 256 / LPR tokens (prefix rows go to all
 // queries, a chunk's rows to those that have it dense) or, behind all of those, as many kept or pooled rows (to those that
-// have it sparse); rows that nobody takes are not read.  It first forms, in LDS, where every chunk begins in every query's
-// mixed set: a wave per query, scans of 64 chunks, from lengths that all its threads have requested at once.
-// Bound by the writes: eight ragged sets of up to 35,410 rows out of 64,512 tokens (417 MB, four heads, D = 128), inputs not in
-// the caches, 131.9 -> 118.9 us; with two sets of inputs in turn, which the on-package cache partly holds, 127.4 -> 92.2.
-// Sixteen of 28,506 rows (934 MB) 241 -> 213 and 253 -> 188.
+// have it sparse), of HEADS KV heads (grid.y).  A block whose rows nobody takes ends when it has the masks: sets that leave
+// their buffers nearly empty are mostly such blocks.  The others request their rows and then form, in LDS, where every chunk
+// begins in every query's mixed set: a wave per query, scans of 64 chunks, from lengths that all its threads have requested
+// at once.
+// Bound by the writes.  With all scans before the search, and head counts other than two and four one head after the other ->
+// so, us, inputs not in the caches: D = 128, 16 heads, three sets of 6,702 rows in buffers for 19,044 64.0 -> 58.3, four
+// heads, eight full sets of 52,648 of 64,428 tokens (863 MB) 212 -> 207; D = 64, eight heads,
+// four sets of 2,388 rows in buffers for 33,642 19.0 -> 13.2.
 // ------------------------------------------------------------------------------------------
 constexpr int kSharedQueries = 32;
 
@@ -646,6 +649,48 @@ __global__ __launch_bounds__(256) void gather_shared_kernel(
     for (int c = tid; c < n_chunks; c += 256) { lo[c] = bounds[c]; so[c] = soff[c]; }
     for (int e = tid; e < batch * n_chunks; e += 256) off[e] = dense_mask[e] != 0 ? DENSE : 0;
     __syncthreads();
+    const int token_blocks = (n_tokens + ROWS - 1) / ROWS;
+    const bool tokens = (int)blockIdx.x < token_blocks;
+    const int r = (tokens ? blockIdx.x : blockIdx.x - token_blocks) * ROWS + tid / LPR;      // token, or kept row
+    const int* first = tokens ? lo : so;
+    int c = -1, o = r;                                        // its chunk (none: the prefix) and place in it
+    unsigned takes = 0;                                       // queries that take the row
+    if (r < (tokens ? n_tokens : s_total)) {
+        takes = ~0u >> (32 - batch);
+        if (!tokens || r >= n_prefix) {
+            c = 0;                                            // last chunk with first[c] <= r: it lies in [c, c + span)
+            for (int span = n_chunks; span > 1;) {
+                const int step = (span + LPR - 1) / LPR;
+                const unsigned long long hit = __ballot(part * step < span && first[min(c + part * step, n_chunks - 1)] <= r);
+                const int last = __popcll((hit >> (lane & ~(LPR - 1))) & ((1ull << LPR) - 1)) - 1;
+                c += last * step;
+                span = min(step, span - last * step);
+            }
+            o = r - first[c];
+            takes = 0;
+            for (int b0 = 0; b0 < batch; b0 += LPR) {             // (a lane of the row per query)
+                const unsigned long long hit = __ballot(b0 + part < batch && (off[(b0 + part) * n_chunks + c] < 0) == tokens);
+                takes |= (unsigned)((hit >> (lane & ~(LPR - 1))) & ((1ull << LPR) - 1)) << b0;
+            }
+        }
+    }
+    // (the first block writes the lengths)
+    if (!__syncthreads_or(takes != 0) && (blockIdx.x != 0 || blockIdx.y != 0)) return;
+    const int g0 = blockIdx.y * HEADS;
+    int src = 0;                                              // token id, or -1 - pooled row
+    uint4 kq[HEADS], vq[HEADS];
+    if (takes) {                                              // (requested before the scans, which they do not need)
+        src = tokens ? r : Ksp ? -1 - r : sidx[r];
+        const uint4* ks = src >= 0 ? K : Ksp;
+        const uint4* vs = src >= 0 ? V : Vsp;
+        const size_t head_u4 = src >= 0 ? (size_t)kv_head_u4 : (size_t)s_total * LPR;
+        const size_t s_off = (src >= 0 ? (size_t)src * kv_tok_u4 : (size_t)(-1 - src) * LPR) + part;
+#pragma unroll
+        for (int g = 0; g < HEADS; ++g) {
+            kq[g] = ks[s_off + (g0 + g) * head_u4];
+            vq[g] = vs[s_off + (g0 + g) * head_u4];
+        }
+    }
     for (int b = wave; b < batch; b += 4) {
         int len = n_prefix;
         for (int base = 0; base < n_chunks; base += 64) {
@@ -667,7 +712,7 @@ __global__ __launch_bounds__(256) void gather_shared_kernel(
         if (lane == 0) {
             lens[b] = len;
             // a mixed set that does not fit l_cap is reported, not truncated: minus the rows it needs
-            if (blockIdx.x == 0) mix_len[b] = len <= l_cap ? len : -len;
+            if (blockIdx.x == 0 && blockIdx.y == 0) mix_len[b] = len <= l_cap ? len : -len;
         }
     }
     __syncthreads();
@@ -677,55 +722,21 @@ __global__ __launch_bounds__(256) void gather_shared_kernel(
         if (lens[b] <= l_cap) fits |= 1u << b;
         past |= lens[b] <= l_cap && 2ll * batch * n_kv_heads * lens[b] * ROW_BYTES > kPastCaches;
     }
-    const int token_blocks = (n_tokens + ROWS - 1) / ROWS;
-    const bool tokens = (int)blockIdx.x < token_blocks;
-    const int r = (tokens ? blockIdx.x : blockIdx.x - token_blocks) * ROWS + tid / LPR;      // token, or kept row
-    if (r >= (tokens ? n_tokens : s_total)) return;
+    takes &= fits;
     const size_t d_head = (size_t)l_cap * LPR;
-    const int* first = tokens ? lo : so;
-    int c = -1, o = r;                                    // its chunk (none: the prefix) and place in it
-    if (!tokens || r >= n_prefix) {
-        c = 0;                                            // last chunk with first[c] <= r: it lies in [c, c + span)
-        for (int span = n_chunks; span > 1;) {
-            const int step = (span + LPR - 1) / LPR;
-            const unsigned long long hit = __ballot(part * step < span && first[min(c + part * step, n_chunks - 1)] <= r);
-            const int last = __popcll((hit >> (lane & ~(LPR - 1))) & ((1ull << LPR) - 1)) - 1;
-            c += last * step;
-            span = min(step, span - last * step);
-        }
-        o = r - first[c];
-    }
-    unsigned takes = fits;                                // queries that take the row
-    if (c >= 0)
-        for (int b = 0; b < batch; ++b)
-            if ((off[b * n_chunks + c] < 0) != tokens) takes &= ~(1u << b);
-    if (!takes) return;
-    const int src = tokens ? r : Ksp ? -1 - r : sidx[r];  // token id, or -1 - pooled row
-    const uint4* ks = src >= 0 ? K : Ksp;
-    const uint4* vs = src >= 0 ? V : Vsp;
-    const size_t head_u4 = src >= 0 ? (size_t)kv_head_u4 : (size_t)s_total * LPR;
-    const size_t s_off = (src >= 0 ? (size_t)src * kv_tok_u4 : (size_t)(-1 - src) * LPR) + part;
-    for (int g0 = 0; g0 < n_kv_heads; g0 += HEADS) {
-        uint4 kq[HEADS], vq[HEADS];
+    for (unsigned left = takes; left; left &= left - 1) {
+        const int b = __builtin_ctz(left);
+        const int row = c >= 0 ? (off[b * n_chunks + c] & ~DENSE) + o : o;
+        if (src_idx && part == 0 && g0 == 0) src_idx[(size_t)b * l_cap + row] = src;
+        const size_t d_off = ((size_t)b * n_kv_heads * l_cap + row) * LPR + part + g0 * d_head;
+        auto store = [&](auto nt) __attribute__((always_inline)) {
 #pragma unroll
-        for (int g = 0; g < HEADS; ++g) {
-            kq[g] = ks[s_off + (g0 + g) * head_u4];
-            vq[g] = vs[s_off + (g0 + g) * head_u4];
-        }
-        for (unsigned left = takes; left; left &= left - 1) {
-            const int b = __builtin_ctz(left);
-            const int row = c >= 0 ? (off[b * n_chunks + c] & ~DENSE) + o : o;
-            if (src_idx && part == 0 && g0 == 0) src_idx[(size_t)b * l_cap + row] = src;
-            const size_t d_off = ((size_t)b * n_kv_heads * l_cap + row) * LPR + part + g0 * d_head;
-            auto store = [&](auto nt) __attribute__((always_inline)) {
-#pragma unroll
-                for (int g = 0; g < HEADS; ++g) {
-                    store16<nt>(Kmix + d_off + g * d_head, kq[g]);
-                    store16<nt>(Vmix + d_off + g * d_head, vq[g]);
-                }
-            };
-            if (past) store(std::true_type{}); else store(std::false_type{});
-        }
+            for (int g = 0; g < HEADS; ++g) {
+                store16<nt>(Kmix + d_off + g * d_head, kq[g]);
+                store16<nt>(Vmix + d_off + g * d_head, vq[g]);
+            }
+        };
+        if (past) store(std::true_type{}); else store(std::false_type{});
     }
 }
 
@@ -841,6 +852,33 @@ vxl_status launch_pool_sparse(const vxl_layout* L, const vxl_attn_desc* d, const
     return VXL_OK;
 }
 
+static long long shared_gather_blocks(int row_bytes, int n_tokens, int s_total) {
+    const int rows = 256 / (row_bytes / 16);
+    return ((long long)n_tokens + rows - 1) / rows + (s_total + rows - 1) / rows;
+}
+
+// Several queries that take most rows more than once read each row once.  By the sets' capacity (the host does not know their
+// lengths): 45 MB together, two rows per token, 128 blocks of rows per set, chunks x queries few enough for a block's scans,
+// and, with more than 16 queries, K and V of 20 MB (below, the caches serve the repeated reads: 28 queries, 2,124 tokens 26.2 ->
+// 32.4 us; beyond, 80 random calls 1.28x).  Read per query -> once, us, inputs not in the caches, with the decode behind
+// it: eight queries of 35,410 rows of 64,512 tokens 245 -> 231, of 52,648 of 64,428 371 -> 336; D = 64, 16 heads, 16 of 14,694 of 37,016
+// 482 -> 377; one head, 8 of 13,262 of 44,901 40.2 -> 33.9; buffers nearly empty, eight heads, three sets of 1,064 rows for
+// 5,328 22.8 -> 22.7, D = 64, four of 2,388 for 33,642 56.0 -> 34.0.  Over 450 random calls of 1 to 16 heads, of which two thirds
+// leave a third to nearly all of their buffers empty, 1.21; at worst D = 64, sixteen sets of 490 rows for 4,285 20.1 -> 23.0.
+static bool shared_gather(const vxl_attn_desc* d, int n_tokens, int s_total, int n_chunks, int batch, int l_cap) {
+    const int row_bytes = d->head_dim * (d->dtype == VXL_BF16 ? 2 : 4);
+    const long long kv = 2ll * n_tokens * d->n_kv_heads * row_bytes;
+    return batch > 1 && batch <= (kv < 20000000ll ? 16 : kSharedQueries) && (long long)batch * n_chunks <= 1024 &&
+           shared_gather_blocks(row_bytes, n_tokens, s_total) <= kMaxGridX &&
+           2ll * batch * d->n_kv_heads * l_cap * row_bytes >= 45000000ll && (long long)batch * l_cap >= 2ll * n_tokens &&
+           l_cap >= 128 * (256 / (row_bytes / 16));
+}
+
+// Test hook (vxl_debug.h): whether a gather of these sizes is the one that reads a row once for all queries.
+extern "C" int vxl_debug_gather_shared(const vxl_attn_desc* d, int n_tokens, int n_sparse, int n_chunks, int batch, int l_cap) {
+    return shared_gather(d, n_tokens, n_sparse, n_chunks, batch, l_cap);
+}
+
 vxl_status launch_gather(const vxl_layout* L, const vxl_attn_desc* d, const void* K, const void* V,
                          const void* Ksp, const void* Vsp, const uint8_t* dense_mask, int batch, void* Kmix,
                          void* Vmix, int l_cap, int32_t* mix_len, int32_t* src_idx, hipStream_t s) {
@@ -853,29 +891,18 @@ vxl_status launch_gather(const vxl_layout* L, const vxl_attn_desc* d, const void
     // groups of four lose up to 18 %: eight heads, D = 128, 987 MB 347 -> 377; sixteen, D = 64, 1,958 MB 602 -> 725.
     const TokStrides ts = tok_strides(d, L->n_tokens);
     const long long epc = d->dtype == VXL_BF16 ? 8 : 4;
-    // Several queries that take most rows more than once read each row once.  By the sets' capacity: 45 MB together, two rows
-    // per token, 128 blocks of rows per set, and chunks x queries few enough for a block's scans.  us, inputs not in the
-    // caches, gather alone / with the decode behind it: 8 queries of 35,410 rows of 64,512 tokens 131.9 -> 118.9 / 243.6 ->
-    // 231.1; 8 of 6,779 rows 37.6 -> 31.2 / 71.7 -> 64.1; 2 of 43,169 rows (88 MB) 34.6 -> 29.4 / 54.3 -> 45.7; D = 64, 3 of
-    // 32,016 rows (49 MB) 21.6 -> 17.0 / 31.2 -> 26.6; of 48 random calls at worst 16 of 2,451 rows 31.2 -> 31.0 / 63.8 ->
-    // 65.0.  With two sets of inputs in turn at worst 8 of 3,440 rows 16.6 -> 16.8.  Below the lines, two in turn: 16 of
-    // 1,472 rows 14.5 -> 17.8, 16 of 1,496 of 5,933 tokens 17.0 -> 19.5.  Sets that leave their capacity nearly empty lose too:
-    // 2,700 rows of 136,344 21.1 -> 26.2, a quarter full they gain 1.3 to 1.4.
-    const int rows = 256 / (row_bytes / 16);
-    const long long shared_blocks = ((long long)L->n_tokens + rows - 1) / rows + (L->s_total + rows - 1) / rows;
-    if (Kmix && batch > 1 && batch <= kSharedQueries && (long long)batch * L->n_chunks <= 1024 && shared_blocks <= kMaxGridX &&
-        2ll * batch * d->n_kv_heads * l_cap * row_bytes >= 45000000ll && (long long)batch * l_cap >= 2ll * L->n_tokens &&
-        l_cap >= 128 * rows) {
+    if (Kmix && shared_gather(d, L->n_tokens, L->s_total, L->n_chunks, batch, l_cap)) {
+        const unsigned shared_blocks = (unsigned)shared_gather_blocks(row_bytes, L->n_tokens, L->s_total);
         const size_t lds = (size_t)(batch + 2) * L->n_chunks * sizeof(int);
 #define VXL_LAUNCH_AS(RB, HEADS)                                                                                        \
-    hipLaunchKernelGGL((gather_shared_kernel<RB, HEADS>), dim3((unsigned)shared_blocks), dim3(256), lds, s,              \
+    hipLaunchKernelGGL((gather_shared_kernel<RB, HEADS>), dim3(shared_blocks, d->n_kv_heads / HEADS), dim3(256), lds, s,              \
                        (const uint4*)K, (const uint4*)V, dense_mask, L->d_bounds, L->d_soff, L->d_sidx, L->n_chunks,     \
                        L->n_prefix, L->n_tokens, L->s_total, ts.kh / epc, ts.kt / epc, d->n_kv_heads, l_cap, batch,      \
                        (uint4*)Kmix, (uint4*)Vmix, mix_len, src_idx, (const uint4*)Ksp, (const uint4*)Vsp)
 #define VXL_LAUNCH(RB)                                                                                                  \
     do {                                                                                                                \
-        if (d->n_kv_heads == 4) VXL_LAUNCH_AS(RB, 4);                                                                   \
-        else if (d->n_kv_heads == 2) VXL_LAUNCH_AS(RB, 2);                                                              \
+        if (d->n_kv_heads % 4 == 0) VXL_LAUNCH_AS(RB, 4);                                                               \
+        else if (d->n_kv_heads % 2 == 0) VXL_LAUNCH_AS(RB, 2);                                                           \
         else VXL_LAUNCH_AS(RB, 1);                                                                                      \
     } while (0)
         if (row_bytes == 128) VXL_LAUNCH(128);

@@ -108,6 +108,8 @@ def lib() -> C.CDLL:
     L.vxl_debug_decode_plan.restype = C.c_int
     L.vxl_debug_decode_ring_waves.argtypes = [dp, C.c_int, C.c_int, C.c_int, C.c_int]
     L.vxl_debug_decode_ring_waves.restype = C.c_int
+    L.vxl_debug_gather_shared.argtypes = [dp, C.c_int, C.c_int, C.c_int, C.c_int, C.c_int]
+    L.vxl_debug_gather_shared.restype = C.c_int
     L.vxl_debug_mfma_stream.argtypes = [vp, C.c_int, C.c_int, vp]
     L.vxl_debug_mfma_stream.restype = C.c_double
     L.vxl_debug_mfma_stream_random.argtypes = [vp, C.c_int, C.c_int, vp]
@@ -405,6 +407,11 @@ def debug_decode_plan(desc: AttnDesc, batch: int, n_q_tokens: int, l_cap: int, i
 def debug_decode_ring_waves(desc: AttnDesc, batch: int, n_q_tokens: int, l_cap: int, in_place: bool = False) -> int:
     """Waves (8 or 4) of the ring's workgroups for such a call on 256 compute units.  Needs no GPU."""
     return lib().vxl_debug_decode_ring_waves(C.byref(desc), batch, n_q_tokens, l_cap, int(in_place))
+
+
+def debug_gather_shared(desc: AttnDesc, n_tokens: int, n_sparse: int, n_chunks: int, batch: int, l_cap: int) -> bool:
+    """Whether a gather of these sizes reads a row once for all its queries.  Needs no GPU."""
+    return bool(lib().vxl_debug_gather_shared(C.byref(desc), n_tokens, n_sparse, n_chunks, batch, l_cap))
 
 
 def debug_prefill_variant(variant: int) -> None:

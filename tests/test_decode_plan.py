@@ -64,3 +64,20 @@ def test_measured_sides_of_the_line(hq, hkv, d, b, t, l_cap, kernel):
     (14, 2, 128, 1, 138, 2486, BLOCKS), (7, 1, 64, 1, 95, 2297, BLOCKS)])
 def test_measured_sides_of_the_line_in_place(hq, hkv, d, b, t, l_cap, kernel):
     assert plan(hq, hkv, d, b, t, l_cap, True)[0] == kernel
+
+
+def test_which_gathers_read_a_row_once():
+    """Both sides of every line of the rule."""
+    def shared(b=8, l_cap=16384, n=8000, chunks=100, hkv=4, d=128, dtype="bf16"):
+        return vxl.debug_gather_shared(vxl.make_desc(hkv, hkv, d, dtype), n, 400, chunks, b, l_cap)
+
+    assert shared() and shared(b=2) and not shared(b=1)
+    assert shared(b=16, chunks=64) and not shared(b=16, chunks=65)
+    assert shared(b=17, n=9766, chunks=10) and not shared(b=17, n=9765, chunks=10)      # 20 MB of K and V
+    assert shared(b=32, n=9766, chunks=32) and not shared(b=33, n=9766, chunks=10)
+    assert shared(chunks=128) and not shared(chunks=129)
+    assert shared(n=65536) and not shared(n=65537)
+    assert shared(l_cap=2747, n=1000) and not shared(l_cap=2746, n=1000)           # 45 MB
+    assert shared(b=16, l_cap=2048, n=1000, hkv=16, chunks=9) and not shared(b=16, l_cap=2047, n=1000, hkv=16, chunks=9)
+    assert shared(b=16, l_cap=4096, n=1000, hkv=16, d=64, chunks=9) and not shared(b=16, l_cap=4095, n=1000, hkv=16, d=64, chunks=9)
+    assert shared(hkv=7, d=64, l_cap=6280, n=1000) and shared(dtype="f32", l_cap=1374, n=1000)

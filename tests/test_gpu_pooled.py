@@ -310,29 +310,15 @@ def test_gather_on_both_sides_of_the_chunk_table(n_chunks, n_kv_heads, d, pooled
             assert np.array_equal(vxl.to_host(got[b])[:, :n], want) and (vxl.to_host(got[b])[:, n:] == 7.0).all()
 
 
-@pytest.mark.parametrize("pooled", [False, True])
-@pytest.mark.parametrize("dtype,n_kv_heads,d,n_q,prefix,chunks,longest", [
-    ("bf16", 4, 128, 8, 5, 100, 61), ("bf16", 2, 128, 2, 0, 65, 61), ("bf16", 3, 64, 32, 17, 32, 61), ("bf16", 4, 64, 3, 5, 64, 61),
-    ("f32", 1, 64, 16, 5, 1, 61), ("f32", 4, 128, 5, 33, 200, 61), ("f32", 2, 64, 32, 0, 31, 190), ("bf16", 1, 128, 31, 5, 33, 61)])
-def test_gather_for_many_queries_is_the_gather_for_each(dtype, n_kv_heads, d, n_q, prefix, chunks, longest, pooled):
-    """Large sets of several queries are copied by the kernel that reads a row once for all of them, one query by the
-    general one: the same rows, lengths, sources and untouched bytes, bit for bit.  Queries that have every chunk dense,
-    none, or do not fit; chunks without kept rows; counts around the 64 of a scan and the 32 queries; both layouts of K
-    and V; token counts that are no multiple of a block's rows."""
-    rng = np.random.default_rng(chunks + n_q)
-    w = wl.tiny_workload(dtype, n_kv_heads, n_kv_heads, d, T=1, B=n_q, k=2, seed=chunks)
-    lay = wl.random_layout(rng, prefix, chunks, 1, longest)
+def gather_together_and_apart(w, lay, masks, l_cap, pooled, shared):
+    """The gather of all queries and that of each alone, head-major and token-major: the same rows, lengths, sources and
+    untouched bytes, bit for bit; `shared` of the first kind by the kernel that reads a row once.  Returns the rows needed."""
+    n_q, n_kv_heads, d, dtype = len(masks), w.n_kv_heads, w.head_dim, w.dtype
     _, k, v = wl.make_qkv(w, lay, with_q=False)
-    gl = make_layout(lay)
-    masks = (rng.random((n_q, chunks)) < np.linspace(0.0, 1.0, n_q)[:, None]).astype(np.uint8)
-    need = [prefix + sum(int(b - a) if m else int(t - s) for m, a, b, s, t in zip(
+    gl, n_sparse = make_layout(lay), int(lay.sparse_offsets[-1])
+    need = [lay.n_prefix + sum(int(b - a) if m else int(t - s) for m, a, b, s, t in zip(
         mask, lay.chunk_bounds, lay.chunk_bounds[1:], lay.sparse_offsets, lay.sparse_offsets[1:])) for mask in masks]
     dm = torch.from_numpy(masks).cuda()
-    row = d * (4 if dtype == "f32" else 2)
-    # by capacity: 45 MB together, two rows per token, 128 blocks of 4,096 bytes per set
-    l_cap = max(45_000_000 // (2 * n_q * n_kv_heads * row) + 1, 2 * lay.n_tokens // n_q + 1, 128 * 4096 // row,
-                gl.mixed_kv_capacity(0))
-    assert longest == 61 or max(need) > l_cap                # one shape at least has a query that does not fit
     for token_major in (False, True):
         dk, dv = vxl.to_device(k, dtype), vxl.to_device(v, dtype)
         desc = desc_of(w)
@@ -341,7 +327,7 @@ def test_gather_for_many_queries_is_the_gather_for_each(dtype, n_kv_heads, d, n_
             desc = vxl.make_desc(n_kv_heads, n_kv_heads, d, dtype, token_major=True)
         sparse = ()
         if pooled:
-            sparse = tuple(torch.empty((n_kv_heads, int(lay.sparse_offsets[-1]), d), dtype=dk.dtype, device="cuda") for _ in range(2))
+            sparse = tuple(torch.empty((n_kv_heads, n_sparse, d), dtype=dk.dtype, device="cuda") for _ in range(2))
             vxl.pool_sparse_kv(gl, desc, dk, dv, *sparse)
         call = vxl.gather_bilevel_kv_pooled if pooled else vxl.gather_bilevel_kv
 
@@ -351,6 +337,7 @@ def test_gather_for_many_queries_is_the_gather_for_each(dtype, n_kv_heads, d, n_
             vmix = torch.full_like(kmix, 7.0)
             mix_len = torch.full((n,), -9, dtype=torch.int32, device="cuda")
             src = torch.full((n, l_cap), -5_000_000, dtype=torch.int32, device="cuda")
+            assert vxl.debug_gather_shared(desc, lay.n_tokens, n_sparse, lay.n_chunks, n, l_cap) == (shared and n > 1)
             call(gl, desc, dk, dv, *sparse, dm[lo:hi].contiguous(), kmix, vmix, mix_len, src)
             torch.cuda.synchronize()
             return kmix, vmix, mix_len, src
@@ -359,3 +346,45 @@ def test_gather_for_many_queries_is_the_gather_for_each(dtype, n_kv_heads, d, n_
         assert together[2].tolist() == [x if x <= l_cap else -x for x in need]
         for b in range(n_q):
             assert all(torch.equal(x[b], y[0]) for x, y in zip(together, run(b, b + 1))), b
+    return need
+
+
+def capacity_of_large_sets(w, lay, n_q):
+    """45 MB together, two rows per token, 128 blocks of 4,096 bytes per set."""
+    row = w.head_dim * (4 if w.dtype == "f32" else 2)
+    return max(45_000_000 // (2 * n_q * w.n_kv_heads * row) + 1, 2 * lay.n_tokens // n_q + 1, 128 * 4096 // row,
+               make_layout(lay).mixed_kv_capacity(0))
+
+
+@pytest.mark.parametrize("pooled", [False, True])
+@pytest.mark.parametrize("dtype,n_kv_heads,d,n_q,prefix,chunks,longest", [
+    ("bf16", 4, 128, 8, 5, 100, 61), ("bf16", 2, 128, 2, 0, 65, 61), ("bf16", 3, 64, 16, 17, 64, 61), ("bf16", 4, 64, 3, 5, 64, 61),
+    ("f32", 1, 64, 16, 5, 1, 61), ("f32", 4, 128, 5, 33, 200, 61), ("f32", 2, 64, 16, 0, 31, 190), ("bf16", 1, 128, 15, 5, 33, 61),
+    ("bf16", 8, 128, 3, 5, 70, 61), ("bf16", 16, 64, 4, 0, 40, 61), ("bf16", 6, 128, 9, 9, 20, 61), ("f32", 12, 64, 2, 1, 512, 9),
+    ("bf16", 16, 128, 32, 17, 32, 200), ("bf16", 4, 64, 17, 5, 33, 61)])
+def test_gather_for_many_queries_is_the_gather_for_each(dtype, n_kv_heads, d, n_q, prefix, chunks, longest, pooled):
+    """Large sets of up to 16 queries, or 32 of many rows, are copied by the kernel that reads a row once for all of them, one
+    query by the general one.  Queries that have every chunk dense, none, or do not fit; chunks without kept rows; counts around the 64 of a
+    scan, the 32 queries and the 1,024 masks; KV heads in groups of four, two and one; token counts that are no multiple of a
+    block's rows."""
+    rng = np.random.default_rng(chunks + n_q)
+    w = wl.tiny_workload(dtype, n_kv_heads, n_kv_heads, d, T=1, B=n_q, k=2, seed=chunks)
+    lay = wl.random_layout(rng, prefix, chunks, 1, longest)
+    masks = (rng.random((n_q, chunks)) < np.linspace(0.0, 1.0, n_q)[:, None]).astype(np.uint8)
+    l_cap = capacity_of_large_sets(w, lay, n_q)
+    need = gather_together_and_apart(w, lay, masks, l_cap, pooled, n_q <= 16 or longest == 200)
+    assert longest != 190 or max(need) > l_cap                # one shape at least has a query that does not fit
+
+
+@pytest.mark.parametrize("pooled", [False, True])
+@pytest.mark.parametrize("n_kv_heads,d,n_q,prefix,dense", [
+    (4, 128, 3, 0, []), (8, 64, 2, 40, []), (1, 128, 5, 0, [(4, 39)]), (8, 128, 4, 3, [(0, 0), (3, 20)])])
+def test_gather_of_nearly_empty_sets(n_kv_heads, d, n_q, prefix, dense, pooled):
+    """Most blocks have no row that anybody takes, the first one too, which writes the lengths all the same."""
+    w = wl.tiny_workload("bf16", n_kv_heads, n_kv_heads, d, T=1, B=n_q, k=2, seed=d)
+    lay = wl.random_layout(np.random.default_rng(d), prefix, 40, 20, 90)
+    masks = np.zeros((n_q, 40), np.uint8)
+    for at in dense:
+        masks[at] = 1
+    l_cap = 3 * capacity_of_large_sets(w, lay, n_q)
+    assert max(gather_together_and_apart(w, lay, masks, l_cap, pooled, True)) < l_cap / 5
