@@ -734,6 +734,7 @@ static vxl_status launch_merge(int n_split, const float* part_o, const float* pa
 struct RingLaunch {
     int waves, n_split, n_rtile;
     bool spread;                // no two workgroups on a compute unit
+    long long walk;             // tiles that the last workgroup has ended with
     float us;                   // estimate of kernel and merge
 };
 static RingLaunch ring_launch(const vxl_attn_desc* d, int batch, int rows, int l_cap, int most_splits, int n_cus, int waves,
@@ -752,27 +753,32 @@ static RingLaunch ring_launch(const vxl_attn_desc* d, int batch, int rows, int l
     r.spread = d64 && r.n_split * per_split <= n_cus;
     const int slots = d64 && !r.spread ? 2 * n_cus : n_cus;
     const long long rounds = (r.n_split * per_split + slots - 1) / slots;
-    // us of start, a tile and a MB of partial rows: least squares over 139 (D = 128) and 120 (D = 64) random calls of 129 to
-    // 1,400 rows, off by 4 to 7 % (rms), and over 53 and 7 in place, off by 4.
-    static constexpr float kUs[2][2][2][3] = {{{{8.9f, 1.62f, 0.51f}, {7.3f, 1.05f, 0.61f}},          // gathered
-                                               {{7.2f, 1.08f, 0.70f}, {5.8f, 0.72f, 0.91f}}},
-                                              {{{18.5f, 1.69f, 0.22f}, {15.0f, 1.09f, 0.46f}},        // in place
-                                               {{13.7f, 1.19f, 0.51f}, {12.9f, 0.85f, 0.50f}}}};      // [D = 64][4 waves]
+    // us of start, a tile (D = 64: of a workgroup alone on its unit, of one of two) and a MB of partial rows: least squares over
+    // random calls of 129 to 1,400 rows.  Gathered, 139 (D = 128) and 120, in place 120 and 210; off by 6 to 8 % (rms) on the
+    // half of the calls that was kept out of the fit.
+    static constexpr float kUs[2][2][2][4] = {{{{8.9f, 1.62f, 1.62f, 0.51f}, {7.3f, 1.05f, 1.05f, 0.61f}},          // gathered
+                                               {{7.1f, 1.04f, 1.73f, 0.72f}, {5.8f, 0.69f, 1.03f, 0.99f}}},
+                                              {{{10.3f, 1.61f, 1.61f, 0.44f}, {8.4f, 1.10f, 1.10f, 0.62f}},         // in place
+                                               {{7.9f, 1.08f, 2.24f, 0.70f}, {6.3f, 0.77f, 1.17f, 0.95f}}}};        // [D = 64][4 waves]
     const float* us = kUs[in_place][d64][waves == 4];
-    const float walk = (float)((tiles + r.n_split - 1) / r.n_split * rounds);
+    r.walk = (tiles + r.n_split - 1) / r.n_split * rounds;
     const float mb = r.n_split > 1 ? 4e-6f * pairs * rows * r.n_split * d->head_dim : 0.f;
-    r.us = us[0] + us[1] * walk + us[2] * mb;
+    r.us = us[0] + us[r.spread ? 1 : 2] * (float)r.walk + us[3] * mb;
     return r;
 }
 
-// Four waves where they are the shorter call by these estimates: over 160 random calls the time is 0.91 of that of always
-// eight (0.72 to 1.00), in place over 70 0.94 (0.81 to 1.04).  448 rows, 10,368 keys 29.4 -> 25.7 us; 588 rows x 8 queries, 674 keys, one split
-// 26.2 -> 18.8; but 301 rows x 8, 23,830 keys 174.9 against 202 with four.
+// Four waves where they are the shorter call by these estimates, in place by more than 4 %: over 159 gathered calls outside
+// the fits the time is 0.92 of that of always eight (0.70 to 1.04), over 199 in place 0.92 (0.72 to 1.03; by 2 % three more were
+// slower, to 1.04).  448 rows, 10,368 keys 29.4 -> 25.7 us; 588 rows x 8 queries, 674 keys, one split 26.2 -> 18.8; but 301 rows x 8,
+// 23,830 keys 174.9 against 202 with four.  D = 64: not where a unit's two workgroups of four walk as many tiles each as its one
+// of eight, the same waves that read the keys twice (in place, 1,316 rows x 8, 1,094 keys 27.4 with four, 25.1; 1,360 on eight
+// heads x 3, 35,009 keys 673, 633; gathered, 1,233 on 16 heads x 3, 856 keys 23.4, 22.5).
 static RingLaunch choose_ring(const vxl_attn_desc* d, int batch, int rows, int l_cap, int most_splits, int n_cus,
                               bool in_place) {
     const RingLaunch eight = ring_launch(d, batch, rows, l_cap, most_splits, n_cus, 8, in_place);
     const RingLaunch four = ring_launch(d, batch, rows, l_cap, most_splits, n_cus, 4, in_place);
-    return four.us < 0.98f * eight.us && (long long)four.n_rtile * d->n_kv_heads <= 65535 ? four : eight;
+    if (d->head_dim == 64 && !four.spread && eight.spread && four.walk >= eight.walk) return eight;
+    return four.us < (in_place ? 0.96f : 0.98f) * eight.us && (long long)four.n_rtile * d->n_kv_heads <= 65535 ? four : eight;
 }
 
 // Test hook (vxl_debug.h): the waves of the ring kernel's workgroups on 256 compute units.

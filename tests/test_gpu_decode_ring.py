@@ -57,7 +57,7 @@ def test_either_number_of_waves(hq, hkv, t, d, waves, lens, l_cap):
 
 @pytest.mark.parametrize("mode", ["kept_in_place", "pooled"])
 @pytest.mark.parametrize("hq,t,d,waves,chunks,length", [
-    (14, 150, 128, 4, 15, 800), (14, 300, 64, 4, 20, 800), (14, 55, 128, 8, 90, 900)])
+    (14, 150, 128, 4, 15, 800), (14, 300, 64, 4, 20, 800), (14, 55, 128, 8, 90, 900), (14, 55, 64, 8, 90, 900)])
 def test_either_number_of_waves_in_place(mode, hq, t, d, waves, chunks, length):
     rng = np.random.default_rng(87 + t)
     w = wl.tiny_workload("bf16", hq, 2, d, T=t, B=1, k=3, seed=87, value_scale=0.5)
