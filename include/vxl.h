@@ -263,7 +263,8 @@ vxl_status vxl_gather_bilevel_kv_pooled(const vxl_layout* layout, const vxl_attn
  *   workspace  VXL_F32: may be NULL, misaligned or too small; the call then cuts no keys, which is slower for long
  *            sets and sums in another order (the same result within the tolerance of the path)
  *            VXL_BF16: 33 to 128 stacked rows over a long l_cap are asked for more bytes than the call must have: with fewer it
- *            takes a form that needs less and is slower, and is refused only where that does not fit either
+ *            takes a form that needs less, is slower and sums in another order (the same result within the tolerance of
+ *            the path), and is refused only where that does not fit either
  */
 vxl_status vxl_bilevel_decode(const vxl_attn_desc* desc, const void* Qd, int32_t batch,
                               int32_t n_q_tokens, const void* Kmix, const void* Vmix,
@@ -298,7 +299,8 @@ vxl_status vxl_bilevel_decode(const vxl_attn_desc* desc, const void* Qd, int32_t
  *   mix_len     device int32 [batch] (the mixed lengths: written when map_ready == 0, read
  *               otherwise) or NULL (they are then kept in the workspace)
  *   workspace   sized by vxl_workspace_bytes(VXL_OP_DECODE_INPLACE, layout, desc, batch, n_q_tokens, l_cap)
- *               (VXL_F32: one that holds the map and 256 bytes is enough; see vxl_bilevel_decode)
+ *               (VXL_F32: one that holds the map and 256 bytes is enough; VXL_BF16: 33 to 128 rows over a long l_cap
+ *               take fewer bytes too, in another form; see vxl_bilevel_decode for both)
  * The set of rows a query attends to is exactly that of the gathered path; the summation order
  * differs, so results agree with it within the tolerance of the path, not bit for bit.
  * Errors: VXL_ERR_INVALID_ARG, VXL_ERR_UNSUPPORTED, VXL_ERR_WORKSPACE, VXL_ERR_HIP.

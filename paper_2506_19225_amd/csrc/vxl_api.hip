@@ -158,14 +158,14 @@ DecodePlan decode_plan(const vxl_attn_desc* d, int batch, int T, int l_cap, bool
         // row blocks sharing them have, and reads them once.  From 20 tiles per wave on, D = 64 28 and more than 64 rows
         // (blocks -> ring, us: 70 rows, 50,500 keys, 20 tiles 34.1 -> 32.0; 8 queries of 91 rows, 34,847 keys, 136 tiles 168.6
         // -> 104.7; D = 64, 8 of 70, 7,795 keys, 30 tiles 27.0 -> 22.7; but 91 rows, 38,299 keys, 15 tiles 28.1 against 29.1, 49
-        // rows, 19 tiles 36.7 and 37.1, D = 64, 8 of 35 rows, 42 tiles 38.6 and 40.6).  As many splits as give every
-        // compute unit a workgroup, if the scratch memory holds them.
+        // rows, 19 tiles 36.7 and 37.1, D = 64, 8 of 35 rows, 42 tiles 38.6 and 40.6).  In place, over 20 random calls of 20
+        // (28) to 32 tiles 1.08x to 2.0x; below, 8 to 19 tiles, 0.84x to 1.41x, and D = 64, 20 to 27, 0.93x to 1.37x.  As many splits
+        // as give every compute unit a workgroup, if the scratch memory holds them.
         if (!p.use_ring && fits && few && !single && rows > (d64 ? 64 : kRowBlock) && tpw >= (d64 ? 28 : 20)) {
             const long base_blocks = units * ((rows + 127) / 128);
             const int want = (int)std::max<long>(1, std::min<long>(p.n_split, 256 / base_blocks));
             if (partials(want) <= have) {
                 p.n_split = want;
-                p.split_len = (tiles + want - 1) / want * kKeyTile;
                 few = false;
             }
         }

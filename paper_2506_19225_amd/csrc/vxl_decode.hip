@@ -147,7 +147,7 @@ __global__ __launch_bounds__(64 * NW, 2) void decode_ring_kernel(
         for (int i = 0; i < C::IPW; ++i)
             m.e[i] = load_i32_hidden(src_s + row0 + min((wave + i * C::WAVES) * C::RPI + r_in, rlim));
     };
-    // Tile t -> stage t % NS.  Every wave issues GROUP loads: instruction slots wave, wave + 8, ...
+    // Tile t -> stage t % NS.  Every wave issues GROUP loads: instruction slots wave + i * WAVES, ...
     // Rows past the end of the split are clamped to its last row (scores masked, V finite).
     auto issue = [&](int t, const TileMap& m) __attribute__((always_inline)) {
         const int row0 = t * kKeyTile;

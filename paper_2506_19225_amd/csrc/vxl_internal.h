@@ -184,7 +184,7 @@ vxl_status launch_pool_sparse(const vxl_layout* L, const vxl_attn_desc* d, const
 // ---- decode ----
 struct DecodePlan {
     int n_split;        // key splits per (batch, kv head)
-    int split_len;      // keys per split (multiple of 64)
+    int split_len;      // step_waves != 0: keys per split (the ring deals them out by a query's length)
     int use_ring;       // step_waves == 0: the ring kernel, 0 = with 4 waves (128 rows), 1 = with 4 or 8
     int step_waves;     // step mode: waves per workgroup (8 single-buffered or 4 double-buffered); 0 = another kernel
     int one;            // step mode: one workgroup walks all keys of its rows, several tiles per wave
@@ -192,7 +192,7 @@ struct DecodePlan {
     size_t part_ml;
     size_t total;
 };
-// gathered = false plans the in-place form (always the 4-wave step kernel, splits bounded by its row-map area)
+// gathered = false plans the in-place form (the step kernel with 4 waves, its splits bounded by its row-map area, or the ring)
 // `have`: scratch bytes there are; a plan that the shorter call needs more for is given up for one that takes less.
 DecodePlan decode_plan(const vxl_attn_desc* d, int batch, int T, int l_cap, bool gathered = true, size_t have = SIZE_MAX);
 // fp32, either form: total == 0 with one split; a call without this much scratch memory takes one split

@@ -8,7 +8,7 @@ import torch
 import oracle
 from paper_2506_19225_amd import vxl, workloads as wl
 
-from gpu_util import DECODE_128, DECODE_RING, assert_close, decode_kernel, desc_of, gpu_decode
+from gpu_util import DECODE_128, DECODE_RING, assert_close, decode_kernel, desc_of, gpu_decode, make_layout
 from test_gpu_inplace import check_case
 
 pytestmark = pytest.mark.gpu
@@ -111,3 +111,57 @@ def test_long_walks_and_the_scratch_that_row_blocks_take(hq, hkv, t, d, bsz, l_c
                 assert_close(got, want, "bf16", head_axis=1, what=f"query {b}, {n} keys, {size} bytes")
                 wlse = torch.logsumexp(s, -1).reshape(t, g)
                 assert (lse[b, :, h * g:(h + 1) * g].double() - wlse).abs().max() < 2e-2
+
+
+@pytest.mark.parametrize("pooled", [False, True])
+def test_long_walks_in_place_and_the_scratch_that_row_blocks_take(pooled):
+    """The same in place, where the row map comes before the partial rows: 70 rows of eight queries, 21 tiles per wave of row
+    blocks in two splits, by the ring, by row blocks (the bytes that those need) and refused (one byte less)."""
+    hq, hkv, t, d, bsz, l_cap, blocks = 28, 4, 10, 128, 8, 5200, 2
+    w = wl.tiny_workload("bf16", hq, hkv, d, T=t, B=bsz, k=1, seed=89, value_scale=0.5)
+    rng, g, rows = np.random.default_rng(89), hq // hkv, hq // hkv * t
+    lens = [330] * 20
+    lay = wl.layout_from_lists(9, lens, [np.sort(rng.choice(330, 40, replace=False)).astype(np.int32) + 9 + 330 * c
+                                         for c in range(20)])
+    masks = np.zeros((bsz, 20), np.uint8)
+    for b, n in enumerate((15, 14, 15, 0, 1, 15, 20, 7)):     # (20 dense chunks do not fit)
+        masks[b, rng.choice(20, n, replace=False)] = 1
+    desc, gl = desc_of(w), make_layout(lay)
+    kernel, n_split = vxl.debug_decode_plan(desc, bsz, t, l_cap, True)
+    assert kernel == DECODE_128 and n_split > blocks
+    _, k, v = wl.make_qkv(w, lay, with_q=False)
+    dk, dv, qd = vxl.to_device(k, "bf16"), vxl.to_device(v, "bf16"), vxl.to_device(wl.make_decode_queries(w), "bf16")
+    dm, sp = torch.from_numpy(masks).cuda(), (None, None)
+    kmix = torch.zeros((bsz, hkv, l_cap, d), dtype=torch.bfloat16, device="cuda")
+    vmix, need = torch.zeros_like(kmix), torch.zeros(bsz, dtype=torch.int32, device="cuda")
+    if pooled:
+        sp = tuple(torch.empty((hkv, 800, d), dtype=torch.bfloat16, device="cuda") for _ in range(2))
+        vxl.pool_sparse_kv(gl, desc, dk, dv, *sp)
+        vxl.gather_bilevel_kv_pooled(gl, desc, dk, dv, *sp, dm, kmix, vmix, need)
+    else:
+        vxl.gather_bilevel_kv(gl, desc, dk, dv, dm, kmix, vmix, need)
+
+    def partials(n):
+        return sum((bsz * hkv * n * rows * x * 4 + 255) // 256 * 256 for x in (d, 1))
+
+    full = vxl.workspace_bytes(vxl.OP_DECODE_INPLACE, gl, desc, bsz, t, l_cap)
+    small = full - partials(n_split) + partials(blocks)
+    with pytest.raises(vxl.VxlError):
+        vxl.bilevel_decode_inplace(gl, desc, qd, dk, dv, *sp, dm, l_cap, torch.empty_like(qd), None, None,
+                                   torch.empty(small - 1, dtype=torch.uint8, device="cuda"))
+    for size in (full, small):
+        ws = torch.empty(size, dtype=torch.uint8, device="cuda")
+        for map_ready in (False, True):
+            out, lse = torch.full_like(qd, float("nan")), torch.full((bsz, t, hq), float("nan"), device="cuda")
+            vxl.bilevel_decode_inplace(gl, desc, qd, dk, dv, *sp, dm, l_cap, out, lse, None, ws, map_ready)
+            for b, n in enumerate(need.tolist()):
+                if n <= 0:
+                    assert not out[b].any() and torch.isneginf(lse[b]).all()
+                    continue
+                for h in range(hkv):
+                    s = qd[b, :, h * g:(h + 1) * g].reshape(-1, d).double() @ kmix[b, h, :n].double().T / d ** 0.5
+                    want = (torch.softmax(s, -1) @ vmix[b, h, :n].double()).reshape(t, g, d).cpu().numpy()
+                    got = vxl.to_host(out[b, :, h * g:(h + 1) * g].contiguous())
+                    assert_close(got, want, "bf16", head_axis=1, what=f"query {b}, {n} keys, {size} bytes")
+                    wlse = torch.logsumexp(s, -1).reshape(t, g)
+                    assert (lse[b, :, h * g:(h + 1) * g].double() - wlse).abs().max() < 2e-2
