@@ -40,7 +40,7 @@ __device__ __forceinline__ void store16(uint4* p, uint4 v) {
 // by one -> so, 25.6 -> 24.1 us with the selection).  How many threads, and whether past the caches: launch_summaries.
 // ------------------------------------------------------------------------------------------
 // qbar[b, g, :] = mean over the T query tokens and the query heads of KV head g of Qd[b, t, h, :].
-// A few tokens: one block per (b, g), a thread owns one 16-byte column piece of one head and adds its T tokens in
+// Up to kMeanLoads tokens: one block per (b, g), a thread owns one 16-byte column piece of one head and adds its T tokens in
 // token order; the heads of the group are then added in head order.  (Eight loads of a thread in flight here and below:
 // sixteen take 82 to 98 registers, which leave the chunks of the launch five or four waves per SIMD instead of eight, 256
 // chunks 18.5 -> 19.8 us; streamed past the caches four are as good as eight and steadier, 640 chunks 35.4 -> 34.6.)
@@ -59,20 +59,16 @@ __device__ __forceinline__ void query_mean_block(const T* __restrict__ Qd, float
         float acc[EPC];
 #pragma unroll
         for (int i = 0; i < EPC; ++i) acc[i] = 0.f;
-        for (int t0 = 0; t0 < T_q; t0 += kMeanLoads) {
-            uint4 v[kMeanLoads];
+        uint4 v[kMeanLoads];
 #pragma unroll
-            for (int u = 0; u < kMeanLoads; ++u) {
-                const int t = t0 + u < T_q ? t0 + u : T_q - 1;      // clamped rows are not added below
-                v[u] = ((const uint4*)qb)[(size_t)t * row_pieces + gp];
-            }
+        for (int u = 0; u < kMeanLoads; ++u)                   // (clamped rows are not added below)
+            v[u] = ((const uint4*)qb)[(size_t)min(u, T_q - 1) * row_pieces + gp];
 #pragma unroll
-            for (int u = 0; u < kMeanLoads; ++u) {
-                if (t0 + u < T_q) {
-                    const T* e = (const T*)&v[u];
+        for (int u = 0; u < kMeanLoads; ++u) {
+            if (u < T_q) {
+                const T* e = (const T*)&v[u];
 #pragma unroll
-                    for (int i = 0; i < EPC; ++i) acc[i] += ld(e + i);
-                }
+                for (int i = 0; i < EPC; ++i) acc[i] += ld(e + i);
             }
         }
 #pragma unroll
@@ -91,7 +87,8 @@ __device__ __forceinline__ void query_mean_block(const T* __restrict__ Qd, float
 // round trips: with all tokens of a piece in one thread, 128 tokens took eight, behind the chunks of the launch (28 heads on
 // four, D = 128, with the selection: 64 chunks of 256 tokens 17.3 -> 11.3 us, 256 chunks 28.2 -> 20.6, 640 40.1 -> 35.5;
 // 8 of 128 tokens 14.0 -> 8.3; 64 tokens 10.1 -> 8.0, 32 8.4 -> 7.6, 16 7.6 -> 7.5).
-constexpr int kMeanPieces = 4, kMeanTokens = 8;               // pieces of a block; tokens up to which one block takes a row
+constexpr int kMeanPieces = 4, kMeanTokens = kMeanLoads;      // pieces of a block; tokens up to which one block takes a row
+constexpr int kMeanThreads = 256;                             // threads of a block that own a piece and tokens of it
 
 template <typename T, int D, int THREADS>
 __device__ __forceinline__ void query_mean_part(const T* __restrict__ Qd, float* __restrict__ qbar, int b, int g, int first,
@@ -100,7 +97,7 @@ __device__ __forceinline__ void query_mean_part(const T* __restrict__ Qd, float*
     constexpr int PPR = D / EPC, COLS = kMeanPieces * EPC;
     const int group = n_q_heads / n_kv_heads, tid = threadIdx.x, n = group * kMeanPieces;
     // token groups, this thread's (as many from 512 threads as from 256: a query's mean does not depend on the layout)
-    const int tg_n = max(1, min(256 / n, (T_q + kMeanLoads - 1) / kMeanLoads)), tg = tid / n;
+    const int tg_n = max(1, min(kMeanThreads / n, (T_q + kMeanLoads - 1) / kMeanLoads)), tg = tid / n;
     const T* qb = Qd + (size_t)b * T_q * n_q_heads * D;
     const int row_pieces = n_q_heads * PPR;
     if (tg < tg_n) {
@@ -161,7 +158,7 @@ __global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(NT ? 4 
     // of them, and they are added in the same tree.
     constexpr int A = THREADS == 512 ? 2 : 4, CHAINS = A * RG, GROUPS = CHAINS / 4;
     constexpr int KEPT = THREADS == 512 ? CHAINS : GROUPS;      // (256 threads: a thread adds the four of its group)
-    extern __shared__ float dyn[];                  // for the query blocks: [group][D], or a piece per thread
+    extern __shared__ float dyn[];                  // for the query blocks: [group][D], or four pieces per head and group of tokens
     __shared__ float part[KEPT][D];
     if ((int)blockIdx.x < n_mean) {
         constexpr int PARTS = PPR / kMeanPieces;
@@ -766,7 +763,7 @@ vxl_status launch_summaries(const vxl_layout* L, const vxl_attn_desc* d, const v
     const int pieces = d->head_dim / (int)epc, n_mean = T > kMeanTokens ? batch * (pieces / kMeanPieces) : 0;
     const int group = d->n_q_heads / d->n_kv_heads;
     const dim3 grid(nc + (n_mean ? n_mean : batch), d->n_kv_heads);
-    const size_t smem = (size_t)(n_mean ? std::max(wide ? 512 : 256, group * kMeanPieces) * (int)epc : group * d->head_dim) * sizeof(float);
+    const size_t smem = (size_t)(n_mean ? std::max(kMeanThreads, group * kMeanPieces) * (int)epc : group * d->head_dim) * sizeof(float);
 #define VXL_LAUNCH_AS(T_, D, THREADS, NT)                                                                        \
     hipLaunchKernelGGL((chunk_summarize_kernel<T_, D, THREADS, NT>), grid, dim3(THREADS), smem, s, (const T_*)K,  \
                        L->d_bounds, kbar, ts.kh / epc, ts.kt / epc, nc, n_mean, (const T_*)Qd, qbar, T,     \
