@@ -69,7 +69,7 @@ DECODE_128, DECODE_RING, DECODE_BLOCKS = range(3)
 
 
 def decode_kernel(w, batch, t, l_cap, in_place=False):
-    """The kernel a bf16 decode of these sizes takes: 128 rows per workgroup, the 256-row ring, 32-row blocks (one row
+    """The kernel a bf16 decode of these sizes takes: the ring with 128 rows per workgroup, with 128 or 256, 32-row blocks (one row
     block: the step kernel)."""
     return vxl.debug_decode_plan(desc_of(w), batch, t, l_cap, in_place)[0]
 

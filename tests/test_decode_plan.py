@@ -1,5 +1,5 @@
 """The choice between the decode kernels, which is made on the host and needs no GPU: where 32-row blocks take the place
-of the 256-row ring, they are the shorter call by the times of a tile, a round of workgroups on the busiest XCD, and a
+of the ring kernel, they are the shorter call by the times of a tile, a round of workgroups on the busiest XCD, and a
 call."""
 import numpy as np
 import pytest
@@ -28,7 +28,7 @@ def test_row_blocks_are_the_shorter_call(d, in_place):
         for b in (1, 2, 3, 5, 9, 12):
             for t in (37, 64, 92, 128, 129, 160, 256, 512, 2000):
                 rows, units = g * t, hkv * b
-                if rows <= 256:                    # (fewer rows: the 128-row kernel may be the other choice)
+                if rows <= 256:                    # (fewer rows: the ring of 128 rows may be the other choice)
                     continue
                 for l_cap in (300, 1000, 1300, 1800, 4096, 16384, 45000):
                     kernel, n_split = plan(g * hkv, hkv, d, b, t, l_cap, in_place)

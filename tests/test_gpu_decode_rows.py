@@ -96,7 +96,7 @@ def test_merge_of_every_number_of_splits(l_cap, d):
     (64, 128, [3000, 1, 63, 64, 65, 0], 3000),        # 448 rows, the ring: fewer tiles than splits, none, a ragged last one
     (64, 64, [700, 2500, 129], 9000),                 # lengths far below the capacity
     (100, 64, [15500, 4000], 15500),                  # 700 rows on four KV heads: more planned splits than one round holds
-    (16, 128, [700, 650, 64] * 11, 800),              # 112 rows on 66 KV heads: the 128-row kernel
+    (16, 128, [700, 650, 64] * 11, 800),              # 112 rows on 66 KV heads: the ring with four waves
 ])
 def test_keys_dealt_out_by_length(t, d, lens, l_cap):
     rng = np.random.default_rng(t + l_cap)
@@ -126,7 +126,7 @@ def test_keys_dealt_out_by_length(t, d, lens, l_cap):
     (2, 2, 1, 128, [90, 0]),
     (14, 2, 40, 128, [300, 0, 64]),                # 280 rows
     (8, 1, 100, 128, [200, 0, 7, 64] * 16),        # 800 rows, one split: the ring
-    (14, 2, 16, 64, [100, 0] * 17),                # 112 rows, one split: the 128-row kernel
+    (14, 2, 16, 64, [100, 0] * 17),                # 112 rows, one split: the ring with four waves
 ])
 def test_calls_without_a_merge(hq, hkv, t, d, lens):
     """Mixed sets that one key split covers: the kernel writes O and LSE itself; O may be the buffer of the queries."""

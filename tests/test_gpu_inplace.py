@@ -70,7 +70,7 @@ def test_inplace_config0_fp32(mode):
     (36, 27, 64, DECODE_RING), (40, 13, 128, DECODE_RING)], ids=lambda x: str(x))
 def test_inplace_ragged_bf16(mode, t_q, bsz, d, kernel):
     """Stacked rows 7 and 28 (step kernel), 126, 280 and 210 (its form of several 32-row blocks), 35, 112 and 252
-    (128-row kernel, one and two row tiles), 252 and 280 (256-row ring, one and two); ragged chunks, some without kept
+    (the ring with 128 rows per workgroup, one and two row tiles), 252 and 280 (with 128 or 256); ragged chunks, some without kept
     rows, random selections including none and all."""
     rng = np.random.default_rng(1000 + 7 * t_q + d)
     w = wl.tiny_workload("bf16", 14, 2, d, T=t_q, B=bsz, k=2, seed=1000 + t_q, value_scale=0.5)

@@ -412,8 +412,8 @@ def test_decode_config0_fp32_and_tiny_bf16():
     want, wlse = oracle.decode_lse(qd, wk, wv, wlen)
     assert_close(got, want, "f32", head_axis=2, what="config0 decode")
     assert np.abs(lse - wlse).max() < 1e-4
-    # stacked rows 7 (step kernel), 35 and 252 (128-row kernel, one and two row tiles), 280 and 210 (32-row blocks), 280
-    # and 560 (256-row ring)
+    # stacked rows 7 (step kernel), 35 and 252 (the ring with 128 rows per workgroup, one and two row tiles), 280 and 210 (32-row
+    # blocks), 280 and 560 (the ring with 128 or 256)
     for t_q, bsz, d, kernel in ((1, 2, 128, DECODE_BLOCKS), (5, 3, 64, DECODE_128), (36, 20, 128, DECODE_128),
                                 (40, 1, 128, DECODE_BLOCKS), (30, 2, 64, DECODE_BLOCKS), (40, 20, 128, DECODE_RING),
                                 (80, 20, 64, DECODE_RING)):
@@ -643,7 +643,7 @@ def test_decode_step_mode_more_splits_than_the_merge_prefetches(d, lens):
     (72, 64, [1500, 90, 4096, 64, 1, 65], DECODE_RING)], ids=lambda x: str(x))
 def test_decode_never_uses_rows_past_the_mixed_length(t_q, d, lens, kernel):
     """Rows of the mixed buffers at and past mix_len[b] are NaN (what an uninitialised buffer may
-    hold): no kernel form (step, row blocks, 128-row, 256-row ring) may let them reach O or LSE, also where
+    hold): no kernel form (step, row blocks, the ring with 128 and 256 rows) may let them reach O or LSE, also where
     the length falls inside a tile, at a tile border and in a wave's first tile."""
     rng = np.random.default_rng(900 + t_q + d)
     hq, hkv, l_cap, bsz = 14, 2, 4096, len(lens)
